@@ -250,7 +250,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 1) void sdp_gemm_kernel(Dev 
         }
     }
 
-    // ---- depth steps; a partial last step (K % 64 in {16, 32, 48}) reads its missing chunks from a
+    // ---- depth steps; a partial last step (K % 64 != 0, K % 8 == 0) reads its missing chunks from a
     // zero buffer, so that every step issues the same loads and runs all four MFMA sub-steps ----
     const int nk_all = (g.K + BK - 1) / BK;
     const bool ranged = kSplit || (kTail && cut);
@@ -1108,8 +1108,10 @@ size_t gemm_tail_ws_bytes(int M, int N, int K, int nbatch) {
 bool gemm_mfma_supported(const GemmDesc& d) {
     if (d.M < 1 || d.N < 1 || d.K < 1) return false;
     if (d.force_tile != 0 && d.force_tile != 128 && d.force_tile != 192 && d.force_tile != 256) return false;
-    // 16-byte global chunks, 16-deep MFMA steps, 32-bit byte offsets inside each operand
-    if (d.K % 16 || d.lda % 8 || d.ldb % 8 || d.N % 8 || d.ldc % 8) return false;
+    // 16-byte global chunks (a depth that is no multiple of 64 ends in a step whose missing chunks are zeros: any
+    // multiple of 8 will do.  T = 5000, d = 1600, p = 2664, whose depths p and T are odd multiples of 8: a step of two
+    // workers takes 1.07 ms here, 12.0 ms with those depths on the plain kernel), 32-bit byte offsets inside each operand
+    if (d.K % 8 || d.lda % 8 || d.ldb % 8 || d.N % 8 || d.ldc % 8) return false;
     if (d.a_km) return false; // depth-major A goes through the transposing pre-pass or the plain kernel
     // the epilogue addresses a wave's part of the tile (at most 128 rows) with 32-bit byte offsets below 2^31
     constexpr int64_t kMaxLd = (int64_t)1 << 22;

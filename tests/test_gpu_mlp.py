@@ -90,6 +90,16 @@ SMALL = [
 ]
 
 
+# every contraction depth (d, p or F, T) an odd multiple of 8: partial last steps of 8, 24, 40 and 56
+ODD_DEPTHS = [MlpWorkload(f"tails{t}_bf16_{mode}", "bf16", 128 + t, 64 + t, 256 + t, 192 + t, 2, mode, 24)
+              for t in (8, 24, 40, 56) for mode in ("fm", "bm")]
+
+
+@pytest.mark.parametrize("w", ODD_DEPTHS, ids=[w.name for w in ODD_DEPTHS])
+def test_depths_that_are_odd_multiples_of_8(sdp, orc, w):
+    run_case(sdp, orc, w, [0, 1], dw_layout="scatter" if w.mode == "bm" else "compact")
+
+
 @pytest.mark.parametrize("w", SMALL, ids=[w.name for w in SMALL])
 def test_small_shapes_all_outputs(sdp, orc, w):
     run_case(sdp, orc, w, range(min(w.K, 2)))
