@@ -12,8 +12,10 @@
 //   backward  dO = dY . WoT[rows_o]^T (T x E);  core backward -> dQ, dK, dV (T x 3E);
 //             dWqkv[rows_qkv] = dQKV^T . X, dWoT[rows_o] = O^T . dY (depth T);  dX = dQKV . Wqkv[rows_qkv]
 // The contractions are the ones of the MLP path (same kernels, other shapes).  The core is written here:
-// causal attention on 32x32x16 bf16 MFMA tiles for hd = 64, with the running-maximum formulation of
-// the softmax (logits in base 2), so that no T x T matrix is stored.
+// causal attention on 32x32x16 bf16 MFMA tiles for heads of 64, 96 or 128 columns (wider and narrower ones take the next
+// of these widths), with the running-maximum formulation of the softmax (logits in base 2), so that no T x T matrix is
+// stored.  Heads of 65 .. 128 used to run the plain core: one sequence of 1500 tokens, 4 of 8 heads of 128, forward and
+// backward of the block 20.0 ms then, 0.26 ms on the wide MFMA core.
 //
 // Accumulator convention.  v_mfma_f32_32x32x16 computes D[m][n] += sum_k A[m][k] B[k][n]; lane L supplies
 // A[L % 32][8 (L / 32) + e] and B[8 (L / 32) + e][L % 32], e = 0..7, and holds D[8 q + 4 (L / 32) + r][L % 32]
@@ -54,14 +56,15 @@ typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
 #define SDP_ATTN_FWD_NW 4
 #endif
 
-constexpr int HD = 64;              // head width of the MFMA core
-constexpr int RSB = 144;            // bytes per LDS tile row: 64 bf16 + 16 bytes (bank spread), 16-byte aligned
-constexpr int TILE_BYTES = 64 * RSB; // one 64 x 64 tile
+constexpr int HD = 64;              // narrowest width of the MFMA core
+// Widths of the core: HW = 64, 96 or 128 columns per head.  An LDS tile row holds HW bf16 + 16 bytes: consecutive rows
+// then start 4 (an odd multiple of 4) banks apart, so the 16 lanes that a ds_read_b128 serves together hit every bank once.
+constexpr int row_bytes(int hw) { return hw * 2 + 16; }
 constexpr float kSlack = 8.f;      // forward: how far a query's maximum may run ahead of its reference exponent
 constexpr int BQ = 128;             // rows (queries, or keys in the dK/dV kernel) per workgroup: 4 waves x 32
 
 struct CoreArgs {
-    const uint16_t* qkv; // [T][ldq]: Q | K | V of the held heads, head i at columns i * 64 of each part
+    const uint16_t* qkv; // [T][ldq]: Q | K | V of the held heads, head i at columns i * hd of each part
     int64_t ldq;
     const uint16_t* o;   // [T][ldo] attention output (forward: written; backward: read)
     uint16_t* o_out;
@@ -71,7 +74,8 @@ struct CoreArgs {
     float* delta;        // [Bt][ph][S]: sum_h dO[t][h] O[t][h]
     uint16_t* dqkv;      // [T][ldq]
     int S, ph;
-    float scale, scale2; // 1 / sqrt(hd), and that times log2(e)
+    int hd;              // columns a head takes in qkv, o, dO, dqkv: HW, or a smaller multiple of 8 when HW > 64
+    float scale, scale2; // 1 / sqrt(head width), and that times log2(e)
 };
 
 __device__ inline uint32_t pack_bf16(float lo, float hi) {
@@ -95,15 +99,18 @@ __device__ inline bf16x8 pack_operand(const f32x16& a, int s) {
 }
 
 // operand whose depth runs along a tile row: row `row` of the tile, depth 16 s + 8 lhi .. + 7
+template <int HW>
 __device__ inline bf16x8 frag_rows(const unsigned char* tile, int row, int s, int lhi) {
-    return __builtin_bit_cast(bf16x8, *(const u32x4*)(tile + row * RSB + 32 * s + 16 * lhi));
+    return __builtin_bit_cast(bf16x8, *(const u32x4*)(tile + row * row_bytes(HW) + 32 * s + 16 * lhi));
 }
 
 // A operand whose depth runs down the tile rows: for lane L, column col0 + L % 32 and the rows
 // krow + 4 (L / 32) + e (e = 0..3), then krow + 8 + 4 (L / 32) + e.  Within each block of 16 lanes a
 // transposing read hands lane n the e-th 16-bit element (e = 0..3) of what lane 4 e + n / 4 addressed,
 // at position n % 4 of its 8 bytes: the 16 lanes address 4 rows x 4 groups of 4 columns.
+template <int HW>
 __device__ inline bf16x8 frag_cols(const unsigned char* tile, int krow, int col0, int lane) {
+    constexpr int RSB = row_bytes(HW);
     const int gi = lane >> 4, li = lane & 15;
     const unsigned char* p = tile + (krow + 4 * (gi >> 1) + (li >> 2)) * RSB + (col0 + 16 * (gi & 1) + 4 * (li & 3)) * 2;
     const s16x4 h0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)p);
@@ -112,48 +119,59 @@ __device__ inline bf16x8 frag_cols(const unsigned char* tile, int krow, int col0
     return __builtin_bit_cast(bf16x8, u32x4{a[0], a[1], b[0], b[1]});
 }
 
-// The 16-byte pieces of a 64-row x 64-column tile that thread `tid` of a workgroup of NW waves moves from
+// The 16-byte pieces of a ROWS-row x HW-column tile that thread `tid` of a workgroup of NW waves moves from
 // global memory to LDS through registers.  Rows are clamped to the last valid one (such rows only meet masked
-// logits).  `g` is uniform over the workgroup; the per-thread part of the address is a 32-bit byte offset
-// (the host checks that a sequence's rows span less than 4 GiB), which keeps the address arithmetic to a
-// minimum, one multiply and add per piece.
-template <int NW>
+// logits); columns from hd on (HW > 64 only) become zeros.  `g` is uniform over the workgroup and the tile's first
+// row moves it by 64-bit scalar arithmetic; the per-thread part of the address is a 32-bit byte offset inside the
+// tile, one multiply and add per piece.
+template <int NW, int HW, int ROWS = 64>
 struct TileMover {
-    static constexpr int PER = 512 / (64 * NW); // pieces per thread and tile
+    static constexpr int CPR = HW == HD ? 8 : 16;      // pieces per row (HW = 96: the last 4 of 16 move nothing)
+    static constexpr int PER = ROWS * CPR / (64 * NW); // pieces per thread and tile
+    static_assert(ROWS * CPR % (64 * NW) == 0 && 64 * NW % CPR == 0, "a thread's pieces share one column");
     u32x4 v[PER];
-    __device__ void fetch(const uint16_t* g, uint32_t ld, int row0, int last_row, int tid) {
+    __device__ void fetch(const uint16_t* g, uint32_t ld, int row0, int last_row, int hd, int tid) {
+        const int r0 = row0 < last_row ? row0 : last_row, rmax = last_row - r0;
+        const unsigned char* base = (const unsigned char*)(g + (int64_t)r0 * ld);
+        int col = tid % CPR;
+        if (HW > HD) col = col * 8 < hd ? col : 0;
 #pragma unroll
         for (int i = 0; i < PER; ++i) {
-            const int c = tid + 64 * NW * i;
-            int row = row0 + (c >> 3);
-            row = row < last_row ? row : last_row;
-            const uint32_t off = ((uint32_t)row * ld + (uint32_t)(c & 7) * 8u) * 2u;
-            v[i] = *(const u32x4*)((const unsigned char*)g + off);
+            int row = tid / CPR + 64 * NW / CPR * i;
+            row = row < rmax ? row : rmax;
+            v[i] = *(const u32x4*)(base + ((uint32_t)row * ld + (uint32_t)col * 8u) * 2u);
         }
     }
-    __device__ void stash(unsigned char* tile, int tid) const {
+    __device__ void stash(unsigned char* tile, int hd, int tid) const {
+        const int col = tid % CPR;
+        if (HW % 64 != 0 && col >= HW / 8) return;
+        const bool pad = HW > HD && col * 8 >= hd;
 #pragma unroll
-        for (int i = 0; i < PER; ++i) {
-            const int c = tid + 64 * NW * i;
-            *(u32x4*)(tile + (c >> 3) * RSB + (c & 7) * 16) = v[i];
-        }
+        for (int i = 0; i < PER; ++i)
+            *(u32x4*)(tile + (tid / CPR + 64 * NW / CPR * i) * row_bytes(HW) + col * 16) = pad ? u32x4{0u, 0u, 0u, 0u} : v[i];
     }
 };
-typedef TileMover<4> TilePieces;
 
-// a row of 64 bf16 as the depth-along-row operand of lane (row, lhi): sub-step s holds depth 16 s + 8 lhi .. + 7
-__device__ inline void load_row_operand(const uint16_t* g, int64_t ld, int row, int lhi, bf16x8 (&f)[4]) {
+// a row of HW bf16 as the depth-along-row operand of lane (row, lhi): sub-step s holds depth 16 s + 8 lhi .. + 7
+template <int HW>
+__device__ inline void load_row_operand(const uint16_t* g, int64_t ld, int row, int hd, int lhi, bf16x8 (&f)[HW / 16]) {
 #pragma unroll
-    for (int s = 0; s < 4; ++s) f[s] = __builtin_bit_cast(bf16x8, *(const u32x4*)(g + (int64_t)row * ld + 16 * s + 8 * lhi));
+    for (int s = 0; s < HW / 16; ++s) {
+        const int col = 16 * s + 8 * lhi;
+        const bool pad = HW > HD && col >= hd;
+        const u32x4 v = *(const u32x4*)(g + (int64_t)row * ld + (pad ? 0 : col));
+        f[s] = __builtin_bit_cast(bf16x8, pad ? u32x4{0u, 0u, 0u, 0u} : v);
+    }
 }
 
-// accumulator tiles D[h][row] (two 32-row blocks of h) -> out[row][32 j + 8 q + 4 lhi + r], scaled, 8-byte stores
-__device__ inline void store_rows(uint16_t* out_row, const f32x16 (&acc)[2], float f, int lhi) {
+// accumulator tiles D[h][row] (32-row blocks of h) -> out[row][32 j + 8 q + 4 lhi + r], scaled, 8-byte stores
+template <int HW>
+__device__ inline void store_rows(uint16_t* out_row, const f32x16 (&acc)[HW / 32], float f, int hd, int lhi) {
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < HW / 32; ++j)
 #pragma unroll
         for (int q = 0; q < 4; ++q)
-            *(u32x2*)(out_row + 32 * j + 8 * q + 4 * lhi) =
+            if (HW == HD || 32 * j + 8 * q < hd) *(u32x2*)(out_row + 32 * j + 8 * q + 4 * lhi) =
                 u32x2{pack_bf16(acc[j][4 * q] * f, acc[j][4 * q + 1] * f), pack_bf16(acc[j][4 * q + 2] * f, acc[j][4 * q + 3] * f)};
 }
 
@@ -169,56 +187,58 @@ __device__ inline float exp2_neg(float x) { return __builtin_amdgcn_exp2f(x); }
 // buffer and tile t + 2 is fetched from memory.  Every K and V fragment read from LDS serves all QF query
 // blocks of the wave.
 // ---------------------------------------------------------------------------------------------------
-template <int QF, int NW>
+template <int HW, int QF, int NW>
 __device__ inline void attn_fwd_block(const CoreArgs& a, const int q0, const int head, const int b,
-                                      unsigned char (&sK)[2][TILE_BYTES], unsigned char (&sV)[2][TILE_BYTES]) {
+                                      unsigned char (&sK)[2][64 * row_bytes(HW)], unsigned char (&sV)[2][64 * row_bytes(HW)]) {
+    constexpr int KS = HW / 16, JB = HW / 32; // depth steps of a logit, 32-column blocks of the output
+    const int hd = HW == HD ? HD : a.hd;
     constexpr int ROWS = 32 * QF * NW; // queries per block
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int S = a.S;
-    const uint16_t* gQ = a.qkv + (int64_t)b * S * a.ldq + head * HD;
-    const uint16_t* gK = gQ + a.ph * HD;
-    const uint16_t* gV = gK + a.ph * HD;
+    const uint16_t* gQ = a.qkv + (int64_t)b * S * a.ldq + head * hd;
+    const uint16_t* gK = gQ + a.ph * hd;
+    const uint16_t* gV = gK + a.ph * hd;
     const int qrow0 = q0 + 32 * QF * wave; // first query of the wave
-    bf16x8 qf[QF][4];
+    bf16x8 qf[QF][KS];
 #pragma unroll
     for (int f = 0; f < QF; ++f) {
         const int qrow = qrow0 + 32 * f + l32;
-        load_row_operand(gQ, a.ldq, qrow < S ? qrow : S - 1, lhi, qf[f]);
+        load_row_operand<HW>(gQ, a.ldq, qrow < S ? qrow : S - 1, hd, lhi, qf[f]);
     }
 
     const int kv_end = q0 + ROWS < S ? q0 + ROWS : S;
     const int ntiles = (kv_end + 63) / 64;
-    f32x16 acc_o[QF][2];
+    f32x16 acc_o[QF][JB];
     float m[QF], lsum[QF];
 #pragma unroll
     for (int f = 0; f < QF; ++f) {
         m[f] = -INFINITY, lsum[f] = 0.f;
 #pragma unroll
-        for (int j = 0; j < 2; ++j)
+        for (int j = 0; j < JB; ++j)
 #pragma unroll
             for (int e = 0; e < 16; ++e) acc_o[f][j][e] = 0.f;
     }
 
-    TileMover<NW> pk, pv;
+    TileMover<NW, HW> pk, pv;
     const uint32_t ld = (uint32_t)a.ldq;
-    pk.fetch(gK, ld, 0, S - 1, tid);
-    pv.fetch(gV, ld, 0, S - 1, tid);
-    pk.stash(sK[0], tid);
-    pv.stash(sV[0], tid);
+    pk.fetch(gK, ld, 0, S - 1, hd, tid);
+    pv.fetch(gV, ld, 0, S - 1, hd, tid);
+    pk.stash(sK[0], hd, tid);
+    pv.stash(sV[0], hd, tid);
     // fetches and stashes run unconditionally (rows are clamped, and a tile beyond the last one is never
     // read): no branch, hence no register copies, around the loop-carried pieces
-    pk.fetch(gK, ld, 64, S - 1, tid);
-    pv.fetch(gV, ld, 64, S - 1, tid);
+    pk.fetch(gK, ld, 64, S - 1, hd, tid);
+    pv.fetch(gV, ld, 64, S - 1, hd, tid);
     __syncthreads();
     for (int t = 0; t < ntiles; ++t) {
         const unsigned char* tK = sK[t & 1];
         const unsigned char* tV = sV[t & 1];
         // the other buffer was last read before the barrier that ended step t - 1
-        pk.stash(sK[(t + 1) & 1], tid);
-        pv.stash(sV[(t + 1) & 1], tid);
-        pk.fetch(gK, ld, 64 * (t + 2), S - 1, tid);
-        pv.fetch(gV, ld, 64 * (t + 2), S - 1, tid);
+        pk.stash(sK[(t + 1) & 1], hd, tid);
+        pv.stash(sV[(t + 1) & 1], hd, tid);
+        pk.fetch(gK, ld, 64 * (t + 2), S - 1, hd, tid);
+        pv.fetch(gV, ld, 64 * (t + 2), S - 1, hd, tid);
         const int kv0 = 64 * t;
         if (kv0 <= qrow0 + 32 * QF - 1) { // wave-uniform: otherwise every key lies after the wave's queries
             // logits, transposed: sc[f][tb] = D[key 32 tb + ..][query of block f]
@@ -232,8 +252,8 @@ __device__ inline void attn_fwd_block(const CoreArgs& a, const int q0, const int
 #pragma unroll
             for (int tb = 0; tb < 2; ++tb)
 #pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    const bf16x8 kfr = frag_rows(tK, 32 * tb + l32, s, lhi);
+                for (int s = 0; s < KS; ++s) {
+                    const bf16x8 kfr = frag_rows<HW>(tK, 32 * tb + l32, s, lhi);
 #pragma unroll
                     for (int f = 0; f < QF; ++f)
                         sc[f][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr, qf[f][s], sc[f][tb], 0, 0, 0);
@@ -272,7 +292,7 @@ __device__ inline void attn_fwd_block(const CoreArgs& a, const int q0, const int
                     m[f] = m_new;
                     lsum[f] *= alpha;
 #pragma unroll
-                    for (int j = 0; j < 2; ++j)
+                    for (int j = 0; j < JB; ++j)
 #pragma unroll
                         for (int e = 0; e < 16; ++e) acc_o[f][j][e] *= alpha;
                 }
@@ -300,8 +320,8 @@ __device__ inline void attn_fwd_block(const CoreArgs& a, const int q0, const int
 #pragma unroll
                 for (int s = 0; s < 2; ++s)
 #pragma unroll
-                    for (int j = 0; j < 2; ++j) {
-                        const bf16x8 vfr = frag_cols(tV, 32 * tb + 16 * s, 32 * j, lane);
+                    for (int j = 0; j < JB; ++j) {
+                        const bf16x8 vfr = frag_cols<HW>(tV, 32 * tb + 16 * s, 32 * j, lane);
 #pragma unroll
                         for (int f = 0; f < QF; ++f)
                             acc_o[f][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfr, pf[f][tb][s], acc_o[f][j], 0, 0, 0);
@@ -314,7 +334,7 @@ __device__ inline void attn_fwd_block(const CoreArgs& a, const int q0, const int
         const int qrow = qrow0 + 32 * f + l32;
         const float l = lsum[f] + other_half(lsum[f]);
         if (qrow < S) {
-            store_rows(a.o_out + ((int64_t)b * S + qrow) * a.ldo + head * HD, acc_o[f], 1.f / l, lhi);
+            store_rows<HW>(a.o_out + ((int64_t)b * S + qrow) * a.ldo + head * hd, acc_o[f], 1.f / l, hd, lhi);
             if (lhi == 0) a.lse[((int64_t)b * a.ph + head) * S + qrow] = m[f] + log2f(l);
         }
     }
@@ -337,14 +357,14 @@ __device__ inline void causal_item(int L, int nitems, int nbh, int nblocks, int 
     head = bh % ph, b = bh / ph;
 }
 
-template <int QF, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(SDP_ATTN_WPE_FWD, SDP_ATTN_WPE_FWD)))
+template <int HW, int QF, int NW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HW == HD ? SDP_ATTN_WPE_FWD : 2, HW == HD ? SDP_ATTN_WPE_FWD : 2)))
 void attn_fwd_kernel(CoreArgs a, int nblocks, int nbh) {
-    __shared__ __attribute__((aligned(16))) unsigned char sK[2][TILE_BYTES];
-    __shared__ __attribute__((aligned(16))) unsigned char sV[2][TILE_BYTES];
+    __shared__ __attribute__((aligned(16))) unsigned char sK[2][64 * row_bytes(HW)];
+    __shared__ __attribute__((aligned(16))) unsigned char sV[2][64 * row_bytes(HW)];
     int blk, head, b;
     causal_item(blockIdx.x, gridDim.x, nbh, nblocks, a.ph, blk, head, b);
-    attn_fwd_block<QF, NW>(a, blk * 32 * QF * NW, head, b, sK, sV);
+    attn_fwd_block<HW, QF, NW>(a, blk * 32 * QF * NW, head, b, sK, sV);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -352,26 +372,29 @@ void attn_fwd_kernel(CoreArgs a, int nblocks, int nbh) {
 // register operands; P is recomputed from the stored log-sum-exp.
 //   dP[q][k] = dO[q] . V[k];  dZ = P (dP - delta[q]);  dQ[q] = scale sum_k dZ[q][k] K[k]
 // ---------------------------------------------------------------------------------------------------
+template <int HW>
 __device__ inline void attn_bwd_dq_block(const CoreArgs& a, const int q0, const int head, const int b,
-                                         unsigned char (&sK)[TILE_BYTES], unsigned char (&sV)[TILE_BYTES]) {
+                                         unsigned char (&sK)[64 * row_bytes(HW)], unsigned char (&sV)[64 * row_bytes(HW)]) {
+    constexpr int KS = HW / 16, JB = HW / 32;
+    const int hd = HW == HD ? HD : a.hd;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int S = a.S;
-    const uint16_t* gQ = a.qkv + (int64_t)b * S * a.ldq + head * HD;
-    const uint16_t* gK = gQ + a.ph * HD;
-    const uint16_t* gV = gK + a.ph * HD;
+    const uint16_t* gQ = a.qkv + (int64_t)b * S * a.ldq + head * hd;
+    const uint16_t* gK = gQ + a.ph * hd;
+    const uint16_t* gV = gK + a.ph * hd;
     const int qrow0 = q0 + 32 * wave, qrow = qrow0 + l32;
     const int qc = qrow < S ? qrow : S - 1;
-    bf16x8 qf[4], dof[4];
-    load_row_operand(gQ, a.ldq, qc, lhi, qf);
-    const int64_t orow = ((int64_t)b * S + qc) * a.ldo + head * HD;
-    load_row_operand(a.dO + orow, 0, 0, lhi, dof);
+    bf16x8 qf[KS], dof[KS];
+    load_row_operand<HW>(gQ, a.ldq, qc, hd, lhi, qf);
+    const int64_t orow = ((int64_t)b * S + qc) * a.ldo + head * hd;
+    load_row_operand<HW>(a.dO + orow, 0, 0, hd, lhi, dof);
     float delta = 0.f;
     {
-        bf16x8 of[4];
-        load_row_operand(a.o + orow, 0, 0, lhi, of);
+        bf16x8 of[KS];
+        load_row_operand<HW>(a.o + orow, 0, 0, hd, lhi, of);
 #pragma unroll
-        for (int s = 0; s < 4; ++s)
+        for (int s = 0; s < KS; ++s)
 #pragma unroll
             for (int e = 0; e < 8; ++e) delta += (float)dof[s][e] * (float)of[s][e];
         delta += other_half(delta);
@@ -382,23 +405,23 @@ __device__ inline void attn_bwd_dq_block(const CoreArgs& a, const int q0, const 
 
     const int kv_end = q0 + BQ < S ? q0 + BQ : S;
     const int ntiles = (kv_end + 63) / 64;
-    f32x16 acc[2];
+    f32x16 acc[JB];
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < JB; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[j][e] = 0.f;
 
-    TilePieces pk, pv;
+    TileMover<4, HW> pk, pv;
     const uint32_t ld = (uint32_t)a.ldq;
-    pk.fetch(gK, ld, 0, S - 1, tid);
-    pv.fetch(gV, ld, 0, S - 1, tid);
+    pk.fetch(gK, ld, 0, S - 1, hd, tid);
+    pv.fetch(gV, ld, 0, S - 1, hd, tid);
     for (int t = 0; t < ntiles; ++t) {
         __syncthreads();
-        pk.stash(sK, tid);
-        pv.stash(sV, tid);
+        pk.stash(sK, hd, tid);
+        pv.stash(sV, hd, tid);
         __syncthreads();
-        pk.fetch(gK, ld, 64 * (t + 1), S - 1, tid); // unconditional: rows are clamped
-        pv.fetch(gV, ld, 64 * (t + 1), S - 1, tid);
+        pk.fetch(gK, ld, 64 * (t + 1), S - 1, hd, tid); // unconditional: rows are clamped
+        pv.fetch(gV, ld, 64 * (t + 1), S - 1, hd, tid);
         const int kv0 = 64 * t;
         if (kv0 > qrow0 + 31) continue;
         const bool edge = kv0 + 63 > qrow0 || kv0 + 64 > S;
@@ -408,9 +431,9 @@ __device__ inline void attn_bwd_dq_block(const CoreArgs& a, const int q0, const 
 #pragma unroll
             for (int e = 0; e < 16; ++e) sc[e] = 0.f, dp[e] = 0.f;
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows(sK, 32 * tb + l32, s, lhi), qf[s], sc, 0, 0, 0);
-                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows(sV, 32 * tb + l32, s, lhi), dof[s], dp, 0, 0, 0);
+            for (int s = 0; s < KS; ++s) {
+                sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<HW>(sK, 32 * tb + l32, s, lhi), qf[s], sc, 0, 0, 0);
+                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<HW>(sV, 32 * tb + l32, s, lhi), dof[s], dp, 0, 0, 0);
             }
             if (edge) {
 #pragma unroll
@@ -426,20 +449,22 @@ __device__ inline void attn_bwd_dq_block(const CoreArgs& a, const int q0, const 
             for (int s = 0; s < 2; ++s) {
                 const bf16x8 zf = pack_operand(sc, s);
 #pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols(sK, 32 * tb + 16 * s, 32 * j, lane), zf, acc[j], 0, 0, 0);
+                for (int j = 0; j < JB; ++j)
+                    acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols<HW>(sK, 32 * tb + 16 * s, 32 * j, lane), zf, acc[j], 0, 0, 0);
             }
         }
     }
-    if (qrow < S) store_rows(a.dqkv + ((int64_t)b * S + qrow) * a.ldq + head * HD, acc, a.scale, lhi);
+    if (qrow < S) store_rows<HW>(a.dqkv + ((int64_t)b * S + qrow) * a.ldq + head * hd, acc, a.scale, hd, lhi);
 }
 
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SDP_ATTN_WPE_DQ, SDP_ATTN_WPE_DQ))) void attn_bwd_dq_kernel(CoreArgs a, int nblocks, int nbh) {
-    __shared__ __attribute__((aligned(16))) unsigned char sK[TILE_BYTES];
-    __shared__ __attribute__((aligned(16))) unsigned char sV[TILE_BYTES];
+template <int HW>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HW == HD ? SDP_ATTN_WPE_DQ : 2, HW == HD ? SDP_ATTN_WPE_DQ : 2)))
+void attn_bwd_dq_kernel(CoreArgs a, int nblocks, int nbh) {
+    __shared__ __attribute__((aligned(16))) unsigned char sK[64 * row_bytes(HW)];
+    __shared__ __attribute__((aligned(16))) unsigned char sV[64 * row_bytes(HW)];
     int blk, head, b;
     causal_item(blockIdx.x, gridDim.x, nbh, nblocks, a.ph, blk, head, b);
-    attn_bwd_dq_block(a, blk * BQ, head, b, sK, sV);
+    attn_bwd_dq_block<HW>(a, blk * BQ, head, b, sK, sV);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -448,63 +473,88 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(SDP_ATTN_WP
 // sequence; Q, dO and the per-query statistics of a tile of 64 queries are staged in LDS.
 //   dV[k] = sum_q P[q][k] dO[q];   dK[k] = scale sum_q dZ[q][k] Q[q]
 // ---------------------------------------------------------------------------------------------------
+// At HW = 128 a wave's accumulators (128 registers), K rows (32), one 32 x 32 block of logits and of logit gradients
+// (32) leave no room for its V rows (32) and the pieces of 64 staged queries (32) under the 256 registers of two waves
+// per SIMD: the workgroup's V rows then stay in LDS and are read from there per block, and a tile has 32 queries.  At
+// HW = 96 the shorter tile is enough.
+template <int HW>
+struct DkvShape {
+    static constexpr bool kVInLds = HW == 128;
+    static constexpr int QT = HW == HD ? 64 : 32; // queries per tile
+    static constexpr int V_BYTES = kVInLds ? BQ * row_bytes(HW) : 16;
+};
+
+template <int HW>
 __device__ inline void attn_bwd_dkv_block(const CoreArgs& a, const int k0, const int head, const int b,
-                                          unsigned char (&sQ)[TILE_BYTES], unsigned char (&sO)[TILE_BYTES], float (&sL)[64],
-                                          float (&sD)[64]) {
+                                          unsigned char (&sQ)[DkvShape<HW>::QT * row_bytes(HW)],
+                                          unsigned char (&sO)[DkvShape<HW>::QT * row_bytes(HW)], float (&sL)[DkvShape<HW>::QT],
+                                          float (&sD)[DkvShape<HW>::QT], unsigned char (&sV)[DkvShape<HW>::V_BYTES]) {
+    constexpr int KS = HW / 16, JB = HW / 32, QT = DkvShape<HW>::QT;
+    constexpr bool kVInLds = DkvShape<HW>::kVInLds;
+    const int hd = HW == HD ? HD : a.hd;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int S = a.S;
-    const uint16_t* gQ = a.qkv + (int64_t)b * S * a.ldq + head * HD;
-    const uint16_t* gK = gQ + a.ph * HD;
-    const uint16_t* gV = gK + a.ph * HD;
-    const uint16_t* gO = a.dO + (int64_t)b * S * a.ldo + head * HD;
+    const uint16_t* gQ = a.qkv + (int64_t)b * S * a.ldq + head * hd;
+    const uint16_t* gK = gQ + a.ph * hd;
+    const uint16_t* gV = gK + a.ph * hd;
+    const uint16_t* gO = a.dO + (int64_t)b * S * a.ldo + head * hd;
     const int64_t stat = ((int64_t)b * a.ph + head) * S;
     const int krow0 = k0 + 32 * wave, krow = krow0 + l32;
     const int kc = krow < S ? krow : S - 1;
-    bf16x8 kf[4], vf[4];
-    load_row_operand(gK, a.ldq, kc, lhi, kf);
-    load_row_operand(gV, a.ldq, kc, lhi, vf);
+    bf16x8 kf[KS], vf[kVInLds ? 1 : KS];
+    load_row_operand<HW>(gK, a.ldq, kc, hd, lhi, kf);
+    if constexpr (kVInLds) {
+        TileMover<4, HW, BQ> mv;
+        mv.fetch(gV, (uint32_t)a.ldq, k0, S - 1, hd, tid);
+        mv.stash(sV, hd, tid); // read after the barriers of the first tile
+    } else {
+        load_row_operand<HW>(gV, a.ldq, kc, hd, lhi, vf);
+    }
 
-    f32x16 acc_k[2], acc_v[2];
+    f32x16 acc_k[JB], acc_v[JB];
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < JB; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc_k[j][e] = 0.f, acc_v[j][e] = 0.f;
 
-    const int t0 = k0 / 64, t1 = (S + 63) / 64; // query tiles [t0, t1); t0 < t1 because k0 < S
-    TilePieces pq, po;
+    const int t0 = k0 / QT, t1 = (S + QT - 1) / QT; // query tiles [t0, t1); t0 < t1 because k0 < S
+    TileMover<4, HW, QT> pq, po;
     const uint32_t ldq32 = (uint32_t)a.ldq, ldo32 = (uint32_t)a.ldo;
-    // per-query statistics of a tile: threads 0..63 carry the log-sum-exp, 64..127 delta
-    const float* gstat = (tid < 64 ? a.lse : a.delta) + stat;
-    const int sq = tid & 63;
+    // per-query statistics of a tile: threads 0 .. QT - 1 carry the log-sum-exp, QT .. 2 QT - 1 delta
+    const float* gstat = (tid < QT ? a.lse : a.delta) + stat;
+    const int sq = tid % QT;
     float pstat;
-    pq.fetch(gQ, ldq32, 64 * t0, S - 1, tid);
-    po.fetch(gO, ldo32, 64 * t0, S - 1, tid);
-    pstat = gstat[64 * t0 + sq < S ? 64 * t0 + sq : S - 1];
+    pq.fetch(gQ, ldq32, QT * t0, S - 1, hd, tid);
+    po.fetch(gO, ldo32, QT * t0, S - 1, hd, tid);
+    pstat = gstat[QT * t0 + sq < S ? QT * t0 + sq : S - 1];
     for (int t = t0; t < t1; ++t) {
         __syncthreads();
-        pq.stash(sQ, tid);
-        po.stash(sO, tid);
-        if (tid < 64) sL[tid] = pstat;
-        else if (tid < 128) sD[tid - 64] = pstat;
+        pq.stash(sQ, hd, tid);
+        po.stash(sO, hd, tid);
+        if (tid < QT) sL[tid] = pstat;
+        else if (tid < 2 * QT) sD[tid - QT] = pstat;
         __syncthreads();
         // the next tile, unconditionally: rows are clamped
-        pq.fetch(gQ, ldq32, 64 * (t + 1), S - 1, tid);
-        po.fetch(gO, ldo32, 64 * (t + 1), S - 1, tid);
-        pstat = gstat[64 * (t + 1) + sq < S ? 64 * (t + 1) + sq : S - 1];
-        const int qt0 = 64 * t;
-        if (qt0 + 63 < krow0) continue; // wave-uniform: every query of the tile lies before the wave's keys
-        const bool edge = qt0 < krow0 + 31 || qt0 + 64 > S;
+        pq.fetch(gQ, ldq32, QT * (t + 1), S - 1, hd, tid);
+        po.fetch(gO, ldo32, QT * (t + 1), S - 1, hd, tid);
+        pstat = gstat[QT * (t + 1) + sq < S ? QT * (t + 1) + sq : S - 1];
+        const int qt0 = QT * t;
+        if (qt0 + QT - 1 < krow0) continue; // wave-uniform: every query of the tile lies before the wave's keys
+        const bool edge = qt0 < krow0 + 31 || qt0 + QT > S;
 #pragma unroll
-        for (int tb = 0; tb < 2; ++tb) {
+        for (int tb = 0; tb < QT / 32; ++tb) {
             // sc = D[query 32 tb + ..][key], dp likewise
             f32x16 sc, dp;
 #pragma unroll
             for (int e = 0; e < 16; ++e) sc[e] = 0.f, dp[e] = 0.f;
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows(sQ, 32 * tb + l32, s, lhi), kf[s], sc, 0, 0, 0);
-                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows(sO, 32 * tb + l32, s, lhi), vf[s], dp, 0, 0, 0);
+            for (int s = 0; s < KS; ++s) {
+                sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<HW>(sQ, 32 * tb + l32, s, lhi), kf[s], sc, 0, 0, 0);
+                bf16x8 v;
+                if constexpr (kVInLds) v = frag_rows<HW>(sV, 32 * wave + l32, s, lhi);
+                else v = vf[s];
+                dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<HW>(sO, 32 * tb + l32, s, lhi), v, dp, 0, 0, 0);
             }
             if (edge) { // a branch of its own: only the tiles on the diagonal and the ragged last one pay for it
 #pragma unroll
@@ -530,29 +580,31 @@ __device__ inline void attn_bwd_dkv_block(const CoreArgs& a, const int k0, const
             for (int s = 0; s < 2; ++s) {
                 const bf16x8 pf = pack_operand(sc, s), zf = pack_operand(dp, s);
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    acc_v[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols(sO, 32 * tb + 16 * s, 32 * j, lane), pf, acc_v[j], 0, 0, 0);
-                    acc_k[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols(sQ, 32 * tb + 16 * s, 32 * j, lane), zf, acc_k[j], 0, 0, 0);
+                for (int j = 0; j < JB; ++j) {
+                    acc_v[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols<HW>(sO, 32 * tb + 16 * s, 32 * j, lane), pf, acc_v[j], 0, 0, 0);
+                    acc_k[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols<HW>(sQ, 32 * tb + 16 * s, 32 * j, lane), zf, acc_k[j], 0, 0, 0);
                 }
             }
         }
     }
     if (krow < S) {
-        uint16_t* row = a.dqkv + ((int64_t)b * S + krow) * a.ldq + head * HD;
-        store_rows(row + a.ph * HD, acc_k, a.scale, lhi);
-        store_rows(row + 2 * a.ph * HD, acc_v, 1.f, lhi);
+        uint16_t* row = a.dqkv + ((int64_t)b * S + krow) * a.ldq + head * hd;
+        store_rows<HW>(row + a.ph * hd, acc_k, a.scale, hd, lhi);
+        store_rows<HW>(row + 2 * a.ph * hd, acc_v, 1.f, hd, lhi);
     }
 }
 
+template <int HW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dkv_kernel(CoreArgs a, int nblocks, int nbh) {
-    __shared__ __attribute__((aligned(16))) unsigned char sQ[TILE_BYTES];
-    __shared__ __attribute__((aligned(16))) unsigned char sO[TILE_BYTES];
-    __shared__ __attribute__((aligned(16))) float sL[64];
-    __shared__ __attribute__((aligned(16))) float sD[64];
+    __shared__ __attribute__((aligned(16))) unsigned char sQ[DkvShape<HW>::QT * row_bytes(HW)];
+    __shared__ __attribute__((aligned(16))) unsigned char sO[DkvShape<HW>::QT * row_bytes(HW)];
+    __shared__ __attribute__((aligned(16))) float sL[DkvShape<HW>::QT];
+    __shared__ __attribute__((aligned(16))) float sD[DkvShape<HW>::QT];
+    __shared__ __attribute__((aligned(16))) unsigned char sV[DkvShape<HW>::V_BYTES];
     int blk, head, b;
     causal_item(blockIdx.x, gridDim.x, nbh, nblocks, a.ph, blk, head, b);
     // key block i meets the query blocks i .. n - 1: the first key blocks are the long ones
-    attn_bwd_dkv_block(a, (nblocks - 1 - blk) * BQ, head, b, sQ, sO, sL, sD);
+    attn_bwd_dkv_block<HW>(a, (nblocks - 1 - blk) * BQ, head, b, sQ, sO, sL, sD, sV);
 }
 
 // rows of [Wq; Wk; Wv] ([3 H hd][d]) and of WoT ([H hd][d]) that belong to the held heads
@@ -567,15 +619,19 @@ __global__ void head_rows_kernel(const int32_t* __restrict__ head_idx, int ph, i
     if (part == 0) rows_o[rem] = row;
 }
 
-int64_t ld_tokens(int64_t T) { return T + 64; } // see the MLP path: rows must not sit a power of two apart
+// Token-contiguous copies: T tokens, zeros up to the next multiple of 8 (so that a depth of ragged T is whole 16-byte
+// chunks), and 64 more (see the MLP path: rows must not sit a power of two apart).
+int64_t depth_tokens(int64_t T) { return (T + 7) / 8 * 8; }
+int64_t ld_tokens(int64_t T) { return depth_tokens(T) + 64; }
 
-// Head width the core runs on.  The MFMA core takes bf16 heads of width 64; narrower bf16 heads (the paper's
-// 500M / 1B models have width 50) are padded to 64 with zero features: a zero feature of Q and K adds nothing to a
+// Columns a head takes in the saved tensors.  Bf16 heads narrower than 64 (the paper's 500M / 1B models have width
+// 50) are padded to 64 with zero features: a zero feature of Q and K adds nothing to a
 // logit, a zero feature of V gives a zero feature of O, and every gradient of a zero feature is zero.  The padding
 // is made once, on the weights (pad_heads_kernel): the saved Q | K | V and O then carry 64 columns per head, of
-// which the last 64 - hd are zero.  Everything else (fp32, wider heads) goes through the plain core unpadded.
+// which the last 64 - hd are zero.  Wider bf16 heads are saved as they are and run the MFMA core of the next width
+// (64, 96, 128), which sets the missing columns to zero as it stages them; fp32 heads go through the plain core.
 int core_width(int dtype, int hd) { return dtype == SDP_BF16 && hd <= HD ? HD : hd; }
-bool mfma_core(int dtype, int hd) { return core_width(dtype, hd) == HD && dtype == SDP_BF16; }
+bool mfma_core(int dtype) { return dtype == SDP_BF16; }
 size_t esize(int dtype) { return dtype == SDP_F32 ? 4 : 2; }
 
 // out[(i hw + r)][:] = r < hd ? in[(heads ? heads[i] : i) hd + r][:] : 0 for i < n, r < hw, per stacked matrix
@@ -620,8 +676,8 @@ int check(int mode, int dtype, int Bt, int S, int d, int H, int hd, int ph) {
     if (Bt > 65535 || H > 65535) return SDP_ERR_SHAPE;
     const int hw = core_width(dtype, hd);
     if ((int64_t)Bt * S >= ((int64_t)1 << 31) || (int64_t)Bt * S * 3 * H * hw >= ((int64_t)1 << 40)) return SDP_ERR_SHAPE;
-    // MFMA core: 32-bit byte offsets inside a sequence
-    if (mfma_core(dtype, hd) && (int64_t)S * 3 * H * hw * 2 >= ((int64_t)1 << 32)) return SDP_ERR_SHAPE;
+    // padded heads: a sequence's rows span less than 4 GiB
+    if (mfma_core(dtype) && hd <= HD && (int64_t)S * 3 * H * hw * 2 >= ((int64_t)1 << 32)) return SDP_ERR_SHAPE;
     return SDP_OK;
 }
 
@@ -667,7 +723,7 @@ BwdWs bwd_ws(char* w, size_t e, int64_t T, int d, int E, int Eh, int64_t stats, 
     r.Xt = take((size_t)d * ld_tokens(T) * e);
     r.dYt = take((size_t)d * ld_tokens(T) * e);
     r.Wc = take((size_t)d * 3 * E * e);
-    const size_t sp = e == 2 ? gemm_split_ws_bytes(Eh, d, (int)T, 4) : 0; // partial sums of the batched weight-gradient launch
+    const size_t sp = e == 2 ? gemm_split_ws_bytes(Eh, d, (int)depth_tokens(T), 4) : 0; // partial sums of the batched weight-gradient launch
     r.split = sp ? take(sp) : nullptr;
     r.Wp = padded ? take((size_t)3 * E * d * e) : nullptr;
     r.WoP = padded ? take((size_t)E * d * e) : nullptr;
@@ -768,18 +824,21 @@ int sdp::attn_fwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     rc = run(dtype, pj, s);
     if (rc != SDP_OK) return rc;
 
-    if (mfma_core(dtype, hd)) {
+    if (mfma_core(dtype)) {
         CoreArgs a{};
         a.qkv = (const uint16_t*)QKV_save, a.ldq = 3 * E;
         a.o_out = (uint16_t*)O_save, a.ldo = E;
         a.lse = LSE_save;
-        a.S = S, a.ph = ph;
+        a.S = S, a.ph = ph, a.hd = hw;
         a.scale = 1.f / sqrtf((float)hd), a.scale2 = a.scale * 1.44269504088896340736f;
         ProfileScope ps("attn_core_fwd", s);
         constexpr int QF = SDP_ATTN_FWD_QF, NW = SDP_ATTN_FWD_NW, ROWS = 32 * QF * NW;
         const int nblocks = (S + ROWS - 1) / ROWS;
         if ((int64_t)nblocks * ph * Bt > INT32_MAX) return SDP_ERR_UNSUPPORTED;
-        attn_fwd_kernel<QF, NW><<<dim3(nblocks * ph * Bt), 64 * NW, 0, s>>>(a, nblocks, ph * Bt);
+        const dim3 grid(nblocks * ph * Bt);
+        if (hw <= 64) attn_fwd_kernel<64, QF, NW><<<grid, 64 * NW, 0, s>>>(a, nblocks, ph * Bt);
+        else if (hw <= 96) attn_fwd_kernel<96, QF, NW><<<grid, 64 * NW, 0, s>>>(a, nblocks, ph * Bt);
+        else attn_fwd_kernel<128, QF, NW><<<grid, 64 * NW, 0, s>>>(a, nblocks, ph * Bt);
         rc = launch_status();
     } else {
         AttnCoreDesc c;
@@ -863,26 +922,30 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     rc = run(dtype, go, s);
     if (rc != SDP_OK) return rc;
 
-    if (mfma_core(dtype, hd)) {
+    if (mfma_core(dtype)) {
         CoreArgs a{};
         a.qkv = (const uint16_t*)QKV_save, a.ldq = 3 * E;
         a.o = (const uint16_t*)O_save, a.dO = (const uint16_t*)w.dO, a.ldo = E;
         a.lse = const_cast<float*>(LSE_save), a.delta = w.delta;
         a.dqkv = (uint16_t*)w.dQKV;
-        a.S = S, a.ph = hr;
+        a.S = S, a.ph = hr, a.hd = hw;
         a.scale = 1.f / sqrtf((float)hd), a.scale2 = a.scale * 1.44269504088896340736f;
         const int nblocks = (S + BQ - 1) / BQ;
         if ((int64_t)nblocks * hr * Bt > INT32_MAX) return SDP_ERR_UNSUPPORTED;
         const dim3 grid(nblocks * hr * Bt);
         {
             ProfileScope ps("attn_core_bwd_dq", s);
-            attn_bwd_dq_kernel<<<grid, 256, 0, s>>>(a, nblocks, hr * Bt);
+            if (hw <= 64) attn_bwd_dq_kernel<64><<<grid, 256, 0, s>>>(a, nblocks, hr * Bt);
+            else if (hw <= 96) attn_bwd_dq_kernel<96><<<grid, 256, 0, s>>>(a, nblocks, hr * Bt);
+            else attn_bwd_dq_kernel<128><<<grid, 256, 0, s>>>(a, nblocks, hr * Bt);
             rc = launch_status();
             if (rc != SDP_OK) return rc;
         }
         {
             ProfileScope ps("attn_core_bwd_dkv", s); // reads the delta written by the dQ kernel
-            attn_bwd_dkv_kernel<<<grid, 256, 0, s>>>(a, nblocks, hr * Bt);
+            if (hw <= 64) attn_bwd_dkv_kernel<64><<<grid, 256, 0, s>>>(a, nblocks, hr * Bt);
+            else if (hw <= 96) attn_bwd_dkv_kernel<96><<<grid, 256, 0, s>>>(a, nblocks, hr * Bt);
+            else attn_bwd_dkv_kernel<128><<<grid, 256, 0, s>>>(a, nblocks, hr * Bt);
             rc = launch_status();
             if (rc != SDP_OK) return rc;
         }
@@ -922,7 +985,7 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     // the held heads' rows only (row gather on the left operand): the gradient is computed on the mask.
     GemmDesc dw;
     dw.name = "attn_dw";
-    dw.M = Eh, dw.N = d, dw.K = T;
+    dw.M = Eh, dw.N = d, dw.K = dtype == SDP_BF16 ? (int)depth_tokens(T) : T; // zeros from T on (transpose_rows_vec_kernel)
     dw.lda = ldt, dw.ldb = ldt;
     if (!gathered && !all_heads) dw.a_gather = w.rows_o, dw.a_rows = E;
     dw.epilogue = EPI_STORE;

@@ -1,14 +1,11 @@
-// Plain causal attention core (forward, dQ, dK/dV) for the head-masked attention block: fp32 or bf16 storage,
-// fp32 arithmetic throughout, any head width up to 128, no matrix instructions and no rounding of intermediate
-// results.  It serves the fp32 path (parity to 1e-5) and the bf16 shapes the MFMA core does not take (head
-// widths other than 64).  Same interface and the same saved statistics as the MFMA core: base-2 log-sum-exp of
+// Plain causal attention core (forward, dQ, dK/dV) for the head-masked attention block: fp32 storage and arithmetic
+// throughout, any head width up to 128, no matrix instructions.  It serves the fp32 path (parity to 1e-5).  Same interface and the same saved statistics as the MFMA core: base-2 log-sum-exp of
 // the scaled logits, delta = sum_h dO[t][h] O[t][h].
 //
 // One wave per (token, head, sequence).  The 64 lanes share out the other axis (keys for a query, queries for a
 // key); every lane keeps a partial of the hd-wide result row, and the wave sums the partials with shuffles.
 // Logits are recomputed in each sweep instead of being stored: nothing of size S x S exists.
 #include "sdp_internal.h"
-#include "sdp_swiglu.h"
 
 #include <cmath>
 
@@ -21,14 +18,10 @@ template <typename T>
 __device__ inline float ldv(const T* p);
 template <>
 __device__ inline float ldv<float>(const float* p) { return *p; }
-template <>
-__device__ inline float ldv<uint16_t>(const uint16_t* p) { return bf16_to_f32(*p); }
 template <typename T>
 __device__ inline void stv(T* p, float v);
 template <>
 __device__ inline void stv<float>(float* p, float v) { *p = v; }
-template <>
-__device__ inline void stv<uint16_t>(uint16_t* p, float v) { *p = f32_to_bf16(v); }
 
 __device__ inline float wave_sum(float v) {
 #pragma unroll
@@ -209,11 +202,11 @@ bool attn_plain_supported(const AttnCoreDesc& c) { return c.hd >= 1 && c.hd <= M
 
 int attn_plain_fwd(int dtype, const AttnCoreDesc& c, hipStream_t s) {
     if (!attn_plain_supported(c)) return SDP_ERR_UNSUPPORTED;
-    return dtype == SDP_F32 ? fwd_t<float>(c, s) : fwd_t<uint16_t>(c, s);
+    return dtype == SDP_F32 ? fwd_t<float>(c, s) : SDP_ERR_UNSUPPORTED;
 }
 int attn_plain_bwd(int dtype, const AttnCoreDesc& c, hipStream_t s) {
     if (!attn_plain_supported(c)) return SDP_ERR_UNSUPPORTED;
-    return dtype == SDP_F32 ? bwd_t<float>(c, s) : bwd_t<uint16_t>(c, s);
+    return dtype == SDP_F32 ? bwd_t<float>(c, s) : SDP_ERR_UNSUPPORTED;
 }
 
 } // namespace sdp

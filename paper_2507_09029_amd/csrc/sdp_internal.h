@@ -146,7 +146,7 @@ struct AttnCoreDesc {
     void* dqkv = nullptr;
     int Bt = 0, S = 0, n = 0, hd = 0;
 };
-// plain core: fp32 or bf16 storage, fp32 arithmetic, hd <= 128 (SDP_ERR_UNSUPPORTED beyond)
+// plain core: fp32, hd <= 128 (SDP_ERR_UNSUPPORTED beyond)
 bool attn_plain_supported(const AttnCoreDesc& c);
 int attn_plain_fwd(int dtype, const AttnCoreDesc& c, hipStream_t s);
 int attn_plain_bwd(int dtype, const AttnCoreDesc& c, hipStream_t s);

@@ -14,7 +14,8 @@ namespace sdp {
 namespace {
 
 // 16-bit elements, 16-byte accesses on both sides.  Tile: 64 input rows x 64 columns.
-// Requires C % 8 == 0, R % 8 == 0, ld_in % 8 == 0, ld_out % 8 == 0 and 16-byte aligned bases.
+// Requires C % 8 == 0, ld_in % 8 == 0, ld_out % 8 == 0, ld_out >= R and 16-byte aligned bases.  Output rows are written
+// in whole 16-byte pieces: when R is no multiple of 8, elements R .. round_up(R, 8) - 1 of an output row become zeros.
 // Up to kMaxJobs independent transposes run as one launch (grid.z = job); workgroups beyond a job's
 // own extent leave at once.
 struct Jobs {
@@ -92,7 +93,7 @@ __global__ __launch_bounds__(256) void transpose_rows_kernel(const T* __restrict
 } // namespace
 
 static bool vec_ok(const TransposeJob& t) {
-    return t.C % 8 == 0 && t.R % 8 == 0 && t.ld_in % 8 == 0 && t.ld_out % 8 == 0 && aligned16(t.in) && aligned16(t.out);
+    return t.C % 8 == 0 && t.ld_out >= t.R && t.ld_in % 8 == 0 && t.ld_out % 8 == 0 && aligned16(t.in) && aligned16(t.out);
 }
 
 int transpose_rows(int elem_bytes, const void* in, int64_t ld_in, const int32_t* rows, int R, int C, void* out,

@@ -158,6 +158,18 @@ def test_padded_heads_backward_masking(sdp, orc):
 BM_CASES = [CASES[0], CASES[2], CASES[3], CASES[4], CASES[5], CASES[6], CASES[7], CASES[8], CASES[10]]
 
 
+# heads wider than 64 on the MFMA core: widths that fill it and that leave zero columns, sequences around the edges of
+# its 32- and 64-row tiles and 128-row blocks; token counts that are no multiple of 8 (weight gradients over padded depth)
+WIDE = [AttnWorkload(f"wide{hd}_S{S}", Bt, S, 72, 3, hd, 2, 2, 47) for hd, Bt, S in
+        ((72, 1, 129), (80, 3, 31), (88, 1, 193), (96, 2, 64), (104, 1, 127), (112, 5, 1), (120, 2, 33), (128, 1, 65), (128, 3, 150))]
+
+
+@pytest.mark.parametrize("mode", ["fm", "bm"])
+@pytest.mark.parametrize("w", WIDE, ids=[w.name for w in WIDE])
+def test_attention_wide_heads(sdp, orc, w, mode):
+    run_case(sdp, orc, w, [0], dw_layout="scatter" if w.hd % 16 else "compact", mode=mode)
+
+
 @pytest.mark.parametrize("w", BM_CASES, ids=[w.name for w in BM_CASES])
 def test_attention_backward_masking_all_outputs(sdp, orc, w):
     """Dense forward and dX, weight gradients on the held heads only."""
