@@ -742,8 +742,8 @@ int pad_heads(const void* in, int nmat, const int32_t* heads, int n, int H, int 
 }
 
 int run(int dtype, const GemmDesc& g, hipStream_t s) {
-    if (dtype == SDP_BF16 && gemm_mfma_supported(g)) return gemm_mfma_bf16(g, s);
-    return gemm_simple(dtype, g, s);
+    if (dtype == SDP_F32) return gemm_f32(g, s);
+    return gemm_mfma_supported(g) ? gemm_mfma_bf16(g, s) : gemm_simple(g, s);
 }
 
 int head_rows(const int32_t* head_idx, int ph, int H, int hd, int32_t* rows_qkv, int32_t* rows_o, hipStream_t s) {
@@ -848,14 +848,16 @@ int sdp::attn_fwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     }
     if (rc != SDP_OK) return rc;
 
-    rc = transpose_rows((int)esize(dtype), padded ? w.WoP : WoT, d, gathered && !padded ? w.rows_o : nullptr, E, d, w.WoC, E,
-                        "attn_wt_fwd", s);
-    if (rc != SDP_OK) return rc;
+    if (dtype == SDP_BF16) {
+        rc = transpose_rows(padded ? w.WoP : WoT, d, gathered && !padded ? w.rows_o : nullptr, E, d, w.WoC, E, "attn_wt_fwd", s);
+        if (rc != SDP_OK) return rc;
+    }
     GemmDesc op;
     op.name = "attn_out";
     op.M = T, op.N = d, op.K = E;
     op.A = O_save, op.lda = E;
-    op.B = w.WoC, op.ldb = E;
+    if (dtype == SDP_BF16) op.B = w.WoC, op.ldb = E;
+    else op.B = WoT, op.ldb = d, op.b_km = 1, op.b_gather = gathered ? w.rows_o : nullptr, op.b_rows = (int64_t)H * hd;
     op.epilogue = EPI_STORE;
     op.C = Y, op.ldc = d;
     op.R = residual, op.ldr = d;
@@ -958,25 +960,51 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         if (rc != SDP_OK) return rc;
     }
 
-    rc = transpose_rows((int)esize(dtype), padded ? w.Wp : Wqkv, d, gathered && !padded ? w.rows_qkv : nullptr, 3 * E, d, w.Wc,
-                        3 * E, "attn_wt_bwd", s);
-    if (rc != SDP_OK) return rc;
+    if (dtype == SDP_BF16) {
+        rc = transpose_rows(padded ? w.Wp : Wqkv, d, gathered && !padded ? w.rows_qkv : nullptr, 3 * E, d, w.Wc, 3 * E,
+                            "attn_wt_bwd", s);
+        if (rc != SDP_OK) return rc;
+    }
     GemmDesc dx;
     dx.name = "attn_dx";
     dx.M = T, dx.N = d, dx.K = 3 * E;
     dx.A = w.dQKV, dx.lda = 3 * E;
-    dx.B = w.Wc, dx.ldb = 3 * E;
+    if (dtype == SDP_BF16) dx.B = w.Wc, dx.ldb = 3 * E;
+    else dx.B = Wqkv, dx.ldb = d, dx.b_km = 1, dx.b_gather = gathered ? w.rows_qkv : nullptr, dx.b_rows = (int64_t)3 * H * hd;
     dx.epilogue = EPI_STORE;
     dx.C = dX, dx.ldc = d;
     dx.R = dx_residual, dx.ldr = d;
     if (!want_dw) return run(dtype, dx, s);
+
+    const int64_t part = (int64_t)(dw_layout == SDP_DW_SCATTER ? H * hd : ph * hd) * d;
+    if (dtype == SDP_F32) { // every operand as it is stored: dQKV, O, X, dY depth-major, the held heads' columns by their list
+        GemmDesc dw;
+        dw.name = "attn_dw";
+        dw.M = Eh, dw.N = d, dw.K = T;
+        dw.lda = 3 * E, dw.a_km = 1;
+        if (!gathered && !all_heads) dw.a_gather = w.rows_o, dw.a_rows = E;
+        dw.ldb = d, dw.b_km = 1;
+        dw.epilogue = EPI_STORE;
+        dw.ldc = d;
+        dw.c_scatter = dw_layout == SDP_DW_SCATTER && !all_heads ? w.rows_o : nullptr;
+        dw.nbatch = 3;
+        for (int i = 0; i < 3; ++i)
+            dw.Ab[i] = (const float*)w.dQKV + (int64_t)i * E, dw.Bb[i] = X, dw.Cb[i] = (float*)dWqkv + i * part;
+        rc = gemm_f32(dw, s);
+        if (rc != SDP_OK) return rc;
+        dw.nbatch = 0;
+        dw.lda = E;
+        dw.A = O_save, dw.B = dY, dw.C = dWoT;
+        rc = gemm_f32(dw, s);
+        return rc != SDP_OK ? rc : gemm_f32(dx, s);
+    }
 
     const int64_t ldt = ld_tokens(T);
     const TransposeJob tj[4] = {{w.dQKV, w.dQKVt, 3 * E, ldt, nullptr, T, 3 * E},
                                 {O_save, w.Ot, E, ldt, nullptr, T, E},
                                 {X, w.Xt, d, ldt, nullptr, T, d},
                                 {dY, w.dYt, d, ldt, nullptr, T, d}};
-    rc = transpose_batch((int)esize(dtype), tj, 4, "attn_tr_bwd", s);
+    rc = transpose_batch(tj, 4, "attn_tr_bwd", s);
     if (rc != SDP_OK) return rc;
 
     // the four weight gradients share one shape (Eh x d, depth T): dWq, dWk, dWv from the three row blocks of
@@ -985,7 +1013,7 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     // the held heads' rows only (row gather on the left operand): the gradient is computed on the mask.
     GemmDesc dw;
     dw.name = "attn_dw";
-    dw.M = Eh, dw.N = d, dw.K = dtype == SDP_BF16 ? (int)depth_tokens(T) : T; // zeros from T on (transpose_rows_vec_kernel)
+    dw.M = Eh, dw.N = d, dw.K = (int)depth_tokens(T); // zeros from T on (transpose_rows_vec_kernel)
     dw.lda = ldt, dw.ldb = ldt;
     if (!gathered && !all_heads) dw.a_gather = w.rows_o, dw.a_rows = E;
     dw.epilogue = EPI_STORE;
@@ -996,24 +1024,22 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         else dw.a_gather = w.rows_o, dw.a_rows = E;
         dw.c_scatter = w.rows_qkv;
     }
-    const int64_t part = (int64_t)(dw_layout == SDP_DW_SCATTER ? H * hd : ph * hd) * d;
     dw.nbatch = 4;
-    const size_t e = esize(dtype);
     for (int i = 0; i < 3; ++i) {
-        dw.Ab[i] = (const char*)w.dQKVt + (size_t)i * E * ldt * e;
+        dw.Ab[i] = (const uint16_t*)w.dQKVt + (size_t)i * E * ldt;
         dw.Bb[i] = w.Xt;
-        dw.Cb[i] = (char*)dWqkv + (size_t)i * part * e;
+        dw.Cb[i] = (uint16_t*)dWqkv + (size_t)i * part;
     }
     dw.Ab[3] = w.Ot, dw.Bb[3] = w.dYt, dw.Cb[3] = dWoT;
     dw.split_ws = w.split;
-    if (dtype == SDP_BF16 && gemm_mfma_supported(dw)) {
+    if (gemm_mfma_supported(dw)) {
         rc = gemm_mfma_bf16(dw, s);
         if (rc != SDP_OK) return rc;
     } else {
         dw.nbatch = 0;
         for (int i = 0; i < 4; ++i) {
             dw.A = dw.Ab[i], dw.B = dw.Bb[i], dw.C = dw.Cb[i];
-            rc = gemm_simple(dtype, dw, s);
+            rc = gemm_simple(dw, s);
             if (rc != SDP_OK) return rc;
         }
     }

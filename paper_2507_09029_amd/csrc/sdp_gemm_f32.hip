@@ -1,0 +1,423 @@
+// fp32 contraction on the matrix cores (v_mfma_f32_16x16x4_f32: fp32 operands, fp32 accumulation), with the SwiGLU
+// epilogues: the fp32 path of the masked MLP and of the attention projections.  Any M, N, K >= 1.
+//
+//   C[M][N] = sum_k A(m,k) B(k,n); each operand is read as it is stored, so no transposed or compacted copy is made:
+//     rows   : row r of the operand is contiguous along the depth (optional gather of rows)
+//     depth-major : depth step k is contiguous along the rows (B: optional gather of depth steps, which is how a list
+//              of neurons or heads restricts a depth; A: optional gather of columns, the same for the weight gradients)
+//
+// What bounds it: the matrix cores give 157 TFLOP/s (a plain fp32 FMA half of that), i.e. 32 cycles per 16x16x4 tile, so
+// operand traffic is cheap here (a wave reads 4 KB of LDS per 512 matrix cycles) and the shapes that use fp32 are small:
+// latency, launches and idle CUs decide.  Hence three tiles, one loop:
+//   128 x 128 (4 waves of 64 x 64), 64 x 64 (4 waves of 32 x 32), and 32 x 32 whose 4 waves share one tile and split its
+//   depth (each takes 16 of every 64 depth steps; their sums meet in LDS), for launches with fewer tiles than CUs.
+// Tiles move global -> registers -> LDS, the next two or three steps in flight; one barrier per step.
+//
+// A depth slot is free to stand for any k as long as both operands agree: in a group of 16 depth steps, lane group
+// g = lane / 16 takes k = 4 g + j in the j-th of four MFMAs, so an operand stored by rows is one 16-byte LDS read per
+// 16 x 16 fragment, a depth-major one four 4-byte reads; row strides of 4 (mod 16) words keep both free of conflicts.
+//
+// Measured: four workers' steps at T = 256, d = 256, F = 1024, p = 512 (twelve launches a worker with a plain FMA kernel
+// and transposed copies before, five now): 2079 -> 206 us; per launch 7.5 - 16 us, of which about 4 us is what an empty
+// kernel takes.
+#include "sdp_internal.h"
+#include "sdp_swiglu.h"
+
+#include <type_traits>
+
+namespace sdp {
+namespace {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+struct Dev {
+    int M, N, K;
+    const float *A, *A2, *B, *B2;
+    int64_t lda, ldb;
+    const int32_t *ag, *bg, *cs;
+    int vec_a, vec_b; // 16-byte loads: aligned bases and strides, extents along the contiguous axis multiples of 4
+    float *C, *C2, *C3;
+    int64_t ldc;
+    const float *Gin, *Uin;
+    int64_t ldg;
+    const float* R;
+    int64_t ldr;
+    int vec_out; // 16-byte epilogue accesses
+    int nbatch, tiles_m, tiles_n;
+    const float *Ab[kMaxBatch], *Bb[kMaxBatch];
+    float* Cb[kMaxBatch];
+};
+
+template <int BM_, int BN_, int KSPLIT_>
+struct Cfg {
+    static constexpr int BM = BM_, BN = BN_, KSPLIT = KSPLIT_; // KSPLIT waves share a tile's depth
+    static constexpr int BK = KSPLIT == 1 ? 32 : 16 * KSPLIT;
+    static constexpr int WM = KSPLIT == 1 ? BM / 2 : BM, WN = KSPLIT == 1 ? BN / 2 : BN; // a wave's part
+    static constexpr int FM = WM / 16, FN = WN / 16;
+    static constexpr int AHEAD = BM >= 128 ? 1 : 3; // steps in registers beyond the one in LDS
+};
+
+// One operand's tile: R rows (M or N side) x BK depth.
+template <int R, int BK, bool DM>
+struct Operand {
+    static constexpr int LD = DM ? R + 4 : BK + 4;               // LDS row stride in floats
+    static constexpr int FLOATS = DM ? BK * LD : R * LD;
+    static constexpr int Q = DM ? R / 4 : BK / 4;                // 4-float pieces per LDS row
+    static constexpr int PER = R * BK / 4 / 256;                 // pieces per thread
+    static constexpr int STEP = 256 / Q;                         // LDS rows between a thread's pieces
+};
+
+// Where a thread's pieces of an operand come from; rows beyond the matrix are clamped (their products are never stored)
+template <int R, int BK, bool DM>
+struct Source {
+    typedef Operand<R, BK, DM> Op;
+    const float* p[DM ? 1 : Op::PER]; // by rows: each piece's row; depth-major: the thread's column
+    int64_t ld;
+    const int32_t *kg, *cg; // depth-major: gather of depth steps / of columns
+    int col[4];             // depth-major with single loads: the piece's four columns
+    int K, q4, r0;
+    bool vec;
+    int kidx[DM ? Op::PER : 1]; // gathered depth steps of the next tile to be fetched
+
+    __device__ void init(const float* base, int64_t ld_, int rows, int row0, int K_, const int32_t* gather_rows,
+                         const int32_t* gather_depth, bool vec_, int tid) {
+        ld = ld_, K = K_, vec = vec_, kg = gather_depth, cg = DM ? gather_rows : nullptr;
+        q4 = (tid % Op::Q) * 4, r0 = tid / Op::Q;
+        if constexpr (DM) {
+            p[0] = base;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                int c = row0 + q4 + j;
+                c = c < rows ? c : (vec ? rows - 4 + j : rows - 1);
+                col[j] = cg ? cg[c] : c;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < Op::PER; ++i) {
+                int r = row0 + r0 + Op::STEP * i;
+                r = r < rows ? r : rows - 1;
+                p[i] = base + (int64_t)(gather_rows ? gather_rows[r] : r) * ld;
+            }
+        }
+    }
+    __device__ void next_depth(int k0) { // list entries of the tile that starts at depth k0
+        if constexpr (DM) {
+#pragma unroll
+            for (int i = 0; i < Op::PER; ++i) {
+                int k = k0 + r0 + Op::STEP * i;
+                k = k < K ? k : K - 1;
+                kidx[i] = kg ? kg[k] : k;
+            }
+        }
+    }
+    __device__ void fetch(f32x4 (&v)[Op::PER], int k0) {
+        if constexpr (DM) {
+#pragma unroll
+            for (int i = 0; i < Op::PER; ++i) {
+                const float* row = p[0] + (int64_t)kidx[i] * ld;
+                if (vec) v[i] = *(const f32x4*)(row + col[0]);
+                else v[i] = f32x4{row[col[0]], row[col[1]], row[col[2]], row[col[3]]};
+            }
+        } else {
+            if (vec) {
+                const int k = k0 + q4 < K ? k0 + q4 : K - 4;
+#pragma unroll
+                for (int i = 0; i < Op::PER; ++i) v[i] = *(const f32x4*)(p[i] + k);
+            } else {
+                int k[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) k[j] = k0 + q4 + j < K ? k0 + q4 + j : K - 1;
+#pragma unroll
+                for (int i = 0; i < Op::PER; ++i) v[i] = f32x4{p[i][k[0]], p[i][k[1]], p[i][k[2]], p[i][k[3]]};
+            }
+        }
+    }
+    // registers -> LDS; depth steps from K on become zeros
+    __device__ void stash(float* lds, const f32x4 (&v)[Op::PER], int k0) const {
+#pragma unroll
+        for (int i = 0; i < Op::PER; ++i) {
+            f32x4 w = v[i];
+            if (k0 + BK > K) { // uniform: the last, partial step
+                if constexpr (DM) {
+                    if (k0 + r0 + Op::STEP * i >= K) w = f32x4{0.f, 0.f, 0.f, 0.f};
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) w[j] = k0 + q4 + j < K ? w[j] : 0.f;
+                }
+            }
+            *(f32x4*)(lds + (r0 + Op::STEP * i) * Op::LD + q4) = w;
+        }
+    }
+};
+
+// fragment of 16 rows at depth 16 t: element j belongs to depth 16 t + 4 g + j
+template <int R, int BK, bool DM>
+__device__ inline f32x4 fragment(const float* lds, int row, int t, int g) {
+    constexpr int LD = Operand<R, BK, DM>::LD;
+    if constexpr (DM) {
+        const float* p = lds + (16 * t + 4 * g) * LD + row;
+        return f32x4{p[0], p[LD], p[2 * LD], p[3 * LD]};
+    } else {
+        return *(const f32x4*)(lds + row * LD + 16 * t + 4 * g);
+    }
+}
+
+template <class C, int EPI, bool ADM, bool BDM>
+__global__ __launch_bounds__(256) void gemm_f32_kernel(Dev g) {
+    constexpr int BM = C::BM, BN = C::BN, BK = C::BK, FM = C::FM, FN = C::FN, AHEAD = C::AHEAD;
+    constexpr bool kTwoB = EPI == EPI_SWIGLU_FWD;
+    typedef Operand<BM, BK, ADM> OA;
+    typedef Operand<BN, BK, BDM> OB;
+    constexpr int NB = kTwoB ? 2 : 1, STAGE = OA::FLOATS + NB * OB::FLOATS;
+    extern __shared__ __attribute__((aligned(16))) float smem[]; // two stages of A, B (, B2)
+
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int per = g.tiles_m * g.tiles_n;
+    const int z = blockIdx.x / per, tile = blockIdx.x - z * per;
+    const int m0 = (tile % g.tiles_m) * BM, n0 = (tile / g.tiles_m) * BN;
+    const float *gA = g.A, *gB = g.B;
+    float* gC = g.C;
+    if (g.nbatch > 0) {
+        gA = z == 0 ? g.Ab[0] : (z == 1 ? g.Ab[1] : (z == 2 ? g.Ab[2] : g.Ab[3]));
+        gB = z == 0 ? g.Bb[0] : (z == 1 ? g.Bb[1] : (z == 2 ? g.Bb[2] : g.Bb[3]));
+        gC = z == 0 ? g.Cb[0] : (z == 1 ? g.Cb[1] : (z == 2 ? g.Cb[2] : g.Cb[3]));
+    }
+    const int wrow = C::KSPLIT == 1 ? (wave >> 1) * C::WM : 0, wcol = C::KSPLIT == 1 ? (wave & 1) * C::WN : 0;
+
+    f32x4 acc[NB][FM][FN];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j) acc[b][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    const int steps = (g.K + BK - 1) / BK;
+#pragma unroll
+    for (int pass = 0; pass < (EPI == EPI_DUAL_ACC ? 2 : 1); ++pass) {
+        Source<BM, BK, ADM> sa;
+        Source<BN, BK, BDM> sb, sb2;
+        sa.init(pass ? g.A2 : gA, g.lda, g.M, m0, g.K, g.ag, nullptr, g.vec_a, tid);
+        sb.init(pass ? g.B2 : gB, g.ldb, g.N, n0, g.K, BDM ? nullptr : g.bg, BDM ? g.bg : nullptr, g.vec_b, tid);
+        if (kTwoB) sb2.init(g.B2, g.ldb, g.N, n0, g.K, BDM ? nullptr : g.bg, BDM ? g.bg : nullptr, g.vec_b, tid);
+        f32x4 ra[AHEAD][OA::PER], rb[NB][AHEAD][OB::PER];
+        // tile t of the depth into register set s; the lists of the tile after it follow
+        auto fetch = [&](int t, auto set) {
+            constexpr int s = decltype(set)::value;
+            sa.fetch(ra[s], t * BK);
+            sb.fetch(rb[0][s], t * BK);
+            if (kTwoB) sb2.fetch(rb[NB - 1][s], t * BK);
+            sa.next_depth((t + 1) * BK);
+            sb.next_depth((t + 1) * BK);
+            if (kTwoB) sb2.next_depth((t + 1) * BK);
+        };
+        auto stash = [&](int t, auto set) {
+            constexpr int s = decltype(set)::value;
+            float* st = smem + (t & 1) * STAGE;
+            sa.stash(st, ra[s], t * BK);
+            sb.stash(st + OA::FLOATS, rb[0][s], t * BK);
+            if (kTwoB) sb2.stash(st + OA::FLOATS + OB::FLOATS, rb[NB - 1][s], t * BK);
+        };
+        auto compute = [&](int t) {
+            const float* st = smem + (t & 1) * STAGE;
+#pragma unroll
+            for (int u = 0; u < (C::KSPLIT == 1 ? BK / 16 : 1); ++u) {
+                const int kt = C::KSPLIT == 1 ? u : wave;
+                f32x4 fa[FM], fb[NB][FN];
+#pragma unroll
+                for (int i = 0; i < FM; ++i) fa[i] = fragment<BM, BK, ADM>(st, wrow + 16 * i + l16, kt, lg);
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int j = 0; j < FN; ++j)
+                        fb[b][j] = fragment<BN, BK, BDM>(st + OA::FLOATS + b * OB::FLOATS, wcol + 16 * j + l16, kt, lg);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int b = 0; b < NB; ++b)
+#pragma unroll
+                        for (int i = 0; i < FM; ++i)
+#pragma unroll
+                            for (int j = 0; j < FN; ++j) // B first: a lane then holds 4 consecutive columns of one row
+                                acc[b][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[b][j][e], fa[i][e], acc[b][i][j], 0, 0, 0);
+            }
+        };
+        // tile t is in LDS, t + 1 .. t + AHEAD in registers (set of tile t: t % AHEAD); tiles beyond the last are
+        // clamped loads that nothing uses
+        sa.next_depth(0);
+        sb.next_depth(0);
+        if (kTwoB) sb2.next_depth(0);
+        fetch(0, std::integral_constant<int, 0>{});
+        stash(0, std::integral_constant<int, 0>{});
+        if constexpr (AHEAD == 1) {
+            fetch(1, std::integral_constant<int, 0>{});
+        } else {
+            fetch(1, std::integral_constant<int, 1>{});
+            fetch(2, std::integral_constant<int, 2>{});
+            fetch(3, std::integral_constant<int, 0>{});
+        }
+        __syncthreads();
+        auto step = [&](int t, auto set) { // `set`: register set of tile t + 1
+            if (t + 1 < steps) stash(t + 1, set);
+            fetch(t + 1 + AHEAD, set);
+            compute(t);
+            __syncthreads();
+        };
+        int t = 0;
+        if constexpr (AHEAD == 1) {
+            for (; t < steps; ++t) step(t, std::integral_constant<int, 0>{});
+        } else {
+            for (; t < steps; t += 3) {
+                step(t, std::integral_constant<int, 1>{});
+                if (t + 1 < steps) step(t + 1, std::integral_constant<int, 2>{});
+                if (t + 2 < steps) step(t + 2, std::integral_constant<int, 0>{});
+            }
+        }
+    }
+
+    // four consecutive columns n .. n + 3 of row m
+    auto emit = [&](int m, int n, f32x4 v, f32x4 v2) {
+        if (m >= g.M || n >= g.N) return;
+        const int cnt = g.N - n < 4 ? g.N - n : 4;
+        auto put = [&](float* base, int64_t row, int64_t ld, f32x4 x) {
+            float* p = base + row * ld + n;
+            if (g.vec_out) *(f32x4*)p = x;
+            else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (e < cnt) p[e] = x[e];
+            }
+        };
+        auto get = [&](const float* base, int64_t ld) {
+            const float* p = base + (int64_t)m * ld + n;
+            if (g.vec_out) return *(const f32x4*)p;
+            f32x4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (e < cnt) x[e] = p[e];
+            return x;
+        };
+        if (EPI == EPI_STORE || EPI == EPI_DUAL_ACC) {
+            const int64_t row = g.cs ? g.cs[m] : m;
+            if (row < 0) return; // dropped row
+            if (g.R) v += get(g.R, g.ldr);
+            put(gC, row, g.ldc, v);
+        } else if (EPI == EPI_SWIGLU_FWD) {
+            put(g.C, m, g.ldc, v);
+            put(g.C2, m, g.ldc, v2);
+            f32x4 act;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) act[e] = swiglu_fwd<true>(v[e], v2[e]);
+            put(g.C3, m, g.ldc, act);
+        } else {
+            const f32x4 gv = get(g.Gin, g.ldg), uv = get(g.Uin, g.ldg);
+            f32x4 dg, du, act;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float a, b, c;
+                swiglu_bwd<true>(v[e], gv[e], uv[e], a, b, c);
+                dg[e] = a, du[e] = b, act[e] = c;
+            }
+            put(g.C, m, g.ldc, dg);
+            put(g.C2, m, g.ldc, du);
+            put(g.C3, m, g.ldc, act);
+        }
+    };
+    if constexpr (C::KSPLIT == 1) {
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+                emit(m0 + wrow + 16 * i + l16, n0 + wcol + 16 * j + 4 * lg, acc[0][i][j], acc[NB - 1][i][j]);
+    } else {
+        // the waves' depth shares meet in LDS, added in wave order; one thread per 4 columns
+        static_assert(BM * BN / 4 == 256 && BN == 32 && C::KSPLIT * BM * (BN + 4) * NB <= 2 * STAGE, "one piece per thread");
+        constexpr int RS = BN + 4;
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+#pragma unroll
+            for (int i = 0; i < FM; ++i)
+#pragma unroll
+                for (int j = 0; j < FN; ++j)
+                    *(f32x4*)(smem + ((b * C::KSPLIT + wave) * BM + 16 * i + l16) * RS + 16 * j + 4 * lg) = acc[b][i][j];
+        __syncthreads();
+        const int row = tid / 8, c = (tid % 8) * 4;
+        f32x4 s[NB];
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            s[b] = *(const f32x4*)(smem + (b * C::KSPLIT * BM + row) * RS + c);
+#pragma unroll
+            for (int w = 1; w < C::KSPLIT; ++w) s[b] += *(const f32x4*)(smem + ((b * C::KSPLIT + w) * BM + row) * RS + c);
+        }
+        emit(m0 + row, n0 + c, s[0], s[NB - 1]);
+    }
+}
+
+template <class C, int EPI, bool ADM, bool BDM>
+int launch(Dev g, const char* name, hipStream_t s) {
+    constexpr int STAGE = Operand<C::BM, C::BK, ADM>::FLOATS + (EPI == EPI_SWIGLU_FWD ? 2 : 1) * Operand<C::BN, C::BK, BDM>::FLOATS;
+    constexpr int LDS = 2 * STAGE * 4;
+    static_assert(LDS <= 160 * 1024, "LDS of one CU");
+    g.tiles_m = (g.M + C::BM - 1) / C::BM, g.tiles_n = (g.N + C::BN - 1) / C::BN;
+    const int64_t blocks = (int64_t)g.tiles_m * g.tiles_n * (g.nbatch > 0 ? g.nbatch : 1);
+    if (blocks > 0x7FFFFFFF) return SDP_ERR_SHAPE;
+    auto kern = gemm_f32_kernel<C, EPI, ADM, BDM>;
+    static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+    if (attr != hipSuccess) return SDP_ERR_HIP;
+    ProfileScope ps(name, s);
+    kern<<<(unsigned)blocks, 256, LDS, s>>>(g);
+    return launch_status();
+}
+
+// Tile of a launch: the fewest matrix cycles on the busiest CU (rounds of tiles over 256 CUs x tile area), each tile
+// weighted by what its loop loses to staging and barriers.  With fewer 64-wide tiles than CUs the 32-wide ones win on
+// both counts (T = 256, p = 512, d = 256: 128 tiles whose waves each run a quarter of the depth, against 32).
+template <int EPI, bool ADM, bool BDM>
+int choose(const Dev& g, const char* name, hipStream_t s) {
+    auto cost = [&](int b, double weight) {
+        const int64_t tiles = (int64_t)((g.M + b - 1) / b) * ((g.N + b - 1) / b) * (g.nbatch > 0 ? g.nbatch : 1);
+        return (double)((tiles + 255) / 256) * b * b * weight;
+    };
+    const double c128 = cost(128, 1.0), c64 = cost(64, 1.1), c32 = cost(32, 1.3);
+    if (c32 < c64 && c32 < c128) return launch<Cfg<32, 32, 4>, EPI, ADM, BDM>(g, name, s);
+    if (c64 < c128) return launch<Cfg<64, 64, 1>, EPI, ADM, BDM>(g, name, s);
+    return launch<Cfg<128, 128, 1>, EPI, ADM, BDM>(g, name, s);
+}
+
+} // namespace
+
+int gemm_f32(const GemmDesc& d, hipStream_t s) {
+    if (d.M < 1 || d.N < 1 || d.K < 1) return SDP_ERR_SHAPE;
+    if (d.nbatch < 0 || d.nbatch > kMaxBatch || d.Cc || d.Ct) return SDP_ERR_UNSUPPORTED;
+    Dev g{};
+    g.M = d.M, g.N = d.N, g.K = d.K;
+    g.A = (const float*)d.A, g.A2 = (const float*)d.A2, g.B = (const float*)d.B, g.B2 = (const float*)d.B2;
+    g.lda = d.lda, g.ldb = d.ldb, g.ag = d.a_gather, g.bg = d.b_gather, g.cs = d.c_scatter;
+    g.C = (float*)d.C, g.C2 = (float*)d.C2, g.C3 = (float*)d.C3, g.ldc = d.ldc;
+    g.Gin = (const float*)d.Gin, g.Uin = (const float*)d.Uin, g.ldg = d.ldg;
+    g.R = (const float*)d.R, g.ldr = d.ldr;
+    g.nbatch = d.nbatch;
+    auto al = [](const void* p) { return !p || aligned16(p); };
+    bool va = al(d.A) && al(d.A2), vb = al(d.B) && al(d.B2), vo = al(d.C) && al(d.C2) && al(d.C3);
+    for (int z = 0; z < d.nbatch; ++z) {
+        g.Ab[z] = (const float*)d.Ab[z], g.Bb[z] = (const float*)d.Bb[z], g.Cb[z] = (float*)d.Cb[z];
+        va = va && al(d.Ab[z]), vb = vb && al(d.Bb[z]), vo = vo && al(d.Cb[z]);
+    }
+    // along the contiguous axis: the depth for an operand stored by rows, M or N for a depth-major one
+    g.vec_a = va && d.lda % 4 == 0 && (d.a_km ? d.M : d.K) % 4 == 0 && !(d.a_km && d.a_gather);
+    g.vec_b = vb && d.ldb % 4 == 0 && (d.b_km ? d.N : d.K) % 4 == 0;
+    g.vec_out = vo && d.N % 4 == 0 && d.ldc % 4 == 0 && (!d.R || (al(d.R) && d.ldr % 4 == 0)) &&
+                (d.epilogue != EPI_SWIGLU_BWD || (al(d.Gin) && al(d.Uin) && d.ldg % 4 == 0));
+    switch (d.epilogue) {
+    case EPI_STORE:
+        if (d.a_km) return d.b_km ? choose<EPI_STORE, true, true>(g, d.name, s) : SDP_ERR_UNSUPPORTED;
+        return d.b_km ? choose<EPI_STORE, false, true>(g, d.name, s) : choose<EPI_STORE, false, false>(g, d.name, s);
+    case EPI_DUAL_ACC: return d.a_km || !d.b_km ? SDP_ERR_UNSUPPORTED : choose<EPI_DUAL_ACC, false, true>(g, d.name, s);
+    case EPI_SWIGLU_FWD: return d.a_km || d.b_km ? SDP_ERR_UNSUPPORTED : choose<EPI_SWIGLU_FWD, false, false>(g, d.name, s);
+    case EPI_SWIGLU_BWD: return d.a_km || d.b_km ? SDP_ERR_UNSUPPORTED : choose<EPI_SWIGLU_BWD, false, false>(g, d.name, s);
+    }
+    return SDP_ERR_INVALID_ARG;
+}
+
+} // namespace sdp

@@ -1,5 +1,5 @@
-// Plain LDS-tiled FMA contraction with the SwiGLU epilogues: the fp32 path of the masked MLP and
-// the fallback for bf16 shapes the MFMA kernel does not take (ragged sizes).  Any M, N, K >= 1.
+// Plain LDS-tiled bf16 FMA contraction with the SwiGLU epilogues: the fallback for operands the MFMA kernel cannot
+// address (4 GiB or more, rows of 2^22 elements or more).  Any M, N, K >= 1.
 //
 // 64 x 64 output tile per 256-thread workgroup, K step 16, 4 x 4 outputs per thread, operands
 // widened to fp32 in LDS, fp32 accumulation.
@@ -14,19 +14,11 @@ constexpr int BM = 64, BN = 64, BK = 16, NT = 256;
 template <typename T>
 __device__ inline float ld(const T* p);
 template <>
-__device__ inline float ld<float>(const float* p) {
-    return *p;
-}
-template <>
 __device__ inline float ld<uint16_t>(const uint16_t* p) {
     return bf16_to_f32(*p);
 }
 template <typename T>
 __device__ inline void st(T* p, float v);
-template <>
-__device__ inline void st<float>(float* p, float v) {
-    *p = v;
-}
 template <>
 __device__ inline void st<uint16_t>(uint16_t* p, float v) {
     *p = f32_to_bf16(v);
@@ -148,12 +140,12 @@ __global__ __launch_bounds__(NT) void gemm_simple_kernel(Dev g) {
                 const float gv = acc[i][j], uv = acc2[i][j];
                 st<T>((T*)g.C + (int64_t)m * g.ldc + n, gv);
                 st<T>((T*)g.C2 + (int64_t)m * g.ldc + n, uv);
-                st<T>((T*)g.C3 + (int64_t)m * g.ldc + n, swiglu_fwd<sizeof(T) == 4>(gv, uv));
+                st<T>((T*)g.C3 + (int64_t)m * g.ldc + n, swiglu_fwd<false>(gv, uv));
             } else {
                 const float gv = ld<T>((const T*)g.Gin + (int64_t)m * g.ldg + n);
                 const float uv = ld<T>((const T*)g.Uin + (int64_t)m * g.ldg + n);
                 float dg, du, act;
-                swiglu_bwd<sizeof(T) == 4>(acc[i][j], gv, uv, dg, du, act);
+                swiglu_bwd<false>(acc[i][j], gv, uv, dg, du, act);
                 st<T>((T*)g.C + (int64_t)m * g.ldc + n, dg);
                 st<T>((T*)g.C2 + (int64_t)m * g.ldc + n, du);
                 st<T>((T*)g.C3 + (int64_t)m * g.ldc + n, act);
@@ -193,11 +185,11 @@ int dispatch(const GemmDesc& d, hipStream_t s) {
 
 } // namespace
 
-int gemm_simple(int dtype, const GemmDesc& d, hipStream_t s) {
+int gemm_simple(const GemmDesc& d, hipStream_t s) {
     if (d.M < 1 || d.N < 1 || d.K < 1) return SDP_ERR_SHAPE;
-    if (d.a_gather && d.a_km) return SDP_ERR_UNSUPPORTED;
+    if ((d.a_gather && d.a_km) || d.b_km) return SDP_ERR_UNSUPPORTED;
     if ((d.N + BN - 1) / BN > 0x7FFFFFFF || (d.M + BM - 1) / BM > 65535) return SDP_ERR_SHAPE;
-    return dtype == SDP_F32 ? dispatch<float>(d, s) : dispatch<uint16_t>(d, s);
+    return dispatch<uint16_t>(d, s);
 }
 
 } // namespace sdp

@@ -36,9 +36,10 @@ inline size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 // ---- contraction descriptor --------------------------------------------------------------------
 // C[M][N] = sum_k A(m,k) * B(k,n), fp32 accumulation, all matrices row-major.
 //   A(m,k) = a_km ? A[k * lda + m] : A[ra(m) * lda + k]  (a_km: A is stored depth-major, [K][M])
-//   B(k,n) = B[rb(n) * ldb + k]                           (B is stored [N][K], rows contiguous along k)
+//   B(k,n) = b_km ? B[rb(k) * ldb + n] : B[rb(n) * ldb + k] (b_km: B is stored depth-major, [K][N])
 // rb is the identity when b_gather is null, else a lookup in an int32 table (active-neuron rows); ra likewise
-// with a_gather (not together with a_km).
+// with a_gather (with a_km it applies to the columns: A[k * lda + ra(m)]).  b_km and a_km with a_gather: fp32
+// contraction only.
 // A second operand pair (A2, B2) with the same shapes and strides is used by two of the epilogues.
 enum Epilogue {
     EPI_STORE = 0,       // C[rc(m) * ldc + n] = acc      (rc: optional row scatter; rc(m) < 0 drops row m)
@@ -46,7 +47,7 @@ enum Epilogue {
     EPI_SWIGLU_FWD = 2,  // g = A.B, u = A.B2: G = g, U = u, Act = silu(g) * u, all [M][N] (ld = ldc)
     EPI_SWIGLU_BWD = 3   // da = A.B; with g = Gin[m][n], u = Uin[m][n]  (ld = ldg):
                          //   dU = da silu(g), dG = da u silu'(g), act = silu(g) u, all [M][N] (ld = ldc);
-                         //   plain kernel: with cidx != null also the column-compacted copies [M][pc]
+                         //   plain bf16 kernel: with cidx != null also the column-compacted copies [M][pc]
                          //   (ld = ldcc): column c of Cc / Cc2 / Cc3 is column cidx[c] of dG / dU / act
 };
 
@@ -63,6 +64,7 @@ struct GemmDesc {
     const void* B = nullptr;
     const void* B2 = nullptr;
     int64_t ldb = 0;
+    int b_km = 0;
     const int32_t* b_gather = nullptr;
     int64_t b_rows = 0; // number of rows of the stored B (bounds the gathered row index); 0 = N
     int epilogue = EPI_STORE;
@@ -120,8 +122,10 @@ struct GemmDesc {
 // tags that give each call site of the MFMA contraction its own kernel symbol
 enum GemmOp { OP_GATE_UP = 0, OP_DOWN = 1, OP_DACT = 2, OP_DX = 3, OP_DW = 4, OP_DW_SPLIT = 5, OP_DW_TAIL = 6 };
 
-// Plain LDS-tiled FMA contraction, any shape; element type float or bf16 (dtype as sdp_dtype).
-int gemm_simple(int dtype, const GemmDesc& g, hipStream_t s);
+// fp32 contraction on the matrix cores, any shape.
+int gemm_f32(const GemmDesc& g, hipStream_t s);
+// Plain LDS-tiled bf16 contraction, any shape: what the MFMA kernel's address ranges do not take.
+int gemm_simple(const GemmDesc& g, hipStream_t s);
 // bf16 MFMA contraction; returns SDP_ERR_UNSUPPORTED when the shape / alignment does not fit.
 int gemm_mfma_bf16(const GemmDesc& g, hipStream_t s);
 bool gemm_mfma_supported(const GemmDesc& g);
@@ -172,11 +176,12 @@ int attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd, int 
                   const float* LSE_save, void* dX, void* dWqkv, void* dWoT, int dw_layout, const void* dx_residual,
                   bool want_dw, void* ws, hipStream_t s);
 
-// out[c][r] = in[rows ? rows[r] : r][c] for r < R, c < C: (gathered) transpose, element size 2 or 4.
-int transpose_rows(int elem_bytes, const void* in, int64_t ld_in, const int32_t* rows, int R, int C, void* out,
-                   int64_t ld_out, const char* name, hipStream_t s);
+// out[c][r] = in[rows ? rows[r] : r][c] for r < R, c < C: (gathered) transpose of 16-bit elements; C, ld_in and ld_out
+// multiples of 8, ld_out >= R (elements R .. round_up(R, 8) - 1 of an output row become zeros), 16-byte aligned bases.
+int transpose_rows(const void* in, int64_t ld_in, const int32_t* rows, int R, int C, void* out, int64_t ld_out,
+                   const char* name, hipStream_t s);
 
-// Several such transposes as one launch (16-bit elements with 8-element aligned shapes; otherwise one launch each).
+// Several such transposes as one launch.
 constexpr int kMaxTransposeJobs = 4;
 struct TransposeJob {
     const void* in;
@@ -185,7 +190,7 @@ struct TransposeJob {
     const int32_t* rows; // optional gather of input rows
     int R, C;
 };
-int transpose_batch(int elem_bytes, const TransposeJob* jobs, int n, const char* name, hipStream_t s);
+int transpose_batch(const TransposeJob* jobs, int n, const char* name, hipStream_t s);
 
 // crank[n] for n < N from the ascending list cidx[0 .. pc): the number of listed columns below n if n is listed,
 // else -1 - that number

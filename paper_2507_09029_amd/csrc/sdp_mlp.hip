@@ -16,9 +16,10 @@
 //                        one batched launch over the neuron-major copies and XT, dYT
 //             dx      : dX = dG . W1c^T + dU . W3c^T         (T x d, depth 2n)
 // Under backward masking the weight-gradient contraction reads only the p kept rows: the gradient is
-// computed on the worker's mask and nowhere else.  fp32 tensors and bf16 shapes the MFMA kernel does
-// not take go through the plain kernel, which reads dG, dU, Act depth-major as they are (and, under
-// backward masking, their column-compacted copies [T][p]).
+// computed on the worker's mask and nowhere else.  fp32 tensors take the fp32 contraction, which reads every
+// operand as it is stored (the weights depth-major through the worker's list, dG, dU, Act depth-major on its
+// columns): no copies, five launches.  bf16 operands beyond the MFMA kernel's address range go through the plain
+// kernel, which reads dG, dU, Act depth-major (and, under backward masking, their column-compacted copies [T][p]).
 #include "sdp_internal.h"
 
 namespace {
@@ -56,8 +57,8 @@ __global__ __launch_bounds__(256) void column_ranks_kernel(const int32_t* __rest
 }
 
 int run(int dtype, const GemmDesc& g, hipStream_t s) {
-    if (dtype == SDP_BF16 && gemm_mfma_supported(g)) return gemm_mfma_bf16(g, s);
-    return gemm_simple(dtype, g, s);
+    if (dtype == SDP_F32) return gemm_f32(g, s);
+    return gemm_mfma_supported(g) ? gemm_mfma_bf16(g, s) : gemm_simple(g, s);
 }
 
 } // namespace
@@ -116,8 +117,10 @@ int sdp::mlp_fwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
     void* Act = w;
     void* W2c = w + round_up((size_t)T * n * e, 256);
 
-    rc = transpose_rows((int)e, W2T, d, gather, n, d, W2c, n, "mlp_wt_fwd", s);
-    if (rc != SDP_OK) return rc;
+    if (dtype == SDP_BF16) {
+        rc = transpose_rows(W2T, d, gather, n, d, W2c, n, "mlp_wt_fwd", s);
+        if (rc != SDP_OK) return rc;
+    }
 
     GemmDesc gu;
     gu.name = "mlp_gate_up";
@@ -133,7 +136,8 @@ int sdp::mlp_fwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
     dn.name = "mlp_down";
     dn.M = T, dn.N = d, dn.K = n;
     dn.A = Act, dn.lda = n;
-    dn.B = W2c, dn.ldb = n;
+    if (dtype == SDP_BF16) dn.B = W2c, dn.ldb = n;
+    else dn.B = W2T, dn.ldb = d, dn.b_km = 1, dn.b_gather = gather, dn.b_rows = F;
     dn.epilogue = EPI_STORE;
     dn.C = Y, dn.ldc = d;
     dn.R = residual, dn.ldr = d;
@@ -188,12 +192,51 @@ int sdp::mlp_bwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
     if (mode == SDP_MASK_BACKWARD) w += round_up((size_t)F * sizeof(int32_t), 256);
     void* tail_ws = dtype == SDP_BF16 && gemm_tail_ws_bytes(p, d, T, 3) > 0 ? w : nullptr;
 
+    if (dtype == SDP_F32) {
+        GemmDesc da;
+        da.name = "mlp_dact";
+        da.M = T, da.N = n, da.K = d;
+        da.A = dY, da.lda = d;
+        da.B = W2T, da.ldb = d, da.b_gather = gather, da.b_rows = F;
+        da.epilogue = EPI_SWIGLU_BWD;
+        da.Gin = G_save, da.Uin = U_save, da.ldg = n;
+        da.C = dG, da.C2 = dU, da.C3 = Act, da.ldc = n;
+        rc = gemm_f32(da, s);
+        if (rc != SDP_OK) return rc;
+        if (want_dw) {
+            GemmDesc dw;
+            dw.name = "mlp_dw";
+            dw.M = p, dw.N = d, dw.K = T;
+            dw.lda = n, dw.a_km = 1;
+            if (mode == SDP_MASK_BACKWARD) dw.a_gather = idx_k, dw.a_rows = n;
+            dw.ldb = d, dw.b_km = 1;
+            dw.epilogue = EPI_STORE;
+            dw.ldc = d;
+            dw.c_scatter = dw_layout == SDP_DW_SCATTER ? idx_k : nullptr;
+            dw.nbatch = 3;
+            dw.Ab[0] = dG, dw.Ab[1] = dU, dw.Ab[2] = Act;
+            dw.Bb[0] = X, dw.Bb[1] = X, dw.Bb[2] = dY;
+            dw.Cb[0] = dW1, dw.Cb[1] = dW3, dw.Cb[2] = dW2T;
+            rc = gemm_f32(dw, s);
+            if (rc != SDP_OK) return rc;
+        }
+        GemmDesc dx;
+        dx.name = "mlp_dx";
+        dx.M = T, dx.N = d, dx.K = n;
+        dx.A = dG, dx.A2 = dU, dx.lda = n;
+        dx.B = W1, dx.B2 = W3, dx.ldb = d, dx.b_km = 1, dx.b_gather = gather, dx.b_rows = F;
+        dx.epilogue = EPI_DUAL_ACC;
+        dx.C = dX, dx.ldc = d;
+        dx.R = dx_residual, dx.ldr = d;
+        return gemm_f32(dx, s);
+    }
+
     // the four operand copies of the backward pass as one launch (X^T, dY^T only feed the weight gradients)
     const TransposeJob tj[4] = {{W1, W1c, d, n, gather, n, d},
                                 {W3, W3c, d, n, gather, n, d},
                                 {X, XT, d, ld_tokens(T), nullptr, T, d},
                                 {dY, dYT, d, ld_tokens(T), nullptr, T, d}};
-    rc = transpose_batch((int)e, tj, want_dw ? 4 : 2, "mlp_tr_bwd", s);
+    rc = transpose_batch(tj, want_dw ? 4 : 2, "mlp_tr_bwd", s);
     if (rc != SDP_OK) return rc;
 
     // weight-gradient contraction (set up first: whether it can take the MFMA path decides what the
@@ -226,11 +269,11 @@ int sdp::mlp_bwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
     // weight-gradient contraction reads both operands depth-contiguous; act is not stored row-major.
     da.Ct = dGn, da.Ct2 = dUn, da.Ct3 = Actn, da.ldct = ld_tokens(T);
     if (mode == SDP_MASK_BACKWARD) da.cidx = idx_k, da.pc = p, da.crank = ranks;
-    const bool fused = want_dw && dtype == SDP_BF16 && p % 8 == 0 && T % 8 == 0 && gemm_mfma_supported(dw) && gemm_mfma_supported(da);
+    const bool fused = want_dw && p % 8 == 0 && T % 8 == 0 && gemm_mfma_supported(dw) && gemm_mfma_supported(da);
     if (!fused) {
         da.Ct = da.Ct2 = da.Ct3 = nullptr, da.cidx = nullptr, da.pc = 0, da.crank = nullptr;
         // without weight gradients nothing reads act: the MFMA kernel then skips its store, the plain one writes it anyway
-        if (want_dw || dtype != SDP_BF16 || !gemm_mfma_supported(da)) da.C3 = Act;
+        if (want_dw || !gemm_mfma_supported(da)) da.C3 = Act;
         if (mode == SDP_MASK_BACKWARD && want_dw) {
             da.Cc = dGc, da.Cc2 = dUc, da.Cc3 = Actc, da.ldcc = p;
             da.cidx = idx_k, da.pc = p;
@@ -265,7 +308,7 @@ int sdp::mlp_bwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
     dw.lda = p, dw.a_km = 1;
     for (int i = 0; i < 3; ++i) {
         dw.A = lhs[i], dw.B = rhs[i], dw.C = outp[i];
-        rc = gemm_simple(dtype, dw, s);
+        rc = gemm_simple(dw, s);
         if (rc != SDP_OK) return rc;
     }
     return SDP_OK;

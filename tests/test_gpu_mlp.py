@@ -100,6 +100,19 @@ def test_depths_that_are_odd_multiples_of_8(sdp, orc, w):
     run_case(sdp, orc, w, [0, 1], dw_layout="scatter" if w.mode == "bm" else "compact")
 
 
+# fp32 contraction: extents around the edges of its 32- and 64-wide tiles and of its depth steps (single-element and
+# 16-byte loads), and one case per operand layout that is large enough for the 128-wide tile
+F32_TILES = [MlpWorkload(f"f32_{T}x{d}x{F}p{p}_{mode}", "f32", T, d, F, p, 2, mode, 25) for T, d, F, p, mode in (
+    (1, 1, 3, 2, "fm"), (31, 33, 70, 65, "bm"), (32, 64, 128, 64, "fm"), (65, 31, 130, 127, "bm"), (64, 96, 192, 96, "bm"),
+    (129, 63, 140, 100, "fm"), (200, 132, 516, 260, "bm"), (2040, 40, 2040, 2040, "fm"), (40, 2040, 2040, 1020, "bm"),
+    (2040, 2040, 64, 33, "fm"))]
+
+
+@pytest.mark.parametrize("w", F32_TILES, ids=[w.name for w in F32_TILES])
+def test_f32_tiles(sdp, orc, w):
+    run_case(sdp, orc, w, [1], dw_layout="scatter" if w.T % 2 else "compact")
+
+
 @pytest.mark.parametrize("w", SMALL, ids=[w.name for w in SMALL])
 def test_small_shapes_all_outputs(sdp, orc, w):
     run_case(sdp, orc, w, range(min(w.K, 2)))
