@@ -204,7 +204,7 @@ int sdp_masked_mlp_bwd(int mode, int dtype, int T, int d, int F, int p, const vo
  *   ws: sdp_masked_attn_fwd_workspace_bytes(...).
  * Limits: hd <= 128 (else UNSUPPORTED); for SDP_BF16 d a multiple of 8 (16-byte rows), and hd a multiple of 8 when
  * above 64; Bt, H <= 65535; pointers 16-byte aligned.  bf16 runs the MFMA attention core (probabilities and
- * logit gradients are rounded once to bf16 where they enter a product), fp32 a plain fp32-arithmetic core.  Errors as for the MLP calls.
+ * logit gradients are rounded once to bf16 where they enter a product), fp32 a core in fp32 throughout.  Errors as for the MLP calls.
  * ------------------------------------------------------------------------------------------- */
 int sdp_masked_attn_saved_head_width(int dtype, int hd);
 size_t sdp_masked_attn_fwd_workspace_bytes(int mode, int dtype, int Bt, int S, int d, int H, int hd, int ph);

@@ -629,7 +629,7 @@ int64_t ld_tokens(int64_t T) { return depth_tokens(T) + 64; }
 // logit, a zero feature of V gives a zero feature of O, and every gradient of a zero feature is zero.  The padding
 // is made once, on the weights (pad_heads_kernel): the saved Q | K | V and O then carry 64 columns per head, of
 // which the last 64 - hd are zero.  Wider bf16 heads are saved as they are and run the MFMA core of the next width
-// (64, 96, 128), which sets the missing columns to zero as it stages them; fp32 heads go through the plain core.
+// (64, 96, 128), which sets the missing columns to zero as it stages them; fp32 heads go through the fp32 core (sdp_attn_f32.hip).
 int core_width(int dtype, int hd) { return dtype == SDP_BF16 && hd <= HD ? HD : hd; }
 bool mfma_core(int dtype) { return dtype == SDP_BF16; }
 size_t esize(int dtype) { return dtype == SDP_F32 ? 4 : 2; }
@@ -844,7 +844,7 @@ int sdp::attn_fwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         AttnCoreDesc c;
         c.qkv = QKV_save, c.ldq = 3 * E, c.o_out = O_save, c.ldo = E, c.lse = LSE_save;
         c.Bt = Bt, c.S = S, c.n = ph, c.hd = hd;
-        rc = attn_plain_fwd(dtype, c, s);
+        rc = attn_f32_fwd(c, s);
     }
     if (rc != SDP_OK) return rc;
 
@@ -956,7 +956,7 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         c.qkv = QKV_save, c.ldq = 3 * E, c.o = O_save, c.dO = w.dO, c.ldo = E;
         c.lse = const_cast<float*>(LSE_save), c.delta = w.delta, c.dqkv = w.dQKV;
         c.Bt = Bt, c.S = S, c.n = hr, c.hd = hd;
-        rc = attn_plain_bwd(dtype, c, s);
+        rc = attn_f32_bwd(c, s);
         if (rc != SDP_OK) return rc;
     }
 

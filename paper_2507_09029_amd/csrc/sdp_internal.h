@@ -150,10 +150,9 @@ struct AttnCoreDesc {
     void* dqkv = nullptr;
     int Bt = 0, S = 0, n = 0, hd = 0;
 };
-// plain core: fp32, hd <= 128 (SDP_ERR_UNSUPPORTED beyond)
-bool attn_plain_supported(const AttnCoreDesc& c);
-int attn_plain_fwd(int dtype, const AttnCoreDesc& c, hipStream_t s);
-int attn_plain_bwd(int dtype, const AttnCoreDesc& c, hipStream_t s);
+// fp32 core, hd <= 128 (SDP_ERR_UNSUPPORTED beyond)
+int attn_f32_fwd(const AttnCoreDesc& c, hipStream_t s);
+int attn_f32_bwd(const AttnCoreDesc& c, hipStream_t s);
 
 // ---- one worker's MLP / attention passes with the options the block-level calls need ----------------
 // As sdp_masked_mlp_fwd / _bwd and sdp_masked_attn_fwd / _bwd after argument checks, plus:

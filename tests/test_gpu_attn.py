@@ -170,6 +170,19 @@ def test_attention_wide_heads(sdp, orc, w, mode):
     run_case(sdp, orc, w, [0], dw_layout="scatter" if w.hd % 16 else "compact", mode=mode)
 
 
+# fp32 core: every width it is instantiated for, 16-byte and single-element loads, sequences around its 16-row tiles and
+# the 64 rows its four waves take at a time
+F32_CORE = [AttnWorkload(f"f32_{hd}_S{S}", Bt, S, 24, 3, hd, 2, 2, 48, "f32") for hd, Bt, S in
+            ((7, 2, 17), (16, 1, 1), (32, 3, 15), (36, 1, 65), (64, 2, 16), (75, 1, 33), (80, 2, 64), (96, 1, 130), (127, 1, 18),
+             (128, 2, 49))]
+
+
+@pytest.mark.parametrize("mode", ["fm", "bm"])
+@pytest.mark.parametrize("w", F32_CORE, ids=[w.name for w in F32_CORE])
+def test_attention_f32_core(sdp, orc, w, mode):
+    run_case(sdp, orc, w, [0], dw_layout="scatter" if w.S % 2 else "compact", mode=mode)
+
+
 @pytest.mark.parametrize("w", BM_CASES, ids=[w.name for w in BM_CASES])
 def test_attention_backward_masking_all_outputs(sdp, orc, w):
     """Dense forward and dX, weight gradients on the held heads only."""
