@@ -18,8 +18,9 @@
 // 16 x 16 fragment, a depth-major one four 4-byte reads; row strides of 4 (mod 16) words keep both free of conflicts.
 //
 // Measured: four workers' steps at T = 256, d = 256, F = 1024, p = 512 (twelve launches a worker with a plain FMA kernel
-// and transposed copies before, five now): 2079 -> 206 us; per launch 7.5 - 16 us, of which about 4 us is what an empty
-// kernel takes.
+// and transposed copies before, five now): 2079 -> 165 us; per launch 7 - 12 us, of which about 4 us is what an empty
+// kernel takes.  (206 us while every step waited for the newest list entry, computed clamped 64-bit addresses per load
+// and branched around its loads, so that the loads in flight could not be counted.)
 #include "sdp_internal.h"
 #include "sdp_swiglu.h"
 
@@ -35,7 +36,6 @@ struct Dev {
     const float *A, *A2, *B, *B2;
     int64_t lda, ldb;
     const int32_t *ag, *bg, *cs;
-    int vec_a, vec_b; // 16-byte loads: aligned bases and strides, extents along the contiguous axis multiples of 4
     float *C, *C2, *C3;
     int64_t ldc;
     const float *Gin, *Uin;
@@ -67,82 +67,92 @@ struct Operand {
     static constexpr int STEP = 256 / Q;                         // LDS rows between a thread's pieces
 };
 
-// Where a thread's pieces of an operand come from; rows beyond the matrix are clamped (their products are never stored)
-template <int R, int BK, bool DM>
+// Where a thread's pieces of an operand come from.  VEC: 16-byte loads (aligned bases and strides, extents along the
+// contiguous axis multiples of 4), else single elements.  Rows beyond the matrix are clamped (their products are never
+// stored).  The depth needs no clamp per load: a tile that would reach beyond it starts at K - BK instead and the depth
+// steps that an earlier tile has had (all of them, for tiles beyond the last) become zeros on the way to LDS; only a
+// depth shorter than one tile clamps, once.  A load's address is then one 64-bit add to a pointer kept per piece: the
+// loop has one wave per SIMD on small launches, and address arithmetic would cost it as much as the MFMAs.
+template <int R, int BK, bool DM, int SETS, bool VEC>
 struct Source {
     typedef Operand<R, BK, DM> Op;
-    const float* p[DM ? 1 : Op::PER]; // by rows: each piece's row; depth-major: the thread's column
-    int64_t ld;
-    const int32_t *kg, *cg; // depth-major: gather of depth steps / of columns
-    int col[4];             // depth-major with single loads: the piece's four columns
-    int K, q4, r0;
-    bool vec;
-    int kidx[DM ? Op::PER : 1]; // gathered depth steps of the next tile to be fetched
+    const float* p[Op::PER]; // each piece's row of the tile at depth 0 (depth-major: its depth step, first column)
+    const float* base;
+    uint32_t ld;
+    const int32_t* kg; // depth-major: gather of depth steps
+    int off[4];        // single loads: the piece's elements, relative to p
+    int K, q4, r0, col0;
+    int kidx[SETS][DM ? Op::PER : 1]; // gathered depth steps of the next tile of each register set
 
-    __device__ void init(const float* base, int64_t ld_, int rows, int row0, int K_, const int32_t* gather_rows,
-                         const int32_t* gather_depth, bool vec_, int tid) {
-        ld = ld_, K = K_, vec = vec_, kg = gather_depth, cg = DM ? gather_rows : nullptr;
+    __device__ int start(int k0) const { // depth at which the tile nominally at k0 is read
+        const int last = K > BK ? K - BK : 0;
+        return k0 < last ? k0 : last;
+    }
+    __device__ void init(const float* base_, int64_t ld_, int rows, int row0, int K_, const int32_t* gather_rows,
+                         const int32_t* gather_depth, int tid) {
+        base = base_, ld = (uint32_t)ld_, K = K_, kg = gather_depth;
         q4 = (tid % Op::Q) * 4, r0 = tid / Op::Q;
+        const int kmax = K - 1;
         if constexpr (DM) {
-            p[0] = base;
+            int col[4];
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 int c = row0 + q4 + j;
-                c = c < rows ? c : (vec ? rows - 4 + j : rows - 1);
-                col[j] = cg ? cg[c] : c;
+                c = c < rows ? c : (VEC ? rows - 4 + j : rows - 1);
+                col[j] = !VEC && gather_rows ? gather_rows[c] : c;
+                off[j] = col[j] - col[0];
+            }
+            col0 = col[0];
+#pragma unroll
+            for (int i = 0; i < Op::PER; ++i) {
+                const int k = r0 + Op::STEP * i;
+                p[i] = base + (int64_t)(k < kmax ? k : kmax) * ld_ + col0;
             }
         } else {
+            const int k = VEC ? (q4 < K ? q4 : K - 4) : (q4 < kmax ? q4 : kmax);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) off[j] = (q4 + j < kmax ? q4 + j : kmax) - k;
 #pragma unroll
             for (int i = 0; i < Op::PER; ++i) {
                 int r = row0 + r0 + Op::STEP * i;
                 r = r < rows ? r : rows - 1;
-                p[i] = base + (int64_t)(gather_rows ? gather_rows[r] : r) * ld;
+                p[i] = base + (int64_t)(gather_rows ? gather_rows[r] : r) * ld_ + k;
             }
         }
     }
-    __device__ void next_depth(int k0) { // list entries of the tile that starts at depth k0
+    __device__ void list(int set, int k0) { // list entries of the tile at depth k0
         if constexpr (DM) {
+            if (kg) {
+                const int32_t* q = kg + start(k0);
 #pragma unroll
-            for (int i = 0; i < Op::PER; ++i) {
-                int k = k0 + r0 + Op::STEP * i;
-                k = k < K ? k : K - 1;
-                kidx[i] = kg ? kg[k] : k;
+                for (int i = 0; i < Op::PER; ++i) {
+                    const int k = r0 + Op::STEP * i;
+                    kidx[set][i] = q[k < K ? k : K - 1];
+                }
             }
         }
     }
-    __device__ void fetch(f32x4 (&v)[Op::PER], int k0) {
-        if constexpr (DM) {
+    __device__ void fetch(f32x4 (&v)[Op::PER], int set, int k0) {
+        const int64_t shift = DM ? (int64_t)start(k0) * ld : start(k0);
 #pragma unroll
-            for (int i = 0; i < Op::PER; ++i) {
-                const float* row = p[0] + (int64_t)kidx[i] * ld;
-                if (vec) v[i] = *(const f32x4*)(row + col[0]);
-                else v[i] = f32x4{row[col[0]], row[col[1]], row[col[2]], row[col[3]]};
-            }
-        } else {
-            if (vec) {
-                const int k = k0 + q4 < K ? k0 + q4 : K - 4;
-#pragma unroll
-                for (int i = 0; i < Op::PER; ++i) v[i] = *(const f32x4*)(p[i] + k);
-            } else {
-                int k[4];
-#pragma unroll
-                for (int j = 0; j < 4; ++j) k[j] = k0 + q4 + j < K ? k0 + q4 + j : K - 1;
-#pragma unroll
-                for (int i = 0; i < Op::PER; ++i) v[i] = f32x4{p[i][k[0]], p[i][k[1]], p[i][k[2]], p[i][k[3]]};
-            }
+        for (int i = 0; i < Op::PER; ++i) {
+            const float* q = p[i] + shift;
+            if (DM && kg) q = base + ((uint64_t)(uint32_t)kidx[set][i] * ld + col0);
+            if (VEC) v[i] = *(const f32x4*)q;
+            else v[i] = f32x4{q[off[0]], q[off[1]], q[off[2]], q[off[3]]};
         }
     }
-    // registers -> LDS; depth steps from K on become zeros
+    // registers -> LDS
     __device__ void stash(float* lds, const f32x4 (&v)[Op::PER], int k0) const {
 #pragma unroll
         for (int i = 0; i < Op::PER; ++i) {
             f32x4 w = v[i];
-            if (k0 + BK > K) { // uniform: the last, partial step
-                if constexpr (DM) {
-                    if (k0 + r0 + Op::STEP * i >= K) w = f32x4{0.f, 0.f, 0.f, 0.f};
-                } else {
+            if (k0 + BK > K) { // uniform: a shifted or short tile
+                const int k = start(k0) + (DM ? r0 + Op::STEP * i : q4);
 #pragma unroll
-                    for (int j = 0; j < 4; ++j) w[j] = k0 + q4 + j < K ? w[j] : 0.f;
+                for (int j = 0; j < 4; ++j) {
+                    const int kj = DM ? k : k + j;
+                    w[j] = kj >= k0 && kj < K ? w[j] : 0.f;
                 }
             }
             *(f32x4*)(lds + (r0 + Op::STEP * i) * Op::LD + q4) = w;
@@ -162,7 +172,7 @@ __device__ inline f32x4 fragment(const float* lds, int row, int t, int g) {
     }
 }
 
-template <class C, int EPI, bool ADM, bool BDM>
+template <class C, int EPI, bool ADM, bool BDM, bool VEC>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(Dev g) {
     constexpr int BM = C::BM, BN = C::BN, BK = C::BK, FM = C::FM, FN = C::FN, AHEAD = C::AHEAD;
     constexpr bool kTwoB = EPI == EPI_SWIGLU_FWD;
@@ -196,21 +206,25 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(Dev g) {
     const int steps = (g.K + BK - 1) / BK;
 #pragma unroll
     for (int pass = 0; pass < (EPI == EPI_DUAL_ACC ? 2 : 1); ++pass) {
-        Source<BM, BK, ADM> sa;
-        Source<BN, BK, BDM> sb, sb2;
-        sa.init(pass ? g.A2 : gA, g.lda, g.M, m0, g.K, g.ag, nullptr, g.vec_a, tid);
-        sb.init(pass ? g.B2 : gB, g.ldb, g.N, n0, g.K, BDM ? nullptr : g.bg, BDM ? g.bg : nullptr, g.vec_b, tid);
-        if (kTwoB) sb2.init(g.B2, g.ldb, g.N, n0, g.K, BDM ? nullptr : g.bg, BDM ? g.bg : nullptr, g.vec_b, tid);
+        Source<BM, BK, ADM, AHEAD, VEC> sa;
+        Source<BN, BK, BDM, AHEAD, VEC> sb, sb2;
+        sa.init(pass ? g.A2 : gA, g.lda, g.M, m0, g.K, g.ag, nullptr, tid);
+        sb.init(pass ? g.B2 : gB, g.ldb, g.N, n0, g.K, BDM ? nullptr : g.bg, BDM ? g.bg : nullptr, tid);
+        if (kTwoB) sb2.init(g.B2, g.ldb, g.N, n0, g.K, BDM ? nullptr : g.bg, BDM ? g.bg : nullptr, tid);
         f32x4 ra[AHEAD][OA::PER], rb[NB][AHEAD][OB::PER];
-        // tile t of the depth into register set s; the lists of the tile after it follow
+        auto list = [&](int t, int s) {
+            sa.list(s, t * BK);
+            sb.list(s, t * BK);
+            if (kTwoB) sb2.list(s, t * BK);
+        };
+        // tile t of the depth into register set s, then the lists of the set's next tile: when those are used, the
+        // loads issued after them may still be in flight
         auto fetch = [&](int t, auto set) {
             constexpr int s = decltype(set)::value;
-            sa.fetch(ra[s], t * BK);
-            sb.fetch(rb[0][s], t * BK);
-            if (kTwoB) sb2.fetch(rb[NB - 1][s], t * BK);
-            sa.next_depth((t + 1) * BK);
-            sb.next_depth((t + 1) * BK);
-            if (kTwoB) sb2.next_depth((t + 1) * BK);
+            sa.fetch(ra[s], s, t * BK);
+            sb.fetch(rb[0][s], s, t * BK);
+            if (kTwoB) sb2.fetch(rb[NB - 1][s], s, t * BK);
+            list(t + AHEAD, s);
         };
         auto stash = [&](int t, auto set) {
             constexpr int s = decltype(set)::value;
@@ -243,37 +257,36 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(Dev g) {
                                 acc[b][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[b][j][e], fa[i][e], acc[b][i][j], 0, 0, 0);
             }
         };
-        // tile t is in LDS, t + 1 .. t + AHEAD in registers (set of tile t: t % AHEAD); tiles beyond the last are
-        // clamped loads that nothing uses
-        sa.next_depth(0);
-        sb.next_depth(0);
-        if (kTwoB) sb2.next_depth(0);
-        fetch(0, std::integral_constant<int, 0>{});
-        stash(0, std::integral_constant<int, 0>{});
-        if constexpr (AHEAD == 1) {
-            fetch(1, std::integral_constant<int, 0>{});
-        } else {
-            fetch(1, std::integral_constant<int, 1>{});
-            fetch(2, std::integral_constant<int, 2>{});
-            fetch(3, std::integral_constant<int, 0>{});
+        // tile t is in LDS, t + 1 .. t + AHEAD in registers (set of tile t: t % AHEAD).  Everything runs unconditionally:
+        // tiles beyond the last are clamped loads and zeros that no step computes on, and without branches the loads in
+        // flight are counted exactly.
+#pragma unroll
+        for (int s = 0; s < AHEAD; ++s) list(s, s);
+        typedef std::integral_constant<int, 0> Set0;
+        typedef std::integral_constant<int, 1 % AHEAD> Set1;
+        typedef std::integral_constant<int, 2 % AHEAD> Set2;
+        fetch(0, Set0{});
+        if constexpr (AHEAD == 3) {
+            fetch(1, Set1{});
+            fetch(2, Set2{});
         }
+        stash(0, Set0{});
+        fetch(AHEAD, Set0{});
         __syncthreads();
         auto step = [&](int t, auto set) { // `set`: register set of tile t + 1
-            if (t + 1 < steps) stash(t + 1, set);
+            stash(t + 1, set);
             fetch(t + 1 + AHEAD, set);
             compute(t);
             __syncthreads();
         };
         int t = 0;
-        if constexpr (AHEAD == 1) {
-            for (; t < steps; ++t) step(t, std::integral_constant<int, 0>{});
-        } else {
-            for (; t < steps; t += 3) {
-                step(t, std::integral_constant<int, 1>{});
-                if (t + 1 < steps) step(t + 1, std::integral_constant<int, 2>{});
-                if (t + 2 < steps) step(t + 2, std::integral_constant<int, 0>{});
-            }
+        for (; t + 3 <= steps; t += 3) {
+            step(t, Set1{});
+            step(t + 1, Set2{});
+            step(t + 2, Set0{});
         }
+        if (t < steps) step(t, Set1{});
+        if (t + 1 < steps) step(t + 1, Set2{});
     }
 
     // four consecutive columns n .. n + 3 of row m
@@ -354,7 +367,7 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(Dev g) {
     }
 }
 
-template <class C, int EPI, bool ADM, bool BDM>
+template <class C, int EPI, bool ADM, bool BDM, bool VEC>
 int launch(Dev g, const char* name, hipStream_t s) {
     constexpr int STAGE = Operand<C::BM, C::BK, ADM>::FLOATS + (EPI == EPI_SWIGLU_FWD ? 2 : 1) * Operand<C::BN, C::BK, BDM>::FLOATS;
     constexpr int LDS = 2 * STAGE * 4;
@@ -362,7 +375,7 @@ int launch(Dev g, const char* name, hipStream_t s) {
     g.tiles_m = (g.M + C::BM - 1) / C::BM, g.tiles_n = (g.N + C::BN - 1) / C::BN;
     const int64_t blocks = (int64_t)g.tiles_m * g.tiles_n * (g.nbatch > 0 ? g.nbatch : 1);
     if (blocks > 0x7FFFFFFF) return SDP_ERR_SHAPE;
-    auto kern = gemm_f32_kernel<C, EPI, ADM, BDM>;
+    auto kern = gemm_f32_kernel<C, EPI, ADM, BDM, VEC>;
     static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
     if (attr != hipSuccess) return SDP_ERR_HIP;
     ProfileScope ps(name, s);
@@ -373,16 +386,20 @@ int launch(Dev g, const char* name, hipStream_t s) {
 // Tile of a launch: the fewest matrix cycles on the busiest CU (rounds of tiles over 256 CUs x tile area), each tile
 // weighted by what its loop loses to staging and barriers.  With fewer 64-wide tiles than CUs the 32-wide ones win on
 // both counts (T = 256, p = 512, d = 256: 128 tiles whose waves each run a quarter of the depth, against 32).
-template <int EPI, bool ADM, bool BDM>
+template <int EPI, bool ADM, bool BDM, bool VEC>
 int choose(const Dev& g, const char* name, hipStream_t s) {
     auto cost = [&](int b, double weight) {
         const int64_t tiles = (int64_t)((g.M + b - 1) / b) * ((g.N + b - 1) / b) * (g.nbatch > 0 ? g.nbatch : 1);
         return (double)((tiles + 255) / 256) * b * b * weight;
     };
     const double c128 = cost(128, 1.0), c64 = cost(64, 1.1), c32 = cost(32, 1.3);
-    if (c32 < c64 && c32 < c128) return launch<Cfg<32, 32, 4>, EPI, ADM, BDM>(g, name, s);
-    if (c64 < c128) return launch<Cfg<64, 64, 1>, EPI, ADM, BDM>(g, name, s);
-    return launch<Cfg<128, 128, 1>, EPI, ADM, BDM>(g, name, s);
+    if (c32 < c64 && c32 < c128) return launch<Cfg<32, 32, 4>, EPI, ADM, BDM, VEC>(g, name, s);
+    if (c64 < c128) return launch<Cfg<64, 64, 1>, EPI, ADM, BDM, VEC>(g, name, s);
+    return launch<Cfg<128, 128, 1>, EPI, ADM, BDM, VEC>(g, name, s);
+}
+template <int EPI, bool ADM, bool BDM>
+int choose(bool vec, const Dev& g, const char* name, hipStream_t s) {
+    return vec ? choose<EPI, ADM, BDM, true>(g, name, s) : choose<EPI, ADM, BDM, false>(g, name, s);
 }
 
 } // namespace
@@ -405,17 +422,17 @@ int gemm_f32(const GemmDesc& d, hipStream_t s) {
         va = va && al(d.Ab[z]), vb = vb && al(d.Bb[z]), vo = vo && al(d.Cb[z]);
     }
     // along the contiguous axis: the depth for an operand stored by rows, M or N for a depth-major one
-    g.vec_a = va && d.lda % 4 == 0 && (d.a_km ? d.M : d.K) % 4 == 0 && !(d.a_km && d.a_gather);
-    g.vec_b = vb && d.ldb % 4 == 0 && (d.b_km ? d.N : d.K) % 4 == 0;
+    const bool vec = va && vb && d.lda % 4 == 0 && d.ldb % 4 == 0 && (d.a_km ? d.M : d.K) % 4 == 0 &&
+                     (d.b_km ? d.N : d.K) % 4 == 0 && !(d.a_km && d.a_gather);
     g.vec_out = vo && d.N % 4 == 0 && d.ldc % 4 == 0 && (!d.R || (al(d.R) && d.ldr % 4 == 0)) &&
                 (d.epilogue != EPI_SWIGLU_BWD || (al(d.Gin) && al(d.Uin) && d.ldg % 4 == 0));
     switch (d.epilogue) {
     case EPI_STORE:
-        if (d.a_km) return d.b_km ? choose<EPI_STORE, true, true>(g, d.name, s) : SDP_ERR_UNSUPPORTED;
-        return d.b_km ? choose<EPI_STORE, false, true>(g, d.name, s) : choose<EPI_STORE, false, false>(g, d.name, s);
-    case EPI_DUAL_ACC: return d.a_km || !d.b_km ? SDP_ERR_UNSUPPORTED : choose<EPI_DUAL_ACC, false, true>(g, d.name, s);
-    case EPI_SWIGLU_FWD: return d.a_km || d.b_km ? SDP_ERR_UNSUPPORTED : choose<EPI_SWIGLU_FWD, false, false>(g, d.name, s);
-    case EPI_SWIGLU_BWD: return d.a_km || d.b_km ? SDP_ERR_UNSUPPORTED : choose<EPI_SWIGLU_BWD, false, false>(g, d.name, s);
+        if (d.a_km) return d.b_km ? choose<EPI_STORE, true, true>(vec, g, d.name, s) : SDP_ERR_UNSUPPORTED;
+        return d.b_km ? choose<EPI_STORE, false, true>(vec, g, d.name, s) : choose<EPI_STORE, false, false>(vec, g, d.name, s);
+    case EPI_DUAL_ACC: return d.a_km || !d.b_km ? SDP_ERR_UNSUPPORTED : choose<EPI_DUAL_ACC, false, true>(vec, g, d.name, s);
+    case EPI_SWIGLU_FWD: return d.a_km || d.b_km ? SDP_ERR_UNSUPPORTED : choose<EPI_SWIGLU_FWD, false, false>(vec, g, d.name, s);
+    case EPI_SWIGLU_BWD: return d.a_km || d.b_km ? SDP_ERR_UNSUPPORTED : choose<EPI_SWIGLU_BWD, false, false>(vec, g, d.name, s);
     }
     return SDP_ERR_INVALID_ARG;
 }
