@@ -15,7 +15,7 @@
 // causal attention on 32x32x16 bf16 MFMA tiles for heads of 64, 96 or 128 columns (wider and narrower ones take the next
 // of these widths), with the running-maximum formulation of the softmax (logits in base 2), so that no T x T matrix is
 // stored.  Heads of 65 .. 128 used to run the plain core: one sequence of 1500 tokens, 4 of 8 heads of 128, forward and
-// backward of the block 20.0 ms then, 0.26 ms on the wide MFMA core.
+// backward of the block 20.0 ms then, 0.18 ms on the wide MFMA core.
 //
 // Accumulator convention.  v_mfma_f32_32x32x16 computes D[m][n] += sum_k A[m][k] B[k][n]; lane L supplies
 // A[L % 32][8 (L / 32) + e] and B[8 (L / 32) + e][L % 32], e = 0..7, and holds D[8 q + 4 (L / 32) + r][L % 32]
@@ -40,28 +40,29 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
 
-// Tuning knobs (compile time): waves per SIMD the forward and dQ kernels are register-allocated for, query blocks
-// per wave and waves per workgroup of the forward kernel.  Measured at 4 x 2048 tokens, 12 heads: 3 waves per
-// SIMD beat 2 (forward 86 -> 77 us) and 4 spill; 2 query blocks per wave spill and were slower.
-#ifndef SDP_ATTN_WPE_FWD
-#define SDP_ATTN_WPE_FWD 3
-#endif
-#ifndef SDP_ATTN_WPE_DQ
-#define SDP_ATTN_WPE_DQ 3
-#endif
-#ifndef SDP_ATTN_FWD_QF
-#define SDP_ATTN_FWD_QF 1
-#endif
-#ifndef SDP_ATTN_FWD_NW
-#define SDP_ATTN_FWD_NW 4
-#endif
-
 constexpr int HD = 64;              // narrowest width of the MFMA core
 // Widths of the core: HW = 64, 96 or 128 columns per head.  An LDS tile row holds HW bf16 + 16 bytes: consecutive rows
 // then start 4 (an odd multiple of 4) banks apart, so the 16 lanes that a ds_read_b128 serves together hit every bank once.
 constexpr int row_bytes(int hw) { return hw * 2 + 16; }
 constexpr float kSlack = 8.f;      // forward: how far a query's maximum may run ahead of its reference exponent
-constexpr int BQ = 128;             // rows (queries, or keys in the dK/dV kernel) per workgroup: 4 waves x 32
+constexpr int NW = 4;               // waves per workgroup
+
+// A workgroup's four waves share out the work in one of two ways (KW = waves along the walked axis):
+//   KW = 1: four blocks of 32 rows (queries, or keys in the dK/dV kernel), every wave walks all tiles of the other axis.
+//           The tiles are staged once for the workgroup.
+//   KW = 4: one block of 32 rows; wave w walks the 32-row tiles w, w + 4, ... of the other axis, which it stages for
+//           itself (no barrier in the loop), and the four partial results are added at the end through LDS.  Four times
+//           the workgroups with a quarter of the chain each, for four times the reads of the other axis.
+template <int KW>
+struct Split {
+    static_assert(KW == 1 || KW == NW, "all waves on one axis");
+    static constexpr int ROWS = KW == 1 ? 32 * NW : 32; // rows per workgroup
+};
+
+// Heads wider than 64 take the probabilities (and their gradients) into the second products as two bf16 terms, value =
+// hi + lo, i.e. with 16 bits of mantissa: the plain core that served them held these in fp32.  Heads up to 64 take them
+// as one bf16 term.
+constexpr bool two_terms(int hw) { return hw > HD; }
 
 struct CoreArgs {
     const uint16_t* qkv; // [T][ldq]: Q | K | V of the held heads, head i at columns i * hd of each part
@@ -96,6 +97,22 @@ __device__ inline bf16x8 pack_operand(const f32x16& a, int s) {
     const u32x4 v = {pack_bf16(a[8 * s], a[8 * s + 1]), pack_bf16(a[8 * s + 2], a[8 * s + 3]),
                      pack_bf16(a[8 * s + 4], a[8 * s + 5]), pack_bf16(a[8 * s + 6], a[8 * s + 7])};
     return __builtin_bit_cast(bf16x8, v);
+}
+
+// what pack_operand's rounding left out, as a second operand
+__device__ inline bf16x8 pack_rest(const f32x16& a, int s, bf16x8 hi) {
+    const u32x4 h = __builtin_bit_cast(u32x4, hi);
+    u32x4 v;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        v[i] = pack_bf16(a[8 * s + 2 * i] - __uint_as_float(h[i] << 16), a[8 * s + 2 * i + 1] - __uint_as_float(h[i] & 0xFFFF0000u));
+    return __builtin_bit_cast(bf16x8, v);
+}
+
+// orders this wave's LDS accesses around it: what one lane wrote another one reads, within the wave
+__device__ inline void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 
 // operand whose depth runs along a tile row: row `row` of the tile, depth 16 s + 8 lhi .. + 7
@@ -180,162 +197,235 @@ __device__ inline float other_half(float x) { return __shfl_xor(x, 32, 64); }
 // 2^x for x <= 0 (or -inf): the hardware instruction alone; results below the normal range may flush to zero
 __device__ inline float exp2_neg(float x) { return __builtin_amdgcn_exp2f(x); }
 
+// KW = 4: LDS of one wave, its two 32-row tiles and 64 statistics; after the loop its partial result, 32 rows of HW
+// floats (rows 16 bytes longer, so that both the writes by row and the reads along a row hit every bank), and the statistics.
+constexpr int wave_lds(int hw) { return 64 * row_bytes(hw) + 256; }
+constexpr int part_row(int hw) { return hw + 4; }
+static_assert(32 * part_row(HD) * 4 + 256 <= wave_lds(HD) && 32 * part_row(128) * 4 + 256 <= wave_lds(128), "fits the tiles");
+
+// accumulator tiles D[h][row] -> the wave's partial result
+template <int HW>
+__device__ inline void put_part(unsigned char* mine, const f32x16 (&acc)[HW / 32], int l32, int lhi) {
+    float* row = (float*)mine + l32 * part_row(HW);
+#pragma unroll
+    for (int j = 0; j < HW / 32; ++j)
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            *(f32x4*)(row + 32 * j + 8 * q + 4 * lhi) = f32x4{acc[j][4 * q], acc[j][4 * q + 1], acc[j][4 * q + 2], acc[j][4 * q + 3]};
+}
+
+// sum over the waves of f[w] x partial result, as bf16 rows of `out` (row0 + 0 .. 31, those below S); weights(row, f)
+// fills f.  Columns from hd on are left alone.
+template <int HW, class W>
+__device__ inline void store_parts(const unsigned char* lds, uint16_t* out, int64_t ld, int row0, int S, int hd, int tid, W weights) {
+#pragma unroll
+    for (int i = 0; i < HW / 32; ++i) {
+        const int e = tid + 256 * i, row = e / (HW / 4), c = e % (HW / 4) * 4;
+        float f[NW];
+        weights(row, f);
+        f32x4 v = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            const f32x4 x = *(const f32x4*)((const float*)(lds + w * wave_lds(HW)) + row * part_row(HW) + c);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) v[r] = __builtin_fmaf(x[r], f[w], v[r]);
+        }
+        if (row0 + row < S && (HW == HD || c < hd))
+            *(u32x2*)(out + (int64_t)(row0 + row) * ld + c) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+    }
+}
+
 // ---------------------------------------------------------------------------------------------------
-// Forward.  Workgroup = NW waves; wave w keeps QF blocks of 32 queries (q0 + 32 QF w ..) as register
-// operands and walks the key/value tiles of 64 keys up to the diagonal.  K and V tiles are double-buffered
-// in LDS (one barrier per tile): while tile t is used, tile t + 1 moves from registers into the other
-// buffer and tile t + 2 is fetched from memory.  Every K and V fragment read from LDS serves all QF query
-// blocks of the wave.
+// Forward.  A wave keeps a block of 32 queries as register operands and walks key/value tiles up to the diagonal.
+// KW = 1: tiles of 64 keys, double-buffered in LDS (one barrier per tile): while tile t is used, tile t + 1 moves from
+// registers into the other buffer and tile t + 2 is fetched from memory.  KW = 4: the wave's own tiles of 32 keys,
+// single-buffered; the next one is in flight in registers.
 // ---------------------------------------------------------------------------------------------------
-template <int HW, int QF, int NW>
-__device__ inline void attn_fwd_block(const CoreArgs& a, const int q0, const int head, const int b,
-                                      unsigned char (&sK)[2][64 * row_bytes(HW)], unsigned char (&sV)[2][64 * row_bytes(HW)]) {
+template <int HW, int KW>
+constexpr int fwd_lds() { return KW == 1 ? 4 * 64 * row_bytes(HW) : NW * wave_lds(HW); }
+
+template <int HW, int KW>
+__device__ inline void attn_fwd_block(const CoreArgs& a, const int q0, const int head, const int b, unsigned char* lds) {
     constexpr int KS = HW / 16, JB = HW / 32; // depth steps of a logit, 32-column blocks of the output
+    constexpr int TR = KW == 1 ? 64 : 32;     // keys per tile
+    constexpr int TILE = TR * row_bytes(HW);
     const int hd = HW == HD ? HD : a.hd;
-    constexpr int ROWS = 32 * QF * NW; // queries per block
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int S = a.S;
     const uint16_t* gQ = a.qkv + (int64_t)b * S * a.ldq + head * hd;
     const uint16_t* gK = gQ + a.ph * hd;
     const uint16_t* gV = gK + a.ph * hd;
-    const int qrow0 = q0 + 32 * QF * wave; // first query of the wave
-    bf16x8 qf[QF][KS];
-#pragma unroll
-    for (int f = 0; f < QF; ++f) {
-        const int qrow = qrow0 + 32 * f + l32;
-        load_row_operand<HW>(gQ, a.ldq, qrow < S ? qrow : S - 1, hd, lhi, qf[f]);
-    }
+    const int qrow0 = KW == 1 ? q0 + 32 * wave : q0, qrow = qrow0 + l32;
+    bf16x8 qf[KS];
+    load_row_operand<HW>(gQ, a.ldq, qrow < S ? qrow : S - 1, hd, lhi, qf);
 
-    const int kv_end = q0 + ROWS < S ? q0 + ROWS : S;
-    const int ntiles = (kv_end + 63) / 64;
-    f32x16 acc_o[QF][JB];
-    float m[QF], lsum[QF];
+    // tile t holds the keys first + step t ..
+    const int first = KW == 1 ? 0 : TR * wave, step = TR * KW;
+    const int kv_end = q0 + Split<KW>::ROWS < S ? q0 + Split<KW>::ROWS : S;
+    const int ntiles = kv_end > first ? (kv_end - first + step - 1) / step : 0;
+    f32x16 acc[JB];
+    // KW = 4: a wave's first tile may hold no key of some queries; the reference then starts from the lowest finite value
+    float m = KW == 1 ? -INFINITY : -3.402823466e38f, lsum = 0.f;
 #pragma unroll
-    for (int f = 0; f < QF; ++f) {
-        m[f] = -INFINITY, lsum[f] = 0.f;
+    for (int j = 0; j < JB; ++j)
 #pragma unroll
-        for (int j = 0; j < JB; ++j)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) acc_o[f][j][e] = 0.f;
-    }
+        for (int e = 0; e < 16; ++e) acc[j][e] = 0.f;
 
-    TileMover<NW, HW> pk, pv;
+    TileMover<KW == 1 ? NW : 1, HW, TR> pk, pv;
+    const int mt = KW == 1 ? tid : lane; // the mover's thread
+    unsigned char* const mine = lds + wave * wave_lds(HW);
     const uint32_t ld = (uint32_t)a.ldq;
-    pk.fetch(gK, ld, 0, S - 1, hd, tid);
-    pv.fetch(gV, ld, 0, S - 1, hd, tid);
-    pk.stash(sK[0], hd, tid);
-    pv.stash(sV[0], hd, tid);
+    pk.fetch(gK, ld, first, S - 1, hd, mt);
+    pv.fetch(gV, ld, first, S - 1, hd, mt);
     // fetches and stashes run unconditionally (rows are clamped, and a tile beyond the last one is never
     // read): no branch, hence no register copies, around the loop-carried pieces
-    pk.fetch(gK, ld, 64, S - 1, hd, tid);
-    pv.fetch(gV, ld, 64, S - 1, hd, tid);
-    __syncthreads();
+    if constexpr (KW == 1) {
+        pk.stash(lds, hd, mt);
+        pv.stash(lds + 2 * TILE, hd, mt);
+        pk.fetch(gK, ld, step, S - 1, hd, mt);
+        pv.fetch(gV, ld, step, S - 1, hd, mt);
+        __syncthreads();
+    }
     for (int t = 0; t < ntiles; ++t) {
-        const unsigned char* tK = sK[t & 1];
-        const unsigned char* tV = sV[t & 1];
-        // the other buffer was last read before the barrier that ended step t - 1
-        pk.stash(sK[(t + 1) & 1], hd, tid);
-        pv.stash(sV[(t + 1) & 1], hd, tid);
-        pk.fetch(gK, ld, 64 * (t + 2), S - 1, hd, tid);
-        pv.fetch(gV, ld, 64 * (t + 2), S - 1, hd, tid);
-        const int kv0 = 64 * t;
-        if (kv0 <= qrow0 + 32 * QF - 1) { // wave-uniform: otherwise every key lies after the wave's queries
-            // logits, transposed: sc[f][tb] = D[key 32 tb + ..][query of block f]
-            f32x16 sc[QF][2];
+        const unsigned char *tK, *tV;
+        if constexpr (KW == 1) {
+            tK = lds + (t & 1) * TILE, tV = tK + 2 * TILE;
+            // the other buffer was last read before the barrier that ended step t - 1
+            pk.stash(lds + ((t + 1) & 1) * TILE, hd, mt);
+            pv.stash(lds + (2 + ((t + 1) & 1)) * TILE, hd, mt);
+            pk.fetch(gK, ld, step * (t + 2), S - 1, hd, mt);
+            pv.fetch(gV, ld, step * (t + 2), S - 1, hd, mt);
+        } else {
+            tK = mine, tV = mine + TILE;
+            pk.stash(mine, hd, mt);
+            pv.stash(mine + TILE, hd, mt);
+            pk.fetch(gK, ld, first + step * (t + 1), S - 1, hd, mt);
+            pv.fetch(gV, ld, first + step * (t + 1), S - 1, hd, mt);
+            wave_sync();
+        }
+        const int kv0 = first + step * t;
+        if (kv0 <= qrow0 + 31) { // wave-uniform: otherwise every key lies after the wave's queries
+            // logits, transposed: sc[tb] = D[key 32 tb + ..][query]
+            f32x16 sc[TR / 32];
 #pragma unroll
-            for (int f = 0; f < QF; ++f)
+            for (int tb = 0; tb < TR / 32; ++tb)
 #pragma unroll
-                for (int tb = 0; tb < 2; ++tb)
+                for (int e = 0; e < 16; ++e) sc[tb][e] = 0.f;
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) sc[f][tb][e] = 0.f;
+            for (int tb = 0; tb < TR / 32; ++tb)
 #pragma unroll
-            for (int tb = 0; tb < 2; ++tb)
+                for (int s = 0; s < KS; ++s)
+                    sc[tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<HW>(tK, 32 * tb + l32, s, lhi), qf[s], sc[tb], 0, 0, 0);
+            if (kv0 + TR - 1 > qrow0 || kv0 + TR > S) { // wave-uniform: some logits of this tile are masked
 #pragma unroll
-                for (int s = 0; s < KS; ++s) {
-                    const bf16x8 kfr = frag_rows<HW>(tK, 32 * tb + l32, s, lhi);
+                for (int tb = 0; tb < TR / 32; ++tb)
 #pragma unroll
-                    for (int f = 0; f < QF; ++f)
-                        sc[f][tb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr, qf[f][s], sc[f][tb], 0, 0, 0);
-                }
-            if (kv0 + 63 > qrow0 || kv0 + 64 > S) { // wave-uniform: some logits of this tile are masked
-#pragma unroll
-                for (int f = 0; f < QF; ++f) {
-                    const int qrow = qrow0 + 32 * f + l32;
-#pragma unroll
-                    for (int tb = 0; tb < 2; ++tb)
-#pragma unroll
-                        for (int e = 0; e < 16; ++e) {
-                            const int key = kv0 + 32 * tb + 8 * (e >> 2) + 4 * lhi + (e & 3);
-                            if (key > qrow || key >= S) sc[f][tb][e] = -INFINITY;
-                        }
-                }
+                    for (int e = 0; e < 16; ++e) {
+                        const int key = kv0 + 32 * tb + 8 * (e >> 2) + 4 * lhi + (e & 3);
+                        if (key > qrow || key >= S) sc[tb][e] = -INFINITY;
+                    }
             }
-            bf16x8 pf[QF][2][2]; // probabilities as operands: [query block][key block][depth half]
+            float mx = -INFINITY;
 #pragma unroll
-            for (int f = 0; f < QF; ++f) {
-                float mx = -INFINITY;
+            for (int tb = 0; tb < TR / 32; ++tb)
 #pragma unroll
-                for (int tb = 0; tb < 2; ++tb)
+                for (int e = 0; e < 16; ++e) mx = fmaxf(mx, sc[tb][e]);
+            mx = fmaxf(mx, other_half(mx));
+            // m is the reference the exponents are taken against, in units of the scaled base-2 logits (the
+            // scale rides in the multiply-add).  It follows the running maximum lazily: only when a query's
+            // maximum has grown by more than kSlack is the reference moved and the accumulators rescaled, so
+            // probabilities stay below 2^kSlack and the multiplies of the rescale run on few tiles (with KW = 1 the
+            // first one always: it holds key 0, which no query masks, so m is finite from then on).
+            const float m_cand = mx * a.scale2;
+            if (__builtin_amdgcn_ballot_w64(m_cand > m + kSlack) != 0) { // wave-uniform
+                const float m_new = m_cand > m + kSlack ? m_cand : m;
+                const float alpha = exp2_neg(m - m_new);
+                m = m_new;
+                lsum *= alpha;
 #pragma unroll
-                    for (int e = 0; e < 16; ++e) mx = fmaxf(mx, sc[f][tb][e]);
-                mx = fmaxf(mx, other_half(mx));
-                // m is the reference the exponents are taken against, in units of the scaled base-2 logits (the
-                // scale rides in the multiply-add).  It follows the running maximum lazily: only when a query's
-                // maximum has grown by more than kSlack is the reference moved and the accumulators rescaled, so
-                // probabilities stay below 2^kSlack and the 32 multiplies of the rescale run on few tiles (the
-                // first one always: it holds key 0, which no query masks, so m is finite from then on).
-                const float m_cand = mx * a.scale2;
-                if (__builtin_amdgcn_ballot_w64(m_cand > m[f] + kSlack) != 0) { // wave-uniform
-                    const float m_new = m_cand > m[f] + kSlack ? m_cand : m[f];
-                    const float alpha = exp2_neg(m[f] - m_new);
-                    m[f] = m_new;
-                    lsum[f] *= alpha;
+                for (int j = 0; j < JB; ++j)
 #pragma unroll
-                    for (int j = 0; j < JB; ++j)
+                    for (int e = 0; e < 16; ++e) acc[j][e] *= alpha;
+            }
+            // One term: the sum runs over the rounded probabilities, the ones the second product sees, two per
+            // instruction.  Two terms: over the probabilities themselves.
+            bf16x8 pf[TR / 32][2]; // probabilities as operands: [key block][depth half]
+            float ps = 0.f;
 #pragma unroll
-                        for (int e = 0; e < 16; ++e) acc_o[f][j][e] *= alpha;
-                }
-                // the sum runs over the rounded probabilities, the ones the second product sees, two per instruction
-                float ps = 0.f;
+            for (int tb = 0; tb < TR / 32; ++tb)
 #pragma unroll
-                for (int tb = 0; tb < 2; ++tb)
+                for (int h = 0; h < 2; ++h) {
+                    u32x4 w;
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        u32x4 w;
-#pragma unroll
-                        for (int i = 0; i < 4; ++i) {
-                            const float p0 = exp2_neg(__builtin_fmaf(sc[f][tb][8 * h + 2 * i], a.scale2, -m[f]));
-                            const float p1 = exp2_neg(__builtin_fmaf(sc[f][tb][8 * h + 2 * i + 1], a.scale2, -m[f]));
-                            w[i] = pack_bf16(p0, p1);
+                    for (int i = 0; i < 4; ++i) {
+                        const float p0 = exp2_neg(__builtin_fmaf(sc[tb][8 * h + 2 * i], a.scale2, -m));
+                        const float p1 = exp2_neg(__builtin_fmaf(sc[tb][8 * h + 2 * i + 1], a.scale2, -m));
+                        w[i] = pack_bf16(p0, p1);
+                        if constexpr (two_terms(HW)) {
+                            sc[tb][8 * h + 2 * i] = p0, sc[tb][8 * h + 2 * i + 1] = p1;
+                            ps += p0 + p1;
+                        } else {
                             ps = pair_sum(w[i], ps);
                         }
-                        pf[f][tb][h] = __builtin_bit_cast(bf16x8, w);
                     }
-                lsum[f] += ps;
-            }
+                    pf[tb][h] = __builtin_bit_cast(bf16x8, w);
+                }
+            lsum += ps;
             // O^T[h][query] += sum_key V[key][h] P[query][key]
 #pragma unroll
-            for (int tb = 0; tb < 2; ++tb)
+            for (int tb = 0; tb < TR / 32; ++tb)
 #pragma unroll
-                for (int s = 0; s < 2; ++s)
+                for (int s = 0; s < 2; ++s) {
+                    bf16x8 rest;
+                    if constexpr (two_terms(HW)) rest = pack_rest(sc[tb], s, pf[tb][s]);
 #pragma unroll
                     for (int j = 0; j < JB; ++j) {
                         const bf16x8 vfr = frag_cols<HW>(tV, 32 * tb + 16 * s, 32 * j, lane);
-#pragma unroll
-                        for (int f = 0; f < QF; ++f)
-                            acc_o[f][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfr, pf[f][tb][s], acc_o[f][j], 0, 0, 0);
+                        acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfr, pf[tb][s], acc[j], 0, 0, 0);
+                        if constexpr (two_terms(HW)) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vfr, rest, acc[j], 0, 0, 0);
                     }
+                }
         }
-        __syncthreads(); // tile t is released, tile t + 1 is in place
+        // tile t is released (KW = 1: and tile t + 1 is in place)
+        if constexpr (KW == 1) __syncthreads(); else wave_sync();
     }
-#pragma unroll
-    for (int f = 0; f < QF; ++f) {
-        const int qrow = qrow0 + 32 * f + l32;
-        const float l = lsum[f] + other_half(lsum[f]);
+    const float l = lsum + other_half(lsum);
+    uint16_t* const out = a.o_out + (int64_t)b * S * a.ldo + head * hd;
+    float* const lse = a.lse + ((int64_t)b * a.ph + head) * S;
+    if constexpr (KW == 1) {
         if (qrow < S) {
-            store_rows<HW>(a.o_out + ((int64_t)b * S + qrow) * a.ldo + head * hd, acc_o[f], 1.f / l, hd, lhi);
-            if (lhi == 0) a.lse[((int64_t)b * a.ph + head) * S + qrow] = m[f] + log2f(l);
+            store_rows<HW>(out + (int64_t)qrow * a.ldo, acc, 1.f / l, hd, lhi);
+            if (lhi == 0) lse[qrow] = m + log2f(l);
+        }
+    } else {
+        put_part<HW>(mine, acc, l32, lhi);
+        constexpr int STAT = 32 * part_row(HW) * 4; // [32] references, [32] sums
+        ((float*)(mine + STAT))[lane] = lhi == 0 ? m : l;
+        __syncthreads();
+        store_parts<HW>(lds, out, a.ldo, q0, S, hd, tid, [&](int row, float (&f)[NW]) {
+            float top = -INFINITY, sum = 0.f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) top = fmaxf(top, ((const float*)(lds + w * wave_lds(HW) + STAT))[row]);
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const float* st = (const float*)(lds + w * wave_lds(HW) + STAT);
+                f[w] = exp2_neg(st[row] - top);
+                sum = __builtin_fmaf(f[w], st[32 + row], sum);
+            }
+#pragma unroll
+            for (int w = 0; w < NW; ++w) f[w] /= sum;
+        });
+        if (tid < 32 && q0 + tid < S) {
+            float top = -INFINITY, sum = 0.f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) top = fmaxf(top, ((const float*)(lds + w * wave_lds(HW) + STAT))[tid]);
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const float* st = (const float*)(lds + w * wave_lds(HW) + STAT);
+                sum = __builtin_fmaf(exp2_neg(st[tid] - top), st[32 + tid], sum);
+            }
+            lse[q0 + tid] = top + log2f(sum);
         }
     }
 }
@@ -357,14 +447,19 @@ __device__ inline void causal_item(int L, int nitems, int nbh, int nblocks, int 
     head = bh % ph, b = bh / ph;
 }
 
-template <int HW, int QF, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(HW == HD ? SDP_ATTN_WPE_FWD : 2, HW == HD ? SDP_ATTN_WPE_FWD : 2)))
+// waves per SIMD the registers are allotted for.  KW = 1, heads of 64: 3 beat 2 (86 -> 77 us at 4 x 2048 tokens, 12 heads)
+// and 4 spill.  KW = 4 has a workgroup per CU or less, and the wide heads then take the registers of one or two waves.
+constexpr int waves_fwd(int hw, int kw) { return kw == 1 ? (hw == HD ? 3 : 2) : 2; }
+constexpr int waves_dq(int hw, int kw) { return kw == 1 ? (hw == HD ? 3 : 2) : (hw == HD ? 2 : 1); }
+constexpr int waves_dkv(int hw, int kw) { return kw == 1 || hw == HD ? 2 : 1; }
+
+template <int HW, int KW>
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(waves_fwd(HW, KW), waves_fwd(HW, KW))))
 void attn_fwd_kernel(CoreArgs a, int nblocks, int nbh) {
-    __shared__ __attribute__((aligned(16))) unsigned char sK[2][64 * row_bytes(HW)];
-    __shared__ __attribute__((aligned(16))) unsigned char sV[2][64 * row_bytes(HW)];
+    __shared__ __attribute__((aligned(16))) unsigned char lds[fwd_lds<HW, KW>()];
     int blk, head, b;
     causal_item(blockIdx.x, gridDim.x, nbh, nblocks, a.ph, blk, head, b);
-    attn_fwd_block<HW, QF, NW>(a, blk * 32 * QF * NW, head, b, sK, sV);
+    attn_fwd_block<HW, KW>(a, blk * Split<KW>::ROWS, head, b, lds);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -372,10 +467,13 @@ void attn_fwd_kernel(CoreArgs a, int nblocks, int nbh) {
 // register operands; P is recomputed from the stored log-sum-exp.
 //   dP[q][k] = dO[q] . V[k];  dZ = P (dP - delta[q]);  dQ[q] = scale sum_k dZ[q][k] K[k]
 // ---------------------------------------------------------------------------------------------------
-template <int HW>
-__device__ inline void attn_bwd_dq_block(const CoreArgs& a, const int q0, const int head, const int b,
-                                         unsigned char (&sK)[64 * row_bytes(HW)], unsigned char (&sV)[64 * row_bytes(HW)]) {
+template <int HW, int KW>
+constexpr int dq_lds() { return KW == 1 ? 2 * 64 * row_bytes(HW) : NW * wave_lds(HW); }
+
+template <int HW, int KW>
+__device__ inline void attn_bwd_dq_block(const CoreArgs& a, const int q0, const int head, const int b, unsigned char* lds) {
     constexpr int KS = HW / 16, JB = HW / 32;
+    constexpr int TR = KW == 1 ? 64 : 32; // keys per tile
     const int hd = HW == HD ? HD : a.hd;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -383,7 +481,7 @@ __device__ inline void attn_bwd_dq_block(const CoreArgs& a, const int q0, const 
     const uint16_t* gQ = a.qkv + (int64_t)b * S * a.ldq + head * hd;
     const uint16_t* gK = gQ + a.ph * hd;
     const uint16_t* gV = gK + a.ph * hd;
-    const int qrow0 = q0 + 32 * wave, qrow = qrow0 + l32;
+    const int qrow0 = KW == 1 ? q0 + 32 * wave : q0, qrow = qrow0 + l32;
     const int qc = qrow < S ? qrow : S - 1;
     bf16x8 qf[KS], dof[KS];
     load_row_operand<HW>(gQ, a.ldq, qc, hd, lhi, qf);
@@ -400,33 +498,37 @@ __device__ inline void attn_bwd_dq_block(const CoreArgs& a, const int q0, const 
         delta += other_half(delta);
     }
     const int64_t stat = ((int64_t)b * a.ph + head) * S;
-    if (qrow < S && lhi == 0) a.delta[stat + qrow] = delta;
+    if (qrow < S && lhi == 0 && (KW == 1 || wave == 0)) a.delta[stat + qrow] = delta;
     const float L2 = a.lse[stat + qc];
 
-    const int kv_end = q0 + BQ < S ? q0 + BQ : S;
-    const int ntiles = (kv_end + 63) / 64;
+    const int first = KW == 1 ? 0 : TR * wave, step = TR * KW;
+    const int kv_end = q0 + Split<KW>::ROWS < S ? q0 + Split<KW>::ROWS : S;
+    const int ntiles = kv_end > first ? (kv_end - first + step - 1) / step : 0;
     f32x16 acc[JB];
 #pragma unroll
     for (int j = 0; j < JB; ++j)
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc[j][e] = 0.f;
 
-    TileMover<4, HW> pk, pv;
+    TileMover<KW == 1 ? NW : 1, HW, TR> pk, pv;
+    const int mt = KW == 1 ? tid : lane;
+    unsigned char* const sK = KW == 1 ? lds : lds + wave * wave_lds(HW);
+    unsigned char* const sV = sK + TR * row_bytes(HW);
     const uint32_t ld = (uint32_t)a.ldq;
-    pk.fetch(gK, ld, 0, S - 1, hd, tid);
-    pv.fetch(gV, ld, 0, S - 1, hd, tid);
+    pk.fetch(gK, ld, first, S - 1, hd, mt);
+    pv.fetch(gV, ld, first, S - 1, hd, mt);
     for (int t = 0; t < ntiles; ++t) {
-        __syncthreads();
-        pk.stash(sK, hd, tid);
-        pv.stash(sV, hd, tid);
-        __syncthreads();
-        pk.fetch(gK, ld, 64 * (t + 1), S - 1, hd, tid); // unconditional: rows are clamped
-        pv.fetch(gV, ld, 64 * (t + 1), S - 1, hd, tid);
-        const int kv0 = 64 * t;
+        if constexpr (KW == 1) __syncthreads(); else wave_sync();
+        pk.stash(sK, hd, mt);
+        pv.stash(sV, hd, mt);
+        if constexpr (KW == 1) __syncthreads(); else wave_sync();
+        pk.fetch(gK, ld, first + step * (t + 1), S - 1, hd, mt); // unconditional: rows are clamped
+        pv.fetch(gV, ld, first + step * (t + 1), S - 1, hd, mt);
+        const int kv0 = first + step * t;
         if (kv0 > qrow0 + 31) continue;
-        const bool edge = kv0 + 63 > qrow0 || kv0 + 64 > S;
+        const bool edge = kv0 + TR - 1 > qrow0 || kv0 + TR > S;
 #pragma unroll
-        for (int tb = 0; tb < 2; ++tb) {
+        for (int tb = 0; tb < TR / 32; ++tb) {
             f32x16 sc, dp;
 #pragma unroll
             for (int e = 0; e < 16; ++e) sc[e] = 0.f, dp[e] = 0.f;
@@ -448,49 +550,62 @@ __device__ inline void attn_bwd_dq_block(const CoreArgs& a, const int q0, const 
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
                 const bf16x8 zf = pack_operand(sc, s);
+                bf16x8 rest;
+                if constexpr (two_terms(HW)) rest = pack_rest(sc, s, zf);
 #pragma unroll
-                for (int j = 0; j < JB; ++j)
-                    acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols<HW>(sK, 32 * tb + 16 * s, 32 * j, lane), zf, acc[j], 0, 0, 0);
+                for (int j = 0; j < JB; ++j) {
+                    const bf16x8 kfr = frag_cols<HW>(sK, 32 * tb + 16 * s, 32 * j, lane);
+                    acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr, zf, acc[j], 0, 0, 0);
+                    if constexpr (two_terms(HW)) acc[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kfr, rest, acc[j], 0, 0, 0);
+                }
             }
         }
     }
-    if (qrow < S) store_rows<HW>(a.dqkv + ((int64_t)b * S + qrow) * a.ldq + head * hd, acc, a.scale, hd, lhi);
+    if constexpr (KW == 1) {
+        if (qrow < S) store_rows<HW>(a.dqkv + ((int64_t)b * S + qrow) * a.ldq + head * hd, acc, a.scale, hd, lhi);
+    } else {
+        wave_sync();
+        put_part<HW>(sK, acc, l32, lhi);
+        __syncthreads();
+        store_parts<HW>(lds, a.dqkv + (int64_t)b * S * a.ldq + head * hd, a.ldq, q0, S, hd, tid, [&](int, float (&f)[NW]) {
+#pragma unroll
+            for (int w = 0; w < NW; ++w) f[w] = a.scale;
+        });
+    }
 }
 
-template <int HW>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(HW == HD ? SDP_ATTN_WPE_DQ : 2, HW == HD ? SDP_ATTN_WPE_DQ : 2)))
+template <int HW, int KW>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_dq(HW, KW), waves_dq(HW, KW))))
 void attn_bwd_dq_kernel(CoreArgs a, int nblocks, int nbh) {
-    __shared__ __attribute__((aligned(16))) unsigned char sK[64 * row_bytes(HW)];
-    __shared__ __attribute__((aligned(16))) unsigned char sV[64 * row_bytes(HW)];
+    __shared__ __attribute__((aligned(16))) unsigned char lds[dq_lds<HW, KW>()];
     int blk, head, b;
     causal_item(blockIdx.x, gridDim.x, nbh, nblocks, a.ph, blk, head, b);
-    attn_bwd_dq_block<HW>(a, blk * BQ, head, b, sK, sV);
+    attn_bwd_dq_block<HW, KW>(a, blk * Split<KW>::ROWS, head, b, lds);
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Backward, dK and dV.  Workgroup = 128 keys of one (sequence, head); wave w keeps keys k0 + 32 w .. + 31
-// (K and V rows) as register operands and walks the query tiles from the diagonal to the end of the
-// sequence; Q, dO and the per-query statistics of a tile of 64 queries are staged in LDS.
+// Backward, dK and dV.  A wave keeps 32 keys of one (sequence, head) (K and V rows) as register operands
+// and walks query tiles from the diagonal to the end of the sequence; Q, dO and the per-query statistics of a tile
+// are staged in LDS.
 //   dV[k] = sum_q P[q][k] dO[q];   dK[k] = scale sum_q dZ[q][k] Q[q]
 // ---------------------------------------------------------------------------------------------------
 // At HW = 128 a wave's accumulators (128 registers), K rows (32), one 32 x 32 block of logits and of logit gradients
 // (32) leave no room for its V rows (32) and the pieces of 64 staged queries (32) under the 256 registers of two waves
 // per SIMD: the workgroup's V rows then stay in LDS and are read from there per block, and a tile has 32 queries.  At
-// HW = 96 the shorter tile is enough.
-template <int HW>
+// HW = 96 the shorter tile is enough.  (KW = 4 runs one wave per SIMD there: 512 registers, all operands kept.)
+template <int HW, int KW>
 struct DkvShape {
-    static constexpr bool kVInLds = HW == 128;
-    static constexpr int QT = HW == HD ? 64 : 32; // queries per tile
-    static constexpr int V_BYTES = kVInLds ? BQ * row_bytes(HW) : 16;
+    static constexpr bool kVInLds = HW == 128 && KW == 1;
+    static constexpr int QT = HW == HD && KW == 1 ? 64 : 32; // queries per tile
+    static constexpr int V_BYTES = kVInLds ? 32 * NW * row_bytes(HW) : 0;
+    static constexpr int LDS = KW == 1 ? 2 * QT * row_bytes(HW) + 2 * QT * 4 + V_BYTES : NW * wave_lds(HW);
 };
 
-template <int HW>
-__device__ inline void attn_bwd_dkv_block(const CoreArgs& a, const int k0, const int head, const int b,
-                                          unsigned char (&sQ)[DkvShape<HW>::QT * row_bytes(HW)],
-                                          unsigned char (&sO)[DkvShape<HW>::QT * row_bytes(HW)], float (&sL)[DkvShape<HW>::QT],
-                                          float (&sD)[DkvShape<HW>::QT], unsigned char (&sV)[DkvShape<HW>::V_BYTES]) {
-    constexpr int KS = HW / 16, JB = HW / 32, QT = DkvShape<HW>::QT;
-    constexpr bool kVInLds = DkvShape<HW>::kVInLds;
+template <int HW, int KW>
+__device__ inline void attn_bwd_dkv_block(const CoreArgs& a, const int k0, const int head, const int b, unsigned char* lds) {
+    using Shape = DkvShape<HW, KW>;
+    constexpr int KS = HW / 16, JB = HW / 32, QT = Shape::QT;
+    constexpr bool kVInLds = Shape::kVInLds;
     const int hd = HW == HD ? HD : a.hd;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -500,12 +615,17 @@ __device__ inline void attn_bwd_dkv_block(const CoreArgs& a, const int k0, const
     const uint16_t* gV = gK + a.ph * hd;
     const uint16_t* gO = a.dO + (int64_t)b * S * a.ldo + head * hd;
     const int64_t stat = ((int64_t)b * a.ph + head) * S;
-    const int krow0 = k0 + 32 * wave, krow = krow0 + l32;
+    const int krow0 = KW == 1 ? k0 + 32 * wave : k0, krow = krow0 + l32;
     const int kc = krow < S ? krow : S - 1;
+    unsigned char* const sQ = KW == 1 ? lds : lds + wave * wave_lds(HW);
+    unsigned char* const sO = sQ + QT * row_bytes(HW);
+    float* const sL = (float*)(sO + QT * row_bytes(HW)); // log-sum-exp of the tile's queries, then delta
+    float* const sD = sL + QT;
+    unsigned char* const sV = (unsigned char*)(sD + QT);
     bf16x8 kf[KS], vf[kVInLds ? 1 : KS];
     load_row_operand<HW>(gK, a.ldq, kc, hd, lhi, kf);
     if constexpr (kVInLds) {
-        TileMover<4, HW, BQ> mv;
+        TileMover<NW, HW, 32 * NW> mv;
         mv.fetch(gV, (uint32_t)a.ldq, k0, S - 1, hd, tid);
         mv.stash(sV, hd, tid); // read after the barriers of the first tile
     } else {
@@ -518,28 +638,30 @@ __device__ inline void attn_bwd_dkv_block(const CoreArgs& a, const int k0, const
 #pragma unroll
         for (int e = 0; e < 16; ++e) acc_k[j][e] = 0.f, acc_v[j][e] = 0.f;
 
-    const int t0 = k0 / QT, t1 = (S + QT - 1) / QT; // query tiles [t0, t1); t0 < t1 because k0 < S
-    TileMover<4, HW, QT> pq, po;
+    // tile t holds the queries QT (t0 + KW t) ..; t0 lies at the diagonal, which lies inside the sequence (k0 < S)
+    const int t0 = k0 / QT + (KW == 1 ? 0 : wave), tend = (S + QT - 1) / QT;
+    const int ntiles = tend > t0 ? (tend - t0 + KW - 1) / KW : 0;
+    TileMover<KW == 1 ? NW : 1, HW, QT> pq, po;
+    const int mt = KW == 1 ? tid : lane;
     const uint32_t ldq32 = (uint32_t)a.ldq, ldo32 = (uint32_t)a.ldo;
     // per-query statistics of a tile: threads 0 .. QT - 1 carry the log-sum-exp, QT .. 2 QT - 1 delta
-    const float* gstat = (tid < QT ? a.lse : a.delta) + stat;
-    const int sq = tid % QT;
-    float pstat;
-    pq.fetch(gQ, ldq32, QT * t0, S - 1, hd, tid);
-    po.fetch(gO, ldo32, QT * t0, S - 1, hd, tid);
-    pstat = gstat[QT * t0 + sq < S ? QT * t0 + sq : S - 1];
-    for (int t = t0; t < t1; ++t) {
-        __syncthreads();
-        pq.stash(sQ, hd, tid);
-        po.stash(sO, hd, tid);
-        if (tid < QT) sL[tid] = pstat;
-        else if (tid < 2 * QT) sD[tid - QT] = pstat;
-        __syncthreads();
+    const float* gstat = (mt < QT ? a.lse : a.delta) + stat;
+    const int sq = mt % QT;
+    auto stat_of = [&](int q) { return gstat[q < S ? q : S - 1]; };
+    pq.fetch(gQ, ldq32, QT * t0, S - 1, hd, mt);
+    po.fetch(gO, ldo32, QT * t0, S - 1, hd, mt);
+    float pstat = stat_of(QT * t0 + sq);
+    for (int t = 0; t < ntiles; ++t) {
+        if constexpr (KW == 1) __syncthreads(); else wave_sync();
+        pq.stash(sQ, hd, mt);
+        po.stash(sO, hd, mt);
+        if (mt < 2 * QT) sL[mt] = pstat;
+        if constexpr (KW == 1) __syncthreads(); else wave_sync();
         // the next tile, unconditionally: rows are clamped
-        pq.fetch(gQ, ldq32, QT * (t + 1), S - 1, hd, tid);
-        po.fetch(gO, ldo32, QT * (t + 1), S - 1, hd, tid);
-        pstat = gstat[QT * (t + 1) + sq < S ? QT * (t + 1) + sq : S - 1];
-        const int qt0 = QT * t;
+        const int qt0 = QT * (t0 + KW * t), next = qt0 + QT * KW;
+        pq.fetch(gQ, ldq32, next, S - 1, hd, mt);
+        po.fetch(gO, ldo32, next, S - 1, hd, mt);
+        pstat = stat_of(next + sq);
         if (qt0 + QT - 1 < krow0) continue; // wave-uniform: every query of the tile lies before the wave's keys
         const bool edge = qt0 < krow0 + 31 || qt0 + QT > S;
 #pragma unroll
@@ -579,32 +701,79 @@ __device__ inline void attn_bwd_dkv_block(const CoreArgs& a, const int k0, const
 #pragma unroll
             for (int s = 0; s < 2; ++s) {
                 const bf16x8 pf = pack_operand(sc, s), zf = pack_operand(dp, s);
+                bf16x8 pr, zr;
+                if constexpr (two_terms(HW)) pr = pack_rest(sc, s, pf), zr = pack_rest(dp, s, zf);
 #pragma unroll
                 for (int j = 0; j < JB; ++j) {
-                    acc_v[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols<HW>(sO, 32 * tb + 16 * s, 32 * j, lane), pf, acc_v[j], 0, 0, 0);
-                    acc_k[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_cols<HW>(sQ, 32 * tb + 16 * s, 32 * j, lane), zf, acc_k[j], 0, 0, 0);
+                    const bf16x8 ofr = frag_cols<HW>(sO, 32 * tb + 16 * s, 32 * j, lane);
+                    acc_v[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ofr, pf, acc_v[j], 0, 0, 0);
+                    if constexpr (two_terms(HW)) acc_v[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ofr, pr, acc_v[j], 0, 0, 0);
+                    const bf16x8 qfr = frag_cols<HW>(sQ, 32 * tb + 16 * s, 32 * j, lane);
+                    acc_k[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qfr, zf, acc_k[j], 0, 0, 0);
+                    if constexpr (two_terms(HW)) acc_k[j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qfr, zr, acc_k[j], 0, 0, 0);
                 }
             }
         }
     }
-    if (krow < S) {
-        uint16_t* row = a.dqkv + ((int64_t)b * S + krow) * a.ldq + head * hd;
-        store_rows<HW>(row + a.ph * hd, acc_k, a.scale, hd, lhi);
-        store_rows<HW>(row + 2 * a.ph * hd, acc_v, 1.f, hd, lhi);
+    if constexpr (KW == 1) {
+        if (krow < S) {
+            uint16_t* row = a.dqkv + ((int64_t)b * S + krow) * a.ldq + head * hd;
+            store_rows<HW>(row + a.ph * hd, acc_k, a.scale, hd, lhi);
+            store_rows<HW>(row + 2 * a.ph * hd, acc_v, 1.f, hd, lhi);
+        }
+    } else {
+        uint16_t* const out = a.dqkv + (int64_t)b * S * a.ldq + head * hd;
+#pragma unroll
+        for (int part = 1; part <= 2; ++part) { // dK, then dV
+            const float f1 = part == 1 ? a.scale : 1.f;
+            if (part == 1) wave_sync(); else __syncthreads();
+            put_part<HW>(sQ, part == 1 ? acc_k : acc_v, l32, lhi);
+            __syncthreads();
+            store_parts<HW>(lds, out + part * a.ph * hd, a.ldq, k0, S, hd, tid, [&](int, float (&f)[NW]) {
+#pragma unroll
+                for (int w = 0; w < NW; ++w) f[w] = f1;
+            });
+        }
     }
 }
 
-template <int HW>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bwd_dkv_kernel(CoreArgs a, int nblocks, int nbh) {
-    __shared__ __attribute__((aligned(16))) unsigned char sQ[DkvShape<HW>::QT * row_bytes(HW)];
-    __shared__ __attribute__((aligned(16))) unsigned char sO[DkvShape<HW>::QT * row_bytes(HW)];
-    __shared__ __attribute__((aligned(16))) float sL[DkvShape<HW>::QT];
-    __shared__ __attribute__((aligned(16))) float sD[DkvShape<HW>::QT];
-    __shared__ __attribute__((aligned(16))) unsigned char sV[DkvShape<HW>::V_BYTES];
+template <int HW, int KW>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_dkv(HW, KW), waves_dkv(HW, KW))))
+void attn_bwd_dkv_kernel(CoreArgs a, int nblocks, int nbh) {
+    __shared__ __attribute__((aligned(16))) unsigned char lds[DkvShape<HW, KW>::LDS];
     int blk, head, b;
     causal_item(blockIdx.x, gridDim.x, nbh, nblocks, a.ph, blk, head, b);
     // key block i meets the query blocks i .. n - 1: the first key blocks are the long ones
-    attn_bwd_dkv_block<HW>(a, (nblocks - 1 - blk) * BQ, head, b, sQ, sO, sL, sD, sV);
+    attn_bwd_dkv_block<HW, KW>(a, (nblocks - 1 - blk) * Split<KW>::ROWS, head, b, lds);
+}
+
+// KW = 4 up to this many workgroups of the KW = 1 form, i.e. while those leave CUs idle: its shorter chains then weigh
+// more than the re-reads.  Block forward + backward in us, KW = 1 / KW = 4: heads of 64, 96 workgroups (1 x 1024 tokens,
+// 12 heads) 158 / 124, 192 (2 x 1024) 168 / 149, 384 (4 x 1024) 184 / 187; heads of 128, 64 workgroups (1 x 1024, 8 heads)
+// 238 / 165, 128 (2 x 1024) 249 / 203, 256 (4 x 1024) 267 / 281; heads of 96, 192 workgroups 208 / 195.
+constexpr int split_below(int hw) { return hw == HD ? 256 : 192; }
+
+enum CoreKernel { CORE_FWD, CORE_DQ, CORE_DKV };
+template <int HW, int KW>
+int launch_core(CoreKernel which, const CoreArgs& a, int nbh, hipStream_t s) {
+    const int nblocks = (a.S + Split<KW>::ROWS - 1) / Split<KW>::ROWS;
+    const dim3 grid((unsigned)(nblocks * nbh));
+    if (which == CORE_FWD) attn_fwd_kernel<HW, KW><<<grid, 64 * NW, 0, s>>>(a, nblocks, nbh);
+    else if (which == CORE_DQ) attn_bwd_dq_kernel<HW, KW><<<grid, 64 * NW, 0, s>>>(a, nblocks, nbh);
+    else attn_bwd_dkv_kernel<HW, KW><<<grid, 64 * NW, 0, s>>>(a, nblocks, nbh);
+    return launch_status();
+}
+template <int HW>
+int launch_core(CoreKernel which, const CoreArgs& a, int64_t nbh, hipStream_t s) {
+    const int64_t wide = (a.S + Split<1>::ROWS - 1) / Split<1>::ROWS * nbh; // workgroups of the launch with KW = 1
+    if (wide > INT32_MAX) return SDP_ERR_UNSUPPORTED;
+    return wide <= split_below(HW) ? launch_core<HW, NW>(which, a, (int)nbh, s) : launch_core<HW, 1>(which, a, (int)nbh, s);
+}
+int launch_core(CoreKernel which, const CoreArgs& a, int64_t nbh, const char* name, hipStream_t s) {
+    ProfileScope ps(name, s);
+    if (a.hd <= 64) return launch_core<64>(which, a, nbh, s);
+    if (a.hd <= 96) return launch_core<96>(which, a, nbh, s);
+    return launch_core<128>(which, a, nbh, s);
 }
 
 // rows of [Wq; Wk; Wv] ([3 H hd][d]) and of WoT ([H hd][d]) that belong to the held heads
@@ -831,15 +1000,7 @@ int sdp::attn_fwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         a.lse = LSE_save;
         a.S = S, a.ph = ph, a.hd = hw;
         a.scale = 1.f / sqrtf((float)hd), a.scale2 = a.scale * 1.44269504088896340736f;
-        ProfileScope ps("attn_core_fwd", s);
-        constexpr int QF = SDP_ATTN_FWD_QF, NW = SDP_ATTN_FWD_NW, ROWS = 32 * QF * NW;
-        const int nblocks = (S + ROWS - 1) / ROWS;
-        if ((int64_t)nblocks * ph * Bt > INT32_MAX) return SDP_ERR_UNSUPPORTED;
-        const dim3 grid(nblocks * ph * Bt);
-        if (hw <= 64) attn_fwd_kernel<64, QF, NW><<<grid, 64 * NW, 0, s>>>(a, nblocks, ph * Bt);
-        else if (hw <= 96) attn_fwd_kernel<96, QF, NW><<<grid, 64 * NW, 0, s>>>(a, nblocks, ph * Bt);
-        else attn_fwd_kernel<128, QF, NW><<<grid, 64 * NW, 0, s>>>(a, nblocks, ph * Bt);
-        rc = launch_status();
+        rc = launch_core(CORE_FWD, a, (int64_t)ph * Bt, "attn_core_fwd", s);
     } else {
         AttnCoreDesc c;
         c.qkv = QKV_save, c.ldq = 3 * E, c.o_out = O_save, c.ldo = E, c.lse = LSE_save;
@@ -932,25 +1093,9 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         a.dqkv = (uint16_t*)w.dQKV;
         a.S = S, a.ph = hr, a.hd = hw;
         a.scale = 1.f / sqrtf((float)hd), a.scale2 = a.scale * 1.44269504088896340736f;
-        const int nblocks = (S + BQ - 1) / BQ;
-        if ((int64_t)nblocks * hr * Bt > INT32_MAX) return SDP_ERR_UNSUPPORTED;
-        const dim3 grid(nblocks * hr * Bt);
-        {
-            ProfileScope ps("attn_core_bwd_dq", s);
-            if (hw <= 64) attn_bwd_dq_kernel<64><<<grid, 256, 0, s>>>(a, nblocks, hr * Bt);
-            else if (hw <= 96) attn_bwd_dq_kernel<96><<<grid, 256, 0, s>>>(a, nblocks, hr * Bt);
-            else attn_bwd_dq_kernel<128><<<grid, 256, 0, s>>>(a, nblocks, hr * Bt);
-            rc = launch_status();
-            if (rc != SDP_OK) return rc;
-        }
-        {
-            ProfileScope ps("attn_core_bwd_dkv", s); // reads the delta written by the dQ kernel
-            if (hw <= 64) attn_bwd_dkv_kernel<64><<<grid, 256, 0, s>>>(a, nblocks, hr * Bt);
-            else if (hw <= 96) attn_bwd_dkv_kernel<96><<<grid, 256, 0, s>>>(a, nblocks, hr * Bt);
-            else attn_bwd_dkv_kernel<128><<<grid, 256, 0, s>>>(a, nblocks, hr * Bt);
-            rc = launch_status();
-            if (rc != SDP_OK) return rc;
-        }
+        rc = launch_core(CORE_DQ, a, (int64_t)hr * Bt, "attn_core_bwd_dq", s);
+        if (rc == SDP_OK) rc = launch_core(CORE_DKV, a, (int64_t)hr * Bt, "attn_core_bwd_dkv", s); // reads the delta written by the dQ kernel
+        if (rc != SDP_OK) return rc;
     } else {
         AttnCoreDesc c;
         c.qkv = QKV_save, c.ldq = 3 * E, c.o = O_save, c.dO = w.dO, c.ldo = E;

@@ -170,6 +170,18 @@ def test_attention_wide_heads(sdp, orc, w, mode):
     run_case(sdp, orc, w, [0], dw_layout="scatter" if w.hd % 16 else "compact", mode=mode)
 
 
+# launches of enough 128-row blocks for the form whose waves share the tiles (the smaller ones above split the walked
+# axis over the waves): every width of the core, sequences just beyond a block and within one
+GRID = [AttnWorkload(f"grid{hd}_S{S}", Bt, S, 72, H, hd, H - 1, 2, 49) for hd, Bt, S, H in
+        ((64, 4, 131, 36), (50, 9, 33, 31), (96, 3, 129, 35), (128, 4, 190, 26), (88, 7, 64, 30))]
+
+
+@pytest.mark.parametrize("mode", ["fm", "bm"])
+@pytest.mark.parametrize("w", GRID, ids=[w.name for w in GRID])
+def test_attention_many_blocks(sdp, orc, w, mode):
+    run_case(sdp, orc, w, [0], mode=mode)
+
+
 # fp32 core: every width it is instantiated for, 16-byte and single-element loads, sequences around its 16-row tiles and
 # the 64 rows its four waves take at a time
 F32_CORE = [AttnWorkload(f"f32_{hd}_S{S}", Bt, S, 24, 3, hd, 2, 2, 48, "f32") for hd, Bt, S in
@@ -259,12 +271,13 @@ def test_plain_core_and_mfma_core_agree_on_the_same_inputs(sdp, mode):
         assert norm <= 1e-2 and elem <= 3e-2, f"{what}: elementwise {elem:.3e}, normwise {norm:.3e}"
 
 
-def test_forward_core_with_logits_that_keep_growing(sdp, orc):
+@pytest.mark.parametrize("Bt", [2, 26])  # few workgroups: keys split over the waves; 260 of 128 queries: not split
+def test_forward_core_with_logits_that_keep_growing(sdp, orc, Bt):
     """Keys later in a sequence carry larger logits, so a query's running maximum climbs far beyond what it was
     after the first tile: the forward kernel has to move its reference exponent (and rescale what it has
     accumulated) several times on the way.  The core is isolated from the projections: the oracle evaluates
     the attention of the Q, K, V the library stored (bf16 values, widened exactly), through selector matrices."""
-    w = AttnWorkload("growing_logits", 2, 520, 128, 2, 64, 2, 2, 45)
+    w = AttnWorkload("growing_logits", Bt, 520, 128, 2, 64, 2, 2, 45)
     Wqkv, WoT = workloads.attn_weights(w)
     Wqkv = Wqkv.clone()
     Wqkv[:2] *= 10.0  # W_Q, W_K
