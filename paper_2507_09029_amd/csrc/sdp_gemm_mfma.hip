@@ -6,18 +6,21 @@
 //
 // Tile: BM x BN outputs per workgroup, depth step 64, WAVES_M x WAVES_N waves of 64 lanes, each wave
 // owning (BM/WAVES_M) x (BN/WAVES_N) outputs as 32 x 32 blocks of four 16 x 16 MFMA tiles.  The flagship shape is
-// 256 x 256 with 8 waves: 128 accumulator registers per lane, two waves per SIMD, one workgroup per CU.
+// 256 x 256 with 8 waves: 128 accumulator registers per lane, two waves per SIMD, one workgroup per CU.  Launches that
+// it would leave on few CUs take 128-row tiles of 8 waves, or 64 x 64 tiles whose 4 waves each run their own depth steps
+// (choose_shape has the rule and the times).
 //
 // HBM/L2 -> LDS: direct loads (global_load_lds_dwordx4).  One wave instruction moves 64 chunks of
 // 16 bytes into 1 KB of consecutive LDS ("slab"); which global chunk a lane fetches is free, so the
 // LDS layout below is produced by choosing the global address per lane.  No registers and no
-// ds_write instructions are spent on staging.  LDS holds two stages of A and three of B.
+// ds_write instructions are spent on staging.  LDS holds two stages of A and three of B (three and three for the
+// 128-row tiles, two and two per wave for the 64 x 64 tile).
 //
 // LDS layout of an operand stage, [R rows][64 k] in 16-byte chunks: chunk (r, c) sits at
 // r*8 + (c ^ ((r >> 1) & 7)).  A lane's MFMA operand (8 consecutive k of one row) is one chunk, one
 // ds_read_b128, and the lanes served together fall on distinct banks.
 //
-// Main loop: the waves form two groups that alternate between a phase of LDS reads + load issue and a
+// Main loop (not the 64 x 64 tile): the waves form two groups that alternate between a phase of LDS reads + load issue and a
 // phase of MFMAs only, one phase apart, so that on every SIMD one wave computes while the other one
 // fetches (see the comment at the loop).
 //
@@ -161,7 +164,13 @@ struct Geometry {
     static constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
     static constexpr int FM = WM / 32, FN = WN / 32;
     static constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
-    static constexpr int RING = 2 * A_BYTES + 3 * B_BYTES; // two A stages, three B stages
+    static constexpr bool kWaveDepth = BM == 64; // each wave runs its own depth steps on the whole tile (see the loop)
+    // LDS stages of A (B has three): two, or three for the 128-row tiles, whose steps are about as short as a load takes
+    // (A of the next step asked for only one step ahead: 32 steps of a 128 x 128 tile of 4 waves 31 us, 21 us this way
+    // with 8; four and five stages of both operands were no faster, 25 us)
+    static constexpr int A_STAGES = BM == 128 ? 3 : 2;
+    // kWaveDepth: two stages of both operands per wave
+    static constexpr int RING = kWaveDepth ? 2 * NW * (A_BYTES + B_BYTES) : A_STAGES * A_BYTES + 3 * B_BYTES;
     // epilogue strip: 32 rows x SW columns of bf16, rows padded by 8 bytes
     static constexpr int SW = EPI == EPI_SWIGLU_FWD ? WN / 2 : WN;
     static constexpr int RS = SW * 2 + 8;
@@ -174,11 +183,12 @@ struct Geometry {
 };
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int OP>
-__global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 1) void sdp_gemm_kernel(Dev g) {
+__global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1) void sdp_gemm_kernel(Dev g) {
     using Geo = Geometry<BM, BN, WAVES_M, WAVES_N, EPI>;
     constexpr int NW = Geo::NW, WM = Geo::WM, WN = Geo::WN, FM = Geo::FM, FN = Geo::FN;
     constexpr int A_BYTES = Geo::A_BYTES, B_BYTES = Geo::B_BYTES;
     constexpr bool kFwd = EPI == EPI_SWIGLU_FWD;
+    constexpr bool kWaveDepth = Geo::kWaveDepth;
     constexpr int SA = (BM / 8) / NW;  // A slabs (1 KB) per wave per step
     constexpr int SB = (BN / 8) / NW;  // B slabs per wave per step
     static_assert((BM / 8) % NW == 0 && (BN / 8) % NW == 0, "slabs must divide among the waves");
@@ -258,6 +268,122 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 1) void sdp_gemm_kernel(Dev 
     const int nk1 = ranged ? (nk_all - kt0 < g.ksteps ? nk_all - kt0 : g.ksteps) : nk_all;
     const int nk = EPI == EPI_DUAL_ACC ? 2 * nk1 : nk1;
 
+    // Accumulators: the wave's WM x WN outputs as 16 x 16 tiles of v_mfma_f32_16x16x32_bf16, grouped by 32 x 32
+    // blocks (i, j): acc[i][j][q] is the tile with rows 32 i + 16 (q >> 1) .. and columns 32 j + 16 (q & 1) ..
+    // (the 16 x 16 x 32 form sustains a higher clock than 32 x 32 x 16 on random operands: the same flops draw
+    // less power)
+    f32x4 acc[FM][FN][4];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[i][j][q] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    auto read_tile_frags = [&](const unsigned char* sa, const unsigned char* sb, int s, bf16x8* fa, bf16x8* fb) {
+        const int off = (((4 * s + lq) ^ ((l16 >> 1) & 7)) * 16) + l16 * 128;
+#pragma unroll
+        for (int i = 0; i < BM / 16; ++i) fa[i] = __builtin_bit_cast(bf16x8, *(const u32x4*)(sa + i * 2048 + off));
+#pragma unroll
+        for (int j = 0; j < BN / 16; ++j) fb[j] = __builtin_bit_cast(bf16x8, *(const u32x4*)(sb + j * 2048 + off));
+    };
+    if constexpr (kWaveDepth) {
+        // ---- main loop of the 64-row tiles: wave w runs the depth steps w, w + NW, ... on the whole tile, in two LDS stages
+        // of its own (no barrier); the partial tiles are then added through LDS, in wave order, every wave taking the part
+        // whose epilogue it runs.  What such a launch lacks is not matrix-core time but workgroups, and its time is the
+        // chain of loads of one tile: this runs NW x 2 steps of it at a time.
+        static_assert(!kFwd, "no gate / up pairing inside a 64-column tile");
+        constexpr int TM = BM / 16, TN = BN / 16; // fragments of the tile
+        uint32_t a_off[BM / 8], b_off[BN / 8];
+        const int ck = ((lane & 7) ^ ((lane >> 4) & 7)) & 7; // slab s: lane -> row 8 s + lane / 8; (row >> 1) & 7 = 4 (s & 1) + lane / 16
+#pragma unroll
+        for (int i = 0; i < BM / 8; ++i) {
+            int m = m0 + 8 * i + (lane >> 3);
+            m = m < g.M ? m : g.M - 1;
+            const int64_t arow = g.ag ? g.ag[m] : m;
+            a_off[i] = (uint32_t)((arow * g.lda + (ck ^ (4 * (i & 1))) * 8) * 2);
+        }
+#pragma unroll
+        for (int j = 0; j < BN / 8; ++j) {
+            int n = n0 + 8 * j + (lane >> 3);
+            n = n < g.N ? n : g.N - 1;
+            const int64_t row = g.bg ? g.bg[n] : n;
+            b_off[j] = (uint32_t)((row * g.ldb + (ck ^ (4 * (j & 1))) * 8) * 2);
+        }
+        f32x4 part[TM][TN];
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) part[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+        unsigned char* const mine = smem + wave * 2 * (A_BYTES + B_BYTES);
+        auto issue = [&](int kt, int stage, auto tail_c) {
+            constexpr bool TAIL = decltype(tail_c)::value;
+            const bool second = EPI == EPI_DUAL_ACC && kt >= nk1;
+            const int k0 = (kt0 + (second ? kt - nk1 : kt)) * BK;
+            const unsigned char* abase = (const unsigned char*)(second ? g.A2 : gA) + (int64_t)k0 * 2;
+            const unsigned char* bbase = (const unsigned char*)(second ? g.B2 : gB) + (int64_t)k0 * 2;
+            unsigned char* st = mine + stage * (A_BYTES + B_BYTES);
+            const bool out0 = TAIL && k0 + ck * 8 >= g.K, out1 = TAIL && k0 + (ck ^ 4) * 8 >= g.K; // even and odd slabs
+#pragma unroll
+            for (int i = 0; i < BM / 8; ++i) {
+                const unsigned char* src = ((i & 1) ? out1 : out0) ? (const unsigned char*)kZeroChunk : abase + a_off[i];
+                __builtin_amdgcn_global_load_lds((glb_void_ptr)src, (lds_void_ptr)(st + i * 1024), 16, 0, 0);
+            }
+#pragma unroll
+            for (int j = 0; j < BN / 8; ++j) {
+                const unsigned char* src = ((j & 1) ? out1 : out0) ? (const unsigned char*)kZeroChunk : bbase + b_off[j];
+                __builtin_amdgcn_global_load_lds((glb_void_ptr)src, (lds_void_ptr)(st + A_BYTES + j * 1024), 16, 0, 0);
+            }
+        };
+        auto run = [&](auto tail_c) {
+            if (wave < nk) issue(wave, 0, tail_c);
+            if (wave + NW < nk) issue(wave + NW, 1, tail_c);
+            int stage = 0;
+            for (int kt = wave; kt < nk; kt += NW, stage ^= 1) {
+                if (kt + NW < nk) SDP_WAIT_VMCNT(BM / 8 + BN / 8); else SDP_WAIT_VMCNT(0);
+                __builtin_amdgcn_sched_barrier(0);
+                const unsigned char* st = mine + stage * (A_BYTES + B_BYTES);
+                bf16x8 ta[2][TM], tb[2][TN];
+                read_tile_frags(st, st + A_BYTES, 0, ta[0], tb[0]);
+                read_tile_frags(st, st + A_BYTES, 1, ta[1], tb[1]);
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    if (h == 1) { // both halves have been read: the stage can be filled again
+                        SDP_WAIT_LGKMCNT0();
+                        __builtin_amdgcn_sched_barrier(0);
+                        if (kt + 2 * NW < nk) issue(kt + 2 * NW, stage, tail_c);
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+#pragma unroll
+                    for (int i = 0; i < TM; ++i)
+#pragma unroll
+                        for (int j = 0; j < TN; ++j)
+                            part[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tb[h][j], ta[h][i], part[i][j], 0, 0, 0);
+                }
+            }
+        };
+        if (g.K % BK == 0) run(std::false_type{}); else run(std::true_type{});
+        __syncthreads(); // every wave is done with its stages
+        f32x4* const parts = (f32x4*)smem; // [wave][fragment][lane]
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) parts[((wave * TM + i) * TN + j) * 64 + lane] = part[i][j];
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    const int tm = WM / 16 * wm + 2 * i + (q >> 1);
+                    const int tn = WN / 16 * wn + 2 * j + (q & 1);
+                    f32x4 v = parts[(tm * TN + tn) * 64 + lane];
+#pragma unroll
+                    for (int w = 1; w < NW; ++w) v += parts[((w * TM + tm) * TN + tn) * 64 + lane];
+                    acc[i][j][q] = v;
+                }
+    } else {
     // ---- per-lane global source of every slab this wave fills: byte offsets from a uniform base.
     // Row indices beyond the matrix are clamped to the last valid one: such lanes fetch valid
     // memory whose products only reach outputs that are never stored.
@@ -285,17 +411,17 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 1) void sdp_gemm_kernel(Dev 
         b_k[i] = c * 8;
     }
 
-    // LDS: two A stages, then a ring of three B stages
+    // LDS: the A stages, then a ring of three B stages
     unsigned char* const lds_a = smem;
-    unsigned char* const lds_b = smem + 2 * A_BYTES;
+    unsigned char* const lds_b = smem + Geo::A_STAGES * A_BYTES;
 
     // loads [first, last) of the SA (resp. SB) slabs of depth step kt; TAIL: K % 64 != 0
-    auto issue_a = [&](int kt, auto tail_c, int first, int last) {
+    auto issue_a = [&](int kt, int slot, auto tail_c, int first, int last) {
         constexpr bool TAIL = decltype(tail_c)::value;
         const bool second = EPI == EPI_DUAL_ACC && kt >= nk1;
         const int k0 = (kt0 + (second ? kt - nk1 : kt)) * BK;
         const int krem = g.K - k0;
-        unsigned char* sa = lds_a + (kt & 1) * A_BYTES;
+        unsigned char* sa = lds_a + slot * A_BYTES;
         const unsigned char* abase = (const unsigned char*)(second ? g.A2 : gA) + (int64_t)k0 * 2;
 #pragma unroll
         for (int i = 0; i < SA; ++i) {
@@ -323,18 +449,6 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 1) void sdp_gemm_kernel(Dev 
             __builtin_amdgcn_global_load_lds((glb_void_ptr)src, (lds_void_ptr)(sb + (wave + NW * i) * 1024), 16, 0, 0);
         }
     };
-
-    // Accumulators: the wave's WM x WN outputs as 16 x 16 tiles of v_mfma_f32_16x16x32_bf16, grouped by 32 x 32
-    // blocks (i, j): acc[i][j][q] is the tile with rows 32 i + 16 (q >> 1) .. and columns 32 j + 16 (q & 1) ..
-    // (the 16 x 16 x 32 form sustains a higher clock than 32 x 32 x 16 on random operands: the same flops draw
-    // less power)
-    f32x4 acc[FM][FN][4];
-#pragma unroll
-    for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) acc[i][j][q] = f32x4{0.f, 0.f, 0.f, 0.f};
 
     // B tile row where fragment j of this wave starts (wave-uniform)
     int bfrag[FN];
@@ -392,12 +506,15 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 1) void sdp_gemm_kernel(Dev 
     //   phase 4 k + 1 : group 0 computes (k, 0);  group 1 reads (k, 0), issues A(k + 1)
     //   phase 4 k + 2 : group 0 reads (k, 1), issues the loads of B for step k + 2;  group 1 computes (k, 0)
     //   phase 4 k + 3 : group 0 computes (k, 1);  group 1 reads (k, 1), issues B(k + 2)
-    // A has two LDS stages and B three.  Stage contents of step k are read in phases 4 k .. 4 k + 3;
+    // A has two LDS stages (or three) and B three.  Stage contents of step k are read in phases 4 k .. 4 k + 3;
     // loads into the stages of step k - 1 are issued from phase 4 k on, after the barrier that ends
     // phase 4 k - 1, before which every wave has waited for its own LDS reads.  Before that same
     // barrier every wave waits until its loads for step k have landed (loads complete in issue
     // order; only the newest SB, B of step k + 1, may still be in flight).
+    // With three stages of A (kA3) phase 4 k issues A of step k + 2 instead, into the stage of step k - 1 like B.
     const int grp = wave / (NW / 2);
+    constexpr bool kA3 = Geo::A_STAGES == 3;
+    constexpr int kAhead = kA3 ? SA + SB : SB; // loads that may still be in flight when a step begins
     bf16x8 fa[2 * FM], fb[2 * FN];
     auto read_half = [&](const unsigned char* sa, const unsigned char* sb, int h) { read_frags(sa, sb, h, fa, fb); };
     auto compute_half = [&]() {
@@ -413,12 +530,16 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 1) void sdp_gemm_kernel(Dev 
     auto step = [&](int kt, int slot, auto ia_c, auto ib_c, auto tail_c) {
         constexpr bool IA = decltype(ia_c)::value; // step kt + 1 exists
         constexpr bool IB = decltype(ib_c)::value; // step kt + 2 exists
-        const unsigned char* sa = lds_a + (kt & 1) * A_BYTES;
+        const unsigned char* sa = lds_a + (kA3 ? slot : kt & 1) * A_BYTES;
         const unsigned char* sb = lds_b + slot * B_BYTES;
         const int slot2 = slot == 0 ? 2 : slot - 1; // (kt + 2) % 3
         // READ (kt, 0)
         read_half(sa, sb, 0);
-        if (IA) issue_a(kt + 1, tail_c, 0, SA);
+        if (kA3) {
+            if (IB) issue_a(kt + 2, slot2, tail_c, 0, SA);
+        } else if (IA) {
+            issue_a(kt + 1, (kt + 1) & 1, tail_c, 0, SA);
+        }
         SDP_WAIT_LGKMCNT0();
         phase_end();
         // COMPUTE (kt, 0)
@@ -429,22 +550,23 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 1) void sdp_gemm_kernel(Dev 
         if (IB) issue_b(kt + 2, slot2, tail_c, 0, SB);
         SDP_WAIT_LGKMCNT0();
         if (grp == 1) {
-            if (IB) SDP_WAIT_VMCNT(SB); else SDP_WAIT_VMCNT(0);
+            if (IB) SDP_WAIT_VMCNT(kAhead); else SDP_WAIT_VMCNT(0);
         }
         phase_end();
         // COMPUTE (kt, 1)
         compute_half();
         if (grp == 0) {
-            if (IB) SDP_WAIT_VMCNT(SB); else SDP_WAIT_VMCNT(0);
+            if (IB) SDP_WAIT_VMCNT(kAhead); else SDP_WAIT_VMCNT(0);
         }
         phase_end();
     };
     auto run = [&](auto tail_c) {
-        issue_a(0, tail_c, 0, SA);
+        issue_a(0, 0, tail_c, 0, SA);
         issue_b(0, 0, tail_c, 0, SB);
         if (nk > 1) {
+            if (kA3) issue_a(1, 1, tail_c, 0, SA);
             issue_b(1, 1, tail_c, 0, SB);
-            SDP_WAIT_VMCNT(SB);
+            SDP_WAIT_VMCNT(kAhead);
         } else {
             SDP_WAIT_VMCNT(0);
         }
@@ -465,6 +587,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, 1) void sdp_gemm_kernel(Dev 
         if (grp == 0) phase_end();
     };
     if (g.K % BK == 0) run(std::false_type{}); else run(std::true_type{});
+    }
 
     // ================================ epilogue ================================
     // acc[i][j][q][r] = C(m, n),  m = m0 + WM wm + 32 i + 16 (q >> 1) + l16,
@@ -751,7 +874,7 @@ constexpr int kNumCU = 256;
 // arguments: the environment is consulted only in a build with -DSDP_TUNING_SWITCHES (never the shipped one),
 // once per process, and values outside the accepted sets are ignored.
 struct Tuning {
-    int force_tile = 0; // 0 = choose; 128 / 192 / 256
+    int force_tile = 0; // SDP_FORCE_TILE: 0 = choose; 1 + a Shape
     int group_m = 0;    // 0 = choose
     bool plain_order = false;
     int tail_parts = -1; // SDP_TAIL_PARTS: -1 = choose; 0 = no tail cut; n = cut into n ranges where a cut applies
@@ -762,7 +885,7 @@ const Tuning& tuning() {
 #ifdef SDP_TUNING_SWITCHES
         if (const char* e = getenv("SDP_FORCE_TILE")) {
             const int f = atoi(e);
-            if (f == 128 || f == 192 || f == 256) v.force_tile = f;
+            if (f >= 1 && f <= 6) v.force_tile = f;
         }
         if (const char* e = getenv("SDP_GROUP_M")) v.group_m = atoi(e) > 0 ? atoi(e) : 0;
         v.plain_order = getenv("SDP_PLAIN_ORDER") != nullptr;
@@ -981,38 +1104,66 @@ int launch_cfg(const GemmDesc& d, hipStream_t s) {
     return rc;
 }
 
-// estimated time of a tile shape, in units of 256 x 256 tile-depths: rounds over the CUs times tile
-// area, times a penalty for the smaller shapes' lower MFMA duty (more LDS traffic per flop).
-double shape_cost(int M, int ncols_total, int nbatch, int bm, int bn, double penalty) {
-    const int64_t tiles = (int64_t)((M + bm - 1) / bm) * ((ncols_total + bn - 1) / bn) * nbatch;
-    const int64_t rounds = (tiles + kNumCU - 1) / kNumCU;
-    return (double)rounds * bm * bn * penalty;
+// Tile shapes (rows x columns), and what each costs: a workgroup takes step0 us a depth step on an otherwise idle chip and
+// step1 us with all CUs at work, plus an epilogue of e0 us and e1 us per 1024 outputs that depends on what it moves; the
+// launch takes as many such rounds as its tiles need on 256 CUs.  Fitted to 75 contractions of 15 MLP and attention
+// shapes (128 to 8192 rows, depths of 128 to 8192), each timed at every shape: the choice is the fastest one or within 5 %
+// of it on all but one (14 %: 280 small tiles, barely a second round).  The smaller shapes buy idle CUs at more
+// L2 -> LDS traffic per flop: 1024 x 768 outputs, depth 2048: 41, 38, 27, 26, 21, 11 us in the order below; 8192 x 1536,
+// depth 4096: 87, 84, 116, 110, 125, 175 us.
+enum Shape { T256x256, T256x192, T128x256, T128x192, T128x128, T64x64, NUM_SHAPES };
+struct ShapeInfo {
+    int bm, bn;
+    double step0, step1;
+};
+constexpr ShapeInfo kShapes[NUM_SHAPES] = {{256, 256, 1.02, 1.35}, {256, 192, 0.87, 1.20}, {128, 256, 0.82, 0.90},
+                                           {128, 192, 0.80, 0.88}, {128, 128, 0.56, 0.66}, {64, 64, 0.23, 0.22}};
+struct EpilogueCost {
+    double e0, e1;
+};
+constexpr EpilogueCost epilogue_cost(int epi) {
+    return epi == EPI_SWIGLU_FWD ? EpilogueCost{5.0, 0.055} : epi == EPI_SWIGLU_BWD ? EpilogueCost{4.0, 0.30} : EpilogueCost{2.8, 0.03};
+}
+// the SwiGLU-forward epilogue pairs gate and up columns inside a wave's columns and has no 192- or 64-wide variant
+constexpr bool shape_exists(int epi, int shape) {
+    return epi != EPI_SWIGLU_FWD || (shape != T256x192 && shape != T128x192 && shape != T64x64);
 }
 
-// tile shape of a launch: 256 (x 256), 192 (256 x 192) or 128 (x 128)
+// nbatch problems, the depth of each cut into ksplit ranges that are problems of their own
 template <int EPI>
-int choose_shape(const GemmDesc& d, int nbatch) {
-    // columns of tile space (gate and up interleaved double the tile columns)
-    const int ncols = EPI == EPI_SWIGLU_FWD ? 2 * d.N : d.N;
-    const double c256 = shape_cost(d.M, ncols, nbatch, 256, 256, 1.0);
-    // the SwiGLU-forward epilogue pairs gate and up columns inside a tile and has no 192-wide variant
-    const double c192 = EPI == EPI_SWIGLU_FWD ? 1e300 : shape_cost(d.M, ncols, nbatch, 256, 192, 1.08);
-    const double c128 = shape_cost(d.M, ncols, nbatch, 128, 128, 1.6);
-    const int force = tuning().force_tile ? tuning().force_tile : d.force_tile;
-    if (force == 256 || (!force && c256 <= c192 && c256 <= c128)) return 256;
-    if (EPI != EPI_SWIGLU_FWD && (force == 192 || (!force && c192 <= c128))) return 192;
-    return 128;
+Shape choose_shape(const GemmDesc& d, int nbatch, int ksplit) {
+    const int force = tuning().force_tile - 1;
+    if (force >= 0 && shape_exists(EPI, force)) return (Shape)force;
+    const int ncols = EPI == EPI_SWIGLU_FWD ? 2 * d.N : d.N; // gate and up interleaved double the tile columns
+    const double steps = ((d.K + BK - 1) / BK + ksplit - 1) / ksplit * (EPI == EPI_DUAL_ACC ? 2 : 1);
+    const EpilogueCost e = epilogue_cost(EPI);
+    Shape best = T256x256;
+    double best_cost = -1;
+    for (int i = 0; i < NUM_SHAPES; ++i) {
+        if (!shape_exists(EPI, i)) continue;
+        const ShapeInfo& h = kShapes[i];
+        const int64_t tiles = (int64_t)((d.M + h.bm - 1) / h.bm) * ((ncols + h.bn - 1) / h.bn) * nbatch * ksplit;
+        const int64_t rounds = (tiles + kNumCU - 1) / kNumCU;
+        const double busy = tiles < kNumCU ? (double)tiles / kNumCU : 1.0;
+        const double cost = (double)rounds * (steps * (h.step0 + (h.step1 - h.step0) * busy) + e.e0 + e.e1 * h.bm * h.bn / 1024);
+        if (best_cost < 0 || cost < best_cost) best_cost = cost, best = (Shape)i;
+    }
+    return best;
 }
 
 template <int EPI, int OP>
 int launch(const GemmDesc& d, hipStream_t s) {
-    const int nbatch = OP == OP_DW || OP == OP_DW_TAIL ? d.nbatch : (OP == OP_DW_SPLIT ? d.nbatch * d.ksplit : 1);
-    const int shape = choose_shape<EPI>(d, nbatch);
-    if (shape == 256) return launch_cfg<256, 256, 2, 4, EPI, OP>(d, s);
+    const int nbatch = OP == OP_DW || OP == OP_DW_TAIL || OP == OP_DW_SPLIT ? d.nbatch : 1;
+    const Shape shape = choose_shape<EPI>(d, nbatch, OP == OP_DW_SPLIT ? d.ksplit : 1);
+    if (shape == T256x256) return launch_cfg<256, 256, 2, 4, EPI, OP>(d, s);
+    if (shape == T128x256) return launch_cfg<128, 256, 2, 4, EPI, OP>(d, s);
+    if (shape == T128x128) return launch_cfg<128, 128, 4, 2, EPI, OP>(d, s);
     if constexpr (EPI != EPI_SWIGLU_FWD) {
-        if (shape == 192) return launch_cfg<256, 192, 4, 2, EPI, OP>(d, s);
+        if (shape == T256x192) return launch_cfg<256, 192, 4, 2, EPI, OP>(d, s);
+        if (shape == T128x192) return launch_cfg<128, 192, 4, 2, EPI, OP>(d, s);
+        if (shape == T64x64) return launch_cfg<64, 64, 2, 2, EPI, OP>(d, s);
     }
-    return launch_cfg<128, 128, 2, 2, EPI, OP>(d, s);
+    return SDP_ERR_UNSUPPORTED; // not reached: choose_shape returns one of the above
 }
 
 // Tail cut of a batched launch (OP_DW_TAIL).  With T tiles on 256 CUs the launch runs floor(T / 256) full rounds
@@ -1022,8 +1173,8 @@ int launch(const GemmDesc& d, hipStream_t s) {
 // picks; *tail_tiles and *tile_elems describe the scratch.
 int plan_tail(const GemmDesc& d, int* tail_tiles, int* tile_elems) {
     if (d.nbatch < 1 || d.N % 8 || d.M < 1 || d.K < 1) return 0;
-    const int shape = choose_shape<EPI_STORE>(d, d.nbatch);
-    const int bm = shape == 128 ? 128 : 256, bn = shape == 256 ? 256 : (shape == 192 ? 192 : 128);
+    const ShapeInfo& shape = kShapes[choose_shape<EPI_STORE>(d, d.nbatch, 1)];
+    const int bm = shape.bm, bn = shape.bn;
     const int64_t tiles = (int64_t)((d.M + bm - 1) / bm) * ((d.N + bn - 1) / bn) * d.nbatch;
     if (tiles > 0x7FFFFFFF) return 0;
     const int head = (int)(tiles / kNumCU) * kNumCU, tail = (int)tiles - head;
@@ -1107,7 +1258,6 @@ size_t gemm_tail_ws_bytes(int M, int N, int K, int nbatch) {
 
 bool gemm_mfma_supported(const GemmDesc& d) {
     if (d.M < 1 || d.N < 1 || d.K < 1) return false;
-    if (d.force_tile != 0 && d.force_tile != 128 && d.force_tile != 192 && d.force_tile != 256) return false;
     // 16-byte global chunks (a depth that is no multiple of 64 ends in a step whose missing chunks are zeros: any
     // multiple of 8 will do.  T = 5000, d = 1600, p = 2664, whose depths p and T are odd multiples of 8: a step of two
     // workers takes 1.07 ms here, 12.0 ms with those depths on the plain kernel), 32-bit byte offsets inside each operand

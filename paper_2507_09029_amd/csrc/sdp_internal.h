@@ -106,7 +106,6 @@ struct GemmDesc {
     const void* Ab[4] = {nullptr, nullptr, nullptr, nullptr};
     const void* Bb[4] = {nullptr, nullptr, nullptr, nullptr};
     void* Cb[4] = {nullptr, nullptr, nullptr, nullptr};
-    int force_tile = 0; // 0 = choose; 256 / 192 / 128 force a tile shape (tuning and tests)
     // batched launches only: optional fp32 scratch of gemm_split_ws_bytes(M, N, K, nbatch) bytes.  With it, a
     // launch that has few tiles and a deep K cuts the depth into ranges that run as extra problems, and a second
     // kernel sums the ranges' partial results (gemm_choose_ksplit decides; 1 = no cut).

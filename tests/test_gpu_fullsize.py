@@ -217,3 +217,32 @@ def test_attention_500M_one_sequence_and_sampled_gradient_rows(sdp, orc):
     for i, (name, want) in enumerate((("dWq", gq), ("dWk", gk), ("dWv", gv))):
         assert_close(g[i], want, TOL_BF16, name, elem_tol=3e-2)
     assert_close(workloads.to_f64(gWoT), go, TOL_BF16, "dWoT", elem_tol=3e-2)
+
+
+# sizes between the small cases and the benchmark's, at which the contractions' tile rule takes the shapes for launches of
+# few tiles; rows, columns and depths that end inside a tile.  The tiles: those the launches are meant to exercise.
+TILES = [
+    (workloads.MlpWorkload("t1000", "bf16", 1000, 760, 1600, 1032, 2, "fm", 71),
+     {"mlp_gate_up": "128x128", "mlp_down": "64x64", "mlp_dact": "64x64", "mlp_dx": "64x64", "mlp_dw": "128x128"}),
+    (workloads.MlpWorkload("t2056", "bf16", 2040, 1016, 2600, 2040, 2, "fm", 72),
+     {"mlp_gate_up": "128x256", "mlp_down": "64x64", "mlp_dact": "128x128", "mlp_dx": "64x64", "mlp_dw": "128x256"}),
+    (workloads.MlpWorkload("t4072", "bf16", 4072, 1192, 3600, 3208, 2, "fm", 73),
+     {"mlp_down": "128x192", "mlp_dx": "128x192", "mlp_dact": "256x256", "mlp_dw": "256x256"}),
+    (workloads.MlpWorkload("t3000", "bf16", 3000, 776, 1544, 1000, 2, "bm", 74),
+     {"mlp_dact": "128x192", "mlp_down": "128x128", "mlp_dw": "128x128"}),
+]
+
+
+@pytest.mark.parametrize("w,tiles", TILES, ids=[w.name for w, _ in TILES])
+def test_tile_shapes_sampled(sdp, orc, w, tiles):
+    W = workloads.mlp_weights(w)
+    Wd = [t.cuda() for t in W]
+    mask, idx, pos, cov = sdp.make_masks(w.K, w.F, w.p, w.mask_seed, True)
+    want_mask = orc.make_masks(w.K, w.F, w.p, w.mask_seed, True)
+    sdp.profile_enable(True)
+    try:
+        _fullsize_worker(sdp, orc, w, 1, Wd, [workloads.to_f64(t) for t in W], idx, want_mask, "scatter")
+        taken = {name: sdp.profile_launch_shape(name)["tile"] for name in ("mlp_gate_up", "mlp_down", "mlp_dact", "mlp_dx", "mlp_dw")}
+    finally:
+        sdp.profile_enable(False)
+    assert {k: taken[k] for k in tiles} == tiles, taken
