@@ -1123,7 +1123,8 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
 
     const int64_t part = (int64_t)(dw_layout == SDP_DW_SCATTER ? H * hd : ph * hd) * d;
     if (dtype == SDP_F32) { // every operand as it is stored: dQKV, O, X, dY depth-major, the held heads' columns by their list
-        GemmDesc dw;
+        GemmDesc all[3];
+        GemmDesc &dw = all[1], &dwo = all[2];
         dw.name = "attn_dw";
         dw.M = Eh, dw.N = d, dw.K = T;
         dw.lda = 3 * E, dw.a_km = 1;
@@ -1132,15 +1133,17 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         dw.epilogue = EPI_STORE;
         dw.ldc = d;
         dw.c_scatter = dw_layout == SDP_DW_SCATTER && !all_heads ? w.rows_o : nullptr;
+        dwo = dw;
+        dwo.lda = E;
+        dwo.A = O_save, dwo.B = dY, dwo.C = dWoT;
         dw.nbatch = 3;
         for (int i = 0; i < 3; ++i)
             dw.Ab[i] = (const float*)w.dQKV + (int64_t)i * E, dw.Bb[i] = X, dw.Cb[i] = (float*)dWqkv + i * part;
+        all[0] = dx;
+        rc = gemm_f32_group(all, 3, "attn_dx_dw", s);
+        if (rc != SDP_ERR_UNSUPPORTED) return rc;
         rc = gemm_f32(dw, s);
-        if (rc != SDP_OK) return rc;
-        dw.nbatch = 0;
-        dw.lda = E;
-        dw.A = O_save, dw.B = dY, dw.C = dWoT;
-        rc = gemm_f32(dw, s);
+        if (rc == SDP_OK) rc = gemm_f32(dwo, s);
         return rc != SDP_OK ? rc : gemm_f32(dx, s);
     }
 

@@ -10,7 +10,8 @@
 // operand traffic is cheap here (a wave reads 4 KB of LDS per 512 matrix cycles) and the shapes that use fp32 are small:
 // latency, launches and idle CUs decide.  Hence three tiles, one loop:
 //   128 x 128 (4 waves of 64 x 64), 64 x 64 (4 waves of 32 x 32), and 32 x 32 whose 4 waves share one tile and split its
-//   depth (each takes 16 of every 64 depth steps; their sums meet in LDS), for launches with fewer tiles than CUs.
+//   depth (each takes 16 of every 64 depth steps; their sums meet in LDS), for launches with fewer tiles than CUs;
+//   the smallest launches take 16 x 16 tiles in a loop of their own (further down).
 // Tiles move global -> registers -> LDS, the next two or three steps in flight; one barrier per step.
 //
 // A depth slot is free to stand for any k as long as both operands agree: in a group of 16 depth steps, lane group
@@ -172,6 +173,56 @@ __device__ inline f32x4 fragment(const float* lds, int row, int t, int g) {
     }
 }
 
+// epilogue of four consecutive columns n .. n + 3 of row m
+template <int EPI>
+__device__ inline void emit(const Dev& g, float* gC, int m, int n, f32x4 v, f32x4 v2) {
+    if (m >= g.M || n >= g.N) return;
+    const int cnt = g.N - n < 4 ? g.N - n : 4;
+    auto put = [&](float* base, int64_t row, int64_t ld, f32x4 x) {
+        float* p = base + row * ld + n;
+        if (g.vec_out) *(f32x4*)p = x;
+        else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (e < cnt) p[e] = x[e];
+        }
+    };
+    auto get = [&](const float* base, int64_t ld) {
+        const float* p = base + (int64_t)m * ld + n;
+        if (g.vec_out) return *(const f32x4*)p;
+        f32x4 x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (e < cnt) x[e] = p[e];
+        return x;
+    };
+    if (EPI == EPI_STORE || EPI == EPI_DUAL_ACC) {
+        const int64_t row = g.cs ? g.cs[m] : m;
+        if (row < 0) return; // dropped row
+        if (g.R) v += get(g.R, g.ldr);
+        put(gC, row, g.ldc, v);
+    } else if (EPI == EPI_SWIGLU_FWD) {
+        put(g.C, m, g.ldc, v);
+        put(g.C2, m, g.ldc, v2);
+        f32x4 act;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) act[e] = swiglu_fwd<true>(v[e], v2[e]);
+        put(g.C3, m, g.ldc, act);
+    } else {
+        const f32x4 gv = get(g.Gin, g.ldg), uv = get(g.Uin, g.ldg);
+        f32x4 dg, du, act;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            float a, b, c;
+            swiglu_bwd<true>(v[e], gv[e], uv[e], a, b, c);
+            dg[e] = a, du[e] = b, act[e] = c;
+        }
+        put(g.C, m, g.ldc, dg);
+        put(g.C2, m, g.ldc, du);
+        put(g.C3, m, g.ldc, act);
+    }
+}
+
 template <class C, int EPI, bool ADM, bool BDM, bool VEC>
 __global__ __launch_bounds__(256) void gemm_f32_kernel(Dev g) {
     constexpr int BM = C::BM, BN = C::BN, BK = C::BK, FM = C::FM, FN = C::FN, AHEAD = C::AHEAD;
@@ -289,60 +340,12 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(Dev g) {
         if (t + 1 < steps) step(t + 1, Set2{});
     }
 
-    // four consecutive columns n .. n + 3 of row m
-    auto emit = [&](int m, int n, f32x4 v, f32x4 v2) {
-        if (m >= g.M || n >= g.N) return;
-        const int cnt = g.N - n < 4 ? g.N - n : 4;
-        auto put = [&](float* base, int64_t row, int64_t ld, f32x4 x) {
-            float* p = base + row * ld + n;
-            if (g.vec_out) *(f32x4*)p = x;
-            else {
-#pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    if (e < cnt) p[e] = x[e];
-            }
-        };
-        auto get = [&](const float* base, int64_t ld) {
-            const float* p = base + (int64_t)m * ld + n;
-            if (g.vec_out) return *(const f32x4*)p;
-            f32x4 x = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (e < cnt) x[e] = p[e];
-            return x;
-        };
-        if (EPI == EPI_STORE || EPI == EPI_DUAL_ACC) {
-            const int64_t row = g.cs ? g.cs[m] : m;
-            if (row < 0) return; // dropped row
-            if (g.R) v += get(g.R, g.ldr);
-            put(gC, row, g.ldc, v);
-        } else if (EPI == EPI_SWIGLU_FWD) {
-            put(g.C, m, g.ldc, v);
-            put(g.C2, m, g.ldc, v2);
-            f32x4 act;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) act[e] = swiglu_fwd<true>(v[e], v2[e]);
-            put(g.C3, m, g.ldc, act);
-        } else {
-            const f32x4 gv = get(g.Gin, g.ldg), uv = get(g.Uin, g.ldg);
-            f32x4 dg, du, act;
-#pragma unroll
-            for (int e = 0; e < 4; ++e) {
-                float a, b, c;
-                swiglu_bwd<true>(v[e], gv[e], uv[e], a, b, c);
-                dg[e] = a, du[e] = b, act[e] = c;
-            }
-            put(g.C, m, g.ldc, dg);
-            put(g.C2, m, g.ldc, du);
-            put(g.C3, m, g.ldc, act);
-        }
-    };
     if constexpr (C::KSPLIT == 1) {
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
             for (int j = 0; j < FN; ++j)
-                emit(m0 + wrow + 16 * i + l16, n0 + wcol + 16 * j + 4 * lg, acc[0][i][j], acc[NB - 1][i][j]);
+                emit<EPI>(g, gC, m0 + wrow + 16 * i + l16, n0 + wcol + 16 * j + 4 * lg, acc[0][i][j], acc[NB - 1][i][j]);
     } else {
         // the waves' depth shares meet in LDS, added in wave order; one thread per 4 columns
         static_assert(BM * BN / 4 == 256 && BN == 32 && C::KSPLIT * BM * (BN + 4) * NB <= 2 * STAGE, "one piece per thread");
@@ -363,8 +366,246 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(Dev g) {
 #pragma unroll
             for (int w = 1; w < C::KSPLIT; ++w) s[b] += *(const f32x4*)(smem + ((b * C::KSPLIT + w) * BM + row) * RS + c);
         }
-        emit(m0 + row, n0 + c, s[0], s[NB - 1]);
+        emit<EPI>(g, gC, m0 + row, n0 + c, s[0], s[NB - 1]);
     }
+}
+
+// ---------------------------------------------------------------------------------------------------
+// Launches of few tiles: B x B outputs a workgroup (B = 16 or 32), whose four waves take the 32-deep steps w, w + 4, ...
+// of the tile's depth, each in LDS stages of its own.  Operands go memory -> LDS by direct loads (16 bytes a lane, 1 KB
+// an instruction, no registers, no barrier), `S` steps of every wave in flight; the waves' sums meet in LDS at the end.
+// Such a launch is bound by the latency of its loads and by the share of the chip's matrix cores that its tiles reach:
+// B = 16 spreads 256 x 256 outputs over all CUs, where the 32 x 32 tile of the other kernel (KSPLIT) takes 64 of them and
+// meets at a barrier every 64 depth steps.  B = 32 serves launches of several problems (gemm_f32_group).  More stages than
+// two (S = 4) gained nothing and keep a second workgroup off the CU.
+//
+// LDS of one operand's step, 16-byte chunks:
+//   rows        : [B rows][8 chunks of 4 depth steps], chunk c of row r at position c ^ ((r >> 1) & 7)
+//   depth-major : [32 depth steps][B / 4 chunks of 4 rows]; depth step 16 t + 4 g + j in LDS row 16 t + 4 j + g, and for
+//                 B = 32 chunk c of LDS row q at position c ^ (4 ((q >> 1) & 1))
+// A 16 x 16 fragment is one 16-byte read per lane of the first, four 4-byte reads of the second; both free of conflicts.
+// ---------------------------------------------------------------------------------------------------
+typedef __attribute__((address_space(3))) void* lds_void_ptr;
+typedef __attribute__((address_space(1))) const void* glb_void_ptr;
+#define SDP_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (7 << 4) | (15 << 8) | (((n) >> 4) << 14))
+#define SDP_WAIT_LGKMCNT0() __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14))
+
+constexpr int kListMax = 4096; // entries of a gathered depth's list that are kept in LDS
+
+// source of the chunks beyond the depth
+__device__ __attribute__((aligned(16))) const float kZero4[4] = {0.f, 0.f, 0.f, 0.f};
+
+template <int B, bool DM>
+struct WaveOperand {
+    static constexpr int BYTES = B * 128, SLABS = BYTES / 1024; // of one step; direct loads a step
+    static constexpr int CPR = DM ? B / 4 : 8;                  // chunks per LDS row
+    static constexpr int RPS = 64 / CPR;                        // LDS rows per slab
+    const float* p[DM ? 1 : SLABS]; // rows: this lane's chunk of each slab at depth 0; depth-major: its first column
+    int k[SLABS];                   // depth of that chunk within a step
+    int64_t ld;
+    __device__ void init(const float* base, int64_t ld_, int rows, int row0, const int32_t* gather, int lane) {
+        ld = ld_;
+        const int pos = lane % CPR;
+#pragma unroll
+        for (int i = 0; i < SLABS; ++i) {
+            const int q = RPS * i + lane / CPR; // LDS row
+            if constexpr (DM) {
+                k[i] = (q & 16) + 4 * (q & 3) + ((q >> 2) & 3);
+                if (i == 0) {
+                    // the swizzle bit of LDS row q is the same in every slab: a slab holds 8 or 16 rows
+                    int c = row0 + 4 * (B == 32 ? pos ^ (4 * ((q >> 1) & 1)) : pos);
+                    p[0] = base + (c < rows ? c : rows - 4);
+                }
+            } else {
+                const int c = pos ^ ((q >> 1) & 7);
+                int r = row0 + q;
+                r = r < rows ? r : rows - 1;
+                p[i] = base + (int64_t)(gather ? gather[r] : r) * ld_ + 4 * c;
+                k[i] = 4 * c;
+            }
+        }
+    }
+    // the direct loads of the step that begins at depth k0; list: gathered depth (in LDS), or null
+    __device__ void issue(unsigned char* lds, int k0, int K, const int* list) const {
+#pragma unroll
+        for (int i = 0; i < SLABS; ++i) {
+            const int kk = k0 + k[i];
+            const float* src;
+            if constexpr (DM) {
+                const int kc = kk < K ? kk : K - 1;
+                src = p[0] + (int64_t)(list ? list[kc] : kc) * ld;
+            } else {
+                src = p[i] + k0;
+            }
+            if (kk >= K) src = kZero4;
+            __builtin_amdgcn_global_load_lds((glb_void_ptr)src, (lds_void_ptr)(lds + 1024 * i), 16, 0, 0);
+        }
+    }
+    // rows 16 f .. of the tile at depth 16 t of the step: element j belongs to depth 16 t + 4 lg + j
+    __device__ static f32x4 fragment(const unsigned char* lds, int f, int t, int l16, int lg) {
+        if constexpr (DM) {
+            const float* w = (const float*)lds;
+            f32x4 v;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int q = 16 * t + 4 * j + lg, col = 16 * f + l16;
+                v[j] = w[q * B + (B == 32 ? col ^ (16 * ((q >> 1) & 1)) : col)];
+            }
+            return v;
+        } else {
+            const int r = 16 * f + l16;
+            return *(const f32x4*)(lds + r * 128 + (((4 * t + lg) ^ ((r >> 1) & 7)) * 16));
+        }
+    }
+};
+
+template <int B, int S, int EPI, bool ADM, bool BDM>
+struct WaveShape {
+    static constexpr int NB = EPI == EPI_SWIGLU_FWD ? 2 : 1;
+    static constexpr int STAGE = (1 + NB) * B * 128, LOADS = STAGE / 1024;
+    static constexpr int TILES = 4 * S * STAGE, LDS = TILES + (BDM ? kListMax * 4 : 0);
+    static_assert(LDS <= 160 * 1024 && 4 * NB * B * (B + 4) * 4 <= TILES && (S - 1) * LOADS < 64, "fits");
+};
+
+template <int B, int S, int EPI, bool ADM, bool BDM>
+__device__ inline void wave_body(const Dev& g, int block, unsigned char* smem) {
+    using Sh = WaveShape<B, S, EPI, ADM, BDM>;
+    typedef WaveOperand<B, ADM> OA;
+    typedef WaveOperand<B, BDM> OB;
+    constexpr int NB = Sh::NB, F = B / 16;
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int per = g.tiles_m * g.tiles_n;
+    const int z = block / per, tile = block - z * per;
+    const int m0 = (tile % g.tiles_m) * B, n0 = (tile / g.tiles_m) * B;
+    const float *gA = g.A, *gB = g.B;
+    float* gC = g.C;
+    if (g.nbatch > 0) {
+        gA = z == 0 ? g.Ab[0] : (z == 1 ? g.Ab[1] : (z == 2 ? g.Ab[2] : g.Ab[3]));
+        gB = z == 0 ? g.Bb[0] : (z == 1 ? g.Bb[1] : (z == 2 ? g.Bb[2] : g.Bb[3]));
+        gC = z == 0 ? g.Cb[0] : (z == 1 ? g.Cb[1] : (z == 2 ? g.Cb[2] : g.Cb[3]));
+    }
+    int* list = nullptr;
+    if constexpr (BDM) {
+        if (g.bg) { // K <= kListMax
+            list = (int*)(smem + Sh::TILES);
+            for (int i = tid; i < g.K; i += 256) list[i] = g.bg[i];
+            __syncthreads();
+        }
+    }
+    OA a;
+    OB b[NB];
+    a.init(gA, g.lda, g.M, m0, ADM ? nullptr : g.ag, lane);
+    b[0].init(gB, g.ldb, g.N, n0, BDM ? nullptr : g.bg, lane);
+    if constexpr (NB == 2) b[1].init(g.B2, g.ldb, g.N, n0, g.bg, lane);
+    f32x4 acc[NB][F][F];
+#pragma unroll
+    for (int c = 0; c < NB; ++c)
+#pragma unroll
+        for (int i = 0; i < F; ++i)
+#pragma unroll
+            for (int j = 0; j < F; ++j) acc[c][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    unsigned char* const mine = smem + wave * S * Sh::STAGE;
+    const int steps = (g.K + 31) / 32;
+#pragma unroll
+    for (int pass = 0; pass < (EPI == EPI_DUAL_ACC ? 2 : 1); ++pass) {
+        if (pass == 1) {
+            a.init(g.A2, g.lda, g.M, m0, ADM ? nullptr : g.ag, lane);
+            b[0].init(g.B2, g.ldb, g.N, n0, BDM ? nullptr : g.bg, lane);
+        }
+        const int n = steps > wave ? (steps - wave + 3) / 4 : 0; // this wave's steps
+        auto issue = [&](int t, int stage) {
+            unsigned char* st = mine + stage * Sh::STAGE;
+            const int k0 = 32 * (wave + 4 * t);
+            a.issue(st, k0, g.K, nullptr);
+#pragma unroll
+            for (int c = 0; c < NB; ++c) b[c].issue(st + OA::BYTES + c * OB::BYTES, k0, g.K, list);
+        };
+        for (int t = 0; t < S && t < n; ++t) issue(t, t);
+        int stage = 0;
+        for (int t = 0; t < n; ++t) {
+            // steps issued beyond this one: S - 1, fewer at the end
+            const int ahead = n - 1 - t;
+            if (ahead >= S - 1) SDP_WAIT_VMCNT((S - 1) * Sh::LOADS);
+            else if (S > 2 && ahead == 2) SDP_WAIT_VMCNT(2 * Sh::LOADS);
+            else if (S > 1 && ahead == 1) SDP_WAIT_VMCNT(Sh::LOADS);
+            else SDP_WAIT_VMCNT(0);
+            __builtin_amdgcn_sched_barrier(0);
+            const unsigned char* st = mine + stage * Sh::STAGE;
+            f32x4 fa[2][F], fb[2][NB][F];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+#pragma unroll
+                for (int i = 0; i < F; ++i) fa[u][i] = OA::fragment(st, i, u, l16, lg);
+#pragma unroll
+                for (int c = 0; c < NB; ++c)
+#pragma unroll
+                    for (int j = 0; j < F; ++j) fb[u][c][j] = OB::fragment(st + OA::BYTES + c * OB::BYTES, j, u, l16, lg);
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                if (u == 1) { // the whole step has been read: its stage can be filled again
+                    SDP_WAIT_LGKMCNT0();
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (t + S < n) issue(t + S, stage);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int c = 0; c < NB; ++c)
+#pragma unroll
+                        for (int i = 0; i < F; ++i)
+#pragma unroll
+                            for (int j = 0; j < F; ++j) // B first: a lane then holds 4 consecutive columns of one row
+                                acc[c][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[u][c][j][e], fa[u][i][e], acc[c][i][j], 0, 0, 0);
+            }
+            stage = stage == S - 1 ? 0 : stage + 1;
+        }
+    }
+    __syncthreads(); // every wave is done with its stages
+    constexpr int RS = B + 4;
+    float* const sum = (float*)smem;
+#pragma unroll
+    for (int c = 0; c < NB; ++c)
+#pragma unroll
+        for (int i = 0; i < F; ++i)
+#pragma unroll
+            for (int j = 0; j < F; ++j)
+                *(f32x4*)(sum + ((c * 4 + wave) * B + 16 * i + l16) * RS + 16 * j + 4 * lg) = acc[c][i][j];
+    __syncthreads();
+    if (tid < B * B / 4) {
+        const int row = tid / (B / 4), col = (tid % (B / 4)) * 4;
+        f32x4 v[NB];
+#pragma unroll
+        for (int c = 0; c < NB; ++c) {
+            v[c] = *(const f32x4*)(sum + (c * 4 * B + row) * RS + col);
+#pragma unroll
+            for (int w = 1; w < 4; ++w) v[c] += *(const f32x4*)(sum + ((c * 4 + w) * B + row) * RS + col);
+        }
+        emit<EPI>(g, gC, m0 + row, n0 + col, v[0], v[NB - 1]);
+    }
+}
+
+template <int B, int S, int EPI, bool ADM, bool BDM>
+__global__ __launch_bounds__(256) void gemm_f32_wave_kernel(Dev g) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char wave_lds[];
+    wave_body<B, S, EPI, ADM, BDM>(g, blockIdx.x, wave_lds);
+}
+
+template <int B, int S, int EPI, bool ADM, bool BDM>
+int launch_wave(Dev g, const char* name, hipStream_t s) {
+    constexpr int LDS = WaveShape<B, S, EPI, ADM, BDM>::LDS;
+    g.tiles_m = (g.M + B - 1) / B, g.tiles_n = (g.N + B - 1) / B;
+    const int64_t blocks = (int64_t)g.tiles_m * g.tiles_n * (g.nbatch > 0 ? g.nbatch : 1);
+    if (blocks > 0x7FFFFFFF) return SDP_ERR_SHAPE;
+    auto kern = gemm_f32_wave_kernel<B, S, EPI, ADM, BDM>;
+    static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+    if (attr != hipSuccess) return SDP_ERR_HIP;
+    ProfileScope ps(name, s);
+    kern<<<(unsigned)blocks, 256, LDS, s>>>(g);
+    return launch_status();
 }
 
 template <class C, int EPI, bool ADM, bool BDM, bool VEC>
@@ -383,11 +624,21 @@ int launch(Dev g, const char* name, hipStream_t s) {
     return launch_status();
 }
 
+// Launches whose 16 x 16 tiles are resident all at once (two workgroups a CU).  Against the 32 x 32 tile (times with about
+// 5 us of event overhead): 256 x 512, depth 256, two operands 10.1 -> 7.5 us; 256 x 256, depth 2 x 512 15.0 -> 9.1; 128 x
+// 512, depth 1024 13.3 -> 9.2; but 512 x 512, depth 512 (1024 tiles) 10.4 -> 12.1.
+bool few_tiles(const Dev& g) {
+    return (int64_t)((g.M + 15) / 16) * ((g.N + 15) / 16) * (g.nbatch > 0 ? g.nbatch : 1) <= 512;
+}
+
 // Tile of a launch: the fewest matrix cycles on the busiest CU (rounds of tiles over 256 CUs x tile area), each tile
 // weighted by what its loop loses to staging and barriers.  With fewer 64-wide tiles than CUs the 32-wide ones win on
 // both counts (T = 256, p = 512, d = 256: 128 tiles whose waves each run a quarter of the depth, against 32).
 template <int EPI, bool ADM, bool BDM, bool VEC>
 int choose(const Dev& g, const char* name, hipStream_t s) {
+    if constexpr (VEC) {
+        if (few_tiles(g) && !(BDM && g.bg && g.K > kListMax)) return launch_wave<16, 2, EPI, ADM, BDM>(g, name, s);
+    }
     auto cost = [&](int b, double weight) {
         const int64_t tiles = (int64_t)((g.M + b - 1) / b) * ((g.N + b - 1) / b) * (g.nbatch > 0 ? g.nbatch : 1);
         return (double)((tiles + 255) / 256) * b * b * weight;
@@ -402,12 +653,11 @@ int choose(bool vec, const Dev& g, const char* name, hipStream_t s) {
     return vec ? choose<EPI, ADM, BDM, true>(g, name, s) : choose<EPI, ADM, BDM, false>(g, name, s);
 }
 
-} // namespace
-
-int gemm_f32(const GemmDesc& d, hipStream_t s) {
+// kernel arguments of a descriptor; *vec: the 16-byte loads can take it
+int describe(const GemmDesc& d, Dev& g, bool* vec) {
     if (d.M < 1 || d.N < 1 || d.K < 1) return SDP_ERR_SHAPE;
     if (d.nbatch < 0 || d.nbatch > kMaxBatch || d.Cc || d.Ct) return SDP_ERR_UNSUPPORTED;
-    Dev g{};
+    g = Dev{};
     g.M = d.M, g.N = d.N, g.K = d.K;
     g.A = (const float*)d.A, g.A2 = (const float*)d.A2, g.B = (const float*)d.B, g.B2 = (const float*)d.B2;
     g.lda = d.lda, g.ldb = d.ldb, g.ag = d.a_gather, g.bg = d.b_gather, g.cs = d.c_scatter;
@@ -422,10 +672,81 @@ int gemm_f32(const GemmDesc& d, hipStream_t s) {
         va = va && al(d.Ab[z]), vb = vb && al(d.Bb[z]), vo = vo && al(d.Cb[z]);
     }
     // along the contiguous axis: the depth for an operand stored by rows, M or N for a depth-major one
-    const bool vec = va && vb && d.lda % 4 == 0 && d.ldb % 4 == 0 && (d.a_km ? d.M : d.K) % 4 == 0 &&
+    *vec = va && vb && d.lda % 4 == 0 && d.ldb % 4 == 0 && (d.a_km ? d.M : d.K) % 4 == 0 &&
                      (d.b_km ? d.N : d.K) % 4 == 0 && !(d.a_km && d.a_gather);
     g.vec_out = vo && d.N % 4 == 0 && d.ldc % 4 == 0 && (!d.R || (al(d.R) && d.ldr % 4 == 0)) &&
                 (d.epilogue != EPI_SWIGLU_BWD || (al(d.Gin) && al(d.Uin) && d.ldg % 4 == 0));
+    return SDP_OK;
+}
+
+template <int BX, int EPIX>
+__global__ __launch_bounds__(256) void gemm_f32_group_kernel(Dev x, Dev w0, Dev w1, int nx, int n0) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char wave_lds[];
+    const int b = blockIdx.x;
+    if (b < nx) wave_body<BX, 2, EPIX, false, true>(x, b, wave_lds);
+    else if (b < nx + n0) wave_body<32, 2, EPI_STORE, true, true>(w0, b - nx, wave_lds);
+    else wave_body<32, 2, EPI_STORE, true, true>(w1, b - nx - n0, wave_lds);
+}
+
+template <int BX, int EPIX>
+int launch_group(Dev x, Dev w0, Dev w1, int n, const char* name, hipStream_t s) {
+    constexpr int LX = WaveShape<BX, 2, EPIX, false, true>::LDS, LW = WaveShape<32, 2, EPI_STORE, true, true>::LDS;
+    constexpr int LDS = LX > LW ? LX : LW;
+    auto tiles = [](Dev& g, int b) {
+        g.tiles_m = (g.M + b - 1) / b, g.tiles_n = (g.N + b - 1) / b;
+        return (int64_t)g.tiles_m * g.tiles_n * (g.nbatch > 0 ? g.nbatch : 1);
+    };
+    const int64_t nx = tiles(x, BX), n0 = tiles(w0, 32), n1 = n > 2 ? tiles(w1, 32) : 0;
+    if (nx + n0 + n1 > 0x7FFFFFFF) return SDP_ERR_SHAPE;
+    auto kern = gemm_f32_group_kernel<BX, EPIX>;
+    static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+    if (attr != hipSuccess) return SDP_ERR_HIP;
+    ProfileScope ps(name, s);
+    kern<<<(unsigned)(nx + n0 + n1), 256, LDS, s>>>(x, w0, w1, (int)nx, (int)n0);
+    return launch_status();
+}
+
+} // namespace
+
+int gemm_f32_group(const GemmDesc* d, int n, const char* name, hipStream_t s) {
+    if (n < 2 || n > 3) return SDP_ERR_UNSUPPORTED;
+    Dev g[3] = {};
+    for (int i = 0; i < n; ++i) {
+        bool vec;
+        const int rc = describe(d[i], g[i], &vec);
+        if (rc != SDP_OK) return rc;
+        if (!vec || !d[i].b_km || (d[i].b_gather && d[i].K > kListMax)) return SDP_ERR_UNSUPPORTED;
+        if (i == 0 ? d[i].a_km || d[i].nbatch > 0 || (d[i].epilogue != EPI_STORE && d[i].epilogue != EPI_DUAL_ACC)
+                   : !d[i].a_km || d[i].epilogue != EPI_STORE)
+            return SDP_ERR_UNSUPPORTED;
+    }
+    // the first problem's output may be an operand of the others in the caller's memory (dX in place of dY): they then
+    // have to follow one another
+    const uintptr_t c0 = (uintptr_t)d[0].C, c1 = c0 + ((size_t)d[0].M * d[0].ldc) * 4;
+    auto apart = [&](const void* p, int64_t rows, int64_t ld) {
+        const uintptr_t q = (uintptr_t)p;
+        return !p || q >= c1 || q + (size_t)rows * ld * 4 <= c0;
+    };
+    for (int i = 1; i < n; ++i) {
+        if (!apart(d[i].A, d[i].K, d[i].lda) || !apart(d[i].B, d[i].K, d[i].ldb)) return SDP_ERR_UNSUPPORTED;
+        for (int z = 0; z < d[i].nbatch; ++z)
+            if (!apart(d[i].Ab[z], d[i].K, d[i].lda) || !apart(d[i].Bb[z], d[i].K, d[i].ldb)) return SDP_ERR_UNSUPPORTED;
+    }
+    // Worth it while d[0] alone leaves room on the chip.  Launches of 512 x 512 outputs, depth 2 x 1376, beside three of
+    // 1376 x 512, depth 512: step 114 -> 109 us; 1000 x 512, depth 2 x 1600 (512 tiles of 32 x 32, two on every CU): 209 ->
+    // 215 us.
+    const bool few = few_tiles(g[0]);
+    if (!few && (int64_t)((d[0].M + 31) / 32) * ((d[0].N + 31) / 32) > 256) return SDP_ERR_UNSUPPORTED;
+    if (d[0].epilogue == EPI_DUAL_ACC)
+        return few ? launch_group<16, EPI_DUAL_ACC>(g[0], g[1], g[2], n, name, s) : launch_group<32, EPI_DUAL_ACC>(g[0], g[1], g[2], n, name, s);
+    return few ? launch_group<16, EPI_STORE>(g[0], g[1], g[2], n, name, s) : launch_group<32, EPI_STORE>(g[0], g[1], g[2], n, name, s);
+}
+
+int gemm_f32(const GemmDesc& d, hipStream_t s) {
+    Dev g;
+    bool vec;
+    const int rc = describe(d, g, &vec);
+    if (rc != SDP_OK) return rc;
     switch (d.epilogue) {
     case EPI_STORE:
         if (d.a_km) return d.b_km ? choose<EPI_STORE, true, true>(vec, g, d.name, s) : SDP_ERR_UNSUPPORTED;

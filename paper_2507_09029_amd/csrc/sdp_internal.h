@@ -123,6 +123,9 @@ enum GemmOp { OP_GATE_UP = 0, OP_DOWN = 1, OP_DACT = 2, OP_DX = 3, OP_DW = 4, OP
 
 // fp32 contraction on the matrix cores, any shape.
 int gemm_f32(const GemmDesc& g, hipStream_t s);
+// A contraction d[0] with a row-major left operand (STORE or DUAL_ACC) and one or two with depth-major ones (STORE), all with
+// depth-major right operands, none an input of another, as one launch.  SDP_ERR_UNSUPPORTED: not these; nothing was launched.
+int gemm_f32_group(const GemmDesc* d, int n, const char* name, hipStream_t s);
 // Plain LDS-tiled bf16 contraction, any shape: what the MFMA kernel's address ranges do not take.
 int gemm_simple(const GemmDesc& g, hipStream_t s);
 // bf16 MFMA contraction; returns SDP_ERR_UNSUPPORTED when the shape / alignment does not fit.

@@ -203,24 +203,8 @@ int sdp::mlp_bwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
         da.C = dG, da.C2 = dU, da.C3 = Act, da.ldc = n;
         rc = gemm_f32(da, s);
         if (rc != SDP_OK) return rc;
-        if (want_dw) {
-            GemmDesc dw;
-            dw.name = "mlp_dw";
-            dw.M = p, dw.N = d, dw.K = T;
-            dw.lda = n, dw.a_km = 1;
-            if (mode == SDP_MASK_BACKWARD) dw.a_gather = idx_k, dw.a_rows = n;
-            dw.ldb = d, dw.b_km = 1;
-            dw.epilogue = EPI_STORE;
-            dw.ldc = d;
-            dw.c_scatter = dw_layout == SDP_DW_SCATTER ? idx_k : nullptr;
-            dw.nbatch = 3;
-            dw.Ab[0] = dG, dw.Ab[1] = dU, dw.Ab[2] = Act;
-            dw.Bb[0] = X, dw.Bb[1] = X, dw.Bb[2] = dY;
-            dw.Cb[0] = dW1, dw.Cb[1] = dW3, dw.Cb[2] = dW2T;
-            rc = gemm_f32(dw, s);
-            if (rc != SDP_OK) return rc;
-        }
-        GemmDesc dx;
+        GemmDesc both[2];
+        GemmDesc &dx = both[0], &dw = both[1];
         dx.name = "mlp_dx";
         dx.M = T, dx.N = d, dx.K = n;
         dx.A = dG, dx.A2 = dU, dx.lda = n;
@@ -228,7 +212,23 @@ int sdp::mlp_bwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
         dx.epilogue = EPI_DUAL_ACC;
         dx.C = dX, dx.ldc = d;
         dx.R = dx_residual, dx.ldr = d;
-        return gemm_f32(dx, s);
+        if (!want_dw) return gemm_f32(dx, s);
+        dw.name = "mlp_dw";
+        dw.M = p, dw.N = d, dw.K = T;
+        dw.lda = n, dw.a_km = 1;
+        if (mode == SDP_MASK_BACKWARD) dw.a_gather = idx_k, dw.a_rows = n;
+        dw.ldb = d, dw.b_km = 1;
+        dw.epilogue = EPI_STORE;
+        dw.ldc = d;
+        dw.c_scatter = dw_layout == SDP_DW_SCATTER ? idx_k : nullptr;
+        dw.nbatch = 3;
+        dw.Ab[0] = dG, dw.Ab[1] = dU, dw.Ab[2] = Act;
+        dw.Bb[0] = X, dw.Bb[1] = X, dw.Bb[2] = dY;
+        dw.Cb[0] = dW1, dw.Cb[1] = dW3, dw.Cb[2] = dW2T;
+        rc = gemm_f32_group(both, 2, "mlp_dx_dw", s);
+        if (rc != SDP_ERR_UNSUPPORTED) return rc;
+        rc = gemm_f32(dw, s);
+        return rc != SDP_OK ? rc : gemm_f32(dx, s);
     }
 
     // the four operand copies of the backward pass as one launch (X^T, dY^T only feed the weight gradients)

@@ -108,6 +108,33 @@ F32_TILES = [MlpWorkload(f"f32_{T}x{d}x{F}p{p}_{mode}", "f32", T, d, F, p, 2, mo
     (2040, 2040, 64, 33, "fm"))]
 
 
+# 16 x 16 tiles (depths around the 32 steps a wave takes and the 128 its workgroup does, rows and columns that end inside a
+# tile, a list longer than the kernel keeps), and dX and dW as one launch with either tile
+F32_FEW = [MlpWorkload(f"few_{T}x{d}x{F}p{p}_{mode}", "f32", T, d, F, p, 2, mode, 26) for T, d, F, p, mode in (
+    (4, 4, 8, 4, "fm"), (33, 36, 200, 124, "fm"), (100, 132, 300, 260, "bm"), (17, 260, 64, 36, "fm"), (260, 256, 520, 388, "fm"),
+    (16, 20, 4400, 4200, "fm"), (300, 700, 400, 204, "fm"), (52, 64, 40, 40, "bm"))]
+
+
+@pytest.mark.parametrize("w", F32_FEW, ids=[w.name for w in F32_FEW])
+def test_f32_few_tiles(sdp, orc, w):
+    run_case(sdp, orc, w, [1], dw_layout="scatter" if w.T % 2 else "compact")
+
+
+def test_f32_dx_may_take_the_place_of_dy(sdp):
+    """dX written over dY: the weight gradients, which read dY, come first."""
+    w = F32_FEW[4]
+    Wd = [t.cuda() for t in workloads.mlp_weights(w)]
+    mask, idx, pos, cov = sdp.make_masks(w.K, w.F, w.p, w.mask_seed, True)
+    X, dY = (t.cuda() for t in workloads.mlp_batch(w, 0))
+    Y, G, U = sdp.masked_mlp_fwd(w.mode, X, *Wd, idx[0])
+    want = sdp.masked_mlp_bwd(w.mode, X, dY, *Wd, idx[0], G, U)
+    out = (dY.clone(),) + tuple(torch.empty_like(t) for t in want[1:])
+    got = sdp.masked_mlp_bwd(w.mode, X, out[0], *Wd, idx[0], G, U, out=out)
+    torch.cuda.synchronize()
+    for a, b in zip(got, want):
+        assert (a - b).abs().max() <= 1e-5 * b.abs().max()
+
+
 @pytest.mark.parametrize("w", F32_TILES, ids=[w.name for w in F32_TILES])
 def test_f32_tiles(sdp, orc, w):
     run_case(sdp, orc, w, [1], dw_layout="scatter" if w.T % 2 else "compact")
