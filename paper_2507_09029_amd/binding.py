@@ -1,8 +1,10 @@
-"""ctypes binding of the C ABI in include/sdp.h.
+"""Binding of the C ABI in include/sdp.h.
 
 Argument marshalling only: every function here checks tensor dtypes / devices, passes raw device
 pointers and torch's current HIP stream to the library call of the same name and raises SdpError on
-a negative status.  PyTorch supplies device memory and streams; no step of the path runs in torch.
+a negative status.  The calls a training step makes per worker (MLP, attention, block) go through the
+compiled module _sdp_native (csrc/sdp_native.cpp), the others through ctypes.  PyTorch
+supplies device memory and streams; no step of the path runs in torch.
 There is no fallback: if libsdp_hip.so is missing or fails to load, importing `lib()` raises.
 """
 import ctypes
@@ -120,6 +122,24 @@ def lib():
     return L
 
 
+_calls = None
+
+
+def _native():
+    """The compiled module with the per-step calls; it binds to the library that lib() loads."""
+    global _calls
+    if _calls is None:
+        lib()
+        if not os.path.exists(os.path.join(_HERE, "_sdp_native.so")):
+            from . import build as _build
+
+            _build.build_library()
+        from . import _sdp_native
+
+        _calls = _sdp_native
+    return _calls
+
+
 def _check(status, what):
     if status < 0:
         raise SdpError(status, what)
@@ -132,7 +152,12 @@ def _dev(t, dtype, name):
 
 
 def _stream():
-    return torch.cuda.current_stream().cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())  # that of torch.cuda.current_stream()
+
+
+def _stream_of(X):
+    """The current stream for a compiled call, which checks its tensors itself: X on the CPU is refused there."""
+    return _stream() if X.is_cuda else 0
 
 
 def _ws(nbytes, device):
@@ -235,7 +260,7 @@ def masked_mlp_fwd(mode, X, W1, W3, W2T, idx_k, out=None, ws=None):
     p = int(idx_k.numel()) if idx_k is not None else F
     n = p if m == MASK_FORWARD else F
     for name, w in (("W1", W1), ("W3", W3), ("W2T", W2T)):
-        if tuple(w.shape) != (F, d):
+        if w.shape != (F, d):
             raise ValueError(f"{name}: expected shape {(F, d)}")
     if out is None:
         out = (torch.empty((T, d), dtype=dt, device=X.device), torch.empty((T, n), dtype=dt, device=X.device),
@@ -243,10 +268,7 @@ def masked_mlp_fwd(mode, X, W1, W3, W2T, idx_k, out=None, ws=None):
     Y, G, U = out
     if ws is None:
         ws = _ws(masked_mlp_fwd_workspace_bytes(m, dt, T, d, F, p), X.device)
-    st = lib().sdp_masked_mlp_fwd(
-        m, _DTYPES[dt], T, d, F, p, _dev(X, dt, "X"), _dev(W1, dt, "W1"), _dev(W3, dt, "W3"), _dev(W2T, dt, "W2T"),
-        _dev(idx_k, torch.int32, "idx_k") if idx_k is not None else None, _dev(Y, dt, "Y"), _dev(G, dt, "G_save"),
-        _dev(U, dt, "U_save"), ws.data_ptr(), ws.numel(), _stream())
+    st = _native().mlp_fwd(m, _DTYPES[dt], T, d, F, p, X, W1, W3, W2T, idx_k, Y, G, U, ws.data_ptr(), ws.numel(), _stream_of(X))
     _check(st, "sdp_masked_mlp_fwd")
     return Y, G, U
 
@@ -266,11 +288,8 @@ def masked_mlp_bwd(mode, X, dY, W1, W3, W2T, idx_k, G_save, U_save, dw_layout="c
     dX, dW1, dW3, dW2T = out
     if ws is None:
         ws = _ws(masked_mlp_bwd_workspace_bytes(m, dt, T, d, F, p), X.device)
-    st = lib().sdp_masked_mlp_bwd(
-        m, _DTYPES[dt], T, d, F, p, _dev(X, dt, "X"), _dev(dY, dt, "dY"), _dev(W1, dt, "W1"), _dev(W3, dt, "W3"),
-        _dev(W2T, dt, "W2T"), _dev(idx_k, torch.int32, "idx_k"), _dev(G_save, dt, "G_save"), _dev(U_save, dt, "U_save"),
-        _dev(dX, dt, "dX"), _dev(dW1, dt, "dW1"), _dev(dW3, dt, "dW3"), _dev(dW2T, dt, "dW2T"), lay,
-        ws.data_ptr(), ws.numel(), _stream())
+    st = _native().mlp_bwd(m, _DTYPES[dt], T, d, F, p, X, dY, W1, W3, W2T, idx_k, G_save, U_save, dX, dW1, dW3, dW2T, lay,
+                           ws.data_ptr(), ws.numel(), _stream_of(X))
     _check(st, "sdp_masked_mlp_bwd")
     return dX, dW1, dW3, dW2T
 
@@ -311,7 +330,7 @@ def masked_attn_fwd(mode, Bt, S, hd, X, Wqkv, WoT, head_idx_k, out=None, ws=None
     H = E_all // hd
     ph = int(head_idx_k.numel()) if head_idx_k is not None else H
     n = ph if m == MASK_FORWARD else H
-    if T != Bt * S or tuple(Wqkv.shape) != (3, E_all, d) or tuple(WoT.shape) != (E_all, d) or H * hd != E_all:
+    if T != Bt * S or Wqkv.shape != (3, E_all, d) or WoT.shape != (E_all, d) or H * hd != E_all:
         raise ValueError("attention shapes do not fit together")
     hw = attn_saved_head_width(dt, hd)
     if out is None:
@@ -321,11 +340,8 @@ def masked_attn_fwd(mode, Bt, S, hd, X, Wqkv, WoT, head_idx_k, out=None, ws=None
     Y, QKV, O, LSE = out
     if ws is None:
         ws = _ws(masked_attn_fwd_workspace_bytes(m, dt, Bt, S, d, H, hd, ph), X.device)
-    st = lib().sdp_masked_attn_fwd(
-        m, _DTYPES[dt], Bt, S, d, H, hd, ph, _dev(X, dt, "X"), _dev(Wqkv, dt, "Wqkv"), _dev(WoT, dt, "WoT"),
-        _dev(head_idx_k, torch.int32, "head_idx_k") if head_idx_k is not None else None, _dev(Y, dt, "Y"),
-        _dev(QKV, dt, "QKV_save"), _dev(O, dt, "O_save"), _dev(LSE, torch.float32, "LSE_save"), ws.data_ptr(), ws.numel(),
-        _stream())
+    st = _native().attn_fwd(m, _DTYPES[dt], Bt, S, d, H, hd, ph, X, Wqkv, WoT, head_idx_k, Y, QKV, O, LSE, ws.data_ptr(),
+                            ws.numel(), _stream_of(X))
     _check(st, "sdp_masked_attn_fwd")
     return Y, QKV, O, LSE
 
@@ -351,11 +367,8 @@ def masked_attn_bwd(mode, Bt, S, hd, X, dY, Wqkv, WoT, head_idx_k, QKV_save, O_s
     dX, dWqkv, dWoT = out
     if ws is None:
         ws = _ws(masked_attn_bwd_workspace_bytes(m, dt, Bt, S, d, H, hd, ph), X.device)
-    st = lib().sdp_masked_attn_bwd(
-        m, _DTYPES[dt], Bt, S, d, H, hd, ph, _dev(X, dt, "X"), _dev(dY, dt, "dY"), _dev(Wqkv, dt, "Wqkv"), _dev(WoT, dt, "WoT"),
-        _dev(head_idx_k, torch.int32, "head_idx_k"), _dev(QKV_save, dt, "QKV_save"), _dev(O_save, dt, "O_save"),
-        _dev(LSE_save, torch.float32, "LSE_save"), _dev(dX, dt, "dX"), _dev(dWqkv, dt, "dWqkv"), _dev(dWoT, dt, "dWoT"),
-        lay, ws.data_ptr(), ws.numel(), _stream())
+    st = _native().attn_bwd(m, _DTYPES[dt], Bt, S, d, H, hd, ph, X, dY, Wqkv, WoT, head_idx_k, QKV_save, O_save, LSE_save, dX,
+                            dWqkv, dWoT, lay, ws.data_ptr(), ws.numel(), _stream_of(X))
     _check(st, "sdp_masked_attn_bwd")
     return dX, dWqkv, dWoT
 
@@ -370,10 +383,6 @@ def block_fwd_workspace_bytes(dtype, Bt, S, d, H, hd, F):
 
 def block_bwd_workspace_bytes(dtype, Bt, S, d, H, hd, F):
     return int(lib().sdp_block_bwd_workspace_bytes(_DTYPES[dtype], Bt, S, d, H, hd, F))
-
-
-def _opt(t, dtype, name):
-    return _dev(t, dtype, name) if t is not None else None
 
 
 def block_fwd(mode, m, Bt, S, hd, X, Wqkv, WoT, W1, W3, W2T, out=None, ws=None):
@@ -403,11 +412,8 @@ def block_fwd(mode, m, Bt, S, hd, X, Wqkv, WoT, W1, W3, W2T, out=None, ws=None):
     Y, Hm, QKV, O, LSE, G, U = out
     if ws is None:
         ws = _ws(block_fwd_workspace_bytes(dt, Bt, S, d, H, hd, F), dev)
-    st = lib().sdp_block_fwd(md, int(bool(m)), _DTYPES[dt], Bt, S, d, H, hd, F, _dev(X, dt, "X"), _dev(Wqkv, dt, "Wqkv"),
-                             _dev(WoT, dt, "WoT"), _dev(W1, dt, "W1"), _dev(W3, dt, "W3"), _dev(W2T, dt, "W2T"), _dev(Y, dt, "Y"),
-                             _dev(Hm, dt, "Hm_save"), _dev(QKV, dt, "QKV_save"), _dev(O, dt, "O_save"),
-                             _dev(LSE, torch.float32, "LSE_save"), _dev(G, dt, "G_save"), _dev(U, dt, "U_save"),
-                             ws.data_ptr(), ws.numel(), _stream())
+    st = _native().block_fwd(md, int(bool(m)), _DTYPES[dt], Bt, S, d, H, hd, F, X, Wqkv, WoT, W1, W3, W2T, Y, Hm, QKV, O,
+                             LSE, G, U, ws.data_ptr(), ws.numel(), _stream_of(X))
     _check(st, "sdp_block_fwd")
     return Y, (Hm, QKV, O, LSE, G, U)
 
@@ -440,11 +446,8 @@ def block_bwd(mode, m, Bt, S, hd, X, dY, Wqkv, WoT, W1, W3, W2T, saved, dx_rule=
     g = tuple(out[1:6]) if m else (None,) * 5
     if ws is None:
         ws = _ws(block_bwd_workspace_bytes(dt, Bt, S, d, H, hd, F), dev)
-    st = lib().sdp_block_bwd(md, int(bool(m)), rule, _DTYPES[dt], Bt, S, d, H, hd, F, _dev(X, dt, "X"), _dev(dY, dt, "dY"),
-                             _dev(Wqkv, dt, "Wqkv"), _dev(WoT, dt, "WoT"), _dev(W1, dt, "W1"), _dev(W3, dt, "W3"),
-                             _dev(W2T, dt, "W2T"), _dev(Hm, dt, "Hm_save"), _dev(QKV, dt, "QKV_save"), _dev(O, dt, "O_save"),
-                             _dev(LSE, torch.float32, "LSE_save"), _dev(G, dt, "G_save"), _dev(U, dt, "U_save"),
-                             _dev(dX, dt, "dX"), *[_opt(t, dt, "dW") for t in g], ws.data_ptr(), ws.numel(), _stream())
+    st = _native().block_bwd(md, int(bool(m)), rule, _DTYPES[dt], Bt, S, d, H, hd, F, X, dY, Wqkv, WoT, W1, W3, W2T, Hm, QKV,
+                             O, LSE, G, U, dX, *g, ws.data_ptr(), ws.numel(), _stream_of(X))
     _check(st, "sdp_block_bwd")
     return dX, (g if m else None)
 
@@ -458,9 +461,9 @@ def coverage_grad_avg(grads, mask, out=None, cov=None):
     R, D = grads[0].shape
     ptrs = (ctypes.c_void_p * K)(*[_dev(g, dt, f"grads[{i}]") for i, g in enumerate(grads)])
     for g in grads:
-        if tuple(g.shape) != (R, D):
+        if g.shape != (R, D):
             raise ValueError("all gradient buffers must share one shape")
-    if tuple(mask.shape) != (K, R):
+    if mask.shape != (K, R):
         raise ValueError("mask must be [K][R]")
     if out is None:
         out = torch.empty((R, D), dtype=torch.float32, device=grads[0].device)
@@ -481,9 +484,9 @@ def coverage_grad_sqnorm(grads, mask, out=None, ws=None):
     R, D = grads[0].shape
     ptrs = (ctypes.c_void_p * K)(*[_dev(g, dt, f"grads[{i}]") for i, g in enumerate(grads)])
     for g in grads:
-        if tuple(g.shape) != (R, D):
+        if g.shape != (R, D):
             raise ValueError("all gradient buffers must share one shape")
-    if tuple(mask.shape) != (K, R):
+    if mask.shape != (K, R):
         raise ValueError("mask must be [K][R]")
     if out is None:
         out = torch.empty((1,), dtype=torch.float64, device=grads[0].device)
@@ -524,9 +527,9 @@ def coverage_avg_adamw(grads, mask, theta, m, v, lr, beta1, beta2, eps, weight_d
     R, D = grads[0].shape
     ptrs = (ctypes.c_void_p * K)(*[_dev(g, dt, f"grads[{i}]") for i, g in enumerate(grads)])
     for t, name in ((theta, "theta"), (m, "m"), (v, "v")):
-        if tuple(t.shape) != (R, D):
+        if t.shape != (R, D):
             raise ValueError(f"{name} must be [R][D]")
-    if tuple(mask.shape) != (K, R):
+    if mask.shape != (K, R):
         raise ValueError("mask must be [K][R]")
     if cov is None:
         cov = torch.empty((R,), dtype=torch.uint8, device=grads[0].device)

@@ -1,8 +1,9 @@
-"""Builds libsdp_hip.so (gfx950) from csrc/*.hip with hipcc, in-tree."""
+"""Builds libsdp_hip.so (gfx950) from csrc/*.hip with hipcc and the Python call module from csrc/sdp_native.cpp, in-tree."""
 import glob
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -10,6 +11,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsdp_hip.so")
+NATIVE = os.path.join(HERE, "_sdp_native.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
@@ -59,6 +61,19 @@ def build_library(force=False, verbose=False):
         _, rc, out = run(cmd)
         if rc != 0:
             raise RuntimeError(f"link failed:\n{out}")
+    src = os.path.join(CSRC, "sdp_native.cpp")
+    if force or _stale(NATIVE, [src] + hdrs):
+        import torch
+
+        T = os.path.dirname(torch.__file__)
+        cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC",
+               f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", os.path.join(ROOT, "include"),
+               "-I", os.path.join(T, "include"), "-I", os.path.join(T, "include", "torch", "csrc", "api", "include"),
+               "-I", sysconfig.get_paths()["include"], src, "-o", NATIVE, "-L", HERE, "-l:libsdp_hip.so",
+               "-L", os.path.join(T, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN"]
+        _, rc, out = run(cmd)
+        if rc != 0:
+            raise RuntimeError(f"building {NATIVE} failed:\n{out}")
     return LIB
 
 

@@ -235,3 +235,19 @@ def test_block_argument_errors():
     ok = [f, f, f, f, f, f, g, h, f, f, f, f, f, f]
     assert L.sdp_block_fwd(0, 1, 1, 1, 64, 64, 2, 32, 64, *ok, ctypes.c_size_t(0), None) == -3      # workspace too small
     assert L.sdp_block_bwd(1, 0, 7, 1, 1, 64, 64, 2, 32, 64, *([f] * 20), big, None) == -1   # unknown dx_rule
+
+
+def test_compiled_calls_refuse_what_is_no_gpu_tensor():
+    import torch
+
+    X, W = torch.zeros(8, 16, dtype=torch.bfloat16), torch.zeros(24, 16, dtype=torch.bfloat16)
+    idx, ws = torch.zeros(8, dtype=torch.int32), torch.zeros(256, dtype=torch.uint8)
+    with pytest.raises(TypeError, match="X: expected a contiguous torch.bfloat16 tensor on the GPU"):
+        sdp.masked_mlp_fwd("fm", X, W, W, W, idx, out=(X, X, X), ws=ws)
+    with pytest.raises(TypeError, match="X: expected a contiguous torch.float32 tensor on the GPU"):
+        sdp.masked_attn_fwd("bm", 1, 8, 8, X.float(), torch.zeros(3, 16, 16), torch.zeros(16, 16), None, out=(X,) * 4, ws=ws)
+    call = binding._native().mlp_fwd
+    with pytest.raises(TypeError, match="expected 17 arguments"):
+        call(0, 1)
+    with pytest.raises(OverflowError):
+        call(1 << 40, 1, 8, 16, 24, 8, X, W, W, W, None, X, X, X, 0, 0, 0)

@@ -237,3 +237,17 @@ def test_results_do_not_depend_on_what_workspace_and_outputs_held(sdp, w):
     for fill in ("nan", "big"):
         for name, a, b in zip(("Y", "G", "U", "dX", "dW1", "dW3", "dW2T"), res["zero"], res[fill]):
             assert torch.equal(a, b), f"{w.name}: {name} depends on the previous contents of a buffer ({fill})"
+
+
+def test_compiled_calls_name_the_argument_they_refuse(sdp):
+    X = torch.zeros(8, 16, dtype=torch.bfloat16, device="cuda")
+    W = torch.zeros(24, 16, dtype=torch.bfloat16, device="cuda")
+    idx = torch.arange(8, dtype=torch.int32, device="cuda")
+    for args, what in (((X, W, W.float(), W, idx), "W3: expected a contiguous torch.bfloat16"),
+                       ((X, W, W.t().contiguous().t(), W, idx), "W3: expected a contiguous torch.bfloat16"),
+                       ((X, W, W, W.cpu(), idx), "W2T: expected a contiguous torch.bfloat16"),
+                       ((X, W, W, W, idx.long()), "idx_k: expected a contiguous torch.int32")):
+        with pytest.raises(TypeError, match=what):
+            sdp.masked_mlp_fwd("fm", *args)
+    with pytest.raises(TypeError, match="dY: expected"):
+        sdp.masked_mlp_bwd("fm", X, None, W, W, W, idx, X, X)
