@@ -25,7 +25,7 @@
 // are, for this lane, the depth indices {16 s + 4 (L / 32) + r} and {16 s + 8 + 4 (L / 32) + r}, and the other
 // operand is read from LDS in that same order with two transposing reads (ds_read_tr16_b64), which turn a
 // row-major [depth][column] tile into the per-lane layout of an A operand.
-#include "sdp_internal.h"
+#include "sdp_transpose.h"
 
 #include <cmath>
 
@@ -447,6 +447,12 @@ __device__ inline void causal_item(int L, int nitems, int nbh, int nblocks, int 
     head = bh % ph, b = bh / ph;
 }
 
+// The core's launches carry transposes that the contractions after them read (WoT in the forward pass; X, dY, O, Wqkv beside
+// dQ; dQ beside dK/dV) as workgroups from `nitems` on: the core moves little memory, and the blocks of a causal sequence
+// end at different times.  On launches of their own: block of 4 x 2048 tokens, 12 heads of 64 464 us, this way 438; 24 heads
+// of 50, 12 held 690 -> 658.
+constexpr int side_tiles(int lds) { return lds / kTransposeLds < 4 ? lds / kTransposeLds : 4; }
+
 // waves per SIMD the registers are allotted for.  KW = 1, heads of 64: 3 beat 2 (86 -> 77 us at 4 x 2048 tokens, 12 heads)
 // and 4 spill.  KW = 4 has a workgroup per CU or less, and the wide heads then take the registers of one or two waves.
 constexpr int waves_fwd(int hw, int kw) { return kw == 1 ? (hw == HD ? 3 : 2) : 2; }
@@ -455,10 +461,12 @@ constexpr int waves_dkv(int hw, int kw) { return kw == 1 || hw == HD ? 2 : 1; }
 
 template <int HW, int KW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(waves_fwd(HW, KW), waves_fwd(HW, KW))))
-void attn_fwd_kernel(CoreArgs a, int nblocks, int nbh) {
+void attn_fwd_kernel(CoreArgs a, int nblocks, int nbh, SideJobs side) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[fwd_lds<HW, KW>()];
+    const int nitems = nblocks * nbh;
+    if ((int)blockIdx.x >= nitems) return side_transposes<side_tiles(sizeof(lds))>(side, blockIdx.x - nitems, lds, threadIdx.x);
     int blk, head, b;
-    causal_item(blockIdx.x, gridDim.x, nbh, nblocks, a.ph, blk, head, b);
+    causal_item(blockIdx.x, nitems, nbh, nblocks, a.ph, blk, head, b);
     attn_fwd_block<HW, KW>(a, blk * Split<KW>::ROWS, head, b, lds);
 }
 
@@ -576,10 +584,12 @@ __device__ inline void attn_bwd_dq_block(const CoreArgs& a, const int q0, const 
 
 template <int HW, int KW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_dq(HW, KW), waves_dq(HW, KW))))
-void attn_bwd_dq_kernel(CoreArgs a, int nblocks, int nbh) {
+void attn_bwd_dq_kernel(CoreArgs a, int nblocks, int nbh, SideJobs side) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[dq_lds<HW, KW>()];
+    const int nitems = nblocks * nbh;
+    if ((int)blockIdx.x >= nitems) return side_transposes<side_tiles(sizeof(lds))>(side, blockIdx.x - nitems, lds, threadIdx.x);
     int blk, head, b;
-    causal_item(blockIdx.x, gridDim.x, nbh, nblocks, a.ph, blk, head, b);
+    causal_item(blockIdx.x, nitems, nbh, nblocks, a.ph, blk, head, b);
     attn_bwd_dq_block<HW, KW>(a, blk * Split<KW>::ROWS, head, b, lds);
 }
 
@@ -739,10 +749,12 @@ __device__ inline void attn_bwd_dkv_block(const CoreArgs& a, const int k0, const
 
 template <int HW, int KW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_dkv(HW, KW), waves_dkv(HW, KW))))
-void attn_bwd_dkv_kernel(CoreArgs a, int nblocks, int nbh) {
+void attn_bwd_dkv_kernel(CoreArgs a, int nblocks, int nbh, SideJobs side) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[DkvShape<HW, KW>::LDS];
+    const int nitems = nblocks * nbh;
+    if ((int)blockIdx.x >= nitems) return side_transposes<side_tiles(sizeof(lds))>(side, blockIdx.x - nitems, lds, threadIdx.x);
     int blk, head, b;
-    causal_item(blockIdx.x, gridDim.x, nbh, nblocks, a.ph, blk, head, b);
+    causal_item(blockIdx.x, nitems, nbh, nblocks, a.ph, blk, head, b);
     // key block i meets the query blocks i .. n - 1: the first key blocks are the long ones
     attn_bwd_dkv_block<HW, KW>(a, (nblocks - 1 - blk) * Split<KW>::ROWS, head, b, lds);
 }
@@ -755,25 +767,31 @@ constexpr int split_below(int hw) { return hw == HD ? 256 : 192; }
 
 enum CoreKernel { CORE_FWD, CORE_DQ, CORE_DKV };
 template <int HW, int KW>
-int launch_core(CoreKernel which, const CoreArgs& a, int nbh, hipStream_t s) {
+int launch_core(CoreKernel which, const CoreArgs& a, int nbh, const SideJobs& side, hipStream_t s) {
     const int nblocks = (a.S + Split<KW>::ROWS - 1) / Split<KW>::ROWS;
-    const dim3 grid((unsigned)(nblocks * nbh));
-    if (which == CORE_FWD) attn_fwd_kernel<HW, KW><<<grid, 64 * NW, 0, s>>>(a, nblocks, nbh);
-    else if (which == CORE_DQ) attn_bwd_dq_kernel<HW, KW><<<grid, 64 * NW, 0, s>>>(a, nblocks, nbh);
-    else attn_bwd_dkv_kernel<HW, KW><<<grid, 64 * NW, 0, s>>>(a, nblocks, nbh);
+    auto grid = [&](int lds) {
+        const int per = side_tiles(lds);
+        return dim3((unsigned)(nblocks * nbh) + (unsigned)((side.end[kMaxTransposeJobs - 1] + per - 1) / per));
+    };
+    if (which == CORE_FWD) attn_fwd_kernel<HW, KW><<<grid(fwd_lds<HW, KW>()), 64 * NW, 0, s>>>(a, nblocks, nbh, side);
+    else if (which == CORE_DQ) attn_bwd_dq_kernel<HW, KW><<<grid(dq_lds<HW, KW>()), 64 * NW, 0, s>>>(a, nblocks, nbh, side);
+    else attn_bwd_dkv_kernel<HW, KW><<<grid(DkvShape<HW, KW>::LDS), 64 * NW, 0, s>>>(a, nblocks, nbh, side);
     return launch_status();
 }
 template <int HW>
-int launch_core(CoreKernel which, const CoreArgs& a, int64_t nbh, hipStream_t s) {
+int launch_core(CoreKernel which, const CoreArgs& a, int64_t nbh, const SideJobs& side, hipStream_t s) {
     const int64_t wide = (a.S + Split<1>::ROWS - 1) / Split<1>::ROWS * nbh; // workgroups of the launch with KW = 1
-    if (wide > INT32_MAX) return SDP_ERR_UNSUPPORTED;
-    return wide <= split_below(HW) ? launch_core<HW, NW>(which, a, (int)nbh, s) : launch_core<HW, 1>(which, a, (int)nbh, s);
+    if (wide > INT32_MAX / 2) return SDP_ERR_UNSUPPORTED;
+    return wide <= split_below(HW) ? launch_core<HW, NW>(which, a, (int)nbh, side, s) : launch_core<HW, 1>(which, a, (int)nbh, side, s);
 }
-int launch_core(CoreKernel which, const CoreArgs& a, int64_t nbh, const char* name, hipStream_t s) {
+// the core kernel and, in its launch, n transposes
+int launch_core(CoreKernel which, const CoreArgs& a, int64_t nbh, const TransposeJob* jobs, int n, const char* name, hipStream_t s) {
+    SideJobs side;
+    if (side_jobs(jobs, n, &side) < 0) return SDP_ERR_UNSUPPORTED;
     ProfileScope ps(name, s);
-    if (a.hd <= 64) return launch_core<64>(which, a, nbh, s);
-    if (a.hd <= 96) return launch_core<96>(which, a, nbh, s);
-    return launch_core<128>(which, a, nbh, s);
+    if (a.hd <= 64) return launch_core<64>(which, a, nbh, side, s);
+    if (a.hd <= 96) return launch_core<96>(which, a, nbh, side, s);
+    return launch_core<128>(which, a, nbh, side, s);
 }
 
 // rows of [Wq; Wk; Wv] ([3 H hd][d]) and of WoT ([H hd][d]) that belong to the held heads
@@ -803,36 +821,41 @@ int core_width(int dtype, int hd) { return dtype == SDP_BF16 && hd <= HD ? HD : 
 bool mfma_core(int dtype) { return dtype == SDP_BF16; }
 size_t esize(int dtype) { return dtype == SDP_F32 ? 4 : 2; }
 
-// out[(i hw + r)][:] = r < hd ? in[(heads ? heads[i] : i) hd + r][:] : 0 for i < n, r < hw, per stacked matrix
-// (blockIdx.y: matrix z of `in` [z][H hd][d] -> matrix z of `out` [z][n hw][d]); d % 8 == 0, 16 bytes per thread
-__global__ __launch_bounds__(256) void pad_heads_kernel(const uint16_t* __restrict__ in, const int32_t* __restrict__ heads,
-                                                        int n, int H, int hd, int hw, int d, uint16_t* __restrict__ out) {
+// What a padded pass needs of its weights, one launch.  blockIdx.y = 0 .. 3: Wq, Wk, Wv, WoT of the n run heads, each padded
+// to hw rows: out[(i hw + r)][:] = r < hd ? in[(heads ? heads[i] : i) hd + r][:] : 0 for i < n, r < hw (Wp [3][n hw][d], WoP
+// [n hw][d]); d % 8 == 0, 16 bytes per thread.  blockIdx.y = 4 (backward): row lists of the weight-gradient launch, for
+// padded row m = i hw + r of the ph held heads
+//   gather[m]  = held[i] hw + r             (row of the all-heads operand, backward masking)
+//   scatter[m] = r < hd ? (full ? held[i] : i) hd + r : -1     (output row; padding rows are dropped)
+// (Three launches before, of 5 to 6 us each.)
+struct PadArgs {
+    const uint16_t *Wqkv, *WoT;
+    uint16_t *Wp, *WoP;
+    const int32_t *heads, *held; // null: every head, in order
+    int n, ph, H, hd, hw, d, full;
+    int32_t *gather, *scatter;
+};
+__global__ __launch_bounds__(256) void pad_heads_kernel(PadArgs a) {
     typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
-    const int chunks = d / 8;
-    const int64_t total = (int64_t)n * hw * chunks;
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= total) return;
-    const int row = (int)(i / chunks), c = (int)(i % chunks);
-    const int head = row / hw, r = row % hw;
-    u32x4_t v = {0u, 0u, 0u, 0u};
-    if (r < hd) {
-        const int64_t src = (int64_t)blockIdx.y * H * hd + (int64_t)(heads ? heads[head] : head) * hd + r;
-        v = *(const u32x4_t*)(in + src * d + c * 8);
+    const int y = blockIdx.y;
+    if (y == 4) {
+        if (i >= a.ph * a.hw) return;
+        const int m = (int)i, k = m / a.hw, r = m % a.hw, h = a.held ? a.held[k] : k;
+        a.gather[m] = h * a.hw + r;
+        a.scatter[m] = r < a.hd ? (a.full ? h : k) * a.hd + r : -1;
+        return;
     }
-    *(u32x4_t*)(out + ((int64_t)blockIdx.y * n * hw + row) * d + c * 8) = v;
-}
-
-// Row lists of the weight-gradient launch when heads are padded: for padded row m = i hw + r of the held heads
-//   gather[m]  = heads[i] hw + r            (row of the all-heads operand, backward masking)
-//   scatter[m] = r < hd ? (full ? heads[i] : i) hd + r : -1     (output row; padding rows are dropped)
-__global__ void pad_rows_kernel(const int32_t* __restrict__ heads, int ph, int hd, int hw, int full,
-                                int32_t* __restrict__ gather, int32_t* __restrict__ scatter) {
-    const int m = blockIdx.x * blockDim.x + threadIdx.x;
-    if (m >= ph * hw) return;
-    const int i = m / hw, r = m % hw;
-    const int h = heads ? heads[i] : i;
-    gather[m] = h * hw + r;
-    scatter[m] = r < hd ? (full ? h : i) * hd + r : -1;
+    const int chunks = a.d / 8;
+    if (i >= (int64_t)a.n * a.hw * chunks) return;
+    const int row = (int)(i / chunks), c = (int)(i % chunks);
+    const int head = row / a.hw, r = row % a.hw;
+    const int z = y < 3 ? y : 0;
+    const uint16_t* in = (y < 3 ? a.Wqkv : a.WoT) + (int64_t)z * a.H * a.hd * a.d;
+    uint16_t* out = (y < 3 ? a.Wp : a.WoP) + (int64_t)z * a.n * a.hw * a.d;
+    u32x4_t v = {0u, 0u, 0u, 0u};
+    if (r < a.hd) v = *(const u32x4_t*)(in + ((int64_t)(a.heads ? a.heads[head] : head) * a.hd + r) * a.d + c * 8);
+    *(u32x4_t*)(out + (int64_t)row * a.d + c * 8) = v;
 }
 
 int check(int mode, int dtype, int Bt, int S, int d, int H, int hd, int ph) {
@@ -900,13 +923,11 @@ BwdWs bwd_ws(char* w, size_t e, int64_t T, int d, int E, int Eh, int64_t stats, 
     return r;
 }
 
-// padded copies of the run heads' weight rows (heads == nullptr: all n = H heads in order)
-int pad_heads(const void* in, int nmat, const int32_t* heads, int n, int H, int hd, int hw, int d, void* out,
-              const char* name, hipStream_t s) {
-    ProfileScope ps(name, s);
-    const int64_t total = (int64_t)n * hw * (d / 8);
-    pad_heads_kernel<<<dim3((unsigned)((total + 255) / 256), nmat), 256, 0, s>>>((const uint16_t*)in, heads, n, H, hd, hw, d,
-                                                                                  (uint16_t*)out);
+// rows: the weight-gradient launch's lists as well
+int pad_heads(const PadArgs& a, bool rows, hipStream_t s) {
+    ProfileScope ps("attn_pad_w", s);
+    const int64_t total = (int64_t)a.n * a.hw * (a.d / 8); // d >= 8: no fewer threads than list rows when n >= ph
+    pad_heads_kernel<<<dim3((unsigned)((total + 255) / 256), rows ? 5 : 4), 256, 0, s>>>(a);
     return launch_status();
 }
 
@@ -976,9 +997,9 @@ int sdp::attn_fwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         if (rc != SDP_OK) return rc;
     }
     if (padded) { // the run heads' rows of W_Q, W_K, W_V and W_O, each head padded to hw rows
-        rc = pad_heads(Wqkv, 3, gathered ? head_idx_k : nullptr, ph, H, hd, hw, d, w.Wp, "attn_pad_w", s);
-        if (rc != SDP_OK) return rc;
-        rc = pad_heads(WoT, 1, gathered ? head_idx_k : nullptr, ph, H, hd, hw, d, w.WoP, "attn_pad_w", s);
+        const PadArgs pa{(const uint16_t*)Wqkv, (const uint16_t*)WoT, (uint16_t*)w.Wp, (uint16_t*)w.WoP,
+                         gathered ? head_idx_k : nullptr, nullptr, ph, ph, H, hd, hw, d, 0, nullptr, nullptr};
+        rc = pad_heads(pa, false, s);
         if (rc != SDP_OK) return rc;
     }
 
@@ -1000,7 +1021,8 @@ int sdp::attn_fwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         a.lse = LSE_save;
         a.S = S, a.ph = ph, a.hd = hw;
         a.scale = 1.f / sqrtf((float)hd), a.scale2 = a.scale * 1.44269504088896340736f;
-        rc = launch_core(CORE_FWD, a, (int64_t)ph * Bt, "attn_core_fwd", s);
+        const TransposeJob wt{padded ? w.WoP : WoT, w.WoC, d, E, gathered && !padded ? w.rows_o : nullptr, E, d};
+        rc = launch_core(CORE_FWD, a, (int64_t)ph * Bt, &wt, 1, "attn_core_fwd", s);
     } else {
         AttnCoreDesc c;
         c.qkv = QKV_save, c.ldq = 3 * E, c.o_out = O_save, c.ldo = E, c.lse = LSE_save;
@@ -1009,10 +1031,6 @@ int sdp::attn_fwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     }
     if (rc != SDP_OK) return rc;
 
-    if (dtype == SDP_BF16) {
-        rc = transpose_rows(padded ? w.WoP : WoT, d, gathered && !padded ? w.rows_o : nullptr, E, d, w.WoC, E, "attn_wt_fwd", s);
-        if (rc != SDP_OK) return rc;
-    }
     GemmDesc op;
     op.name = "attn_out";
     op.M = T, op.N = d, op.K = E;
@@ -1058,17 +1076,12 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     const bool all_heads = !gathered && head_idx_k == nullptr;
 
     if (padded) {
-        rc = pad_heads(Wqkv, 3, gathered ? head_idx_k : nullptr, hr, H, hd, hw, d, w.Wp, "attn_pad_w", s);
+        // with the rows of the held heads in the padded operands, and where each of them goes (padding rows: nowhere)
+        const PadArgs pa{(const uint16_t*)Wqkv, (const uint16_t*)WoT, (uint16_t*)w.Wp, (uint16_t*)w.WoP,
+                         gathered ? head_idx_k : nullptr, head_idx_k, hr, ph, H, hd, hw, d, dw_layout == SDP_DW_SCATTER, w.rows_o,
+                         w.rows_qkv};
+        rc = pad_heads(pa, want_dw, s);
         if (rc != SDP_OK) return rc;
-        rc = pad_heads(WoT, 1, gathered ? head_idx_k : nullptr, hr, H, hd, hw, d, w.WoP, "attn_pad_w", s);
-        if (rc != SDP_OK) return rc;
-        if (want_dw) { // rows of the held heads in the padded operands, and where each of them goes (padding rows: nowhere)
-            ProfileScope ps("attn_rows", s);
-            pad_rows_kernel<<<(Eh + 255) / 256, 256, 0, s>>>(head_idx_k, ph, hd, hw, dw_layout == SDP_DW_SCATTER, w.rows_o,
-                                                             w.rows_qkv);
-            rc = launch_status();
-            if (rc != SDP_OK) return rc;
-        }
     } else if (!all_heads) {
         rc = head_rows(head_idx_k, ph, H, hd, w.rows_qkv, w.rows_o, s);
         if (rc != SDP_OK) return rc;
@@ -1093,8 +1106,16 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         a.dqkv = (uint16_t*)w.dQKV;
         a.S = S, a.ph = hr, a.hd = hw;
         a.scale = 1.f / sqrtf((float)hd), a.scale2 = a.scale * 1.44269504088896340736f;
-        rc = launch_core(CORE_DQ, a, (int64_t)hr * Bt, "attn_core_bwd_dq", s);
-        if (rc == SDP_OK) rc = launch_core(CORE_DKV, a, (int64_t)hr * Bt, "attn_core_bwd_dkv", s); // reads the delta written by the dQ kernel
+        // Wqkv's rows for dX; token-contiguous copies for the weight gradients
+        const int64_t ldt = ld_tokens(T);
+        const TransposeJob beside_dq[4] = {{padded ? w.Wp : Wqkv, w.Wc, d, 3 * E, gathered && !padded ? w.rows_qkv : nullptr, 3 * E, d},
+                                           {O_save, w.Ot, E, ldt, nullptr, T, E},
+                                           {X, w.Xt, d, ldt, nullptr, T, d},
+                                           {dY, w.dYt, d, ldt, nullptr, T, d}};
+        const TransposeJob beside_dkv{w.dQKV, w.dQKVt, 3 * E, ldt, nullptr, T, E}; // dQ
+        rc = launch_core(CORE_DQ, a, (int64_t)hr * Bt, beside_dq, want_dw ? 4 : 1, "attn_core_bwd_dq", s);
+        // reads the delta written by the dQ kernel
+        if (rc == SDP_OK) rc = launch_core(CORE_DKV, a, (int64_t)hr * Bt, &beside_dkv, want_dw ? 1 : 0, "attn_core_bwd_dkv", s);
         if (rc != SDP_OK) return rc;
     } else {
         AttnCoreDesc c;
@@ -1105,11 +1126,6 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         if (rc != SDP_OK) return rc;
     }
 
-    if (dtype == SDP_BF16) {
-        rc = transpose_rows(padded ? w.Wp : Wqkv, d, gathered && !padded ? w.rows_qkv : nullptr, 3 * E, d, w.Wc, 3 * E,
-                            "attn_wt_bwd", s);
-        if (rc != SDP_OK) return rc;
-    }
     GemmDesc dx;
     dx.name = "attn_dx";
     dx.M = T, dx.N = d, dx.K = 3 * E;
@@ -1148,11 +1164,8 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     }
 
     const int64_t ldt = ld_tokens(T);
-    const TransposeJob tj[4] = {{w.dQKV, w.dQKVt, 3 * E, ldt, nullptr, T, 3 * E},
-                                {O_save, w.Ot, E, ldt, nullptr, T, E},
-                                {X, w.Xt, d, ldt, nullptr, T, d},
-                                {dY, w.dYt, d, ldt, nullptr, T, d}};
-    rc = transpose_batch(tj, 4, "attn_tr_bwd", s);
+    // dK, dV; the other copies were made beside the core
+    rc = transpose_rows((const uint16_t*)w.dQKV + E, 3 * E, nullptr, T, 2 * E, (uint16_t*)w.dQKVt + (size_t)E * ldt, ldt, "attn_tr_bwd", s);
     if (rc != SDP_OK) return rc;
 
     // the four weight gradients share one shape (Eh x d, depth T): dWq, dWk, dWv from the three row blocks of

@@ -41,6 +41,7 @@
 // run as one launch of 3 x tiles workgroups, so that their few, deep tiles fill the CUs together.
 #include "sdp_internal.h"
 #include "sdp_swiglu.h"
+#include "sdp_transpose.h"
 
 #include <hip/hip_ext.h>
 
@@ -182,8 +183,18 @@ struct Geometry {
     static_assert(LDS <= 160 * 1024, "LDS of one CU");
 };
 
+// Transposes carried by a launch (the MLP's gate_up and dact): workgroups from g.ntot on do `side_tiles` tiles at a time.
+struct NoSide {};
+constexpr bool carries_side(int op) { return op == OP_GATE_UP || op == OP_DACT; }
+template <int OP>
+using SideArg = std::conditional_t<carries_side(OP), SideJobs, NoSide>;
+// tiles each 256 threads of a workgroup take at once: as many as the contraction's LDS holds, at most 8 (64 registers)
+constexpr int side_tiles(int threads, int lds) {
+    return lds / (threads / 256 * kTransposeLds) < 8 ? lds / (threads / 256 * kTransposeLds) : 8;
+}
+
 template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int OP>
-__global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1) void sdp_gemm_kernel(Dev g) {
+__global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1) void sdp_gemm_kernel(Dev g, SideArg<OP> side) {
     using Geo = Geometry<BM, BN, WAVES_M, WAVES_N, EPI>;
     constexpr int NW = Geo::NW, WM = Geo::WM, WN = Geo::WN, FM = Geo::FM, FN = Geo::FN;
     constexpr int A_BYTES = Geo::A_BYTES, B_BYTES = Geo::B_BYTES;
@@ -195,6 +206,15 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
     static_assert(!kFwd || FN % 2 == 0, "gate/up fragments come in pairs");
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
 
+    if constexpr (carries_side(OP)) {
+        if ((int)blockIdx.x >= g.ntot) {
+            constexpr int HALVES = NW / 4, N = side_tiles(NW * 64, Geo::LDS);
+            const int half = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
+            side_transposes<N>(side, ((int)blockIdx.x - g.ntot) * HALVES + half, smem + half * N * kTransposeLds,
+                               threadIdx.x & 255);
+            return;
+        }
+    }
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6); // wave-uniform: keeps what derives from it scalar
     const int wm = wave / WAVES_N, wn = wave % WAVES_N;
@@ -1022,8 +1042,17 @@ int tail_reduce(const Dev& g, const GemmDesc& d, hipStream_t s) {
     return launch_status();
 }
 
+// Whether a launch of `tiles` tiles, `round` us a round, carries `wgs` workgroups of transposes: when the CUs that its last
+// round leaves idle get through them meanwhile.  A workgroup moves 16 tiles, one after the other about 5 us each and 5 more
+// for the first.  T = 5000, d = 1600, p = 2664 (28 us of transposes a worker beside 420 and 220 tiles): step of two workers
+// 1020 -> 980 us; beside the 512 tiles of T = 8192, p = 2048, two full rounds, W2's transpose cost 12 us more than on its own.
+bool carry(int64_t tiles, double round, int64_t wgs) {
+    const int64_t idle = tiles % kNumCU ? kNumCU - tiles % kNumCU : 0;
+    return idle > 0 && (double)((wgs + idle - 1) / idle) * 5.0 + 5.0 <= 1.2 * round;
+}
+
 template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int OP>
-int launch_cfg(const GemmDesc& d, hipStream_t s) {
+int launch_cfg(const GemmDesc& d, double round, hipStream_t s) {
     using Geo = Geometry<BM, BN, WAVES_M, WAVES_N, EPI>;
     constexpr int NTHREADS = WAVES_M * WAVES_N * 64;
     constexpr int LDS = Geo::LDS;
@@ -1086,6 +1115,20 @@ int launch_cfg(const GemmDesc& d, hipStream_t s) {
         std::lock_guard<std::mutex> lk(g_shape_mu);
         g_last_shape[d.name] = {BM, BN, g.group_m, g.np0 > 0 ? 1 : 0};
     }
+    SideArg<OP> side{};
+    if constexpr (carries_side(OP)) {
+        if (d.nside > 0) {
+            constexpr int PER_WG = side_tiles(NTHREADS, LDS) * (NTHREADS / 256);
+            const int t = side_jobs(d.side, d.nside, &side);
+            const int64_t wgs = ((int64_t)t + PER_WG - 1) / PER_WG;
+            if (t > 0 && carry(g.ntot, round, wgs) && grid + wgs <= 0x7FFFFFFF) {
+                grid += wgs;
+            } else {
+                const int rc = transpose_batch(d.side, d.nside, d.side_name, s);
+                if (rc != SDP_OK) return rc;
+            }
+        }
+    }
     auto kern = sdp_gemm_kernel<BM, BN, WAVES_M, WAVES_N, EPI, OP>;
     // once per instantiation (initialisation of a function-local static is thread-safe)
     static const hipError_t attr =
@@ -1096,9 +1139,9 @@ int launch_cfg(const GemmDesc& d, hipStream_t s) {
     // microseconds on either side of it.
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (profile_launch_events(d.name, &ev0, &ev1))
-        hipExtLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NTHREADS), (uint32_t)LDS, s, ev0, ev1, 0u, g);
+        hipExtLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NTHREADS), (uint32_t)LDS, s, ev0, ev1, 0u, g, side);
     else
-        kern<<<dim3((unsigned)grid), NTHREADS, LDS, s>>>(g);
+        kern<<<dim3((unsigned)grid), NTHREADS, LDS, s>>>(g, side);
     const int rc = launch_status();
     if (OP == OP_DW_TAIL && rc == SDP_OK) return tail_reduce<BM, BN>(g, d, s);
     return rc;
@@ -1131,22 +1174,24 @@ constexpr bool shape_exists(int epi, int shape) {
 
 // nbatch problems, the depth of each cut into ksplit ranges that are problems of their own
 template <int EPI>
-Shape choose_shape(const GemmDesc& d, int nbatch, int ksplit) {
+Shape choose_shape(const GemmDesc& d, int nbatch, int ksplit, double* round = nullptr) {
     const int force = tuning().force_tile - 1;
-    if (force >= 0 && shape_exists(EPI, force)) return (Shape)force;
     const int ncols = EPI == EPI_SWIGLU_FWD ? 2 * d.N : d.N; // gate and up interleaved double the tile columns
     const double steps = ((d.K + BK - 1) / BK + ksplit - 1) / ksplit * (EPI == EPI_DUAL_ACC ? 2 : 1);
     const EpilogueCost e = epilogue_cost(EPI);
     Shape best = T256x256;
     double best_cost = -1;
     for (int i = 0; i < NUM_SHAPES; ++i) {
-        if (!shape_exists(EPI, i)) continue;
+        if (!shape_exists(EPI, i) || (force >= 0 && i != force && shape_exists(EPI, force))) continue;
         const ShapeInfo& h = kShapes[i];
         const int64_t tiles = (int64_t)((d.M + h.bm - 1) / h.bm) * ((ncols + h.bn - 1) / h.bn) * nbatch * ksplit;
         const int64_t rounds = (tiles + kNumCU - 1) / kNumCU;
         const double busy = tiles < kNumCU ? (double)tiles / kNumCU : 1.0;
         const double cost = (double)rounds * (steps * (h.step0 + (h.step1 - h.step0) * busy) + e.e0 + e.e1 * h.bm * h.bn / 1024);
-        if (best_cost < 0 || cost < best_cost) best_cost = cost, best = (Shape)i;
+        if (best_cost < 0 || cost < best_cost) {
+            best_cost = cost, best = (Shape)i;
+            if (round) *round = cost / rounds;
+        }
     }
     return best;
 }
@@ -1154,14 +1199,15 @@ Shape choose_shape(const GemmDesc& d, int nbatch, int ksplit) {
 template <int EPI, int OP>
 int launch(const GemmDesc& d, hipStream_t s) {
     const int nbatch = OP == OP_DW || OP == OP_DW_TAIL || OP == OP_DW_SPLIT ? d.nbatch : 1;
-    const Shape shape = choose_shape<EPI>(d, nbatch, OP == OP_DW_SPLIT ? d.ksplit : 1);
-    if (shape == T256x256) return launch_cfg<256, 256, 2, 4, EPI, OP>(d, s);
-    if (shape == T128x256) return launch_cfg<128, 256, 2, 4, EPI, OP>(d, s);
-    if (shape == T128x128) return launch_cfg<128, 128, 4, 2, EPI, OP>(d, s);
+    double round = 0;
+    const Shape shape = choose_shape<EPI>(d, nbatch, OP == OP_DW_SPLIT ? d.ksplit : 1, &round);
+    if (shape == T256x256) return launch_cfg<256, 256, 2, 4, EPI, OP>(d, round, s);
+    if (shape == T128x256) return launch_cfg<128, 256, 2, 4, EPI, OP>(d, round, s);
+    if (shape == T128x128) return launch_cfg<128, 128, 4, 2, EPI, OP>(d, round, s);
     if constexpr (EPI != EPI_SWIGLU_FWD) {
-        if (shape == T256x192) return launch_cfg<256, 192, 4, 2, EPI, OP>(d, s);
-        if (shape == T128x192) return launch_cfg<128, 192, 4, 2, EPI, OP>(d, s);
-        if (shape == T64x64) return launch_cfg<64, 64, 2, 2, EPI, OP>(d, s);
+        if (shape == T256x192) return launch_cfg<256, 192, 4, 2, EPI, OP>(d, round, s);
+        if (shape == T128x192) return launch_cfg<128, 192, 4, 2, EPI, OP>(d, round, s);
+        if (shape == T64x64) return launch_cfg<64, 64, 2, 2, EPI, OP>(d, round, s);
     }
     return SDP_ERR_UNSUPPORTED; // not reached: choose_shape returns one of the above
 }

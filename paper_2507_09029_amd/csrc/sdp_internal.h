@@ -116,6 +116,11 @@ struct GemmDesc {
     // round's tiles into ranges (gemm_choose_tail), which a second small kernel adds up.
     void* tail_ws = nullptr;
     const char* tail_name = "dw_tail_reduce"; // profile name of that second kernel
+    // SWIGLU_FWD / SWIGLU_BWD, MFMA kernel: transposes that have to be done when the contraction is, by extra workgroups of
+    // its launch or by one of their own before it
+    const struct TransposeJob* side = nullptr;
+    int nside = 0;
+    const char* side_name = "transposes";
 };
 
 // tags that give each call site of the MFMA contraction its own kernel symbol
@@ -192,6 +197,10 @@ struct TransposeJob {
     int R, C;
 };
 int transpose_batch(const TransposeJob* jobs, int n, const char* name, hipStream_t s);
+// The same jobs prepared for a launch that carries them (sdp_transpose.h): their number of 64 x 64 tiles, or -1 when
+// transpose_batch would refuse them.
+struct SideJobs;
+int side_jobs(const TransposeJob* jobs, int n, SideJobs* side);
 
 // crank[n] for n < N from the ascending list cidx[0 .. pc): the number of listed columns below n if n is listed,
 // else -1 - that number

@@ -58,7 +58,12 @@ __global__ __launch_bounds__(256) void column_ranks_kernel(const int32_t* __rest
 
 int run(int dtype, const GemmDesc& g, hipStream_t s) {
     if (dtype == SDP_F32) return gemm_f32(g, s);
-    return gemm_mfma_supported(g) ? gemm_mfma_bf16(g, s) : gemm_simple(g, s);
+    if (gemm_mfma_supported(g)) return gemm_mfma_bf16(g, s);
+    if (g.nside > 0) {
+        const int rc = transpose_batch(g.side, g.nside, g.side_name, s);
+        if (rc != SDP_OK) return rc;
+    }
+    return gemm_simple(g, s);
 }
 
 } // namespace
@@ -117,11 +122,8 @@ int sdp::mlp_fwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
     void* Act = w;
     void* W2c = w + round_up((size_t)T * n * e, 256);
 
-    if (dtype == SDP_BF16) {
-        rc = transpose_rows(W2T, d, gather, n, d, W2c, n, "mlp_wt_fwd", s);
-        if (rc != SDP_OK) return rc;
-    }
-
+    // bf16: the down projection reads W2c, its weights transposed; made beside gate_up, which does not need them
+    const TransposeJob wt{W2T, W2c, d, n, gather, n, d};
     GemmDesc gu;
     gu.name = "mlp_gate_up";
     gu.M = T, gu.N = n, gu.K = d;
@@ -129,6 +131,7 @@ int sdp::mlp_fwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
     gu.B = W1, gu.B2 = W3, gu.ldb = d, gu.b_gather = gather, gu.b_rows = F;
     gu.epilogue = EPI_SWIGLU_FWD;
     gu.C = G_save, gu.C2 = U_save, gu.C3 = Act, gu.ldc = n;
+    if (dtype == SDP_BF16) gu.side = &wt, gu.nside = 1, gu.side_name = "mlp_wt_fwd";
     rc = run(dtype, gu, s);
     if (rc != SDP_OK) return rc;
 
@@ -231,13 +234,12 @@ int sdp::mlp_bwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
         return rc != SDP_OK ? rc : gemm_f32(dx, s);
     }
 
-    // the four operand copies of the backward pass as one launch (X^T, dY^T only feed the weight gradients)
+    // the four operand copies of the backward pass (X^T, dY^T only feed the weight gradients), made beside dact, which needs
+    // none of them
     const TransposeJob tj[4] = {{W1, W1c, d, n, gather, n, d},
                                 {W3, W3c, d, n, gather, n, d},
                                 {X, XT, d, ld_tokens(T), nullptr, T, d},
                                 {dY, dYT, d, ld_tokens(T), nullptr, T, d}};
-    rc = transpose_batch(tj, want_dw ? 4 : 2, "mlp_tr_bwd", s);
-    if (rc != SDP_OK) return rc;
 
     // weight-gradient contraction (set up first: whether it can take the MFMA path decides what the
     // activation-gradient kernel writes)
@@ -283,6 +285,7 @@ int sdp::mlp_bwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
         rc = column_ranks(idx_k, p, F, ranks, s);
         if (rc != SDP_OK) return rc;
     }
+    da.side = tj, da.nside = want_dw ? 4 : 2, da.side_name = "mlp_tr_bwd";
     rc = run(dtype, da, s);
     if (rc != SDP_OK) return rc;
 
