@@ -63,18 +63,21 @@ int sample_masks(int K, int F, int p, uint64_t seed, bool cover, uint8_t* m) {
     for (int k = 0; k < K; ++k)
         for (int j = 0; j < F; ++j) c[j] += m[(size_t)k * F + j];
     Stream rng(seed, (uint64_t)K);
-    std::vector<int32_t> cand;
-    cand.reserve(F);
+    std::vector<int32_t> cand(F);
     for (int j = 0; j < F; ++j) {
         if (c[j] > 0) continue;
         const int k0 = (int)rng.below((uint64_t)K);
         for (int step = 0; step < K; ++step) {
             uint8_t* row = m + (size_t)((k0 + step) % K) * F;
-            cand.clear();
-            for (int q = 0; q < F; ++q)
-                if (row[q] && c[q] > 1) cand.push_back(q);
-            if (cand.empty()) continue;
-            const int give = cand[rng.below((uint64_t)cand.size())];
+            // without a branch per column: the branch is a coin toss, and with it the two workers' masks of F = 4264 took 7
+            // or 24 ms from one build to the next, by where the loop came to lie
+            int n = 0;
+            for (int q = 0; q < F; ++q) {
+                cand[n] = q;
+                n += (row[q] != 0) & (c[q] > 1);
+            }
+            if (n == 0) continue;
+            const int give = cand[rng.below((uint64_t)n)];
             row[give] = 0;
             --c[give];
             row[j] = 1;
