@@ -1031,12 +1031,19 @@ int sdp::attn_fwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     }
     if (rc != SDP_OK) return rc;
 
+    // fp32 reads WoT itself: an output that takes its place needs a copy
+    const int32_t* wo_rows = gathered ? w.rows_o : nullptr;
+    if (dtype == SDP_F32 && overlap({{Y, (size_t)T * d * 4}}, {{WoT, (size_t)H * hd * d * 4}})) {
+        rc = copy_rows_f32((const float*)WoT, wo_rows, E, d, (float*)w.WoC, "attn_wt_fwd", s);
+        if (rc != SDP_OK) return rc;
+        WoT = w.WoC, wo_rows = nullptr;
+    }
     GemmDesc op;
     op.name = "attn_out";
     op.M = T, op.N = d, op.K = E;
     op.A = O_save, op.lda = E;
     if (dtype == SDP_BF16) op.B = w.WoC, op.ldb = E;
-    else op.B = WoT, op.ldb = d, op.b_km = 1, op.b_gather = gathered ? w.rows_o : nullptr, op.b_rows = (int64_t)H * hd;
+    else op.B = WoT, op.ldb = d, op.b_km = 1, op.b_gather = wo_rows, op.b_rows = wo_rows ? (int64_t)H * hd : E;
     op.epilogue = EPI_STORE;
     op.C = Y, op.ldc = d;
     op.R = residual, op.ldr = d;
@@ -1126,18 +1133,36 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         if (rc != SDP_OK) return rc;
     }
 
+    const int64_t part = (int64_t)(dw_layout == SDP_DW_SCATTER ? H * hd : ph * hd) * d; // elements of one weight gradient
+    const int32_t* w_rows = gathered ? w.rows_qkv : nullptr;
+    if (dtype == SDP_F32) {
+        // What follows reads Wqkv, X, dY and O_save as they are; where an output takes the place of one of these (dX over dY, a
+        // gradient over its weights), copies of them, as the bf16 path always does.
+        const size_t tok_b = (size_t)T * d * 4, dw_b = (size_t)part * 4;
+        const Extent x{X, tok_b}, dy{dY, tok_b}, o{O_save, (size_t)T * E * 4}, wq{Wqkv, (size_t)3 * H * hd * d * 4}, ox{dX, tok_b};
+        if (want_dw ? overlap({ox, {dWqkv, 3 * dw_b}, {dWoT, dw_b}}, {x, dy, o, wq}) : overlap({ox}, {wq})) {
+            const struct { const void* in; const int32_t* rows; int R, C; void* out; } copies[4] = {
+                {Wqkv, w_rows, 3 * E, d, w.Wc}, {X, nullptr, T, d, w.Xt}, {dY, nullptr, T, d, w.dYt}, {O_save, nullptr, T, E, w.Ot}};
+            for (int i = 0; i < (want_dw ? 4 : 1); ++i) {
+                rc = copy_rows_f32((const float*)copies[i].in, copies[i].rows, copies[i].R, copies[i].C, (float*)copies[i].out,
+                                   "attn_copy_bwd", s);
+                if (rc != SDP_OK) return rc;
+            }
+            Wqkv = w.Wc, X = w.Xt, dY = w.dYt, O_save = w.Ot, w_rows = nullptr;
+        }
+    }
+
     GemmDesc dx;
     dx.name = "attn_dx";
     dx.M = T, dx.N = d, dx.K = 3 * E;
     dx.A = w.dQKV, dx.lda = 3 * E;
     if (dtype == SDP_BF16) dx.B = w.Wc, dx.ldb = 3 * E;
-    else dx.B = Wqkv, dx.ldb = d, dx.b_km = 1, dx.b_gather = gathered ? w.rows_qkv : nullptr, dx.b_rows = (int64_t)3 * H * hd;
+    else dx.B = Wqkv, dx.ldb = d, dx.b_km = 1, dx.b_gather = w_rows, dx.b_rows = w_rows ? (int64_t)3 * H * hd : 3 * E;
     dx.epilogue = EPI_STORE;
     dx.C = dX, dx.ldc = d;
     dx.R = dx_residual, dx.ldr = d;
     if (!want_dw) return run(dtype, dx, s);
 
-    const int64_t part = (int64_t)(dw_layout == SDP_DW_SCATTER ? H * hd : ph * hd) * d;
     if (dtype == SDP_F32) { // every operand as it is stored: dQKV, O, X, dY depth-major, the held heads' columns by their list
         GemmDesc all[3];
         GemmDesc &dw = all[1], &dwo = all[2];

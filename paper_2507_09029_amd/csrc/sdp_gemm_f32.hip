@@ -720,18 +720,6 @@ int gemm_f32_group(const GemmDesc* d, int n, const char* name, hipStream_t s) {
                    : !d[i].a_km || d[i].epilogue != EPI_STORE)
             return SDP_ERR_UNSUPPORTED;
     }
-    // the first problem's output may be an operand of the others in the caller's memory (dX in place of dY): they then
-    // have to follow one another
-    const uintptr_t c0 = (uintptr_t)d[0].C, c1 = c0 + ((size_t)d[0].M * d[0].ldc) * 4;
-    auto apart = [&](const void* p, int64_t rows, int64_t ld) {
-        const uintptr_t q = (uintptr_t)p;
-        return !p || q >= c1 || q + (size_t)rows * ld * 4 <= c0;
-    };
-    for (int i = 1; i < n; ++i) {
-        if (!apart(d[i].A, d[i].K, d[i].lda) || !apart(d[i].B, d[i].K, d[i].ldb)) return SDP_ERR_UNSUPPORTED;
-        for (int z = 0; z < d[i].nbatch; ++z)
-            if (!apart(d[i].Ab[z], d[i].K, d[i].lda) || !apart(d[i].Bb[z], d[i].K, d[i].ldb)) return SDP_ERR_UNSUPPORTED;
-    }
     // Worth it while d[0] alone leaves room on the chip.  Launches of 512 x 512 outputs, depth 2 x 1376, beside three of
     // 1376 x 512, depth 512: step 114 -> 109 us; 1000 x 512, depth 2 x 1600 (512 tiles of 32 x 32, two on every CU): 209 ->
     // 215 us.

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <initializer_list>
+
 #include "sdp.h"
 #include "sdp_measure.h"
 
@@ -32,6 +34,20 @@ inline int launch_status() { return hip_status(hipGetLastError()); }
 
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
+
+// memory of a caller's tensor, and whether one of `out` shares any with one of `in`
+struct Extent {
+    const void* p;
+    size_t bytes;
+};
+inline bool overlap(std::initializer_list<Extent> out, std::initializer_list<Extent> in) {
+    for (const Extent& o : out)
+        for (const Extent& i : in) {
+            const uintptr_t a = (uintptr_t)o.p, b = (uintptr_t)i.p;
+            if (a < b + i.bytes && b < a + o.bytes) return true;
+        }
+    return false;
+}
 
 // ---- contraction descriptor --------------------------------------------------------------------
 // C[M][N] = sum_k A(m,k) * B(k,n), fp32 accumulation, all matrices row-major.
@@ -129,7 +145,8 @@ enum GemmOp { OP_GATE_UP = 0, OP_DOWN = 1, OP_DACT = 2, OP_DX = 3, OP_DW = 4, OP
 // fp32 contraction on the matrix cores, any shape.
 int gemm_f32(const GemmDesc& g, hipStream_t s);
 // A contraction d[0] with a row-major left operand (STORE or DUAL_ACC) and one or two with depth-major ones (STORE), all with
-// depth-major right operands, none an input of another, as one launch.  SDP_ERR_UNSUPPORTED: not these; nothing was launched.
+// depth-major right operands, none of whose outputs shares memory with an operand, as one launch.  SDP_ERR_UNSUPPORTED: not
+// these; nothing was launched.
 int gemm_f32_group(const GemmDesc* d, int n, const char* name, hipStream_t s);
 // Plain LDS-tiled bf16 contraction, any shape: what the MFMA kernel's address ranges do not take.
 int gemm_simple(const GemmDesc& g, hipStream_t s);
@@ -201,6 +218,9 @@ int transpose_batch(const TransposeJob* jobs, int n, const char* name, hipStream
 // transpose_batch would refuse them.
 struct SideJobs;
 int side_jobs(const TransposeJob* jobs, int n, SideJobs* side);
+
+// out[r][:] = in[rows ? rows[r] : r][:], R rows of C floats, both without gaps
+int copy_rows_f32(const float* in, const int32_t* rows, int R, int C, float* out, const char* name, hipStream_t s);
 
 // crank[n] for n < N from the ascending list cidx[0 .. pc): the number of listed columns below n if n is listed,
 // else -1 - that number

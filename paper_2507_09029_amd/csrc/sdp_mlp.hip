@@ -122,8 +122,17 @@ int sdp::mlp_fwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
     void* Act = w;
     void* W2c = w + round_up((size_t)T * n * e, 256);
 
-    // bf16: the down projection reads W2c, its weights transposed; made beside gate_up, which does not need them
+    // The down projection reads W2: bf16 its transpose W2c, made beside gate_up, which does not need it; fp32 W2T itself.
+    // An output that takes W2T's place is written too early for that: W2c is then made first (fp32: W2T's rows).
+    const size_t out_b = (size_t)T * n * e, w2_b = (size_t)F * d * e;
     const TransposeJob wt{W2T, W2c, d, n, gather, n, d};
+    const bool w2_first = dtype == SDP_F32 ? overlap({{Y, (size_t)T * d * e}, {G_save, out_b}, {U_save, out_b}}, {{W2T, w2_b}})
+                                           : overlap({{G_save, out_b}, {U_save, out_b}}, {{W2T, w2_b}});
+    if (w2_first) {
+        rc = dtype == SDP_F32 ? copy_rows_f32((const float*)W2T, gather, n, d, (float*)W2c, "mlp_wt_fwd", s)
+                              : transpose_batch(&wt, 1, "mlp_wt_fwd", s);
+        if (rc != SDP_OK) return rc;
+    }
     GemmDesc gu;
     gu.name = "mlp_gate_up";
     gu.M = T, gu.N = n, gu.K = d;
@@ -131,7 +140,7 @@ int sdp::mlp_fwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
     gu.B = W1, gu.B2 = W3, gu.ldb = d, gu.b_gather = gather, gu.b_rows = F;
     gu.epilogue = EPI_SWIGLU_FWD;
     gu.C = G_save, gu.C2 = U_save, gu.C3 = Act, gu.ldc = n;
-    if (dtype == SDP_BF16) gu.side = &wt, gu.nside = 1, gu.side_name = "mlp_wt_fwd";
+    if (dtype == SDP_BF16 && !w2_first) gu.side = &wt, gu.nside = 1, gu.side_name = "mlp_wt_fwd";
     rc = run(dtype, gu, s);
     if (rc != SDP_OK) return rc;
 
@@ -140,6 +149,7 @@ int sdp::mlp_fwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
     dn.M = T, dn.N = d, dn.K = n;
     dn.A = Act, dn.lda = n;
     if (dtype == SDP_BF16) dn.B = W2c, dn.ldb = n;
+    else if (w2_first) dn.B = W2c, dn.ldb = d, dn.b_km = 1, dn.b_rows = n;
     else dn.B = W2T, dn.ldb = d, dn.b_km = 1, dn.b_gather = gather, dn.b_rows = F;
     dn.epilogue = EPI_STORE;
     dn.C = Y, dn.ldc = d;
@@ -206,12 +216,27 @@ int sdp::mlp_bwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
         da.C = dG, da.C2 = dU, da.C3 = Act, da.ldc = n;
         rc = gemm_f32(da, s);
         if (rc != SDP_OK) return rc;
+        // dX and the weight gradients read X, dY, W1 and W3 as they are.  Where an output takes the place of one of these (dX
+        // over dY, a gradient over its weights), they read copies, as the bf16 path always does.
+        const size_t tok_b = (size_t)T * d * e, w_b = (size_t)F * d * e;
+        const size_t dw_b = (size_t)(dw_layout == SDP_DW_SCATTER ? F : p) * d * e;
+        const Extent x{X, tok_b}, dy{dY, tok_b}, w1{W1, w_b}, w3{W3, w_b}, ox{dX, tok_b};
+        if (want_dw ? overlap({ox, {dW1, dw_b}, {dW3, dw_b}, {dW2T, dw_b}}, {x, dy, w1, w3}) : overlap({ox}, {w1, w3})) {
+            const struct { const void* in; const int32_t* rows; int R; void* out; } copies[4] = {
+                {W1, gather, n, W1c}, {W3, gather, n, W3c}, {X, nullptr, T, XT}, {dY, nullptr, T, dYT}};
+            for (int i = 0; i < (want_dw ? 4 : 2); ++i) {
+                rc = copy_rows_f32((const float*)copies[i].in, copies[i].rows, copies[i].R, d, (float*)copies[i].out, "mlp_copy_bwd", s);
+                if (rc != SDP_OK) return rc;
+            }
+            if (want_dw && dx_residual == dY) dx_residual = dYT;
+            W1 = W1c, W3 = W3c, X = XT, dY = dYT, gather = nullptr;
+        }
         GemmDesc both[2];
         GemmDesc &dx = both[0], &dw = both[1];
         dx.name = "mlp_dx";
         dx.M = T, dx.N = d, dx.K = n;
         dx.A = dG, dx.A2 = dU, dx.lda = n;
-        dx.B = W1, dx.B2 = W3, dx.ldb = d, dx.b_km = 1, dx.b_gather = gather, dx.b_rows = F;
+        dx.B = W1, dx.B2 = W3, dx.ldb = d, dx.b_km = 1, dx.b_gather = gather, dx.b_rows = gather ? F : n;
         dx.epilogue = EPI_DUAL_ACC;
         dx.C = dX, dx.ldc = d;
         dx.R = dx_residual, dx.ldr = d;

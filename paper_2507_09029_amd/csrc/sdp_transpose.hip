@@ -32,7 +32,22 @@ __global__ __launch_bounds__(256) void transpose_rows_vec_kernel(TransposeJob j0
     TransposeTile::store(jb, r0, c0, lds, threadIdx.x);
 }
 
+// A copy of an fp32 operand whose memory an output of the same call takes over; no path that matters for speed.
+__global__ __launch_bounds__(256) void copy_rows_f32_kernel(const float* in, const int32_t* rows, int C, int64_t n, float* out) {
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride)
+        out[i] = rows ? in[rows[i / C] * (int64_t)C + i % C] : in[i];
+}
+
 } // namespace
+
+int copy_rows_f32(const float* in, const int32_t* rows, int R, int C, float* out, const char* name, hipStream_t s) {
+    if (R < 1 || C < 1) return SDP_ERR_SHAPE;
+    const int64_t n = (int64_t)R * C;
+    ProfileScope ps(name, s);
+    copy_rows_f32_kernel<<<(unsigned)std::min<int64_t>((n + 255) / 256, 4096), 256, 0, s>>>(in, rows, C, n, out);
+    return launch_status();
+}
 
 static bool vec_ok(const TransposeJob& t) {
     return t.C % 8 == 0 && t.ld_out >= t.R && t.ld_in % 8 == 0 && t.ld_out % 8 == 0 && aligned16(t.in) && aligned16(t.out);

@@ -195,6 +195,53 @@ def test_attention_f32_core(sdp, orc, w, mode):
     run_case(sdp, orc, w, [0], dw_layout="scatter" if w.S % 2 else "compact", mode=mode)
 
 
+TAKEN = {"dX over dY": {0: "dY"}, "dX over X": {0: "X"}, "dX over O": {0: "O"}, "gradients over weights": {1: "Wqkv", 2: "WoT"},
+         "dX over X, gradients over weights": {0: "X", 1: "Wqkv", 2: "WoT"}, "a gradient over dY": {2: "dY"}}
+
+
+@pytest.mark.parametrize("taken", TAKEN.values(), ids=TAKEN.keys())
+@pytest.mark.parametrize("mode", ["fm", "bm"])
+@pytest.mark.parametrize("dtype,hd", [("f32", 32), ("bf16", 64), ("bf16", 50), ("bf16", 72)])
+def test_outputs_may_take_the_place_of_operands(sdp, dtype, hd, mode, taken):
+    """Every operand is read before an output is written, in both dtypes."""
+    w = AttnWorkload("in_place", 2, 100, 2 * hd + hd % 8 * 2, 4, hd, 2, 2, 50, dtype)
+    op = dict(zip(("Wqkv", "WoT"), (t.cuda() for t in workloads.attn_weights(w))))
+    mask, idx, pos, cov = sdp.make_masks(w.K, w.H, w.ph, w.mask_seed, True)
+    op["X"], op["dY"] = (t.cuda() for t in workloads.attn_batch(w, 0))
+    a = (mode, w.Bt, w.S, w.hd)
+    Y, QKV, op["O"], LSE = sdp.masked_attn_fwd(*a, op["X"], op["Wqkv"], op["WoT"], idx[0])
+
+    def bwd(o, out):
+        return sdp.masked_attn_bwd(*a, o["X"], o["dY"], o["Wqkv"], o["WoT"], idx[0], QKV, o["O"], LSE, dw_layout="scatter", out=out)
+
+    fresh = [torch.zeros_like(op[n]) for n in ("X", "Wqkv", "WoT")]
+    want = bwd(op, tuple(fresh))
+    mine = {n: t.clone() for n, t in op.items()}
+    out = tuple(mine[taken[i]].view(-1)[: t.numel()].view(t.shape) if i in taken and mine[taken[i]].numel() >= t.numel() else t.clone()
+                for i, t in enumerate(fresh))
+    got = bwd(mine, out)
+    rows = torch.cat([torch.arange(int(h) * hd, int(h) * hd + hd) for h in idx[0]]).cuda()
+    for i, (x, y) in enumerate(zip(got, want)):
+        if i > 0:
+            x, y = x[..., rows, :], y[..., rows, :]
+        assert (x.double() - y.double()).abs().max() <= (1e-5 if dtype == "f32" else 1e-2) * y.abs().max(), f"output {i}"
+
+
+@pytest.mark.parametrize("mode", ["fm", "bm"])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+def test_forward_output_may_take_the_place_of_its_weights(sdp, dtype, mode):
+    w = AttnWorkload("in_place_fwd", 1, 60, 64, 4, 32, 2, 2, 51, dtype)
+    Wqkv, WoT = (t.cuda() for t in workloads.attn_weights(w))
+    mask, idx, pos, cov = sdp.make_masks(w.K, w.H, w.ph, w.mask_seed, True)
+    X = workloads.attn_batch(w, 0)[0].cuda()
+    want = sdp.masked_attn_fwd(mode, w.Bt, w.S, w.hd, X, Wqkv, WoT, idx[0])
+    mine = WoT.clone()
+    out = (mine[: w.T],) + tuple(torch.empty_like(t) for t in want[1:])
+    got = sdp.masked_attn_fwd(mode, w.Bt, w.S, w.hd, X, Wqkv, mine, idx[0], out=out)
+    for x, y in zip(got, want):
+        assert (x.double() - y.double()).abs().max() <= (1e-5 if dtype == "f32" else 1e-2) * y.abs().max()
+
+
 @pytest.mark.parametrize("w", BM_CASES, ids=[w.name for w in BM_CASES])
 def test_attention_backward_masking_all_outputs(sdp, orc, w):
     """Dense forward and dX, weight gradients on the held heads only."""

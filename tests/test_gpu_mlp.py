@@ -135,6 +135,59 @@ def test_f32_dx_may_take_the_place_of_dy(sdp):
         assert (a - b).abs().max() <= 1e-5 * b.abs().max()
 
 
+# outputs in the memory of operands: (output position in the call's results, operand)
+TAKEN = {"dX over dY": {0: "dY"}, "dX over X": {0: "X"}, "gradients over weights": {1: "W1", 2: "W3", 3: "W2T"},
+         "dX over X, gradients over weights": {0: "X", 1: "W1", 2: "W3", 3: "W2T"}, "gradients over other weights": {1: "W3", 2: "W1"},
+         "a gradient over dY and X": {1: "dY", 2: "X"}}
+
+
+@pytest.mark.parametrize("taken", TAKEN.values(), ids=TAKEN.keys())
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("mode,layout,T,p", [("fm", "scatter", 264, 136), ("bm", "scatter", 264, 136), ("fm", "compact", 136, 136)])
+def test_outputs_may_take_the_place_of_operands(sdp, mode, layout, T, p, dtype, taken):
+    """The backward pass reads every operand before an output is written, in both dtypes."""
+    w = MlpWorkload("in_place", dtype, T, 72, 264, p, 2, mode, 27)
+    names = ("W1", "W3", "W2T")
+    op = dict(zip(names, (t.cuda() for t in workloads.mlp_weights(w))))
+    mask, idx, pos, cov = sdp.make_masks(w.K, w.F, w.p, w.mask_seed, True)
+    op["X"], op["dY"] = (t.cuda() for t in workloads.mlp_batch(w, 0))
+    Y, G, U = sdp.masked_mlp_fwd(mode, op["X"], *(op[n] for n in names), idx[0])
+    dw_shape = (w.F if layout == "scatter" else p, w.d)
+
+    def bwd(o, out):
+        return sdp.masked_mlp_bwd(mode, o["X"], o["dY"], *(o[n] for n in names), idx[0], G, U, dw_layout=layout, out=out)
+
+    fresh = [torch.zeros_like(op["X"])] + [torch.zeros(dw_shape, dtype=Y.dtype, device="cuda") for _ in range(3)]
+    want = bwd(op, tuple(fresh))
+    mine = {n: t.clone() for n, t in op.items()}
+    out = tuple(mine[taken[i]].view(-1)[: t.numel()].view(t.shape) if i in taken and mine[taken[i]].numel() >= t.numel() else t.clone()
+                for i, t in enumerate(fresh))
+    got = bwd(mine, out)
+    rows = idx[0].long() if layout == "scatter" else slice(None)
+    for i, (a, b) in enumerate(zip(got, want)):
+        if i > 0:
+            a, b = a[rows], b[rows]
+        # the same products; fp32 sums may come from another launch shape
+        assert (a.double() - b.double()).abs().max() <= (1e-5 if dtype == "f32" else 1e-2) * b.abs().max(), f"output {i}"
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("mode", ["fm", "bm"])
+@pytest.mark.parametrize("taken", [0, 1, 2], ids=["Y", "G", "U"])
+def test_forward_outputs_may_take_the_place_of_W2(sdp, dtype, mode, taken):
+    w = MlpWorkload("in_place_fwd", dtype, 136, 264, 264, 136, 2, mode, 28)
+    W1, W3, W2T = (t.cuda() for t in workloads.mlp_weights(w))
+    mask, idx, pos, cov = sdp.make_masks(w.K, w.F, w.p, w.mask_seed, True)
+    X = workloads.mlp_batch(w, 0)[0].cuda()
+    want = sdp.masked_mlp_fwd(mode, X, W1, W3, W2T, idx[0])
+    mine = W2T.clone()
+    out = [torch.empty_like(t) for t in want]
+    out[taken] = mine.view(-1)[: want[taken].numel()].view(want[taken].shape)
+    got = sdp.masked_mlp_fwd(mode, X, W1, W3, mine, idx[0], out=tuple(out))
+    for a, b in zip(got, want):
+        assert (a.double() - b.double()).abs().max() <= (1e-5 if dtype == "f32" else 1e-2) * b.abs().max()
+
+
 @pytest.mark.parametrize("w", F32_TILES, ids=[w.name for w in F32_TILES])
 def test_f32_tiles(sdp, orc, w):
     run_case(sdp, orc, w, [1], dw_layout="scatter" if w.T % 2 else "compact")
