@@ -17,8 +17,8 @@
 //   operand's 16-column fragment i takes column NF (L % 16) + i (NF = width / 16), so a lane loads NF consecutive
 //   columns of a row and later stores NF consecutive ones
 // One wave per (row, head) with scalar dot products, as this core was first written, took 555 / 563 / 590 us (forward,
-// dQ, dK/dV) for 2 x 256 tokens and 8 heads of 64.
-#include "sdp_internal.h"
+// dQ, dK/dV) for 2 x 256 tokens and 8 heads of 64.  Rows whose result is not finite are still computed that way (sdp_attn_rows.h).
+#include "sdp_attn_rows.h"
 
 #include <cmath>
 
@@ -148,6 +148,22 @@ __device__ inline void store_cols(float* p, int hd, int piece, const float (&x)[
         if (NF * piece + i < hd) p[NF * piece + i] = x[i];
 }
 
+// 0 when every x is finite, else NaN
+template <int N>
+__device__ inline float finite_check(const float (&x)[N]) {
+    float c = 0.f;
+#pragma unroll
+    for (int i = 0; i < N; ++i) c += x[i] * 0.f;
+    return c;
+}
+// Of the four result rows a wave holds (16 lanes each): bit 16 r set when row r has to be computed again.  bad: this lane holds
+// a value that is not finite, of a row that exists.
+__device__ inline uint64_t rows_again(bool bad) {
+    uint64_t m = __builtin_amdgcn_ballot_w64(bad);
+    m |= m >> 8, m |= m >> 4, m |= m >> 2, m |= m >> 1;
+    return m & 0x0001000100010001ull;
+}
+
 struct Item {
     int row0, head, b;
 };
@@ -229,11 +245,20 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_fwd_kernel(Args a, int nbloc
     float x[NF];
     Merge<HW>::get(sO, row, piece, w, x);
     const int qr = it.row0 + row;
-    if (qr <= last) {
 #pragma unroll
-        for (int i = 0; i < NF; ++i) x[i] /= total;
-        store_cols<NF>(a.o_out + ((int64_t)it.b * a.S + qr) * a.ldo + it.head * hd, hd, piece, x);
-        if (piece == 0) a.lse[((int64_t)it.b * a.n + it.head) * a.S + qr] = top + log2f(total);
+    for (int i = 0; i < NF; ++i) x[i] /= total;
+    float* const out = a.o_out + (int64_t)it.b * a.S * a.ldo + it.head * hd;
+    float* const lse = a.lse + ((int64_t)it.b * a.n + it.head) * a.S;
+    const uint64_t again = rows_again(qr <= last && finite_check(x) != 0.f);
+    if (qr <= last && !(again >> (lane & 48) & 1)) {
+        store_cols<NF>(out + qr * a.ldo, hd, piece, x);
+        if (piece == 0) lse[qr] = top + log2f(total);
+    }
+    if (again == 0) return;
+    const AttnRows<float> ar{Q0, K0, V0, a.ldq, nullptr, 0, a.S, hd, a.scale, a.scale2};
+    for (int r = 0; r < 4; ++r) {
+        const int qa = it.row0 + 4 * wave + r;
+        if (again >> (16 * r) & 1) attn_row_fwd(ar, qa, lane, out + qa * a.ldo, lse + qa);
     }
 }
 
@@ -300,7 +325,16 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_dq_kernel(Args a, int nblock
     float x[NF];
     Merge<HW>::get(sX, row, piece, w, x);
     const int qr = it.row0 + row;
-    if (qr <= last) store_cols<NF>(a.dqkv + ((int64_t)it.b * a.S + qr) * a.ldq + it.head * hd, hd, piece, x);
+    float* const out = a.dqkv + (int64_t)it.b * a.S * a.ldq + it.head * hd;
+    const uint64_t again = rows_again(qr <= last && finite_check(x) != 0.f);
+    if (qr <= last && !(again >> (lane & 48) & 1)) store_cols<NF>(out + qr * a.ldq, hd, piece, x);
+    if (again == 0) return;
+    const AttnRows<float> ar{Q0, K0, V0, a.ldq, a.dO + (int64_t)it.b * a.S * a.ldo + it.head * hd, a.ldo, a.S, hd, a.scale, a.scale2};
+    for (int r = 0; r < 4; ++r) {
+        const int ra = 4 * wave + r, qa = it.row0 + ra; // lane ra holds that row's delta and log-sum-exp
+        const float da = __shfl(d, ra, 64), la = __shfl(L2, ra, 64);
+        if (again >> (16 * r) & 1) attn_row_dq(ar, qa, lane, la, da, out + qa * a.ldq);
+    }
 }
 
 // backward, dK and dV of 16 keys: sums over the queries q >= k; reads delta
@@ -361,12 +395,23 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_dkv_kernel(Args a, int nbloc
     __syncthreads();
     const float wk[NW] = {a.scale, a.scale, a.scale, a.scale}, wv[NW] = {1.f, 1.f, 1.f, 1.f};
     Merge<HW>::get(sX, row, piece, wk, x);
-    if (krow <= last) store_cols<NF>(out + a.n * hd, hd, piece, x);
+    float y[NF];
     __syncthreads();
     Merge<HW>::put(sX, av, wave, l, g);
     __syncthreads();
-    Merge<HW>::get(sX, row, piece, wv, x);
-    if (krow <= last) store_cols<NF>(out + 2 * a.n * hd, hd, piece, x);
+    Merge<HW>::get(sX, row, piece, wv, y);
+    const uint64_t again = rows_again(krow <= last && finite_check(x) + finite_check(y) != 0.f);
+    if (krow <= last && !(again >> (lane & 48) & 1)) {
+        store_cols<NF>(out + a.n * hd, hd, piece, x);
+        store_cols<NF>(out + 2 * a.n * hd, hd, piece, y);
+    }
+    if (again == 0) return;
+    const AttnRows<float> ar{Q0, K0, V0, a.ldq, O0, a.ldo, a.S, hd, a.scale, a.scale2};
+    for (int r = 0; r < 4; ++r) {
+        const int ka = it.row0 + 4 * wave + r;
+        float* o = a.dqkv + ((int64_t)it.b * a.S + ka) * a.ldq + it.head * hd;
+        if (again >> (16 * r) & 1) attn_row_dkv(ar, ka, lane, a.lse + st, a.delta + st, o + a.n * hd, o + 2 * a.n * hd);
+    }
 }
 
 Args make_args(const AttnCoreDesc& c) {

@@ -195,6 +195,76 @@ def test_attention_f32_core(sdp, orc, w, mode):
     run_case(sdp, orc, w, [0], dw_layout="scatter" if w.S % 2 else "compact", mode=mode)
 
 
+# one bad token in the fp32 core: around the edges of its 16-row tiles and of the ragged last one, 16-byte and single loads
+BAD_F32 = [AttnWorkload(f"bad_f32_{hd}", 2, 75, 24, 3, hd, 2, 2, 52, "f32") for hd in (32, 50, 75, 128)]
+
+
+def _check_bad_token(sdp, w, mode, t):
+    """Causality for values that are not finite: a NaN or Inf at token t changes no row that does not depend on token t."""
+    Wqkv, WoT = (x.cuda() for x in workloads.attn_weights(w))
+    mask, idx, pos, cov = sdp.make_masks(w.K, w.H, w.ph, w.mask_seed, True)
+    X, dY = (x.cuda() for x in workloads.attn_batch(w, 0))
+    a = (mode, w.Bt, w.S, w.hd)
+    tok = w.S + t  # in the second sequence; the others must not notice at all
+    seq = torch.arange(w.T, device="cuda") // w.S
+    pos_in = torch.arange(w.T, device="cuda") % w.S
+    before, at, after = ((seq != 1) | (pos_in < t), (seq == 1) & (pos_in == t), (seq != 1) | (pos_in > t))
+    tol = 1e-5 if w.dtype == "f32" else 1e-2
+
+    def same(got, want, rows, what):
+        assert bool(torch.isfinite(got[rows]).all()), f"{what}: rows that do not depend on the bad token are not finite"
+        err = (got[rows].double() - want[rows].double()).abs().max()
+        assert err <= tol * want.double().abs().max(), f"{what}: {float(err):.3e}"
+
+    def bwd(QKV, O, LSE, dy=dY):
+        return sdp.masked_attn_bwd(*a, X, dy, Wqkv, WoT, idx[0], QKV, O, LSE)[0]
+
+    want = sdp.masked_attn_fwd(*a, X, Wqkv, WoT, idx[0])
+    Y, QKV, O, LSE = want
+    want_dX = bwd(QKV, O, LSE)
+    lse_rows = lambda x: x.permute(0, 2, 1).reshape(w.T, -1)
+
+    bad = X.clone()
+    bad[tok] = float("nan")
+    got = sdp.masked_attn_fwd(*a, bad, Wqkv, WoT, idx[0])
+    for g, x, what in ((got[0], Y, "Y"), (got[2], O, "O"), (lse_rows(got[3]), lse_rows(LSE), "LSE")):
+        same(g, x, before, f"NaN in X, {what}")
+    assert bool(torch.isnan(got[2][~before]).all())
+
+    # V alone overflows at token t: infinite outputs from there on, finite probabilities
+    X0, Xinf, Wv = X.clone(), X.clone(), Wqkv.clone()
+    X0[:, 0] = 0
+    Xinf[:, 0] = 0
+    Xinf[tok, 0] = 1e30
+    Wv[:2, :, 0] = 0
+    Wv[2, :, 0] = 1e30
+    ref = sdp.masked_attn_fwd(*a, X0, Wv, WoT, idx[0])
+    got = sdp.masked_attn_fwd(*a, Xinf, Wv, WoT, idx[0])
+    same(got[2], ref[2], before, "Inf in V, O")
+    same(lse_rows(got[3]), lse_rows(ref[3]), slice(None), "Inf in V, LSE")
+    assert bool((sdp.attn_unpad(got[2], w.hd)[~before] == float("inf")).all())
+
+    n = QKV.shape[1] // 3
+    for value in (float("nan"), float("inf")):
+        for part, what in ((1, "K"), (2, "V")):
+            bad = QKV.clone()
+            bad[tok, part * n:(part + 1) * n] = value
+            same(bwd(bad, O, LSE), want_dX, before, f"{value} in {what}, dX")  # dQ before t, dK and dV of the other keys
+        bad = QKV.clone()
+        bad[tok, :n] = value
+        same(bwd(bad, O, LSE), want_dX, after, f"{value} in Q, dX")
+        bad = dY.clone()
+        bad[tok] = value
+        same(bwd(QKV, O, LSE, bad), want_dX, after, f"{value} in dY, dX")
+
+
+@pytest.mark.parametrize("mode", ["fm", "bm"])
+@pytest.mark.parametrize("t", [0, 17, 40, 63, 74])
+@pytest.mark.parametrize("w", BAD_F32, ids=[w.name for w in BAD_F32])
+def test_bad_token_reaches_only_what_depends_on_it_f32(sdp, w, t, mode):
+    _check_bad_token(sdp, w, mode, t)
+
+
 TAKEN = {"dX over dY": {0: "dY"}, "dX over X": {0: "X"}, "dX over O": {0: "O"}, "gradients over weights": {1: "Wqkv", 2: "WoT"},
          "dX over X, gradients over weights": {0: "X", 1: "Wqkv", 2: "WoT"}, "a gradient over dY": {2: "dY"}}
 
