@@ -25,6 +25,7 @@
 // are, for this lane, the depth indices {16 s + 4 (L / 32) + r} and {16 s + 8 + 4 (L / 32) + r}, and the other
 // operand is read from LDS in that same order with two transposing reads (ds_read_tr16_b64), which turn a
 // row-major [depth][column] tile into the per-lane layout of an A operand.
+#include "sdp_attn_rows.h"
 #include "sdp_transpose.h"
 
 #include <cmath>
@@ -194,6 +195,26 @@ __device__ inline void store_rows(uint16_t* out_row, const f32x16 (&acc)[HW / 32
 
 __device__ inline float other_half(float x) { return __shfl_xor(x, 32, 64); }
 
+// Heads wider than 64: rows whose result is not finite are computed again, pair by pair (sdp_attn_rows.h): the plain core that
+// served them read no masked pair and split no operand.  Heads up to 64 have always multiplied masked pairs by zero.
+constexpr bool rows_again(int hw) { return two_terms(hw); }
+
+// 0 when every element of the tiles times f is finite, else NaN
+template <int N>
+__device__ inline float finite_check(const f32x16 (&acc)[N], float f) {
+    float c = 0.f;
+#pragma unroll
+    for (int j = 0; j < N; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) c += acc[j][e] * f * 0.f;
+    return c;
+}
+// of a wave's 32 rows (lane % 32): those of which either half is bad
+__device__ inline uint32_t bad_rows(bool bad) {
+    const uint64_t m = __builtin_amdgcn_ballot_w64(bad);
+    return (uint32_t)m | (uint32_t)(m >> 32);
+}
+
 // 2^x for x <= 0 (or -inf): the hardware instruction alone; results below the normal range may flush to zero
 __device__ inline float exp2_neg(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -202,6 +223,13 @@ __device__ inline float exp2_neg(float x) { return __builtin_amdgcn_exp2f(x); }
 constexpr int wave_lds(int hw) { return 64 * row_bytes(hw) + 256; }
 constexpr int part_row(int hw) { return hw + 4; }
 static_assert(32 * part_row(HD) * 4 + 256 <= wave_lds(HD) && 32 * part_row(128) * 4 + 256 <= wave_lds(128), "fits the tiles");
+
+// KW = 4: one flag per row of the workgroup's block, in what a wave's LDS has left beyond its partial result and statistics:
+// set where store_parts met a value that is not finite.
+constexpr int FLAGS = 32 * 4;
+static_assert(32 * part_row(96) * 4 + 256 + FLAGS <= wave_lds(96) && 32 * part_row(128) * 4 + 256 + FLAGS <= wave_lds(128), "fits the tiles");
+template <int HW>
+__device__ inline uint32_t* row_flags(unsigned char* lds) { return (uint32_t*)(lds + wave_lds(HW) - FLAGS); }
 
 // accumulator tiles D[h][row] -> the wave's partial result
 template <int HW>
@@ -215,9 +243,9 @@ __device__ inline void put_part(unsigned char* mine, const f32x16 (&acc)[HW / 32
 }
 
 // sum over the waves of f[w] x partial result, as bf16 rows of `out` (row0 + 0 .. 31, those below S); weights(row, f)
-// fills f.  Columns from hd on are left alone.
+// fills f.  Columns from hd on are left alone.  Rows with a value that is not finite are flagged (rows_again).
 template <int HW, class W>
-__device__ inline void store_parts(const unsigned char* lds, uint16_t* out, int64_t ld, int row0, int S, int hd, int tid, W weights) {
+__device__ inline void store_parts(unsigned char* lds, uint16_t* out, int64_t ld, int row0, int S, int hd, int tid, W weights) {
 #pragma unroll
     for (int i = 0; i < HW / 32; ++i) {
         const int e = tid + 256 * i, row = e / (HW / 4), c = e % (HW / 4) * 4;
@@ -230,8 +258,25 @@ __device__ inline void store_parts(const unsigned char* lds, uint16_t* out, int6
 #pragma unroll
             for (int r = 0; r < 4; ++r) v[r] = __builtin_fmaf(x[r], f[w], v[r]);
         }
-        if (row0 + row < S && (HW == HD || c < hd))
+        if (row0 + row < S && (HW == HD || c < hd)) {
             *(u32x2*)(out + (int64_t)(row0 + row) * ld + c) = u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
+            if constexpr (rows_again(HW))
+                if (v[0] * 0.f + v[1] * 0.f + v[2] * 0.f + v[3] * 0.f != 0.f) row_flags<HW>(lds)[row] = 1;
+        }
+    }
+}
+
+// The rows to compute again, each by one wave: `again` holds a wave's own rows (KW = 1), or the flags in LDS say which
+// (KW = 4; called by all waves, after store_parts).
+template <int HW, int KW, class F>
+__device__ inline void each_row_again(unsigned char* lds, uint32_t again, int wave, int lane, F f) {
+    if constexpr (KW != 1) {
+        __syncthreads(); // the flags, and the values that these replace
+        again = (uint32_t)__builtin_amdgcn_ballot_w64(lane < 32 && row_flags<HW>(lds)[lane & 31] != 0) & (0x11111111u << wave);
+    }
+    while (again) {
+        f(__builtin_ctz(again));
+        again &= again - 1;
     }
 }
 
@@ -393,8 +438,10 @@ __device__ inline void attn_fwd_block(const CoreArgs& a, const int q0, const int
     const float l = lsum + other_half(lsum);
     uint16_t* const out = a.o_out + (int64_t)b * S * a.ldo + head * hd;
     float* const lse = a.lse + ((int64_t)b * a.ph + head) * S;
+    uint32_t again = 0;
     if constexpr (KW == 1) {
-        if (qrow < S) {
+        if constexpr (rows_again(HW)) again = bad_rows(qrow < S && finite_check(acc, 1.f / l) != 0.f);
+        if (qrow < S && !(again >> l32 & 1)) {
             store_rows<HW>(out + (int64_t)qrow * a.ldo, acc, 1.f / l, hd, lhi);
             if (lhi == 0) lse[qrow] = m + log2f(l);
         }
@@ -402,6 +449,7 @@ __device__ inline void attn_fwd_block(const CoreArgs& a, const int q0, const int
         put_part<HW>(mine, acc, l32, lhi);
         constexpr int STAT = 32 * part_row(HW) * 4; // [32] references, [32] sums
         ((float*)(mine + STAT))[lane] = lhi == 0 ? m : l;
+        if (rows_again(HW) && tid < 32) row_flags<HW>(lds)[tid] = 0;
         __syncthreads();
         store_parts<HW>(lds, out, a.ldo, q0, S, hd, tid, [&](int row, float (&f)[NW]) {
             float top = -INFINITY, sum = 0.f;
@@ -428,6 +476,11 @@ __device__ inline void attn_fwd_block(const CoreArgs& a, const int q0, const int
             lse[q0 + tid] = top + log2f(sum);
         }
     }
+    if constexpr (rows_again(HW))
+        each_row_again<HW, KW>(lds, again, wave, lane, [&](int r) {
+            const AttnRows<uint16_t> ar{gQ, gK, gV, a.ldq, nullptr, 0, S, hd, a.scale, a.scale2};
+            attn_row_fwd(ar, qrow0 + r, lane, out + (int64_t)(qrow0 + r) * a.ldo, lse + qrow0 + r);
+        });
 }
 
 // Causal rows differ in length: block i of a sequence meets i + 1 blocks of keys, and at the sizes this
@@ -569,17 +622,27 @@ __device__ inline void attn_bwd_dq_block(const CoreArgs& a, const int q0, const 
             }
         }
     }
+    uint16_t* const out = a.dqkv + (int64_t)b * S * a.ldq + head * hd;
+    uint32_t again = 0;
     if constexpr (KW == 1) {
-        if (qrow < S) store_rows<HW>(a.dqkv + ((int64_t)b * S + qrow) * a.ldq + head * hd, acc, a.scale, hd, lhi);
+        if constexpr (rows_again(HW)) again = bad_rows(qrow < S && finite_check(acc, a.scale) != 0.f);
+        if (qrow < S && !(again >> l32 & 1)) store_rows<HW>(out + (int64_t)qrow * a.ldq, acc, a.scale, hd, lhi);
     } else {
         wave_sync();
         put_part<HW>(sK, acc, l32, lhi);
+        if (rows_again(HW) && tid < 32) row_flags<HW>(lds)[tid] = 0;
         __syncthreads();
-        store_parts<HW>(lds, a.dqkv + (int64_t)b * S * a.ldq + head * hd, a.ldq, q0, S, hd, tid, [&](int, float (&f)[NW]) {
+        store_parts<HW>(lds, out, a.ldq, q0, S, hd, tid, [&](int, float (&f)[NW]) {
 #pragma unroll
             for (int w = 0; w < NW; ++w) f[w] = a.scale;
         });
     }
+    if constexpr (rows_again(HW))
+        each_row_again<HW, KW>(lds, again, wave, lane, [&](int r) {
+            const AttnRows<uint16_t> ar{gQ, gK, gV, a.ldq, a.dO + (int64_t)b * S * a.ldo + head * hd, a.ldo, S, hd, a.scale, a.scale2};
+            // lane r holds that row's statistics
+            attn_row_dq(ar, qrow0 + r, lane, __shfl(L2, r, 64), __shfl(delta, r, 64), out + (int64_t)(qrow0 + r) * a.ldq);
+        });
 }
 
 template <int HW, int KW>
@@ -725,19 +788,22 @@ __device__ inline void attn_bwd_dkv_block(const CoreArgs& a, const int k0, const
             }
         }
     }
+    uint16_t* const out = a.dqkv + (int64_t)b * S * a.ldq + head * hd;
+    uint32_t again = 0;
     if constexpr (KW == 1) {
-        if (krow < S) {
-            uint16_t* row = a.dqkv + ((int64_t)b * S + krow) * a.ldq + head * hd;
+        if constexpr (rows_again(HW)) again = bad_rows(krow < S && finite_check(acc_k, a.scale) + finite_check(acc_v, 1.f) != 0.f);
+        if (krow < S && !(again >> l32 & 1)) {
+            uint16_t* row = out + (int64_t)krow * a.ldq;
             store_rows<HW>(row + a.ph * hd, acc_k, a.scale, hd, lhi);
             store_rows<HW>(row + 2 * a.ph * hd, acc_v, 1.f, hd, lhi);
         }
     } else {
-        uint16_t* const out = a.dqkv + (int64_t)b * S * a.ldq + head * hd;
 #pragma unroll
         for (int part = 1; part <= 2; ++part) { // dK, then dV
             const float f1 = part == 1 ? a.scale : 1.f;
             if (part == 1) wave_sync(); else __syncthreads();
             put_part<HW>(sQ, part == 1 ? acc_k : acc_v, l32, lhi);
+            if (rows_again(HW) && part == 1 && tid < 32) row_flags<HW>(lds)[tid] = 0;
             __syncthreads();
             store_parts<HW>(lds, out + part * a.ph * hd, a.ldq, k0, S, hd, tid, [&](int, float (&f)[NW]) {
 #pragma unroll
@@ -745,6 +811,12 @@ __device__ inline void attn_bwd_dkv_block(const CoreArgs& a, const int k0, const
             });
         }
     }
+    if constexpr (rows_again(HW))
+        each_row_again<HW, KW>(lds, again, wave, lane, [&](int r) {
+            const AttnRows<uint16_t> ar{gQ, gK, gV, a.ldq, gO, a.ldo, S, hd, a.scale, a.scale2};
+            uint16_t* row = out + (int64_t)(krow0 + r) * a.ldq;
+            attn_row_dkv(ar, krow0 + r, lane, a.lse + stat, a.delta + stat, row + a.ph * hd, row + 2 * a.ph * hd);
+        });
 }
 
 template <int HW, int KW>

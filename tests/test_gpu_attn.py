@@ -265,6 +265,18 @@ def test_bad_token_reaches_only_what_depends_on_it_f32(sdp, w, t, mode):
     _check_bad_token(sdp, w, mode, t)
 
 
+# bf16 heads wider than 64: the form whose waves split the walked axis, and (from 193 blocks of 128 rows) the one whose waves
+# share the tiles
+BAD_WIDE = [AttnWorkload(f"bad{hd}_S{S}", Bt, S, 72, H, hd, H, 2, 53) for hd, Bt, S, H in
+            ((72, 2, 75, 3), (96, 2, 150, 2), (128, 2, 150, 2), (88, 13, 150, 8), (128, 13, 150, 8))]
+
+
+@pytest.mark.parametrize("t", [0, 17, 63, 70, -1])
+@pytest.mark.parametrize("w", BAD_WIDE, ids=[w.name for w in BAD_WIDE])
+def test_bad_token_reaches_only_what_depends_on_it_wide_heads(sdp, w, t):
+    _check_bad_token(sdp, w, "fm", t % w.S)
+
+
 TAKEN = {"dX over dY": {0: "dY"}, "dX over X": {0: "X"}, "dX over O": {0: "O"}, "gradients over weights": {1: "Wqkv", 2: "WoT"},
          "dX over X, gradients over weights": {0: "X", 1: "Wqkv", 2: "WoT"}, "a gradient over dY": {2: "dY"}}
 
