@@ -29,6 +29,7 @@
 #include "sdp_transpose.h"
 
 #include <cmath>
+#include <type_traits>
 
 namespace sdp {
 namespace {
@@ -141,12 +142,15 @@ __device__ inline bf16x8 frag_cols(const unsigned char* tile, int krow, int col0
 // global memory to LDS through registers.  Rows are clamped to the last valid one (such rows only meet masked
 // logits); columns from hd on (HW > 64 only) become zeros.  `g` is uniform over the workgroup and the tile's first
 // row moves it by 64-bit scalar arithmetic; the per-thread part of the address is a 32-bit byte offset inside the
-// tile, one multiply and add per piece.
+// tile, one multiply and add per piece: 63 rows of kMaxLd elements stay below 4 GiB, taller tiles take 64-bit offsets.
+constexpr int64_t kMaxHeads = 65535;
 template <int NW, int HW, int ROWS = 64>
 struct TileMover {
     static constexpr int CPR = HW == HD ? 8 : 16;      // pieces per row (HW = 96: the last 4 of 16 move nothing)
     static constexpr int PER = ROWS * CPR / (64 * NW); // pieces per thread and tile
     static_assert(ROWS * CPR % (64 * NW) == 0 && 64 * NW % CPR == 0, "a thread's pieces share one column");
+    static constexpr int64_t kMaxLd = 3 * kMaxHeads * HW; // Q | K | V
+    typedef std::conditional_t<(ROWS * kMaxLd * 2 < ((int64_t)1 << 32)), uint32_t, uint64_t> Offset;
     u32x4 v[PER];
     __device__ void fetch(const uint16_t* g, uint32_t ld, int row0, int last_row, int hd, int tid) {
         const int r0 = row0 < last_row ? row0 : last_row, rmax = last_row - r0;
@@ -157,7 +161,7 @@ struct TileMover {
         for (int i = 0; i < PER; ++i) {
             int row = tid / CPR + 64 * NW / CPR * i;
             row = row < rmax ? row : rmax;
-            v[i] = *(const u32x4*)(base + ((uint32_t)row * ld + (uint32_t)col * 8u) * 2u);
+            v[i] = *(const u32x4*)(base + ((Offset)row * ld + (uint32_t)col * 8u) * 2u);
         }
     }
     __device__ void stash(unsigned char* tile, int hd, int tid) const {
@@ -937,7 +941,7 @@ int check(int mode, int dtype, int Bt, int S, int d, int H, int hd, int ph) {
     if (hd > 128) return SDP_ERR_UNSUPPORTED;
     if (ph < 1 || ph > H) return SDP_ERR_SHAPE;
     if (dtype == SDP_BF16 && (d % 8 || (hd > HD && hd % 8))) return SDP_ERR_SHAPE; // 16-byte rows; heads up to 64 are padded
-    if (Bt > 65535 || H > 65535) return SDP_ERR_SHAPE;
+    if (Bt > 65535 || H > kMaxHeads) return SDP_ERR_SHAPE;
     const int hw = core_width(dtype, hd);
     if ((int64_t)Bt * S >= ((int64_t)1 << 31) || (int64_t)Bt * S * 3 * H * hw >= ((int64_t)1 << 40)) return SDP_ERR_SHAPE;
     // padded heads: a sequence's rows span less than 4 GiB

@@ -217,3 +217,27 @@ def test_results_do_not_depend_on_what_workspace_and_outputs_held(sdp, mode, m, 
         assert len(res[fill]) == len(res["zero"])
         for i, (a, b) in enumerate(zip(res["zero"], res[fill])):
             assert torch.equal(a, b), f"block {mode} m={m}: tensor {i} depends on the previous contents of a buffer ({fill})"
+
+
+def test_wide_heads_beyond_4_GiB_of_row_offsets(sdp, orc):
+    """60,000 heads of 128, of which one has weights: a row of Q | K | V is 46 MB, so that row 94 on of the dK/dV kernel's tile
+    of 128 rows of V lies beyond 32-bit byte offsets.  The other heads add nothing, so the block equals that of the one head."""
+    S, d, H, hd, F, h = 128, 8, 60000, 128, 8, 31000
+    t = _setup(9, 1, S, d, 1, hd, F, "bf16")
+    t["Wqkv"] *= 6.0
+    t["WoT"] *= 6.0
+    print(f"block bf16 S={S} d={d} H={H} hd={hd}", flush=True)
+    big = {}
+    for n in ("Wqkv", "WoT"):
+        big[n] = torch.zeros(t[n].shape[:-2] + (H * hd, d), dtype=torch.bfloat16, device="cuda")
+        big[n][..., h * hd:(h + 1) * hd, :] = t[n].cuda()
+    c = {k: v.cuda() for k, v in t.items()}
+    W = (big["Wqkv"], big["WoT"], c["W1"], c["W3"], c["W2T"])
+    ref = orc.block_step("bm", 0, 1, S, hd, _f64(t["X"]), _f64(t["dY"]), *_oracle_weights(t))
+    mod = rm.block_model("bm", 0, 1, S, hd, _f64(t["X"]), _f64(t["dY"]), *_oracle_weights(t))
+    Y, saved = sdp.block_fwd("bm", 0, 1, S, hd, c["X"], *W)
+    dX, _ = sdp.block_bwd("bm", 0, 1, S, hd, c["X"], c["dY"], *W, saved)
+    torch.cuda.synchronize()
+    # 8 columns a row: the elementwise bounds are those of the small random shapes
+    assert_close_with_model(_f64(Y.cpu()), mod["Y"], ref["Y"], 2e-2, "Y", rows=True, elem_allow=4e-2)
+    assert_close_with_model(_f64(dX.cpu()), mod["dX"], ref["dX"], 2e-2, "dX", rows=True, elem_allow=4e-2)
