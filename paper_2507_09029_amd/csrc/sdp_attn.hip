@@ -510,6 +510,19 @@ __device__ inline void causal_item(int L, int nitems, int nbh, int nblocks, int 
 // of 50, 12 held 690 -> 658.
 constexpr int side_tiles(int lds) { return lds / kTransposeLds < 4 ? lds / kTransposeLds : 4; }
 
+// A launch's workgroups in one order.  One axis of a grid holds fewer than 2^32 threads (2^24 workgroups); with more
+// workgroups the second axis counts rows of kGridRow, the last of which may be partly beyond them.
+constexpr int kGridRow = 1 << 23;
+__device__ inline int workgroup_id() { return (int)(blockIdx.y * kGridRow + blockIdx.x); }
+inline dim3 workgroup_grid(int64_t n) {
+    return n < 2 * kGridRow ? dim3((unsigned)n) : dim3(kGridRow, (unsigned)((n + kGridRow - 1) / kGridRow));
+}
+template <int LDS>
+__device__ inline void carried(const SideJobs& side, int w, unsigned char* lds) {
+    constexpr int PER = side_tiles(LDS);
+    if (w < (side.end[kMaxTransposeJobs - 1] + PER - 1) / PER) side_transposes<PER>(side, w, lds, threadIdx.x);
+}
+
 // waves per SIMD the registers are allotted for.  KW = 1, heads of 64: 3 beat 2 (86 -> 77 us at 4 x 2048 tokens, 12 heads)
 // and 4 spill.  KW = 4 has a workgroup per CU or less, and the wide heads then take the registers of one or two waves.
 constexpr int waves_fwd(int hw, int kw) { return kw == 1 ? (hw == HD ? 3 : 2) : 2; }
@@ -521,9 +534,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(waves_f
 void attn_fwd_kernel(CoreArgs a, int nblocks, int nbh, SideJobs side) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[fwd_lds<HW, KW>()];
     const int nitems = nblocks * nbh;
-    if ((int)blockIdx.x >= nitems) return side_transposes<side_tiles(sizeof(lds))>(side, blockIdx.x - nitems, lds, threadIdx.x);
+    const int id = workgroup_id();
+    if (id >= nitems) return carried<sizeof(lds)>(side, id - nitems, lds);
     int blk, head, b;
-    causal_item(blockIdx.x, nitems, nbh, nblocks, a.ph, blk, head, b);
+    causal_item(id, nitems, nbh, nblocks, a.ph, blk, head, b);
     attn_fwd_block<HW, KW>(a, blk * Split<KW>::ROWS, head, b, lds);
 }
 
@@ -654,9 +668,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_dq(HW
 void attn_bwd_dq_kernel(CoreArgs a, int nblocks, int nbh, SideJobs side) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[dq_lds<HW, KW>()];
     const int nitems = nblocks * nbh;
-    if ((int)blockIdx.x >= nitems) return side_transposes<side_tiles(sizeof(lds))>(side, blockIdx.x - nitems, lds, threadIdx.x);
+    const int id = workgroup_id();
+    if (id >= nitems) return carried<sizeof(lds)>(side, id - nitems, lds);
     int blk, head, b;
-    causal_item(blockIdx.x, nitems, nbh, nblocks, a.ph, blk, head, b);
+    causal_item(id, nitems, nbh, nblocks, a.ph, blk, head, b);
     attn_bwd_dq_block<HW, KW>(a, blk * Split<KW>::ROWS, head, b, lds);
 }
 
@@ -828,9 +843,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_dkv(H
 void attn_bwd_dkv_kernel(CoreArgs a, int nblocks, int nbh, SideJobs side) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[DkvShape<HW, KW>::LDS];
     const int nitems = nblocks * nbh;
-    if ((int)blockIdx.x >= nitems) return side_transposes<side_tiles(sizeof(lds))>(side, blockIdx.x - nitems, lds, threadIdx.x);
+    const int id = workgroup_id();
+    if (id >= nitems) return carried<sizeof(lds)>(side, id - nitems, lds);
     int blk, head, b;
-    causal_item(blockIdx.x, nitems, nbh, nblocks, a.ph, blk, head, b);
+    causal_item(id, nitems, nbh, nblocks, a.ph, blk, head, b);
     // key block i meets the query blocks i .. n - 1: the first key blocks are the long ones
     attn_bwd_dkv_block<HW, KW>(a, (nblocks - 1 - blk) * Split<KW>::ROWS, head, b, lds);
 }
@@ -847,7 +863,7 @@ int launch_core(CoreKernel which, const CoreArgs& a, int nbh, const SideJobs& si
     const int nblocks = (a.S + Split<KW>::ROWS - 1) / Split<KW>::ROWS;
     auto grid = [&](int lds) {
         const int per = side_tiles(lds);
-        return dim3((unsigned)(nblocks * nbh) + (unsigned)((side.end[kMaxTransposeJobs - 1] + per - 1) / per));
+        return workgroup_grid((int64_t)nblocks * nbh + (side.end[kMaxTransposeJobs - 1] + per - 1) / per);
     };
     if (which == CORE_FWD) attn_fwd_kernel<HW, KW><<<grid(fwd_lds<HW, KW>()), 64 * NW, 0, s>>>(a, nblocks, nbh, side);
     else if (which == CORE_DQ) attn_bwd_dq_kernel<HW, KW><<<grid(dq_lds<HW, KW>()), 64 * NW, 0, s>>>(a, nblocks, nbh, side);

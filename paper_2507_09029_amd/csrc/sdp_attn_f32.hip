@@ -164,24 +164,29 @@ __device__ inline uint64_t rows_again(bool bad) {
     return m & 0x0001000100010001ull;
 }
 
+// Long items first: blocks of rows along the grid's slowest axis (heads, sequences, blocks), so that no axis is a product of
+// sizes.  A grid has 65535 on its slower axes: with more blocks than that (16 rows each) they take the first one instead.
+constexpr int kSlowAxis = 65535;
 struct Item {
     int row0, head, b;
 };
-__device__ inline Item item_of(const Args& a, int nblocks, int nbh, bool first_is_long) {
-    const int blk = blockIdx.x / nbh, bh = blockIdx.x % nbh; // long items first
-    return {16 * (first_is_long ? blk : nblocks - 1 - blk), bh % a.n, bh / a.n};
+__device__ inline Item item_of(int nblocks, bool first_is_long) {
+    const bool slow = nblocks <= kSlowAxis;
+    const int blk = slow ? blockIdx.z : blockIdx.x;
+    return {16 * (first_is_long ? blk : nblocks - 1 - blk), (int)(slow ? blockIdx.x : blockIdx.y), (int)(slow ? blockIdx.y : blockIdx.z)};
 }
+inline dim3 item_grid(int nblocks, int n, int Bt) { return nblocks <= kSlowAxis ? dim3(n, Bt, nblocks) : dim3(nblocks, n, Bt); }
 
 // forward: O[q] = sum_{k <= q} softmax(z[q][.])[k] V[k]
 template <int HW, bool VEC>
-__global__ __launch_bounds__(64 * NW) void attn_f32_fwd_kernel(Args a, int nblocks, int nbh) {
+__global__ __launch_bounds__(64 * NW) void attn_f32_fwd_kernel(Args a, int nblocks) {
     typedef Head<HW, VEC> H;
     constexpr int NF = H::NF;
     __shared__ __attribute__((aligned(16))) float sO[NW * 16 * (HW + 4)];
     __shared__ float sM[NW][16], sL[NW][16];
     const int tid = threadIdx.x, lane = tid & 63, l = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const Item it = item_of(a, nblocks, nbh, false);
+    const Item it = item_of(nblocks, false);
     const int hd = a.hd, last = a.S - 1;
     const float* Q0 = a.qkv + (int64_t)it.b * a.S * a.ldq + it.head * hd;
     const float* K0 = Q0 + a.n * hd;
@@ -264,13 +269,13 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_fwd_kernel(Args a, int nbloc
 
 // backward, dQ and delta: dQ[q] = scale sum_{k <= q} dZ[q][k] K[k], dZ = P (dP - delta), dP[q][k] = dO[q] . V[k]
 template <int HW, bool VEC>
-__global__ __launch_bounds__(64 * NW) void attn_f32_dq_kernel(Args a, int nblocks, int nbh) {
+__global__ __launch_bounds__(64 * NW) void attn_f32_dq_kernel(Args a, int nblocks) {
     typedef Head<HW, VEC> H;
     constexpr int NF = H::NF;
     __shared__ __attribute__((aligned(16))) float sX[NW * 16 * (HW + 4)];
     const int tid = threadIdx.x, lane = tid & 63, l = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const Item it = item_of(a, nblocks, nbh, false);
+    const Item it = item_of(nblocks, false);
     const int hd = a.hd, last = a.S - 1;
     const float* Q0 = a.qkv + (int64_t)it.b * a.S * a.ldq + it.head * hd;
     const float* K0 = Q0 + a.n * hd;
@@ -339,13 +344,13 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_dq_kernel(Args a, int nblock
 
 // backward, dK and dV of 16 keys: sums over the queries q >= k; reads delta
 template <int HW, bool VEC>
-__global__ __launch_bounds__(64 * NW) void attn_f32_dkv_kernel(Args a, int nblocks, int nbh) {
+__global__ __launch_bounds__(64 * NW) void attn_f32_dkv_kernel(Args a, int nblocks) {
     typedef Head<HW, VEC> H;
     constexpr int NF = H::NF;
     __shared__ __attribute__((aligned(16))) float sX[NW * 16 * (HW + 4)];
     const int tid = threadIdx.x, lane = tid & 63, l = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const Item it = item_of(a, nblocks, nbh, true); // the first key blocks meet the most queries
+    const Item it = item_of(nblocks, true); // the first key blocks meet the most queries
     const int hd = a.hd, last = a.S - 1;
     const float* Q0 = a.qkv + (int64_t)it.b * a.S * a.ldq + it.head * hd;
     const float* K0 = Q0 + a.n * hd;
@@ -427,31 +432,30 @@ Args make_args(const AttnCoreDesc& c) {
 template <int HW, bool VEC>
 int fwd_t(const AttnCoreDesc& c, int nblocks, hipStream_t s) {
     ProfileScope ps("attn_core_fwd", s);
-    attn_f32_fwd_kernel<HW, VEC><<<dim3(nblocks * c.n * c.Bt), 64 * NW, 0, s>>>(make_args(c), nblocks, c.n * c.Bt);
+    attn_f32_fwd_kernel<HW, VEC><<<item_grid(nblocks, c.n, c.Bt), 64 * NW, 0, s>>>(make_args(c), nblocks);
     return launch_status();
 }
 template <int HW, bool VEC>
 int bwd_t(const AttnCoreDesc& c, int nblocks, hipStream_t s) {
-    const dim3 grid(nblocks * c.n * c.Bt);
+    const dim3 grid = item_grid(nblocks, c.n, c.Bt);
     {
         ProfileScope ps("attn_core_bwd_dq", s);
-        attn_f32_dq_kernel<HW, VEC><<<grid, 64 * NW, 0, s>>>(make_args(c), nblocks, c.n * c.Bt);
+        attn_f32_dq_kernel<HW, VEC><<<grid, 64 * NW, 0, s>>>(make_args(c), nblocks);
         const int rc = launch_status();
         if (rc != SDP_OK) return rc;
     }
     ProfileScope ps("attn_core_bwd_dkv", s); // reads the delta written by the dQ kernel
-    attn_f32_dkv_kernel<HW, VEC><<<grid, 64 * NW, 0, s>>>(make_args(c), nblocks, c.n * c.Bt);
+    attn_f32_dkv_kernel<HW, VEC><<<grid, 64 * NW, 0, s>>>(make_args(c), nblocks);
     return launch_status();
 }
 
 template <class F>
 int by_width(const AttnCoreDesc& c, F f) {
     if (c.hd < 1 || c.hd > 128) return SDP_ERR_UNSUPPORTED;
-    const int64_t nblocks = (c.S + 15) / 16;
-    if (nblocks * c.n * c.Bt > INT32_MAX) return SDP_ERR_UNSUPPORTED;
+    const int nblocks = (int)(((int64_t)c.S + 15) / 16);
     const bool vec = c.hd % 4 == 0 && c.ldq % 4 == 0 && c.ldo % 4 == 0 && aligned16(c.qkv) && (!c.o || aligned16(c.o)) &&
                      (!c.dO || aligned16(c.dO));
-    return f(vec, (int)nblocks);
+    return f(vec, nblocks);
 }
 
 } // namespace

@@ -324,6 +324,40 @@ def test_forward_output_may_take_the_place_of_its_weights(sdp, dtype, mode):
         assert (x.double() - y.double()).abs().max() <= (1e-5 if dtype == "f32" else 1e-2) * y.abs().max()
 
 
+@pytest.mark.parametrize("dtype,hd,d", [("f32", 1, 1), ("bf16", 72, 8)])
+def test_more_items_than_one_grid_axis_holds(sdp, dtype, hd, d):
+    """65535 sequences of one token and 260 heads: 17 million items of the core, more workgroups of 256 threads than one axis of
+    a grid takes.  A softmax over one key is constant, so Y = X Wv^T Wo and dX likewise, dWq = dWk = 0.  X and dY are positive:
+    the weight gradients' sums over 65535 tokens then do not cancel, and fp32 roundings along the way (at worst one of 2^-24 for
+    each of the 16384 additions to an accumulator, 1e-3; a random walk of them, 1e-5) stay below 1e-4 of the result."""
+    Bt, H = 65535, 260
+    g = torch.Generator(device="cuda").manual_seed(54)
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    X, dY, Wqkv, WoT = (torch.randn(s, generator=g, device="cuda").mul_(f).to(dt) for s, f in
+                        (((Bt, d), 1.0), ((Bt, d), 1.0), ((3, H * hd, d), 0.1), ((H * hd, d), 0.1)))
+    X, dY = X.abs(), dY.abs()
+    idx = torch.arange(H, dtype=torch.int32, device="cuda")
+    print(f"one token a sequence: {dtype} Bt={Bt} H={H} hd={hd} d={d}", flush=True)
+    Y, QKV, O, LSE = sdp.masked_attn_fwd("fm", Bt, 1, hd, X, Wqkv, WoT, idx)
+    dX, gW, gO = sdp.masked_attn_bwd("fm", Bt, 1, hd, X, dY, Wqkv, WoT, idx, QKV, O, LSE)
+    V = QKV[:, 2 * H * hd:]
+    assert torch.equal(O, V)
+    del QKV, O, LSE
+    M = Wqkv[2].double().t() @ WoT.double()  # [d][d]
+    tol = 1e-5 if dtype == "f32" else 2e-2
+
+    def close(got, want, what, tol=tol):
+        err = float((got.double() - want).norm() / want.norm())
+        assert err <= tol, f"{what}: {err:.3e}"
+
+    close(Y, X.double() @ M, "Y")
+    close(dX, dY.double() @ M.t(), "dX")
+    XtdY = X.double().t() @ dY.double()
+    close(gW[2], WoT.double() @ XtdY.t(), "dWv", max(tol, 1e-4))
+    close(gO, Wqkv[2].double() @ XtdY, "dWoT", max(tol, 1e-4))
+    assert float(gW[:2].double().abs().max()) <= 1e-5 * float(gW[2].double().abs().max())
+
+
 @pytest.mark.parametrize("w", BM_CASES, ids=[w.name for w in BM_CASES])
 def test_attention_backward_masking_all_outputs(sdp, orc, w):
     """Dense forward and dX, weight gradients on the held heads only."""
