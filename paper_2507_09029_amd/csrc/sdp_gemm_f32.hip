@@ -25,6 +25,7 @@
 #include "sdp_internal.h"
 #include "sdp_swiglu.h"
 
+#include <cmath>
 #include <type_traits>
 
 namespace sdp {
@@ -641,6 +642,7 @@ int choose(const Dev& g, const char* name, hipStream_t s) {
     }
     auto cost = [&](int b, double weight) {
         const int64_t tiles = (int64_t)((g.M + b - 1) / b) * ((g.N + b - 1) / b) * (g.nbatch > 0 ? g.nbatch : 1);
+        if (tiles * 256 > UINT32_MAX) return HUGE_VAL; // threads of one launch
         return (double)((tiles + 255) / 256) * b * b * weight;
     };
     const double c128 = cost(128, 1.0), c64 = cost(64, 1.1), c32 = cost(32, 1.3);

@@ -188,6 +188,22 @@ def test_forward_outputs_may_take_the_place_of_W2(sdp, dtype, mode, taken):
         assert (a.double() - b.double()).abs().max() <= (1e-5 if dtype == "f32" else 1e-2) * b.abs().max()
 
 
+def test_f32_more_tiles_than_one_launch_holds(sdp):
+    """F = 2^29 + 64 columns of one token: more 32-wide tiles than a launch of 256-thread workgroups takes."""
+    F, d = (1 << 29) + 64, 4
+    X = torch.tensor([[0.5, -0.25, 1.0, 0.75]], device="cuda")
+    W1, W3 = (torch.ones((F, d), device="cuda") for _ in range(2))
+    W2T = torch.zeros((F, d), device="cuda")
+    rows = torch.tensor([0, 1, 12345, 1 << 28, F - 65, F - 2, F - 1], device="cuda")
+    W2T[rows] = torch.arange(28, dtype=torch.float32, device="cuda").view(7, 4) - 11.0
+    print(f"f32 bm T=1 d={d} F={F}", flush=True)
+    Y, G, U = sdp.masked_mlp_fwd("bm", X, W1, W3, W2T, None)
+    assert bool((G == 2.0).all()) and bool((U == 2.0).all())
+    act = 4.0 / (1.0 + np.exp(-2.0))
+    want = act * W2T[rows].double().sum(0)
+    assert float((Y[0].double() - want).abs().max() / want.abs().max()) <= 1e-5
+
+
 @pytest.mark.parametrize("w", F32_TILES, ids=[w.name for w in F32_TILES])
 def test_f32_tiles(sdp, orc, w):
     run_case(sdp, orc, w, [1], dw_layout="scatter" if w.T % 2 else "compact")
