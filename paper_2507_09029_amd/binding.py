@@ -136,6 +136,9 @@ def _native():
             _build.build_library()
         from . import _sdp_native
 
+        if _sdp_native.torch_version != torch.__version__:
+            raise ImportError(f"_sdp_native.so was built against torch {_sdp_native.torch_version}, this is torch "
+                              f"{torch.__version__}: build the library again (python -m paper_2507_09029_amd.build)")
         _calls = _sdp_native
     return _calls
 

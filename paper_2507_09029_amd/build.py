@@ -12,6 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libsdp_hip.so")
 NATIVE = os.path.join(HERE, "_sdp_native.so")
+NATIVE_FOR = os.path.join(OBJ, "_sdp_native.torch")  # version of the torch it was built against
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
@@ -28,6 +29,14 @@ def _stale(target, deps):
         return True
     t = os.path.getmtime(target)
     return any(os.path.getmtime(d) > t for d in deps)
+
+
+def _native_stale(deps, torch_version):
+    """The call module uses torch's C++ interface: it is as old as its sources or built against another torch."""
+    if _stale(NATIVE, deps) or not os.path.exists(NATIVE_FOR):
+        return True
+    with open(NATIVE_FOR) as f:
+        return f.read() != torch_version
 
 
 def build_library(force=False, verbose=False):
@@ -62,18 +71,20 @@ def build_library(force=False, verbose=False):
         if rc != 0:
             raise RuntimeError(f"link failed:\n{out}")
     src = os.path.join(CSRC, "sdp_native.cpp")
-    if force or _stale(NATIVE, [src] + hdrs):
-        import torch
+    import torch
 
+    if force or _native_stale([src] + hdrs, torch.__version__):
         T = os.path.dirname(torch.__file__)
         cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-shared", "-fPIC",
-               f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I", os.path.join(ROOT, "include"),
+               f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", f'-DSDP_TORCH_VERSION="{torch.__version__}"', "-I", os.path.join(ROOT, "include"),
                "-I", os.path.join(T, "include"), "-I", os.path.join(T, "include", "torch", "csrc", "api", "include"),
                "-I", sysconfig.get_paths()["include"], src, "-o", NATIVE, "-L", HERE, "-l:libsdp_hip.so",
                "-L", os.path.join(T, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-Wl,-rpath,$ORIGIN"]
         _, rc, out = run(cmd)
         if rc != 0:
             raise RuntimeError(f"building {NATIVE} failed:\n{out}")
+        with open(NATIVE_FOR, "w") as f:
+            f.write(torch.__version__)
     return LIB
 
 

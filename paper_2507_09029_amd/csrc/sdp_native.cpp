@@ -120,4 +120,12 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_sdp_native", nullptr, -1, methods
 
 } // namespace
 
-PyMODINIT_FUNC PyInit__sdp_native() { return PyModule_Create(&module); }
+PyMODINIT_FUNC PyInit__sdp_native() {
+    PyObject* m = PyModule_Create(&module);
+    // the C++ interface of one torch build: binding.py compares
+    if (m && PyModule_AddStringConstant(m, "torch_version", SDP_TORCH_VERSION) < 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
+}

@@ -251,3 +251,23 @@ def test_compiled_calls_refuse_what_is_no_gpu_tensor():
         call(0, 1)
     with pytest.raises(OverflowError):
         call(1 << 40, 1, 8, 16, 24, 8, X, W, W, W, None, X, X, X, 0, 0, 0)
+
+
+def test_compiled_calls_belong_to_one_torch(monkeypatch, tmp_path):
+    import torch
+
+    from paper_2507_09029_amd import build
+
+    binding._native()
+    monkeypatch.setattr(binding, "_calls", None)
+    monkeypatch.setattr(torch, "__version__", "0.0")
+    with pytest.raises(ImportError, match="built against torch"):
+        binding._native()
+    target, stamp = tmp_path / "native.so", tmp_path / "native.torch"
+    target.write_bytes(b"")
+    monkeypatch.setattr(build, "NATIVE", str(target))
+    monkeypatch.setattr(build, "NATIVE_FOR", str(stamp))
+    assert build._native_stale([], "2.0")  # of an unknown torch
+    stamp.write_text("2.0")
+    assert not build._native_stale([], "2.0")
+    assert build._native_stale([], "2.1")
