@@ -122,10 +122,10 @@ CASES = [
     AttnWorkload("one_token", 3, 1, 64, 2, 64, 2, 2, 32),
     AttnWorkload("two_heads_of_four", 2, 128, 128, 4, 64, 2, 4, 33),
     AttnWorkload("ragged_seq_all_heads", 2, 200, 136, 3, 64, 3, 2, 34),     # C = 1: the dense block; S % 64 = 8
-    AttnWorkload("ragged_depth", 1, 300, 72, 4, 64, 1, 4, 35),             # d % 16 != 0: plain contraction kernels
+    AttnWorkload("ragged_depth", 1, 300, 72, 4, 64, 1, 4, 35),             # d % 64 = 8: a partial last depth step
     AttnWorkload("several_blocks", 2, 520, 256, 8, 64, 4, 4, 36),          # 5 query blocks, tail of 8
     AttnWorkload("odd_tokens", 1, 77, 64, 2, 64, 1, 2, 37),                # T % 8 != 0
-    # plain core: fp32 (1e-5), the paper's head width 50, bf16 with head widths other than 64
+    # fp32 core (1e-5); bf16 heads other than 64 wide
     AttnWorkload("f32_hd64", 2, 150, 96, 4, 64, 2, 4, 38, "f32"),
     AttnWorkload("f32_hd50_odd_sizes", 2, 93, 75, 3, 50, 2, 2, 39, "f32"),
     AttnWorkload("f32_hd128", 1, 70, 64, 2, 128, 1, 2, 40, "f32"),
@@ -326,11 +326,11 @@ def test_forward_output_may_take_the_place_of_its_weights(sdp, dtype, mode):
 
 @pytest.mark.parametrize("dtype,hd,d", [("f32", 1, 1), ("bf16", 72, 8)])
 def test_more_items_than_one_grid_axis_holds(sdp, dtype, hd, d):
-    """65535 sequences of one token and 260 heads: 17 million items of the core, more workgroups of 256 threads than one axis of
-    a grid takes.  A softmax over one key is constant, so Y = X Wv^T Wo and dX likewise, dWq = dWk = 0.  X and dY are positive:
+    """65535 sequences of one token and 460 heads: 30 million items of the core, more workgroups of 256 threads than one axis of
+    a grid takes (bf16: and operands of 4 GiB and more, so that dX and the weight gradients run on the plain contraction).  A softmax over one key is constant, so Y = X Wv^T Wo and dX likewise, dWq = dWk = 0.  X and dY are positive:
     the weight gradients' sums over 65535 tokens then do not cancel, and fp32 roundings along the way (at worst one of 2^-24 for
     each of the 16384 additions to an accumulator, 1e-3; a random walk of them, 1e-5) stay below 1e-4 of the result."""
-    Bt, H = 65535, 260
+    Bt, H = 65535, 460
     g = torch.Generator(device="cuda").manual_seed(54)
     dt = torch.float32 if dtype == "f32" else torch.bfloat16
     X, dY, Wqkv, WoT = (torch.randn(s, generator=g, device="cuda").mul_(f).to(dt) for s, f in
@@ -412,8 +412,8 @@ def test_attention_full_step_average(sdp, orc):
 
 
 @pytest.mark.parametrize("mode", ["fm", "bm"])
-def test_plain_core_and_mfma_core_agree_on_the_same_inputs(sdp, mode):
-    """The same bf16-valued inputs through the fp32 path (plain contractions and plain attention core, no
+def test_fp32_core_and_bf16_core_agree_on_the_same_inputs(sdp, mode):
+    """The same bf16-valued inputs through the fp32 path (fp32 contractions and fp32 attention core, no
     intermediate rounding) and through the bf16 path (MFMA contractions and MFMA core): two implementations that
     share no kernel must agree to the bf16 path's rounding, without the oracle in between."""
     from helpers import err_report, err_report_rows

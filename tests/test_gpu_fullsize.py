@@ -224,7 +224,7 @@ def test_attention_500M_one_sequence_and_sampled_gradient_rows(sdp, orc):
 TILES = [
     (workloads.MlpWorkload("t1000", "bf16", 1000, 760, 1600, 1032, 2, "fm", 71),
      {"mlp_gate_up": "128x128", "mlp_down": "64x64", "mlp_dact": "64x64", "mlp_dx": "64x64", "mlp_dw": "128x128"}),
-    (workloads.MlpWorkload("t2056", "bf16", 2040, 1016, 2600, 2040, 2, "fm", 72),
+    (workloads.MlpWorkload("t2040", "bf16", 2040, 1016, 2600, 2040, 2, "fm", 72),
      {"mlp_gate_up": "128x256", "mlp_down": "64x64", "mlp_dact": "128x128", "mlp_dx": "64x64", "mlp_dw": "128x256"}),
     (workloads.MlpWorkload("t4072", "bf16", 4072, 1192, 3600, 3208, 2, "fm", 73),
      {"mlp_down": "128x192", "mlp_dx": "128x192", "mlp_dact": "256x256", "mlp_dw": "256x256"}),

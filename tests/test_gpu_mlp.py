@@ -121,7 +121,7 @@ def test_f32_few_tiles(sdp, orc, w):
 
 
 def test_f32_dx_may_take_the_place_of_dy(sdp):
-    """dX written over dY: the weight gradients, which read dY, come first."""
+    """dX written over dY, which the weight gradients read."""
     w = F32_FEW[4]
     Wd = [t.cuda() for t in workloads.mlp_weights(w)]
     mask, idx, pos, cov = sdp.make_masks(w.K, w.F, w.p, w.mask_seed, True)
@@ -204,6 +204,43 @@ def test_f32_more_tiles_than_one_launch_holds(sdp):
     assert float((Y[0].double() - want).abs().max() / want.abs().max()) <= 1e-5
 
 
+def test_rows_beyond_the_mfma_kernels_address_range(sdp, orc):
+    """F = 2^22 + 8 under backward masking: rows of 2^22 elements and more leave the MFMA kernel's address range, so gate_up,
+    down, dact (with the column-compacted copies), dX and the three weight gradients (depth-major left operands) run on the plain
+    bf16 kernel, the transposes in launches of their own.  The weight gradients sum over 8 tokens only, as in the small
+    random shapes (test_gpu_random_shapes.py), but have 1.7e7 elements: the rounding points alone put their elementwise maxima
+    at 4.0e-2, 5.2e-2 and 5.7e-2 (rounding model, on the CPU), so the fixed bound is 8e-2 and the model-relative check (1.5 times
+    those figures) is the tighter one."""
+    T, d, F, p = 8, 8, (1 << 22) + 8, 1 << 21
+    w = MlpWorkload("plain_bf16_bm", "bf16", T, d, F, p, 2, "bm", 29)
+    Wh = workloads.mlp_weights(w)
+    W, W64 = [t.cuda() for t in Wh], [workloads.to_f64(t) for t in Wh]
+    mask, idx, pos, cov = sdp.make_masks(w.K, F, p, w.mask_seed, False)
+    m = orc.make_masks(w.K, F, p, w.mask_seed, False)[1]
+    assert (mask[1].cpu().numpy() == m).all()
+    X, dY = workloads.mlp_batch(w, 1)
+    sdp.profile_filter(None)
+    sdp.profile_reset()
+    sdp.profile_enable(True)
+    try:
+        Y, G, U = sdp.masked_mlp_fwd("bm", X.cuda(), *W, idx[1])
+        dX, *dW = sdp.masked_mlp_bwd("bm", X.cuda(), dY.cuda(), *W, idx[1], G, U)
+        torch.cuda.synchronize()
+        launches = {name: calls for name, (calls, ms) in sdp.profile_read().items()}
+    finally:
+        sdp.profile_enable(False)
+    assert launches["mlp_dw"] == 3 and launches["mlp_tr_bwd"] == 1 and launches["mlp_wt_fwd"] == 1, launches
+    X, dY = workloads.to_f64(X), workloads.to_f64(dY)
+    ref = orc.worker_step("bm", m, X, dY, *W64)
+    for name, got in (("Y", Y), ("G", G), ("U", U), ("dX", dX)):
+        assert_close(workloads.to_f64(got), ref[name], 2e-2, name)
+    S = np.flatnonzero(m)
+    ref = {n: ref[n][S] for n in ("dW1", "dW3", "dW2T")}
+    model = rm.mlp_model("bm", m, X, dY, *W64)
+    for name, got in zip(("dW1", "dW3", "dW2T"), dW):
+        assert_close_with_model(workloads.to_f64(got), model[name][S], ref[name], 2e-2, name, elem_allow=8e-2)
+
+
 @pytest.mark.parametrize("w", F32_TILES, ids=[w.name for w in F32_TILES])
 def test_f32_tiles(sdp, orc, w):
     run_case(sdp, orc, w, [1], dw_layout="scatter" if w.T % 2 else "compact")
@@ -251,7 +288,7 @@ def test_config1_full_step_average(sdp, orc):
 
 @pytest.mark.parametrize("mode", ["fm", "bm"])
 def test_fp32_path_and_bf16_path_agree_on_the_same_inputs(sdp, mode):
-    """The same bf16-valued inputs through the fp32 kernels (plain FMA contractions, no intermediate rounding) and
+    """The same bf16-valued inputs through the fp32 kernels (fp32 matrix instructions, no intermediate rounding) and
     through the bf16 MFMA kernels: two implementations inside the library that share no contraction code must
     agree to the bf16 path's rounding (about 1e-2), without the oracle in between."""
     from helpers import err_report
@@ -280,7 +317,7 @@ def _filled(shape, dtype, fill):
 
 
 POISON = [w for w in SMALL if w.name in ("ragged_f32_fm", "tiles_bf16_fm", "tiles_bf16_bm", "aligned_bf16_bm", "tiny_bf16_fm")] + [
-    MlpWorkload("mixed_paths_bf16_fm", "bf16", 552, 440, 1536, 1312, 4, "fm", 23),  # depth 440: plain kernels beside MFMA ones
+    MlpWorkload("partial_steps_bf16_fm", "bf16", 552, 440, 1536, 1312, 4, "fm", 23),  # every depth ends in a partial step
 ]
 
 
