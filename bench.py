@@ -27,7 +27,7 @@ sys.path.insert(0, ROOT)
 
 PEAK_BF16_TFLOPS = 2500.0  # MI355X dense bf16 MFMA peak (published: 2.5 PFLOP/s)
 PEAK_HBM_GBS = 8000.0      # MI355X HBM3E peak (published: 8 TB/s)
-PEAK_FP32_VECTOR_TFLOPS = 157.3  # 256 CUs x 128 fp32 FMA lanes x 2 flop x 2.4 GHz
+PEAK_FP32_MATRIX_TFLOPS = 157.3  # 256 CUs x 4 matrix cores x 64 flop a cycle (v_mfma_f32_16x16x4_f32) x 2.4 GHz
 
 # HBM-side bytes per launch come from rocprofv3 counter runs (FETCH_SIZE, then WRITE_SIZE, each scaled by what
 # the same counter reads for a 1 GiB copy).  Counters cannot be read from inside this process: the file below is
@@ -86,7 +86,13 @@ def flops_per_launch(name, w):
         "mlp_dact": 2 * w.T * w.d * n,
         "mlp_dx": 4 * w.T * w.d * n,
         "mlp_dw": 6 * w.T * w.d * w.p,  # one batched launch for dW1, dW3, dW2T
+        "mlp_dx_dw": 4 * w.T * w.d * n + 6 * w.T * w.d * w.p,  # fp32: dX and the weight gradients as one launch
     }.get(name)
+
+
+# bf16: transposes that a launch carries as extra workgroups when its last round leaves CUs idle; otherwise they are a
+# launch of their own, under this name.  A carrying kernel's time and rate include them.
+CARRIED = {"mlp_gate_up": "mlp_wt_fwd", "mlp_dact": "mlp_tr_bwd"}
 
 
 def _omp_threads(n=None):
@@ -308,7 +314,8 @@ def bench_attention(sdp, torch, steps, w=None):
                               "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                               "frac": (core_fwd + core_bwd) / (core_ms * 1e-3) / 1e12 / PEAK_BF16_TFLOPS, "traffic": None},
                  "forward_backward_tflops": (core_fwd + core_bwd) / (core_ms * 1e-3) / 1e12,
-                 "note": "causal: the half of the S x S products that is computed is counted (2 S^2 hd per head forward, 5 S^2 hd backward)"},
+                 "note": "causal: the half of the S x S products that is computed is counted (2 S^2 hd per head forward, 5 S^2 hd backward); "
+                         "the times include the transposed copies for the contractions that follow, which the core's launches carry"},
         "vendor_attention_yardstick": vendor_attention_yardstick(torch, w) if w.hd % 8 == 0 else None,
     }
 
@@ -537,6 +544,8 @@ def bench_mlp(sdp, torch, w, a, steps, warmup):
             if f:
                 out[name]["tflops"] = f / (avg_ms * 1e-3) / 1e12
                 out[name]["launch"] = sdp.profile_launch_shape(name)
+            if w.dtype == "bf16" and name in CARRIED and CARRIED[name] not in prof:
+                out[name]["carries"] = CARRIED[name]
         return out
 
     kernels, dominant = {}, None
@@ -583,11 +592,10 @@ def bench_mlp(sdp, torch, w, a, steps, warmup):
         # tiles: its time (from the survey; it is not timed live) counts against the launch
         reduce_ms = kernels.get(dominant + "_reduce", {}).get("avg_ms", 0.0)
         ach = flops_per_launch(dominant, w) / ((avg_ms + reduce_ms) * 1e-3) / 1e12
-        # the fp32 path (config 1, a correctness configuration) runs on the vector ALUs, not on the matrix cores
-        bound, peak = ("mfma", PEAK_BF16_TFLOPS) if w.dtype == "bf16" else ("alu", PEAK_FP32_VECTOR_TFLOPS)
+        peak = PEAK_BF16_TFLOPS if w.dtype == "bf16" else PEAK_FP32_MATRIX_TFLOPS
         shape = kernels[dominant].get("launch")
-        roofline = {"bound": bound, "kernel": dominant, "achieved": ach, "peak": peak, "unit": "TFLOP/s",
-                    "frac": ach / peak,
+        roofline = {"bound": "mfma", "kernel": dominant, "carries": kernels[dominant].get("carries"), "achieved": ach, "peak": peak,
+                    "unit": "TFLOP/s", "frac": ach / peak,
                     "traffic": recorded_traffic(w.name, dominant, shape) if S == 1 else None,
                     "traffic_unit": "bytes per launch (L2 <-> fabric, rocprofv3 FETCH_SIZE + WRITE_SIZE, recorded for this "
                                     "launch configuration in profiles/hbm_traffic_recorded.json; null if none matches)",
