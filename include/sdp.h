@@ -26,6 +26,9 @@
  *   - dtype SDP_F32: all tensors fp32.  dtype SDP_BF16: all tensors bf16,
  *     products accumulated in fp32, intermediates that feed a later
  *     contraction rounded once to bf16 (round to nearest even).
+ *   - Bits: the same call on the same inputs gives the same bits.  The order of its fp32 sums (a
+ *     contraction's depth, a softmax's keys) follows from launch shapes that are chosen from all its
+ *     sizes, so one row, sequence or head may differ in its last bits between calls of other sizes.
  *   - Errors: argument errors are found on the host before any launch and
  *     returned as a negative sdp_status; nothing is enqueued in that case.
  *     No call aborts or throws.
@@ -170,6 +173,8 @@ int sdp_masked_mlp_fwd(int mode, int dtype, int T, int d, int F, int p, const vo
  *   dw_layout SDP_DW_SCATTER: they are full [F][d] buffers; row idx_k[i] is written, rows off the
  *     mask are left untouched (sdp_coverage_grad_avg never reads them).
  *   ws: sdp_masked_mlp_bwd_workspace_bytes(mode, dtype, T, d, F, p).
+ * Outputs may take the place of operands (dX over dY or X, a gradient over its weights): every operand is read, or copied into
+ * the workspace, before an output is written.  The same holds for sdp_masked_attn_bwd.
  * Limits as for the forward call, and additionally T a multiple of 8 for SDP_BF16.
  * ------------------------------------------------------------------------------------------- */
 size_t sdp_masked_mlp_bwd_workspace_bytes(int mode, int dtype, int T, int d, int F, int p);
@@ -203,8 +208,13 @@ int sdp_masked_mlp_bwd(int mode, int dtype, int T, int d, int F, int p, const vo
  *   64 columns of which the last 64 - hd hold zeros, so that the block runs on the MFMA core.
  *   ws: sdp_masked_attn_fwd_workspace_bytes(...).
  * Limits: hd <= 128 (else UNSUPPORTED); for SDP_BF16 d a multiple of 8 (16-byte rows), and hd a multiple of 8 when
- * above 64; Bt, H <= 65535; pointers 16-byte aligned.  bf16 runs the MFMA attention core (probabilities and
- * logit gradients are rounded once to bf16 where they enter a product), fp32 a core in fp32 throughout.  Errors as for the MLP calls.
+ * above 64; Bt, H <= 65535; pointers 16-byte aligned.  Errors as for the MLP calls.
+ * Arithmetic of the core: fp32 throughout for SDP_F32.  SDP_BF16 with hd <= 64: probabilities and logit gradients are rounded
+ * once to bf16 where they enter a product, and the softmax sum runs over the rounded probabilities.  SDP_BF16 with hd > 64:
+ * they enter as two bf16 terms (16 bits of mantissa) and the sum runs over the unrounded ones.  Sums are fp32 in all cases.
+ * A value that is not finite at some token reaches only results that depend on that token (SDP_F32, and SDP_BF16 with
+ * hd > 64); with SDP_BF16 and hd <= 64 it may also make results of other tokens of the same sequence, up to 127 positions
+ * away, NaN.
  * ------------------------------------------------------------------------------------------- */
 int sdp_masked_attn_saved_head_width(int dtype, int hd);
 size_t sdp_masked_attn_fwd_workspace_bytes(int mode, int dtype, int Bt, int S, int d, int H, int hd, int ph);

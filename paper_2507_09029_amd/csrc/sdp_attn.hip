@@ -15,7 +15,7 @@
 // causal attention on 32x32x16 bf16 MFMA tiles for heads of 64, 96 or 128 columns (wider and narrower ones take the next
 // of these widths), with the running-maximum formulation of the softmax (logits in base 2), so that no T x T matrix is
 // stored.  Heads of 65 .. 128 used to run the plain core: one sequence of 1500 tokens, 4 of 8 heads of 128, forward and
-// backward of the block 20.0 ms then, 0.18 ms on the wide MFMA core.
+// backward of the block 20.0 ms then, 0.15 ms on the wide MFMA core.
 //
 // Accumulator convention.  v_mfma_f32_32x32x16 computes D[m][n] += sum_k A[m][k] B[k][n]; lane L supplies
 // A[L % 32][8 (L / 32) + e] and B[8 (L / 32) + e][L % 32], e = 0..7, and holds D[8 q + 4 (L / 32) + r][L % 32]

@@ -12,15 +12,16 @@
 //   128 x 128 (4 waves of 64 x 64), 64 x 64 (4 waves of 32 x 32), and 32 x 32 whose 4 waves share one tile and split its
 //   depth (each takes 16 of every 64 depth steps; their sums meet in LDS), for launches with fewer tiles than CUs;
 //   the smallest launches take 16 x 16 tiles in a loop of their own (further down).
-// Tiles move global -> registers -> LDS, the next two or three steps in flight; one barrier per step.
+// Tiles move global -> registers -> LDS, the next three steps in registers (one for the 128-wide tile); one barrier per step.
 //
 // A depth slot is free to stand for any k as long as both operands agree: in a group of 16 depth steps, lane group
 // g = lane / 16 takes k = 4 g + j in the j-th of four MFMAs, so an operand stored by rows is one 16-byte LDS read per
 // 16 x 16 fragment, a depth-major one four 4-byte reads; row strides of 4 (mod 16) words keep both free of conflicts.
 //
 // Measured: four workers' steps at T = 256, d = 256, F = 1024, p = 512 (twelve launches a worker with a plain FMA kernel
-// and transposed copies before, five now): 2079 -> 165 us; per launch 7 - 12 us, of which about 4 us is what an empty
-// kernel takes.  (206 us while every step waited for the newest list entry, computed clamped 64-bit addresses per load
+// and transposed copies before, five with this loop): 2079 -> 165 us, and 139 with the 16 x 16 tiles and dX and the weight
+// gradients as one launch (four a worker; 101 us since the host calls are compiled); per launch 5 - 10 us, of which about 4 us
+// is what an empty kernel takes.  (206 us while every step waited for the newest list entry, computed clamped 64-bit addresses per load
 // and branched around its loads, so that the loads in flight could not be counted.)
 #include "sdp_internal.h"
 #include "sdp_swiglu.h"

@@ -18,7 +18,7 @@
 // Under backward masking the weight-gradient contraction reads only the p kept rows: the gradient is
 // computed on the worker's mask and nowhere else.  fp32 tensors take the fp32 contraction, which reads every
 // operand as it is stored (the weights depth-major through the worker's list, dG, dU, Act depth-major on its
-// columns): no copies, five launches.  bf16 operands beyond the MFMA kernel's address range go through the plain
+// columns): no copies, four launches (five where dX and the weight gradients are not one).  bf16 operands beyond the MFMA kernel's address range go through the plain
 // kernel, which reads dG, dU, Act depth-major (and, under backward masking, their column-compacted copies [T][p]).
 #include "sdp_internal.h"
 
