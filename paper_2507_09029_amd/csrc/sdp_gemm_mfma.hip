@@ -20,9 +20,10 @@
 // r*8 + (c ^ ((r >> 1) & 7)).  A lane's MFMA operand (8 consecutive k of one row) is one chunk, one
 // ds_read_b128, and the lanes served together fall on distinct banks.
 //
-// Main loop (not the 64 x 64 tile): the waves form two groups that alternate between a phase of LDS reads + load issue and a
+// Main loop of the 256-row tiles: the waves form two groups that alternate between a phase of LDS reads + load issue and a
 // phase of MFMAs only, one phase apart, so that on every SIMD one wave computes while the other one
-// fetches (see the comment at the loop).
+// fetches (see the comment at the loop).  128-row tiles: every wave reads a half step ahead of its MFMAs, with one barrier a
+// step.  64 x 64: each wave on its own, no barrier.
 //
 // The MFMA is issued with the B fragment as its first operand: a lane then holds, for one output
 // row m, 4 consecutive columns n.  Epilogues go through LDS: each wave packs 32 x WN outputs as bf16
@@ -166,10 +167,8 @@ struct Geometry {
     static constexpr int FM = WM / 32, FN = WN / 32;
     static constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
     static constexpr bool kWaveDepth = BM == 64; // each wave runs its own depth steps on the whole tile (see the loop)
-    // LDS stages of A (B has three): two, or three for the 128-row tiles, whose steps are about as short as a load takes
-    // (A of the next step asked for only one step ahead: 32 steps of a 128 x 128 tile of 4 waves 31 us, 21 us this way
-    // with 8; four and five stages of both operands were no faster, 25 us)
-    static constexpr int A_STAGES = BM == 128 ? 3 : 2;
+    static constexpr bool kPipe = BM == 128; // fragments read a half step ahead, one barrier a step (see the loop)
+    static constexpr int A_STAGES = kPipe ? 3 : 2; // LDS stages of A; B has three
     // kWaveDepth: two stages of both operands per wave
     static constexpr int RING = kWaveDepth ? 2 * NW * (A_BYTES + B_BYTES) : A_STAGES * A_BYTES + 3 * B_BYTES;
     // epilogue strip: 32 rows x SW columns of bf16, rows padded by 8 bytes
@@ -435,8 +434,10 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
     unsigned char* const lds_a = smem;
     unsigned char* const lds_b = smem + Geo::A_STAGES * A_BYTES;
 
-    // loads [first, last) of the SA (resp. SB) slabs of depth step kt; TAIL: K % 64 != 0
-    auto issue_a = [&](int kt, int slot, auto tail_c, int first, int last) {
+    // loads [first, last) of the SA (resp. SB) slabs of depth step kt; TAIL: the step may end beyond the depth.  Only the last
+    // step of an operand pair does, and only its loads compare (with the compare and two selects on every load: 3208 deep
+    // instead of 3200 cost a 128 x 192 tile 13 us of 26, a 256 x 192 one 3 of 42).
+    auto issue_a = [&](int kt, int slot, auto tail_c, int first, int last) __attribute__((always_inline)) {
         constexpr bool TAIL = decltype(tail_c)::value;
         const bool second = EPI == EPI_DUAL_ACC && kt >= nk1;
         const int k0 = (kt0 + (second ? kt - nk1 : kt)) * BK;
@@ -451,7 +452,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
             __builtin_amdgcn_global_load_lds((glb_void_ptr)src, (lds_void_ptr)(sa + (wave + NW * i) * 1024), 16, 0, 0);
         }
     };
-    auto issue_b = [&](int kt, int slot, auto tail_c, int first, int last) {
+    auto issue_b = [&](int kt, int slot, auto tail_c, int first, int last) __attribute__((always_inline)) {
         constexpr bool TAIL = decltype(tail_c)::value;
         const bool second = EPI == EPI_DUAL_ACC && kt >= nk1;
         const int k0 = (kt0 + (second ? kt - nk1 : kt)) * BK;
@@ -491,28 +492,112 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
     for (int s = 0; s < BK / 32; ++s) row_off[s] = (((4 * s + lq) ^ ((l16 >> 1) & 7)) * 16) + l16 * 128;
     const int a_base = WM * wm * 128;
 
-    // fragments of sub-step s: fa[2 i + h] = rows 32 i + 16 h .. of the wave's A rows, fb[2 j + w] likewise for B
-    auto read_frags = [&](const unsigned char* sa, const unsigned char* sb, int s, bf16x8 (&fa)[2 * FM], bf16x8 (&fb)[2 * FN]) {
-#pragma unroll
-        for (int i = 0; i < 2 * FM; ++i)
-            fa[i] = __builtin_bit_cast(bf16x8, *(const u32x4*)(sa + a_base + i * 16 * 128 + row_off[s]));
-#pragma unroll
-        for (int j = 0; j < 2 * FN; ++j)
-            fb[j] = __builtin_bit_cast(bf16x8, *(const u32x4*)(sb + (bfrag[j >> 1] + 16 * (j & 1)) * 128 + row_off[s]));
+    // fragment reads of sub-step s: A fragment i = rows 16 i .. of the wave's A rows, B fragment j = rows 16 j .. likewise
+    auto read_a = [&](const unsigned char* sa, int s, int i) __attribute__((always_inline)) {
+        return __builtin_bit_cast(bf16x8, *(const u32x4*)(sa + a_base + i * 16 * 128 + row_off[s]));
+    };
+    auto read_b = [&](const unsigned char* sb, int s, int j) __attribute__((always_inline)) {
+        return __builtin_bit_cast(bf16x8, *(const u32x4*)(sb + (bfrag[j >> 1] + 16 * (j & 1)) * 128 + row_off[s]));
     };
     // B fragment first: the accumulator tile is then indexed [n][m] in the MFMA's own layout, i.e. lane (l16, lq)
     // holds, for output row m = l16 of the tile, its columns n = 4 lq + r in element r.
-    auto mfma_step = [&](const bf16x8 (&fa)[2 * FM], const bf16x8 (&fb)[2 * FN]) {
+    auto mfma_one = [&](bf16x8 a, bf16x8 b, int i, int j) __attribute__((always_inline)) {
+        f32x4& c = acc[i >> 1][j >> 1][2 * (i & 1) + (j & 1)];
+        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b, a, c, 0, 0, 0);
+    };
+    auto barrier = [&]() __attribute__((always_inline)) { // the bare instruction: loads of later steps stay in flight across it
+        __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    using std::false_type;
+    using std::integral_constant;
+    using std::true_type;
+
+    if constexpr (Geo::kPipe) {
+        // ---- main loop of the 128-row tiles.  A depth step is two 32-deep halves; while a wave's MFMAs of one half run, its
+        // fragments of the next half are read and its share of later steps' loads is issued between them, at most one of
+        // either per MFMA.  One barrier a step, between the halves:
+        //   first half of step k: MFMAs on (k, 0); reads of (k, 1); loads of B for step k + 2
+        //   wait for the own loads of step k + 1 and the own reads of step k; barrier: step k + 1 has landed, step k is read
+        //   second half: MFMAs on (k, 1); reads of (k + 1, 0); loads of A for step k + 3
+        // A and B have three stages each; the stage of step k is filled again from that barrier on.  The phases of the
+        // 256-row tiles (four barriers a step) cost such a tile more than its 8 to 16 MFMAs a phase: 4096 x 1200 outputs,
+        // 3200 deep, chip at full clock, 128 x 192 tiles 39.7 -> 32.3 us, 128 x 128 57.7 -> 43.6, 128 x 256 38.4 -> 35.5
+        // (256 x 192 tiles 43.0 -> 46.5: those keep the phases).  The loads issued all at once after the barrier, in front of the
+        // MFMAs: 43.9 instead of 40.6 (at a lower clock).  Four or five stages: no faster.  A step's halves shared out between
+        // two groups of waves, whose tiles are then twice as high (three eighths fewer LDS reads): 33.
+        constexpr int S = 3, L = SA + SB;
+        static_assert(Geo::A_STAGES == S, "both operands have three stages");
+        constexpr int NM = 4 * FM * FN, NR = 2 * FM + 2 * FN; // MFMAs and fragment reads of a half step
+        static_assert(NR <= NM, "one read per MFMA");
+        bf16x8 fa[2][2 * FM], fb[2][2 * FN];
+        auto read_one = [&](int slot, int h, int r) __attribute__((always_inline)) {
+            if (r < 2 * FN) fb[h][r] = read_b(lds_b + slot * B_BYTES, h, r);
+            else fa[h][r - 2 * FN] = read_a(lds_a + slot * A_BYTES, h, r - 2 * FN);
+        };
+        // the MFMAs of half h; between them the reads of the other half from stage `slot` and `nload` loads
+        auto half_step = [&](int h, bool reads, int slot, int nload, auto load) __attribute__((always_inline)) {
 #pragma unroll
-        for (int i = 0; i < 2 * FM; ++i)
+            for (int m = 0; m < NM; ++m) {
+                const bool rd = reads && m < NR;
+                bool ld = false;
+                if (rd) read_one(slot, h ^ 1, m);
 #pragma unroll
-            for (int j = 0; j < 2 * FN; ++j) {
-                f32x4& c = acc[i >> 1][j >> 1][2 * (i & 1) + (j & 1)];
-                c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fb[j], fa[i], c, 0, 0, 0);
+                for (int l = 0; l < nload; ++l)
+                    if ((2 * l + 1) * NM / (2 * nload) == m) load(l), ld = true;
+                if (rd || ld) __builtin_amdgcn_sched_barrier(0);
+                mfma_one(fa[h][m / (2 * FN)], fb[h][m % (2 * FN)], m / (2 * FN), m % (2 * FN));
+                if (rd || ld) __builtin_amdgcn_sched_barrier(0);
             }
+        };
+        int kt = 0, slot = 0, prev = S - 1; // stages of steps kt and kt - 1
+        // R: steps left after this one, at most S; TA / TB: the step of the loads of A / B may end beyond the depth
+        auto step = [&](auto r_c, auto ta_c, auto tb_c) __attribute__((always_inline)) {
+            constexpr int R = decltype(r_c)::value;
+            half_step(0, true, slot, R >= S - 1 ? SB : 0, [&](int l) __attribute__((always_inline)) { issue_b(kt + S - 1, prev, tb_c, l, l + 1); });
+            if constexpr (R > 0) {
+                constexpr int in_flight = (R >= S ? S - 2 : R - 1) * L; // the loads younger than step kt + 1's
+                __builtin_amdgcn_sched_barrier(0);
+                SDP_WAIT_VMCNT(in_flight);
+                SDP_WAIT_LGKMCNT0();
+                barrier();
+            }
+            const int next = slot == S - 1 ? 0 : slot + 1;
+            half_step(1, R > 0, next, R >= S ? SA : 0, [&](int l) __attribute__((always_inline)) { issue_a(kt + S, slot, ta_c, l, l + 1); });
+            __builtin_amdgcn_sched_barrier(0);
+            prev = slot, slot = next, ++kt;
+        };
+#pragma unroll
+        for (int j = 0; j < S; ++j) { // B of step S - 1 follows in step 0
+            if (j < nk) issue_a(j, j, true_type{}, 0, SA);
+            if (j < nk && j < S - 1) issue_b(j, j, true_type{}, 0, SB);
+        }
+        if (nk >= S) SDP_WAIT_VMCNT((S - 2) * L + SA); else SDP_WAIT_VMCNT(0);
+        barrier();
+#pragma unroll
+        for (int r = 0; r < NR; ++r) read_one(0, 0, r);
+        constexpr integral_constant<int, S> full{};
+        if constexpr (EPI == EPI_DUAL_ACC) { // the first pair of operands ends with step nk1 - 1
+            while (kt + S < nk1 - 1) step(full, false_type{}, false_type{});
+            if (kt + S == nk1 - 1) step(full, true_type{}, false_type{});
+            if (kt + S == nk1) step(full, false_type{}, true_type{});
+        }
+        while (kt + S < nk - 1) step(full, false_type{}, false_type{});
+        if (kt + S == nk - 1) step(full, true_type{}, false_type{});
+        if (kt == nk - 3) step(integral_constant<int, 2>{}, true_type{}, true_type{});
+        if (kt == nk - 2) step(integral_constant<int, 1>{}, true_type{}, true_type{});
+        step(integral_constant<int, 0>{}, true_type{}, true_type{});
+    } else {
+    bf16x8 fa[2 * FM], fb[2 * FN];
+    auto read_half = [&](const unsigned char* sa, const unsigned char* sb, int h) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < 2 * FM; ++i) fa[i] = read_a(sa, h, i);
+#pragma unroll
+        for (int j = 0; j < 2 * FN; ++j) fb[j] = read_b(sb, h, j);
     };
 
-    // ---- main loop: two wave groups in alternating phases.
+    // ---- main loop of the 256-row tiles: two wave groups in alternating phases.
     // Group 0 = the first half of the waves, group 1 = the second half; the hardware places wave w of
     // a workgroup on SIMD w % 4, so every SIMD holds one wave of each group.  A depth step is cut into
     // two 32-deep halves.  Each wave alternates a READ phase (the 2 (FM + FN) fragment
@@ -526,87 +611,74 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
     //   phase 4 k + 1 : group 0 computes (k, 0);  group 1 reads (k, 0), issues A(k + 1)
     //   phase 4 k + 2 : group 0 reads (k, 1), issues the loads of B for step k + 2;  group 1 computes (k, 0)
     //   phase 4 k + 3 : group 0 computes (k, 1);  group 1 reads (k, 1), issues B(k + 2)
-    // A has two LDS stages (or three) and B three.  Stage contents of step k are read in phases 4 k .. 4 k + 3;
+    // A has two LDS stages and B three.  Stage contents of step k are read in phases 4 k .. 4 k + 3;
     // loads into the stages of step k - 1 are issued from phase 4 k on, after the barrier that ends
     // phase 4 k - 1, before which every wave has waited for its own LDS reads.  Before that same
     // barrier every wave waits until its loads for step k have landed (loads complete in issue
     // order; only the newest SB, B of step k + 1, may still be in flight).
-    // With three stages of A (kA3) phase 4 k issues A of step k + 2 instead, into the stage of step k - 1 like B.
     const int grp = wave / (NW / 2);
-    constexpr bool kA3 = Geo::A_STAGES == 3;
-    constexpr int kAhead = kA3 ? SA + SB : SB; // loads that may still be in flight when a step begins
-    bf16x8 fa[2 * FM], fb[2 * FN];
-    auto read_half = [&](const unsigned char* sa, const unsigned char* sb, int h) { read_frags(sa, sb, h, fa, fb); };
-    auto compute_half = [&]() {
+    auto compute_half = [&]() __attribute__((always_inline)) {
         __builtin_amdgcn_s_setprio(1);
-        mfma_step(fa, fb);
+#pragma unroll
+        for (int i = 0; i < 2 * FM; ++i)
+#pragma unroll
+            for (int j = 0; j < 2 * FN; ++j) mfma_one(fa[i], fb[j], i, j);
         __builtin_amdgcn_s_setprio(0);
     };
-    auto phase_end = [&]() {
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    auto step = [&](int kt, int slot, auto ia_c, auto ib_c, auto tail_c) {
-        constexpr bool IA = decltype(ia_c)::value; // step kt + 1 exists
-        constexpr bool IB = decltype(ib_c)::value; // step kt + 2 exists
-        const unsigned char* sa = lds_a + (kA3 ? slot : kt & 1) * A_BYTES;
+    int kt = 0, slot = 0;
+    // IA / IB: step kt + 1 / kt + 2 exists; TA / TB: it may end beyond the depth
+    auto step = [&](auto ia_c, auto ta_c, auto ib_c, auto tb_c) __attribute__((always_inline)) {
+        constexpr bool IA = decltype(ia_c)::value;
+        constexpr bool IB = decltype(ib_c)::value;
+        const unsigned char* sa = lds_a + (kt & 1) * A_BYTES;
         const unsigned char* sb = lds_b + slot * B_BYTES;
         const int slot2 = slot == 0 ? 2 : slot - 1; // (kt + 2) % 3
         // READ (kt, 0)
         read_half(sa, sb, 0);
-        if (kA3) {
-            if (IB) issue_a(kt + 2, slot2, tail_c, 0, SA);
-        } else if (IA) {
-            issue_a(kt + 1, (kt + 1) & 1, tail_c, 0, SA);
-        }
+        if (IA) issue_a(kt + 1, (kt + 1) & 1, ta_c, 0, SA);
         SDP_WAIT_LGKMCNT0();
-        phase_end();
+        barrier();
         // COMPUTE (kt, 0)
         compute_half();
-        phase_end();
+        barrier();
         // READ (kt, 1)
         read_half(sa, sb, 1);
-        if (IB) issue_b(kt + 2, slot2, tail_c, 0, SB);
+        if (IB) issue_b(kt + 2, slot2, tb_c, 0, SB);
         SDP_WAIT_LGKMCNT0();
         if (grp == 1) {
-            if (IB) SDP_WAIT_VMCNT(kAhead); else SDP_WAIT_VMCNT(0);
+            if (IB) SDP_WAIT_VMCNT(SB); else SDP_WAIT_VMCNT(0);
         }
-        phase_end();
+        barrier();
         // COMPUTE (kt, 1)
         compute_half();
         if (grp == 0) {
-            if (IB) SDP_WAIT_VMCNT(kAhead); else SDP_WAIT_VMCNT(0);
+            if (IB) SDP_WAIT_VMCNT(SB); else SDP_WAIT_VMCNT(0);
         }
-        phase_end();
+        barrier();
+        slot = slot == 2 ? 0 : slot + 1;
+        ++kt;
     };
-    auto run = [&](auto tail_c) {
-        issue_a(0, 0, tail_c, 0, SA);
-        issue_b(0, 0, tail_c, 0, SB);
-        if (nk > 1) {
-            if (kA3) issue_a(1, 1, tail_c, 0, SA);
-            issue_b(1, 1, tail_c, 0, SB);
-            SDP_WAIT_VMCNT(kAhead);
-        } else {
-            SDP_WAIT_VMCNT(0);
-        }
-        phase_end();
-        if (grp == 1) phase_end(); // group 1 runs one phase behind
-        int slot = 0;
-        int kt = 0;
-        for (; kt + 2 < nk; ++kt) {
-            step(kt, slot, std::true_type{}, std::true_type{}, tail_c);
-            slot = slot == 2 ? 0 : slot + 1;
-        }
-        if (kt + 1 < nk) {
-            step(kt, slot, std::true_type{}, std::false_type{}, tail_c);
-            slot = slot == 2 ? 0 : slot + 1;
-            ++kt;
-        }
-        step(kt, slot, std::false_type{}, std::false_type{}, tail_c);
-        if (grp == 0) phase_end();
-    };
-    if (g.K % BK == 0) run(std::false_type{}); else run(std::true_type{});
+    issue_a(0, 0, true_type{}, 0, SA);
+    issue_b(0, 0, true_type{}, 0, SB);
+    if (nk > 1) {
+        issue_b(1, 1, true_type{}, 0, SB);
+        SDP_WAIT_VMCNT(SB);
+    } else {
+        SDP_WAIT_VMCNT(0);
+    }
+    barrier();
+    if (grp == 1) barrier(); // group 1 runs one phase behind
+    if constexpr (EPI == EPI_DUAL_ACC) { // the first pair of operands ends with step nk1 - 1
+        while (kt + 3 < nk1) step(true_type{}, false_type{}, true_type{}, false_type{});
+        if (kt + 3 == nk1) step(true_type{}, false_type{}, true_type{}, true_type{});
+        if (kt + 2 == nk1) step(true_type{}, true_type{}, true_type{}, false_type{});
+    }
+    while (kt + 3 < nk) step(true_type{}, false_type{}, true_type{}, false_type{});
+    if (kt + 2 < nk) step(true_type{}, false_type{}, true_type{}, true_type{});
+    if (kt + 1 < nk) step(true_type{}, true_type{}, false_type{}, false_type{});
+    step(false_type{}, false_type{}, false_type{}, false_type{});
+    if (grp == 0) barrier();
+    }
     }
 
     // ================================ epilogue ================================
