@@ -901,7 +901,7 @@ __global__ void head_rows_kernel(const int32_t* __restrict__ head_idx, int ph, i
 // Token-contiguous copies: T tokens, zeros up to the next multiple of 8 (so that a depth of ragged T is whole 16-byte
 // chunks), and 64 more (see the MLP path: rows must not sit a power of two apart).
 int64_t depth_tokens(int64_t T) { return (T + 7) / 8 * 8; }
-int64_t ld_tokens(int64_t T) { return depth_tokens(T) + 64; }
+int64_t ld_tokens(int64_t T, int d, int E) { return line_ld(depth_tokens(T) + 64, d > 3 * E ? d : 3 * E); }
 
 // Columns a head takes in the saved tensors.  Bf16 heads narrower than 64 (the paper's 500M / 1B models have width
 // 50) are padded to 64 with zero features: a zero feature of Q and K adds nothing to a
@@ -914,8 +914,8 @@ bool mfma_core(int dtype) { return dtype == SDP_BF16; }
 size_t esize(int dtype) { return dtype == SDP_F32 ? 4 : 2; }
 
 // What a padded pass needs of its weights, one launch.  blockIdx.y = 0 .. 3: Wq, Wk, Wv, WoT of the n run heads, each padded
-// to hw rows: out[(i hw + r)][:] = r < hd ? in[(heads ? heads[i] : i) hd + r][:] : 0 for i < n, r < hw (Wp [3][n hw][d], WoP
-// [n hw][d]); d % 8 == 0, 16 bytes per thread.  blockIdx.y = 4 (backward): row lists of the weight-gradient launch, for
+// to hw rows: out[(i hw + r)][:] = r < hd ? in[(heads ? heads[i] : i) hd + r][:] : 0 for i < n, r < hw (Wp [3][n hw][ldp], WoP
+// [n hw][ldp]); d % 8 == 0, 16 bytes per thread.  blockIdx.y = 4 (backward): row lists of the weight-gradient launch, for
 // padded row m = i hw + r of the ph held heads
 //   gather[m]  = held[i] hw + r             (row of the all-heads operand, backward masking)
 //   scatter[m] = r < hd ? (full ? held[i] : i) hd + r : -1     (output row; padding rows are dropped)
@@ -925,6 +925,7 @@ struct PadArgs {
     uint16_t *Wp, *WoP;
     const int32_t *heads, *held; // null: every head, in order
     int n, ph, H, hd, hw, d, full;
+    int64_t ldp; // of Wp, WoP
     int32_t *gather, *scatter;
 };
 __global__ __launch_bounds__(256) void pad_heads_kernel(PadArgs a) {
@@ -944,10 +945,10 @@ __global__ __launch_bounds__(256) void pad_heads_kernel(PadArgs a) {
     const int head = row / a.hw, r = row % a.hw;
     const int z = y < 3 ? y : 0;
     const uint16_t* in = (y < 3 ? a.Wqkv : a.WoT) + (int64_t)z * a.H * a.hd * a.d;
-    uint16_t* out = (y < 3 ? a.Wp : a.WoP) + (int64_t)z * a.n * a.hw * a.d;
+    uint16_t* out = (y < 3 ? a.Wp : a.WoP) + (int64_t)z * a.n * a.hw * a.ldp;
     u32x4_t v = {0u, 0u, 0u, 0u};
     if (r < a.hd) v = *(const u32x4_t*)(in + ((int64_t)(a.heads ? a.heads[head] : head) * a.hd + r) * a.d + c * 8);
-    *(u32x4_t*)(out + (int64_t)row * a.d + c * 8) = v;
+    *(u32x4_t*)(out + (int64_t)row * a.ldp + c * 8) = v;
 }
 
 int check(int mode, int dtype, int Bt, int S, int d, int H, int hd, int ph) {
@@ -968,6 +969,9 @@ int check(int mode, int dtype, int Bt, int S, int d, int H, int hd, int ph) {
 // heads the forward pass and the core run on: the held ones (forward masking) or all of them (backward masking)
 int heads_run(int mode, int H, int ph) { return mode == SDP_MASK_FORWARD ? ph : H; }
 
+// rows of the weight copies in the workspace: WoC [d][E], Wc [d][3 E], Wp [3 E][d], WoP [E][d]
+int64_t ld_weights(size_t e, int64_t width, int64_t rows) { return e == 2 ? line_ld(width, rows) : width; }
+
 struct FwdWs {
     int32_t *rows_qkv, *rows_o;
     void *WoC, *Wp, *WoP; // Wp, WoP: padded copies of the run heads' rows of Wqkv / WoT (padded head widths only)
@@ -979,9 +983,9 @@ FwdWs fwd_ws(char* w, size_t e, int d, int E, bool padded) {
     auto take = [&](size_t n) { char* p = w ? w + off : nullptr; off += round_up(n, 256); return p; };
     r.rows_qkv = (int32_t*)take((size_t)3 * E * 4);
     r.rows_o = (int32_t*)take((size_t)E * 4);
-    r.WoC = take((size_t)d * E * e);
-    r.Wp = padded ? take((size_t)3 * E * d * e) : nullptr;
-    r.WoP = padded ? take((size_t)E * d * e) : nullptr;
+    r.WoC = take((size_t)d * ld_weights(e, E, d) * e);
+    r.Wp = padded ? take((size_t)3 * E * ld_weights(e, d, 3 * E) * e) : nullptr;
+    r.WoP = padded ? take((size_t)E * ld_weights(e, d, 3 * E) * e) : nullptr;
     r.bytes = off;
     return r;
 }
@@ -997,20 +1001,21 @@ BwdWs bwd_ws(char* w, size_t e, int64_t T, int d, int E, int Eh, int64_t stats, 
     BwdWs r;
     size_t off = 0;
     auto take = [&](size_t n) { char* p = w ? w + off : nullptr; off += round_up(n, 256); return p; };
+    const int64_t ldt = ld_tokens(T, d, E);
     r.rows_qkv = (int32_t*)take((size_t)3 * Eh * 4);
     r.rows_o = (int32_t*)take((size_t)Eh * 4);
     r.dO = take((size_t)T * E * e);
     r.dQKV = take((size_t)T * 3 * E * e);
     r.delta = (float*)take((size_t)stats * 4);
-    r.dQKVt = take((size_t)3 * E * ld_tokens(T) * e);
-    r.Ot = take((size_t)E * ld_tokens(T) * e);
-    r.Xt = take((size_t)d * ld_tokens(T) * e);
-    r.dYt = take((size_t)d * ld_tokens(T) * e);
-    r.Wc = take((size_t)d * 3 * E * e);
+    r.dQKVt = take((size_t)3 * E * ldt * e);
+    r.Ot = take((size_t)E * ldt * e);
+    r.Xt = take((size_t)d * ldt * e);
+    r.dYt = take((size_t)d * ldt * e);
+    r.Wc = take((size_t)d * ld_weights(e, 3 * E, d) * e);
     const size_t sp = e == 2 ? gemm_split_ws_bytes(Eh, d, (int)depth_tokens(T), 4) : 0; // partial sums of the batched weight-gradient launch
     r.split = sp ? take(sp) : nullptr;
-    r.Wp = padded ? take((size_t)3 * E * d * e) : nullptr;
-    r.WoP = padded ? take((size_t)E * d * e) : nullptr;
+    r.Wp = padded ? take((size_t)3 * E * ld_weights(e, d, 3 * E) * e) : nullptr;
+    r.WoP = padded ? take((size_t)E * ld_weights(e, d, 3 * E) * e) : nullptr;
     r.bytes = off;
     return r;
 }
@@ -1083,6 +1088,7 @@ int sdp::attn_fwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     const bool padded = hw != hd;
     const int T = Bt * S, E = ph * hw;
     const FwdWs w = fwd_ws((char*)ws, esize(dtype), d, E, padded);
+    const int64_t ldp = padded ? ld_weights(2, d, 3 * E) : d, ldo = ld_weights(esize(dtype), E, d); // rows of Wp / WoP, of WoC
 
     if (gathered && !padded) {
         rc = head_rows(head_idx_k, ph, H, hd, w.rows_qkv, w.rows_o, s);
@@ -1090,7 +1096,7 @@ int sdp::attn_fwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     }
     if (padded) { // the run heads' rows of W_Q, W_K, W_V and W_O, each head padded to hw rows
         const PadArgs pa{(const uint16_t*)Wqkv, (const uint16_t*)WoT, (uint16_t*)w.Wp, (uint16_t*)w.WoP,
-                         gathered ? head_idx_k : nullptr, nullptr, ph, ph, H, hd, hw, d, 0, nullptr, nullptr};
+                         gathered ? head_idx_k : nullptr, nullptr, ph, ph, H, hd, hw, d, 0, ldp, nullptr, nullptr};
         rc = pad_heads(pa, false, s);
         if (rc != SDP_OK) return rc;
     }
@@ -1099,7 +1105,7 @@ int sdp::attn_fwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     pj.name = "attn_qkv";
     pj.M = T, pj.N = 3 * E, pj.K = d;
     pj.A = X, pj.lda = d;
-    pj.B = padded ? w.Wp : Wqkv, pj.ldb = d;
+    pj.B = padded ? w.Wp : Wqkv, pj.ldb = ldp;
     if (gathered && !padded) pj.b_gather = w.rows_qkv, pj.b_rows = (int64_t)3 * H * hd;
     pj.epilogue = EPI_STORE;
     pj.C = QKV_save, pj.ldc = 3 * E;
@@ -1113,7 +1119,7 @@ int sdp::attn_fwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         a.lse = LSE_save;
         a.S = S, a.ph = ph, a.hd = hw;
         a.scale = 1.f / sqrtf((float)hd), a.scale2 = a.scale * 1.44269504088896340736f;
-        const TransposeJob wt{padded ? w.WoP : WoT, w.WoC, d, E, gathered && !padded ? w.rows_o : nullptr, E, d};
+        const TransposeJob wt{padded ? w.WoP : WoT, w.WoC, ldp, ldo, gathered && !padded ? w.rows_o : nullptr, E, d};
         rc = launch_core(CORE_FWD, a, (int64_t)ph * Bt, &wt, 1, "attn_core_fwd", s);
     } else {
         AttnCoreDesc c;
@@ -1134,7 +1140,7 @@ int sdp::attn_fwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     op.name = "attn_out";
     op.M = T, op.N = d, op.K = E;
     op.A = O_save, op.lda = E;
-    if (dtype == SDP_BF16) op.B = w.WoC, op.ldb = E;
+    if (dtype == SDP_BF16) op.B = w.WoC, op.ldb = ldo;
     else op.B = WoT, op.ldb = d, op.b_km = 1, op.b_gather = wo_rows, op.b_rows = wo_rows ? (int64_t)H * hd : E;
     op.epilogue = EPI_STORE;
     op.C = Y, op.ldc = d;
@@ -1171,13 +1177,14 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     const bool padded = hw != hd;
     const int T = Bt * S, E = hr * hw, Eh = ph * hw; // width the core runs on, width of the held heads (padded columns)
     const BwdWs w = bwd_ws((char*)ws, esize(dtype), T, d, E, Eh, (int64_t)Bt * hr * S, padded);
+    const int64_t ldp = padded ? ld_weights(2, d, 3 * E) : d, ldw = ld_weights(esize(dtype), 3 * E, d); // rows of Wp / WoP, of Wc
     // no list under backward masking: every head is held (ph = H), no row gather and no scatter are needed
     const bool all_heads = !gathered && head_idx_k == nullptr;
 
     if (padded) {
         // with the rows of the held heads in the padded operands, and where each of them goes (padding rows: nowhere)
         const PadArgs pa{(const uint16_t*)Wqkv, (const uint16_t*)WoT, (uint16_t*)w.Wp, (uint16_t*)w.WoP,
-                         gathered ? head_idx_k : nullptr, head_idx_k, hr, ph, H, hd, hw, d, dw_layout == SDP_DW_SCATTER, w.rows_o,
+                         gathered ? head_idx_k : nullptr, head_idx_k, hr, ph, H, hd, hw, d, dw_layout == SDP_DW_SCATTER, ldp, w.rows_o,
                          w.rows_qkv};
         rc = pad_heads(pa, want_dw, s);
         if (rc != SDP_OK) return rc;
@@ -1190,7 +1197,7 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     go.name = "attn_dout";
     go.M = T, go.N = E, go.K = d;
     go.A = dY, go.lda = d;
-    go.B = padded ? w.WoP : WoT, go.ldb = d;
+    go.B = padded ? w.WoP : WoT, go.ldb = ldp;
     if (gathered && !padded) go.b_gather = w.rows_o, go.b_rows = (int64_t)H * hd;
     go.epilogue = EPI_STORE;
     go.C = w.dO, go.ldc = E;
@@ -1206,8 +1213,8 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         a.S = S, a.ph = hr, a.hd = hw;
         a.scale = 1.f / sqrtf((float)hd), a.scale2 = a.scale * 1.44269504088896340736f;
         // Wqkv's rows for dX; token-contiguous copies for the weight gradients
-        const int64_t ldt = ld_tokens(T);
-        const TransposeJob beside_dq[4] = {{padded ? w.Wp : Wqkv, w.Wc, d, 3 * E, gathered && !padded ? w.rows_qkv : nullptr, 3 * E, d},
+        const int64_t ldt = ld_tokens(T, d, E);
+        const TransposeJob beside_dq[4] = {{padded ? w.Wp : Wqkv, w.Wc, ldp, ldw, gathered && !padded ? w.rows_qkv : nullptr, 3 * E, d},
                                            {O_save, w.Ot, E, ldt, nullptr, T, E},
                                            {X, w.Xt, d, ldt, nullptr, T, d},
                                            {dY, w.dYt, d, ldt, nullptr, T, d}};
@@ -1248,7 +1255,7 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     dx.name = "attn_dx";
     dx.M = T, dx.N = d, dx.K = 3 * E;
     dx.A = w.dQKV, dx.lda = 3 * E;
-    if (dtype == SDP_BF16) dx.B = w.Wc, dx.ldb = 3 * E;
+    if (dtype == SDP_BF16) dx.B = w.Wc, dx.ldb = ldw;
     else dx.B = Wqkv, dx.ldb = d, dx.b_km = 1, dx.b_gather = w_rows, dx.b_rows = w_rows ? (int64_t)3 * H * hd : 3 * E;
     dx.epilogue = EPI_STORE;
     dx.C = dX, dx.ldc = d;
@@ -1280,7 +1287,7 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         return rc != SDP_OK ? rc : gemm_f32(dx, s);
     }
 
-    const int64_t ldt = ld_tokens(T);
+    const int64_t ldt = ld_tokens(T, d, E);
     // dK, dV; the other copies were made beside the core
     rc = transpose_rows((const uint16_t*)w.dQKV + E, 3 * E, nullptr, T, 2 * E, (uint16_t*)w.dQKVt + (size_t)E * ldt, ldt, "attn_tr_bwd", s);
     if (rc != SDP_OK) return rc;

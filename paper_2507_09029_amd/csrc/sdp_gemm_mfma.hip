@@ -78,7 +78,7 @@ struct Dev {
     int64_t lda, ldb;
     const int32_t *ag, *bg, *cs;
     uint16_t *C, *C2, *C3;
-    int64_t ldc;
+    int64_t ldc, ldc3; // ldc3: of C3 (SWIGLU_FWD)
     const uint16_t* R; // STORE / DUAL_ACC, single problem: optional residual [M][ldr]
     int64_t ldr;
     const uint16_t *Gin, *Uin;
@@ -907,7 +907,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
                             }
                             strip_put(strip0, 32 * jj, q, pack4(v[0], v[1], v[2], v[3]));
                         }
-                    strip_store(strip0, which == 0 ? g.C : (which == 1 ? g.C2 : g.C3), g.ldc, i, std::integral_constant<int, kKeep>{});
+                    strip_store(strip0, which == 0 ? g.C : (which == 1 ? g.C2 : g.C3), which == 2 ? g.ldc3 : g.ldc, i, std::integral_constant<int, kKeep>{});
                 }
             } else { // EPI_SWIGLU_BWD: three strips per wave (dG, dU, Act)
                 unsigned char* strip1 = strip0 + Geo::STRIP;
@@ -1133,6 +1133,7 @@ int launch_cfg(const GemmDesc& d, double round, hipStream_t s) {
     g.A = (const uint16_t*)d.A, g.A2 = (const uint16_t*)d.A2, g.B = (const uint16_t*)d.B, g.B2 = (const uint16_t*)d.B2;
     g.lda = d.lda, g.ldb = d.ldb, g.ag = d.a_gather, g.bg = d.b_gather, g.cs = d.c_scatter;
     g.C = (uint16_t*)d.C, g.C2 = (uint16_t*)d.C2, g.C3 = (uint16_t*)d.C3, g.ldc = d.ldc;
+    g.ldc3 = d.ldc3 ? d.ldc3 : d.ldc;
     g.R = (const uint16_t*)d.R, g.ldr = d.ldr;
     g.Gin = (const uint16_t*)d.Gin, g.Uin = (const uint16_t*)d.Uin, g.ldg = d.ldg;
     g.Ct = (uint16_t*)d.Ct, g.Ct2 = (uint16_t*)d.Ct2, g.Ct3 = (uint16_t*)d.Ct3, g.ldct = d.ldct;
@@ -1383,7 +1384,7 @@ bool gemm_mfma_supported(const GemmDesc& d) {
     if (d.a_km) return false; // depth-major A goes through the transposing pre-pass or the plain kernel
     // the epilogue addresses a wave's part of the tile (at most 128 rows) with 32-bit byte offsets below 2^31
     constexpr int64_t kMaxLd = (int64_t)1 << 22;
-    if (d.ldc >= kMaxLd || (d.R && d.ldr >= kMaxLd)) return false;
+    if (d.ldc >= kMaxLd || d.ldc3 >= kMaxLd || d.ldc3 % 8 || (d.R && d.ldr >= kMaxLd)) return false;
     if (d.epilogue == EPI_SWIGLU_BWD && (d.ldg >= kMaxLd || (d.Ct && d.ldct >= kMaxLd))) return false;
     if ((d.a_rows > 0 ? d.a_rows : (int64_t)d.M) * d.lda * 2 >= ((int64_t)1 << 32)) return false;
     if (d.a_gather && (d.a_rows <= 0 || d.epilogue == EPI_DUAL_ACC)) return false;

@@ -32,7 +32,7 @@ struct Dev {
     int a_km;
     const int32_t* ag;
     void *C, *C2, *C3;
-    int64_t ldc;
+    int64_t ldc, ldc3;
     const void *Gin, *Uin;
     int64_t ldg;
     void *Cc, *Cc2, *Cc3;
@@ -140,7 +140,7 @@ __global__ __launch_bounds__(NT) void gemm_simple_kernel(Dev g) {
                 const float gv = acc[i][j], uv = acc2[i][j];
                 st<T>((T*)g.C + (int64_t)m * g.ldc + n, gv);
                 st<T>((T*)g.C2 + (int64_t)m * g.ldc + n, uv);
-                st<T>((T*)g.C3 + (int64_t)m * g.ldc + n, swiglu_fwd<false>(gv, uv));
+                st<T>((T*)g.C3 + (int64_t)m * g.ldc3 + n, swiglu_fwd<false>(gv, uv));
             } else {
                 const float gv = ld<T>((const T*)g.Gin + (int64_t)m * g.ldg + n);
                 const float uv = ld<T>((const T*)g.Uin + (int64_t)m * g.ldg + n);
@@ -165,7 +165,7 @@ __global__ __launch_bounds__(NT) void gemm_simple_kernel(Dev g) {
 template <typename T, int EPI>
 int launch(const GemmDesc& d, hipStream_t s) {
     Dev g{d.M, d.N, d.K, d.A, d.A2, d.B, d.B2, d.lda, d.ldb, d.b_gather, d.c_scatter, d.a_km, d.a_gather,
-          d.C, d.C2, d.C3, d.ldc, d.Gin, d.Uin, d.ldg, d.Cc, d.Cc2, d.Cc3, d.ldcc, d.cidx, d.pc, d.R, d.ldr};
+          d.C, d.C2, d.C3, d.ldc, d.ldc3 ? d.ldc3 : d.ldc, d.Gin, d.Uin, d.ldg, d.Cc, d.Cc2, d.Cc3, d.ldcc, d.cidx, d.pc, d.R, d.ldr};
     dim3 grid((d.N + BN - 1) / BN, (d.M + BM - 1) / BM);
     ProfileScope ps(d.name, s);
     gemm_simple_kernel<T, EPI><<<grid, NT, 0, s>>>(g);

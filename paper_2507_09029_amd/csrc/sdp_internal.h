@@ -35,6 +35,15 @@ inline int launch_status() { return hip_status(hipGetLastError()); }
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
+// Leading dimension of `rows` rows of `min` bf16 elements that a contraction reads from the workspace: whole 128-byte lines,
+// so that the 128 bytes that a depth step takes of a row are one line and not two (5000 x 1600 outputs, 2664 deep, rows of
+// 5328 / 5376 bytes: 48.1 / 40.2 us; 5328 x 1600, 5000 deep, rows of 10128 / 10112 bytes: 98.7 / 83.1 us), unless that
+// takes the matrix out of the MFMA contraction's 4 GiB.
+inline int64_t line_ld(int64_t min, int64_t rows) {
+    const int64_t ld = (min + 63) / 64 * 64;
+    return rows * ld * 2 < ((int64_t)1 << 32) ? ld : min;
+}
+
 // memory of a caller's tensor, and whether one of `out` shares any with one of `in`
 struct Extent {
     const void* p;
@@ -60,7 +69,7 @@ inline bool overlap(std::initializer_list<Extent> out, std::initializer_list<Ext
 enum Epilogue {
     EPI_STORE = 0,       // C[rc(m) * ldc + n] = acc      (rc: optional row scatter; rc(m) < 0 drops row m)
     EPI_DUAL_ACC = 1,    // as STORE with acc = A.B + A2.B2
-    EPI_SWIGLU_FWD = 2,  // g = A.B, u = A.B2: G = g, U = u, Act = silu(g) * u, all [M][N] (ld = ldc)
+    EPI_SWIGLU_FWD = 2,  // g = A.B, u = A.B2: G = g, U = u, Act = silu(g) * u, all [M][N] (ld = ldc; Act: ldc3)
     EPI_SWIGLU_BWD = 3   // da = A.B; with g = Gin[m][n], u = Uin[m][n]  (ld = ldg):
                          //   dU = da silu(g), dG = da u silu'(g), act = silu(g) u, all [M][N] (ld = ldc);
                          //   plain bf16 kernel: with cidx != null also the column-compacted copies [M][pc]
@@ -89,6 +98,7 @@ struct GemmDesc {
     void* C2 = nullptr; // SWIGLU_FWD: U.  SWIGLU_BWD: dU
     void* C3 = nullptr; // SWIGLU_FWD / SWIGLU_BWD: Act
     int64_t ldc = 0;
+    int64_t ldc3 = 0;   // SWIGLU_FWD: leading dimension of C3, 0 = ldc
     const int32_t* c_scatter = nullptr;
     // STORE / DUAL_ACC of a single problem: optional residual, C = acc + R[m][n] (added in fp32 before the
     // result is rounded; R is indexed like C without the row scatter; R may be C itself: an element is read

@@ -28,10 +28,12 @@ using namespace sdp;
 
 size_t esize(int dtype) { return dtype == SDP_F32 ? 4 : 2; }
 
-// Leading dimension of the token-contiguous copies X^T, dY^T [d][T]: T plus 64 elements, so that
-// consecutive rows do not sit a power of two apart (rows 2^k bytes apart fall onto the same memory
-// channels, and a depth step touches one 128-byte piece of each of 192-256 rows).
-int64_t ld_tokens(int T) { return (int64_t)T + 64; }
+// Leading dimensions in the workspace.  Rows of n: Act, dG, dU [T][..], W1c, W2c, W3c [d][..] (fp32 reads them as they come).
+int64_t ld_neurons(int dtype, int T, int d, int n) { return dtype == SDP_BF16 ? line_ld(n, T > d ? T : d) : n; }
+// Token-contiguous copies X^T, dY^T [d][T], dG^T, dU^T, Act^T [p][T]: 64 elements more, so that consecutive rows do not sit a
+// power of two apart (rows 2^k bytes apart fall onto the same memory channels, and a depth step touches one 128-byte piece
+// of each of 192-256 rows).
+int64_t ld_tokens(int T, int d, int p) { return line_ld((int64_t)T + 64, d > p ? d : p); }
 
 int check_common(int mode, int dtype, int T, int d, int F, int p) {
     if (mode != SDP_MASK_FORWARD && mode != SDP_MASK_BACKWARD) return SDP_ERR_INVALID_ARG;
@@ -78,17 +80,20 @@ int sdp::column_ranks(const int32_t* cidx, int pc, int N, int32_t* crank, hipStr
 extern "C" size_t sdp_masked_mlp_fwd_workspace_bytes(int mode, int dtype, int T, int d, int F, int p) {
     if (check_common(mode, dtype, T, d, F, mode == SDP_MASK_BACKWARD ? F : p) != SDP_OK) return 0;
     const size_t n = mode == SDP_MASK_FORWARD ? p : F;
-    return round_up((size_t)T * n * esize(dtype), 256) + round_up((size_t)d * n * esize(dtype), 256);
+    const size_t row_b = ld_neurons(dtype, T, d, (int)n) * esize(dtype);
+    return round_up(T * row_b, 256) + round_up(d * row_b, 256);
 }
 
 extern "C" size_t sdp_masked_mlp_bwd_workspace_bytes(int mode, int dtype, int T, int d, int F, int p) {
     if (check_common(mode, dtype, T, d, F, p) != SDP_OK) return 0;
     const size_t n = mode == SDP_MASK_FORWARD ? p : F;
     const size_t e = esize(dtype);
-    size_t bytes = 3 * round_up((size_t)T * n * e, 256) + 2 * round_up((size_t)d * n * e, 256) +
-                   2 * round_up((size_t)d * ld_tokens(T) * e, 256);
+    const int64_t ldt = ld_tokens(T, d, p);
+    const size_t row_b = ld_neurons(dtype, T, d, (int)n) * e;
+    size_t bytes = 3 * round_up(T * row_b, 256) + 2 * round_up(d * row_b, 256) +
+                   2 * round_up((size_t)d * ldt * e, 256);
     if (mode == SDP_MASK_BACKWARD) bytes += 3 * round_up((size_t)T * p * e, 256);
-    bytes += 3 * round_up((size_t)p * ld_tokens(T) * e, 256); // neuron-major copies of dG, dU, Act on the mask
+    bytes += 3 * round_up((size_t)p * ldt * e, 256); // neuron-major copies of dG, dU, Act on the mask
     if (mode == SDP_MASK_BACKWARD) bytes += round_up((size_t)F * sizeof(int32_t), 256); // rank of every neuron in the list
     if (dtype == SDP_BF16) bytes += round_up(gemm_tail_ws_bytes(p, d, T, 3), 256); // depth ranges of the weight gradients' last round
     return bytes;
@@ -120,12 +125,13 @@ int sdp::mlp_fwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
     const size_t e = esize(dtype);
     char* w = (char*)ws;
     void* Act = w;
-    void* W2c = w + round_up((size_t)T * n * e, 256);
+    const int64_t ldn = ld_neurons(dtype, T, d, n);
+    void* W2c = w + round_up((size_t)T * ldn * e, 256);
 
     // The down projection reads W2: bf16 its transpose W2c, made beside gate_up, which does not need it; fp32 W2T itself.
     // An output that takes W2T's place is written too early for that: W2c is then made first (fp32: W2T's rows).
     const size_t out_b = (size_t)T * n * e, w2_b = (size_t)F * d * e;
-    const TransposeJob wt{W2T, W2c, d, n, gather, n, d};
+    const TransposeJob wt{W2T, W2c, d, ldn, gather, n, d};
     const bool w2_first = dtype == SDP_F32 ? overlap({{Y, (size_t)T * d * e}, {G_save, out_b}, {U_save, out_b}}, {{W2T, w2_b}})
                                            : overlap({{G_save, out_b}, {U_save, out_b}}, {{W2T, w2_b}});
     if (w2_first) {
@@ -139,7 +145,7 @@ int sdp::mlp_fwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
     gu.A = X, gu.lda = d;
     gu.B = W1, gu.B2 = W3, gu.ldb = d, gu.b_gather = gather, gu.b_rows = F;
     gu.epilogue = EPI_SWIGLU_FWD;
-    gu.C = G_save, gu.C2 = U_save, gu.C3 = Act, gu.ldc = n;
+    gu.C = G_save, gu.C2 = U_save, gu.ldc = n, gu.C3 = Act, gu.ldc3 = ldn;
     if (dtype == SDP_BF16 && !w2_first) gu.side = &wt, gu.nside = 1, gu.side_name = "mlp_wt_fwd";
     rc = run(dtype, gu, s);
     if (rc != SDP_OK) return rc;
@@ -147,8 +153,8 @@ int sdp::mlp_fwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
     GemmDesc dn;
     dn.name = "mlp_down";
     dn.M = T, dn.N = d, dn.K = n;
-    dn.A = Act, dn.lda = n;
-    if (dtype == SDP_BF16) dn.B = W2c, dn.ldb = n;
+    dn.A = Act, dn.lda = ldn;
+    if (dtype == SDP_BF16) dn.B = W2c, dn.ldb = ldn;
     else if (w2_first) dn.B = W2c, dn.ldb = d, dn.b_km = 1, dn.b_rows = n;
     else dn.B = W2T, dn.ldb = d, dn.b_km = 1, dn.b_gather = gather, dn.b_rows = F;
     dn.epilogue = EPI_STORE;
@@ -184,8 +190,9 @@ int sdp::mlp_bwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
     const int n = mode == SDP_MASK_FORWARD ? p : F;
     const int32_t* gather = mode == SDP_MASK_FORWARD ? idx_k : nullptr;
     const size_t e = esize(dtype);
-    const size_t act_b = round_up((size_t)T * n * e, 256), wt_b = round_up((size_t)d * n * e, 256);
-    const size_t xt_b = round_up((size_t)d * ld_tokens(T) * e, 256), cmp_b = round_up((size_t)T * p * e, 256);
+    const int64_t ldn = ld_neurons(dtype, T, d, n), ldt = ld_tokens(T, d, p);
+    const size_t act_b = round_up((size_t)T * ldn * e, 256), wt_b = round_up((size_t)d * ldn * e, 256);
+    const size_t xt_b = round_up((size_t)d * ldt * e, 256), cmp_b = round_up((size_t)T * p * e, 256);
     char* w = (char*)ws;
     void *dG = w, *dU = w + act_b, *Act = w + 2 * act_b;
     w += 3 * act_b;
@@ -198,7 +205,7 @@ int sdp::mlp_bwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
         dGc = w, dUc = w + cmp_b, Actc = w + 2 * cmp_b;
         w += 3 * cmp_b;
     }
-    const size_t nm_b = round_up((size_t)p * ld_tokens(T) * e, 256);
+    const size_t nm_b = round_up((size_t)p * ldt * e, 256);
     void *dGn = w, *dUn = w + nm_b, *Actn = w + 2 * nm_b; // [p][T(+pad)]: neuron-major
     w += 3 * nm_b;
     int32_t* ranks = (int32_t*)w; // backward masking: [F]
@@ -261,10 +268,10 @@ int sdp::mlp_bwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
 
     // the four operand copies of the backward pass (X^T, dY^T only feed the weight gradients), made beside dact, which needs
     // none of them
-    const TransposeJob tj[4] = {{W1, W1c, d, n, gather, n, d},
-                                {W3, W3c, d, n, gather, n, d},
-                                {X, XT, d, ld_tokens(T), nullptr, T, d},
-                                {dY, dYT, d, ld_tokens(T), nullptr, T, d}};
+    const TransposeJob tj[4] = {{W1, W1c, d, ldn, gather, n, d},
+                                {W3, W3c, d, ldn, gather, n, d},
+                                {X, XT, d, ldt, nullptr, T, d},
+                                {dY, dYT, d, ldt, nullptr, T, d}};
 
     // weight-gradient contraction (set up first: whether it can take the MFMA path decides what the
     // activation-gradient kernel writes)
@@ -274,12 +281,12 @@ int sdp::mlp_bwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
     GemmDesc dw;
     dw.name = "mlp_dw";
     dw.M = p, dw.N = d, dw.K = T;
-    dw.ldb = ld_tokens(T);
+    dw.ldb = ldt;
     dw.epilogue = EPI_STORE;
     dw.ldc = d;
     dw.c_scatter = dw_layout == SDP_DW_SCATTER ? idx_k : nullptr;
     dw.nbatch = 3;
-    dw.lda = ld_tokens(T), dw.a_km = 0;
+    dw.lda = ldt, dw.a_km = 0;
     dw.tail_ws = tail_ws, dw.tail_name = "mlp_dw_reduce";
     for (int i = 0; i < 3; ++i) dw.Ab[i] = nmaj[i], dw.Bb[i] = rhs[i], dw.Cb[i] = outp[i];
 
@@ -290,11 +297,11 @@ int sdp::mlp_bwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
     da.B = W2T, da.ldb = d, da.b_gather = gather, da.b_rows = F;
     da.epilogue = EPI_SWIGLU_BWD;
     da.Gin = G_save, da.Uin = U_save, da.ldg = n;
-    da.C = dG, da.C2 = dU, da.ldc = n;
+    da.C = dG, da.C2 = dU, da.ldc = ldn;
     // bf16, aligned shapes: the epilogue also writes dG, dU and act transposed (neuron-major [p][T],
     // under backward masking only the worker's p columns), which is the layout in which the batched
     // weight-gradient contraction reads both operands depth-contiguous; act is not stored row-major.
-    da.Ct = dGn, da.Ct2 = dUn, da.Ct3 = Actn, da.ldct = ld_tokens(T);
+    da.Ct = dGn, da.Ct2 = dUn, da.Ct3 = Actn, da.ldct = ldt;
     if (mode == SDP_MASK_BACKWARD) da.cidx = idx_k, da.pc = p, da.crank = ranks;
     const bool fused = want_dw && p % 8 == 0 && T % 8 == 0 && gemm_mfma_supported(dw) && gemm_mfma_supported(da);
     if (!fused) {
@@ -321,8 +328,8 @@ int sdp::mlp_bwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
     GemmDesc dx;
     dx.name = "mlp_dx";
     dx.M = T, dx.N = d, dx.K = n;
-    dx.A = dG, dx.A2 = dU, dx.lda = n;
-    dx.B = W1c, dx.B2 = W3c, dx.ldb = n;
+    dx.A = dG, dx.A2 = dU, dx.lda = ldn;
+    dx.B = W1c, dx.B2 = W3c, dx.ldb = ldn;
     dx.epilogue = EPI_DUAL_ACC;
     dx.C = dX, dx.ldc = d;
     dx.R = dx_residual, dx.ldr = d;
@@ -330,10 +337,10 @@ int sdp::mlp_bwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
     if (rc != SDP_OK) return rc;
 
     if (fused || !want_dw) return SDP_OK;
-    // plain path: read the left operands depth-major ([T][p]) as they are
+    // plain path: read the left operands depth-major ([T][ldn], or the compact copies [T][p]) as they are
     const void* lhs[3] = {dGc, dUc, Actc};
     dw.nbatch = 0;
-    dw.lda = p, dw.a_km = 1;
+    dw.lda = mode == SDP_MASK_BACKWARD ? p : ldn, dw.a_km = 1;
     for (int i = 0; i < 3; ++i) {
         dw.A = lhs[i], dw.B = rhs[i], dw.C = outp[i];
         rc = gemm_simple(dw, s);
