@@ -504,10 +504,10 @@ __device__ inline void causal_item(int L, int nitems, int nbh, int nblocks, int 
     head = bh % ph, b = bh / ph;
 }
 
-// The core's launches carry transposes that the contractions after them read (WoT in the forward pass; X, dY, O, Wqkv beside
-// dQ; dQ beside dK/dV) as workgroups from `nitems` on: the core moves little memory, and the blocks of a causal sequence
-// end at different times.  On launches of their own: block of 4 x 2048 tokens, 12 heads of 64 464 us, this way 438; 24 heads
-// of 50, 12 held 690 -> 658.
+// The core's launches carry transposes that the contractions after them read (WoT in the forward pass, Wqkv beside dQ; for
+// plain weight gradients X, dY, O beside dQ and dQ beside dK/dV as well) as workgroups from `nitems` on: the core moves little
+// memory, and the blocks of a causal sequence end at different times.  With X, dY, O and dQ among them, on launches of their own:
+// block of 4 x 2048 tokens, 12 heads of 64 464 us, this way 438; 24 heads of 50, 12 held 690 -> 658.
 constexpr int side_tiles(int lds) { return lds / kTransposeLds < 4 ? lds / kTransposeLds : 4; }
 
 // A launch's workgroups in one order.  One axis of a grid holds fewer than 2^32 threads (2^24 workgroups); with more
@@ -1193,6 +1193,35 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         if (rc != SDP_OK) return rc;
     }
 
+    // bf16: the four weight gradients share one shape (Eh x d, depth T): dWq, dWk, dWv from the three column blocks of dQKV and
+    // X, dWoT from O and dY; one batched launch fills the CUs four times better than four would, and reads all of these as
+    // they are stored, depth-major.  (With token-contiguous copies, made beside the core and, of dK and dV, in a launch of their
+    // own: block of 4 x 2048 tokens, 12 of 24 heads of 64 432 us, this way 398; 12 of 24 heads of 50, backward masking 666, 610.)
+    // Under backward masking the blocks hold all heads and the launch reads the held heads' columns only: the gradient is
+    // computed on the mask.
+    const int64_t part = (int64_t)(dw_layout == SDP_DW_SCATTER ? H * hd : ph * hd) * d; // elements of one weight gradient
+    GemmDesc wg;
+    bool direct = false;
+    if (dtype == SDP_BF16 && want_dw) {
+        wg.name = "attn_dw";
+        wg.M = Eh, wg.N = d, wg.K = T;
+        wg.a_km = wg.b_km = 1;
+        wg.lda = 3 * E, wg.ldb = d;
+        if (!gathered && !all_heads) wg.a_gather = w.rows_o, wg.a_rows = E, wg.a_gather_chunks = 1; // heads of a multiple of 8
+        wg.epilogue = EPI_STORE;
+        wg.ldc = d;
+        // rows of the held heads inside each matrix; padded heads: w.rows_o = the held heads' columns of the operands, w.rows_qkv =
+        // output rows (-1: dropped)
+        wg.c_scatter = padded ? w.rows_qkv : dw_layout == SDP_DW_SCATTER && !all_heads ? w.rows_o : nullptr;
+        if (padded && !gathered) wg.a_gather = w.rows_o, wg.a_rows = E, wg.a_gather_chunks = 1;
+        wg.nbatch = 4;
+        for (int i = 0; i < 3; ++i)
+            wg.Ab[i] = (const uint16_t*)w.dQKV + (int64_t)i * E, wg.Bb[i] = X, wg.Cb[i] = (uint16_t*)dWqkv + (size_t)i * part;
+        wg.Ab[3] = O_save, wg.ldab[3] = E, wg.Bb[3] = dY, wg.Cb[3] = dWoT;
+        wg.split_ws = w.split;
+        direct = gemm_mfma_supported(wg);
+    }
+
     GemmDesc go;
     go.name = "attn_dout";
     go.M = T, go.N = E, go.K = d;
@@ -1212,16 +1241,16 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         a.dqkv = (uint16_t*)w.dQKV;
         a.S = S, a.ph = hr, a.hd = hw;
         a.scale = 1.f / sqrtf((float)hd), a.scale2 = a.scale * 1.44269504088896340736f;
-        // Wqkv's rows for dX; token-contiguous copies for the weight gradients
+        // Wqkv's rows for dX; token-contiguous copies for the plain weight gradients
         const int64_t ldt = ld_tokens(T, d, E);
         const TransposeJob beside_dq[4] = {{padded ? w.Wp : Wqkv, w.Wc, ldp, ldw, gathered && !padded ? w.rows_qkv : nullptr, 3 * E, d},
                                            {O_save, w.Ot, E, ldt, nullptr, T, E},
                                            {X, w.Xt, d, ldt, nullptr, T, d},
                                            {dY, w.dYt, d, ldt, nullptr, T, d}};
         const TransposeJob beside_dkv{w.dQKV, w.dQKVt, 3 * E, ldt, nullptr, T, E}; // dQ
-        rc = launch_core(CORE_DQ, a, (int64_t)hr * Bt, beside_dq, want_dw ? 4 : 1, "attn_core_bwd_dq", s);
+        rc = launch_core(CORE_DQ, a, (int64_t)hr * Bt, beside_dq, want_dw && !direct ? 4 : 1, "attn_core_bwd_dq", s);
         // reads the delta written by the dQ kernel
-        if (rc == SDP_OK) rc = launch_core(CORE_DKV, a, (int64_t)hr * Bt, &beside_dkv, want_dw ? 1 : 0, "attn_core_bwd_dkv", s);
+        if (rc == SDP_OK) rc = launch_core(CORE_DKV, a, (int64_t)hr * Bt, &beside_dkv, want_dw && !direct ? 1 : 0, "attn_core_bwd_dkv", s);
         if (rc != SDP_OK) return rc;
     } else {
         AttnCoreDesc c;
@@ -1232,7 +1261,6 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         if (rc != SDP_OK) return rc;
     }
 
-    const int64_t part = (int64_t)(dw_layout == SDP_DW_SCATTER ? H * hd : ph * hd) * d; // elements of one weight gradient
     const int32_t* w_rows = gathered ? w.rows_qkv : nullptr;
     if (dtype == SDP_F32) {
         // What follows reads Wqkv, X, dY and O_save as they are; where an output takes the place of one of these (dX over dY, a
@@ -1287,47 +1315,34 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         return rc != SDP_OK ? rc : gemm_f32(dx, s);
     }
 
+    if (direct) {
+        // a gradient in the place of X, dY or O: the launch reads copies of those
+        const size_t tok_b = (size_t)T * d * 2, dw_b = (size_t)part * 2;
+        if (overlap({{dWqkv, 3 * dw_b}, {dWoT, dw_b}}, {{X, tok_b}, {dY, tok_b}, {O_save, (size_t)T * E * 2}})) {
+            const struct { const void* in; int C; void* out; } copies[3] = {{X, d, w.Xt}, {dY, d, w.dYt}, {O_save, E, w.Ot}};
+            for (const auto& c : copies) { // d % 8 == 0, E % 8 == 0: rows of bf16 as rows of half as many floats
+                rc = copy_rows_f32((const float*)c.in, nullptr, T, c.C / 2, (float*)c.out, "attn_copy_bwd", s);
+                if (rc != SDP_OK) return rc;
+            }
+            wg.Bb[0] = wg.Bb[1] = wg.Bb[2] = w.Xt, wg.Bb[3] = w.dYt, wg.Ab[3] = w.Ot;
+            if (dx_residual == dY) dx.R = w.dYt;
+        }
+        rc = gemm_mfma_bf16(wg, s);
+        return rc != SDP_OK ? rc : run(dtype, dx, s);
+    }
+    // plain weight gradients from token-contiguous copies: dK, dV; the others were made beside the core
     const int64_t ldt = ld_tokens(T, d, E);
-    // dK, dV; the other copies were made beside the core
     rc = transpose_rows((const uint16_t*)w.dQKV + E, 3 * E, nullptr, T, 2 * E, (uint16_t*)w.dQKVt + (size_t)E * ldt, ldt, "attn_tr_bwd", s);
     if (rc != SDP_OK) return rc;
-
-    // the four weight gradients share one shape (Eh x d, depth T): dWq, dWk, dWv from the three row blocks of
-    // dQKV^T against X^T, dWoT from O^T against dY^T; one batched launch fills the CUs four times better than
-    // the four launches would.  Under backward masking the row blocks hold all heads and the contraction reads
-    // the held heads' rows only (row gather on the left operand): the gradient is computed on the mask.
-    GemmDesc dw;
-    dw.name = "attn_dw";
-    dw.M = Eh, dw.N = d, dw.K = (int)depth_tokens(T); // zeros from T on (transpose_rows_vec_kernel)
-    dw.lda = ldt, dw.ldb = ldt;
-    if (!gathered && !all_heads) dw.a_gather = w.rows_o, dw.a_rows = E;
-    dw.epilogue = EPI_STORE;
-    dw.ldc = d;
-    dw.c_scatter = dw_layout == SDP_DW_SCATTER && !all_heads ? w.rows_o : nullptr; // rows of the held heads inside each matrix
-    if (padded) { // padded rows: w.rows_o = the held heads' rows of the operands, w.rows_qkv = output rows (-1: dropped)
-        if (gathered) dw.a_gather = nullptr;
-        else dw.a_gather = w.rows_o, dw.a_rows = E;
-        dw.c_scatter = w.rows_qkv;
-    }
-    dw.nbatch = 4;
-    for (int i = 0; i < 3; ++i) {
-        dw.Ab[i] = (const uint16_t*)w.dQKVt + (size_t)i * E * ldt;
-        dw.Bb[i] = w.Xt;
-        dw.Cb[i] = (uint16_t*)dWqkv + (size_t)i * part;
-    }
-    dw.Ab[3] = w.Ot, dw.Bb[3] = w.dYt, dw.Cb[3] = dWoT;
-    dw.split_ws = w.split;
-    if (gemm_mfma_supported(dw)) {
-        rc = gemm_mfma_bf16(dw, s);
+    wg.nbatch = 0;
+    wg.a_km = wg.b_km = 0;
+    wg.K = (int)depth_tokens(T); // zeros from T on (transpose_rows_vec_kernel)
+    wg.lda = wg.ldb = ldt;
+    for (int i = 0; i < 4; ++i) {
+        wg.A = i < 3 ? (const uint16_t*)w.dQKVt + (size_t)i * E * ldt : (const uint16_t*)w.Ot;
+        wg.B = i < 3 ? w.Xt : w.dYt, wg.C = wg.Cb[i];
+        rc = gemm_simple(wg, s);
         if (rc != SDP_OK) return rc;
-    } else {
-        dw.nbatch = 0;
-        for (int i = 0; i < 4; ++i) {
-            dw.A = dw.Ab[i], dw.B = dw.Bb[i], dw.C = dw.Cb[i];
-            rc = gemm_simple(dw, s);
-            if (rc != SDP_OK) return rc;
-        }
     }
-
     return run(dtype, dx, s);
 }

@@ -16,7 +16,11 @@
 // ds_write instructions are spent on staging.  LDS holds two stages of A and three of B (three and three for the
 // 128-row tiles, two and two per wave for the 64 x 64 tile).
 //
-// LDS layout of an operand stage, [R rows][64 k] in 16-byte chunks: chunk (r, c) sits at
+// Depth-major operands (the weight gradients: dG, dU, Act, Q, K, V gradients, O, X and dY are [T][..] and the depth is T): a
+// stage holds 64 depth rows of the tile's columns, and a lane's 8 consecutive k of one column come from two transposing
+// LDS reads (ds_read_b64_tr_b16; read_km).  No transposed copies are made of them.
+//
+// LDS layout of a row-major operand stage, [R rows][64 k] in 16-byte chunks: chunk (r, c) sits at
 // r*8 + (c ^ ((r >> 1) & 7)).  A lane's MFMA operand (8 consecutive k of one row) is one chunk, one
 // ds_read_b128, and the lanes served together fall on distinct banks.
 //
@@ -92,6 +96,7 @@ struct Dev {
     // batched launch (weight gradients): problem z uses Ab[z], Bb[z], Cb[z]
     const uint16_t *Ab[kMaxBatch], *Bb[kMaxBatch];
     uint16_t* Cb[kMaxBatch];
+    int64_t ldab[kMaxBatch]; // depth-major A: leading dimension of each problem's
     // OP_DW_SPLIT: the depth is cut into ksplit ranges of ksteps steps; each (range, problem) is a "problem" of
     // the launch and leaves its fp32 partial sums in partial[range][problem][M][N]
     int ksplit, ksteps;
@@ -160,15 +165,74 @@ __host__ __device__ inline int tail_position(int q, int ntiles, int n_head) {
 #define SDP_WAIT_LGKMCNT0() __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14))
 #define SDP_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (7 << 4) | (15 << 8) | (((n) >> 4) << 14))
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI>
+// ---- depth-major operands: LDS stage [64 depth rows][COLS columns], rows without gaps, in granules of 16 columns (32 bytes).
+// A fragment (16 columns x 32 depth) is two transposing reads: within each block of 16 lanes such a read hands lane n the e-th
+// element (e = 0..3) of what lane 4 e + n / 4 addressed, at position n % 4 of its 8 bytes.  Lane (l16, lq) therefore addresses
+// row 8 lq + l16 / 4 (+ 4), columns 4 (l16 % 4) .. of the fragment's granule and gets column l16, depths 8 lq .. 8 lq + 7.
+// The 32 lanes served together touch rows {0 .. 3, 8 .. 11} (+ 4, + 16) of one granule column, 32 bytes each: granule g of
+// row r sits at g ^ swizzle(r), which puts these 8 pieces on distinct groups of 8 banks.
+template <int COLS>
+__device__ inline int km_swizzle(int row) {
+    static_assert(COLS % 64 == 0, "whole blocks of 4 granules");
+    // rows a multiple of 256 bytes apart start on the same bank, odd multiples of 128 bytes alternate between two halves
+    return COLS % 128 == 0 ? (row & 3) | ((row >> 3) & 1) << 2 : ((row >> 1) & 1) | ((row >> 3) & 1) << 1;
+}
+// the row and column of the 16-byte chunk that a direct load puts at chunk position q of the stage
+template <int COLS>
+__device__ inline void km_chunk(int q, int& row, int& col) {
+    row = q / (COLS / 8);
+    const int c = q % (COLS / 8);
+    col = (((c >> 1) ^ km_swizzle<COLS>(row)) * 2 + (c & 1)) * 8;
+}
+// byte offset of this lane's first read of the fragment in granule g (depths 0 .. 31)
+template <int COLS>
+__device__ inline int km_offset(int g, int l16, int lq) {
+    const int row = 8 * lq + (l16 >> 2);
+    return row * COLS * 2 + (g ^ km_swizzle<COLS>(row)) * 32 + (l16 & 3) * 8;
+}
+template <int COLS>
+__device__ inline bf16x8 read_km(const unsigned char* stage, int offset, int s) {
+    const unsigned char* p = stage + offset + s * 32 * COLS * 2;
+    const u32x2 a = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)p));
+    const u32x2 b = __builtin_bit_cast(u32x2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + 4 * COLS * 2)));
+    return __builtin_bit_cast(bf16x8, u32x4{a[0], a[1], b[0], b[1]});
+}
+
+// One direct load: 64 lanes x 16 bytes from base + off (per lane; the zero chunk where `zero`) to 1 KB of LDS at dst.
+// kAsm: written out, for the kernels with transposing reads.  The compiler does not tell the stages apart and puts a wait for all
+// direct loads in flight in front of every group of such reads (not in front of ordinary ones): 128 x 128 tiles 2 x slower, 128 x 256
+// 2.2 x.  The instruction has no output register, reads its address and M0 as it is issued, and is waited for by the loop's own
+// counts (SDP_WAIT_VMCNT), which are the same for both forms; the memory clobber keeps LDS accesses on their side of it.
+template <bool kAsm, bool kTail>
+__device__ __attribute__((always_inline)) inline void direct_load(const unsigned char* base, uint32_t off, bool zero, unsigned char* dst) {
+    const unsigned char* src = kTail && zero ? (const unsigned char*)kZeroChunk : base + off;
+    if constexpr (!kAsm) {
+        __builtin_amdgcn_global_load_lds((glb_void_ptr)src, (lds_void_ptr)dst, 16, 0, 0);
+    } else {
+        const uint32_t m0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(uintptr_t)(lds_void_ptr)dst);
+        if constexpr (kTail) {
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(m0), "v"(src) : "memory", "m0");
+        } else {
+            const uint64_t a = (uint64_t)base; // the same in all lanes
+            const uint64_t u = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(a >> 32)) << 32) |
+                               (uint32_t)__builtin_amdgcn_readfirstlane((int)a);
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(m0), "v"(off), "s"(u) : "memory", "m0");
+        }
+    }
+}
+
+template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int KM>
 struct Geometry {
     static constexpr int NW = WAVES_M * WAVES_N;
     static constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
     static constexpr int FM = WM / 32, FN = WN / 32;
     static constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
     static constexpr bool kWaveDepth = BM == 64; // each wave runs its own depth steps on the whole tile (see the loop)
-    static constexpr bool kPipe = BM == 128; // fragments read a half step ahead, one barrier a step (see the loop)
-    static constexpr int A_STAGES = kPipe ? 3 : 2; // LDS stages of A; B has three
+    // fragments read a half step ahead, one barrier a step (see the loop).  With both operands depth-major also the 256 x 192
+    // tile, whose reads are twice as many there: 2048 x 1536 outputs x 3, 8192 deep 170 -> 162 us; 256 x 256 no faster (135 us
+    // both ways at 2664 x 1600 x 3, 5000 deep) and short of registers
+    static constexpr bool kPipe = BM == 128 || (KM == 3 && BN == 192);
+    static constexpr int A_STAGES = BM == 128 ? 3 : 2; // LDS stages of A; B has three
     // kWaveDepth: two stages of both operands per wave
     static constexpr int RING = kWaveDepth ? 2 * NW * (A_BYTES + B_BYTES) : A_STAGES * A_BYTES + 3 * B_BYTES;
     // epilogue strip: 32 rows x SW columns of bf16, rows padded by 8 bytes
@@ -192,13 +256,16 @@ constexpr int side_tiles(int threads, int lds) {
     return lds / (threads / 256 * kTransposeLds) < 8 ? lds / (threads / 256 * kTransposeLds) : 8;
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int OP>
+// KM: bit 0 = A is depth-major ([K][lda]), bit 1 = B is
+template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int OP, int KM>
 __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1) void sdp_gemm_kernel(Dev g, SideArg<OP> side) {
-    using Geo = Geometry<BM, BN, WAVES_M, WAVES_N, EPI>;
+    using Geo = Geometry<BM, BN, WAVES_M, WAVES_N, EPI, KM>;
     constexpr int NW = Geo::NW, WM = Geo::WM, WN = Geo::WN, FM = Geo::FM, FN = Geo::FN;
     constexpr int A_BYTES = Geo::A_BYTES, B_BYTES = Geo::B_BYTES;
     constexpr bool kFwd = EPI == EPI_SWIGLU_FWD;
     constexpr bool kWaveDepth = Geo::kWaveDepth;
+    constexpr bool kAkm = (KM & 1) != 0, kBkm = (KM & 2) != 0;
+    static_assert(KM == 0 || EPI == EPI_STORE, "depth-major operands: plain store epilogue only");
     constexpr int SA = (BM / 8) / NW;  // A slabs (1 KB) per wave per step
     constexpr int SB = (BN / 8) / NW;  // B slabs per wave per step
     static_assert((BM / 8) % NW == 0 && (BN / 8) % NW == 0, "slabs must divide among the waves");
@@ -255,6 +322,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
     const uint16_t* gA = g.A;
     const uint16_t* gB = g.B;
     uint16_t* gC = g.C;
+    int64_t lda = g.lda;
     int kpart = 0; // depth range of this workgroup (OP_DW_SPLIT, and the cut tiles of OP_DW_TAIL)
     if (kSplit) kpart = batch / g.nbatch, batch -= kpart * g.nbatch;
     if (kTail) kpart = tail_part;
@@ -263,6 +331,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
         static_assert(kMaxBatch == 4, "one comparison per problem");
         gA = batch == 0 ? g.Ab[0] : (batch == 1 ? g.Ab[1] : (batch == 2 ? g.Ab[2] : g.Ab[3]));
         gB = batch == 0 ? g.Bb[0] : (batch == 1 ? g.Bb[1] : (batch == 2 ? g.Bb[2] : g.Bb[3]));
+        if (kAkm) lda = batch == 0 ? g.ldab[0] : (batch == 1 ? g.ldab[1] : (batch == 2 ? g.ldab[2] : g.ldab[3]));
         gC = batch == 0 ? g.Cb[0] : (batch == 1 ? g.Cb[1] : (batch == 2 ? g.Cb[2] : g.Cb[3]));
     }
     const int m0 = tile_m * BM;
@@ -302,10 +371,54 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
     auto read_tile_frags = [&](const unsigned char* sa, const unsigned char* sb, int s, bf16x8* fa, bf16x8* fb) {
         const int off = (((4 * s + lq) ^ ((l16 >> 1) & 7)) * 16) + l16 * 128;
 #pragma unroll
-        for (int i = 0; i < BM / 16; ++i) fa[i] = __builtin_bit_cast(bf16x8, *(const u32x4*)(sa + i * 2048 + off));
+        for (int i = 0; i < BM / 16; ++i) {
+            if constexpr (kAkm) fa[i] = read_km<BM>(sa, km_offset<BM>(i, l16, lq), s);
+            else fa[i] = __builtin_bit_cast(bf16x8, *(const u32x4*)(sa + i * 2048 + off));
+        }
 #pragma unroll
-        for (int j = 0; j < BN / 16; ++j) fb[j] = __builtin_bit_cast(bf16x8, *(const u32x4*)(sb + j * 2048 + off));
+        for (int j = 0; j < BN / 16; ++j) {
+            if constexpr (kBkm) fb[j] = read_km<BN>(sb, km_offset<BN>(j, l16, lq), s);
+            else fb[j] = __builtin_bit_cast(bf16x8, *(const u32x4*)(sb + j * 2048 + off));
+        }
     };
+    // Offsets of a direct load's source within a depth step, and the step's depth rows / chunks it takes.  Indices beyond the
+    // matrix are clamped to the last valid ones: such lanes fetch valid memory whose products only reach outputs that are
+    // never stored.  Row-major: slab s of 1 KB holds tile rows 8 s .. 8 s + 7, lane -> row 8 s + lane / 8, stored chunk
+    // position lane % 8.  Depth-major: chunk positions 64 s .. (km_chunk).
+    auto source_a = [&](int slab, int& k) __attribute__((always_inline)) -> uint32_t {
+        if constexpr (kAkm) {
+            int row, col;
+            km_chunk<BM>(64 * slab + lane, row, col);
+            const int m = m0 + col < g.M ? m0 + col : g.M - 8; // M % 8 == 0, and a gather list moves whole chunks
+            k = row;
+            return (uint32_t)((row * lda + (g.ag ? g.ag[m] : m)) * 2);
+        } else {
+            const int r = 8 * slab + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
+            const int m = m0 + r < g.M ? m0 + r : g.M - 1;
+            const int64_t row = g.ag ? g.ag[m] : m;
+            k = c * 8;
+            return (uint32_t)((row * lda + k) * 2);
+        }
+    };
+    auto source_b = [&](int slab, int& k) __attribute__((always_inline)) -> uint32_t {
+        if constexpr (kBkm) {
+            int row, col;
+            km_chunk<BN>(64 * slab + lane, row, col);
+            const int n = n0 + col < g.N ? n0 + col : g.N - 8;
+            k = row;
+            return (uint32_t)((row * g.ldb + n) * 2);
+        } else {
+            const int r = 8 * slab + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
+            int n = kFwd ? n0 + (r % (BN / 2)) : n0 + r;
+            n = n < g.N ? n : g.N - 1;
+            const int64_t row = g.bg ? g.bg[n] : n;
+            k = c * 8;
+            return (uint32_t)((row * g.ldb + k) * 2);
+        }
+    };
+    // what depth step k0 / 64 adds to an operand's base
+    auto step_a = [&](int k0) __attribute__((always_inline)) { return kAkm ? (int64_t)k0 * lda * 2 : (int64_t)k0 * 2; };
+    auto step_b = [&](int k0) __attribute__((always_inline)) { return kBkm ? (int64_t)k0 * g.ldb * 2 : (int64_t)k0 * 2; };
     if constexpr (kWaveDepth) {
         // ---- main loop of the 64-row tiles: wave w runs the depth steps w, w + NW, ... on the whole tile, in two LDS stages
         // of its own (no barrier); the partial tiles are then added through LDS, in wave order, every wave taking the part
@@ -314,21 +427,11 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
         static_assert(!kFwd, "no gate / up pairing inside a 64-column tile");
         constexpr int TM = BM / 16, TN = BN / 16; // fragments of the tile
         uint32_t a_off[BM / 8], b_off[BN / 8];
-        const int ck = ((lane & 7) ^ ((lane >> 4) & 7)) & 7; // slab s: lane -> row 8 s + lane / 8; (row >> 1) & 7 = 4 (s & 1) + lane / 16
+        int a_k[BM / 8], b_k[BN / 8];
 #pragma unroll
-        for (int i = 0; i < BM / 8; ++i) {
-            int m = m0 + 8 * i + (lane >> 3);
-            m = m < g.M ? m : g.M - 1;
-            const int64_t arow = g.ag ? g.ag[m] : m;
-            a_off[i] = (uint32_t)((arow * g.lda + (ck ^ (4 * (i & 1))) * 8) * 2);
-        }
+        for (int i = 0; i < BM / 8; ++i) a_off[i] = source_a(i, a_k[i]);
 #pragma unroll
-        for (int j = 0; j < BN / 8; ++j) {
-            int n = n0 + 8 * j + (lane >> 3);
-            n = n < g.N ? n : g.N - 1;
-            const int64_t row = g.bg ? g.bg[n] : n;
-            b_off[j] = (uint32_t)((row * g.ldb + (ck ^ (4 * (j & 1))) * 8) * 2);
-        }
+        for (int j = 0; j < BN / 8; ++j) b_off[j] = source_b(j, b_k[j]);
         f32x4 part[TM][TN];
 #pragma unroll
         for (int i = 0; i < TM; ++i)
@@ -339,19 +442,16 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
             constexpr bool TAIL = decltype(tail_c)::value;
             const bool second = EPI == EPI_DUAL_ACC && kt >= nk1;
             const int k0 = (kt0 + (second ? kt - nk1 : kt)) * BK;
-            const unsigned char* abase = (const unsigned char*)(second ? g.A2 : gA) + (int64_t)k0 * 2;
-            const unsigned char* bbase = (const unsigned char*)(second ? g.B2 : gB) + (int64_t)k0 * 2;
+            const unsigned char* abase = (const unsigned char*)(second ? g.A2 : gA) + step_a(k0);
+            const unsigned char* bbase = (const unsigned char*)(second ? g.B2 : gB) + step_b(k0);
             unsigned char* st = mine + stage * (A_BYTES + B_BYTES);
-            const bool out0 = TAIL && k0 + ck * 8 >= g.K, out1 = TAIL && k0 + (ck ^ 4) * 8 >= g.K; // even and odd slabs
 #pragma unroll
             for (int i = 0; i < BM / 8; ++i) {
-                const unsigned char* src = ((i & 1) ? out1 : out0) ? (const unsigned char*)kZeroChunk : abase + a_off[i];
-                __builtin_amdgcn_global_load_lds((glb_void_ptr)src, (lds_void_ptr)(st + i * 1024), 16, 0, 0);
+                direct_load<KM != 0, TAIL>(abase, a_off[i], k0 + a_k[i] >= g.K, st + i * 1024);
             }
 #pragma unroll
             for (int j = 0; j < BN / 8; ++j) {
-                const unsigned char* src = ((j & 1) ? out1 : out0) ? (const unsigned char*)kZeroChunk : bbase + b_off[j];
-                __builtin_amdgcn_global_load_lds((glb_void_ptr)src, (lds_void_ptr)(st + A_BYTES + j * 1024), 16, 0, 0);
+                direct_load<KM != 0, TAIL>(bbase, b_off[j], k0 + b_k[j] >= g.K, st + A_BYTES + j * 1024);
             }
         };
         auto run = [&](auto tail_c) {
@@ -403,32 +503,13 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
                     acc[i][j][q] = v;
                 }
     } else {
-    // ---- per-lane global source of every slab this wave fills: byte offsets from a uniform base.
-    // Row indices beyond the matrix are clamped to the last valid one: such lanes fetch valid
-    // memory whose products only reach outputs that are never stored.
-    // Slab s holds tile rows 8s .. 8s+7; lane -> row 8s + lane/8, stored chunk position lane%8.
+    // ---- per-lane global source of every slab this wave fills: byte offsets from a uniform base
     uint32_t a_off[SA], b_off[SB];
     int a_k[SA], b_k[SB]; // depth offset of this lane's chunk inside a step
 #pragma unroll
-    for (int i = 0; i < SA; ++i) {
-        const int r = 8 * (wave + NW * i) + (lane >> 3);
-        const int c = (lane & 7) ^ ((r >> 1) & 7);
-        int m = m0 + r;
-        m = m < g.M ? m : g.M - 1;
-        const int64_t arow = g.ag ? g.ag[m] : m;
-        a_off[i] = (uint32_t)((arow * g.lda + c * 8) * 2);
-        a_k[i] = c * 8;
-    }
+    for (int i = 0; i < SA; ++i) a_off[i] = source_a(wave + NW * i, a_k[i]);
 #pragma unroll
-    for (int i = 0; i < SB; ++i) {
-        const int r = 8 * (wave + NW * i) + (lane >> 3);
-        const int c = (lane & 7) ^ ((r >> 1) & 7);
-        int n = kFwd ? n0 + (r % (BN / 2)) : n0 + r;
-        n = n < g.N ? n : g.N - 1;
-        const int64_t row = g.bg ? g.bg[n] : n;
-        b_off[i] = (uint32_t)((row * g.ldb + c * 8) * 2);
-        b_k[i] = c * 8;
-    }
+    for (int i = 0; i < SB; ++i) b_off[i] = source_b(wave + NW * i, b_k[i]);
 
     // LDS: the A stages, then a ring of three B stages
     unsigned char* const lds_a = smem;
@@ -443,13 +524,11 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
         const int k0 = (kt0 + (second ? kt - nk1 : kt)) * BK;
         const int krem = g.K - k0;
         unsigned char* sa = lds_a + slot * A_BYTES;
-        const unsigned char* abase = (const unsigned char*)(second ? g.A2 : gA) + (int64_t)k0 * 2;
+        const unsigned char* abase = (const unsigned char*)(second ? g.A2 : gA) + step_a(k0);
 #pragma unroll
         for (int i = 0; i < SA; ++i) {
             if (i < first || i >= last) continue;
-            const unsigned char* src = abase + a_off[i];
-            if (TAIL && a_k[i] >= krem) src = (const unsigned char*)kZeroChunk;
-            __builtin_amdgcn_global_load_lds((glb_void_ptr)src, (lds_void_ptr)(sa + (wave + NW * i) * 1024), 16, 0, 0);
+            direct_load<KM != 0, TAIL>(abase, a_off[i], a_k[i] >= krem, sa + (wave + NW * i) * 1024);
         }
     };
     auto issue_b = [&](int kt, int slot, auto tail_c, int first, int last) __attribute__((always_inline)) {
@@ -458,16 +537,14 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
         const int k0 = (kt0 + (second ? kt - nk1 : kt)) * BK;
         const int krem = g.K - k0;
         unsigned char* sb = lds_b + slot * B_BYTES;
-        const unsigned char* bbase0 = (const unsigned char*)(second ? g.B2 : gB) + (int64_t)k0 * 2;
-        const unsigned char* bbase1 = (const unsigned char*)g.B2 + (int64_t)k0 * 2;
+        const unsigned char* bbase0 = (const unsigned char*)(second ? g.B2 : gB) + step_b(k0);
+        const unsigned char* bbase1 = (const unsigned char*)g.B2 + step_b(k0);
 #pragma unroll
         for (int i = 0; i < SB; ++i) {
             if (i < first || i >= last) continue;
             // SWIGLU_FWD: tile rows BN/2.. hold the up-projection rows (second matrix)
             const bool up = kFwd && 8 * (wave + NW * i) >= BN / 2;
-            const unsigned char* src = (up ? bbase1 : bbase0) + b_off[i];
-            if (TAIL && b_k[i] >= krem) src = (const unsigned char*)kZeroChunk;
-            __builtin_amdgcn_global_load_lds((glb_void_ptr)src, (lds_void_ptr)(sb + (wave + NW * i) * 1024), 16, 0, 0);
+            direct_load<KM != 0, TAIL>(up ? bbase1 : bbase0, b_off[i], b_k[i] >= krem, sb + (wave + NW * i) * 1024);
         }
     };
 
@@ -493,11 +570,22 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
     const int a_base = WM * wm * 128;
 
     // fragment reads of sub-step s: A fragment i = rows 16 i .. of the wave's A rows, B fragment j = rows 16 j .. likewise
+    int a_km[kAkm ? 2 * FM : 1], b_km[kBkm ? 2 * FN : 1]; // depth-major: this lane's offset of every fragment
+    if constexpr (kAkm) {
+#pragma unroll
+        for (int i = 0; i < 2 * FM; ++i) a_km[i] = km_offset<BM>(WM * wm / 16 + i, l16, lq);
+    }
+    if constexpr (kBkm) {
+#pragma unroll
+        for (int j = 0; j < 2 * FN; ++j) b_km[j] = km_offset<BN>(bfrag[j >> 1] / 16 + (j & 1), l16, lq);
+    }
     auto read_a = [&](const unsigned char* sa, int s, int i) __attribute__((always_inline)) {
-        return __builtin_bit_cast(bf16x8, *(const u32x4*)(sa + a_base + i * 16 * 128 + row_off[s]));
+        if constexpr (kAkm) return read_km<BM>(sa, a_km[i], s);
+        else return __builtin_bit_cast(bf16x8, *(const u32x4*)(sa + a_base + i * 16 * 128 + row_off[s]));
     };
     auto read_b = [&](const unsigned char* sb, int s, int j) __attribute__((always_inline)) {
-        return __builtin_bit_cast(bf16x8, *(const u32x4*)(sb + (bfrag[j >> 1] + 16 * (j & 1)) * 128 + row_off[s]));
+        if constexpr (kBkm) return read_km<BN>(sb, b_km[j], s);
+        else return __builtin_bit_cast(bf16x8, *(const u32x4*)(sb + (bfrag[j >> 1] + 16 * (j & 1)) * 128 + row_off[s]));
     };
     // B fragment first: the accumulator tile is then indexed [n][m] in the MFMA's own layout, i.e. lane (l16, lq)
     // holds, for output row m = l16 of the tile, its columns n = 4 lq + r in element r.
@@ -515,34 +603,33 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
     using std::true_type;
 
     if constexpr (Geo::kPipe) {
-        // ---- main loop of the 128-row tiles.  A depth step is two 32-deep halves; while a wave's MFMAs of one half run, its
+        // ---- main loop of the 128-row tiles (and see kPipe).  A depth step is two 32-deep halves; while a wave's MFMAs of one half run, its
         // fragments of the next half are read and its share of later steps' loads is issued between them, at most one of
         // either per MFMA.  One barrier a step, between the halves:
         //   first half of step k: MFMAs on (k, 0); reads of (k, 1); loads of B for step k + 2
         //   wait for the own loads of step k + 1 and the own reads of step k; barrier: step k + 1 has landed, step k is read
-        //   second half: MFMAs on (k, 1); reads of (k + 1, 0); loads of A for step k + 3
+        //   second half: MFMAs on (k, 1); reads of (k + 1, 0); loads of A for step k + 3 (256 rows: two stages of A, k + 2)
         // A and B have three stages each; the stage of step k is filled again from that barrier on.  The phases of the
         // 256-row tiles (four barriers a step) cost such a tile more than its 8 to 16 MFMAs a phase: 4096 x 1200 outputs,
         // 3200 deep, chip at full clock, 128 x 192 tiles 39.7 -> 32.3 us, 128 x 128 57.7 -> 43.6, 128 x 256 38.4 -> 35.5
         // (256 x 192 tiles 43.0 -> 46.5: those keep the phases).  The loads issued all at once after the barrier, in front of the
         // MFMAs: 43.9 instead of 40.6 (at a lower clock).  Four or five stages: no faster.  A step's halves shared out between
         // two groups of waves, whose tiles are then twice as high (three eighths fewer LDS reads): 33.
-        constexpr int S = 3, L = SA + SB;
-        static_assert(Geo::A_STAGES == S, "both operands have three stages");
+        constexpr int NA = Geo::A_STAGES, S = 3, L = SA + SB; // stages of A and of B
         constexpr int NM = 4 * FM * FN, NR = 2 * FM + 2 * FN; // MFMAs and fragment reads of a half step
         static_assert(NR <= NM, "one read per MFMA");
         bf16x8 fa[2][2 * FM], fb[2][2 * FN];
-        auto read_one = [&](int slot, int h, int r) __attribute__((always_inline)) {
-            if (r < 2 * FN) fb[h][r] = read_b(lds_b + slot * B_BYTES, h, r);
-            else fa[h][r - 2 * FN] = read_a(lds_a + slot * A_BYTES, h, r - 2 * FN);
+        auto read_one = [&](int sa, int sb, int h, int r) __attribute__((always_inline)) {
+            if (r < 2 * FN) fb[h][r] = read_b(lds_b + sb * B_BYTES, h, r);
+            else fa[h][r - 2 * FN] = read_a(lds_a + sa * A_BYTES, h, r - 2 * FN);
         };
-        // the MFMAs of half h; between them the reads of the other half from stage `slot` and `nload` loads
-        auto half_step = [&](int h, bool reads, int slot, int nload, auto load) __attribute__((always_inline)) {
+        // the MFMAs of half h; between them the reads of the other half from stages sa, sb and `nload` loads
+        auto half_step = [&](int h, bool reads, int sa, int sb, int nload, auto load) __attribute__((always_inline)) {
 #pragma unroll
             for (int m = 0; m < NM; ++m) {
                 const bool rd = reads && m < NR;
                 bool ld = false;
-                if (rd) read_one(slot, h ^ 1, m);
+                if (rd) read_one(sa, sb, h ^ 1, m);
 #pragma unroll
                 for (int l = 0; l < nload; ++l)
                     if ((2 * l + 1) * NM / (2 * nload) == m) load(l), ld = true;
@@ -551,32 +638,33 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
                 if (rd || ld) __builtin_amdgcn_sched_barrier(0);
             }
         };
-        int kt = 0, slot = 0, prev = S - 1; // stages of steps kt and kt - 1
+        int kt = 0, slot = 0, prev = S - 1, slot_a = 0; // B's stages of steps kt and kt - 1, A's of step kt
         // R: steps left after this one, at most S; TA / TB: the step of the loads of A / B may end beyond the depth
         auto step = [&](auto r_c, auto ta_c, auto tb_c) __attribute__((always_inline)) {
             constexpr int R = decltype(r_c)::value;
-            half_step(0, true, slot, R >= S - 1 ? SB : 0, [&](int l) __attribute__((always_inline)) { issue_b(kt + S - 1, prev, tb_c, l, l + 1); });
+            half_step(0, true, slot_a, slot, R >= S - 1 ? SB : 0, [&](int l) __attribute__((always_inline)) { issue_b(kt + S - 1, prev, tb_c, l, l + 1); });
             if constexpr (R > 0) {
-                constexpr int in_flight = (R >= S ? S - 2 : R - 1) * L; // the loads younger than step kt + 1's
+                // the loads younger than step kt + 1's
+                constexpr int in_flight = NA == S ? (R >= S ? S - 2 : R - 1) * L : R > 1 ? SB : 0;
                 __builtin_amdgcn_sched_barrier(0);
                 SDP_WAIT_VMCNT(in_flight);
                 SDP_WAIT_LGKMCNT0();
                 barrier();
             }
-            const int next = slot == S - 1 ? 0 : slot + 1;
-            half_step(1, R > 0, next, R >= S ? SA : 0, [&](int l) __attribute__((always_inline)) { issue_a(kt + S, slot, ta_c, l, l + 1); });
+            const int next = slot == S - 1 ? 0 : slot + 1, next_a = slot_a == NA - 1 ? 0 : slot_a + 1;
+            half_step(1, R > 0, next_a, next, R >= NA ? SA : 0, [&](int l) __attribute__((always_inline)) { issue_a(kt + NA, slot_a, ta_c, l, l + 1); });
             __builtin_amdgcn_sched_barrier(0);
-            prev = slot, slot = next, ++kt;
+            prev = slot, slot = next, slot_a = next_a, ++kt;
         };
 #pragma unroll
-        for (int j = 0; j < S; ++j) { // B of step S - 1 follows in step 0
-            if (j < nk) issue_a(j, j, true_type{}, 0, SA);
-            if (j < nk && j < S - 1) issue_b(j, j, true_type{}, 0, SB);
+        for (int j = -S; j < 0; ++j) { // what the steps before the first would have issued; B of step S - 1 follows in step 0
+            if (j + NA >= 0 && j + NA < nk) issue_a(j + NA, j + NA, true_type{}, 0, SA);
+            if (j + S < nk && j < -1) issue_b(j + S, j + S, true_type{}, 0, SB);
         }
-        if (nk >= S) SDP_WAIT_VMCNT((S - 2) * L + SA); else SDP_WAIT_VMCNT(0);
+        if (nk >= S) SDP_WAIT_VMCNT(SA + SB + (NA == S ? SA : 0)); else SDP_WAIT_VMCNT(0);
         barrier();
 #pragma unroll
-        for (int r = 0; r < NR; ++r) read_one(0, 0, r);
+        for (int r = 0; r < NR; ++r) read_one(0, 0, 0, r);
         constexpr integral_constant<int, S> full{};
         if constexpr (EPI == EPI_DUAL_ACC) { // the first pair of operands ends with step nk1 - 1
             while (kt + S < nk1 - 1) step(full, false_type{}, false_type{});
@@ -584,7 +672,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
             if (kt + S == nk1) step(full, false_type{}, true_type{});
         }
         while (kt + S < nk - 1) step(full, false_type{}, false_type{});
-        if (kt + S == nk - 1) step(full, true_type{}, false_type{});
+        if (kt + S == nk - 1) step(full, integral_constant<bool, NA == S>{}, false_type{});
         if (kt == nk - 3) step(integral_constant<int, 2>{}, true_type{}, true_type{});
         if (kt == nk - 2) step(integral_constant<int, 1>{}, true_type{}, true_type{});
         step(integral_constant<int, 0>{}, true_type{}, true_type{});
@@ -1123,9 +1211,9 @@ bool carry(int64_t tiles, double round, int64_t wgs) {
     return idle > 0 && (double)((wgs + idle - 1) / idle) * 5.0 + 5.0 <= 1.2 * round;
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int OP>
+template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int OP, int KM>
 int launch_cfg(const GemmDesc& d, double round, hipStream_t s) {
-    using Geo = Geometry<BM, BN, WAVES_M, WAVES_N, EPI>;
+    using Geo = Geometry<BM, BN, WAVES_M, WAVES_N, EPI, KM>;
     constexpr int NTHREADS = WAVES_M * WAVES_N * 64;
     constexpr int LDS = Geo::LDS;
     Dev g;
@@ -1161,6 +1249,7 @@ int launch_cfg(const GemmDesc& d, double round, hipStream_t s) {
     int na = 1, nbo = 1; // distinct A / B operands among the problems of a batch
     for (int z = 0; z < kMaxBatch; ++z) {
         g.Ab[z] = (const uint16_t*)d.Ab[z], g.Bb[z] = (const uint16_t*)d.Bb[z], g.Cb[z] = (uint16_t*)d.Cb[z];
+        g.ldab[z] = d.ldab[z] ? d.ldab[z] : d.lda;
     }
     if (kBatched) {
         na = nbo = 0;
@@ -1202,7 +1291,7 @@ int launch_cfg(const GemmDesc& d, double round, hipStream_t s) {
             }
         }
     }
-    auto kern = sdp_gemm_kernel<BM, BN, WAVES_M, WAVES_N, EPI, OP>;
+    auto kern = sdp_gemm_kernel<BM, BN, WAVES_M, WAVES_N, EPI, OP, KM>;
     // once per instantiation (initialisation of a function-local static is thread-safe)
     static const hipError_t attr =
         hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
@@ -1269,18 +1358,18 @@ Shape choose_shape(const GemmDesc& d, int nbatch, int ksplit, double* round = nu
     return best;
 }
 
-template <int EPI, int OP>
+template <int EPI, int OP, int KM = 0>
 int launch(const GemmDesc& d, hipStream_t s) {
     const int nbatch = OP == OP_DW || OP == OP_DW_TAIL || OP == OP_DW_SPLIT ? d.nbatch : 1;
     double round = 0;
     const Shape shape = choose_shape<EPI>(d, nbatch, OP == OP_DW_SPLIT ? d.ksplit : 1, &round);
-    if (shape == T256x256) return launch_cfg<256, 256, 2, 4, EPI, OP>(d, round, s);
-    if (shape == T128x256) return launch_cfg<128, 256, 2, 4, EPI, OP>(d, round, s);
-    if (shape == T128x128) return launch_cfg<128, 128, 4, 2, EPI, OP>(d, round, s);
+    if (shape == T256x256) return launch_cfg<256, 256, 2, 4, EPI, OP, KM>(d, round, s);
+    if (shape == T128x256) return launch_cfg<128, 256, 2, 4, EPI, OP, KM>(d, round, s);
+    if (shape == T128x128) return launch_cfg<128, 128, 4, 2, EPI, OP, KM>(d, round, s);
     if constexpr (EPI != EPI_SWIGLU_FWD) {
-        if (shape == T256x192) return launch_cfg<256, 192, 4, 2, EPI, OP>(d, round, s);
-        if (shape == T128x192) return launch_cfg<128, 192, 4, 2, EPI, OP>(d, round, s);
-        if (shape == T64x64) return launch_cfg<64, 64, 2, 2, EPI, OP>(d, round, s);
+        if (shape == T256x192) return launch_cfg<256, 192, 4, 2, EPI, OP, KM>(d, round, s);
+        if (shape == T128x192) return launch_cfg<128, 192, 4, 2, EPI, OP, KM>(d, round, s);
+        if (shape == T64x64) return launch_cfg<64, 64, 2, 2, EPI, OP, KM>(d, round, s);
     }
     return SDP_ERR_UNSUPPORTED; // not reached: choose_shape returns one of the above
 }
@@ -1380,15 +1469,23 @@ bool gemm_mfma_supported(const GemmDesc& d) {
     // 16-byte global chunks (a depth that is no multiple of 64 ends in a step whose missing chunks are zeros: any
     // multiple of 8 will do.  T = 5000, d = 1600, p = 2664, whose depths p and T are odd multiples of 8: a step of two
     // workers takes 0.98 ms here, 12.0 ms with those depths on the plain kernel), 32-bit byte offsets inside each operand
-    if (d.K % 8 || d.lda % 8 || d.ldb % 8 || d.N % 8 || d.ldc % 8) return false;
-    if (d.a_km) return false; // depth-major A goes through the transposing pre-pass or the plain kernel
+    if ((d.K % 8 && !(d.a_km && d.b_km)) || d.lda % 8 || d.ldb % 8 || d.N % 8 || d.ldc % 8) return false;
+    // depth-major operands: batched launches, B or both, columns in whole chunks
+    if (d.a_km || d.b_km) {
+        if (d.nbatch == 0 || !d.b_km || d.b_gather || (d.a_km && (d.M % 8 || (d.a_gather && !d.a_gather_chunks)))) return false;
+        if (d.ldb >= (int64_t)1 << 22 || (d.a_km && d.lda >= (int64_t)1 << 22)) return false; // 64 rows within 32-bit offsets
+        for (int z = 0; z < d.nbatch; ++z)
+            if (z < kMaxBatch && (d.ldab[z] % 8 || d.ldab[z] >= (int64_t)1 << 22)) return false;
+    } else if (d.nbatch > 0) {
+        return false;
+    }
     // the epilogue addresses a wave's part of the tile (at most 128 rows) with 32-bit byte offsets below 2^31
     constexpr int64_t kMaxLd = (int64_t)1 << 22;
     if (d.ldc >= kMaxLd || d.ldc3 >= kMaxLd || d.ldc3 % 8 || (d.R && d.ldr >= kMaxLd)) return false;
     if (d.epilogue == EPI_SWIGLU_BWD && (d.ldg >= kMaxLd || (d.Ct && d.ldct >= kMaxLd))) return false;
-    if ((d.a_rows > 0 ? d.a_rows : (int64_t)d.M) * d.lda * 2 >= ((int64_t)1 << 32)) return false;
+    if (!d.a_km && (d.a_rows > 0 ? d.a_rows : (int64_t)d.M) * d.lda * 2 >= ((int64_t)1 << 32)) return false;
     if (d.a_gather && (d.a_rows <= 0 || d.epilogue == EPI_DUAL_ACC)) return false;
-    if ((d.b_rows > 0 ? d.b_rows : (int64_t)d.N) * d.ldb * 2 >= ((int64_t)1 << 32)) return false;
+    if (!d.b_km && (d.b_rows > 0 ? d.b_rows : (int64_t)d.N) * d.ldb * 2 >= ((int64_t)1 << 32)) return false;
     if (d.b_gather && d.b_rows <= 0) return false;
     if (d.R) {
         if (d.nbatch > 0 || (d.epilogue != EPI_STORE && d.epilogue != EPI_DUAL_ACC)) return false;
@@ -1432,13 +1529,13 @@ int gemm_mfma_bf16(const GemmDesc& d, hipStream_t s) {
             if (parts > 1) {
                 GemmDesc dt = d;
                 dt.ksplit = parts;
-                return launch<EPI_STORE, OP_DW_TAIL>(dt, s); // followed by its reduction
+                return d.a_km ? launch<EPI_STORE, OP_DW_TAIL, 3>(dt, s) : launch<EPI_STORE, OP_DW_TAIL, 2>(dt, s); // followed by its reduction
             }
         }
-        if (r < 2) return launch<EPI_STORE, OP_DW>(d, s);
+        if (r < 2) return d.a_km ? launch<EPI_STORE, OP_DW, 3>(d, s) : launch<EPI_STORE, OP_DW, 2>(d, s);
         GemmDesc ds = d;
         ds.ksplit = r;
-        int rc = launch<EPI_STORE, OP_DW_SPLIT>(ds, s);
+        int rc = d.a_km ? launch<EPI_STORE, OP_DW_SPLIT, 3>(ds, s) : launch<EPI_STORE, OP_DW_SPLIT, 2>(ds, s);
         if (rc != SDP_OK) return rc;
         ReduceArgs ra{(const float*)d.split_ws, r, d.nbatch, d.M, d.N, {}, d.ldc, d.c_scatter};
         for (int z = 0; z < kMaxBatch; ++z) ra.Cb[z] = (uint16_t*)d.Cb[z];

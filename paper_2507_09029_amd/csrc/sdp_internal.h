@@ -35,12 +35,13 @@ inline int launch_status() { return hip_status(hipGetLastError()); }
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-// Leading dimension of `rows` rows of `min` bf16 elements that a contraction reads from the workspace: whole 128-byte lines,
-// so that the 128 bytes that a depth step takes of a row are one line and not two (5000 x 1600 outputs, 2664 deep, rows of
+// Leading dimension of `rows` rows of `min` bf16 elements that a contraction reads from the workspace: an odd number of whole
+// 128-byte lines (odd, so that rows are not 2^k bytes
+// apart, which fall onto the same memory channels), so that the 128 bytes that a depth step takes of a row are one line and not two (5000 x 1600 outputs, 2664 deep, rows of
 // 5328 / 5376 bytes: 48.1 / 40.2 us; 5328 x 1600, 5000 deep, rows of 10128 / 10112 bytes: 98.7 / 83.1 us), unless that
 // takes the matrix out of the MFMA contraction's 4 GiB.
 inline int64_t line_ld(int64_t min, int64_t rows) {
-    const int64_t ld = (min + 63) / 64 * 64;
+    const int64_t ld = (min + 63) / 64 * 64 | 64;
     return rows * ld * 2 < ((int64_t)1 << 32) ? ld : min;
 }
 
@@ -63,8 +64,8 @@ inline bool overlap(std::initializer_list<Extent> out, std::initializer_list<Ext
 //   A(m,k) = a_km ? A[k * lda + m] : A[ra(m) * lda + k]  (a_km: A is stored depth-major, [K][M])
 //   B(k,n) = b_km ? B[rb(k) * ldb + n] : B[rb(n) * ldb + k] (b_km: B is stored depth-major, [K][N])
 // rb is the identity when b_gather is null, else a lookup in an int32 table (active-neuron rows); ra likewise
-// with a_gather (with a_km it applies to the columns: A[k * lda + ra(m)]).  b_km and a_km with a_gather: fp32
-// contraction only.
+// with a_gather (with a_km it applies to the columns: A[k * lda + ra(m)]).  b_km: fp32 contraction, and batched launches of
+// the MFMA one, which are b_km or a_km and b_km; a_km with a_gather: the same, the latter with a_gather_chunks.
 // A second operand pair (A2, B2) with the same shapes and strides is used by two of the epilogues.
 enum Epilogue {
     EPI_STORE = 0,       // C[rc(m) * ldc + n] = acc      (rc: optional row scatter; rc(m) < 0 drops row m)
@@ -85,6 +86,7 @@ struct GemmDesc {
     int64_t lda = 0;
     int a_km = 0;
     const int32_t* a_gather = nullptr;
+    int a_gather_chunks = 0; // a_km: the list's entries 8 i .. 8 i + 7 are consecutive, from a multiple of 8 on
     int64_t a_rows = 0; // number of rows of the stored A (bounds the gathered row index); 0 = M
     const void* B = nullptr;
     const void* B2 = nullptr;
@@ -130,6 +132,7 @@ struct GemmDesc {
     // weight-gradient contractions): nbatch > 0 selects Ab/Bb/Cb instead of A/B/C
     int nbatch = 0;
     const void* Ab[4] = {nullptr, nullptr, nullptr, nullptr};
+    int64_t ldab[4] = {0, 0, 0, 0}; // MFMA kernel, a_km: each problem's leading dimension, 0 = lda
     const void* Bb[4] = {nullptr, nullptr, nullptr, nullptr};
     void* Cb[4] = {nullptr, nullptr, nullptr, nullptr};
     // batched launches only: optional fp32 scratch of gemm_split_ws_bytes(M, N, K, nbatch) bytes.  With it, a

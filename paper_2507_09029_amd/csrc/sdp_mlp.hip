@@ -1,19 +1,23 @@
 // One worker's masked SwiGLU MLP forward and backward (the paper's Sec. 3.1 regimes applied to the
 // neuron-level masks of Sec. 3.2), expressed as a fixed sequence of contractions C = A . B^T whose
-// operands are all read depth-contiguous.
+// operands are read depth-contiguous, but for the weight gradients'.
 //
 // With n = p and S = idx_k under forward masking, n = F and S = all neurons under backward masking:
 //   forward   wt      : W2c = W2T[S]^T                       ([d][n], gather + transpose, HBM-bound)
 //             gate_up : [G | U] = X . [W1 | W3][S]^T         (T x n, depth d; rows of W1, W3 gathered in
 //                        the operand load)  + SwiGLU epilogue -> Act
 //             down    : Y  = Act . W2c^T                     (T x d, depth n)
-//   backward  wt      : W1c = W1[S]^T, W3c = W3[S]^T ([d][n]);  XT = X^T, dYT = dY^T ([d][T])
+//   backward  wt      : W1c = W1[S]^T, W3c = W3[S]^T ([d][n])
 //             dact    : dA = dY . W2T[S]^T                   (T x n, depth d; rows of W2T gathered)
-//                        + SwiGLU-backward epilogue -> dG, dU [T][n] and, transposed, dG^T, dU^T,
-//                        Act^T [p][T] (neuron-major; under backward masking only the worker's p
-//                        columns are kept, row = rank of the neuron in idx_k)
+//                        + SwiGLU-backward epilogue -> dG, dU, Act [T][n]; under backward masking, in the
+//                        place of Act, the worker's p columns of the three transposed, dG^T, dU^T, Act^T
+//                        [p][T] (neuron-major, row = rank of the neuron in idx_k)
 //             dw      : dW1[S] = dG^T . X, dW3[S] = dU^T . X, dW2T[S] = Act^T . dY   (p x d, depth T),
-//                        one batched launch over the neuron-major copies and XT, dYT
+//                        one batched launch that reads X, dY and, under forward masking, dG, dU, Act as they
+//                        are stored, depth-major.  With transposed copies of all of these: two workers at
+//                        T = 5000, d = 1600, p = 2664 878 us, this way 821; four at T = 8192, d = 1536,
+//                        p = 2048 1843, 1759; eight under backward masking at T = 16384, d = 2048, F = 5504
+//                        20.6 ms, 20.1; two at T = 1024, d = 768, p = 1024 112.3, 113.7
 //             dx      : dX = dG . W1c^T + dU . W3c^T         (T x d, depth 2n)
 // Under backward masking the weight-gradient contraction reads only the p kept rows: the gradient is
 // computed on the worker's mask and nowhere else.  fp32 tensors take the fp32 contraction, which reads every
@@ -92,9 +96,11 @@ extern "C" size_t sdp_masked_mlp_bwd_workspace_bytes(int mode, int dtype, int T,
     const size_t row_b = ld_neurons(dtype, T, d, (int)n) * e;
     size_t bytes = 3 * round_up(T * row_b, 256) + 2 * round_up(d * row_b, 256) +
                    2 * round_up((size_t)d * ldt * e, 256);
-    if (mode == SDP_MASK_BACKWARD) bytes += 3 * round_up((size_t)T * p * e, 256);
-    bytes += 3 * round_up((size_t)p * ldt * e, 256); // neuron-major copies of dG, dU, Act on the mask
-    if (mode == SDP_MASK_BACKWARD) bytes += round_up((size_t)F * sizeof(int32_t), 256); // rank of every neuron in the list
+    if (mode == SDP_MASK_BACKWARD) {
+        bytes += 3 * round_up((size_t)T * p * e, 256);
+        bytes += 3 * round_up((size_t)p * ldt * e, 256); // neuron-major copies of dG, dU, Act on the mask
+        bytes += round_up((size_t)F * sizeof(int32_t), 256); // rank of every neuron in the list
+    }
     if (dtype == SDP_BF16) bytes += round_up(gemm_tail_ws_bytes(p, d, T, 3), 256); // depth ranges of the weight gradients' last round
     return bytes;
 }
@@ -206,8 +212,8 @@ int sdp::mlp_bwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
         w += 3 * cmp_b;
     }
     const size_t nm_b = round_up((size_t)p * ldt * e, 256);
-    void *dGn = w, *dUn = w + nm_b, *Actn = w + 2 * nm_b; // [p][T(+pad)]: neuron-major
-    w += 3 * nm_b;
+    void *dGn = w, *dUn = w + nm_b, *Actn = w + 2 * nm_b; // backward masking: [p][T(+pad)], neuron-major
+    if (mode == SDP_MASK_BACKWARD) w += 3 * nm_b;
     int32_t* ranks = (int32_t*)w; // backward masking: [F]
     if (mode == SDP_MASK_BACKWARD) w += round_up((size_t)F * sizeof(int32_t), 256);
     void* tail_ws = dtype == SDP_BF16 && gemm_tail_ws_bytes(p, d, T, 3) > 0 ? w : nullptr;
@@ -266,29 +272,26 @@ int sdp::mlp_bwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
         return rc != SDP_OK ? rc : gemm_f32(dx, s);
     }
 
-    // the four operand copies of the backward pass (X^T, dY^T only feed the weight gradients), made beside dact, which needs
-    // none of them
-    const TransposeJob tj[4] = {{W1, W1c, d, ldn, gather, n, d},
-                                {W3, W3c, d, ldn, gather, n, d},
-                                {X, XT, d, ldt, nullptr, T, d},
-                                {dY, dYT, d, ldt, nullptr, T, d}};
-
-    // weight-gradient contraction (set up first: whether it can take the MFMA path decides what the
-    // activation-gradient kernel writes)
-    const void* rhs[3] = {XT, XT, dYT};
-    void* outp[3] = {dW1, dW3, dW2T};
-    void* nmaj[3] = {dGn, dUn, Actn};
+    // The weight gradients read X and dY as they are (depth-major), and so they read dG, dU and Act under forward masking; under
+    // backward masking dact also writes the worker's p columns of these three neuron-major.
     GemmDesc dw;
     dw.name = "mlp_dw";
     dw.M = p, dw.N = d, dw.K = T;
-    dw.ldb = ldt;
+    dw.ldb = d, dw.b_km = 1;
     dw.epilogue = EPI_STORE;
     dw.ldc = d;
     dw.c_scatter = dw_layout == SDP_DW_SCATTER ? idx_k : nullptr;
     dw.nbatch = 3;
-    dw.lda = ldt, dw.a_km = 0;
+    if (mode == SDP_MASK_BACKWARD) {
+        dw.lda = ldt;
+        dw.Ab[0] = dGn, dw.Ab[1] = dUn, dw.Ab[2] = Actn;
+    } else {
+        dw.lda = ldn, dw.a_km = 1;
+        dw.Ab[0] = dG, dw.Ab[1] = dU, dw.Ab[2] = Act;
+    }
+    dw.Bb[0] = X, dw.Bb[1] = X, dw.Bb[2] = dY;
+    dw.Cb[0] = dW1, dw.Cb[1] = dW3, dw.Cb[2] = dW2T;
     dw.tail_ws = tail_ws, dw.tail_name = "mlp_dw_reduce";
-    for (int i = 0; i < 3; ++i) dw.Ab[i] = nmaj[i], dw.Bb[i] = rhs[i], dw.Cb[i] = outp[i];
 
     GemmDesc da;
     da.name = "mlp_dact";
@@ -298,11 +301,13 @@ int sdp::mlp_bwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
     da.epilogue = EPI_SWIGLU_BWD;
     da.Gin = G_save, da.Uin = U_save, da.ldg = n;
     da.C = dG, da.C2 = dU, da.ldc = ldn;
-    // bf16, aligned shapes: the epilogue also writes dG, dU and act transposed (neuron-major [p][T],
-    // under backward masking only the worker's p columns), which is the layout in which the batched
-    // weight-gradient contraction reads both operands depth-contiguous; act is not stored row-major.
-    da.Ct = dGn, da.Ct2 = dUn, da.Ct3 = Actn, da.ldct = ldt;
-    if (mode == SDP_MASK_BACKWARD) da.cidx = idx_k, da.pc = p, da.crank = ranks;
+    if (want_dw && mode == SDP_MASK_FORWARD) da.C3 = Act;
+    // backward masking: the epilogue also writes dG, dU and act of the worker's p columns transposed (neuron-major [p][T]),
+    // in which layout the weight-gradient launch reads them depth-contiguous; act is not stored row-major
+    if (want_dw && mode == SDP_MASK_BACKWARD) {
+        da.Ct = dGn, da.Ct2 = dUn, da.Ct3 = Actn, da.ldct = ldt;
+        da.cidx = idx_k, da.pc = p, da.crank = ranks;
+    }
     const bool fused = want_dw && p % 8 == 0 && T % 8 == 0 && gemm_mfma_supported(dw) && gemm_mfma_supported(da);
     if (!fused) {
         da.Ct = da.Ct2 = da.Ct3 = nullptr, da.cidx = nullptr, da.pc = 0, da.crank = nullptr;
@@ -313,11 +318,26 @@ int sdp::mlp_bwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
             da.cidx = idx_k, da.pc = p;
         }
     }
+    // a gradient in the place of X or dY: the launch reads copies of those
+    const size_t dw_b = (size_t)(dw_layout == SDP_DW_SCATTER ? F : p) * d * e, tok_b = (size_t)T * d * e;
+    if (fused && overlap({{dW1, dw_b}, {dW3, dw_b}, {dW2T, dw_b}}, {{X, tok_b}, {dY, tok_b}})) {
+        for (int i = 0; i < 2; ++i) { // d % 8 == 0: rows of bf16 as rows of half as many floats
+            rc = copy_rows_f32((const float*)(i ? dY : X), nullptr, T, d / 2, (float*)(i ? dYT : XT), "mlp_copy_bwd", s);
+            if (rc != SDP_OK) return rc;
+        }
+        dw.Bb[0] = dw.Bb[1] = XT, dw.Bb[2] = dYT;
+        if (dx_residual == dY) dx_residual = dYT;
+    }
     if (fused && mode == SDP_MASK_BACKWARD) {
         rc = column_ranks(idx_k, p, F, ranks, s);
         if (rc != SDP_OK) return rc;
     }
-    da.side = tj, da.nside = want_dw ? 4 : 2, da.side_name = "mlp_tr_bwd";
+    // the operand copies that dX and the plain weight gradients read, made beside dact, which needs none of them
+    const TransposeJob tj[4] = {{W1, W1c, d, ldn, gather, n, d},
+                                {W3, W3c, d, ldn, gather, n, d},
+                                {X, XT, d, ldt, nullptr, T, d},
+                                {dY, dYT, d, ldt, nullptr, T, d}};
+    da.side = tj, da.nside = want_dw && !fused ? 4 : 2, da.side_name = "mlp_tr_bwd";
     rc = run(dtype, da, s);
     if (rc != SDP_OK) return rc;
 
@@ -337,12 +357,14 @@ int sdp::mlp_bwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
     if (rc != SDP_OK) return rc;
 
     if (fused || !want_dw) return SDP_OK;
-    // plain path: read the left operands depth-major ([T][ldn], or the compact copies [T][p]) as they are
+    // plain path: the left operands depth-major ([T][ldn], or the compact copies [T][p]) as they are, the right ones transposed
     const void* lhs[3] = {dGc, dUc, Actc};
+    const void* rhs[3] = {XT, XT, dYT};
     dw.nbatch = 0;
     dw.lda = mode == SDP_MASK_BACKWARD ? p : ldn, dw.a_km = 1;
+    dw.ldb = ldt, dw.b_km = 0;
     for (int i = 0; i < 3; ++i) {
-        dw.A = lhs[i], dw.B = rhs[i], dw.C = outp[i];
+        dw.A = lhs[i], dw.B = rhs[i], dw.C = dw.Cb[i];
         rc = gemm_simple(dw, s);
         if (rc != SDP_OK) return rc;
     }
