@@ -1312,22 +1312,23 @@ int launch_cfg(const GemmDesc& d, double round, hipStream_t s) {
 // Tile shapes (rows x columns), and what each costs: a workgroup takes step0 us a depth step on an otherwise idle chip and
 // step1 us with all CUs at work, plus an epilogue of e0 us and e1 us per 1024 outputs that depends on what it moves; the
 // launch takes as many such rounds as its tiles need on 256 CUs.  Fitted to 75 contractions of 15 MLP and attention
-// shapes (128 to 8192 rows, depths of 128 to 8192), each timed at every shape: the choice is the fastest one or within 5 %
-// of it on all but one (14 %: 280 small tiles, barely a second round).  The smaller shapes buy idle CUs at more
-// L2 -> LDS traffic per flop: 1024 x 768 outputs, depth 2048: 41, 38, 27, 26, 21, 11 us in the order below; 8192 x 1536,
-// depth 4096: 87, 84, 116, 110, 125, 175 us.
+// shapes (128 to 8192 rows, depths of 128 to 8192), each timed at every shape, and the 128-row tiles again, for the loop they
+// have now, to the launches of seven of them (depths of 512 to 8192): of these the choice is the fastest or within 6 % of it.
+// The smaller shapes buy idle CUs at more L2 -> LDS traffic per flop: 4096 x 1200
+// outputs, depth 3200: 57, 47, 41, 35, 46, 60 us in the order below; 8192 x 1536, depth 2048: 46, 44, 54, 49, 53, 94;
+// 1500 x 1024, depth 1536: 29, 24, 19, 15, 12, 15.
 enum Shape { T256x256, T256x192, T128x256, T128x192, T128x128, T64x64, NUM_SHAPES };
 struct ShapeInfo {
     int bm, bn;
     double step0, step1;
 };
-constexpr ShapeInfo kShapes[NUM_SHAPES] = {{256, 256, 1.02, 1.35}, {256, 192, 0.87, 1.20}, {128, 256, 0.82, 0.90},
-                                           {128, 192, 0.80, 0.88}, {128, 128, 0.56, 0.66}, {64, 64, 0.23, 0.22}};
+constexpr ShapeInfo kShapes[NUM_SHAPES] = {{256, 256, 1.02, 1.35}, {256, 192, 0.87, 1.20}, {128, 256, 0.74, 0.84},
+                                           {128, 192, 0.58, 0.78}, {128, 128, 0.47, 0.60}, {64, 64, 0.23, 0.22}};
 struct EpilogueCost {
     double e0, e1;
 };
 constexpr EpilogueCost epilogue_cost(int epi) {
-    return epi == EPI_SWIGLU_FWD ? EpilogueCost{5.0, 0.055} : epi == EPI_SWIGLU_BWD ? EpilogueCost{4.0, 0.30} : EpilogueCost{2.8, 0.03};
+    return epi == EPI_SWIGLU_FWD ? EpilogueCost{5.0, 0.055} : epi == EPI_SWIGLU_BWD ? EpilogueCost{2.4, 0.36} : EpilogueCost{2.8, 0.03};
 }
 // the SwiGLU-forward epilogue pairs gate and up columns inside a wave's columns and has no 192- or 64-wide variant
 constexpr bool shape_exists(int epi, int shape) {
