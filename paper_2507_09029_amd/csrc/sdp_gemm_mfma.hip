@@ -246,9 +246,10 @@ struct Geometry {
     static_assert(LDS <= 160 * 1024, "LDS of one CU");
 };
 
-// Transposes carried by a launch (the MLP's gate_up and dact): workgroups from g.ntot on do `side_tiles` tiles at a time.
+// Transposes carried by a launch (the MLP's gate_up, dact and weight gradients): workgroups from g.ntot on do `side_tiles`
+// tiles at a time.
 struct NoSide {};
-constexpr bool carries_side(int op) { return op == OP_GATE_UP || op == OP_DACT; }
+constexpr bool carries_side(int op) { return op == OP_GATE_UP || op == OP_DACT || op == OP_DW; }
 template <int OP>
 using SideArg = std::conditional_t<carries_side(OP), SideJobs, NoSide>;
 // tiles each 256 threads of a workgroup take at once: as many as the contraction's LDS holds, at most 8 (64 registers)
@@ -1206,6 +1207,8 @@ int tail_reduce(const Dev& g, const GemmDesc& d, hipStream_t s) {
 // round leaves idle get through them meanwhile.  A workgroup moves 16 tiles, one after the other about 5 us each and 5 more
 // for the first.  T = 5000, d = 1600, p = 2664 (28 us of transposes a worker beside 420 and 220 tiles): step of two workers
 // 1020 -> 980 us; beside the 512 tiles of T = 8192, p = 2048, two full rounds, W2's transpose cost 12 us more than on its own.
+// W1's and W3's beside the weight gradients (144 tiles; dact has 256) at T = 1024, d = 768, p = 1024: step of two workers
+// 113.7 -> 107.1 us; four at T = 8192, d = 1536, p = 2048 (192 tiles) 1786 -> 1754.
 bool carry(int64_t tiles, double round, int64_t wgs) {
     const int64_t idle = tiles % kNumCU ? kNumCU - tiles % kNumCU : 0;
     return idle > 0 && (double)((wgs + idle - 1) / idle) * 5.0 + 5.0 <= 1.2 * round;
@@ -1375,6 +1378,18 @@ int launch(const GemmDesc& d, hipStream_t s) {
     return SDP_ERR_UNSUPPORTED; // not reached: choose_shape returns one of the above
 }
 
+// Whether the launch of `d` would carry its transposes (a tile's workgroups take 16 at a time, with 128 x 128 and 64 x 64 tiles
+// 10 and 7: counted as 7).
+template <int EPI>
+bool would_carry(const GemmDesc& d, int nbatch) {
+    double round = 0;
+    const ShapeInfo& h = kShapes[choose_shape<EPI>(d, nbatch, 1, &round)];
+    int64_t side = 0;
+    for (int i = 0; i < d.nside; ++i) side += (int64_t)((d.side[i].R + 63) / 64) * ((d.side[i].C + 63) / 64);
+    const int64_t tiles = (int64_t)((d.M + h.bm - 1) / h.bm) * ((d.N + h.bn - 1) / h.bn) * nbatch;
+    return carry(tiles, round, (side + 6) / 7);
+}
+
 // Tail cut of a batched launch (OP_DW_TAIL).  With T tiles on 256 CUs the launch runs floor(T / 256) full rounds
 // and a last round of T mod 256 tiles; when that round leaves many CUs idle, each of its tiles is cut into
 // `parts` depth ranges that spread over all CUs (every range at least 32 steps deep), at the price of one fp32
@@ -1518,6 +1533,14 @@ bool gemm_mfma_supported(const GemmDesc& d) {
         }
     }
     return true;
+}
+
+bool gemm_carries(const GemmDesc& d) {
+    if (!gemm_mfma_supported(d)) return false;
+    if (d.epilogue == EPI_SWIGLU_BWD) return would_carry<EPI_SWIGLU_BWD>(d, 1);
+    if (d.nbatch == 0 || (d.split_ws && gemm_choose_ksplit(d.M, d.N, d.K, d.nbatch) > 1)) return false;
+    if (d.tail_ws && plan_tail(d, nullptr, nullptr) > 1) return false;
+    return would_carry<EPI_STORE>(d, d.nbatch);
 }
 
 int gemm_mfma_bf16(const GemmDesc& d, hipStream_t s) {

@@ -145,7 +145,7 @@ struct GemmDesc {
     // round's tiles into ranges (gemm_choose_tail), which a second small kernel adds up.
     void* tail_ws = nullptr;
     const char* tail_name = "dw_tail_reduce"; // profile name of that second kernel
-    // SWIGLU_FWD / SWIGLU_BWD, MFMA kernel: transposes that have to be done when the contraction is, by extra workgroups of
+    // SWIGLU_FWD / SWIGLU_BWD and batched launches without a depth cut, MFMA kernel: transposes that have to be done when the contraction is, by extra workgroups of
     // its launch or by one of their own before it
     const struct TransposeJob* side = nullptr;
     int nside = 0;
@@ -166,6 +166,8 @@ int gemm_simple(const GemmDesc& g, hipStream_t s);
 // bf16 MFMA contraction; returns SDP_ERR_UNSUPPORTED when the shape / alignment does not fit.
 int gemm_mfma_bf16(const GemmDesc& g, hipStream_t s);
 bool gemm_mfma_supported(const GemmDesc& g);
+// whether the launch of g (SWIGLU_BWD, or batched without a depth cut) would carry g.side
+bool gemm_carries(const GemmDesc& g);
 // depth ranges a batched launch of nbatch problems of shape M x N x K would be cut into, and the scratch that takes
 int gemm_choose_ksplit(int M, int N, int K, int nbatch);
 size_t gemm_split_ws_bytes(int M, int N, int K, int nbatch);

@@ -332,12 +332,17 @@ int sdp::mlp_bwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
         rc = column_ranks(idx_k, p, F, ranks, s);
         if (rc != SDP_OK) return rc;
     }
-    // the operand copies that dX and the plain weight gradients read, made beside dact, which needs none of them
+    // the operand copies that dX and the plain weight gradients read, made beside dact, which needs none of them, or beside the
+    // weight gradients where dact's tiles leave no CU idle
     const TransposeJob tj[4] = {{W1, W1c, d, ldn, gather, n, d},
                                 {W3, W3c, d, ldn, gather, n, d},
                                 {X, XT, d, ldt, nullptr, T, d},
                                 {dY, dYT, d, ldt, nullptr, T, d}};
     da.side = tj, da.nside = want_dw && !fused ? 4 : 2, da.side_name = "mlp_tr_bwd";
+    if (fused && !overlap({{dW1, dw_b}, {dW3, dw_b}, {dW2T, dw_b}}, {{W1, (size_t)F * d * e}, {W3, (size_t)F * d * e}})) {
+        dw.side = tj, dw.nside = 2, dw.side_name = "mlp_tr_bwd";
+        if (gemm_carries(da) || !gemm_carries(dw)) dw.nside = 0; else da.nside = 0;
+    }
     rc = run(dtype, da, s);
     if (rc != SDP_OK) return rc;
 
