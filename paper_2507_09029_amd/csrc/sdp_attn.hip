@@ -520,7 +520,7 @@ inline dim3 workgroup_grid(int64_t n) {
 template <int LDS>
 __device__ inline void carried(const SideJobs& side, int w, unsigned char* lds) {
     constexpr int PER = side_tiles(LDS);
-    if (w < (side.end[kMaxTransposeJobs - 1] + PER - 1) / PER) side_transposes<PER>(side, w, lds, threadIdx.x);
+    if (w < (side.end[kMaxTransposeJobs - 1] + PER - 1) / PER) side_transposes<PER, true>(side, w, lds, threadIdx.x);
 }
 
 // waves per SIMD the registers are allotted for.  KW = 1, heads of 64: 3 beat 2 (86 -> 77 us at 4 x 2048 tokens, 12 heads)
@@ -1090,10 +1090,14 @@ int sdp::attn_fwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     const FwdWs w = fwd_ws((char*)ws, esize(dtype), d, E, padded);
     const int64_t ldp = padded ? ld_weights(2, d, 3 * E) : d, ldo = ld_weights(esize(dtype), E, d); // rows of Wp / WoP, of WoC
 
-    if (gathered && !padded) {
+    // rows of the held heads: bf16 from the list of heads itself, fp32 from lists of rows
+    const HeadList heads = dtype == SDP_BF16 ? head_list(hd, ph, H) : HeadList{};
+    if (gathered && dtype == SDP_F32) {
         rc = head_rows(head_idx_k, ph, H, hd, w.rows_qkv, w.rows_o, s);
         if (rc != SDP_OK) return rc;
     }
+    const int32_t* rows_qkv = !gathered || padded ? nullptr : dtype == SDP_BF16 ? head_idx_k : w.rows_qkv;
+    const int32_t* rows_o = !gathered || padded ? nullptr : dtype == SDP_BF16 ? head_idx_k : w.rows_o;
     if (padded) { // the run heads' rows of W_Q, W_K, W_V and W_O, each head padded to hw rows
         const PadArgs pa{(const uint16_t*)Wqkv, (const uint16_t*)WoT, (uint16_t*)w.Wp, (uint16_t*)w.WoP,
                          gathered ? head_idx_k : nullptr, nullptr, ph, ph, H, hd, hw, d, 0, ldp, nullptr, nullptr};
@@ -1106,7 +1110,7 @@ int sdp::attn_fwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     pj.M = T, pj.N = 3 * E, pj.K = d;
     pj.A = X, pj.lda = d;
     pj.B = padded ? w.Wp : Wqkv, pj.ldb = ldp;
-    if (gathered && !padded) pj.b_gather = w.rows_qkv, pj.b_rows = (int64_t)3 * H * hd;
+    if (rows_qkv) pj.b_gather = rows_qkv, pj.b_rows = (int64_t)3 * H * hd, pj.heads = heads;
     pj.epilogue = EPI_STORE;
     pj.C = QKV_save, pj.ldc = 3 * E;
     rc = run(dtype, pj, s);
@@ -1119,7 +1123,7 @@ int sdp::attn_fwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         a.lse = LSE_save;
         a.S = S, a.ph = ph, a.hd = hw;
         a.scale = 1.f / sqrtf((float)hd), a.scale2 = a.scale * 1.44269504088896340736f;
-        const TransposeJob wt{padded ? w.WoP : WoT, w.WoC, ldp, ldo, gathered && !padded ? w.rows_o : nullptr, E, d};
+        const TransposeJob wt{padded ? w.WoP : WoT, w.WoC, ldp, ldo, rows_o, E, d, heads};
         rc = launch_core(CORE_FWD, a, (int64_t)ph * Bt, &wt, 1, "attn_core_fwd", s);
     } else {
         AttnCoreDesc c;
@@ -1130,7 +1134,7 @@ int sdp::attn_fwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     if (rc != SDP_OK) return rc;
 
     // fp32 reads WoT itself: an output that takes its place needs a copy
-    const int32_t* wo_rows = gathered ? w.rows_o : nullptr;
+    const int32_t* wo_rows = rows_o;
     if (dtype == SDP_F32 && overlap({{Y, (size_t)T * d * 4}}, {{WoT, (size_t)H * hd * d * 4}})) {
         rc = copy_rows_f32((const float*)WoT, wo_rows, E, d, (float*)w.WoC, "attn_wt_fwd", s);
         if (rc != SDP_OK) return rc;
@@ -1188,10 +1192,14 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
                          w.rows_qkv};
         rc = pad_heads(pa, want_dw, s);
         if (rc != SDP_OK) return rc;
-    } else if (!all_heads) {
+    } else if (!all_heads && dtype == SDP_F32) {
         rc = head_rows(head_idx_k, ph, H, hd, w.rows_qkv, w.rows_o, s);
         if (rc != SDP_OK) return rc;
     }
+    // rows of the held heads: padded, the lists just made; bf16, from the list of heads itself; fp32, lists of rows
+    const HeadList heads = dtype == SDP_BF16 && !padded ? head_list(hd, ph, H) : HeadList{};
+    const int32_t* rows_qkv = dtype == SDP_BF16 && !padded ? head_idx_k : w.rows_qkv;
+    const int32_t* rows_o = dtype == SDP_BF16 && !padded ? head_idx_k : w.rows_o;
 
     // bf16: the four weight gradients share one shape (Eh x d, depth T): dWq, dWk, dWv from the three column blocks of dQKV and
     // X, dWoT from O and dY; one batched launch fills the CUs four times better than four would, and reads all of these as
@@ -1207,12 +1215,13 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         wg.M = Eh, wg.N = d, wg.K = T;
         wg.a_km = wg.b_km = 1;
         wg.lda = 3 * E, wg.ldb = d;
-        if (!gathered && !all_heads) wg.a_gather = w.rows_o, wg.a_rows = E, wg.a_gather_chunks = 1; // heads of a multiple of 8
+        if (!gathered && !all_heads) wg.a_gather = rows_o, wg.a_rows = E, wg.a_gather_chunks = 1; // heads of a multiple of 8
         wg.epilogue = EPI_STORE;
         wg.ldc = d;
         // rows of the held heads inside each matrix; padded heads: w.rows_o = the held heads' columns of the operands, w.rows_qkv =
         // output rows (-1: dropped)
-        wg.c_scatter = padded ? w.rows_qkv : dw_layout == SDP_DW_SCATTER && !all_heads ? w.rows_o : nullptr;
+        wg.c_scatter = padded ? w.rows_qkv : dw_layout == SDP_DW_SCATTER && !all_heads ? rows_o : nullptr;
+        wg.heads = heads;
         if (padded && !gathered) wg.a_gather = w.rows_o, wg.a_rows = E, wg.a_gather_chunks = 1;
         wg.nbatch = 4;
         for (int i = 0; i < 3; ++i)
@@ -1227,7 +1236,7 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     go.M = T, go.N = E, go.K = d;
     go.A = dY, go.lda = d;
     go.B = padded ? w.WoP : WoT, go.ldb = ldp;
-    if (gathered && !padded) go.b_gather = w.rows_o, go.b_rows = (int64_t)H * hd;
+    if (gathered && !padded) go.b_gather = rows_o, go.b_rows = (int64_t)H * hd, go.heads = heads;
     go.epilogue = EPI_STORE;
     go.C = w.dO, go.ldc = E;
     rc = run(dtype, go, s);
@@ -1243,7 +1252,7 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         a.scale = 1.f / sqrtf((float)hd), a.scale2 = a.scale * 1.44269504088896340736f;
         // Wqkv's rows for dX; token-contiguous copies for the plain weight gradients
         const int64_t ldt = ld_tokens(T, d, E);
-        const TransposeJob beside_dq[4] = {{padded ? w.Wp : Wqkv, w.Wc, ldp, ldw, gathered && !padded ? w.rows_qkv : nullptr, 3 * E, d},
+        const TransposeJob beside_dq[4] = {{padded ? w.Wp : Wqkv, w.Wc, ldp, ldw, gathered && !padded ? rows_qkv : nullptr, 3 * E, d, heads},
                                            {O_save, w.Ot, E, ldt, nullptr, T, E},
                                            {X, w.Xt, d, ldt, nullptr, T, d},
                                            {dY, w.dYt, d, ldt, nullptr, T, d}};

@@ -81,6 +81,7 @@ struct Dev {
     const uint16_t *A, *A2, *B, *B2;
     int64_t lda, ldb;
     const int32_t *ag, *bg, *cs;
+    HeadList heads; // of these three
     uint16_t *C, *C2, *C3;
     int64_t ldc, ldc3; // ldc3: of C3 (SWIGLU_FWD)
     const uint16_t* R; // STORE / DUAL_ACC, single problem: optional residual [M][ldr]
@@ -386,36 +387,57 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
     // matrix are clamped to the last valid ones: such lanes fetch valid memory whose products only reach outputs that are
     // never stored.  Row-major: slab s of 1 KB holds tile rows 8 s .. 8 s + 7, lane -> row 8 s + lane / 8, stored chunk
     // position lane % 8.  Depth-major: chunk positions 64 s .. (km_chunk).
-    auto source_a = [&](int slab, int& k) __attribute__((always_inline)) -> uint32_t {
-        if constexpr (kAkm) {
-            int row, col;
-            km_chunk<BM>(64 * slab + lane, row, col);
-            const int m = m0 + col < g.M ? m0 + col : g.M - 8; // M % 8 == 0, and a gather list moves whole chunks
-            k = row;
-            return (uint32_t)((row * lda + (g.ag ? g.ag[m] : m)) * 2);
+    // Row (depth-major: column) indices -> places in the stored matrix; the look-ups of a wave's slabs in flight together.
+    // kHeads: the launches of the attention block, whose lists may be of heads
+    constexpr bool kHeads = OP == OP_DOWN || OP == OP_DW || OP == OP_DW_SPLIT;
+    auto look_up = [&](const int32_t* list, auto& idx) __attribute__((always_inline)) {
+        if (!list) return;
+        if (!kHeads || g.heads.width == 0) {
+            for (int& i : idx) i = list[i];
         } else {
-            const int r = 8 * slab + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
-            const int m = m0 + r < g.M ? m0 + r : g.M - 1;
-            const int64_t row = g.ag ? g.ag[m] : m;
-            k = c * 8;
-            return (uint32_t)((row * lda + k) * 2);
+            for (int& i : idx) i = listed_row(list, g.heads, i);
         }
     };
-    auto source_b = [&](int slab, int& k) __attribute__((always_inline)) -> uint32_t {
-        if constexpr (kBkm) {
-            int row, col;
-            km_chunk<BN>(64 * slab + lane, row, col);
-            const int n = n0 + col < g.N ? n0 + col : g.N - 8;
-            k = row;
-            return (uint32_t)((row * g.ldb + n) * 2);
-        } else {
-            const int r = 8 * slab + (lane >> 3), c = (lane & 7) ^ ((r >> 1) & 7);
-            int n = kFwd ? n0 + (r % (BN / 2)) : n0 + r;
-            n = n < g.N ? n : g.N - 1;
-            const int64_t row = g.bg ? g.bg[n] : n;
-            k = c * 8;
-            return (uint32_t)((row * g.ldb + k) * 2);
+    // slabs first, first + stride, ..
+    auto sources_a = [&](int first, int stride, auto& off, auto& k) __attribute__((always_inline)) {
+        constexpr int N = sizeof(off) / sizeof(off[0]);
+        int idx[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int slab = first + stride * i;
+            if constexpr (kAkm) {
+                int col;
+                km_chunk<BM>(64 * slab + lane, k[i], col);
+                idx[i] = m0 + col < g.M ? m0 + col : g.M - 8; // M % 8 == 0, and a list moves whole chunks
+            } else {
+                const int r = 8 * slab + (lane >> 3);
+                k[i] = ((lane & 7) ^ ((r >> 1) & 7)) * 8;
+                idx[i] = m0 + r < g.M ? m0 + r : g.M - 1;
+            }
         }
+        look_up(g.ag, idx);
+#pragma unroll
+        for (int i = 0; i < N; ++i) off[i] = (uint32_t)((kAkm ? k[i] * lda + idx[i] : idx[i] * lda + k[i]) * 2);
+    };
+    auto sources_b = [&](int first, int stride, auto& off, auto& k) __attribute__((always_inline)) {
+        constexpr int N = sizeof(off) / sizeof(off[0]);
+        int idx[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            const int slab = first + stride * i;
+            if constexpr (kBkm) {
+                int col;
+                km_chunk<BN>(64 * slab + lane, k[i], col);
+                idx[i] = n0 + col < g.N ? n0 + col : g.N - 8;
+            } else {
+                const int r = 8 * slab + (lane >> 3), n = kFwd ? n0 + (r % (BN / 2)) : n0 + r;
+                k[i] = ((lane & 7) ^ ((r >> 1) & 7)) * 8;
+                idx[i] = n < g.N ? n : g.N - 1;
+            }
+        }
+        if (!kBkm) look_up(g.bg, idx);
+#pragma unroll
+        for (int i = 0; i < N; ++i) off[i] = (uint32_t)((kBkm ? k[i] * g.ldb + idx[i] : idx[i] * g.ldb + k[i]) * 2);
     };
     // what depth step k0 / 64 adds to an operand's base
     auto step_a = [&](int k0) __attribute__((always_inline)) { return kAkm ? (int64_t)k0 * lda * 2 : (int64_t)k0 * 2; };
@@ -429,10 +451,8 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
         constexpr int TM = BM / 16, TN = BN / 16; // fragments of the tile
         uint32_t a_off[BM / 8], b_off[BN / 8];
         int a_k[BM / 8], b_k[BN / 8];
-#pragma unroll
-        for (int i = 0; i < BM / 8; ++i) a_off[i] = source_a(i, a_k[i]);
-#pragma unroll
-        for (int j = 0; j < BN / 8; ++j) b_off[j] = source_b(j, b_k[j]);
+        sources_a(0, 1, a_off, a_k);
+        sources_b(0, 1, b_off, b_k);
         f32x4 part[TM][TN];
 #pragma unroll
         for (int i = 0; i < TM; ++i)
@@ -507,10 +527,8 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
     // ---- per-lane global source of every slab this wave fills: byte offsets from a uniform base
     uint32_t a_off[SA], b_off[SB];
     int a_k[SA], b_k[SB]; // depth offset of this lane's chunk inside a step
-#pragma unroll
-    for (int i = 0; i < SA; ++i) a_off[i] = source_a(wave + NW * i, a_k[i]);
-#pragma unroll
-    for (int i = 0; i < SB; ++i) b_off[i] = source_b(wave + NW * i, b_k[i]);
+    sources_a(wave, NW, a_off, a_k);
+    sources_b(wave, NW, b_off, b_k);
 
     // LDS: the A stages, then a ring of three B stages
     unsigned char* const lds_a = smem;
@@ -871,7 +889,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
             const u32x2 hi = *(const u32x2*)(strip + row * RS + cc * 16 + 8);
             const int m = wrow0 + 32 * i + row, n = wcol0 + cc * 8;
             if (m < g.M && n < g.N) {
-                const int64_t orow = scatter[m];
+                const int64_t orow = kHeads ? listed_row(scatter, g.heads, m) : scatter[m];
                 if (orow >= 0) *(u32x4*)(out + orow * ld + n) = u32x4{lo[0], lo[1], hi[0], hi[1]};
             }
         }
@@ -1222,7 +1240,7 @@ int launch_cfg(const GemmDesc& d, double round, hipStream_t s) {
     Dev g;
     g.M = d.M, g.N = d.N, g.K = d.K;
     g.A = (const uint16_t*)d.A, g.A2 = (const uint16_t*)d.A2, g.B = (const uint16_t*)d.B, g.B2 = (const uint16_t*)d.B2;
-    g.lda = d.lda, g.ldb = d.ldb, g.ag = d.a_gather, g.bg = d.b_gather, g.cs = d.c_scatter;
+    g.lda = d.lda, g.ldb = d.ldb, g.ag = d.a_gather, g.bg = d.b_gather, g.cs = d.c_scatter, g.heads = d.heads;
     g.C = (uint16_t*)d.C, g.C2 = (uint16_t*)d.C2, g.C3 = (uint16_t*)d.C3, g.ldc = d.ldc;
     g.ldc3 = d.ldc3 ? d.ldc3 : d.ldc;
     g.R = (const uint16_t*)d.R, g.ldr = d.ldr;
@@ -1428,6 +1446,7 @@ struct ReduceArgs {
     uint16_t* Cb[kMaxBatch];
     int64_t ldc;
     const int32_t* cs;
+    HeadList heads;
 };
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(ReduceArgs r) {
     const int64_t per = (int64_t)r.M * (r.N / 8);
@@ -1443,7 +1462,7 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(ReduceArgs r) {
         b += *(const f32x4*)(p + 4);
     }
     uint16_t* out = z == 0 ? r.Cb[0] : (z == 1 ? r.Cb[1] : (z == 2 ? r.Cb[2] : r.Cb[3]));
-    const int64_t row = r.cs ? r.cs[m] : m;
+    const int64_t row = listed_row(r.cs, r.heads, m);
     if (row < 0) return; // dropped row
     *(u32x4*)(out + row * r.ldc + n) = u32x4{pack_bf16(a[0], a[1]), pack_bf16(a[2], a[3]), pack_bf16(b[0], b[1]), pack_bf16(b[2], b[3])};
 }
@@ -1561,7 +1580,7 @@ int gemm_mfma_bf16(const GemmDesc& d, hipStream_t s) {
         ds.ksplit = r;
         int rc = d.a_km ? launch<EPI_STORE, OP_DW_SPLIT, 3>(ds, s) : launch<EPI_STORE, OP_DW_SPLIT, 2>(ds, s);
         if (rc != SDP_OK) return rc;
-        ReduceArgs ra{(const float*)d.split_ws, r, d.nbatch, d.M, d.N, {}, d.ldc, d.c_scatter};
+        ReduceArgs ra{(const float*)d.split_ws, r, d.nbatch, d.M, d.N, {}, d.ldc, d.c_scatter, d.heads};
         for (int z = 0; z < kMaxBatch; ++z) ra.Cb[z] = (uint16_t*)d.Cb[z];
         const int64_t threads = (int64_t)d.nbatch * d.M * (d.N / 8);
         ProfileScope ps("splitk_reduce", s);

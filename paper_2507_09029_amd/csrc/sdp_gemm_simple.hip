@@ -41,6 +41,7 @@ struct Dev {
     int pc;
     const void* R; // STORE / DUAL_ACC: optional residual [M][ldr]
     int64_t ldr;
+    HeadList heads; // of ag, bg, cs
 };
 
 // rank of column n in the ascending index list, or -1 if it is not listed
@@ -76,7 +77,7 @@ __global__ __launch_bounds__(NT) void gemm_simple_kernel(Dev g) {
                     const int m = e / BK, k = e % BK;
                     float v = 0.f;
                     if (m0 + m < g.M && k0 + k < g.K) {
-                        const int64_t row = g.ag ? g.ag[m0 + m] : (m0 + m);
+                        const int64_t row = listed_row(g.ag, g.heads, m0 + m);
                         v = ld<T>(A + row * g.lda + k0 + k);
                     }
                     As[k][m] = v;
@@ -94,7 +95,7 @@ __global__ __launch_bounds__(NT) void gemm_simple_kernel(Dev g) {
                 const int n = e / BK, k = e % BK;
                 float v = 0.f, v2 = 0.f;
                 if (n0 + n < g.N && k0 + k < g.K) {
-                    const int64_t row = g.bg ? g.bg[n0 + n] : (n0 + n);
+                    const int64_t row = listed_row(g.bg, g.heads, n0 + n);
                     v = ld<T>(B + row * g.ldb + k0 + k);
                     if (kTwoB) v2 = ld<T>(B2 + row * g.ldb + k0 + k);
                 }
@@ -132,7 +133,7 @@ __global__ __launch_bounds__(NT) void gemm_simple_kernel(Dev g) {
             const int n = n0 + tn + j;
             if (n >= g.N) continue;
             if (EPI == EPI_STORE || EPI == EPI_DUAL_ACC) {
-                const int64_t row = g.cs ? g.cs[m] : m;
+                const int64_t row = listed_row(g.cs, g.heads, m);
                 if (row < 0) continue; // dropped row
                 const float r = g.R ? ld<T>((const T*)g.R + (int64_t)m * g.ldr + n) : 0.f;
                 st<T>((T*)g.C + row * g.ldc + n, acc[i][j] + r);
@@ -165,7 +166,7 @@ __global__ __launch_bounds__(NT) void gemm_simple_kernel(Dev g) {
 template <typename T, int EPI>
 int launch(const GemmDesc& d, hipStream_t s) {
     Dev g{d.M, d.N, d.K, d.A, d.A2, d.B, d.B2, d.lda, d.ldb, d.b_gather, d.c_scatter, d.a_km, d.a_gather,
-          d.C, d.C2, d.C3, d.ldc, d.ldc3 ? d.ldc3 : d.ldc, d.Gin, d.Uin, d.ldg, d.Cc, d.Cc2, d.Cc3, d.ldcc, d.cidx, d.pc, d.R, d.ldr};
+          d.C, d.C2, d.C3, d.ldc, d.ldc3 ? d.ldc3 : d.ldc, d.Gin, d.Uin, d.ldg, d.Cc, d.Cc2, d.Cc3, d.ldcc, d.cidx, d.pc, d.R, d.ldr, d.heads};
     dim3 grid((d.N + BN - 1) / BN, (d.M + BM - 1) / BM);
     ProfileScope ps(d.name, s);
     gemm_simple_kernel<T, EPI><<<grid, NT, 0, s>>>(g);

@@ -59,6 +59,29 @@ inline bool overlap(std::initializer_list<Extent> out, std::initializer_list<Ext
     return false;
 }
 
+// A list of rows may be given as a list of heads: row i is then row i % width of the (i / width)-th listed head, in the
+// (i / held)-th of up to three stacked matrices (Q | K | V).  Read where the rows are needed: a launch that expands the heads
+// first took 3 to 4 us of each attention call.
+struct HeadList {
+    int width = 0;          // rows of a head; 0 = the list holds the rows themselves
+    uint32_t magic = 0;     // 2^32 / width, rounded up: i / width = the upper half of i x magic for i x width < 2^32
+    int held = 0x7FFFFFFF;  // rows of the listed heads
+    int all = 0;            // rows of one of the stacked matrices (at most 65535 heads of 128)
+};
+inline HeadList head_list(int width, int held_heads, int all_heads) {
+    return {width, (uint32_t)((((uint64_t)1 << 32) + width - 1) / width), held_heads * width, all_heads * width};
+}
+// One form for both kinds of list, without a branch: several look-ups are then in flight together.
+__device__ inline int listed_row(const int32_t* list, const HeadList& h, int i) {
+    if (!list) return i;
+    int first = 0;
+    if (i >= h.held) i -= h.held, first += h.all;
+    if (i >= h.held) i -= h.held, first += h.all;
+    const int w = h.width ? h.width : 1;
+    const int k = h.width ? (int)__umulhi((uint32_t)i, h.magic) : i;
+    return first + list[k] * w + (i - k * w);
+}
+
 // ---- contraction descriptor --------------------------------------------------------------------
 // C[M][N] = sum_k A(m,k) * B(k,n), fp32 accumulation, all matrices row-major.
 //   A(m,k) = a_km ? A[k * lda + m] : A[ra(m) * lda + k]  (a_km: A is stored depth-major, [K][M])
@@ -127,6 +150,7 @@ struct GemmDesc {
     void* Ct2 = nullptr;
     void* Ct3 = nullptr;
     int64_t ldct = 0;
+    HeadList heads; // bf16: with width > 0, a_gather, b_gather and c_scatter are lists of heads
     const char* name = "gemm";
     // batched launch of up to kMaxBatch problems with the same shape, strides and scatter (the
     // weight-gradient contractions): nbatch > 0 selects Ab/Bb/Cb instead of A/B/C
@@ -227,6 +251,7 @@ struct TransposeJob {
     int64_t ld_in, ld_out;
     const int32_t* rows; // optional gather of input rows
     int R, C;
+    HeadList heads; // of `rows` (jobs carried by the attention core's launches only)
 };
 int transpose_batch(const TransposeJob* jobs, int n, const char* name, hipStream_t s);
 // The same jobs prepared for a launch that carries them (sdp_transpose.h): their number of 64 x 64 tiles, or -1 when

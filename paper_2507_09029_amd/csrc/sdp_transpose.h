@@ -20,7 +20,11 @@ __device__ inline TransposeJob pick_job(const TransposeJob (&j)[kMaxTransposeJob
             z0 ? j[0].ld_out : z1 ? j[1].ld_out : z2 ? j[2].ld_out : j[3].ld_out,
             z0 ? j[0].rows : z1 ? j[1].rows : z2 ? j[2].rows : j[3].rows,
             z0 ? j[0].R : z1 ? j[1].R : z2 ? j[2].R : j[3].R,
-            z0 ? j[0].C : z1 ? j[1].C : z2 ? j[2].C : j[3].C};
+            z0 ? j[0].C : z1 ? j[1].C : z2 ? j[2].C : j[3].C,
+            {z0 ? j[0].heads.width : z1 ? j[1].heads.width : z2 ? j[2].heads.width : j[3].heads.width,
+             z0 ? j[0].heads.magic : z1 ? j[1].heads.magic : z2 ? j[2].heads.magic : j[3].heads.magic,
+             z0 ? j[0].heads.held : z1 ? j[1].heads.held : z2 ? j[2].heads.held : j[3].heads.held,
+             z0 ? j[0].heads.all : z1 ? j[1].heads.all : z2 ? j[2].heads.all : j[3].heads.all}};
 }
 
 // Tile at input rows r0 .., columns c0 .. of a job.  Thread t moves rows t / 8 and t / 8 + 32, columns 8 (t % 8) ..  The
@@ -33,11 +37,13 @@ struct TransposeTile {
     typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
     int row[2];
     u32x4 v[2];
+    // HEADS: the rows may be a list of heads (the attention's; the look-up makes the MLP's carried transposes 2.4 us longer)
+    template <bool HEADS>
     __device__ void index(const TransposeJob& jb, int r0, int t) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int r = r0 + (t >> 3) + 32 * h, rc = r < jb.R ? r : jb.R - 1;
-            row[h] = jb.rows ? jb.rows[rc] : rc;
+            row[h] = HEADS ? listed_row(jb.rows, jb.heads, rc) : jb.rows ? jb.rows[rc] : rc;
         }
     }
     __device__ void load(const TransposeJob& jb, int c0, int t) {
@@ -79,7 +85,7 @@ struct SideJobs {
 
 // N tiles at once by 256 threads (t = 0 .. 255), tiles N w .. N w + N - 1 (the last tile again beyond it); lds: N x
 // kTransposeLds bytes of these threads' own.  Every thread of the workgroup has to get here (barrier).
-template <int N>
+template <int N, bool HEADS = false>
 __device__ inline void side_transposes(const SideJobs& s, int w, unsigned char* lds, int t) {
     TransposeTile tile[N];
     TransposeJob jb[N];
@@ -93,7 +99,7 @@ __device__ inline void side_transposes(const SideJobs& s, int w, unsigned char* 
         const int first = z0 ? 0 : z1 ? s.end[0] : z2 ? s.end[1] : s.end[2];
         const int tr = (jb[i].R + 63) / 64;
         r0[i] = (id - first) % tr * 64, c0[i] = (id - first) / tr * 64;
-        tile[i].index(jb[i], r0[i], t);
+        tile[i].template index<HEADS>(jb[i], r0[i], t);
     }
 #pragma unroll
     for (int i = 0; i < N; ++i) tile[i].load(jb[i], c0[i], t);

@@ -25,7 +25,7 @@ __global__ __launch_bounds__(256) void transpose_rows_vec_kernel(TransposeJob j0
     if (r0 >= jb.R || c0 >= jb.C) return;
     __shared__ __attribute__((aligned(16))) unsigned char lds[kTransposeLds];
     TransposeTile tile;
-    tile.index(jb, r0, threadIdx.x);
+    tile.index<false>(jb, r0, threadIdx.x);
     tile.load(jb, c0, threadIdx.x);
     tile.put(jb, r0, c0, lds, threadIdx.x);
     __syncthreads();
