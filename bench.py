@@ -315,7 +315,7 @@ def bench_attention(sdp, torch, steps, w=None):
                               "frac": (core_fwd + core_bwd) / (core_ms * 1e-3) / 1e12 / PEAK_BF16_TFLOPS, "traffic": None},
                  "forward_backward_tflops": (core_fwd + core_bwd) / (core_ms * 1e-3) / 1e12,
                  "note": "causal: the half of the S x S products that is computed is counted (2 S^2 hd per head forward, 5 S^2 hd backward); "
-                         "the times include the transposed copies for the contractions that follow, which the core's launches carry"},
+                         "the times include the transposed copies of WoT and Wqkv for the contractions that follow, which the core's launches carry"},
         "vendor_attention_yardstick": vendor_attention_yardstick(torch, w) if w.hd % 8 == 0 else None,
     }
 
