@@ -204,6 +204,11 @@ __device__ inline bf16x8 read_km(const unsigned char* stage, int offset, int s) 
 // direct loads in flight in front of every group of such reads (not in front of ordinary ones): 128 x 128 tiles 2 x slower, 128 x 256
 // 2.2 x.  The instruction has no output register, reads its address and M0 as it is issued, and is waited for by the loop's own
 // counts (SDP_WAIT_VMCNT), which are the same for both forms; the memory clobber keeps LDS accesses on their side of it.
+// Its hazards are met inside the block, where the compiler adds no wait states.  A scalar base that the vector unit wrote may be
+// read by a memory instruction only five wait states later, but by a scalar move at once: the load takes a copy made here.  That
+// move is also the wait state between the write of M0 and the load.  (In the place of an s_nop: no instruction more.)
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm" // M0 among the clobbers is reserved: nothing else in these kernels holds a value in it
 template <bool kAsm, bool kTail>
 __device__ __attribute__((always_inline)) inline void direct_load(const unsigned char* base, uint32_t off, bool zero, unsigned char* dst) {
     const unsigned char* src = kTail && zero ? (const unsigned char*)kZeroChunk : base + off;
@@ -217,10 +222,13 @@ __device__ __attribute__((always_inline)) inline void direct_load(const unsigned
             const uint64_t a = (uint64_t)base; // the same in all lanes
             const uint64_t u = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(a >> 32)) << 32) |
                                (uint32_t)__builtin_amdgcn_readfirstlane((int)a);
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2" ::"s"(m0), "v"(off), "s"(u) : "memory", "m0");
+            uint64_t copy;
+            asm volatile("s_mov_b32 m0, %1\n\ts_mov_b64 %0, %3\n\tglobal_load_lds_dwordx4 %2, %0"
+                         : "=&s"(copy) : "s"(m0), "v"(off), "s"(u) : "memory", "m0");
         }
     }
 }
+#pragma clang diagnostic pop
 
 template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int KM>
 struct Geometry {
