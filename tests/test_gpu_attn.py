@@ -327,7 +327,7 @@ def test_forward_output_may_take_the_place_of_its_weights(sdp, dtype, mode):
 @pytest.mark.parametrize("dtype,hd,d", [("f32", 1, 1), ("bf16", 72, 8)])
 def test_more_items_than_one_grid_axis_holds(sdp, dtype, hd, d):
     """65535 sequences of one token and 460 heads: 30 million items of the core, more workgroups of 256 threads than one axis of
-    a grid takes (bf16: and operands of 4 GiB and more, so that dX and the weight gradients run on the plain contraction).  A softmax over one key is constant, so Y = X Wv^T Wo and dX likewise, dWq = dWk = 0.  X and dY are positive:
+    a grid takes (bf16: and dQKV of 4 GiB and more, so that dX runs on the plain contraction).  A softmax over one key is constant, so Y = X Wv^T Wo and dX likewise, dWq = dWk = 0.  X and dY are positive:
     the weight gradients' sums over 65535 tokens then do not cancel, and fp32 roundings along the way (at worst one of 2^-24 for
     each of the 16384 additions to an accumulator, 1e-3; a random walk of them, 1e-5) stay below 1e-4 of the result."""
     Bt, H = 65535, 460
@@ -356,6 +356,71 @@ def test_more_items_than_one_grid_axis_holds(sdp, dtype, hd, d):
     close(gW[2], WoT.double() @ XtdY.t(), "dWv", max(tol, 1e-4))
     close(gO, Wqkv[2].double() @ XtdY, "dWoT", max(tol, 1e-4))
     assert float(gW[:2].double().abs().max()) <= 1e-5 * float(gW[2].double().abs().max())
+
+
+@pytest.mark.parametrize("mode,ph,layout", [("fm", 10923, "compact"), ("bm", 3, "scatter")])
+def test_weight_gradients_beyond_the_mfma_kernels_rows(sdp, orc, mode, ph, layout):
+    """10923 heads of 128: rows of dQKV of 2^22 elements and more, which the MFMA kernel does not read depth-major, so that the four
+    weight gradients run on the plain contraction from transposed copies (X, O, dY and dQ beside the core, dK and dV in a launch of
+    their own); with 3 of the heads held, from the listed columns to the listed rows.  Sums over 8 tokens and up to 1.1e7 elements:
+    the rounding points alone put the elementwise maxima at up to 5.0e-2 (rounding model, on the CPU), so the fixed bound is 8e-2
+    and the model-relative check (1.5 times that) is the tighter one."""
+    Bt, S, d, H, hd = 1, 8, 8, 10923, 128
+    w = AttnWorkload("plain_dw", Bt, S, d, H, hd, ph, 2, 56)
+    Wqkv, WoT = workloads.attn_weights(w)
+    X, dY = workloads.attn_batch(w, 0)
+    heads = np.arange(H) if ph == H else np.array([0, 4999, H - 1])
+    mask = np.zeros(H, np.uint8)
+    mask[heads] = 1
+    idx = torch.from_numpy(heads.astype(np.int32)).cuda()
+    dev = [t.cuda() for t in (X, dY, Wqkv, WoT)]
+    out = None
+    if layout == "scatter":
+        out = tuple(torch.full(s, float("nan"), dtype=X.dtype, device="cuda") for s in (X.shape, Wqkv.shape, WoT.shape))
+    print(f"attention backward {mode} S={S} d={d} H={H} hd={hd} ph={ph} {layout}", flush=True)
+    sdp.profile_filter(None)
+    sdp.profile_reset()
+    sdp.profile_enable(True)
+    try:
+        Y, QKV, O, LSE = sdp.masked_attn_fwd(mode, Bt, S, hd, dev[0], *dev[2:], idx)
+        dX, gWqkv, gWoT = sdp.masked_attn_bwd(mode, Bt, S, hd, *dev, idx, QKV, O, LSE, dw_layout=layout, out=out)
+        torch.cuda.synchronize()
+        launches = {name: calls for name, (calls, ms) in sdp.profile_read().items()}
+    finally:
+        sdp.profile_enable(False)
+    assert launches["attn_dw"] == 4 and launches["attn_tr_bwd"] == 1, launches
+    X, dY = workloads.to_f64(X), workloads.to_f64(dY)
+    W64 = [workloads.to_f64(Wqkv[i]) for i in range(3)] + [workloads.to_f64(WoT)]
+    ref = orc.attn_worker_step(Bt, S, hd, mask, X, dY, *W64, mode=mode)
+    model = rm.attn_model(Bt, S, hd, mask, X, dY, *W64, mode=mode)
+    assert_close_rows(workloads.to_f64(Y), ref["Y"], TOL, "Y")
+    assert_close_rows(workloads.to_f64(dX), ref["dX"], TOL, "dX")
+    rows = held_rows(heads, hd)
+    got = dict(zip(("dWq", "dWk", "dWv", "dWoT"), [*workloads.to_f64(gWqkv), workloads.to_f64(gWoT)]))
+    for name, g in got.items():
+        if layout == "scatter":
+            off = np.ones(H * hd, bool)
+            off[rows] = False
+            assert np.isnan(g[off]).all(), f"{name}: rows of heads not held must stay untouched"
+            g = g[rows]
+        assert_close_with_model(g, model[name][rows], ref[name][rows], TOL, name, elem_allow=8e-2)
+
+
+# 2051 tokens: the weight gradients' few tiles cut in depth, the last range ending in a step of 3 tokens; heads listed as heads
+# (64, 128) or as rows of padded heads (50), as columns of dQKV and O under backward masking
+@pytest.mark.parametrize("hd", [50, 64, 128])
+@pytest.mark.parametrize("mode,layout", [("fm", "scatter"), ("bm", "scatter"), ("bm", "compact")])
+def test_weight_gradients_cut_in_depth_ragged_tokens(sdp, orc, mode, layout, hd):
+    w = AttnWorkload("cut_in_depth", 1, 2051, 200, 3, hd, 2, 2, 57)
+    sdp.profile_filter(None)
+    sdp.profile_reset()
+    sdp.profile_enable(True)
+    try:
+        run_case(sdp, orc, w, [1], dw_layout=layout, mode=mode)
+        launches = {name: calls for name, (calls, ms) in sdp.profile_read().items()}
+    finally:
+        sdp.profile_enable(False)
+    assert launches["splitk_reduce"] == 1, launches
 
 
 @pytest.mark.parametrize("w", BM_CASES, ids=[w.name for w in BM_CASES])
