@@ -1562,10 +1562,15 @@ bool gemm_mfma_supported(const GemmDesc& d) {
     return true;
 }
 
+// depth ranges of a batched launch (both operands depth-major: the only kind whose callers bring the scratch)
+static int uniform_cut(const GemmDesc& d) {
+    return d.split_ws && d.a_km ? gemm_choose_ksplit(d.M, d.N, d.K, d.nbatch) : 1;
+}
+
 bool gemm_carries(const GemmDesc& d) {
     if (!gemm_mfma_supported(d)) return false;
     if (d.epilogue == EPI_SWIGLU_BWD) return would_carry<EPI_SWIGLU_BWD>(d, 1);
-    if (d.nbatch == 0 || (d.split_ws && gemm_choose_ksplit(d.M, d.N, d.K, d.nbatch) > 1)) return false;
+    if (d.nbatch == 0 || uniform_cut(d) > 1) return false;
     if (d.tail_ws && plan_tail(d, nullptr, nullptr) > 1) return false;
     return would_carry<EPI_STORE>(d, d.nbatch);
 }
@@ -1574,7 +1579,7 @@ int gemm_mfma_bf16(const GemmDesc& d, hipStream_t s) {
     if (!gemm_mfma_supported(d)) return SDP_ERR_UNSUPPORTED;
     // OP only gives every call site its own kernel symbol, so that profiles name the step
     if (d.epilogue == EPI_STORE && d.nbatch > 0) {
-        const int r = d.split_ws ? gemm_choose_ksplit(d.M, d.N, d.K, d.nbatch) : 1;
+        const int r = uniform_cut(d);
         if (r < 2 && d.tail_ws) {
             const int parts = plan_tail(d, nullptr, nullptr);
             if (parts > 1) {
@@ -1586,7 +1591,7 @@ int gemm_mfma_bf16(const GemmDesc& d, hipStream_t s) {
         if (r < 2) return d.a_km ? launch<EPI_STORE, OP_DW, 3>(d, s) : launch<EPI_STORE, OP_DW, 2>(d, s);
         GemmDesc ds = d;
         ds.ksplit = r;
-        int rc = d.a_km ? launch<EPI_STORE, OP_DW_SPLIT, 3>(ds, s) : launch<EPI_STORE, OP_DW_SPLIT, 2>(ds, s);
+        int rc = launch<EPI_STORE, OP_DW_SPLIT, 3>(ds, s);
         if (rc != SDP_OK) return rc;
         ReduceArgs ra{(const float*)d.split_ws, r, d.nbatch, d.M, d.N, {}, d.ldc, d.c_scatter, d.heads};
         for (int z = 0; z < kMaxBatch; ++z) ra.Cb[z] = (uint16_t*)d.Cb[z];

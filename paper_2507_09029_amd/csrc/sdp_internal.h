@@ -159,7 +159,7 @@ struct GemmDesc {
     int64_t ldab[4] = {0, 0, 0, 0}; // MFMA kernel, a_km: each problem's leading dimension, 0 = lda
     const void* Bb[4] = {nullptr, nullptr, nullptr, nullptr};
     void* Cb[4] = {nullptr, nullptr, nullptr, nullptr};
-    // batched launches only: optional fp32 scratch of gemm_split_ws_bytes(M, N, K, nbatch) bytes.  With it, a
+    // batched launches with a_km and b_km only: optional fp32 scratch of gemm_split_ws_bytes(M, N, K, nbatch) bytes.  With it, a
     // launch that has few tiles and a deep K cuts the depth into ranges that run as extra problems, and a second
     // kernel sums the ranges' partial results (gemm_choose_ksplit decides; 1 = no cut).
     void* split_ws = nullptr;
