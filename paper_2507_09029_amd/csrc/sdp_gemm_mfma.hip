@@ -259,6 +259,8 @@ struct Geometry {
 // tiles at a time.
 struct NoSide {};
 constexpr bool carries_side(int op) { return op == OP_GATE_UP || op == OP_DACT || op == OP_DW; }
+// the launches of the attention block, whose lists may be of heads
+constexpr bool takes_heads(int op) { return op == OP_DOWN || op == OP_DW || op == OP_DW_SPLIT; }
 template <int OP>
 using SideArg = std::conditional_t<carries_side(OP), SideJobs, NoSide>;
 // tiles each 256 threads of a workgroup take at once: as many as the contraction's LDS holds, at most 8 (64 registers)
@@ -396,8 +398,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
     // never stored.  Row-major: slab s of 1 KB holds tile rows 8 s .. 8 s + 7, lane -> row 8 s + lane / 8, stored chunk
     // position lane % 8.  Depth-major: chunk positions 64 s .. (km_chunk).
     // Row (depth-major: column) indices -> places in the stored matrix; the look-ups of a wave's slabs in flight together.
-    // kHeads: the launches of the attention block, whose lists may be of heads
-    constexpr bool kHeads = OP == OP_DOWN || OP == OP_DW || OP == OP_DW_SPLIT;
+    constexpr bool kHeads = takes_heads(OP);
     auto look_up = [&](const int32_t* list, auto& idx) __attribute__((always_inline)) {
         if (!list) return;
         if (!kHeads || g.heads.width == 0) {
@@ -1245,6 +1246,8 @@ int launch_cfg(const GemmDesc& d, double round, hipStream_t s) {
     using Geo = Geometry<BM, BN, WAVES_M, WAVES_N, EPI, KM>;
     constexpr int NTHREADS = WAVES_M * WAVES_N * 64;
     constexpr int LDS = Geo::LDS;
+    // what this kernel would leave undone or misread
+    if ((!carries_side(OP) && d.nside > 0) || (!takes_heads(OP) && d.heads.width > 0)) return SDP_ERR_INVALID_ARG;
     Dev g;
     g.M = d.M, g.N = d.N, g.K = d.K;
     g.A = (const uint16_t*)d.A, g.A2 = (const uint16_t*)d.A2, g.B = (const uint16_t*)d.B, g.B2 = (const uint16_t*)d.B2;
