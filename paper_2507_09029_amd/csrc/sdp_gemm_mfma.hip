@@ -1231,8 +1231,8 @@ int tail_reduce(const Dev& g, const GemmDesc& d, hipStream_t s) {
 }
 
 // Whether a launch of `tiles` tiles, `round` us a round, carries `wgs` workgroups of transposes: when the CUs that its last
-// round leaves idle get through them meanwhile.  A workgroup moves 16 tiles, one after the other about 5 us each and 5 more
-// for the first.  T = 5000, d = 1600, p = 2664 (28 us of transposes a worker beside 420 and 220 tiles): step of two workers
+// round leaves idle get through them meanwhile.  A workgroup moves 8 to 16 tiles (side_tiles); several of them one after the
+// other on a CU take about 5 us each and 5 more for the first.  T = 5000, d = 1600, p = 2664 (28 us of transposes a worker beside 420 and 220 tiles): step of two workers
 // 1020 -> 980 us; beside the 512 tiles of T = 8192, p = 2048, two full rounds, W2's transpose cost 12 us more than on its own.
 // W1's and W3's beside the weight gradients (144 tiles; dact has 256) at T = 1024, d = 768, p = 1024: step of two workers
 // 113.7 -> 107.1 us; four at T = 8192, d = 1536, p = 2048 (192 tiles) 1786 -> 1754.
@@ -1407,8 +1407,12 @@ int launch(const GemmDesc& d, hipStream_t s) {
     return SDP_ERR_UNSUPPORTED; // not reached: choose_shape returns one of the above
 }
 
-// Whether the launch of `d` would carry its transposes (a tile's workgroups take 16 at a time, with 128 x 128 and 64 x 64 tiles
-// 10 and 7: counted as 7).
+// Whether the launch of `d` is one to give its transposes to.  Their workgroups take 16 tiles each beside 256 x 256 and 128 x 256,
+// 14 to 16 beside 256 x 192, 12 to 16 beside 128 x 192, 10 beside 128 x 128 and 8 beside 64 x 64; 7 are counted, which asks for
+// idle CUs to spare.  Counted exactly, ten shapes whose choice between dact and dw that changes took, geometric mean, 1 % longer:
+// two workers at T = 1800, d = 888, p = 2856 (dw to dact) 356 -> 364 us, at T = 1064, d = 520, p = 1832 (the other way) 162 -> 169,
+// at T = 1064, d = 1320, F = 1520, p = 1080 under backward masking (the other way) 221 -> 215.  The launch then decides by carry
+// with its own count, and transposes that it does not take run before it.
 template <int EPI>
 bool would_carry(const GemmDesc& d, int nbatch) {
     double round = 0;
