@@ -990,6 +990,9 @@ FwdWs fwd_ws(char* w, size_t e, int d, int E, bool padded) {
     return r;
 }
 
+// whether the four weight gradients are one MFMA launch that reads dQKV, O, X and dY as they are
+bool direct_dw(int dtype, int d, int E) { return dtype == SDP_BF16 && gemm_depth_major_ld(3 * (int64_t)E) && gemm_depth_major_ld(d); }
+
 struct BwdWs {
     int32_t *rows_qkv, *rows_o;
     void *dO, *dQKV, *dQKVt, *Ot, *Xt, *dYt, *Wc, *split, *Wp, *WoP;
@@ -1007,7 +1010,7 @@ BwdWs bwd_ws(char* w, size_t e, int64_t T, int d, int E, int Eh, int64_t stats, 
     r.dO = take((size_t)T * E * e);
     r.dQKV = take((size_t)T * 3 * E * e);
     r.delta = (float*)take((size_t)stats * 4);
-    r.dQKVt = take((size_t)3 * E * ldt * e);
+    r.dQKVt = e == 2 && !direct_dw(SDP_BF16, d, E) ? take((size_t)3 * E * ldt * e) : nullptr;
     r.Ot = take((size_t)E * ldt * e);
     r.Xt = take((size_t)d * ldt * e);
     r.dYt = take((size_t)d * ldt * e);
@@ -1209,7 +1212,7 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     // computed on the mask.
     const int64_t part = (int64_t)(dw_layout == SDP_DW_SCATTER ? H * hd : ph * hd) * d; // elements of one weight gradient
     GemmDesc wg;
-    bool direct = false;
+    const bool direct = want_dw && direct_dw(dtype, d, E);
     if (dtype == SDP_BF16 && want_dw) {
         wg.name = "attn_dw";
         wg.M = Eh, wg.N = d, wg.K = T;
@@ -1228,7 +1231,6 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
             wg.Ab[i] = (const uint16_t*)w.dQKV + (int64_t)i * E, wg.Bb[i] = X, wg.Cb[i] = (uint16_t*)dWqkv + (size_t)i * part;
         wg.Ab[3] = O_save, wg.ldab[3] = E, wg.Bb[3] = dY, wg.Cb[3] = dWoT;
         wg.split_ws = w.split;
-        direct = gemm_mfma_supported(wg);
     }
 
     GemmDesc go;

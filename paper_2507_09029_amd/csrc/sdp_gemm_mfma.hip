@@ -1523,9 +1523,9 @@ bool gemm_mfma_supported(const GemmDesc& d) {
     // depth-major operands: batched launches, B or both, columns in whole chunks
     if (d.a_km || d.b_km) {
         if (d.nbatch == 0 || !d.b_km || d.b_gather || (d.a_km && (d.M % 8 || (d.a_gather && !d.a_gather_chunks)))) return false;
-        if (d.ldb >= (int64_t)1 << 22 || (d.a_km && d.lda >= (int64_t)1 << 22)) return false; // 64 rows within 32-bit offsets
+        if (!gemm_depth_major_ld(d.ldb) || (d.a_km && !gemm_depth_major_ld(d.lda))) return false;
         for (int z = 0; z < d.nbatch; ++z)
-            if (z < kMaxBatch && (d.ldab[z] % 8 || d.ldab[z] >= (int64_t)1 << 22)) return false;
+            if (z < kMaxBatch && (d.ldab[z] % 8 || !gemm_depth_major_ld(d.ldab[z]))) return false;
     } else if (d.nbatch > 0) {
         return false;
     }

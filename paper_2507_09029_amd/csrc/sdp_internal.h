@@ -190,6 +190,8 @@ int gemm_simple(const GemmDesc& g, hipStream_t s);
 // bf16 MFMA contraction; returns SDP_ERR_UNSUPPORTED when the shape / alignment does not fit.
 int gemm_mfma_bf16(const GemmDesc& g, hipStream_t s);
 bool gemm_mfma_supported(const GemmDesc& g);
+// rows that the MFMA contraction can read depth-major: 64 of them lie within 32-bit byte offsets
+inline bool gemm_depth_major_ld(int64_t ld) { return ld < (int64_t)1 << 22; }
 // whether the launch of g (SWIGLU_BWD, or batched without a depth cut) would carry g.side
 bool gemm_carries(const GemmDesc& g);
 // depth ranges a batched launch of nbatch problems of shape M x N x K would be cut into, and the scratch that takes

@@ -175,6 +175,19 @@ def test_binding_module_does_not_touch_the_oracle():
     assert "oracle" not in src
 
 
+def test_attention_backward_workspace_holds_what_the_call_uses():
+    """bf16: dO, dQKV, room for copies of O, X and dY, Wqkv's transpose, delta and the partial sums of a cut in 2; a transposed dQKV
+    ([3E][T]) only where its rows have 2^22 elements or more, which the weight-gradient launch cannot read as they are."""
+    L = sdp.lib()
+    Bt, S, d, H, hd, ph = 4, 2048, 1536, 24, 64, 12
+    T, E = Bt * S, ph * hd
+    ldt, ldw = T + 64, 3 * E + 64  # token and weight rows, to an odd number of 64s
+    used = 2 * (4 * T * E + (E + 2 * d) * ldt + d * ldw) + 4 * (4 * E + Bt * ph * S + 2 * 4 * E * d)
+    assert used - 64 * 1024 <= L.sdp_masked_attn_bwd_workspace_bytes(binding.MASK_FORWARD, 1, Bt, S, d, H, hd, ph) <= used + 64 * 1024
+    H = 10923
+    assert L.sdp_masked_attn_bwd_workspace_bytes(binding.MASK_FORWARD, 1, 1, 8, 8, H, 128, H) >= 2 * 3 * H * 128 * 72
+
+
 def test_attention_arguments_are_checked_on_the_host():
     import torch
 
