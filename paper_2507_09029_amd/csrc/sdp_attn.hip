@@ -898,8 +898,9 @@ __global__ void head_rows_kernel(const int32_t* __restrict__ head_idx, int ph, i
     if (part == 0) rows_o[rem] = row;
 }
 
-// Token-contiguous copies: T tokens, zeros up to the next multiple of 8 (so that a depth of ragged T is whole 16-byte
-// chunks), and 64 more (see the MLP path: rows must not sit a power of two apart).
+// Token-contiguous copies, for the plain weight gradients: T tokens, zeros up to the next multiple of 8, and 64 more (see the
+// MLP path: rows must not sit a power of two apart).  The room for those of O, X and dY also takes copies of them as they are,
+// where an output overwrites them.
 int64_t depth_tokens(int64_t T) { return (T + 7) / 8 * 8; }
 int64_t ld_tokens(int64_t T, int d, int E) { return line_ld(depth_tokens(T) + 64, d > 3 * E ? d : 3 * E); }
 
@@ -1207,7 +1208,8 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     // bf16: the four weight gradients share one shape (Eh x d, depth T): dWq, dWk, dWv from the three column blocks of dQKV and
     // X, dWoT from O and dY; one batched launch fills the CUs four times better than four would, and reads all of these as
     // they are stored, depth-major.  (With token-contiguous copies, made beside the core and, of dK and dV, in a launch of their
-    // own: block of 4 x 2048 tokens, 12 of 24 heads of 64 432 us, this way 398; 12 of 24 heads of 50, backward masking 666, 610.)
+    // own: block of 4 x 2048 tokens, 12 of 24 heads of 64 432 us, this way 398; 12 of 24 heads of 50, backward masking 666, 610;
+    // both ways on one box, of which others are up to 5 % slower.)
     // Under backward masking the blocks hold all heads and the launch reads the held heads' columns only: the gradient is
     // computed on the mask.
     const int64_t part = (int64_t)(dw_layout == SDP_DW_SCATTER ? H * hd : ph * hd) * d; // elements of one weight gradient
@@ -1275,7 +1277,7 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     const int32_t* w_rows = gathered ? w.rows_qkv : nullptr;
     if (dtype == SDP_F32) {
         // What follows reads Wqkv, X, dY and O_save as they are; where an output takes the place of one of these (dX over dY, a
-        // gradient over its weights), copies of them, as the bf16 path always does.
+        // gradient over its weights), copies of them.
         const size_t tok_b = (size_t)T * d * 4, dw_b = (size_t)part * 4;
         const Extent x{X, tok_b}, dy{dY, tok_b}, o{O_save, (size_t)T * E * 4}, wq{Wqkv, (size_t)3 * H * hd * d * 4}, ox{dX, tok_b};
         if (want_dw ? overlap({ox, {dWqkv, 3 * dw_b}, {dWoT, dw_b}}, {x, dy, o, wq}) : overlap({ox}, {wq})) {

@@ -10,8 +10,8 @@
 //     block's parameters get no gradient (one 16-byte-wide copy each way; nothing else runs)
 //   backward masking (m_fwd = 1, m_bwd = m):   the forward pass always runs the block;  m = 1 the dense backward
 //     pass;  m = 0 the block's weight gradients are not computed, and dX is either carried through the block
-//     (dX_RULE_THROUGH: dact, dX contractions and the attention core's backward run, no weight-gradient launch,
-//     none of the transposed copies that only feed it) or through the skip connection alone (dX_RULE_SKIP)
+//     (dX_RULE_THROUGH: dact, dX contractions and the attention core's backward run, no weight-gradient launch and
+//     no tensor that only it reads) or through the skip connection alone (dX_RULE_SKIP)
 #include "sdp_internal.h"
 
 namespace {

@@ -121,8 +121,8 @@ __device__ inline float hi_bf16(uint32_t w) { return __uint_as_float(w & 0xFFFF0
 // source of the chunks that lie beyond the depth of the matrices in a partial last step
 __device__ __attribute__((aligned(256))) const uint32_t kZeroChunk[64] = {0};
 
-// Tile order of a batched launch whose problems share B operands (the weight gradients: dG^T and dU^T against
-// X^T, Act^T against dY^T).  Problems that share B are stacked into one matrix of (problems x tiles_m)
+// Tile order of a batched launch whose problems share B operands (the weight gradients: dG and dU against X, Act against
+// dY).  Problems that share B are stacked into one matrix of (problems x tiles_m)
 // tile-rows, and each such stack is walked like a single problem: group_m tile-rows at a time, down the rows
 // first, then along the tile-columns.  The tiles that run together on one XCD then touch fewer distinct operand
 // rows than with the problems interleaved tile by tile.  Per depth range (ksplit > 1: OP_DW_SPLIT) there are two
@@ -161,9 +161,9 @@ __host__ __device__ inline int tail_position(int q, int ntiles, int n_head) {
     return x * base + (x < rem ? x : rem) + jh + i;
 }
 
-// s_waitcnt vmcnt(n) alone (expcnt / lgkmcnt left at their maxima), gfx9 encoding
 // s_waitcnt lgkmcnt(0) alone: this wave's LDS reads have returned
 #define SDP_WAIT_LGKMCNT0() __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14))
+// s_waitcnt vmcnt(n) alone (expcnt / lgkmcnt left at their maxima), gfx9 encoding
 #define SDP_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 15) | (7 << 4) | (15 << 8) | (((n) >> 4) << 14))
 
 // ---- depth-major operands: LDS stage [64 depth rows][COLS columns], rows without gaps, in granules of 16 columns (32 bytes).
@@ -238,8 +238,8 @@ struct Geometry {
     static constexpr int A_BYTES = BM * BK * 2, B_BYTES = BN * BK * 2;
     static constexpr bool kWaveDepth = BM == 64; // each wave runs its own depth steps on the whole tile (see the loop)
     // fragments read a half step ahead, one barrier a step (see the loop).  With both operands depth-major also the 256 x 192
-    // tile, whose reads are twice as many there: 2048 x 1536 outputs x 3, 8192 deep 170 -> 162 us; 256 x 256 no faster (135 us
-    // both ways at 2664 x 1600 x 3, 5000 deep) and short of registers
+    // tile, whose reads are twice as many there: 2048 x 1536 outputs x 3, 8192 deep 170 -> 162 us (the one shape it was timed
+    // at); 256 x 256 no faster (135 us both ways at 2664 x 1600 x 3, 5000 deep) and short of registers
     static constexpr bool kPipe = BM == 128 || (KM == 3 && BN == 192);
     static constexpr int A_STAGES = BM == 128 ? 3 : 2; // LDS stages of A; B has three
     // kWaveDepth: two stages of both operands per wave
@@ -1343,9 +1343,15 @@ int launch_cfg(const GemmDesc& d, double round, hipStream_t s) {
 
 // Tile shapes (rows x columns), and what each costs: a workgroup takes step0 us a depth step on an otherwise idle chip and
 // step1 us with all CUs at work, plus an epilogue of e0 us and e1 us per 1024 outputs that depends on what it moves; the
-// launch takes as many such rounds as its tiles need on 256 CUs.  Fitted to 75 contractions of 15 MLP and attention
-// shapes (128 to 8192 rows, depths of 128 to 8192), each timed at every shape, and the 128-row tiles again, for the loop they
-// have now, to the launches of seven of them (depths of 512 to 8192): of these the choice is the fastest or within 6 % of it.
+// launch takes as many such rounds as its tiles need on 256 CUs.  The 256-row tiles and 64 x 64 are fitted to 75 contractions
+// of 15 MLP and attention shapes (128 to 8192 rows, depths of 128 to 8192) with row-major operands, each timed at every shape;
+// the 128-row tiles and the SwiGLU backward's epilogue, for their present loop and stores under forward masking, to the launches
+// of seven of these shapes (depths of 512 to 8192), where the choice is the fastest or within 6 % of it.  What the model does
+// not know: depth-major operands, whose steps cost the same here though both at once take a tenth longer (256 x 192, 8192
+// deep: 162 us against 147); the neuron-major stores of the SwiGLU backward; and the cut of a last round (plan_tail), which it
+// prices as a whole one: 128-row tiles in whole rounds may then win over 256-row tiles with a cut round that would be faster
+// (3976 x 1984 x 3, 15488 deep under backward masking: 652 us as chosen, 554 with 256 x 256 and their reduction, when the tokens
+// were copied first; 4096 x 1536 x 3, 8192 deep 298 and 281; but 3944 x 1504 x 3, 9120 deep 343 and 365).
 // The smaller shapes buy idle CUs at more L2 -> LDS traffic per flop: 4096 x 1200
 // outputs, depth 3200: 57, 47, 41, 35, 46, 60 us in the order below; 8192 x 1536, depth 2048: 46, 44, 54, 49, 53, 94;
 // 1500 x 1024, depth 1536: 29, 24, 19, 15, 12, 15.

@@ -35,11 +35,11 @@ inline int launch_status() { return hip_status(hipGetLastError()); }
 inline bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
 inline size_t round_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
-// Leading dimension of `rows` rows of `min` bf16 elements that a contraction reads from the workspace: an odd number of whole
-// 128-byte lines (odd, so that rows are not 2^k bytes
-// apart, which fall onto the same memory channels), so that the 128 bytes that a depth step takes of a row are one line and not two (5000 x 1600 outputs, 2664 deep, rows of
-// 5328 / 5376 bytes: 48.1 / 40.2 us; 5328 x 1600, 5000 deep, rows of 10128 / 10112 bytes: 98.7 / 83.1 us), unless that
-// takes the matrix out of the MFMA contraction's 4 GiB.
+// Leading dimension of `rows` rows of `min` bf16 elements that a contraction reads from the workspace: whole 128-byte lines, so
+// that the 128 bytes that a depth step takes of a row are one line and not two (5000 x 1600 outputs, 2664 deep, rows of
+// 5328 / 5376 bytes: 48.1 / 40.2 us; 5328 x 1600, 5000 deep, rows of 10128 / 10112 bytes: 98.7 / 83.1 us), and an odd number of
+// them, since rows 2^k bytes apart fall onto the same memory channels; unless that takes the matrix out of the MFMA
+// contraction's 4 GiB.
 inline int64_t line_ld(int64_t min, int64_t rows) {
     const int64_t ld = (min + 63) / 64 * 64 | 64;
     return rows * ld * 2 < ((int64_t)1 << 32) ? ld : min;
@@ -166,11 +166,11 @@ struct GemmDesc {
     int ksplit = 1; // set by gemm_mfma_bf16
     // batched launches only: optional fp32 scratch of gemm_tail_ws_bytes(M, N, K, nbatch) bytes.  With it, a launch
     // whose tiles fill the CUs more than once but leave the last round partly empty cuts the depth of that last
-    // round's tiles into ranges (gemm_choose_tail), which a second small kernel adds up.
+    // round's tiles into ranges (plan_tail in sdp_gemm_mfma.hip), which a second small kernel adds up.
     void* tail_ws = nullptr;
     const char* tail_name = "dw_tail_reduce"; // profile name of that second kernel
-    // SWIGLU_FWD / SWIGLU_BWD and batched launches without a depth cut, MFMA kernel: transposes that have to be done when the contraction is, by extra workgroups of
-    // its launch or by one of their own before it
+    // SWIGLU_FWD / SWIGLU_BWD and batched launches without a depth cut, MFMA kernel: transposes that have to be done when the
+    // contraction is, by extra workgroups of its launch or by one of their own before it
     const struct TransposeJob* side = nullptr;
     int nside = 0;
     const char* side_name = "transposes";
@@ -223,7 +223,7 @@ int attn_f32_bwd(const AttnCoreDesc& c, hipStream_t s);
 // As sdp_masked_mlp_fwd / _bwd and sdp_masked_attn_fwd / _bwd after argument checks, plus:
 //   residual     [T][d] or null: added to the output Y (forward) in the contraction's epilogue
 //   dx_residual  [T][d] or null: added to dX likewise (the gradient that arrives over the skip connection)
-//   want_dw      false: the weight gradients and everything only they need (transposed copies) are left out
+//   want_dw      false: the weight gradients and everything only they need (Act, dG^T, dU^T, Act^T, copies) are left out
 //   idx_k / head_idx_k null (forward masking with p = F; backward masking of heads): every neuron / head, in order
 int mlp_fwd_impl(int mode, int dtype, int T, int d, int F, int p, const void* X, const void* W1, const void* W3,
                  const void* W2T, const int32_t* idx_k, void* Y, void* G_save, void* U_save, const void* residual,

@@ -22,8 +22,9 @@
 // Under backward masking the weight-gradient contraction reads only the p kept rows: the gradient is
 // computed on the worker's mask and nowhere else.  fp32 tensors take the fp32 contraction, which reads every
 // operand as it is stored (the weights depth-major through the worker's list, dG, dU, Act depth-major on its
-// columns): no copies, four launches (five where dX and the weight gradients are not one).  bf16 operands beyond the MFMA kernel's address range go through the plain
-// kernel, which reads dG, dU, Act depth-major (and, under backward masking, their column-compacted copies [T][p]).
+// columns): no copies, four launches (five where dX and the weight gradients are not one).  bf16 operands beyond the MFMA
+// kernel's address range go through the plain kernel, which reads dG, dU, Act depth-major (and, under backward masking, their
+// column-compacted copies [T][p]) and X, dY from transposed copies.
 #include "sdp_internal.h"
 
 namespace {
@@ -34,9 +35,10 @@ size_t esize(int dtype) { return dtype == SDP_F32 ? 4 : 2; }
 
 // Leading dimensions in the workspace.  Rows of n: Act, dG, dU [T][..], W1c, W2c, W3c [d][..] (fp32 reads them as they come).
 int64_t ld_neurons(int dtype, int T, int d, int n) { return dtype == SDP_BF16 ? line_ld(n, T > d ? T : d) : n; }
-// Token-contiguous copies X^T, dY^T [d][T], dG^T, dU^T, Act^T [p][T]: 64 elements more, so that consecutive rows do not sit a
-// power of two apart (rows 2^k bytes apart fall onto the same memory channels, and a depth step touches one 128-byte piece
-// of each of 192-256 rows).
+// Token-contiguous dG^T, dU^T, Act^T [p][T] (backward masking) and X^T, dY^T [d][T] (plain weight gradients; the same room takes
+// copies of X and dY where a gradient overwrites them): 64 elements more, so that consecutive rows do not sit a power of two
+// apart (rows 2^k bytes apart fall onto the same memory channels, and a depth step touches one 128-byte piece of each of
+// 192-256 rows).
 int64_t ld_tokens(int T, int d, int p) { return line_ld((int64_t)T + 64, d > p ? d : p); }
 
 int check_common(int mode, int dtype, int T, int d, int F, int p) {
@@ -230,7 +232,7 @@ int sdp::mlp_bwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
         rc = gemm_f32(da, s);
         if (rc != SDP_OK) return rc;
         // dX and the weight gradients read X, dY, W1 and W3 as they are.  Where an output takes the place of one of these (dX
-        // over dY, a gradient over its weights), they read copies, as the bf16 path always does.
+        // over dY, a gradient over its weights), they read copies.
         const size_t tok_b = (size_t)T * d * e, w_b = (size_t)F * d * e;
         const size_t dw_b = (size_t)(dw_layout == SDP_DW_SCATTER ? F : p) * d * e;
         const Extent x{X, tok_b}, dy{dY, tok_b}, w1{W1, w_b}, w3{W3, w_b}, ox{dX, tok_b};

@@ -1,7 +1,7 @@
-// (Gathered) matrix transpose: out[c][r] = in[rows[r]][c].  HBM-bound helper of the masked MLP:
-// it materialises a worker's compact weights in depth-contiguous orientation (W2T[S]^T, W1[S]^T,
-// W3[S]^T, each [d][p]) and the token-contiguous copies X^T, dY^T [d][T] that the weight-gradient
-// contractions read, so that every MFMA operand tile can be read from LDS with plain 16-byte reads.
+// (Gathered) matrix transpose: out[c][r] = in[rows[r]][c].  HBM-bound helper of the bf16 contractions that read both operands
+// along the depth: a worker's weights for down and dX (W2T[S]^T, W1[S]^T, W3[S]^T, each [d][n]; WoT[S]^T and Wqkv[S]^T of the
+// attention block), and the token-contiguous copies that the plain weight gradients read (the MFMA ones take their operands
+// as they are stored).
 //
 // 16-bit elements; 64 x 64 element tiles through LDS (padded rows), 256 threads (sdp_transpose.h).  Bytes moved: R*C
 // element reads + R*C element writes, nothing else.
