@@ -2,7 +2,7 @@
 
 The written-out direct loads (sdp_gemm_mfma.hip: direct_load) are out of the compiler's sight, which therefore adds no wait states
 for them.  Two hazards apply: a scalar register that the vector unit wrote may be read by a memory instruction only five wait
-states later, M0 by a load to LDS one instruction after a scalar move.  Each such load must stand behind
+states later, M0 by a load to LDS one instruction after a scalar move.  Each such load from a scalar base must stand behind
     s_mov_b32 m0, ..
     s_mov_b64 <its scalar base>, ..
 and the move's source may come from wherever it likes (the scalar unit waits for the vector unit by itself)."""
