@@ -47,18 +47,19 @@ constexpr int HD = 64;              // narrowest width of the MFMA core
 // then start 4 (an odd multiple of 4) banks apart, so the 16 lanes that a ds_read_b128 serves together hit every bank once.
 constexpr int row_bytes(int hw) { return hw * 2 + 16; }
 constexpr float kSlack = 8.f;      // forward: how far a query's maximum may run ahead of its reference exponent
-constexpr int NW = 4;               // waves per workgroup
+constexpr int NW = 4;               // waves per workgroup of the KW = 1 form
 
-// A workgroup's four waves share out the work in one of two ways (KW = waves along the walked axis):
+// A workgroup's waves share out the work in one of two ways (KW = waves along the walked axis):
 //   KW = 1: four blocks of 32 rows (queries, or keys in the dK/dV kernel), every wave walks all tiles of the other axis.
 //           The tiles are staged once for the workgroup.
-//   KW = 4: one block of 32 rows; wave w walks the 32-row tiles w, w + 4, ... of the other axis, which it stages for
-//           itself (no barrier in the loop), and the four partial results are added at the end through LDS.  Four times
-//           the workgroups with a quarter of the chain each, for four times the reads of the other axis.
+//   KW = 4, 8: one block of 32 rows; wave w walks the 32-row tiles w, w + KW, ... of the other axis, which it stages for
+//           itself (no barrier in the loop), and the partial results are added at the end through LDS.  Four times
+//           the workgroups with a quarter (an eighth) of the chain each, for four times the reads of the other axis.
 template <int KW>
 struct Split {
-    static_assert(KW == 1 || KW == NW, "all waves on one axis");
+    static_assert(KW == 1 || KW == 4 || KW == 8, "all waves on one axis");
     static constexpr int ROWS = KW == 1 ? 32 * NW : 32; // rows per workgroup
+    static constexpr int THREADS = 64 * (KW == 1 ? NW : KW);
 };
 
 // Heads wider than 64 take the probabilities (and their gradients) into the second products as two bf16 terms, value =
@@ -222,13 +223,13 @@ __device__ inline uint32_t bad_rows(bool bad) {
 // 2^x for x <= 0 (or -inf): the hardware instruction alone; results below the normal range may flush to zero
 __device__ inline float exp2_neg(float x) { return __builtin_amdgcn_exp2f(x); }
 
-// KW = 4: LDS of one wave, its two 32-row tiles and 64 statistics; after the loop its partial result, 32 rows of HW
+// KW > 1: LDS of one wave, its two 32-row tiles and 64 statistics; after the loop its partial result, 32 rows of HW
 // floats (rows 16 bytes longer, so that both the writes by row and the reads along a row hit every bank), and the statistics.
 constexpr int wave_lds(int hw) { return 64 * row_bytes(hw) + 256; }
 constexpr int part_row(int hw) { return hw + 4; }
 static_assert(32 * part_row(HD) * 4 + 256 <= wave_lds(HD) && 32 * part_row(128) * 4 + 256 <= wave_lds(128), "fits the tiles");
 
-// KW = 4: one flag per row of the workgroup's block, in what a wave's LDS has left beyond its partial result and statistics:
+// KW > 1: one flag per row of the workgroup's block, in what a wave's LDS has left beyond its partial result and statistics:
 // set where store_parts met a value that is not finite.
 constexpr int FLAGS = 32 * 4;
 static_assert(32 * part_row(96) * 4 + 256 + FLAGS <= wave_lds(96) && 32 * part_row(128) * 4 + 256 + FLAGS <= wave_lds(128), "fits the tiles");
@@ -248,16 +249,18 @@ __device__ inline void put_part(unsigned char* mine, const f32x16 (&acc)[HW / 32
 
 // sum over the waves of f[w] x partial result, as bf16 rows of `out` (row0 + 0 .. 31, those below S); weights(row, f)
 // fills f.  Columns from hd on are left alone.  Rows with a value that is not finite are flagged (rows_again).
-template <int HW, class W>
+template <int HW, int KW, class W>
 __device__ inline void store_parts(unsigned char* lds, uint16_t* out, int64_t ld, int row0, int S, int hd, int tid, W weights) {
+    constexpr int PIECES = 32 * HW / 4, THREADS = Split<KW>::THREADS;
 #pragma unroll
-    for (int i = 0; i < HW / 32; ++i) {
-        const int e = tid + 256 * i, row = e / (HW / 4), c = e % (HW / 4) * 4;
-        float f[NW];
+    for (int i = 0; i < (PIECES + THREADS - 1) / THREADS; ++i) {
+        const int e = tid + THREADS * i, row = e / (HW / 4), c = e % (HW / 4) * 4;
+        if (PIECES % THREADS != 0 && e >= PIECES) break;
+        float f[KW];
         weights(row, f);
         f32x4 v = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int w = 0; w < NW; ++w) {
+        for (int w = 0; w < KW; ++w) {
             const f32x4 x = *(const f32x4*)((const float*)(lds + w * wave_lds(HW)) + row * part_row(HW) + c);
 #pragma unroll
             for (int r = 0; r < 4; ++r) v[r] = __builtin_fmaf(x[r], f[w], v[r]);
@@ -271,12 +274,13 @@ __device__ inline void store_parts(unsigned char* lds, uint16_t* out, int64_t ld
 }
 
 // The rows to compute again, each by one wave: `again` holds a wave's own rows (KW = 1), or the flags in LDS say which
-// (KW = 4; called by all waves, after store_parts).
+// (KW > 1; called by all waves, after store_parts).
 template <int HW, int KW, class F>
 __device__ inline void each_row_again(unsigned char* lds, uint32_t again, int wave, int lane, F f) {
     if constexpr (KW != 1) {
         __syncthreads(); // the flags, and the values that these replace
-        again = (uint32_t)__builtin_amdgcn_ballot_w64(lane < 32 && row_flags<HW>(lds)[lane & 31] != 0) & (0x11111111u << wave);
+        again = (uint32_t)__builtin_amdgcn_ballot_w64(lane < 32 && row_flags<HW>(lds)[lane & 31] != 0) &
+                ((KW == 4 ? 0x11111111u : 0x01010101u) << wave);
     }
     while (again) {
         f(__builtin_ctz(again));
@@ -284,14 +288,19 @@ __device__ inline void each_row_again(unsigned char* lds, uint32_t again, int wa
     }
 }
 
+// Whether a wave fetches a tile beyond its last one rather than branch around the fetch.  KW > 1: the partial results' barrier
+// waits for that tile.  Heads of 96, with the branch: 2 x 512 to 1 x 2048 tokens, 8 heads 1.5 to 5 us of 86 to 194 less; heads of
+// 128, KW = 4: 1 to 1.5 us of 84 to 148; but KW = 8, which has no register to spare, 1 us more, and heads of 64 the same.
+constexpr bool always_fetch(int hw, int kw) { return kw == 1 || hw == HD || (hw == 128 && kw == 8); }
+
 // ---------------------------------------------------------------------------------------------------
 // Forward.  A wave keeps a block of 32 queries as register operands and walks key/value tiles up to the diagonal.
 // KW = 1: tiles of 64 keys, double-buffered in LDS (one barrier per tile): while tile t is used, tile t + 1 moves from
-// registers into the other buffer and tile t + 2 is fetched from memory.  KW = 4: the wave's own tiles of 32 keys,
+// registers into the other buffer and tile t + 2 is fetched from memory.  KW > 1: the wave's own tiles of 32 keys,
 // single-buffered; the next one is in flight in registers.
 // ---------------------------------------------------------------------------------------------------
 template <int HW, int KW>
-constexpr int fwd_lds() { return KW == 1 ? 4 * 64 * row_bytes(HW) : NW * wave_lds(HW); }
+constexpr int fwd_lds() { return KW == 1 ? 4 * 64 * row_bytes(HW) : KW * wave_lds(HW); }
 
 template <int HW, int KW>
 __device__ inline void attn_fwd_block(const CoreArgs& a, const int q0, const int head, const int b, unsigned char* lds) {
@@ -314,7 +323,7 @@ __device__ inline void attn_fwd_block(const CoreArgs& a, const int q0, const int
     const int kv_end = q0 + Split<KW>::ROWS < S ? q0 + Split<KW>::ROWS : S;
     const int ntiles = kv_end > first ? (kv_end - first + step - 1) / step : 0;
     f32x16 acc[JB];
-    // KW = 4: a wave's first tile may hold no key of some queries; the reference then starts from the lowest finite value
+    // KW > 1: a wave's first tile may hold no key of some queries; the reference then starts from the lowest finite value
     float m = KW == 1 ? -INFINITY : -3.402823466e38f, lsum = 0.f;
 #pragma unroll
     for (int j = 0; j < JB; ++j)
@@ -327,8 +336,8 @@ __device__ inline void attn_fwd_block(const CoreArgs& a, const int q0, const int
     const uint32_t ld = (uint32_t)a.ldq;
     pk.fetch(gK, ld, first, S - 1, hd, mt);
     pv.fetch(gV, ld, first, S - 1, hd, mt);
-    // fetches and stashes run unconditionally (rows are clamped, and a tile beyond the last one is never
-    // read): no branch, hence no register copies, around the loop-carried pieces
+    // fetches and stashes run unconditionally where always_fetch says so (rows are clamped, and a tile beyond the last one is
+    // never read): no branch, hence no register copies, around the loop-carried pieces
     if constexpr (KW == 1) {
         pk.stash(lds, hd, mt);
         pv.stash(lds + 2 * TILE, hd, mt);
@@ -349,8 +358,10 @@ __device__ inline void attn_fwd_block(const CoreArgs& a, const int q0, const int
             tK = mine, tV = mine + TILE;
             pk.stash(mine, hd, mt);
             pv.stash(mine + TILE, hd, mt);
-            pk.fetch(gK, ld, first + step * (t + 1), S - 1, hd, mt);
-            pv.fetch(gV, ld, first + step * (t + 1), S - 1, hd, mt);
+            if (always_fetch(HW, KW) || t + 1 < ntiles) {
+                pk.fetch(gK, ld, first + step * (t + 1), S - 1, hd, mt);
+                pv.fetch(gV, ld, first + step * (t + 1), S - 1, hd, mt);
+            }
             wave_sync();
         }
         const int kv0 = first + step * t;
@@ -455,25 +466,25 @@ __device__ inline void attn_fwd_block(const CoreArgs& a, const int q0, const int
         ((float*)(mine + STAT))[lane] = lhi == 0 ? m : l;
         if (rows_again(HW) && tid < 32) row_flags<HW>(lds)[tid] = 0;
         __syncthreads();
-        store_parts<HW>(lds, out, a.ldo, q0, S, hd, tid, [&](int row, float (&f)[NW]) {
+        store_parts<HW, KW>(lds, out, a.ldo, q0, S, hd, tid, [&](int row, float (&f)[KW]) {
             float top = -INFINITY, sum = 0.f;
 #pragma unroll
-            for (int w = 0; w < NW; ++w) top = fmaxf(top, ((const float*)(lds + w * wave_lds(HW) + STAT))[row]);
+            for (int w = 0; w < KW; ++w) top = fmaxf(top, ((const float*)(lds + w * wave_lds(HW) + STAT))[row]);
 #pragma unroll
-            for (int w = 0; w < NW; ++w) {
+            for (int w = 0; w < KW; ++w) {
                 const float* st = (const float*)(lds + w * wave_lds(HW) + STAT);
                 f[w] = exp2_neg(st[row] - top);
                 sum = __builtin_fmaf(f[w], st[32 + row], sum);
             }
 #pragma unroll
-            for (int w = 0; w < NW; ++w) f[w] /= sum;
+            for (int w = 0; w < KW; ++w) f[w] /= sum;
         });
         if (tid < 32 && q0 + tid < S) {
             float top = -INFINITY, sum = 0.f;
 #pragma unroll
-            for (int w = 0; w < NW; ++w) top = fmaxf(top, ((const float*)(lds + w * wave_lds(HW) + STAT))[tid]);
+            for (int w = 0; w < KW; ++w) top = fmaxf(top, ((const float*)(lds + w * wave_lds(HW) + STAT))[tid]);
 #pragma unroll
-            for (int w = 0; w < NW; ++w) {
+            for (int w = 0; w < KW; ++w) {
                 const float* st = (const float*)(lds + w * wave_lds(HW) + STAT);
                 sum = __builtin_fmaf(exp2_neg(st[tid] - top), st[32 + tid], sum);
             }
@@ -517,25 +528,27 @@ __device__ inline int workgroup_id() { return (int)(blockIdx.y * kGridRow + bloc
 inline dim3 workgroup_grid(int64_t n) {
     return n < 2 * kGridRow ? dim3((unsigned)n) : dim3(kGridRow, (unsigned)((n + kGridRow - 1) / kGridRow));
 }
-template <int LDS>
+template <int LDS, int THREADS>
 __device__ inline void carried(const SideJobs& side, int w, unsigned char* lds) {
-    constexpr int PER = side_tiles(LDS);
-    if (w < (side.end[kMaxTransposeJobs - 1] + PER - 1) / PER) side_transposes<PER, true>(side, w, lds, threadIdx.x);
+    constexpr int HALVES = THREADS / 256, PER = side_tiles(LDS / HALVES), ALL = PER * HALVES;
+    if (w >= (side.end[kMaxTransposeJobs - 1] + ALL - 1) / ALL) return;
+    const int half = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
+    side_transposes<PER, true>(side, w * HALVES + half, lds + half * PER * kTransposeLds, threadIdx.x & 255);
 }
 
 // waves per SIMD the registers are allotted for.  KW = 1, heads of 64: 3 beat 2 (86 -> 77 us at 4 x 2048 tokens, 12 heads)
-// and 4 spill.  KW = 4 has a workgroup per CU or less, and the wide heads then take the registers of one or two waves.
+// and 4 spill.  KW = 4: the wide heads take the registers of one or two waves.
 constexpr int waves_fwd(int hw, int kw) { return kw == 1 ? (hw == HD ? 3 : 2) : 2; }
-constexpr int waves_dq(int hw, int kw) { return kw == 1 ? (hw == HD ? 3 : 2) : (hw == HD ? 2 : 1); }
-constexpr int waves_dkv(int hw, int kw) { return kw == 1 || hw == HD ? 2 : 1; }
+constexpr int waves_dq(int hw, int kw) { return kw == 1 ? (hw == HD ? 3 : 2) : (kw == 8 || hw == HD ? 2 : 1); }
+constexpr int waves_dkv(int hw, int kw) { return kw != 4 || hw == HD ? 2 : 1; }
 
 template <int HW, int KW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(waves_fwd(HW, KW), waves_fwd(HW, KW))))
+__global__ __launch_bounds__(Split<KW>::THREADS) __attribute__((amdgpu_waves_per_eu(waves_fwd(HW, KW), waves_fwd(HW, KW))))
 void attn_fwd_kernel(CoreArgs a, int nblocks, int nbh, SideJobs side) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[fwd_lds<HW, KW>()];
     const int nitems = nblocks * nbh;
     const int id = workgroup_id();
-    if (id >= nitems) return carried<sizeof(lds)>(side, id - nitems, lds);
+    if (id >= nitems) return carried<sizeof(lds), Split<KW>::THREADS>(side, id - nitems, lds);
     int blk, head, b;
     causal_item(id, nitems, nbh, nblocks, a.ph, blk, head, b);
     attn_fwd_block<HW, KW>(a, blk * Split<KW>::ROWS, head, b, lds);
@@ -547,7 +560,7 @@ void attn_fwd_kernel(CoreArgs a, int nblocks, int nbh, SideJobs side) {
 //   dP[q][k] = dO[q] . V[k];  dZ = P (dP - delta[q]);  dQ[q] = scale sum_k dZ[q][k] K[k]
 // ---------------------------------------------------------------------------------------------------
 template <int HW, int KW>
-constexpr int dq_lds() { return KW == 1 ? 2 * 64 * row_bytes(HW) : NW * wave_lds(HW); }
+constexpr int dq_lds() { return KW == 1 ? 2 * 64 * row_bytes(HW) : KW * wave_lds(HW); }
 
 template <int HW, int KW>
 __device__ inline void attn_bwd_dq_block(const CoreArgs& a, const int q0, const int head, const int b, unsigned char* lds) {
@@ -601,8 +614,10 @@ __device__ inline void attn_bwd_dq_block(const CoreArgs& a, const int q0, const 
         pk.stash(sK, hd, mt);
         pv.stash(sV, hd, mt);
         if constexpr (KW == 1) __syncthreads(); else wave_sync();
-        pk.fetch(gK, ld, first + step * (t + 1), S - 1, hd, mt); // unconditional: rows are clamped
-        pv.fetch(gV, ld, first + step * (t + 1), S - 1, hd, mt);
+        if (always_fetch(HW, KW) || t + 1 < ntiles) {
+            pk.fetch(gK, ld, first + step * (t + 1), S - 1, hd, mt); // rows are clamped
+            pv.fetch(gV, ld, first + step * (t + 1), S - 1, hd, mt);
+        }
         const int kv0 = first + step * t;
         if (kv0 > qrow0 + 31) continue;
         const bool edge = kv0 + TR - 1 > qrow0 || kv0 + TR > S;
@@ -650,9 +665,9 @@ __device__ inline void attn_bwd_dq_block(const CoreArgs& a, const int q0, const 
         put_part<HW>(sK, acc, l32, lhi);
         if (rows_again(HW) && tid < 32) row_flags<HW>(lds)[tid] = 0;
         __syncthreads();
-        store_parts<HW>(lds, out, a.ldq, q0, S, hd, tid, [&](int, float (&f)[NW]) {
+        store_parts<HW, KW>(lds, out, a.ldq, q0, S, hd, tid, [&](int, float (&f)[KW]) {
 #pragma unroll
-            for (int w = 0; w < NW; ++w) f[w] = a.scale;
+            for (int w = 0; w < KW; ++w) f[w] = a.scale;
         });
     }
     if constexpr (rows_again(HW))
@@ -664,12 +679,12 @@ __device__ inline void attn_bwd_dq_block(const CoreArgs& a, const int q0, const 
 }
 
 template <int HW, int KW>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_dq(HW, KW), waves_dq(HW, KW))))
+__global__ __launch_bounds__(Split<KW>::THREADS) __attribute__((amdgpu_waves_per_eu(waves_dq(HW, KW), waves_dq(HW, KW))))
 void attn_bwd_dq_kernel(CoreArgs a, int nblocks, int nbh, SideJobs side) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[dq_lds<HW, KW>()];
     const int nitems = nblocks * nbh;
     const int id = workgroup_id();
-    if (id >= nitems) return carried<sizeof(lds)>(side, id - nitems, lds);
+    if (id >= nitems) return carried<sizeof(lds), Split<KW>::THREADS>(side, id - nitems, lds);
     int blk, head, b;
     causal_item(id, nitems, nbh, nblocks, a.ph, blk, head, b);
     attn_bwd_dq_block<HW, KW>(a, blk * Split<KW>::ROWS, head, b, lds);
@@ -684,20 +699,23 @@ void attn_bwd_dq_kernel(CoreArgs a, int nblocks, int nbh, SideJobs side) {
 // At HW = 128 a wave's accumulators (128 registers), K rows (32), one 32 x 32 block of logits and of logit gradients
 // (32) leave no room for its V rows (32) and the pieces of 64 staged queries (32) under the 256 registers of two waves
 // per SIMD: the workgroup's V rows then stay in LDS and are read from there per block, and a tile has 32 queries.  At
-// HW = 96 the shorter tile is enough.  (KW = 4 runs one wave per SIMD there: 512 registers, all operands kept.)
+// HW = 96 the shorter tile is enough.  (KW = 4 runs one wave per SIMD there: 512 registers, all operands kept.  KW = 8, two
+// waves per SIMD and the pieces of two whole tiles in every wave's registers, keeps the block's K rows in LDS as well.)
 template <int HW, int KW>
 struct DkvShape {
-    static constexpr bool kVInLds = HW == 128 && KW == 1;
+    static constexpr bool kVInLds = HW == 128 ? KW != 4 : HW == 96 && KW == 8, kKInLds = HW == 128 && KW == 8;
     static constexpr int QT = HW == HD && KW == 1 ? 64 : 32; // queries per tile
-    static constexpr int V_BYTES = kVInLds ? 32 * NW * row_bytes(HW) : 0;
-    static constexpr int LDS = KW == 1 ? 2 * QT * row_bytes(HW) + 2 * QT * 4 + V_BYTES : NW * wave_lds(HW);
+    static constexpr int ROWS_BYTES = Split<KW>::ROWS * row_bytes(HW);
+    static constexpr int LOOP = KW == 1 ? 2 * QT * row_bytes(HW) + 2 * QT * 4 : KW * wave_lds(HW);
+    static constexpr int LDS = LOOP + (kVInLds + kKInLds) * ROWS_BYTES;
+    static_assert(LDS <= 160 * 1024, "LDS of one CU");
 };
 
 template <int HW, int KW>
 __device__ inline void attn_bwd_dkv_block(const CoreArgs& a, const int k0, const int head, const int b, unsigned char* lds) {
     using Shape = DkvShape<HW, KW>;
     constexpr int KS = HW / 16, JB = HW / 32, QT = Shape::QT;
-    constexpr bool kVInLds = Shape::kVInLds;
+    constexpr bool kVInLds = Shape::kVInLds, kKInLds = Shape::kKInLds;
     const int hd = HW == HD ? HD : a.hd;
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lhi = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -713,13 +731,20 @@ __device__ inline void attn_bwd_dkv_block(const CoreArgs& a, const int k0, const
     unsigned char* const sO = sQ + QT * row_bytes(HW);
     float* const sL = (float*)(sO + QT * row_bytes(HW)); // log-sum-exp of the tile's queries, then delta
     float* const sD = sL + QT;
-    unsigned char* const sV = (unsigned char*)(sD + QT);
-    bf16x8 kf[KS], vf[kVInLds ? 1 : KS];
-    load_row_operand<HW>(gK, a.ldq, kc, hd, lhi, kf);
+    unsigned char* const sV = lds + Shape::LOOP;
+    unsigned char* const sK = sV + Shape::ROWS_BYTES;
+    const int own_row = KW == 1 ? 32 * wave + l32 : l32; // of sV, sK
+    bf16x8 kf[kKInLds ? 1 : KS], vf[kVInLds ? 1 : KS];
+    if constexpr (!kKInLds) load_row_operand<HW>(gK, a.ldq, kc, hd, lhi, kf);
     if constexpr (kVInLds) {
-        TileMover<NW, HW, 32 * NW> mv;
+        TileMover<Split<KW>::THREADS / 64, HW, Split<KW>::ROWS> mv, mk;
         mv.fetch(gV, (uint32_t)a.ldq, k0, S - 1, hd, tid);
-        mv.stash(sV, hd, tid); // read after the barriers of the first tile
+        if constexpr (kKInLds) mk.fetch(gK, (uint32_t)a.ldq, k0, S - 1, hd, tid);
+        mv.stash(sV, hd, tid); // KW = 1: read after the barriers of the first tile
+        if constexpr (kKInLds) {
+            mk.stash(sK, hd, tid);
+            __syncthreads();
+        }
     } else {
         load_row_operand<HW>(gV, a.ldq, kc, hd, lhi, vf);
     }
@@ -749,11 +774,13 @@ __device__ inline void attn_bwd_dkv_block(const CoreArgs& a, const int k0, const
         po.stash(sO, hd, mt);
         if (mt < 2 * QT) sL[mt] = pstat;
         if constexpr (KW == 1) __syncthreads(); else wave_sync();
-        // the next tile, unconditionally: rows are clamped
+        // the next tile (rows are clamped)
         const int qt0 = QT * (t0 + KW * t), next = qt0 + QT * KW;
-        pq.fetch(gQ, ldq32, next, S - 1, hd, mt);
-        po.fetch(gO, ldo32, next, S - 1, hd, mt);
-        pstat = stat_of(next + sq);
+        if (always_fetch(HW, KW) || t + 1 < ntiles) {
+            pq.fetch(gQ, ldq32, next, S - 1, hd, mt);
+            po.fetch(gO, ldo32, next, S - 1, hd, mt);
+            pstat = stat_of(next + sq);
+        }
         if (qt0 + QT - 1 < krow0) continue; // wave-uniform: every query of the tile lies before the wave's keys
         const bool edge = qt0 < krow0 + 31 || qt0 + QT > S;
 #pragma unroll
@@ -764,9 +791,11 @@ __device__ inline void attn_bwd_dkv_block(const CoreArgs& a, const int k0, const
             for (int e = 0; e < 16; ++e) sc[e] = 0.f, dp[e] = 0.f;
 #pragma unroll
             for (int s = 0; s < KS; ++s) {
-                sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<HW>(sQ, 32 * tb + l32, s, lhi), kf[s], sc, 0, 0, 0);
-                bf16x8 v;
-                if constexpr (kVInLds) v = frag_rows<HW>(sV, 32 * wave + l32, s, lhi);
+                bf16x8 k, v;
+                if constexpr (kKInLds) k = frag_rows<HW>(sK, own_row, s, lhi);
+                else k = kf[s];
+                sc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<HW>(sQ, 32 * tb + l32, s, lhi), k, sc, 0, 0, 0);
+                if constexpr (kVInLds) v = frag_rows<HW>(sV, own_row, s, lhi);
                 else v = vf[s];
                 dp = __builtin_amdgcn_mfma_f32_32x32x16_bf16(frag_rows<HW>(sO, 32 * tb + l32, s, lhi), v, dp, 0, 0, 0);
             }
@@ -824,9 +853,9 @@ __device__ inline void attn_bwd_dkv_block(const CoreArgs& a, const int k0, const
             put_part<HW>(sQ, part == 1 ? acc_k : acc_v, l32, lhi);
             if (rows_again(HW) && part == 1 && tid < 32) row_flags<HW>(lds)[tid] = 0;
             __syncthreads();
-            store_parts<HW>(lds, out + part * a.ph * hd, a.ldq, k0, S, hd, tid, [&](int, float (&f)[NW]) {
+            store_parts<HW, KW>(lds, out + part * a.ph * hd, a.ldq, k0, S, hd, tid, [&](int, float (&f)[KW]) {
 #pragma unroll
-                for (int w = 0; w < NW; ++w) f[w] = f1;
+                for (int w = 0; w < KW; ++w) f[w] = f1;
             });
         }
     }
@@ -839,12 +868,12 @@ __device__ inline void attn_bwd_dkv_block(const CoreArgs& a, const int k0, const
 }
 
 template <int HW, int KW>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(waves_dkv(HW, KW), waves_dkv(HW, KW))))
+__global__ __launch_bounds__(Split<KW>::THREADS) __attribute__((amdgpu_waves_per_eu(waves_dkv(HW, KW), waves_dkv(HW, KW))))
 void attn_bwd_dkv_kernel(CoreArgs a, int nblocks, int nbh, SideJobs side) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[DkvShape<HW, KW>::LDS];
     const int nitems = nblocks * nbh;
     const int id = workgroup_id();
-    if (id >= nitems) return carried<sizeof(lds)>(side, id - nitems, lds);
+    if (id >= nitems) return carried<sizeof(lds), Split<KW>::THREADS>(side, id - nitems, lds);
     int blk, head, b;
     causal_item(id, nitems, nbh, nblocks, a.ph, blk, head, b);
     // key block i meets the query blocks i .. n - 1: the first key blocks are the long ones
@@ -856,25 +885,36 @@ void attn_bwd_dkv_kernel(CoreArgs a, int nblocks, int nbh, SideJobs side) {
 // 12 heads) 158 / 124, 192 (2 x 1024) 168 / 149, 384 (4 x 1024) 184 / 187; heads of 128, 64 workgroups (1 x 1024, 8 heads)
 // 238 / 165, 128 (2 x 1024) 249 / 203, 256 (4 x 1024) 267 / 281; heads of 96, 192 workgroups 208 / 195.
 constexpr int split_below(int hw) { return hw == HD ? 256 : 192; }
+// KW = 8 (heads wider than 64): a chain half as long again, two waves on a SIMD where KW = 4 with a workgroup per CU has one, for
+// partial results of eight waves to add.  What it shortens grows with S, what it adds with the workgroups: taken from 512 tokens
+// on while four times the workgroups are no more than the tokens.  KW = 4 / KW = 8 at one sequence of 512, 1024, 1500, 2048 tokens
+// and 4, 4, 4, 8 heads: of 128 77 / 75, 103 / 95, 132 / 117, 250 / 232 us; of 96 72 / 70, 94 / 87, 119 / 105, 203 / 193; beyond that
+// line, 2 x 512 tokens, 8 heads: of 128 97 / 98, of 96 86 / 90; 4 x 256, 16 heads 148 / 150, 126 / 130.  Heads of 64 do not gain
+// (1 x 512, 8 heads 61 / 62; 1 x 2048 109 / 124): their tiles are half as long.
+inline bool split_in_eight(int hw, int64_t S, int64_t nbh) { return hw > HD && S >= 512 && (S + 31) / 32 * nbh * 4 <= S; }
 
 enum CoreKernel { CORE_FWD, CORE_DQ, CORE_DKV };
 template <int HW, int KW>
 int launch_core(CoreKernel which, const CoreArgs& a, int nbh, const SideJobs& side, hipStream_t s) {
     const int nblocks = (a.S + Split<KW>::ROWS - 1) / Split<KW>::ROWS;
     auto grid = [&](int lds) {
-        const int per = side_tiles(lds);
+        constexpr int HALVES = Split<KW>::THREADS / 256;
+        const int per = side_tiles(lds / HALVES) * HALVES;
         return workgroup_grid((int64_t)nblocks * nbh + (side.end[kMaxTransposeJobs - 1] + per - 1) / per);
     };
-    if (which == CORE_FWD) attn_fwd_kernel<HW, KW><<<grid(fwd_lds<HW, KW>()), 64 * NW, 0, s>>>(a, nblocks, nbh, side);
-    else if (which == CORE_DQ) attn_bwd_dq_kernel<HW, KW><<<grid(dq_lds<HW, KW>()), 64 * NW, 0, s>>>(a, nblocks, nbh, side);
-    else attn_bwd_dkv_kernel<HW, KW><<<grid(DkvShape<HW, KW>::LDS), 64 * NW, 0, s>>>(a, nblocks, nbh, side);
+    if (which == CORE_FWD) attn_fwd_kernel<HW, KW><<<grid(fwd_lds<HW, KW>()), Split<KW>::THREADS, 0, s>>>(a, nblocks, nbh, side);
+    else if (which == CORE_DQ) attn_bwd_dq_kernel<HW, KW><<<grid(dq_lds<HW, KW>()), Split<KW>::THREADS, 0, s>>>(a, nblocks, nbh, side);
+    else attn_bwd_dkv_kernel<HW, KW><<<grid(DkvShape<HW, KW>::LDS), Split<KW>::THREADS, 0, s>>>(a, nblocks, nbh, side);
     return launch_status();
 }
 template <int HW>
 int launch_core(CoreKernel which, const CoreArgs& a, int64_t nbh, const SideJobs& side, hipStream_t s) {
     const int64_t wide = (a.S + Split<1>::ROWS - 1) / Split<1>::ROWS * nbh; // workgroups of the launch with KW = 1
     if (wide > INT32_MAX / 2) return SDP_ERR_UNSUPPORTED;
-    return wide <= split_below(HW) ? launch_core<HW, NW>(which, a, (int)nbh, side, s) : launch_core<HW, 1>(which, a, (int)nbh, side, s);
+    if constexpr (HW > HD) {
+        if (split_in_eight(HW, a.S, nbh)) return launch_core<HW, 8>(which, a, (int)nbh, side, s);
+    }
+    return wide <= split_below(HW) ? launch_core<HW, 4>(which, a, (int)nbh, side, s) : launch_core<HW, 1>(which, a, (int)nbh, side, s);
 }
 // the core kernel and, in its launch, n transposes
 int launch_core(CoreKernel which, const CoreArgs& a, int64_t nbh, const TransposeJob* jobs, int n, const char* name, hipStream_t s) {
