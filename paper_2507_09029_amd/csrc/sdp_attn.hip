@@ -1160,6 +1160,21 @@ int sdp::attn_fwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     rc = run(dtype, pj, s);
     if (rc != SDP_OK) return rc;
 
+    GemmDesc op;
+    op.name = "attn_out";
+    op.M = T, op.N = d, op.K = E;
+    op.A = O_save, op.lda = E;
+    op.epilogue = EPI_STORE;
+    op.C = Y, op.ldc = d;
+    op.R = residual, op.ldr = d;
+    // bf16: WoT as it is stored (padded: its copy) where the contraction takes it so and no output takes its place
+    GemmDesc as_stored = op;
+    as_stored.B = padded ? w.WoP : WoT, as_stored.ldb = ldp, as_stored.b_km = 1;
+    as_stored.b_gather = rows_o, as_stored.b_rows = rows_o ? (int64_t)H * hd : E, as_stored.heads = heads;
+    const bool stored = dtype == SDP_BF16 && gemm_reads_as_stored(as_stored) &&
+                        (padded || !overlap({{Y, (size_t)T * d * 2}, {O_save, (size_t)T * E * 2}, {LSE_save, (size_t)Bt * ph * S * 4}},
+                                            {{WoT, (size_t)H * hd * d * 2}}));
+
     if (mfma_core(dtype)) {
         CoreArgs a{};
         a.qkv = (const uint16_t*)QKV_save, a.ldq = 3 * E;
@@ -1168,7 +1183,7 @@ int sdp::attn_fwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         a.S = S, a.ph = ph, a.hd = hw;
         a.scale = 1.f / sqrtf((float)hd), a.scale2 = a.scale * 1.44269504088896340736f;
         const TransposeJob wt{padded ? w.WoP : WoT, w.WoC, ldp, ldo, rows_o, E, d, heads};
-        rc = launch_core(CORE_FWD, a, (int64_t)ph * Bt, &wt, 1, "attn_core_fwd", s);
+        rc = launch_core(CORE_FWD, a, (int64_t)ph * Bt, &wt, stored ? 0 : 1, "attn_core_fwd", s);
     } else {
         AttnCoreDesc c;
         c.qkv = QKV_save, c.ldq = 3 * E, c.o_out = O_save, c.ldo = E, c.lse = LSE_save;
@@ -1176,6 +1191,7 @@ int sdp::attn_fwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         rc = attn_f32_fwd(c, s);
     }
     if (rc != SDP_OK) return rc;
+    if (stored) return run(dtype, as_stored, s);
 
     // fp32 reads WoT itself: an output that takes its place needs a copy
     const int32_t* wo_rows = rows_o;
@@ -1184,15 +1200,8 @@ int sdp::attn_fwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         if (rc != SDP_OK) return rc;
         WoT = w.WoC, wo_rows = nullptr;
     }
-    GemmDesc op;
-    op.name = "attn_out";
-    op.M = T, op.N = d, op.K = E;
-    op.A = O_save, op.lda = E;
     if (dtype == SDP_BF16) op.B = w.WoC, op.ldb = ldo;
     else op.B = WoT, op.ldb = d, op.b_km = 1, op.b_gather = wo_rows, op.b_rows = wo_rows ? (int64_t)H * hd : E;
-    op.epilogue = EPI_STORE;
-    op.C = Y, op.ldc = d;
-    op.R = residual, op.ldr = d;
     return run(dtype, op, s);
 }
 
@@ -1286,6 +1295,25 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     rc = run(dtype, go, s);
     if (rc != SDP_OK) return rc;
 
+    GemmDesc dx;
+    dx.name = "attn_dx";
+    dx.M = T, dx.N = d, dx.K = 3 * E;
+    dx.A = w.dQKV, dx.lda = 3 * E;
+    dx.epilogue = EPI_STORE;
+    dx.C = dX, dx.ldc = d;
+    dx.R = dx_residual, dx.ldr = d;
+    // bf16: Wqkv as it is stored (padded: its copy) where the contraction takes it so and no output takes its place
+    const bool listed = gathered && !padded;
+    const size_t dwp_b = want_dw ? (size_t)part * 2 : 0;
+    GemmDesc as_stored = dx;
+    as_stored.B = padded ? w.Wp : Wqkv, as_stored.ldb = ldp, as_stored.b_km = 1;
+    as_stored.b_gather = listed ? rows_qkv : nullptr, as_stored.b_rows = listed ? (int64_t)3 * H * hd : 3 * E, as_stored.heads = heads;
+    const bool apart = dtype == SDP_BF16 &&
+                       (padded || !overlap({{dX, (size_t)T * d * 2}, {dWqkv, 3 * dwp_b}, {dWoT, dwp_b}}, {{Wqkv, (size_t)3 * H * hd * d * 2}}));
+    // and in the launch of the weight gradients, where dX does not take the place of what those read
+    const bool pair = direct && apart && gemm_pairs(as_stored, wg) &&
+                      !overlap({{dX, (size_t)T * d * 2}}, {{X, (size_t)T * d * 2}, {dY, (size_t)T * d * 2}, {O_save, (size_t)T * E * 2}});
+    const bool stored = pair || (apart && gemm_reads_as_stored(as_stored));
     if (mfma_core(dtype)) {
         CoreArgs a{};
         a.qkv = (const uint16_t*)QKV_save, a.ldq = 3 * E;
@@ -1296,12 +1324,13 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         a.scale = 1.f / sqrtf((float)hd), a.scale2 = a.scale * 1.44269504088896340736f;
         // Wqkv's rows for dX; token-contiguous copies for the plain weight gradients
         const int64_t ldt = ld_tokens(T, d, E);
-        const TransposeJob beside_dq[4] = {{padded ? w.Wp : Wqkv, w.Wc, ldp, ldw, gathered && !padded ? rows_qkv : nullptr, 3 * E, d, heads},
+        const TransposeJob beside_dq[4] = {{padded ? w.Wp : Wqkv, w.Wc, ldp, ldw, listed ? rows_qkv : nullptr, 3 * E, d, heads},
                                            {O_save, w.Ot, E, ldt, nullptr, T, E},
                                            {X, w.Xt, d, ldt, nullptr, T, d},
                                            {dY, w.dYt, d, ldt, nullptr, T, d}};
         const TransposeJob beside_dkv{w.dQKV, w.dQKVt, 3 * E, ldt, nullptr, T, E}; // dQ
-        rc = launch_core(CORE_DQ, a, (int64_t)hr * Bt, beside_dq, want_dw && !direct ? 4 : 1, "attn_core_bwd_dq", s);
+        const int skip = stored ? 1 : 0; // dX needs no copy of Wqkv
+        rc = launch_core(CORE_DQ, a, (int64_t)hr * Bt, beside_dq + skip, (want_dw && !direct ? 4 : 1) - skip, "attn_core_bwd_dq", s);
         // reads the delta written by the dQ kernel
         if (rc == SDP_OK) rc = launch_core(CORE_DKV, a, (int64_t)hr * Bt, &beside_dkv, want_dw && !direct ? 1 : 0, "attn_core_bwd_dkv", s);
         if (rc != SDP_OK) return rc;
@@ -1332,15 +1361,9 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         }
     }
 
-    GemmDesc dx;
-    dx.name = "attn_dx";
-    dx.M = T, dx.N = d, dx.K = 3 * E;
-    dx.A = w.dQKV, dx.lda = 3 * E;
-    if (dtype == SDP_BF16) dx.B = w.Wc, dx.ldb = ldw;
+    if (dtype == SDP_BF16 && stored) dx = as_stored;
+    else if (dtype == SDP_BF16) dx.B = w.Wc, dx.ldb = ldw;
     else dx.B = Wqkv, dx.ldb = d, dx.b_km = 1, dx.b_gather = w_rows, dx.b_rows = w_rows ? (int64_t)3 * H * hd : 3 * E;
-    dx.epilogue = EPI_STORE;
-    dx.C = dX, dx.ldc = d;
-    dx.R = dx_residual, dx.ldr = d;
     if (!want_dw) return run(dtype, dx, s);
 
     if (dtype == SDP_F32) { // every operand as it is stored: dQKV, O, X, dY depth-major, the held heads' columns by their list
@@ -1380,6 +1403,7 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
             wg.Bb[0] = wg.Bb[1] = wg.Bb[2] = w.Xt, wg.Bb[3] = w.dYt, wg.Ab[3] = w.Ot;
             if (dx_residual == dY) dx.R = w.dYt;
         }
+        if (pair) return gemm_mfma_pair(dx, wg, "attn_dx_dw", s);
         rc = gemm_mfma_bf16(wg, s);
         return rc != SDP_OK ? rc : run(dtype, dx, s);
     }

@@ -268,31 +268,22 @@ constexpr int side_tiles(int threads, int lds) {
     return lds / (threads / 256 * kTransposeLds) < 8 ? lds / (threads / 256 * kTransposeLds) : 8;
 }
 
-// KM: bit 0 = A is depth-major ([K][lda]), bit 1 = B is
+// One workgroup's tile (id `block` of the launch).  KM: bit 0 = A is depth-major ([K][lda]), bit 1 = B is, bit 2 = B's depth rows
+// are listed (b_gather)
 template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int OP, int KM>
-__global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1) void sdp_gemm_kernel(Dev g, SideArg<OP> side) {
+__device__ __attribute__((always_inline)) inline void gemm_tile(const Dev& g, const int block, unsigned char* const smem) {
     using Geo = Geometry<BM, BN, WAVES_M, WAVES_N, EPI, KM>;
     constexpr int NW = Geo::NW, WM = Geo::WM, WN = Geo::WN, FM = Geo::FM, FN = Geo::FN;
     constexpr int A_BYTES = Geo::A_BYTES, B_BYTES = Geo::B_BYTES;
     constexpr bool kFwd = EPI == EPI_SWIGLU_FWD;
     constexpr bool kWaveDepth = Geo::kWaveDepth;
-    constexpr bool kAkm = (KM & 1) != 0, kBkm = (KM & 2) != 0;
-    static_assert(KM == 0 || EPI == EPI_STORE, "depth-major operands: plain store epilogue only");
+    constexpr bool kAkm = (KM & 1) != 0, kBkm = (KM & 2) != 0, kBList = (KM & 4) != 0;
+    static_assert(KM == 0 || EPI == EPI_STORE || (EPI == EPI_DUAL_ACC && !kAkm), "depth-major operands: store epilogues only");
+    static_assert(!kBList || (kBkm && !kAkm), "a list of depth rows");
     constexpr int SA = (BM / 8) / NW;  // A slabs (1 KB) per wave per step
     constexpr int SB = (BN / 8) / NW;  // B slabs per wave per step
     static_assert((BM / 8) % NW == 0 && (BN / 8) % NW == 0, "slabs must divide among the waves");
     static_assert(!kFwd || FN % 2 == 0, "gate/up fragments come in pairs");
-    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-
-    if constexpr (carries_side(OP)) {
-        if ((int)blockIdx.x >= g.ntot) {
-            constexpr int HALVES = NW / 4, N = side_tiles(NW * 64, Geo::LDS);
-            const int half = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
-            side_transposes<N>(side, ((int)blockIdx.x - g.ntot) * HALVES + half, smem + half * N * kTransposeLds,
-                               threadIdx.x & 255);
-            return;
-        }
-    }
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6); // wave-uniform: keeps what derives from it scalar
     const int wm = wave / WAVES_N, wn = wave % WAVES_N;
@@ -304,7 +295,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
     // tile-columns: the tiles that run together on one XCD then form a compact block of (problems x
     // tile-rows x tile-columns) whose operand rows are fetched into that XCD's L2 once.
     constexpr bool kTail = OP == OP_DW_TAIL;
-    int bid = blockIdx.x;
+    int bid = block;
     bool cut = false;  // OP_DW_TAIL: this workgroup computes one depth range of a tile of the last round
     int tail_part = 0, tail_q = 0;
     if (kTail && bid >= g.n_head) {
@@ -446,11 +437,38 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
         }
         if (!kBkm) look_up(g.bg, idx);
 #pragma unroll
-        for (int i = 0; i < N; ++i) off[i] = (uint32_t)((kBkm ? k[i] * g.ldb + idx[i] : idx[i] * g.ldb + k[i]) * 2);
+        for (int i = 0; i < N; ++i) off[i] = (uint32_t)((kBList ? idx[i] : kBkm ? k[i] * g.ldb + idx[i] : idx[i] * g.ldb + k[i]) * 2);
     };
+    // listed depth rows: the byte offset of each row, in LDS behind the stages, to a whole number of steps
+    uint32_t* const list = (uint32_t*)(smem + Geo::LDS);
+    if constexpr (kBList) {
+        // eight look-ups of a thread in flight together, without a branch among them: one after the other, 4000 rows cost a
+        // workgroup of 256 threads 7 us
+        constexpr int NT = NW * 64, U = 8;
+        const int end = (g.K + BK - 1) / BK * BK;
+        auto fill = [&](auto row_of) __attribute__((always_inline)) {
+            for (int i0 = tid; i0 < end; i0 += U * NT) {
+                int row[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) row[u] = row_of(i0 + u * NT < g.K ? i0 + u * NT : g.K - 1);
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (i0 + u * NT < end) list[i0 + u * NT] = (uint32_t)row[u] * (uint32_t)(g.ldb * 2);
+            }
+        };
+        if (!kHeads || g.heads.width == 0) fill([&](int i) __attribute__((always_inline)) { return g.bg[i]; });
+        else fill([&](int i) __attribute__((always_inline)) { return head_row(g.bg, g.heads, i); });
+        __syncthreads();
+    }
     // what depth step k0 / 64 adds to an operand's base
     auto step_a = [&](int k0) __attribute__((always_inline)) { return kAkm ? (int64_t)k0 * lda * 2 : (int64_t)k0 * 2; };
-    auto step_b = [&](int k0) __attribute__((always_inline)) { return kBkm ? (int64_t)k0 * g.ldb * 2 : (int64_t)k0 * 2; };
+    auto step_b = [&](int k0) __attribute__((always_inline)) { return kBList ? 0 : kBkm ? (int64_t)k0 * g.ldb * 2 : (int64_t)k0 * 2; };
+    // and to the offsets of its chunks of B at depths k: read before the first of the loads that take them, as the written-out
+    // loads keep their order with LDS reads
+    auto listed = [&](int k0, const auto& k, auto& off) __attribute__((always_inline)) {
+#pragma unroll
+        for (int i = 0; i < (int)(sizeof(off) / sizeof(off[0])); ++i) off[i] = kBList ? list[k0 + k[i]] : 0u;
+    };
     if constexpr (kWaveDepth) {
         // ---- main loop of the 64-row tiles: wave w runs the depth steps w, w + NW, ... on the whole tile, in two LDS stages
         // of its own (no barrier); the partial tiles are then added through LDS, in wave order, every wave taking the part
@@ -475,18 +493,27 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
             const unsigned char* abase = (const unsigned char*)(second ? g.A2 : gA) + step_a(k0);
             const unsigned char* bbase = (const unsigned char*)(second ? g.B2 : gB) + step_b(k0);
             unsigned char* st = mine + stage * (A_BYTES + B_BYTES);
+            uint32_t row[BN / 8];
+            listed(k0, b_k, row);
 #pragma unroll
             for (int i = 0; i < BM / 8; ++i) {
                 direct_load<KM != 0, TAIL>(abase, a_off[i], k0 + a_k[i] >= g.K, st + i * 1024);
             }
 #pragma unroll
             for (int j = 0; j < BN / 8; ++j) {
-                direct_load<KM != 0, TAIL>(bbase, b_off[j], k0 + b_k[j] >= g.K, st + A_BYTES + j * 1024);
+                direct_load<KM != 0, TAIL>(bbase, b_off[j] + row[j], k0 + b_k[j] >= g.K, st + A_BYTES + j * 1024);
             }
         };
-        auto run = [&](auto tail_c) {
-            if (wave < nk) issue(wave, 0, tail_c);
-            if (wave + NW < nk) issue(wave + NW, 1, tail_c);
+        // only the last step of an operand pair may end beyond the depth, and only its loads compare (T = 1000, d = 2048, p = 4128:
+        // dX 77 -> 66 us, down 43 -> 40)
+        auto issue_step = [&](int kt, int stage) {
+            const int last = nk_all - 1 - kt0;
+            if (g.K % BK != 0 && (kt == last || (EPI == EPI_DUAL_ACC && kt == nk1 + last))) issue(kt, stage, std::true_type{});
+            else issue(kt, stage, std::false_type{});
+        };
+        {
+            if (wave < nk) issue_step(wave, 0);
+            if (wave + NW < nk) issue_step(wave + NW, 1);
             int stage = 0;
             for (int kt = wave; kt < nk; kt += NW, stage ^= 1) {
                 if (kt + NW < nk) SDP_WAIT_VMCNT(BM / 8 + BN / 8); else SDP_WAIT_VMCNT(0);
@@ -500,7 +527,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
                     if (h == 1) { // both halves have been read: the stage can be filled again
                         SDP_WAIT_LGKMCNT0();
                         __builtin_amdgcn_sched_barrier(0);
-                        if (kt + 2 * NW < nk) issue(kt + 2 * NW, stage, tail_c);
+                        if (kt + 2 * NW < nk) issue_step(kt + 2 * NW, stage);
                         __builtin_amdgcn_sched_barrier(0);
                     }
 #pragma unroll
@@ -510,8 +537,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
                             part[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tb[h][j], ta[h][i], part[i][j], 0, 0, 0);
                 }
             }
-        };
-        if (g.K % BK == 0) run(std::false_type{}); else run(std::true_type{});
+        }
         __syncthreads(); // every wave is done with its stages
         f32x4* const parts = (f32x4*)smem; // [wave][fragment][lane]
 #pragma unroll
@@ -559,6 +585,8 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
             direct_load<KM != 0, TAIL>(abase, a_off[i], a_k[i] >= krem, sa + (wave + NW * i) * 1024);
         }
     };
+    uint32_t b_row[SB]; // listed depth rows: of the next loads of B
+    auto list_b = [&](int kt) __attribute__((always_inline)) { listed(((EPI == EPI_DUAL_ACC && kt >= nk1) ? kt - nk1 : kt) * BK, b_k, b_row); };
     auto issue_b = [&](int kt, int slot, auto tail_c, int first, int last) __attribute__((always_inline)) {
         constexpr bool TAIL = decltype(tail_c)::value;
         const bool second = EPI == EPI_DUAL_ACC && kt >= nk1;
@@ -572,7 +600,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
             if (i < first || i >= last) continue;
             // SWIGLU_FWD: tile rows BN/2.. hold the up-projection rows (second matrix)
             const bool up = kFwd && 8 * (wave + NW * i) >= BN / 2;
-            direct_load<KM != 0, TAIL>(up ? bbase1 : bbase0, b_off[i], b_k[i] >= krem, sb + (wave + NW * i) * 1024);
+            direct_load<KM != 0, TAIL>(up ? bbase1 : bbase0, b_off[i] + (kBList ? b_row[i] : 0u), b_k[i] >= krem, sb + (wave + NW * i) * 1024);
         }
     };
 
@@ -670,6 +698,7 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
         // R: steps left after this one, at most S; TA / TB: the step of the loads of A / B may end beyond the depth
         auto step = [&](auto r_c, auto ta_c, auto tb_c) __attribute__((always_inline)) {
             constexpr int R = decltype(r_c)::value;
+            if (kBList && R >= S - 1) list_b(kt + S - 1);
             half_step(0, true, slot_a, slot, R >= S - 1 ? SB : 0, [&](int l) __attribute__((always_inline)) { issue_b(kt + S - 1, prev, tb_c, l, l + 1); });
             if constexpr (R > 0) {
                 // the loads younger than step kt + 1's
@@ -687,7 +716,10 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
 #pragma unroll
         for (int j = -S; j < 0; ++j) { // what the steps before the first would have issued; B of step S - 1 follows in step 0
             if (j + NA >= 0 && j + NA < nk) issue_a(j + NA, j + NA, true_type{}, 0, SA);
-            if (j + S < nk && j < -1) issue_b(j + S, j + S, true_type{}, 0, SB);
+            if (j + S < nk && j < -1) {
+                if (kBList) list_b(j + S);
+                issue_b(j + S, j + S, true_type{}, 0, SB);
+            }
         }
         if (nk >= S) SDP_WAIT_VMCNT(SA + SB + (NA == S ? SA : 0)); else SDP_WAIT_VMCNT(0);
         barrier();
@@ -1076,6 +1108,44 @@ __global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1
     }
 }
 
+template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int OP, int KM>
+__global__ __launch_bounds__(WAVES_M* WAVES_N * 64, BM == 64 && BN == 64 ? 2 : 1) void sdp_gemm_kernel(Dev g, SideArg<OP> side) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    if constexpr (carries_side(OP)) {
+        if ((int)blockIdx.x >= g.ntot) {
+            constexpr int NW = WAVES_M * WAVES_N, HALVES = NW / 4;
+            constexpr int N = side_tiles(NW * 64, Geometry<BM, BN, WAVES_M, WAVES_N, EPI, KM>::LDS);
+            const int half = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
+            side_transposes<N>(side, ((int)blockIdx.x - g.ntot) * HALVES + half, smem + half * N * kTransposeLds,
+                               threadIdx.x & 255);
+            return;
+        }
+    }
+    gemm_tile<BM, BN, WAVES_M, WAVES_N, EPI, OP, KM>(g, (int)blockIdx.x, smem);
+}
+
+// A single problem with a depth-major right operand (dX) and a batched launch (the weight gradients) side by side, in tiles of
+// BX x BX and BW x BW (128, eight waves; 64, four waves, for which a workgroup of eight has four that leave at once: barriers wait
+// for the others alone).  The longer chains come first: x_first.
+template <int BX, int BW>
+constexpr int pair_threads() { return BX == 128 || BW == 128 ? 512 : 256; }
+template <int B, int THREADS, int EPI, int OP, int KM>
+__device__ __attribute__((always_inline)) inline void pair_tile(const Dev& g, int id, unsigned char* smem) {
+    if constexpr (B == 128) {
+        gemm_tile<128, 128, 4, 2, EPI, OP, KM>(g, id, smem);
+    } else {
+        if (THREADS > 256 && threadIdx.x >= 256) return;
+        gemm_tile<64, 64, 2, 2, EPI, OP, KM>(g, id, smem);
+    }
+}
+template <int BX, int BW, int EPIX, int KMX, int KMW>
+__global__ __launch_bounds__((pair_threads<BX, BW>()), 1) void sdp_gemm_pair_kernel(Dev x, Dev w, int x_first) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
+    const int id = (int)blockIdx.x, ix = x_first ? id : id - w.ntot;
+    if (ix >= 0 && ix < x.ntot) pair_tile<BX, pair_threads<BX, BW>(), EPIX, EPIX == EPI_DUAL_ACC ? OP_DX : OP_DOWN, KMX>(x, ix, smem);
+    else pair_tile<BW, pair_threads<BX, BW>(), EPI_STORE, OP_DW, KMW>(w, x_first ? id - x.ntot : id, smem);
+}
+
 constexpr int kNumCU = 256;
 
 // Overrides of the tile shape and order for tuning runs.  The library's behaviour is a pure function of its
@@ -1241,14 +1311,12 @@ bool carry(int64_t tiles, double round, int64_t wgs) {
     return idle > 0 && (double)((wgs + idle - 1) / idle) * 5.0 + 5.0 <= 1.2 * round;
 }
 
-template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int OP, int KM>
-int launch_cfg(const GemmDesc& d, double round, hipStream_t s) {
-    using Geo = Geometry<BM, BN, WAVES_M, WAVES_N, EPI, KM>;
-    constexpr int NTHREADS = WAVES_M * WAVES_N * 64;
-    constexpr int LDS = Geo::LDS;
-    // what this kernel would leave undone or misread
-    if ((!carries_side(OP) && d.nside > 0) || (!takes_heads(OP) && d.heads.width > 0)) return SDP_ERR_INVALID_ARG;
-    Dev g;
+constexpr int kMaxLds = 160 * 1024;
+inline int list_bytes(int K) { return (K + BK - 1) / BK * BK * 4; }
+
+// kernel arguments of a descriptor, for tiles of BM x BN
+template <int BM, int BN, int EPI, int OP>
+int describe(const GemmDesc& d, Dev& g) {
     g.M = d.M, g.N = d.N, g.K = d.K;
     g.A = (const uint16_t*)d.A, g.A2 = (const uint16_t*)d.A2, g.B = (const uint16_t*)d.B, g.B2 = (const uint16_t*)d.B2;
     g.lda = d.lda, g.ldb = d.ldb, g.ag = d.a_gather, g.bg = d.b_gather, g.cs = d.c_scatter, g.heads = d.heads;
@@ -1272,12 +1340,6 @@ int launch_cfg(const GemmDesc& d, double round, hipStream_t s) {
     g.ksteps = ((d.K + BK - 1) / BK + g.ksplit - 1) / g.ksplit;
     g.partial = (float*)(OP == OP_DW_TAIL ? d.tail_ws : d.split_ws);
     g.n_head = g.ntot, g.tail = 0;
-    int64_t grid = (int64_t)g.ntot;
-    if (OP == OP_DW_TAIL) {
-        g.n_head = g.ntot / kNumCU * kNumCU, g.tail = g.ntot - g.n_head;
-        grid = (int64_t)g.n_head + (int64_t)g.tail * d.ksplit;
-        if (g.tail < 1 || d.ksplit < 2 || !d.tail_ws || grid > 0x7FFFFFFF) return SDP_ERR_INVALID_ARG;
-    }
     int na = 1, nbo = 1; // distinct A / B operands among the problems of a batch
     for (int z = 0; z < kMaxBatch; ++z) {
         g.Ab[z] = (const uint16_t*)d.Ab[z], g.Bb[z] = (const uint16_t*)d.Bb[z], g.Cb[z] = (uint16_t*)d.Cb[z];
@@ -1309,6 +1371,28 @@ int launch_cfg(const GemmDesc& d, double round, hipStream_t s) {
         std::lock_guard<std::mutex> lk(g_shape_mu);
         g_last_shape[d.name] = {BM, BN, g.group_m, g.np0 > 0 ? 1 : 0};
     }
+    return SDP_OK;
+}
+
+template <int BM, int BN, int WAVES_M, int WAVES_N, int EPI, int OP, int KM>
+int launch_cfg(const GemmDesc& d, double round, hipStream_t s) {
+    using Geo = Geometry<BM, BN, WAVES_M, WAVES_N, EPI, KM>;
+    constexpr int NTHREADS = WAVES_M * WAVES_N * 64;
+    constexpr int LDS = Geo::LDS;
+    constexpr bool kBList = (KM & 4) != 0;
+    const int lds = LDS + (kBList ? list_bytes(d.K) : 0);
+    if (lds > kMaxLds) return SDP_ERR_INVALID_ARG;
+    // what this kernel would leave undone or misread
+    if ((!carries_side(OP) && d.nside > 0) || (!takes_heads(OP) && d.heads.width > 0)) return SDP_ERR_INVALID_ARG;
+    Dev g;
+    const int drc = describe<BM, BN, EPI, OP>(d, g);
+    if (drc != SDP_OK) return drc;
+    int64_t grid = (int64_t)g.ntot;
+    if (OP == OP_DW_TAIL) {
+        g.n_head = g.ntot / kNumCU * kNumCU, g.tail = g.ntot - g.n_head;
+        grid = (int64_t)g.n_head + (int64_t)g.tail * d.ksplit;
+        if (g.tail < 1 || d.ksplit < 2 || !d.tail_ws || grid > 0x7FFFFFFF) return SDP_ERR_INVALID_ARG;
+    }
     SideArg<OP> side{};
     if constexpr (carries_side(OP)) {
         if (d.nside > 0) {
@@ -1326,16 +1410,16 @@ int launch_cfg(const GemmDesc& d, double round, hipStream_t s) {
     auto kern = sdp_gemm_kernel<BM, BN, WAVES_M, WAVES_N, EPI, OP, KM>;
     // once per instantiation (initialisation of a function-local static is thread-safe)
     static const hipError_t attr =
-        hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+        hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kBList ? kMaxLds : LDS);
     if (attr != hipSuccess) return SDP_ERR_HIP;
     // When this kernel is being timed, the launch itself carries the two events (their timestamps are the
     // kernel's own begin and end): events recorded around the launch would put a bubble of several
     // microseconds on either side of it.
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     if (profile_launch_events(d.name, &ev0, &ev1))
-        hipExtLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NTHREADS), (uint32_t)LDS, s, ev0, ev1, 0u, g, side);
+        hipExtLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(NTHREADS), (uint32_t)lds, s, ev0, ev1, 0u, g, side);
     else
-        kern<<<dim3((unsigned)grid), NTHREADS, LDS, s>>>(g, side);
+        kern<<<dim3((unsigned)grid), NTHREADS, lds, s>>>(g, side);
     const int rc = launch_status();
     if (OP == OP_DW_TAIL && rc == SDP_OK) return tail_reduce<BM, BN>(g, d, s);
     return rc;
@@ -1375,23 +1459,32 @@ constexpr bool shape_exists(int epi, int shape) {
 
 // nbatch problems, the depth of each cut into ksplit ranges that are problems of their own
 template <int EPI>
-Shape choose_shape(const GemmDesc& d, int nbatch, int ksplit, double* round = nullptr) {
-    const int force = tuning().force_tile - 1;
+int64_t shape_tiles(const GemmDesc& d, int nbatch, int ksplit, int shape) {
     const int ncols = EPI == EPI_SWIGLU_FWD ? 2 * d.N : d.N; // gate and up interleaved double the tile columns
+    const ShapeInfo& h = kShapes[shape];
+    return (int64_t)((d.M + h.bm - 1) / h.bm) * ((ncols + h.bn - 1) / h.bn) * nbatch * ksplit;
+}
+// one round of it, on a chip of which this share of the CUs works
+template <int EPI>
+double round_cost(const GemmDesc& d, int ksplit, int shape, double busy) {
     const double steps = ((d.K + BK - 1) / BK + ksplit - 1) / ksplit * (EPI == EPI_DUAL_ACC ? 2 : 1);
     const EpilogueCost e = epilogue_cost(EPI);
+    const ShapeInfo& h = kShapes[shape];
+    return steps * (h.step0 + (h.step1 - h.step0) * busy) + e.e0 + e.e1 * h.bm * h.bn / 1024;
+}
+template <int EPI>
+Shape choose_shape(const GemmDesc& d, int nbatch, int ksplit, double* round = nullptr, double* whole = nullptr) {
+    const int force = tuning().force_tile - 1;
     Shape best = T256x256;
     double best_cost = -1;
     for (int i = 0; i < NUM_SHAPES; ++i) {
         if (!shape_exists(EPI, i) || (force >= 0 && i != force && shape_exists(EPI, force))) continue;
-        const ShapeInfo& h = kShapes[i];
-        const int64_t tiles = (int64_t)((d.M + h.bm - 1) / h.bm) * ((ncols + h.bn - 1) / h.bn) * nbatch * ksplit;
-        const int64_t rounds = (tiles + kNumCU - 1) / kNumCU;
-        const double busy = tiles < kNumCU ? (double)tiles / kNumCU : 1.0;
-        const double cost = (double)rounds * (steps * (h.step0 + (h.step1 - h.step0) * busy) + e.e0 + e.e1 * h.bm * h.bn / 1024);
+        const int64_t tiles = shape_tiles<EPI>(d, nbatch, ksplit, i), rounds = (tiles + kNumCU - 1) / kNumCU;
+        const double one = round_cost<EPI>(d, ksplit, i, tiles < kNumCU ? (double)tiles / kNumCU : 1.0), cost = (double)rounds * one;
         if (best_cost < 0 || cost < best_cost) {
             best_cost = cost, best = (Shape)i;
-            if (round) *round = cost / rounds;
+            if (round) *round = one;
+            if (whole) *whole = cost;
         }
     }
     return best;
@@ -1411,6 +1504,32 @@ int launch(const GemmDesc& d, hipStream_t s) {
         if (shape == T64x64) return launch_cfg<64, 64, 2, 2, EPI, OP, KM>(d, round, s);
     }
     return SDP_ERR_UNSUPPORTED; // not reached: choose_shape returns one of the above
+}
+
+// Single problems whose right operand is depth-major as it is stored (down, dX and the attention's out and dX with the weights
+// themselves in the place of transposed copies): LDS of one, with the list of its depth rows; 0: not such a shape.
+template <int EPI>
+int stored_lds(const GemmDesc& d, Shape shape) {
+    const int list = d.b_gather ? list_bytes(d.K) : 0;
+    if (shape == T64x64) return Geometry<64, 64, 2, 2, EPI, 2>::LDS + list;
+    return shape == T128x128 ? Geometry<128, 128, 4, 2, EPI, 2>::LDS + list : 0;
+}
+// The 128 bytes that a 64-wide tile takes of a stored row are one line where rows are whole lines, else two: worth it for short
+// depths alone then.  Event times of down, dX and the launches that made or carried the copies, two workers at T = 304, p = 4000
+// (4032): d = 600 89 us with copies, 91 without; d = 640 84, 81; whole steps: T = 2000, d = 400, p = 2400 189 -> 197, T = 1176,
+// d = 456, F = 5472 308 -> 323, but T = 1504, d = 504, p = 1000 131 -> 124.
+template <int EPI>
+bool stored_lines(const GemmDesc& d) {
+    return d.ldb % 64 == 0 || (d.K + BK - 1) / BK * (EPI == EPI_DUAL_ACC ? 2 : 1) <= 40;
+}
+// In a launch of its own: 64 x 64 tiles.  A transposing pair of reads costs what two row-major reads do, so that the larger tiles do
+// better with the copies that other launches carry (block of 4 x 1024 tokens, d = 1200, F = 3200 and its masked neighbour 1068 -> 1098 us
+// with every 128-row tile this way); the smallest launches do better without.  Two workers, with copies / as stored: T = 256, d = 768,
+// p = 1024 104 / 99 us, T = 512, d = 1024, F = 5504 under backward masking 282 / 250, T = 1000, d = 2048, p = 4128 522 / 516;
+// attention of 500 tokens, 28 heads of 64 113 / 104.
+template <int EPI>
+bool stored_shape(const GemmDesc& d) {
+    return choose_shape<EPI>(d, 1, 1) == T64x64 && stored_lines<EPI>(d) && stored_lds<EPI>(d, T64x64) <= kMaxLds;
 }
 
 // Whether the launch of `d` is one to give its transposes to.  Their workgroups take 16 tiles each beside 256 x 256 and 128 x 256,
@@ -1526,8 +1645,12 @@ bool gemm_mfma_supported(const GemmDesc& d) {
     // multiple of 8 will do.  T = 5000, d = 1600, p = 2664, whose depths p and T are odd multiples of 8: a step of two
     // workers takes 0.98 ms here, 12.0 ms with those depths on the plain kernel), 32-bit byte offsets inside each operand
     if ((d.K % 8 && !(d.a_km && d.b_km)) || d.lda % 8 || d.ldb % 8 || d.N % 8 || d.ldc % 8) return false;
-    // depth-major operands: batched launches, B or both, columns in whole chunks
-    if (d.a_km || d.b_km) {
+    // depth-major operands: batched launches, B or both, columns in whole chunks; single ones, B
+    if (d.b_km && d.nbatch == 0) {
+        if (d.a_km || d.a_gather || !gemm_depth_major_ld(d.ldb) || !gemm_depth_major_ld(d.lda)) return false;
+        if (d.b_gather && (d.b_rows <= 0 || d.K > (1 << 20) || d.b_rows * d.ldb * 2 >= ((int64_t)1 << 32))) return false;
+        if (d.epilogue != EPI_STORE && d.epilogue != EPI_DUAL_ACC) return false;
+    } else if (d.a_km || d.b_km) {
         if (d.nbatch == 0 || !d.b_km || d.b_gather || (d.a_km && (d.M % 8 || (d.a_gather && !d.a_gather_chunks)))) return false;
         if (!gemm_depth_major_ld(d.ldb) || (d.a_km && !gemm_depth_major_ld(d.lda))) return false;
         for (int z = 0; z < d.nbatch; ++z)
@@ -1580,6 +1703,93 @@ static int uniform_cut(const GemmDesc& d) {
     return d.split_ws && d.a_km ? gemm_choose_ksplit(d.M, d.N, d.K, d.nbatch) : 1;
 }
 
+bool gemm_reads_as_stored(const GemmDesc& d) {
+    if (!d.b_km || d.nbatch > 0 || !gemm_mfma_supported(d)) return false;
+    return d.epilogue == EPI_STORE ? stored_shape<EPI_STORE>(d) : stored_shape<EPI_DUAL_ACC>(d);
+}
+
+namespace {
+
+template <int BX, int BW, int EPIX, int KMX, int KMW>
+int launch_pair(const GemmDesc& dx, const GemmDesc& dw, bool x_first, const char* name, hipStream_t s) {
+    Dev x, w;
+    int rc = describe<BX, BX, EPIX, EPIX == EPI_DUAL_ACC ? OP_DX : OP_DOWN>(dx, x);
+    if (rc == SDP_OK) rc = describe<BW, BW, EPI_STORE, OP_DW>(dw, w);
+    if (rc != SDP_OK) return rc;
+    const int lx = stored_lds<EPIX>(dx, BX == 64 ? T64x64 : T128x128);
+    constexpr int LW = BW == 64 ? Geometry<64, 64, 2, 2, EPI_STORE, KMW>::LDS : Geometry<128, 128, 4, 2, EPI_STORE, KMW>::LDS;
+    const int lds = lx > LW ? lx : LW;
+    if (lds > kMaxLds || dw.nside > 0) return SDP_ERR_INVALID_ARG;
+    auto kern = sdp_gemm_pair_kernel<BX, BW, EPIX, KMX, KMW>;
+    static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, kMaxLds);
+    if (attr != hipSuccess) return SDP_ERR_HIP;
+    ProfileScope ps(name, s);
+    kern<<<dim3((unsigned)(x.ntot + w.ntot)), pair_threads<BX, BW>(), lds, s>>>(x, w, x_first ? 1 : 0);
+    return launch_status();
+}
+
+struct PairPlan {
+    Shape x, w;
+    bool x_first;
+};
+// Side by side in the tiles that each would take alone, a workgroup per CU: worth it when the two, the longer tiles first, are
+// modelled to end in 85 % of the time of one launch after the other (kGap: what a launch costs between two kernels).  Whole steps,
+// one after the other / side by side: two workers at T = 2048, d = 768, p = 1024 160 / 129 us, T = 128, d = 256, p = 256 66 / 57,
+// T = 1504, d = 504, p = 1000 131 / 124; attention of 1500 tokens, 4 of 8 heads of 128 116 / 105, 2 x 256 tokens, 6 heads of 64 53 / 49.
+bool plan_pair(const GemmDesc& x, const GemmDesc& w, PairPlan& plan) {
+    constexpr double kGap = 2.5;
+    if (uniform_cut(w) > 1 || (w.tail_ws && plan_tail(w, nullptr, nullptr) > 1)) return false;
+    const bool dual = x.epilogue == EPI_DUAL_ACC;
+    double cx = 0, cw = 0;
+    const Shape tw = choose_shape<EPI_STORE>(w, w.nbatch, 1, nullptr, &cw);
+    const Shape tx = dual ? choose_shape<EPI_DUAL_ACC>(x, 1, 1, nullptr, &cx) : choose_shape<EPI_STORE>(x, 1, 1, nullptr, &cx);
+    if ((tw != T128x128 && tw != T64x64) || (tx != T128x128 && tx != T64x64) || (tx == T128x128 && tw == T64x64)) return false;
+    if (dual ? !stored_lines<EPI_DUAL_ACC>(x) || stored_lds<EPI_DUAL_ACC>(x, tx) > kMaxLds
+             : !stored_lines<EPI_STORE>(x) || stored_lds<EPI_STORE>(x, tx) > kMaxLds)
+        return false;
+    const int64_t nx = shape_tiles<EPI_STORE>(x, 1, 1, tx), nw = shape_tiles<EPI_STORE>(w, w.nbatch, 1, tw);
+    const double busy = nx + nw < kNumCU ? (double)(nx + nw) / kNumCU : 1.0;
+    const double rx = dual ? round_cost<EPI_DUAL_ACC>(x, 1, tx, busy) : round_cost<EPI_STORE>(x, 1, tx, busy);
+    const double rw = round_cost<EPI_STORE>(w, 1, tw, busy);
+    plan = {tx, tw, rx > rw};
+    const int64_t n1 = plan.x_first ? nx : nw, n2 = plan.x_first ? nw : nx, beside = kNumCU - n1; // long tiles, short ones
+    const double r1 = plan.x_first ? rx : rw, r2 = plan.x_first ? rw : rx;
+    if (beside <= 0) return false;
+    // the short tiles all beside the long ones, or a round of them there and the others behind both
+    const double all_beside = (double)((n2 + beside - 1) / beside) * r2, behind = n2 - beside <= kNumCU ? r1 + r2 : 1e30;
+    const double end = all_beside < behind ? all_beside : behind;
+    return (end > r1 ? end : r1) < 0.85 * (cx + cw + kGap);
+}
+
+} // namespace
+
+bool gemm_pairs(const GemmDesc& x, const GemmDesc& w) {
+    PairPlan plan;
+    if (!x.b_km || x.nbatch > 0 || w.nbatch < 1 || w.nside > 0 || !w.b_km) return false;
+    if (x.epilogue == EPI_STORE ? !w.a_km : x.b_gather && !w.a_km) return false; // not among the kernels of gemm_mfma_pair
+    return gemm_mfma_supported(x) && gemm_mfma_supported(w) && plan_pair(x, w, plan);
+}
+
+int gemm_mfma_pair(const GemmDesc& x, const GemmDesc& w, const char* name, hipStream_t s) {
+    PairPlan plan;
+    if (!gemm_pairs(x, w) || !plan_pair(x, w, plan)) return SDP_ERR_UNSUPPORTED;
+    auto go = [&](auto epi, auto kmx, auto kmw) {
+        constexpr int EPI = decltype(epi)::value, KMX = decltype(kmx)::value, KMW = decltype(kmw)::value;
+        if (plan.x == T128x128) return launch_pair<128, 128, EPI, KMX, KMW>(x, w, plan.x_first, name, s);
+        if (plan.w == T128x128) return launch_pair<64, 128, EPI, KMX, KMW>(x, w, plan.x_first, name, s);
+        return launch_pair<64, 64, EPI, KMX, KMW>(x, w, plan.x_first, name, s);
+    };
+    using std::integral_constant;
+    constexpr integral_constant<int, EPI_DUAL_ACC> dual{};
+    constexpr integral_constant<int, EPI_STORE> store{};
+    constexpr integral_constant<int, 2> right{};
+    constexpr integral_constant<int, 3> both{};
+    constexpr integral_constant<int, 6> listed{};
+    if (x.epilogue == EPI_STORE) return x.b_gather ? go(store, listed, both) : go(store, right, both);
+    if (!w.a_km) return go(dual, right, right); // backward masking
+    return x.b_gather ? go(dual, listed, both) : go(dual, right, both);
+}
+
 bool gemm_carries(const GemmDesc& d) {
     if (!gemm_mfma_supported(d)) return false;
     if (d.epilogue == EPI_SWIGLU_BWD) return would_carry<EPI_SWIGLU_BWD>(d, 1);
@@ -1612,6 +1822,11 @@ int gemm_mfma_bf16(const GemmDesc& d, hipStream_t s) {
         ProfileScope ps("splitk_reduce", s);
         splitk_reduce_kernel<<<(unsigned)((threads + 255) / 256), 256, 0, s>>>(ra);
         return launch_status();
+    }
+    if (d.b_km && d.nbatch == 0) {
+        if (!gemm_reads_as_stored(d)) return SDP_ERR_UNSUPPORTED;
+        if (d.epilogue == EPI_STORE) return d.b_gather ? launch_cfg<64, 64, 2, 2, EPI_STORE, OP_DOWN, 6>(d, 0, s) : launch_cfg<64, 64, 2, 2, EPI_STORE, OP_DOWN, 2>(d, 0, s);
+        return d.b_gather ? launch_cfg<64, 64, 2, 2, EPI_DUAL_ACC, OP_DX, 6>(d, 0, s) : launch_cfg<64, 64, 2, 2, EPI_DUAL_ACC, OP_DX, 2>(d, 0, s);
     }
     if (d.epilogue == EPI_STORE && d.nbatch == 0) return launch<EPI_STORE, OP_DOWN>(d, s);
     if (d.epilogue == EPI_DUAL_ACC) return launch<EPI_DUAL_ACC, OP_DX>(d, s);

@@ -82,6 +82,15 @@ __device__ inline int listed_row(const int32_t* list, const HeadList& h, int i) 
     return first + list[k] * w + (i - k * w);
 }
 
+// the same for a list of heads alone (width > 0)
+__device__ inline int head_row(const int32_t* list, const HeadList& h, int i) {
+    int first = 0;
+    if (i >= h.held) i -= h.held, first += h.all;
+    if (i >= h.held) i -= h.held, first += h.all;
+    const int k = (int)__umulhi((uint32_t)i, h.magic);
+    return first + list[k] * h.width + (i - k * h.width);
+}
+
 // ---- contraction descriptor --------------------------------------------------------------------
 // C[M][N] = sum_k A(m,k) * B(k,n), fp32 accumulation, all matrices row-major.
 //   A(m,k) = a_km ? A[k * lda + m] : A[ra(m) * lda + k]  (a_km: A is stored depth-major, [K][M])
@@ -190,6 +199,12 @@ int gemm_simple(const GemmDesc& g, hipStream_t s);
 // bf16 MFMA contraction; returns SDP_ERR_UNSUPPORTED when the shape / alignment does not fit.
 int gemm_mfma_bf16(const GemmDesc& g, hipStream_t s);
 bool gemm_mfma_supported(const GemmDesc& g);
+// whether a launch of g alone, a single problem with a depth-major right operand (STORE or DUAL_ACC), is one for gemm_mfma_bf16
+bool gemm_reads_as_stored(const GemmDesc& g);
+// x, such a problem, and w, a batched one without a depth cut, none of whose outputs shares memory with an operand, as one launch:
+// the same bits as in two.  gemm_pairs: whether they are worth it, from sizes and layouts; SDP_ERR_UNSUPPORTED where they are not.
+bool gemm_pairs(const GemmDesc& x, const GemmDesc& w);
+int gemm_mfma_pair(const GemmDesc& x, const GemmDesc& w, const char* name, hipStream_t s);
 // rows that the MFMA contraction can read depth-major: 64 of them lie within 32-bit byte offsets
 inline bool gemm_depth_major_ld(int64_t ld) { return ld < (int64_t)1 << 22; }
 // whether the launch of g (SWIGLU_BWD, or batched without a depth cut) would carry g.side

@@ -142,6 +142,18 @@ int sdp::mlp_fwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
     const TransposeJob wt{W2T, W2c, d, ldn, gather, n, d};
     const bool w2_first = dtype == SDP_F32 ? overlap({{Y, (size_t)T * d * e}, {G_save, out_b}, {U_save, out_b}}, {{W2T, w2_b}})
                                            : overlap({{G_save, out_b}, {U_save, out_b}}, {{W2T, w2_b}});
+    GemmDesc dn;
+    dn.name = "mlp_down";
+    dn.M = T, dn.N = d, dn.K = n;
+    dn.A = Act, dn.lda = ldn;
+    dn.epilogue = EPI_STORE;
+    dn.C = Y, dn.ldc = d;
+    dn.R = residual, dn.ldr = d;
+    // W2T itself, depth-major: fp32 (no output may take its place), and bf16 where the contraction takes it so
+    GemmDesc as_stored = dn;
+    as_stored.B = W2T, as_stored.ldb = d, as_stored.b_km = 1, as_stored.b_gather = gather, as_stored.b_rows = F;
+    const bool stored = dtype == SDP_F32 ? !w2_first
+                                         : !overlap({{Y, (size_t)T * d * e}, {G_save, out_b}, {U_save, out_b}}, {{W2T, w2_b}}) && gemm_reads_as_stored(as_stored);
     if (w2_first) {
         rc = dtype == SDP_F32 ? copy_rows_f32((const float*)W2T, gather, n, d, (float*)W2c, "mlp_wt_fwd", s)
                               : transpose_batch(&wt, 1, "mlp_wt_fwd", s);
@@ -154,20 +166,13 @@ int sdp::mlp_fwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
     gu.B = W1, gu.B2 = W3, gu.ldb = d, gu.b_gather = gather, gu.b_rows = F;
     gu.epilogue = EPI_SWIGLU_FWD;
     gu.C = G_save, gu.C2 = U_save, gu.ldc = n, gu.C3 = Act, gu.ldc3 = ldn;
-    if (dtype == SDP_BF16 && !w2_first) gu.side = &wt, gu.nside = 1, gu.side_name = "mlp_wt_fwd";
+    if (dtype == SDP_BF16 && !w2_first && !stored) gu.side = &wt, gu.nside = 1, gu.side_name = "mlp_wt_fwd";
     rc = run(dtype, gu, s);
     if (rc != SDP_OK) return rc;
 
-    GemmDesc dn;
-    dn.name = "mlp_down";
-    dn.M = T, dn.N = d, dn.K = n;
-    dn.A = Act, dn.lda = ldn;
-    if (dtype == SDP_BF16) dn.B = W2c, dn.ldb = ldn;
-    else if (w2_first) dn.B = W2c, dn.ldb = d, dn.b_km = 1, dn.b_rows = n;
-    else dn.B = W2T, dn.ldb = d, dn.b_km = 1, dn.b_gather = gather, dn.b_rows = F;
-    dn.epilogue = EPI_STORE;
-    dn.C = Y, dn.ldc = d;
-    dn.R = residual, dn.ldr = d;
+    if (stored) return run(dtype, as_stored, s);
+    dn.B = W2c, dn.ldb = ldn;
+    if (dtype == SDP_F32) dn.ldb = d, dn.b_km = 1, dn.b_rows = n;
     return run(dtype, dn, s);
 }
 
@@ -334,33 +339,43 @@ int sdp::mlp_bwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
         rc = column_ranks(idx_k, p, F, ranks, s);
         if (rc != SDP_OK) return rc;
     }
-    // the operand copies that dX and the plain weight gradients read, made beside dact, which needs none of them, or beside the
+    // dX reads W1 and W3 as they are stored where the contraction takes them so and no output takes their place
+    GemmDesc dx;
+    dx.name = "mlp_dx";
+    dx.M = T, dx.N = d, dx.K = n;
+    dx.A = dG, dx.A2 = dU, dx.lda = ldn;
+    dx.epilogue = EPI_DUAL_ACC;
+    dx.C = dX, dx.ldc = d;
+    dx.R = dx_residual, dx.ldr = d;
+    GemmDesc as_stored = dx;
+    as_stored.B = W1, as_stored.B2 = W3, as_stored.ldb = d, as_stored.b_km = 1, as_stored.b_gather = gather, as_stored.b_rows = F;
+    const size_t w_b = (size_t)F * d * e, out_b = want_dw ? dw_b : 0;
+    const bool apart = !overlap({{dX, tok_b}, {dW1, out_b}, {dW3, out_b}, {dW2T, out_b}}, {{W1, w_b}, {W3, w_b}});
+    // and in the launch of the weight gradients, where dX does not take the place of what those read
+    const bool pair = fused && apart && !overlap({{dX, tok_b}}, {{X, tok_b}, {dY, tok_b}}) && gemm_pairs(as_stored, dw);
+    const bool stored = pair || (apart && gemm_reads_as_stored(as_stored));
+    // otherwise the operand copies that dX and the plain weight gradients read, made beside dact, which needs none of them, or beside the
     // weight gradients where dact's tiles leave no CU idle
     const TransposeJob tj[4] = {{W1, W1c, d, ldn, gather, n, d},
                                 {W3, W3c, d, ldn, gather, n, d},
                                 {X, XT, d, ldt, nullptr, T, d},
                                 {dY, dYT, d, ldt, nullptr, T, d}};
-    da.side = tj, da.nside = want_dw && !fused ? 4 : 2, da.side_name = "mlp_tr_bwd";
-    if (fused && !overlap({{dW1, dw_b}, {dW3, dw_b}, {dW2T, dw_b}}, {{W1, (size_t)F * d * e}, {W3, (size_t)F * d * e}})) {
+    const int first = stored ? 2 : 0;
+    da.side = tj + first, da.nside = (want_dw && !fused ? 4 : 2) - first, da.side_name = "mlp_tr_bwd";
+    if (fused && !stored && !overlap({{dW1, dw_b}, {dW3, dw_b}, {dW2T, dw_b}}, {{W1, (size_t)F * d * e}, {W3, (size_t)F * d * e}})) {
         dw.side = tj, dw.nside = 2, dw.side_name = "mlp_tr_bwd";
         if (gemm_carries(da) || !gemm_carries(dw)) dw.nside = 0; else da.nside = 0;
     }
     rc = run(dtype, da, s);
     if (rc != SDP_OK) return rc;
 
+    if (pair) return gemm_mfma_pair(as_stored, dw, "mlp_dx_dw", s);
     if (fused) {
         rc = gemm_mfma_bf16(dw, s);
         if (rc != SDP_OK) return rc;
     }
-    GemmDesc dx;
-    dx.name = "mlp_dx";
-    dx.M = T, dx.N = d, dx.K = n;
-    dx.A = dG, dx.A2 = dU, dx.lda = ldn;
     dx.B = W1c, dx.B2 = W3c, dx.ldb = ldn;
-    dx.epilogue = EPI_DUAL_ACC;
-    dx.C = dX, dx.ldc = d;
-    dx.R = dx_residual, dx.ldr = d;
-    rc = run(dtype, dx, s);
+    rc = run(dtype, stored ? as_stored : dx, s);
     if (rc != SDP_OK) return rc;
 
     if (fused || !want_dw) return SDP_OK;

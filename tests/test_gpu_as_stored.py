@@ -1,0 +1,69 @@
+"""GPU: small bf16 contractions that read the weights as they are stored (down, dX, the attention's out and dX), and dX beside the
+weight gradients in one launch: partial tiles and depth steps, lists of depth rows at the length that still fits, and the same bits
+whether or not the launches could be merged.  Tolerances: test_gpu_mlp.py, test_gpu_random_shapes.py (few tokens)."""
+import pytest
+import torch
+
+import test_gpu_mlp as mlp
+from test_gpu_depth_major import _Launches, _attention, _inputs
+from workloads import MlpWorkload
+
+pytestmark = pytest.mark.gpu
+sdp = mlp.sdp  # the fixture
+
+CASES = [MlpWorkload(f"stored_{T}x{d}p{p}_{mode}", "bf16", T, d, F, p, 2, mode, 71) for T, d, F, p, mode in (
+    (8, 8, 16, 8, "fm"), (72, 72, 136, 120, "fm"), (56, 200, 264, 136, "bm"), (64, 64, 128, 64, "fm"), (136, 328, 72, 64, "bm"),
+    (1032, 264, 520, 264, "fm"),      # 128 x 128 tiles side by side
+    (1032, 264, 520, 264, "bm"),
+    (64, 64, 8200, 8192, "fm"),       # the longest list behind 64 x 64 tiles
+    (64, 64, 8216, 8200, "fm"),       # one chunk longer: transposed copies
+    (64, 72, 2600, 2568, "fm"))]      # rows that are no whole lines, 41 steps: transposed copies
+
+
+@pytest.mark.parametrize("w", CASES, ids=[w.name for w in CASES])
+def test_mlp_weights_as_stored(sdp, orc, w):
+    mlp.run_case(sdp, orc, w, [1], dw_layout="scatter" if w.mode == "bm" else "compact", dw_elem_tol=4e-2)
+
+
+# tiles of 64 x 64 for both; of 64 x 64 beside 128 x 128; of 128 x 128 for both
+@pytest.mark.parametrize("T,d,F,p", [(136, 72, 264, 200), (1024, 768, 1288, 1024), (2048, 768, 1032, 1024)])
+@pytest.mark.parametrize("mode", ["fm", "bm"])
+def test_mlp_same_bits_beside_the_weight_gradients_and_alone(sdp, mode, T, d, F, p):
+    X, dY, W = _inputs(T, d, F, 9)
+    idx = sdp.make_masks(2, F, p, 5, True)[1][0].contiguous()
+    _, G, U = sdp.masked_mlp_fwd(mode, X, *W, idx)
+    with _Launches(sdp) as n:
+        want = sdp.masked_mlp_bwd(mode, X, dY, *W, idx, G, U)
+    if mode == "fm":
+        assert n["mlp_dx_dw"] == 1, n
+    fresh = [torch.empty_like(t) for t in want]
+    dy, w3 = dY.clone(), W[1].clone()
+    with _Launches(sdp) as n:  # dX over dY, which the weight gradients read
+        got = sdp.masked_mlp_bwd(mode, X, dy, *W, idx, G, U, out=(dy, *fresh[1:]))
+    assert n["mlp_dx_dw"] == 0 and n["mlp_dx"] == 1, n
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
+    got = sdp.masked_mlp_bwd(mode, X, dY, W[0], w3, W[2], idx, G, U, out=(fresh[0], fresh[1], w3[:p], fresh[3]))  # dW3 over W3
+    for a, b in zip(got, want):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("hd,S", [(64, 100), (50, 77), (128, 333)])
+@pytest.mark.parametrize("mode", ["fm", "bm"])
+def test_attention_same_bits_beside_the_weight_gradients_and_alone(sdp, mode, hd, S):
+    Bt, H, ph = 2, 4, 2
+    X, dY, Wqkv, WoT, heads, (QKV, O, LSE) = _attention(sdp, mode, Bt, S, 200, H, hd, ph, 4)
+    a = (mode, Bt, S, hd)
+    with _Launches(sdp) as n:
+        want = sdp.masked_attn_bwd(*a, X, dY, Wqkv, WoT, heads, QKV, O, LSE)
+    assert n["attn_dx_dw"] == 1, n
+    fresh = [torch.empty_like(t) for t in want]
+    x, wq = X.clone(), Wqkv.clone()
+    with _Launches(sdp) as n:
+        got = sdp.masked_attn_bwd(*a, x, dY, Wqkv, WoT, heads, QKV, O, LSE, out=(x, *fresh[1:]))  # dX over X
+    assert n["attn_dx_dw"] == 0 and n["attn_dx"] == 1, n
+    for r, w in zip(got, want):
+        assert torch.equal(r, w)
+    got = sdp.masked_attn_bwd(*a, X, dY, wq, WoT, heads, QKV, O, LSE, out=(fresh[0], wq.view(-1)[: want[1].numel()].view(want[1].shape), fresh[2]))
+    for r, w in zip(got, want):
+        assert torch.equal(r, w)
