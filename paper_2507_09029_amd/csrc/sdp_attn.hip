@@ -173,6 +173,26 @@ struct TileMover {
         for (int i = 0; i < PER; ++i)
             *(u32x4*)(tile + (tid / CPR + 64 * NW / CPR * i) * row_bytes(HW) + col * 16) = pad ? u32x4{0u, 0u, 0u, 0u} : v[i];
     }
+    // dot products of the tile's rows with those of another tile (of one wave): the CPR lanes of a group hold rows group + 8 i;
+    // lane i of the group, i < PER, returns row dot_row
+    __device__ static int dot_row(int tid) { return tid / CPR + 64 * NW / CPR * (tid % CPR); }
+    __device__ float row_dots(const TileMover& o, int tid) const {
+        static_assert(NW == 1 && PER <= CPR, "a lane for every row");
+        float out = 0.f;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            float d = 0.f;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                d = __builtin_fmaf(__uint_as_float(v[i][j] << 16), __uint_as_float(o.v[i][j] << 16), d);
+                d = __builtin_fmaf(__uint_as_float(v[i][j] & 0xFFFF0000u), __uint_as_float(o.v[i][j] & 0xFFFF0000u), d);
+            }
+#pragma unroll
+            for (int m = 1; m < CPR; m <<= 1) d += __shfl_xor(d, m, 64);
+            if (tid % CPR == i) out = d;
+        }
+        return out;
+    }
 };
 
 // a row of HW bf16 as the depth-along-row operand of lane (row, lhi): sub-step s holds depth 16 s + 8 lhi .. + 7
@@ -562,7 +582,7 @@ void attn_fwd_kernel(CoreArgs a, int nblocks, int nbh, SideJobs side) {
 template <int HW, int KW>
 constexpr int dq_lds() { return KW == 1 ? 2 * 64 * row_bytes(HW) : KW * wave_lds(HW); }
 
-template <int HW, int KW>
+template <int HW, int KW, bool STORE_DELTA = true>
 __device__ inline void attn_bwd_dq_block(const CoreArgs& a, const int q0, const int head, const int b, unsigned char* lds) {
     constexpr int KS = HW / 16, JB = HW / 32;
     constexpr int TR = KW == 1 ? 64 : 32; // keys per tile
@@ -590,7 +610,7 @@ __device__ inline void attn_bwd_dq_block(const CoreArgs& a, const int q0, const 
         delta += other_half(delta);
     }
     const int64_t stat = ((int64_t)b * a.ph + head) * S;
-    if (qrow < S && lhi == 0 && (KW == 1 || wave == 0)) a.delta[stat + qrow] = delta;
+    if (STORE_DELTA && qrow < S && lhi == 0 && (KW == 1 || wave == 0)) a.delta[stat + qrow] = delta;
     const float L2 = a.lse[stat + qc];
 
     const int first = KW == 1 ? 0 : TR * wave, step = TR * KW;
@@ -711,9 +731,12 @@ struct DkvShape {
     static_assert(LDS <= 160 * 1024, "LDS of one CU");
 };
 
-template <int HW, int KW>
+// OWN_DELTA: the queries' delta is computed from their dO and O rows as the tile is staged (every wave its own tile), in the place
+// of what the dQ kernel has left.
+template <int HW, int KW, bool OWN_DELTA = false>
 __device__ inline void attn_bwd_dkv_block(const CoreArgs& a, const int k0, const int head, const int b, unsigned char* lds) {
     using Shape = DkvShape<HW, KW>;
+    static_assert(!OWN_DELTA || (KW > 1 && HW == HD), "a wave's own tile, in registers that are left");
     constexpr int KS = HW / 16, JB = HW / 32, QT = Shape::QT;
     constexpr bool kVInLds = Shape::kVInLds, kKInLds = Shape::kKInLds;
     const int hd = HW == HD ? HD : a.hd;
@@ -758,27 +781,36 @@ __device__ inline void attn_bwd_dkv_block(const CoreArgs& a, const int k0, const
     // tile t holds the queries QT (t0 + KW t) ..; t0 lies at the diagonal, which lies inside the sequence (k0 < S)
     const int t0 = k0 / QT + (KW == 1 ? 0 : wave), tend = (S + QT - 1) / QT;
     const int ntiles = tend > t0 ? (tend - t0 + KW - 1) / KW : 0;
-    TileMover<KW == 1 ? NW : 1, HW, QT> pq, po;
+    TileMover<KW == 1 ? NW : 1, HW, QT> pq, po, px; // px: O, for delta
+    const uint16_t* gX = OWN_DELTA ? a.o + (int64_t)b * S * a.ldo + head * hd : nullptr;
     const int mt = KW == 1 ? tid : lane;
     const uint32_t ldq32 = (uint32_t)a.ldq, ldo32 = (uint32_t)a.ldo;
     // per-query statistics of a tile: threads 0 .. QT - 1 carry the log-sum-exp, QT .. 2 QT - 1 delta
-    const float* gstat = (mt < QT ? a.lse : a.delta) + stat;
+    const float* gstat = (OWN_DELTA || mt < QT ? a.lse : a.delta) + stat;
     const int sq = mt % QT;
     auto stat_of = [&](int q) { return gstat[q < S ? q : S - 1]; };
     pq.fetch(gQ, ldq32, QT * t0, S - 1, hd, mt);
     po.fetch(gO, ldo32, QT * t0, S - 1, hd, mt);
+    if constexpr (OWN_DELTA) px.fetch(gX, ldo32, QT * t0, S - 1, hd, mt);
     float pstat = stat_of(QT * t0 + sq);
     for (int t = 0; t < ntiles; ++t) {
         if constexpr (KW == 1) __syncthreads(); else wave_sync();
         pq.stash(sQ, hd, mt);
         po.stash(sO, hd, mt);
-        if (mt < 2 * QT) sL[mt] = pstat;
+        if constexpr (OWN_DELTA) {
+            if (mt < QT) sL[mt] = pstat;
+            const float d = po.row_dots(px, mt); // of the tile's row that this lane is to put away
+            if (mt % TileMover<1, HW, QT>::CPR < TileMover<1, HW, QT>::PER) sD[po.dot_row(mt)] = d;
+        } else {
+            if (mt < 2 * QT) sL[mt] = pstat;
+        }
         if constexpr (KW == 1) __syncthreads(); else wave_sync();
         // the next tile (rows are clamped)
         const int qt0 = QT * (t0 + KW * t), next = qt0 + QT * KW;
         if (always_fetch(HW, KW) || t + 1 < ntiles) {
             pq.fetch(gQ, ldq32, next, S - 1, hd, mt);
             po.fetch(gO, ldo32, next, S - 1, hd, mt);
+            if constexpr (OWN_DELTA) px.fetch(gX, ldo32, next, S - 1, hd, mt);
             pstat = stat_of(next + sq);
         }
         if (qt0 + QT - 1 < krow0) continue; // wave-uniform: every query of the tile lies before the wave's keys
@@ -880,6 +912,25 @@ void attn_bwd_dkv_kernel(CoreArgs a, int nblocks, int nbh, SideJobs side) {
     attn_bwd_dkv_block<HW, KW>(a, (nblocks - 1 - blk) * Split<KW>::ROWS, head, b, lds);
 }
 
+// dK, dV and dQ as one launch, where the walked axis is split and heads are at most 64 wide: either alone leaves CUs idle, and what
+// a launch costs between two kernels is a sixteenth of such a call.  dK/dV then takes delta from dO and O itself; wider heads have no
+// registers left for O's rows.  Forward and backward of an attention, two launches / one: 2 x 256 tokens, 6 heads of 64 47 / 42.7 us,
+// 1 x 64, 4 of 50 44 / 39, 4 x 100, 12 of 50 50.5 / 46, 1 x 1024, 12 of 64 80.5 / 75.7, 2 x 1024, 12 122 / 119, 1 x 2048, 14 166 / 167.
+constexpr bool merged(int hw, int kw) { return hw == HD && kw == 4; }
+template <int HW, int KW>
+__global__ __launch_bounds__(Split<KW>::THREADS) __attribute__((amdgpu_waves_per_eu(waves_dkv(HW, KW), waves_dkv(HW, KW))))
+void attn_bwd_kernel(CoreArgs a, int nblocks, int nbh, SideJobs side) {
+    constexpr int LDS = dq_lds<HW, KW>() > DkvShape<HW, KW>::LDS ? dq_lds<HW, KW>() : DkvShape<HW, KW>::LDS;
+    __shared__ __attribute__((aligned(16))) unsigned char lds[LDS];
+    const int nitems = nblocks * nbh;
+    const int id = workgroup_id();
+    if (id >= 2 * nitems) return carried<sizeof(lds), Split<KW>::THREADS>(side, id - 2 * nitems, lds);
+    int blk, head, b;
+    causal_item(id < nitems ? id : id - nitems, nitems, nbh, nblocks, a.ph, blk, head, b);
+    if (id < nitems) attn_bwd_dkv_block<HW, KW, true>(a, (nblocks - 1 - blk) * Split<KW>::ROWS, head, b, lds);
+    else attn_bwd_dq_block<HW, KW, false>(a, blk * Split<KW>::ROWS, head, b, lds);
+}
+
 // KW = 4 up to this many workgroups of the KW = 1 form, i.e. while those leave CUs idle: its shorter chains then weigh
 // more than the re-reads.  Block forward + backward in us, KW = 1 / KW = 4: heads of 64, 96 workgroups (1 x 1024 tokens,
 // 12 heads) 158 / 124, 192 (2 x 1024) 168 / 149, 384 (4 x 1024) 184 / 187; heads of 128, 64 workgroups (1 x 1024, 8 heads)
@@ -893,23 +944,32 @@ constexpr int split_below(int hw) { return hw == HD ? 256 : 192; }
 // (1 x 512, 8 heads 61 / 62; 1 x 2048 109 / 124): their tiles are half as long.
 inline bool split_in_eight(int hw, int64_t S, int64_t nbh) { return hw > HD && S >= 512 && (S + 31) / 32 * nbh * 4 <= S; }
 
-enum CoreKernel { CORE_FWD, CORE_DQ, CORE_DKV };
+enum CoreKernel { CORE_FWD, CORE_DQ, CORE_DKV, CORE_BWD };
 template <int HW, int KW>
 int launch_core(CoreKernel which, const CoreArgs& a, int nbh, const SideJobs& side, hipStream_t s) {
     const int nblocks = (a.S + Split<KW>::ROWS - 1) / Split<KW>::ROWS;
-    auto grid = [&](int lds) {
+    auto grid = [&](int lds, int kernels = 1) {
         constexpr int HALVES = Split<KW>::THREADS / 256;
         const int per = side_tiles(lds / HALVES) * HALVES;
-        return workgroup_grid((int64_t)nblocks * nbh + (side.end[kMaxTransposeJobs - 1] + per - 1) / per);
+        return workgroup_grid((int64_t)nblocks * nbh * kernels + (side.end[kMaxTransposeJobs - 1] + per - 1) / per);
     };
+    if constexpr (merged(HW, KW)) {
+        constexpr int LDS = dq_lds<HW, KW>() > DkvShape<HW, KW>::LDS ? dq_lds<HW, KW>() : DkvShape<HW, KW>::LDS;
+        if (which == CORE_BWD) {
+            attn_bwd_kernel<HW, KW><<<grid(LDS, 2), Split<KW>::THREADS, 0, s>>>(a, nblocks, nbh, side);
+            return launch_status();
+        }
+    }
     if (which == CORE_FWD) attn_fwd_kernel<HW, KW><<<grid(fwd_lds<HW, KW>()), Split<KW>::THREADS, 0, s>>>(a, nblocks, nbh, side);
     else if (which == CORE_DQ) attn_bwd_dq_kernel<HW, KW><<<grid(dq_lds<HW, KW>()), Split<KW>::THREADS, 0, s>>>(a, nblocks, nbh, side);
     else attn_bwd_dkv_kernel<HW, KW><<<grid(DkvShape<HW, KW>::LDS), Split<KW>::THREADS, 0, s>>>(a, nblocks, nbh, side);
     return launch_status();
 }
+int64_t whole_walks(int64_t S, int64_t nbh) { return (S + Split<1>::ROWS - 1) / Split<1>::ROWS * nbh; } // workgroups of a launch with KW = 1
+bool merged_backward(const CoreArgs& a, int64_t nbh) { return a.hd <= HD && whole_walks(a.S, nbh) <= split_below(HD); }
 template <int HW>
 int launch_core(CoreKernel which, const CoreArgs& a, int64_t nbh, const SideJobs& side, hipStream_t s) {
-    const int64_t wide = (a.S + Split<1>::ROWS - 1) / Split<1>::ROWS * nbh; // workgroups of the launch with KW = 1
+    const int64_t wide = whole_walks(a.S, nbh);
     if (wide > INT32_MAX / 2) return SDP_ERR_UNSUPPORTED;
     if constexpr (HW > HD) {
         if (split_in_eight(HW, a.S, nbh)) return launch_core<HW, 8>(which, a, (int)nbh, side, s);
@@ -1330,9 +1390,11 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
                                            {dY, w.dYt, d, ldt, nullptr, T, d}};
         const TransposeJob beside_dkv{w.dQKV, w.dQKVt, 3 * E, ldt, nullptr, T, E}; // dQ
         const int skip = stored ? 1 : 0; // dX needs no copy of Wqkv
-        rc = launch_core(CORE_DQ, a, (int64_t)hr * Bt, beside_dq + skip, (want_dw && !direct ? 4 : 1) - skip, "attn_core_bwd_dq", s);
+        const bool one = merged_backward(a, (int64_t)hr * Bt) && (direct || !want_dw);
+        rc = launch_core(one ? CORE_BWD : CORE_DQ, a, (int64_t)hr * Bt, beside_dq + skip, (want_dw && !direct ? 4 : 1) - skip,
+                         one ? "attn_core_bwd" : "attn_core_bwd_dq", s);
         // reads the delta written by the dQ kernel
-        if (rc == SDP_OK) rc = launch_core(CORE_DKV, a, (int64_t)hr * Bt, &beside_dkv, want_dw && !direct ? 1 : 0, "attn_core_bwd_dkv", s);
+        if (rc == SDP_OK && !one) rc = launch_core(CORE_DKV, a, (int64_t)hr * Bt, &beside_dkv, want_dw && !direct ? 1 : 0, "attn_core_bwd_dkv", s);
         if (rc != SDP_OK) return rc;
     } else {
         AttnCoreDesc c;
