@@ -1525,10 +1525,12 @@ int stored_lds(const GemmDesc& d, Shape shape) {
 // The 128 bytes that a 64-wide tile takes of a stored row are one line where rows are whole lines, else two: worth it for short
 // depths alone then.  Event times of down, dX and the launches that made or carried the copies, two workers at T = 304, p = 4000
 // (4032): d = 600 89 us with copies, 91 without; d = 640 84, 81; whole steps: T = 2000, d = 400, p = 2400 189 -> 197, T = 1176,
-// d = 456, F = 5472 308 -> 323, but T = 1504, d = 504, p = 1000 131 -> 124.
+// d = 456, F = 5472 308 -> 323, but T = 1504, d = 504, p = 1000 131 -> 124.  A launch of its own has only the copy to win, and
+// down at T = 928, d = 376, p = 1832 (29 steps) lost by it, four workers 267 -> 271 us; 20 steps (T = 520, d = 1888, p = 1272,
+// eight workers 766 -> 743) are taken.
 template <int EPI>
-bool stored_lines(const GemmDesc& d) {
-    return d.ldb % 64 == 0 || (d.K + BK - 1) / BK * (EPI == EPI_DUAL_ACC ? 2 : 1) <= 40;
+bool stored_lines(const GemmDesc& d, int most = 40) {
+    return d.ldb % 64 == 0 || (d.K + BK - 1) / BK * (EPI == EPI_DUAL_ACC ? 2 : 1) <= most;
 }
 // In a launch of its own: 64 x 64 tiles.  A transposing pair of reads costs what two row-major reads do, so that the larger tiles do
 // better with the copies that other launches carry (block of 4 x 1024 tokens, d = 1200, F = 3200 and its masked neighbour 1068 -> 1098 us
@@ -1537,7 +1539,7 @@ bool stored_lines(const GemmDesc& d) {
 // attention of 500 tokens, 28 heads of 64 113 / 104.
 template <int EPI>
 bool stored_shape(const GemmDesc& d) {
-    return choose_shape<EPI>(d, 1, 1) == T64x64 && stored_lines<EPI>(d) && stored_lds<EPI>(d, T64x64) <= kMaxLds;
+    return choose_shape<EPI>(d, 1, 1) == T64x64 && stored_lines<EPI>(d, EPI == EPI_DUAL_ACC ? 40 : 20) && stored_lds<EPI>(d, T64x64) <= kMaxLds;
 }
 
 // Whether the launch of `d` is one to give its transposes to.  Their workgroups take 16 tiles each beside 256 x 256 and 128 x 256,
