@@ -8,11 +8,13 @@
 //
 // What bounds it: the matrix cores give 157 TFLOP/s (a plain fp32 FMA half of that), i.e. 32 cycles per 16x16x4 tile, so
 // operand traffic is cheap here (a wave reads 4 KB of LDS per 512 matrix cycles) and the shapes that use fp32 are small:
-// latency, launches and idle CUs decide.  Hence three tiles, one loop:
-//   128 x 128 (4 waves of 64 x 64), 64 x 64 (4 waves of 32 x 32), and 32 x 32 whose 4 waves share one tile and split its
-//   depth (each takes 16 of every 64 depth steps; their sums meet in LDS), for launches with fewer tiles than CUs;
-//   the smallest launches take 16 x 16 tiles in a loop of their own (further down).
-// Tiles move global -> registers -> LDS, the next three steps in registers (one for the 128-wide tile); one barrier per step.
+// latency, launches and idle CUs decide.  Hence three loops:
+//   64 x 64 and 128 x 128 outputs a workgroup, pipelined (gemm_f32_pipe_kernel): where these fill the CUs;
+//   16 x 16 and 32 x 32 outputs a workgroup, whose four waves split the depth (gemm_f32_wave_kernel): launches of few tiles;
+//   32 x 32 with the depth split inside each step of 64 (gemm_f32_kernel, also 64 and 128 wide for lists beyond kListMax): between
+//   the two.
+// The first two fill LDS by direct loads, 16 bytes a lane or, where extents or strides are no multiples of 4 or columns are
+// gathered, 4; the third moves global -> registers -> LDS, the next three steps in registers, one barrier per step.
 //
 // A depth slot is free to stand for any k as long as both operands agree: in a group of 16 depth steps, lane group
 // g = lane / 16 takes k = 4 g + j in the j-th of four MFMAs, so an operand stored by rows is one 16-byte LDS read per
@@ -397,33 +399,40 @@ constexpr int kListMax = 4096; // entries of a gathered depth's list that are ke
 // source of the chunks beyond the depth
 __device__ __attribute__((aligned(16))) const float kZero4[4] = {0.f, 0.f, 0.f, 0.f};
 
-template <int B, bool DM>
+// V: 16-byte loads (aligned base and stride, extent along the contiguous axis a multiple of 4), a lane fills a chunk.  Else 4-byte
+// ones, a lane fills one float, which also lets a depth-major operand gather its columns (the weight gradients' list of neurons).
+template <int B, bool DM, bool V>
 struct WaveOperand {
-    static constexpr int BYTES = B * 128, SLABS = BYTES / 1024; // of one step; direct loads a step
-    static constexpr int CPR = DM ? B / 4 : 8;                  // chunks per LDS row
-    static constexpr int RPS = 64 / CPR;                        // LDS rows per slab
-    const float* p[DM ? 1 : SLABS]; // rows: this lane's chunk of each slab at depth 0; depth-major: its first column
-    int k[SLABS];                   // depth of that chunk within a step
+    static constexpr int BYTES = B * 128, SLABS = BYTES / (V ? 1024 : 256); // of one step; direct loads a step
+    static constexpr int CPR = DM ? B / 4 : 8;                              // chunks per LDS row
+    static constexpr int LPR = V ? CPR : 4 * CPR, RPS = 64 / LPR;           // lanes per LDS row, LDS rows per slab
+    // rows: this lane's place in each slab at depth 0; depth-major: its first column (4-byte loads of 32 columns: two, those of the
+    // even slabs and those of the odd ones)
+    static constexpr int NP = DM ? (!V && B == 32 ? 2 : 1) : SLABS;
+    const float* p[NP];
+    int k[SLABS]; // depth of that place within a step
     int64_t ld;
     __device__ void init(const float* base, int64_t ld_, int rows, int row0, const int32_t* gather, int lane) {
         ld = ld_;
-        const int pos = lane % CPR;
+        const int pos = lane % LPR;
 #pragma unroll
         for (int i = 0; i < SLABS; ++i) {
-            const int q = RPS * i + lane / CPR; // LDS row
+            const int q = RPS * i + lane / LPR; // LDS row
             if constexpr (DM) {
                 k[i] = (q & 16) + 4 * (q & 3) + ((q >> 2) & 3);
-                if (i == 0) {
-                    // the swizzle bit of LDS row q is the same in every slab: a slab holds 8 or 16 rows
-                    int c = row0 + 4 * (B == 32 ? pos ^ (4 * ((q >> 1) & 1)) : pos);
-                    p[0] = base + (c < rows ? c : rows - 4);
+                if (i < NP) {
+                    // the swizzle bit of LDS row q is the same in every slab (in every second one): a slab holds 8 or 16 rows (2 or 4)
+                    const int swap = B == 32 ? 4 * ((q >> 1) & 1) : 0; // chunks
+                    int c = row0 + (V ? 4 * (pos ^ swap) : pos ^ (4 * swap));
+                    c = c < rows ? c : rows - (V ? 4 : 1);
+                    p[i] = base + (!V && gather ? gather[c] : c);
                 }
             } else {
-                const int c = pos ^ ((q >> 1) & 7);
+                const int swap = (q >> 1) & 7;
                 int r = row0 + q;
                 r = r < rows ? r : rows - 1;
-                p[i] = base + (int64_t)(gather ? gather[r] : r) * ld_ + 4 * c;
-                k[i] = 4 * c;
+                k[i] = V ? 4 * (pos ^ swap) : pos ^ (4 * swap);
+                p[i] = base + (int64_t)(gather ? gather[r] : r) * ld_ + k[i];
             }
         }
     }
@@ -435,12 +444,13 @@ struct WaveOperand {
             const float* src;
             if constexpr (DM) {
                 const int kc = kk < K ? kk : K - 1;
-                src = p[0] + (int64_t)(list ? list[kc] : kc) * ld;
+                src = p[i % NP] + (int64_t)(list ? list[kc] : kc) * ld;
             } else {
                 src = p[i] + k0;
             }
             if (kk >= K) src = kZero4;
-            __builtin_amdgcn_global_load_lds((glb_void_ptr)src, (lds_void_ptr)(lds + 1024 * i), 16, 0, 0);
+            if constexpr (V) __builtin_amdgcn_global_load_lds((glb_void_ptr)src, (lds_void_ptr)(lds + 1024 * i), 16, 0, 0);
+            else __builtin_amdgcn_global_load_lds((glb_void_ptr)src, (lds_void_ptr)(lds + 256 * i), 4, 0, 0);
         }
     }
     // rows 16 f .. of the tile at depth 16 t of the step: element j belongs to depth 16 t + 4 lg + j
@@ -461,19 +471,19 @@ struct WaveOperand {
     }
 };
 
-template <int B, int S, int EPI, bool ADM, bool BDM>
+template <int B, int S, int EPI, bool ADM, bool BDM, bool VA, bool VB>
 struct WaveShape {
     static constexpr int NB = EPI == EPI_SWIGLU_FWD ? 2 : 1;
-    static constexpr int STAGE = (1 + NB) * B * 128, LOADS = STAGE / 1024;
+    static constexpr int STAGE = (1 + NB) * B * 128, LOADS = WaveOperand<B, ADM, VA>::SLABS + NB * WaveOperand<B, BDM, VB>::SLABS;
     static constexpr int TILES = 4 * S * STAGE, LDS = TILES + (BDM ? kListMax * 4 : 0);
     static_assert(LDS <= 160 * 1024 && 4 * NB * B * (B + 4) * 4 <= TILES && (S - 1) * LOADS < 64, "fits");
 };
 
-template <int B, int S, int EPI, bool ADM, bool BDM>
+template <int B, int S, int EPI, bool ADM, bool BDM, bool VA = true, bool VB = true>
 __device__ inline void wave_body(const Dev& g, int block, unsigned char* smem) {
-    using Sh = WaveShape<B, S, EPI, ADM, BDM>;
-    typedef WaveOperand<B, ADM> OA;
-    typedef WaveOperand<B, BDM> OB;
+    using Sh = WaveShape<B, S, EPI, ADM, BDM, VA, VB>;
+    typedef WaveOperand<B, ADM, VA> OA;
+    typedef WaveOperand<B, BDM, VB> OB;
     constexpr int NB = Sh::NB, F = B / 16;
     const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -497,7 +507,7 @@ __device__ inline void wave_body(const Dev& g, int block, unsigned char* smem) {
     }
     OA a;
     OB b[NB];
-    a.init(gA, g.lda, g.M, m0, ADM ? nullptr : g.ag, lane);
+    a.init(gA, g.lda, g.M, m0, ADM && VA ? nullptr : g.ag, lane);
     b[0].init(gB, g.ldb, g.N, n0, BDM ? nullptr : g.bg, lane);
     if constexpr (NB == 2) b[1].init(g.B2, g.ldb, g.N, n0, g.bg, lane);
     f32x4 acc[NB][F][F];
@@ -513,7 +523,7 @@ __device__ inline void wave_body(const Dev& g, int block, unsigned char* smem) {
 #pragma unroll
     for (int pass = 0; pass < (EPI == EPI_DUAL_ACC ? 2 : 1); ++pass) {
         if (pass == 1) {
-            a.init(g.A2, g.lda, g.M, m0, ADM ? nullptr : g.ag, lane);
+            a.init(g.A2, g.lda, g.M, m0, ADM && VA ? nullptr : g.ag, lane);
             b[0].init(g.B2, g.ldb, g.N, n0, BDM ? nullptr : g.bg, lane);
         }
         const int n = steps > wave ? (steps - wave + 3) / 4 : 0; // this wave's steps
@@ -590,23 +600,266 @@ __device__ inline void wave_body(const Dev& g, int block, unsigned char* smem) {
     }
 }
 
-template <int B, int S, int EPI, bool ADM, bool BDM>
+template <int B, int S, int EPI, bool ADM, bool BDM, bool VA, bool VB>
 __global__ __launch_bounds__(256) void gemm_f32_wave_kernel(Dev g) {
     extern __shared__ __attribute__((aligned(16))) unsigned char wave_lds[];
-    wave_body<B, S, EPI, ADM, BDM>(g, blockIdx.x, wave_lds);
+    wave_body<B, S, EPI, ADM, BDM, VA, VB>(g, blockIdx.x, wave_lds);
 }
 
-template <int B, int S, int EPI, bool ADM, bool BDM>
+template <int B, int S, int EPI, bool ADM, bool BDM, bool VA = true, bool VB = true>
 int launch_wave(Dev g, const char* name, hipStream_t s) {
-    constexpr int LDS = WaveShape<B, S, EPI, ADM, BDM>::LDS;
+    typedef WaveShape<B, S, EPI, ADM, BDM, VA, VB> Sh;
+    constexpr int LDS = Sh::LDS;
+    const int lds = BDM && g.bg ? LDS : Sh::TILES;
     g.tiles_m = (g.M + B - 1) / B, g.tiles_n = (g.N + B - 1) / B;
     const int64_t blocks = (int64_t)g.tiles_m * g.tiles_n * (g.nbatch > 0 ? g.nbatch : 1);
     if (blocks > 0x7FFFFFFF) return SDP_ERR_SHAPE;
-    auto kern = gemm_f32_wave_kernel<B, S, EPI, ADM, BDM>;
+    auto kern = gemm_f32_wave_kernel<B, S, EPI, ADM, BDM, VA, VB>;
     static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
     if (attr != hipSuccess) return SDP_ERR_HIP;
     ProfileScope ps(name, s);
-    kern<<<(unsigned)blocks, 256, LDS, s>>>(g);
+    kern<<<(unsigned)blocks, 256, lds, s>>>(g);
+    return launch_status();
+}
+
+// ---------------------------------------------------------------------------------------------------
+// Pipelined tile: 64 x 64 (or 128 x 128) outputs, four waves of 32 x 32 (64 x 64), depth steps of 32 in three LDS stages that
+// direct loads fill.  A step is two 16-deep halves; while a wave's MFMAs of one half run, its fragments of the next are read, and
+// one barrier a step, between the halves, hands over the stages:
+//   first half of step k : MFMAs on (k, 0); reads of (k, 1)
+//   wait for the own loads of step k + 1 and the own reads of step k; barrier: step k + 1 has landed, step k is read
+//   second half          : MFMAs on (k, 1); reads of (k + 1, 0); loads of step k + 3 into the stage of step k
+//
+// LDS of an operand's step, 16-byte chunks:
+//   rows        : [rows][8 chunks of 4 depth steps], chunk c of row r at position c ^ ((r >> 1) & 7); a fragment is 16 rows, one
+//                 16-byte read per lane gives 4 depth steps of it
+//   depth-major : [32 depth steps][rows / 4 chunks]; fragment f of a wave's F fragments is its rows F i + f, i = 0 .. 15, so that
+//                 one read of F floats per lane and depth step gives all of them.  F = 2: the 128-byte halves of a row trade
+//                 places where bit 2 of the depth step is set, which keeps the four lane groups (4 steps apart) off each
+//                 other's banks.
+// ---------------------------------------------------------------------------------------------------
+template <int R, bool DM, bool V>
+struct PipeOperand {
+    static constexpr int BYTES = R * 128, PER = R / (V ? 32 : 8); // of a step; direct loads of a wave and step
+    static constexpr int F = R / 32;                              // fragments of a wave
+    static constexpr int LPR = (DM ? R / 4 : 8) * (V ? 1 : 4), RPS = 64 / LPR; // lanes per LDS row, LDS rows per load
+    static_assert(64 % LPR == 0, "whole rows a load");
+    static constexpr int swap(int k) { return DM && F == 2 ? 8 * (k >> 2 & 1) : 0; } // depth-major: chunk c sits at c ^ swap
+    static constexpr int NP = DM ? (swap(4) && !V ? 2 : 1) : PER;
+    int64_t off[NP]; // elements from the base: this lane's places at depth 0 (depth-major: its first column, of even and odd loads)
+    int k[PER];      // and their depth within a step
+    int64_t ld;
+    __device__ void init(int64_t ld_, int rows, int row0, const int32_t* gather, int wave, int lane) {
+        ld = ld_;
+        const int pos = lane % LPR;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            const int q = RPS * (4 * i + wave) + lane / LPR; // LDS row
+            if constexpr (DM) {
+                // bit 2 of q: the same for all loads (V: 4 rows a load and wave), or that of i (one row)
+                static_assert(F != 2 || (V ? RPS == 4 : RPS == 1), "which loads share a swap");
+                k[i] = q;
+                if (i < NP) {
+                    int c = row0 + (V ? 4 * (pos ^ swap(q)) : pos ^ (4 * swap(q)));
+                    c = c < rows ? c : rows - (V ? 4 : 1);
+                    off[i] = !V && gather ? gather[c] : c;
+                }
+            } else {
+                const int turn = (q >> 1) & 7;
+                int r = row0 + q;
+                r = r < rows ? r : rows - 1;
+                k[i] = V ? 4 * (pos ^ turn) : pos ^ (4 * turn);
+                off[i] = (int64_t)(gather ? gather[r] : r) * ld_ + k[i];
+            }
+        }
+    }
+    // load i of the step that begins at depth k0; list: gathered depth (in LDS), or null
+    __device__ void issue(unsigned char* stage, int wave, int i, const float* base, int k0, int K, const int* list) const {
+        const int kk = k0 + k[i];
+        const float* src;
+        if constexpr (DM) {
+            const int kc = kk < K ? kk : K - 1;
+            src = base + off[i % NP] + (int64_t)(list ? list[kc] : kc) * ld;
+        } else {
+            src = base + off[i] + k0;
+        }
+        if (kk >= K) src = kZero4;
+        if constexpr (V) __builtin_amdgcn_global_load_lds((glb_void_ptr)src, (lds_void_ptr)(stage + 1024 * (4 * i + wave)), 16, 0, 0);
+        else __builtin_amdgcn_global_load_lds((glb_void_ptr)src, (lds_void_ptr)(stage + 256 * (4 * i + wave)), 4, 0, 0);
+    }
+    // read r of half h: rows part0 .. of the tile.  fr[f][e] belongs to depth 16 h + 4 lg + e.
+    static constexpr int READS = DM ? 4 : F;
+    __device__ static void read(const unsigned char* stage, int part0, int h, int r, int l16, int lg, f32x4 (&fr)[F]) {
+        if constexpr (DM) {
+            const int kk = 16 * h + 4 * lg + r;
+            const unsigned char* p = stage + kk * R * 4;
+            if constexpr (F == 2) {
+                typedef float f32x2 __attribute__((ext_vector_type(2)));
+                const int col = part0 + 2 * l16; // floats; the swap is of 32 floats, the same for all steps of a lane group
+                const f32x2 v = *(const f32x2*)(p + (col ^ (32 * (lg & 1))) * 4);
+                fr[0][r] = v[0], fr[1][r] = v[1];
+            } else {
+                const f32x4 v = *(const f32x4*)(p + (part0 + 4 * l16) * 4);
+#pragma unroll
+                for (int f = 0; f < 4; ++f) fr[f][r] = v[f];
+            }
+        } else {
+            const int row = part0 + 16 * r + l16;
+            fr[r] = *(const f32x4*)(stage + row * 128 + (((4 * h + lg) ^ ((row >> 1) & 7)) * 16));
+        }
+    }
+};
+
+template <int BM, int BN, int EPI, bool ADM, bool BDM, bool VA, bool VB, bool LIST = BDM>
+struct PipeShape {
+    static constexpr int NB = EPI == EPI_SWIGLU_FWD ? 2 : 1; // BN columns of each
+    typedef PipeOperand<BM, ADM, VA> OA;
+    typedef PipeOperand<BN, BDM, VB> OB;
+    static constexpr int STAGE = OA::BYTES + NB * OB::BYTES, LOADS = OA::PER + NB * OB::PER;
+    static constexpr int RING = 3 * STAGE, LDS = RING + (LIST ? kListMax * 4 : 0);
+};
+
+template <int BM, int BN, int EPI, bool ADM, bool BDM, bool VA, bool VB, bool LIST = BDM>
+__device__ inline void pipe_body(const Dev& g, int block, unsigned char* smem) {
+    using Sh = PipeShape<BM, BN, EPI, ADM, BDM, VA, VB, LIST>;
+    typedef typename Sh::OA OA;
+    typedef typename Sh::OB OB;
+    constexpr int NB = Sh::NB, FM = OA::F, FN = OB::F, L = Sh::LOADS;
+    const int tid = threadIdx.x, lane = tid & 63, l16 = lane & 15, lg = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int per = g.tiles_m * g.tiles_n;
+    const int z = block / per, tile = block - z * per;
+    const int m0 = (tile % g.tiles_m) * BM, n0 = (tile / g.tiles_m) * BN;
+    const int pm = (wave >> 1) * (BM / 2), pn = (wave & 1) * (BN / 2); // the wave's part
+    const float *gA = g.A, *gB = g.B;
+    float* gC = g.C;
+    if (g.nbatch > 0) {
+        gA = z == 0 ? g.Ab[0] : (z == 1 ? g.Ab[1] : (z == 2 ? g.Ab[2] : g.Ab[3]));
+        gB = z == 0 ? g.Bb[0] : (z == 1 ? g.Bb[1] : (z == 2 ? g.Bb[2] : g.Bb[3]));
+        gC = z == 0 ? g.Cb[0] : (z == 1 ? g.Cb[1] : (z == 2 ? g.Cb[2] : g.Cb[3]));
+    }
+    int* list = nullptr;
+    if constexpr (LIST) {
+        if (g.bg) { // K <= kListMax
+            list = (int*)(smem + Sh::RING);
+            for (int i = tid; i < g.K; i += 256) list[i] = g.bg[i];
+            __syncthreads();
+        }
+    }
+    OA a;
+    OB b;
+    a.init(g.lda, g.M, m0, ADM && VA ? nullptr : g.ag, wave, lane);
+    b.init(g.ldb, g.N, n0, BDM ? nullptr : g.bg, wave, lane);
+    f32x4 acc[NB][FM][FN];
+#pragma unroll
+    for (int c = 0; c < NB; ++c)
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int j = 0; j < FN; ++j) acc[c][i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    const int n1 = (g.K + 31) / 32, n = EPI == EPI_DUAL_ACC ? 2 * n1 : n1;
+    auto issue = [&](int t, int stage, int l) { // load l of step t
+        const bool second = EPI == EPI_DUAL_ACC && t >= n1;
+        const int k0 = 32 * (second ? t - n1 : t);
+        unsigned char* st = smem + stage * Sh::STAGE;
+        if (l < OA::PER) a.issue(st, wave, l, second ? g.A2 : gA, k0, g.K, nullptr);
+        else if (l < OA::PER + OB::PER) b.issue(st + OA::BYTES, wave, l - OA::PER, second ? g.B2 : gB, k0, g.K, list);
+        else b.issue(st + OA::BYTES + OB::BYTES, wave, l - OA::PER - OB::PER, g.B2, k0, g.K, list);
+    };
+    f32x4 fa[2][FM], fb[2][NB][FN];
+    constexpr int NR = OA::READS + NB * OB::READS, NM = 4 * NB * FM * FN; // of a half
+    static_assert(NR <= NM && L <= NM, "between the MFMAs");
+    auto read_one = [&](int stage, int h, int r) {
+        const unsigned char* st = smem + stage * Sh::STAGE;
+        if (r < OA::READS) OA::read(st, pm, h, r, l16, lg, fa[h]);
+        else if (r < OA::READS + OB::READS) OB::read(st + OA::BYTES, pn, h, r - OA::READS, l16, lg, fb[h][0]);
+        else OB::read(st + OA::BYTES + OB::BYTES, pn, h, r - OA::READS - OB::READS, l16, lg, fb[h][NB - 1]);
+    };
+    // the MFMAs of half h; between them the reads of the other half from `stage` and the loads of step `t`
+    auto half = [&](int h, bool reads, int stage, bool loads, int t, int into) {
+#pragma unroll
+        for (int m = 0; m < NM; ++m) {
+            const bool rd = reads && m < NR, ldq = loads && m * L / NM != (m + 1) * L / NM;
+            if (rd) read_one(stage, h ^ 1, m);
+            if (ldq) issue(t, into, m * L / NM);
+            if (rd || ldq) __builtin_amdgcn_sched_barrier(0);
+            const int e = m / (NB * FM * FN), c = m / (FM * FN) % NB, i = m / FN % FM, j = m % FN;
+            // B first: a lane then holds outputs of one row
+            acc[c][i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fb[h][c][j][e], fa[h][i][e], acc[c][i][j], 0, 0, 0);
+            if (rd || ldq) __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    int t = 0, stage = 0;
+    auto step = [&](auto left_c) { // steps left after this one, at most 3
+        constexpr int LEFT = decltype(left_c)::value;
+        const int next = stage == 2 ? 0 : stage + 1;
+        half(0, true, stage, false, 0, 0);
+        if constexpr (LEFT > 0) {
+            __builtin_amdgcn_sched_barrier(0);
+            SDP_WAIT_VMCNT(LEFT > 1 ? L : 0);
+            SDP_WAIT_LGKMCNT0();
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        half(1, LEFT > 0, next, LEFT > 2, t + 3, stage);
+        __builtin_amdgcn_sched_barrier(0);
+        stage = next, ++t;
+    };
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+        if (j < n) {
+#pragma unroll
+            for (int l = 0; l < L; ++l) issue(j, j, l);
+        }
+    __builtin_amdgcn_sched_barrier(0);
+    if (n > 2) SDP_WAIT_VMCNT(2 * L); else if (n > 1) SDP_WAIT_VMCNT(L); else SDP_WAIT_VMCNT(0);
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int r = 0; r < NR; ++r) read_one(0, 0, r);
+    while (t + 3 < n) step(std::integral_constant<int, 3>{});
+    if (t + 2 < n) step(std::integral_constant<int, 2>{});
+    if (t + 1 < n) step(std::integral_constant<int, 1>{});
+    step(std::integral_constant<int, 0>{});
+
+    // element r of acc[c][i][j]: fragment row l16 of A's i-th, row 4 lg + r of B's j-th
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+        const int m = m0 + pm + (ADM ? FM * l16 + i : 16 * i + l16);
+#pragma unroll
+        for (int q = 0; q < FN; ++q) {
+            f32x4 v[NB];
+#pragma unroll
+            for (int c = 0; c < NB; ++c) {
+                if constexpr (!BDM) v[c] = acc[c][i][q];
+                else if constexpr (FN == 2) v[c] = f32x4{acc[c][i][0][2 * q], acc[c][i][1][2 * q], acc[c][i][0][2 * q + 1], acc[c][i][1][2 * q + 1]};
+                else v[c] = f32x4{acc[c][i][0][q], acc[c][i][1][q], acc[c][i][2][q], acc[c][i][3][q]};
+            }
+            emit<EPI>(g, gC, m, n0 + pn + (BDM ? 4 * FN * lg + 4 * q : 16 * q + 4 * lg), v[0], v[NB - 1]);
+        }
+    }
+}
+
+template <int BM, int BN, int EPI, bool ADM, bool BDM, bool VA, bool VB>
+__global__ __launch_bounds__(256) void gemm_f32_pipe_kernel(Dev g) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char pipe_lds[];
+    pipe_body<BM, BN, EPI, ADM, BDM, VA, VB>(g, blockIdx.x, pipe_lds);
+}
+
+template <int BM, int BN, int EPI, bool ADM, bool BDM, bool VA, bool VB>
+int launch_pipe(Dev g, const char* name, hipStream_t s) {
+    typedef PipeShape<BM, BN, EPI, ADM, BDM, VA, VB> Sh;
+    const int lds = g.bg && BDM ? Sh::LDS : Sh::RING;
+    g.tiles_m = (g.M + BM - 1) / BM, g.tiles_n = (g.N + BN - 1) / BN;
+    const int64_t blocks = (int64_t)g.tiles_m * g.tiles_n * (g.nbatch > 0 ? g.nbatch : 1);
+    if (blocks > 0x7FFFFFFF) return SDP_ERR_SHAPE;
+    auto kern = gemm_f32_pipe_kernel<BM, BN, EPI, ADM, BDM, VA, VB>;
+    static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, Sh::LDS);
+    if (attr != hipSuccess) return SDP_ERR_HIP;
+    ProfileScope ps(name, s);
+    kern<<<(unsigned)blocks, 256, lds, s>>>(g);
     return launch_status();
 }
 
@@ -636,28 +889,53 @@ bool few_tiles(const Dev& g) {
 // Tile of a launch: the fewest matrix cycles on the busiest CU (rounds of tiles over 256 CUs x tile area), each tile
 // weighted by what its loop loses to staging and barriers.  With fewer 64-wide tiles than CUs the 32-wide ones win on
 // both counts (T = 256, p = 512, d = 256: 128 tiles whose waves each run a quarter of the depth, against 32).
-template <int EPI, bool ADM, bool BDM, bool VEC>
+// Event times, the register-staged tile / the pipelined one: gate_up at T = 1024, d = 256, p = 1500 27.7 / 23.0 us (32 against 64
+// wide), T = 1024, d = 512, F = 2048 under backward masking 85 / 51 (128 wide); weight gradients of the latter 128.5 / 64.3.  32 x 32, four waves
+// on a step / on a tile's depth: down 17.3 / 15.8, attn_dout 9.8 / 8.3 with 256 tiles, but 25.9 / 27.5 with 512 (T = 1000).
+// Extents that are no multiples of 4, whole steps before / now: T = 1023, d = 510, F = 2046, p = 1025 610 / 471 us, T = 255, d = 126,
+// p = 401 126 / 69, T = 101, d = 301, p = 901 201 / 110, backward masking T = 600, d = 66, p = 900 257 / 130.
+template <int EPI, bool ADM, bool BDM, bool VA, bool VB>
 int choose(const Dev& g, const char* name, hipStream_t s) {
-    if constexpr (VEC) {
-        if (few_tiles(g) && !(BDM && g.bg && g.K > kListMax)) return launch_wave<16, 2, EPI, ADM, BDM>(g, name, s);
-    }
-    auto cost = [&](int b, double weight) {
-        const int64_t tiles = (int64_t)((g.M + b - 1) / b) * ((g.N + b - 1) / b) * (g.nbatch > 0 ? g.nbatch : 1);
-        if (tiles * 256 > UINT32_MAX) return HUGE_VAL; // threads of one launch
-        return (double)((tiles + 255) / 256) * b * b * weight;
+    constexpr bool VEC = VA && VB;
+    constexpr int NB = EPI == EPI_SWIGLU_FWD ? 2 : 1; // the pipelined tiles hold BN / 2 columns of both right operands
+    const bool direct = !(BDM && g.bg && g.K > kListMax);
+    auto tiles = [&](int bm, int bn) {
+        return (int64_t)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn) * (g.nbatch > 0 ? g.nbatch : 1);
     };
-    const double c128 = cost(128, 1.0), c64 = cost(64, 1.1), c32 = cost(32, 1.3);
-    if (c32 < c64 && c32 < c128) return launch<Cfg<32, 32, 4>, EPI, ADM, BDM, VEC>(g, name, s);
-    if (c64 < c128) return launch<Cfg<64, 64, 1>, EPI, ADM, BDM, VEC>(g, name, s);
-    return launch<Cfg<128, 128, 1>, EPI, ADM, BDM, VEC>(g, name, s);
+    auto cost = [&](int b, int bn, double weight) {
+        const int64_t t = tiles(b, bn);
+        if (t * 256 > UINT32_MAX) return HUGE_VAL; // threads of one launch
+        return (double)((t + 255) / 256) * b * bn * weight;
+    };
+    if (direct) {
+        if (few_tiles(g)) return launch_wave<16, 2, EPI, ADM, BDM, VA, VB>(g, name, s);
+        const double c128 = cost(128, 128 / NB, 1.0), c64 = cost(64, 64 / NB, 1.1), c32 = cost(32, 32, 1.3);
+        if (c32 < c64 && c32 < c128) {
+            if (!VEC || (!ADM && NB == 1 && EPI != EPI_SWIGLU_BWD && tiles(32, 32) <= 256)) return launch_wave<32, 2, EPI, ADM, BDM, VA, VB>(g, name, s);
+            return launch<Cfg<32, 32, 4>, EPI, ADM, BDM, true>(g, name, s);
+        }
+        if (c64 < c128 || !VEC) return launch_pipe<64, 64 / NB, EPI, ADM, BDM, VA, VB>(g, name, s);
+        return launch_pipe<128, 128 / NB, EPI, ADM, BDM, true, true>(g, name, s);
+    }
+    if constexpr (BDM) { // a list too long for LDS
+        const double c128 = cost(128, 128, 1.0), c64 = cost(64, 64, 1.1), c32 = cost(32, 32, 1.3);
+        if (c32 < c64 && c32 < c128) return launch<Cfg<32, 32, 4>, EPI, ADM, BDM, VEC>(g, name, s);
+        if (c64 < c128) return launch<Cfg<64, 64, 1>, EPI, ADM, BDM, VEC>(g, name, s);
+        return launch<Cfg<128, 128, 1>, EPI, ADM, BDM, VEC>(g, name, s);
+    }
+    return SDP_ERR_INVALID_ARG; // not reached
 }
 template <int EPI, bool ADM, bool BDM>
-int choose(bool vec, const Dev& g, const char* name, hipStream_t s) {
-    return vec ? choose<EPI, ADM, BDM, true>(g, name, s) : choose<EPI, ADM, BDM, false>(g, name, s);
+int choose(bool va, bool vb, const Dev& g, const char* name, hipStream_t s) {
+    if (va && vb) return choose<EPI, ADM, BDM, true, true>(g, name, s);
+    if constexpr (BDM) {
+        if (vb) return choose<EPI, ADM, BDM, false, true>(g, name, s);
+    }
+    return choose<EPI, ADM, BDM, false, false>(g, name, s);
 }
 
-// kernel arguments of a descriptor; *vec: the 16-byte loads can take it
-int describe(const GemmDesc& d, Dev& g, bool* vec) {
+// kernel arguments of a descriptor; *va, *vb: 16-byte loads can take A, B
+int describe(const GemmDesc& d, Dev& g, bool* va_out, bool* vb_out) {
     if (d.M < 1 || d.N < 1 || d.K < 1) return SDP_ERR_SHAPE;
     if (d.nbatch < 0 || d.nbatch > kMaxBatch || d.Cc || d.Ct) return SDP_ERR_UNSUPPORTED;
     g = Dev{};
@@ -675,38 +953,72 @@ int describe(const GemmDesc& d, Dev& g, bool* vec) {
         va = va && al(d.Ab[z]), vb = vb && al(d.Bb[z]), vo = vo && al(d.Cb[z]);
     }
     // along the contiguous axis: the depth for an operand stored by rows, M or N for a depth-major one
-    *vec = va && vb && d.lda % 4 == 0 && d.ldb % 4 == 0 && (d.a_km ? d.M : d.K) % 4 == 0 &&
-                     (d.b_km ? d.N : d.K) % 4 == 0 && !(d.a_km && d.a_gather);
+    *va_out = va && d.lda % 4 == 0 && (d.a_km ? d.M : d.K) % 4 == 0 && !(d.a_km && d.a_gather);
+    *vb_out = vb && d.ldb % 4 == 0 && (d.b_km ? d.N : d.K) % 4 == 0;
     g.vec_out = vo && d.N % 4 == 0 && d.ldc % 4 == 0 && (!d.R || (al(d.R) && d.ldr % 4 == 0)) &&
                 (d.epilogue != EPI_SWIGLU_BWD || (al(d.Gin) && al(d.Uin) && d.ldg % 4 == 0));
     return SDP_OK;
 }
 
-template <int BX, int EPIX>
+// dX (BX x BX tiles, four waves on each) and one or two launches' worth of weight gradients (BW = 32: four waves on a tile;
+// 64: pipelined).  VX: 16-byte loads for both operands of dX; WA, WB: for the weight gradients'.
+template <int BX, int EPIX, int BW, bool VX, bool WA, bool WB>
+struct GroupShape {
+    typedef WaveShape<BX, 2, EPIX, false, true, VX, VX> X;
+    static constexpr int W = BW == 32 ? WaveShape<32, 2, EPI_STORE, true, true, WA, WB>::TILES : PipeShape<64, 64, EPI_STORE, true, true, WA, WB, false>::RING;
+    static constexpr int LDS = X::LDS > W ? X::LDS : W;
+};
+template <int BW, bool WA, bool WB>
+__device__ inline void group_gradients(const Dev& w, int b, unsigned char* lds) {
+    if constexpr (BW == 32) wave_body<32, 2, EPI_STORE, true, true, WA, WB>(w, b, lds);
+    else pipe_body<64, 64, EPI_STORE, true, true, WA, WB, false>(w, b, lds);
+}
+template <int BX, int EPIX, int BW, bool VX, bool WA, bool WB>
 __global__ __launch_bounds__(256) void gemm_f32_group_kernel(Dev x, Dev w0, Dev w1, int nx, int n0) {
-    extern __shared__ __attribute__((aligned(16))) unsigned char wave_lds[];
+    extern __shared__ __attribute__((aligned(16))) unsigned char group_lds[];
     const int b = blockIdx.x;
-    if (b < nx) wave_body<BX, 2, EPIX, false, true>(x, b, wave_lds);
-    else if (b < nx + n0) wave_body<32, 2, EPI_STORE, true, true>(w0, b - nx, wave_lds);
-    else wave_body<32, 2, EPI_STORE, true, true>(w1, b - nx - n0, wave_lds);
+    if (b < nx) wave_body<BX, 2, EPIX, false, true, VX, VX>(x, b, group_lds);
+    else if (b < nx + n0) group_gradients<BW, WA, WB>(w0, b - nx, group_lds);
+    else group_gradients<BW, WA, WB>(w1, b - nx - n0, group_lds);
 }
 
-template <int BX, int EPIX>
-int launch_group(Dev x, Dev w0, Dev w1, int n, const char* name, hipStream_t s) {
-    constexpr int LX = WaveShape<BX, 2, EPIX, false, true>::LDS, LW = WaveShape<32, 2, EPI_STORE, true, true>::LDS;
-    constexpr int LDS = LX > LW ? LX : LW;
+int64_t count_tiles(const Dev& g, int b) {
+    return (int64_t)((g.M + b - 1) / b) * ((g.N + b - 1) / b) * (g.nbatch > 0 ? g.nbatch : 1);
+}
+struct Group {
+    Dev x, w0, w1;
+    int n; // launches' worth: 2 or 3
+    const char* name;
+    hipStream_t s;
+};
+template <int BX, int EPIX, int BW, bool VX, bool WA, bool WB>
+int launch_group(const Group& a) {
+    typedef GroupShape<BX, EPIX, BW, VX, WA, WB> Sh;
+    Dev x = a.x, w0 = a.w0, w1 = a.w1;
+    const int lx = x.bg ? Sh::X::LDS : Sh::X::TILES, lds = lx > Sh::W ? lx : Sh::W;
     auto tiles = [](Dev& g, int b) {
         g.tiles_m = (g.M + b - 1) / b, g.tiles_n = (g.N + b - 1) / b;
-        return (int64_t)g.tiles_m * g.tiles_n * (g.nbatch > 0 ? g.nbatch : 1);
+        return count_tiles(g, b);
     };
-    const int64_t nx = tiles(x, BX), n0 = tiles(w0, 32), n1 = n > 2 ? tiles(w1, 32) : 0;
+    const int64_t nx = tiles(x, BX), n0 = tiles(w0, BW), n1 = a.n > 2 ? tiles(w1, BW) : 0;
     if (nx + n0 + n1 > 0x7FFFFFFF) return SDP_ERR_SHAPE;
-    auto kern = gemm_f32_group_kernel<BX, EPIX>;
-    static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+    auto kern = gemm_f32_group_kernel<BX, EPIX, BW, VX, WA, WB>;
+    static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, Sh::LDS);
     if (attr != hipSuccess) return SDP_ERR_HIP;
-    ProfileScope ps(name, s);
-    kern<<<(unsigned)(nx + n0 + n1), 256, LDS, s>>>(x, w0, w1, (int)nx, (int)n0);
+    ProfileScope ps(a.name, a.s);
+    kern<<<(unsigned)(nx + n0 + n1), 256, lds, a.s>>>(x, w0, w1, (int)nx, (int)n0);
     return launch_status();
+}
+template <int BX, int EPIX>
+int launch_group(const Group& a, bool vx, bool wa, bool wb) {
+    // Weight gradients on 64 x 64 tiles where these are many for the depth of each: a tile's time is its depth's.  32-wide / 64-wide,
+    // by tiles of 64 and steps of 32: 768, 4 (T = 128, d = 512, p = 2000) 32.8 / 25.9 us, 360, 16 57.6 / 56.1, an attention's 256, 16
+    // 32.6 / 28.7; but 231, 16 (T = 512, d = 448) 37.5 / 47.5, 288, 32 58.4 / 66.8, 96, 16 19.3 / 22.4.
+    const int64_t t64 = count_tiles(a.w0, 64) + (a.n > 2 ? count_tiles(a.w1, 64) : 0);
+    const bool pipe = t64 >= 16 * (int64_t)((a.w0.K + 31) / 32);
+    if (vx && wa && wb) return pipe ? launch_group<BX, EPIX, 64, true, true, true>(a) : launch_group<BX, EPIX, 32, true, true, true>(a);
+    if (vx && wb) return pipe ? launch_group<BX, EPIX, 64, true, false, true>(a) : launch_group<BX, EPIX, 32, true, false, true>(a);
+    return pipe ? launch_group<BX, EPIX, 64, false, false, false>(a) : launch_group<BX, EPIX, 32, false, false, false>(a);
 }
 
 } // namespace
@@ -714,11 +1026,11 @@ int launch_group(Dev x, Dev w0, Dev w1, int n, const char* name, hipStream_t s) 
 int gemm_f32_group(const GemmDesc* d, int n, const char* name, hipStream_t s) {
     if (n < 2 || n > 3) return SDP_ERR_UNSUPPORTED;
     Dev g[3] = {};
+    bool va[3] = {true, true, true}, vb[3] = {true, true, true};
     for (int i = 0; i < n; ++i) {
-        bool vec;
-        const int rc = describe(d[i], g[i], &vec);
+        const int rc = describe(d[i], g[i], &va[i], &vb[i]);
         if (rc != SDP_OK) return rc;
-        if (!vec || !d[i].b_km || (d[i].b_gather && d[i].K > kListMax)) return SDP_ERR_UNSUPPORTED;
+        if (!d[i].b_km || (d[i].b_gather && (i > 0 || d[i].K > kListMax))) return SDP_ERR_UNSUPPORTED;
         if (i == 0 ? d[i].a_km || d[i].nbatch > 0 || (d[i].epilogue != EPI_STORE && d[i].epilogue != EPI_DUAL_ACC)
                    : !d[i].a_km || d[i].epilogue != EPI_STORE)
             return SDP_ERR_UNSUPPORTED;
@@ -728,23 +1040,24 @@ int gemm_f32_group(const GemmDesc* d, int n, const char* name, hipStream_t s) {
     // 215 us.
     const bool few = few_tiles(g[0]);
     if (!few && (int64_t)((d[0].M + 31) / 32) * ((d[0].N + 31) / 32) > 256) return SDP_ERR_UNSUPPORTED;
-    if (d[0].epilogue == EPI_DUAL_ACC)
-        return few ? launch_group<16, EPI_DUAL_ACC>(g[0], g[1], g[2], n, name, s) : launch_group<32, EPI_DUAL_ACC>(g[0], g[1], g[2], n, name, s);
-    return few ? launch_group<16, EPI_STORE>(g[0], g[1], g[2], n, name, s) : launch_group<32, EPI_STORE>(g[0], g[1], g[2], n, name, s);
+    const Group a{g[0], g[1], g[2], n, name, s};
+    const bool vx = va[0] && vb[0], wa = va[1] && va[2], wb = vb[1] && vb[2];
+    if (d[0].epilogue == EPI_DUAL_ACC) return few ? launch_group<16, EPI_DUAL_ACC>(a, vx, wa, wb) : launch_group<32, EPI_DUAL_ACC>(a, vx, wa, wb);
+    return few ? launch_group<16, EPI_STORE>(a, vx, wa, wb) : launch_group<32, EPI_STORE>(a, vx, wa, wb);
 }
 
 int gemm_f32(const GemmDesc& d, hipStream_t s) {
     Dev g;
-    bool vec;
-    const int rc = describe(d, g, &vec);
+    bool va, vb;
+    const int rc = describe(d, g, &va, &vb);
     if (rc != SDP_OK) return rc;
     switch (d.epilogue) {
     case EPI_STORE:
-        if (d.a_km) return d.b_km ? choose<EPI_STORE, true, true>(vec, g, d.name, s) : SDP_ERR_UNSUPPORTED;
-        return d.b_km ? choose<EPI_STORE, false, true>(vec, g, d.name, s) : choose<EPI_STORE, false, false>(vec, g, d.name, s);
-    case EPI_DUAL_ACC: return d.a_km || !d.b_km ? SDP_ERR_UNSUPPORTED : choose<EPI_DUAL_ACC, false, true>(vec, g, d.name, s);
-    case EPI_SWIGLU_FWD: return d.a_km || d.b_km ? SDP_ERR_UNSUPPORTED : choose<EPI_SWIGLU_FWD, false, false>(vec, g, d.name, s);
-    case EPI_SWIGLU_BWD: return d.a_km || d.b_km ? SDP_ERR_UNSUPPORTED : choose<EPI_SWIGLU_BWD, false, false>(vec, g, d.name, s);
+        if (d.a_km) return d.b_km ? choose<EPI_STORE, true, true>(va, vb, g, d.name, s) : SDP_ERR_UNSUPPORTED;
+        return d.b_km ? choose<EPI_STORE, false, true>(va, vb, g, d.name, s) : choose<EPI_STORE, false, false>(va, vb, g, d.name, s);
+    case EPI_DUAL_ACC: return d.a_km || !d.b_km ? SDP_ERR_UNSUPPORTED : choose<EPI_DUAL_ACC, false, true>(va, vb, g, d.name, s);
+    case EPI_SWIGLU_FWD: return d.a_km || d.b_km ? SDP_ERR_UNSUPPORTED : choose<EPI_SWIGLU_FWD, false, false>(va, vb, g, d.name, s);
+    case EPI_SWIGLU_BWD: return d.a_km || d.b_km ? SDP_ERR_UNSUPPORTED : choose<EPI_SWIGLU_BWD, false, false>(va, vb, g, d.name, s);
     }
     return SDP_ERR_INVALID_ARG;
 }
