@@ -14,6 +14,7 @@
 #include "sdp_internal.h"
 
 #include <cmath>
+#include <type_traits>
 
 namespace {
 
@@ -241,7 +242,211 @@ __global__ __launch_bounds__(256) void avg_rows_kernel(GradPtrs g, const uint8_t
     }
 }
 
-// Any D: one thread per parameter.
+// Parameter i alone; returns the square of its average (OPT_SQNORM).
+template <int BF16, int OPT>
+__device__ inline double average_one(const GradPtrs& g, const uint8_t* __restrict__ mask, int K, int64_t R, int D,
+                                     float* __restrict__ out, uint8_t* __restrict__ cov, const AdamArgs& ad, float gs,
+                                     int64_t i) {
+    const int64_t r = i / D;
+    float acc = 0.f;
+    int c = 0;
+    for (int k = 0; k < K; ++k) {
+        if (mask[(int64_t)k * R + r] == 0) continue;
+        ++c;
+        if (BF16)
+            acc += __uint_as_float((uint32_t)((const uint16_t*)g.p[k])[i] << 16);
+        else
+            acc += ((const float*)g.p[k])[i];
+    }
+    double square = 0.0;
+    if (OPT == OPT_STORE) {
+        out[i] = acc / (c > 0 ? (float)c : 1.0f);
+    } else if (OPT == OPT_SQNORM) {
+        if (c > 0) {
+            const double a = (double)(acc / (float)c);
+            square = a * a;
+        }
+    } else if (c > 0) {
+        float t = ad.theta[i], m1 = ad.m[i], v1 = ad.v[i];
+        adamw_one(ad, gs, acc / (float)c, t, m1, v1);
+        ad.theta[i] = t, ad.m[i] = m1, ad.v[i] = v1;
+        if (ad.theta_bf16) ad.theta_bf16[i] = (uint16_t)(pack2_bf16(t, 0.f) & 0xFFFFu);
+    }
+    if (cov && i == r * D) cov[r] = (uint8_t)c;
+    return square;
+}
+
+// Where a row is no whole number of segments: one wave handles 64 consecutive groups of 8 parameters of the whole buffer, whatever
+// rows they lie in; each lane finds its row and tests its own mask bytes.  The segment form above leaves the lanes of 512 - D % 512
+// parameters idle there.  8 workers, bf16, two thirds of the rows each, before / now: 60000 x 64 52.4 / 12.5 us (1.1 / 4.5 TB/s),
+// 100000 x 264 101 / 69, 100000 x 520 194 / 129, 100000 x 1288 347 / 314; with norm and update 100000 x 264 291 / 234, 100000 x 1288
+// 1147 / 1081.
+// STRADDLE: the same for rows that are no multiple of 8 (from 8 on): a group may hold the end of one row and the start of the next, and
+// takes each worker's parameters of those of the two that it trains.  One thread per parameter / this: 60000 x 1501 1086 / 218 us
+// (1.2 / 6.0 TB/s), 30000 x 257 75 / 25, with norm and update 2503 / 782 and 168 / 81.
+template <int BF16, int OPT, int STRADDLE>
+__global__ __launch_bounds__(256) void avg_groups_kernel(GradPtrs g, const uint8_t* __restrict__ mask, int K, int64_t R,
+                                                         int D, double inv_d, float* __restrict__ out,
+                                                         uint8_t* __restrict__ cov, AdamArgs ad) {
+    const int64_t n = R * D;
+    const int64_t whole = (n / 8 + 63) / 64; // waves of whole groups; one more for the last n % 8 parameters, a lane each
+    const int64_t nitems = whole + (n % 8 != 0);
+    const int lane = threadIdx.x & 63;
+    const int64_t wave0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    const int64_t nwaves = ((int64_t)gridDim.x * blockDim.x) >> 6;
+    double sq = 0.0; // OPT_SQNORM: this lane's share of the sum of squares
+    float gs = ad.grad_scale;
+    if (OPT == OPT_ADAMW && ad.grad_scale_dev) gs *= *ad.grad_scale_dev;
+    for (int64_t item = wave0; item < nitems; item += nwaves) {
+        if (STRADDLE && item == whole) {
+            if (lane < n % 8) sq += average_one<BF16, OPT>(g, mask, K, R, D, out, cov, ad, gs, n / 8 * 8 + lane);
+            break; // the last item
+        }
+        // this lane's row and first parameter in it: off / D from the product with 1/D, exact after one correction (off < 2^41 is exact
+        // in double, and the product off by less than one)
+        const int64_t off = item * 512 + lane * 8;
+        int64_t r = (int64_t)((double)off * inv_d), in = off - r * D;
+        if (in < 0) --r, in += D;
+        if (in >= D) ++r, in -= D;
+        const int e0 = (int)in;
+        const bool live = off + 8 <= n;
+        // the group's first `split` parameters are row r's, the others row r + 1's (D >= 8: no third row)
+        const int split = STRADDLE ? D - e0 : 8;
+        const bool two = live && split < 8;
+        int c1 = 0;
+        float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+        int c = 0;
+        // optimizer state of the segment: requested first, so that it travels while the gradients are summed
+        // (rows nobody covers are read too, which is harmless and rare, and never written back)
+        f32x4 th[2], mm[2], vv[2];
+        if (OPT == OPT_ADAMW && live) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                th[h] = *((const f32x4*)(ad.theta + off) + h);
+                mm[h] = *((const f32x4*)(ad.m + off) + h);
+                vv[h] = *((const f32x4*)(ad.v + off) + h);
+            }
+        }
+        for (int k0 = 0; k0 < K; k0 += kBatch) {
+            // every mask byte of the batch is requested before the first is looked at
+            int mk[kBatch], mk1[kBatch];
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) {
+                const int k = k0 + i < K ? k0 + i : K - 1; // past the last worker: any byte, not used
+                mk[i] = (int)mask[(int64_t)k * R + (live ? r : R - 1)];
+                mk1[i] = STRADDLE ? (int)mask[(int64_t)k * R + (two ? r + 1 : R - 1)] : 0;
+            }
+            bool covered[kBatch], covered1[kBatch];
+            u32x4 lo[kBatch];
+            f32x4 hi[kBatch];
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) {
+                covered[i] = k0 + i < K && live && mk[i] != 0;
+                covered1[i] = STRADDLE && k0 + i < K && two && mk1[i] != 0;
+                if (covered[i] || covered1[i]) {
+                    if (BF16) {
+                        lo[i] = __builtin_nontemporal_load((const u32x4*)((const uint16_t*)g.p[k0 + i] + off));
+                    } else {
+                        const u32x4* src = (const u32x4*)((const float*)g.p[k0 + i] + off);
+                        lo[i] = __builtin_nontemporal_load(src);
+                        hi[i] = __builtin_nontemporal_load((const f32x4*)(src + 1));
+                    }
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < kBatch; ++i) {
+                if (!covered[i] && !covered1[i]) continue;
+                c += covered[i];
+                c1 += covered1[i];
+                if (STRADDLE) {
+                    // a row nobody of this worker trains is read where the group straddles two, and not used
+                    float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                    if (BF16) {
+                        add_bf16x8(lo[i], x);
+                    } else {
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) x[q] = __uint_as_float(lo[i][q]), x[4 + q] = hi[i][q];
+                    }
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) acc[q] += (q < split ? covered[i] : covered1[i]) ? x[q] : 0.f;
+                } else if (BF16) {
+                    add_bf16x8(lo[i], acc);
+                } else {
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        acc[q] += __uint_as_float(lo[i][q]);
+                        acc[4 + q] += hi[i][q];
+                    }
+                }
+            }
+        }
+        // coverage of parameter i's row
+        auto count = [&](int i) { return STRADDLE && i >= split ? c1 : c; };
+        if (live && OPT == OPT_SQNORM) {
+            // squares of the very fp32 values the storing form would write, added up in double
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                if (count(i) == 0) continue;
+                const double a = (double)(acc[i] / (float)count(i));
+                sq += a * a;
+            }
+        }
+        if (live && OPT == OPT_STORE) {
+            // count 0: nobody covers the row, the average is defined as 0 (acc is still 0)
+            f32x4 a, b;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                a[i] = acc[i] / (count(i) > 0 ? (float)count(i) : 1.0f);
+                b[i] = acc[4 + i] / (count(4 + i) > 0 ? (float)count(4 + i) : 1.0f);
+            }
+            f32x4* dst = (f32x4*)(out + off);
+            __builtin_nontemporal_store(a, dst);
+            __builtin_nontemporal_store(b, dst + 1);
+        }
+        if (live && OPT == OPT_ADAMW && (c > 0 || c1 > 0)) {
+            // rows nobody covers keep their parameters and moments
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    float t = th[h][i], m1 = mm[h][i], v1 = vv[h][i];
+                    adamw_one(ad, gs, acc[4 * h + i] / (float)count(4 * h + i), t, m1, v1);
+                    th[h][i] = t, mm[h][i] = m1, vv[h][i] = v1;
+                }
+            if (STRADDLE && two && (c == 0 || c1 == 0)) {
+                // one of the two rows stays as it is: its parameters' values above are not used
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    if (count(i) == 0) continue;
+                    ad.theta[off + i] = th[i / 4][i % 4];
+                    ad.m[off + i] = mm[i / 4][i % 4];
+                    ad.v[off + i] = vv[i / 4][i % 4];
+                    if (ad.theta_bf16) ad.theta_bf16[off + i] = (uint16_t)(pack2_bf16(th[i / 4][i % 4], 0.f) & 0xFFFFu);
+                }
+            } else {
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    *((f32x4*)(ad.theta + off) + h) = th[h];
+                    *((f32x4*)(ad.m + off) + h) = mm[h];
+                    *((f32x4*)(ad.v + off) + h) = vv[h];
+                }
+                if (ad.theta_bf16) {
+                    const u32x4 packed = {pack2_bf16(th[0][0], th[0][1]), pack2_bf16(th[0][2], th[0][3]),
+                                          pack2_bf16(th[1][0], th[1][1]), pack2_bf16(th[1][2], th[1][3])};
+                    __builtin_nontemporal_store(packed, (u32x4*)(ad.theta_bf16 + off));
+                }
+            }
+        }
+        if (cov && live && e0 == 0) cov[r] = (uint8_t)c;
+        if (STRADDLE && cov && two) cov[r + 1] = (uint8_t)c1;
+    }
+    if (OPT == OPT_SQNORM) {
+        sq = block_sum(sq);
+        if (threadIdx.x == 0) ad.partial[blockIdx.x] = sq;
+    }
+}
+
+// Rows of fewer than 8 parameters, small buffers with rows that are no multiple of 8: one thread per parameter.
 template <int BF16, int OPT>
 __global__ __launch_bounds__(256) void avg_elems_kernel(GradPtrs g, const uint8_t* __restrict__ mask, int K, int64_t R,
                                                         int D, float* __restrict__ out, uint8_t* __restrict__ cov,
@@ -250,33 +455,8 @@ __global__ __launch_bounds__(256) void avg_elems_kernel(GradPtrs g, const uint8_
     double sq = 0.0;
     float gs = ad.grad_scale;
     if (OPT == OPT_ADAMW && ad.grad_scale_dev) gs *= *ad.grad_scale_dev;
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t r = i / D;
-        float acc = 0.f;
-        int c = 0;
-        for (int k = 0; k < K; ++k) {
-            if (mask[(int64_t)k * R + r] == 0) continue;
-            ++c;
-            if (BF16)
-                acc += __uint_as_float((uint32_t)((const uint16_t*)g.p[k])[i] << 16);
-            else
-                acc += ((const float*)g.p[k])[i];
-        }
-        if (OPT == OPT_STORE) {
-            out[i] = acc / (c > 0 ? (float)c : 1.0f);
-        } else if (OPT == OPT_SQNORM) {
-            if (c > 0) {
-                const double a = (double)(acc / (float)c);
-                sq += a * a;
-            }
-        } else if (c > 0) {
-            float t = ad.theta[i], m1 = ad.m[i], v1 = ad.v[i];
-            adamw_one(ad, gs, acc / (float)c, t, m1, v1);
-            ad.theta[i] = t, ad.m[i] = m1, ad.v[i] = v1;
-            if (ad.theta_bf16) ad.theta_bf16[i] = (uint16_t)(pack2_bf16(t, 0.f) & 0xFFFFu);
-        }
-        if (cov && i == r * D) cov[r] = (uint8_t)c;
-    }
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+        sq += average_one<BF16, OPT>(g, mask, K, R, D, out, cov, ad, gs, i);
     if (OPT == OPT_SQNORM) {
         sq = block_sum(sq);
         if (threadIdx.x == 0) ad.partial[blockIdx.x] = sq;
@@ -285,8 +465,22 @@ __global__ __launch_bounds__(256) void avg_elems_kernel(GradPtrs g, const uint8_
 
 // workgroups of the norm pass: enough to keep every CU's queue full, few enough for a small table of partial sums
 constexpr int64_t kNormBlocks = 1 << 13;
+// Where rows are no whole number of segments, groups of 8 across the rows' ends (avg_groups_kernel); but of small buffers, whose waves
+// would be few, segments or single parameters.  Average / norm, clipping and update, without / with: 8 workers, 1400 x 264 4.3 / 4.0
+// and 14.1 / 13.5 us, but 1000 x 264 4.2 / 3.9 and 12.9 / 13.2, 1000 x 200 4.1 / 3.9 and 12.6 / 12.8; rows that are no multiple of 8,
+// 4 workers 12000 x 101 6.7 / 6.7 and 23.7 / 20.6, 1000 x 1001 5.4 / 4.8 and 18.5 / 16.3, but 2 workers 12000 x 65 4.2 / 4.7 and
+// 15.2 / 15.9, 4 workers 5000 x 101 3.8 / 4.6 and 12.9 / 14.5.
+bool packed_rows(int64_t R, int D) {
+    const int64_t few = D % 8 == 0 ? 5 << 16 : 3 << 18;
+    return D >= 8 && D % 512 != 0 && R * D >= few;
+}
+int64_t row_items(int64_t R, int D) {
+    const int64_t n = R * D;
+    return packed_rows(R, D) ? (n / 8 + 63) / 64 + (n % 8 != 0) : R * ((D + 511) / 512);
+}
+bool by_rows(int64_t R, int D) { return D % 8 == 0 || packed_rows(R, D); }
 int64_t norm_blocks(int64_t R, int D) {
-    const int64_t want = D % 8 == 0 ? (R * ((D + 511) / 512) + 3) / 4 : (R * D + 255) / 256;
+    const int64_t want = by_rows(R, D) ? (row_items(R, D) + 3) / 4 : (R * D + 255) / 256;
     return want < 1 ? 1 : (want < kNormBlocks ? want : kNormBlocks);
 }
 
@@ -301,21 +495,24 @@ int launch_average(int K, int64_t R, int D, int gdtype, const void* const* g, co
     for (int k = K; k < SDP_MAX_WORKERS; ++k) ptrs.p[k] = nullptr;
     const AdamArgs a = ad ? *ad : AdamArgs{};
     sdp::ProfileScope ps(name, s);
-    if (D % 8 == 0) {
-        const int segs = (D + 511) / 512;
-        const int64_t items = R * segs;
-        const int64_t blocks64 = (items + 3) / 4; // 4 waves per workgroup
+    if (by_rows(R, D)) {
+        const int64_t blocks64 = (row_items(R, D) + 3) / 4; // 4 waves per workgroup
         const unsigned blocks = norm ? (unsigned)norm_blocks(R, D) : (unsigned)(blocks64 < (1 << 20) ? blocks64 : (1 << 20));
-        if (norm) {
-            if (gdtype == SDP_BF16) avg_rows_kernel<1, OPT_SQNORM><<<blocks, 256, 0, s>>>(ptrs, mask, K, R, D, out, cov, a);
-            else avg_rows_kernel<0, OPT_SQNORM><<<blocks, 256, 0, s>>>(ptrs, mask, K, R, D, out, cov, a);
-        } else if (gdtype == SDP_BF16) {
-            if (ad) avg_rows_kernel<1, 1><<<blocks, 256, 0, s>>>(ptrs, mask, K, R, D, out, cov, a);
-            else avg_rows_kernel<1, 0><<<blocks, 256, 0, s>>>(ptrs, mask, K, R, D, out, cov, a);
-        } else {
-            if (ad) avg_rows_kernel<0, 1><<<blocks, 256, 0, s>>>(ptrs, mask, K, R, D, out, cov, a);
-            else avg_rows_kernel<0, 0><<<blocks, 256, 0, s>>>(ptrs, mask, K, R, D, out, cov, a);
-        }
+        auto launch = [&](auto bf16, auto opt) {
+            if (!packed_rows(R, D))
+                avg_rows_kernel<bf16.value, opt.value><<<blocks, 256, 0, s>>>(ptrs, mask, K, R, D, out, cov, a);
+            else if (D % 8 != 0)
+                avg_groups_kernel<bf16.value, opt.value, 1><<<blocks, 256, 0, s>>>(ptrs, mask, K, R, D, 1.0 / D, out, cov, a);
+            else
+                avg_groups_kernel<bf16.value, opt.value, 0><<<blocks, 256, 0, s>>>(ptrs, mask, K, R, D, 1.0 / D, out, cov, a);
+        };
+        auto launch_form = [&](auto bf16) {
+            if (norm) launch(bf16, std::integral_constant<int, OPT_SQNORM>{});
+            else if (ad) launch(bf16, std::integral_constant<int, OPT_ADAMW>{});
+            else launch(bf16, std::integral_constant<int, OPT_STORE>{});
+        };
+        if (gdtype == SDP_BF16) launch_form(std::integral_constant<int, 1>{});
+        else launch_form(std::integral_constant<int, 0>{});
     } else {
         const int64_t n = R * D;
         const int64_t blocks64 = (n + 255) / 256;
