@@ -173,10 +173,10 @@ struct TileMover {
         for (int i = 0; i < PER; ++i)
             *(u32x4*)(tile + (tid / CPR + 64 * NW / CPR * i) * row_bytes(HW) + col * 16) = pad ? u32x4{0u, 0u, 0u, 0u} : v[i];
     }
-    // dot products of the tile's rows with those of another tile (of one wave): the CPR lanes of a group hold rows group + 8 i;
-    // lane i of the group, i < PER, returns row dot_row
+    // dot products of the tile's rows with those of another tile (of one wave): the CPR lanes of a group hold rows
+    // group + 64 / CPR i; lane i of the group, i < PER, returns row dot_row
     __device__ static int dot_row(int tid) { return tid / CPR + 64 * NW / CPR * (tid % CPR); }
-    __device__ float row_dots(const TileMover& o, int tid) const {
+    __device__ float row_dots(const TileMover& o, int hd, int tid) const {
         static_assert(NW == 1 && PER <= CPR, "a lane for every row");
         float out = 0.f;
 #pragma unroll
@@ -187,6 +187,7 @@ struct TileMover {
                 d = __builtin_fmaf(__uint_as_float(v[i][j] << 16), __uint_as_float(o.v[i][j] << 16), d);
                 d = __builtin_fmaf(__uint_as_float(v[i][j] & 0xFFFF0000u), __uint_as_float(o.v[i][j] & 0xFFFF0000u), d);
             }
+            if (HW > HD && tid % CPR * 8 >= hd) d = 0.f; // a piece beyond the head
 #pragma unroll
             for (int m = 1; m < CPR; m <<= 1) d += __shfl_xor(d, m, 64);
             if (tid % CPR == i) out = d;
@@ -732,11 +733,13 @@ struct DkvShape {
 };
 
 // OWN_DELTA: the queries' delta is computed from their dO and O rows as the tile is staged (every wave its own tile), in the place
-// of what the dQ kernel has left.
+// of what the dQ kernel has left.  O's rows are fetched a tile ahead like the others; KW = 8 has no registers for them and
+// fetches them into those that staging has freed (wide heads).
 template <int HW, int KW, bool OWN_DELTA = false>
 __device__ inline void attn_bwd_dkv_block(const CoreArgs& a, const int k0, const int head, const int b, unsigned char* lds) {
     using Shape = DkvShape<HW, KW>;
-    static_assert(!OWN_DELTA || (KW > 1 && HW == HD), "a wave's own tile, in registers that are left");
+    static_assert(!OWN_DELTA || KW > 1, "a wave's own tile");
+    constexpr bool kAhead = OWN_DELTA && KW == 4;
     constexpr int KS = HW / 16, JB = HW / 32, QT = Shape::QT;
     constexpr bool kVInLds = Shape::kVInLds, kKInLds = Shape::kKInLds;
     const int hd = HW == HD ? HD : a.hd;
@@ -791,15 +794,16 @@ __device__ inline void attn_bwd_dkv_block(const CoreArgs& a, const int k0, const
     auto stat_of = [&](int q) { return gstat[q < S ? q : S - 1]; };
     pq.fetch(gQ, ldq32, QT * t0, S - 1, hd, mt);
     po.fetch(gO, ldo32, QT * t0, S - 1, hd, mt);
-    if constexpr (OWN_DELTA) px.fetch(gX, ldo32, QT * t0, S - 1, hd, mt);
+    if constexpr (kAhead) px.fetch(gX, ldo32, QT * t0, S - 1, hd, mt);
     float pstat = stat_of(QT * t0 + sq);
     for (int t = 0; t < ntiles; ++t) {
         if constexpr (KW == 1) __syncthreads(); else wave_sync();
         pq.stash(sQ, hd, mt);
         po.stash(sO, hd, mt);
         if constexpr (OWN_DELTA) {
+            if constexpr (!kAhead) px.fetch(gX, ldo32, QT * (t0 + KW * t), S - 1, hd, mt);
             if (mt < QT) sL[mt] = pstat;
-            const float d = po.row_dots(px, mt); // of the tile's row that this lane is to put away
+            const float d = po.row_dots(px, hd, mt); // of the tile's row that this lane is to put away
             if (mt % TileMover<1, HW, QT>::CPR < TileMover<1, HW, QT>::PER) sD[po.dot_row(mt)] = d;
         } else {
             if (mt < 2 * QT) sL[mt] = pstat;
@@ -810,7 +814,7 @@ __device__ inline void attn_bwd_dkv_block(const CoreArgs& a, const int k0, const
         if (always_fetch(HW, KW) || t + 1 < ntiles) {
             pq.fetch(gQ, ldq32, next, S - 1, hd, mt);
             po.fetch(gO, ldo32, next, S - 1, hd, mt);
-            if constexpr (OWN_DELTA) px.fetch(gX, ldo32, next, S - 1, hd, mt);
+            if constexpr (kAhead) px.fetch(gX, ldo32, next, S - 1, hd, mt);
             pstat = stat_of(next + sq);
         }
         if (qt0 + QT - 1 < krow0) continue; // wave-uniform: every query of the tile lies before the wave's keys
@@ -895,7 +899,7 @@ __device__ inline void attn_bwd_dkv_block(const CoreArgs& a, const int k0, const
         each_row_again<HW, KW>(lds, again, wave, lane, [&](int r) {
             const AttnRows<uint16_t> ar{gQ, gK, gV, a.ldq, gO, a.ldo, S, hd, a.scale, a.scale2};
             uint16_t* row = out + (int64_t)(krow0 + r) * a.ldq;
-            attn_row_dkv(ar, krow0 + r, lane, a.lse + stat, a.delta + stat, row + a.ph * hd, row + 2 * a.ph * hd);
+            attn_row_dkv(ar, krow0 + r, lane, a.lse + stat, OWN_DELTA ? nullptr : a.delta + stat, row + a.ph * hd, row + 2 * a.ph * hd, gX);
         });
 }
 
@@ -912,11 +916,16 @@ void attn_bwd_dkv_kernel(CoreArgs a, int nblocks, int nbh, SideJobs side) {
     attn_bwd_dkv_block<HW, KW>(a, (nblocks - 1 - blk) * Split<KW>::ROWS, head, b, lds);
 }
 
-// dK, dV and dQ as one launch, where the walked axis is split and heads are at most 64 wide: either alone leaves CUs idle, and what
-// a launch costs between two kernels is a sixteenth of such a call.  dK/dV then takes delta from dO and O itself; wider heads have no
-// registers left for O's rows.  Forward and backward of an attention, two launches / one: 2 x 256 tokens, 6 heads of 64 47 / 42.7 us,
-// 1 x 64, 4 of 50 44 / 39, 4 x 100, 12 of 50 50.5 / 46, 1 x 1024, 12 of 64 80.5 / 75.7, 2 x 1024, 12 122 / 119, 1 x 2048, 14 166 / 167.
-constexpr bool merged(int hw, int kw) { return hw == HD && kw == 4; }
+// dK, dV and dQ as one launch, where the walked axis is split: either alone leaves CUs idle, and what a launch costs between two
+// kernels is a sixteenth of such a call.  dK/dV then takes delta from dO and O itself.  Forward and backward of an attention, two
+// launches / one, heads up to 64: 2 x 256 tokens, 6 heads of 64 47 / 42.7 us, 1 x 64, 4 of 50 44 / 39, 4 x 100, 12 of 50 50.5 / 46,
+// 1 x 1024, 12 of 64 80.5 / 75.7, 2 x 1024, 12 122 / 119, 1 x 2048, 14 166 / 167.
+// Wider heads run one workgroup a CU, so that a block of keys and one of queries, longest first, take turns in the order of the
+// workgroups; up to as many blocks of 32 rows as the first half of them fills the CUs (KW = 8 256, KW = 4 224): 1 x 64 tokens, 4 heads
+// of 128 49.9 / 40.9, 1 x 512, 4 67 / 55.8, 1 x 1500, 4 105 / 92.6, 1 x 1024, 8 (256 blocks, KW = 8) 106.8 / 101.9, 1 x 155, 13 of 96
+// 77.5 / 68.1, 2 x 200, 8 of 128 69.4 / 62; but 2 x 256, 16 (256, KW = 4) 114.3 / 115.7, 1 x 1100, 8 of 96 (280) 103.8 / 110.6, 2 x 1024,
+// 12 of 128 (768) 244 / 270: the re-read of O and the longer tail of a launch of several rounds cost more than the gap there.
+constexpr bool merged(int hw, int kw) { return kw > 1; }
 template <int HW, int KW>
 __global__ __launch_bounds__(Split<KW>::THREADS) __attribute__((amdgpu_waves_per_eu(waves_dkv(HW, KW), waves_dkv(HW, KW))))
 void attn_bwd_kernel(CoreArgs a, int nblocks, int nbh, SideJobs side) {
@@ -926,8 +935,9 @@ void attn_bwd_kernel(CoreArgs a, int nblocks, int nbh, SideJobs side) {
     const int id = workgroup_id();
     if (id >= 2 * nitems) return carried<sizeof(lds), Split<KW>::THREADS>(side, id - 2 * nitems, lds);
     int blk, head, b;
-    causal_item(id < nitems ? id : id - nitems, nitems, nbh, nblocks, a.ph, blk, head, b);
-    if (id < nitems) attn_bwd_dkv_block<HW, KW, true>(a, (nblocks - 1 - blk) * Split<KW>::ROWS, head, b, lds);
+    const bool dkv = HW == HD ? id < nitems : (id & 1) == 0;
+    causal_item(HW != HD ? id >> 1 : dkv ? id : id - nitems, nitems, nbh, nblocks, a.ph, blk, head, b);
+    if (dkv) attn_bwd_dkv_block<HW, KW, true>(a, (nblocks - 1 - blk) * Split<KW>::ROWS, head, b, lds);
     else attn_bwd_dq_block<HW, KW, false>(a, blk * Split<KW>::ROWS, head, b, lds);
 }
 
@@ -935,7 +945,7 @@ void attn_bwd_kernel(CoreArgs a, int nblocks, int nbh, SideJobs side) {
 // more than the re-reads.  Block forward + backward in us, KW = 1 / KW = 4: heads of 64, 96 workgroups (1 x 1024 tokens,
 // 12 heads) 158 / 124, 192 (2 x 1024) 168 / 149, 384 (4 x 1024) 184 / 187; heads of 128, 64 workgroups (1 x 1024, 8 heads)
 // 238 / 165, 128 (2 x 1024) 249 / 203, 256 (4 x 1024) 267 / 281; heads of 96, 192 workgroups 208 / 195.
-constexpr int split_below(int hw) { return hw == HD ? 256 : 192; }
+constexpr int split_below(int hw) { return hw <= HD ? 256 : 192; }
 // KW = 8 (heads wider than 64): a chain half as long again, two waves on a SIMD where KW = 4 with a workgroup per CU has one, for
 // partial results of eight waves to add.  What it shortens grows with S, what it adds with the workgroups: taken from 512 tokens
 // on while four times the workgroups are no more than the tokens.  KW = 4 / KW = 8 at one sequence of 512, 1024, 1500, 2048 tokens
@@ -966,7 +976,11 @@ int launch_core(CoreKernel which, const CoreArgs& a, int nbh, const SideJobs& si
     return launch_status();
 }
 int64_t whole_walks(int64_t S, int64_t nbh) { return (S + Split<1>::ROWS - 1) / Split<1>::ROWS * nbh; } // workgroups of a launch with KW = 1
-bool merged_backward(const CoreArgs& a, int64_t nbh) { return a.hd <= HD && whole_walks(a.S, nbh) <= split_below(HD); }
+// see attn_bwd_kernel
+bool merged_backward(const CoreArgs& a, int64_t nbh) {
+    if (a.hd <= HD) return whole_walks(a.S, nbh) <= split_below(HD);
+    return ((int64_t)a.S + 31) / 32 * nbh <= (split_in_eight(a.hd, a.S, nbh) ? 256 : 224);
+}
 template <int HW>
 int launch_core(CoreKernel which, const CoreArgs& a, int64_t nbh, const SideJobs& side, hipStream_t s) {
     const int64_t wide = whole_walks(a.S, nbh);

@@ -415,7 +415,7 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_dkv_kernel(Args a, int nbloc
     for (int r = 0; r < 4; ++r) {
         const int ka = it.row0 + 4 * wave + r;
         float* o = a.dqkv + ((int64_t)it.b * a.S + ka) * a.ldq + it.head * hd;
-        if (again >> (16 * r) & 1) attn_row_dkv(ar, ka, lane, a.lse + st, a.delta + st, o + a.n * hd, o + 2 * a.n * hd);
+        if (again >> (16 * r) & 1) attn_row_dkv(ar, ka, lane, a.lse + st, a.delta + st, o + a.n * hd, o + 2 * a.n * hd, (const float*)nullptr);
     }
 }
 

@@ -1,5 +1,5 @@
-"""GPU: the bf16 attention backward as one launch (heads up to 64, few blocks): one row to several tiles, every kind of width, the
-last number of blocks that qualifies and one head more.  Tolerances and their reasons: test_gpu_attn.py."""
+"""GPU: the attention backward as one launch (few blocks): one row to several tiles, every kind of width, the last number of blocks
+that qualifies and one head or a tile more.  Tolerances and their reasons: test_gpu_attn.py."""
 import pytest
 
 import test_gpu_attn as t
@@ -9,9 +9,12 @@ from workloads import AttnWorkload
 pytestmark = pytest.mark.gpu
 sdp = t.sdp  # the fixture
 
-CASES = [(AttnWorkload(f"merged{hd}_S{S}_{Bt}x{H}", Bt, S, 72, H, hd, H, 2, 91), one) for hd, Bt, S, H, one in
-         ((64, 1, 1, 2, 1), (50, 3, 31, 2, 1), (64, 2, 33, 3, 1), (32, 1, 129, 2, 1), (64, 1, 300, 2, 1),
-          (64, 8, 130, 16, 1), (50, 8, 130, 17, 0))]
+CASES = [(AttnWorkload(f"merged_{dt}_{hd}_S{S}_{Bt}x{H}", Bt, S, 72, H, hd, H, 2, 91, dt), one) for dt, hd, Bt, S, H, one in
+         (("bf16", 64, 1, 1, 2, 1), ("bf16", 50, 3, 31, 2, 1), ("bf16", 64, 2, 33, 3, 1), ("bf16", 32, 1, 129, 2, 1), ("bf16", 64, 1, 300, 2, 1),
+          ("bf16", 64, 8, 130, 16, 1), ("bf16", 50, 8, 130, 17, 0),
+          # wider heads: four waves on a block, then eight
+          ("bf16", 72, 1, 1, 2, 1), ("bf16", 96, 2, 33, 3, 1), ("bf16", 104, 1, 300, 2, 1), ("bf16", 128, 4, 200, 8, 1), ("bf16", 80, 4, 200, 9, 0),
+          ("bf16", 88, 1, 545, 2, 1), ("bf16", 120, 1, 1024, 8, 1), ("bf16", 80, 1, 1056, 8, 0))]
 
 
 @pytest.mark.parametrize("mode", ["fm", "bm"])
@@ -20,3 +23,12 @@ def test_backward_in_one_launch(sdp, orc, w, one, mode):
     with _Launches(sdp) as n:
         t.run_case(sdp, orc, w, [0], mode=mode)
     assert (n["attn_core_bwd"], n["attn_core_bwd_dq"]) == (one, 1 - one), n
+
+
+# the smaller cases of test_gpu_attn.py run as one launch
+@pytest.mark.parametrize("w", [AttnWorkload("bad_two_bf16", 4, 200, 72, 9, 72, 9, 2, 92)],
+                         ids=lambda w: w.name)
+def test_bad_token_with_two_launches(sdp, w):
+    with _Launches(sdp) as n:
+        t._check_bad_token(sdp, w, "fm", 33)
+    assert n["attn_core_bwd"] == 0 and n["attn_core_bwd_dq"] > 0, n
