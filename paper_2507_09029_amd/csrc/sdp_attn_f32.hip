@@ -177,6 +177,9 @@ __device__ inline Item item_of(int nblocks, bool first_is_long) {
 }
 inline dim3 item_grid(int nblocks, int n, int Bt) { return nblocks <= kSlowAxis ? dim3(n, Bt, nblocks) : dim3(nblocks, n, Bt); }
 
+template <int HW>
+constexpr int merge_floats() { return NW * 16 * (HW + 4); }
+
 // forward: O[q] = sum_{k <= q} softmax(z[q][.])[k] V[k]
 template <int HW, bool VEC>
 __global__ __launch_bounds__(64 * NW) void attn_f32_fwd_kernel(Args a, int nblocks) {
@@ -268,14 +271,12 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_fwd_kernel(Args a, int nbloc
 }
 
 // backward, dQ and delta: dQ[q] = scale sum_{k <= q} dZ[q][k] K[k], dZ = P (dP - delta), dP[q][k] = dO[q] . V[k]
-template <int HW, bool VEC>
-__global__ __launch_bounds__(64 * NW) void attn_f32_dq_kernel(Args a, int nblocks) {
+template <int HW, bool VEC, bool STORE_DELTA>
+__device__ inline void dq_block(const Args& a, const Item it, float* sX) {
     typedef Head<HW, VEC> H;
     constexpr int NF = H::NF;
-    __shared__ __attribute__((aligned(16))) float sX[NW * 16 * (HW + 4)];
     const int tid = threadIdx.x, lane = tid & 63, l = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const Item it = item_of(nblocks, false);
     const int hd = a.hd, last = a.S - 1;
     const float* Q0 = a.qkv + (int64_t)it.b * a.S * a.ldq + it.head * hd;
     const float* K0 = Q0 + a.n * hd;
@@ -293,7 +294,7 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_dq_kernel(Args a, int nblock
     d = sum_slots(d);
     H::row(Q0 + (int64_t)qc * a.ldq, hd, g, qf);
     const int64_t st = ((int64_t)it.b * a.n + it.head) * a.S;
-    if (wave == 0 && g == 0 && q <= last) a.delta[st + q] = d;
+    if (STORE_DELTA && wave == 0 && g == 0 && q <= last) a.delta[st + q] = d;
     const float L2 = a.lse[st + qc];
 
     f32x4 acc[NF];
@@ -342,20 +343,25 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_dq_kernel(Args a, int nblock
     }
 }
 
-// backward, dK and dV of 16 keys: sums over the queries q >= k; reads delta
 template <int HW, bool VEC>
-__global__ __launch_bounds__(64 * NW) void attn_f32_dkv_kernel(Args a, int nblocks) {
+__global__ __launch_bounds__(64 * NW) void attn_f32_dq_kernel(Args a, int nblocks) {
+    __shared__ __attribute__((aligned(16))) float sX[merge_floats<HW>()];
+    dq_block<HW, VEC, true>(a, item_of(nblocks, false), sX);
+}
+
+// backward, dK and dV of 16 keys: sums over the queries q >= k; reads delta (OWN_DELTA: computes it from dO's and O's rows)
+template <int HW, bool VEC, bool OWN_DELTA>
+__device__ inline void dkv_block(const Args& a, const Item it, float* sX) {
     typedef Head<HW, VEC> H;
     constexpr int NF = H::NF;
-    __shared__ __attribute__((aligned(16))) float sX[NW * 16 * (HW + 4)];
     const int tid = threadIdx.x, lane = tid & 63, l = lane & 15, g = lane >> 4;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const Item it = item_of(nblocks, true); // the first key blocks meet the most queries
     const int hd = a.hd, last = a.S - 1;
     const float* Q0 = a.qkv + (int64_t)it.b * a.S * a.ldq + it.head * hd;
     const float* K0 = Q0 + a.n * hd;
     const float* V0 = K0 + a.n * hd;
     const float* O0 = a.dO + (int64_t)it.b * a.S * a.ldo + it.head * hd;
+    const float* X0 = OWN_DELTA ? a.o + (int64_t)it.b * a.S * a.ldo + it.head * hd : nullptr; // O
     const int64_t st = ((int64_t)it.b * a.n + it.head) * a.S;
     const int k = it.row0 + l, kc = k < last ? k : last;
     f32x4 kf[NF], vf[NF];
@@ -371,10 +377,22 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_dkv_kernel(Args a, int nbloc
         H::row(Q0 + (int64_t)qrc * a.ldq, hd, g, qf);
         H::row(O0 + (int64_t)qrc * a.ldo, hd, g, of);
         float L2[4], dl[4], qc[4][NF], oc[4][NF];
+        float d = 0.f; // of query 16 t + l
+        if constexpr (OWN_DELTA) {
+            f32x4 xf[NF];
+            H::row(X0 + (int64_t)qrc * a.ldo, hd, g, xf);
+#pragma unroll
+            for (int i = 0; i < NF; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) d = __builtin_fmaf(of[i][j], xf[i][j], d);
+            d = sum_slots(d);
+        }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int q = 16 * t + 4 * g + j, c = q < last ? q : last;
-            L2[j] = a.lse[st + c], dl[j] = a.delta[st + c];
+            L2[j] = a.lse[st + c];
+            if constexpr (OWN_DELTA) dl[j] = __shfl(d, 4 * g + j, 64);
+            else dl[j] = a.delta[st + c];
             H::cols(Q0 + (int64_t)c * a.ldq, hd, l, qc[j]);
             H::cols(O0 + (int64_t)c * a.ldo, hd, l, oc[j]);
         }
@@ -415,8 +433,30 @@ __global__ __launch_bounds__(64 * NW) void attn_f32_dkv_kernel(Args a, int nbloc
     for (int r = 0; r < 4; ++r) {
         const int ka = it.row0 + 4 * wave + r;
         float* o = a.dqkv + ((int64_t)it.b * a.S + ka) * a.ldq + it.head * hd;
-        if (again >> (16 * r) & 1) attn_row_dkv(ar, ka, lane, a.lse + st, a.delta + st, o + a.n * hd, o + 2 * a.n * hd, (const float*)nullptr);
+        if (again >> (16 * r) & 1) attn_row_dkv(ar, ka, lane, a.lse + st, OWN_DELTA ? nullptr : a.delta + st, o + a.n * hd, o + 2 * a.n * hd, X0);
     }
+}
+
+template <int HW, bool VEC>
+__global__ __launch_bounds__(64 * NW) void attn_f32_dkv_kernel(Args a, int nblocks) {
+    __shared__ __attribute__((aligned(16))) float sX[merge_floats<HW>()];
+    dkv_block<HW, VEC, false>(a, item_of(nblocks, true), sX); // the first key blocks meet the most queries
+}
+
+// dK, dV and dQ as one launch, while the blocks are few: the chain of a block and the gap between two launches bound these, not
+// the matrix cores, and dK/dV does not wait for the delta of the other half.  Forward and backward of an attention, two launches / one:
+// 1 x 64 tokens, 4 heads of 64 (16 blocks) 39.8 / 31.1 us, 1 x 200, 4 of 128 92 / 78, 2 x 200, 6 of 80 97 / 85, 2 x 256, 4 of 128 109 / 96,
+// 2 x 256, 8 of 64 (256 blocks) 84.4 / 79.1, 2 x 256, 8 of 128 222 / 214, 2 x 256, 12 of 64 (384) 161 / 157; but 2 x 256, 16 of 64 (512)
+// 200.5 / 199.7 and 4 x 256, 16 of 32 (1024) 134 / 137, 4 x 512, 8 of 128 (1024) 685 / 774: many blocks pay for the registers of both halves
+// and for reading O again.
+template <int HW, bool VEC>
+__global__ __launch_bounds__(64 * NW) void attn_f32_bwd_kernel(Args a, int nblocks) {
+    __shared__ __attribute__((aligned(16))) float sX[merge_floats<HW>()];
+    const bool dkv = (int)blockIdx.x < a.n;
+    Item it = item_of(nblocks, dkv);
+    if (!dkv) it.head -= a.n;
+    if (dkv) dkv_block<HW, VEC, true>(a, it, sX);
+    else dq_block<HW, VEC, false>(a, it, sX);
 }
 
 Args make_args(const AttnCoreDesc& c) {
@@ -435,9 +475,19 @@ int fwd_t(const AttnCoreDesc& c, int nblocks, hipStream_t s) {
     attn_f32_fwd_kernel<HW, VEC><<<item_grid(nblocks, c.n, c.Bt), 64 * NW, 0, s>>>(make_args(c), nblocks);
     return launch_status();
 }
+// both launches as one, see attn_f32_bwd_kernel; few enough blocks to lie along the grid's slowest axis
+constexpr int kMergedBlocks = 384;
+static_assert(kMergedBlocks <= kSlowAxis, "heads along the fastest axis");
+bool merged_backward(const AttnCoreDesc& c, int nblocks) { return (int64_t)nblocks * c.n * c.Bt <= kMergedBlocks; }
+
 template <int HW, bool VEC>
 int bwd_t(const AttnCoreDesc& c, int nblocks, hipStream_t s) {
     const dim3 grid = item_grid(nblocks, c.n, c.Bt);
+    if (merged_backward(c, nblocks)) {
+        ProfileScope ps("attn_core_bwd", s);
+        attn_f32_bwd_kernel<HW, VEC><<<item_grid(nblocks, 2 * c.n, c.Bt), 64 * NW, 0, s>>>(make_args(c), nblocks);
+        return launch_status();
+    }
     {
         ProfileScope ps("attn_core_bwd_dq", s);
         attn_f32_dq_kernel<HW, VEC><<<grid, 64 * NW, 0, s>>>(make_args(c), nblocks);

@@ -14,7 +14,8 @@ CASES = [(AttnWorkload(f"merged_{dt}_{hd}_S{S}_{Bt}x{H}", Bt, S, 72, H, hd, H, 2
           ("bf16", 64, 8, 130, 16, 1), ("bf16", 50, 8, 130, 17, 0),
           # wider heads: four waves on a block, then eight
           ("bf16", 72, 1, 1, 2, 1), ("bf16", 96, 2, 33, 3, 1), ("bf16", 104, 1, 300, 2, 1), ("bf16", 128, 4, 200, 8, 1), ("bf16", 80, 4, 200, 9, 0),
-          ("bf16", 88, 1, 545, 2, 1), ("bf16", 120, 1, 1024, 8, 1), ("bf16", 80, 1, 1056, 8, 0))]
+          ("bf16", 88, 1, 545, 2, 1), ("bf16", 120, 1, 1024, 8, 1), ("bf16", 80, 1, 1056, 8, 0),
+          ("f32", 7, 1, 1, 2, 1), ("f32", 64, 2, 33, 3, 1), ("f32", 75, 1, 130, 2, 1), ("f32", 128, 8, 49, 12, 1), ("f32", 36, 8, 49, 13, 0))]
 
 
 @pytest.mark.parametrize("mode", ["fm", "bm"])
@@ -26,7 +27,7 @@ def test_backward_in_one_launch(sdp, orc, w, one, mode):
 
 
 # the smaller cases of test_gpu_attn.py run as one launch
-@pytest.mark.parametrize("w", [AttnWorkload("bad_two_bf16", 4, 200, 72, 9, 72, 9, 2, 92)],
+@pytest.mark.parametrize("w", [AttnWorkload("bad_two_f32", 8, 75, 24, 10, 32, 10, 2, 92, "f32"), AttnWorkload("bad_two_bf16", 4, 200, 72, 9, 72, 9, 2, 92)],
                          ids=lambda w: w.name)
 def test_bad_token_with_two_launches(sdp, w):
     with _Launches(sdp) as n:
