@@ -970,6 +970,7 @@ int launch_core(CoreKernel which, const CoreArgs& a, int nbh, const SideJobs& si
             return launch_status();
         }
     }
+    if (which == CORE_BWD) return SDP_ERR_UNSUPPORTED;
     if (which == CORE_FWD) attn_fwd_kernel<HW, KW><<<grid(fwd_lds<HW, KW>()), Split<KW>::THREADS, 0, s>>>(a, nblocks, nbh, side);
     else if (which == CORE_DQ) attn_bwd_dq_kernel<HW, KW><<<grid(dq_lds<HW, KW>()), Split<KW>::THREADS, 0, s>>>(a, nblocks, nbh, side);
     else attn_bwd_dkv_kernel<HW, KW><<<grid(DkvShape<HW, KW>::LDS), Split<KW>::THREADS, 0, s>>>(a, nblocks, nbh, side);
@@ -978,8 +979,8 @@ int launch_core(CoreKernel which, const CoreArgs& a, int nbh, const SideJobs& si
 int64_t whole_walks(int64_t S, int64_t nbh) { return (S + Split<1>::ROWS - 1) / Split<1>::ROWS * nbh; } // workgroups of a launch with KW = 1
 // see attn_bwd_kernel
 bool merged_backward(const CoreArgs& a, int64_t nbh) {
-    if (a.hd <= HD) return whole_walks(a.S, nbh) <= split_below(HD);
-    return ((int64_t)a.S + 31) / 32 * nbh <= (split_in_eight(a.hd, a.S, nbh) ? 256 : 224);
+    if (whole_walks(a.S, nbh) > split_below(a.hd)) return false; // the walked axis is not split
+    return a.hd <= HD || ((int64_t)a.S + 31) / 32 * nbh <= (split_in_eight(a.hd, a.S, nbh) ? 256 : 224);
 }
 template <int HW>
 int launch_core(CoreKernel which, const CoreArgs& a, int64_t nbh, const SideJobs& side, hipStream_t s) {

@@ -15,6 +15,8 @@ CASES = [(AttnWorkload(f"merged_{dt}_{hd}_S{S}_{Bt}x{H}", Bt, S, 72, H, hd, H, 2
           # wider heads: four waves on a block, then eight
           ("bf16", 72, 1, 1, 2, 1), ("bf16", 96, 2, 33, 3, 1), ("bf16", 104, 1, 300, 2, 1), ("bf16", 128, 4, 200, 8, 1), ("bf16", 80, 4, 200, 9, 0),
           ("bf16", 88, 1, 545, 2, 1), ("bf16", 120, 1, 1024, 8, 1), ("bf16", 80, 1, 1056, 8, 0),
+          # short sequences: as many blocks of 32 rows as of 128
+          ("bf16", 128, 48, 32, 4, 1), ("bf16", 128, 50, 32, 4, 0), ("bf16", 80, 56, 17, 4, 0),
           ("f32", 7, 1, 1, 2, 1), ("f32", 64, 2, 33, 3, 1), ("f32", 75, 1, 130, 2, 1), ("f32", 128, 8, 49, 12, 1), ("f32", 36, 8, 49, 13, 0))]
 
 
