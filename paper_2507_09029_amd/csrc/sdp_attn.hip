@@ -721,7 +721,8 @@ void attn_bwd_dq_kernel(CoreArgs a, int nblocks, int nbh, SideJobs side) {
 // (32) leave no room for its V rows (32) and the pieces of 64 staged queries (32) under the 256 registers of two waves
 // per SIMD: the workgroup's V rows then stay in LDS and are read from there per block, and a tile has 32 queries.  At
 // HW = 96 the shorter tile is enough.  (KW = 4 runs one wave per SIMD there: 512 registers, all operands kept.  KW = 8, two
-// waves per SIMD and the pieces of two whole tiles in every wave's registers, keeps the block's K rows in LDS as well.)
+// waves per SIMD and the pieces of two whole tiles in every wave's registers, keeps the block's V rows in LDS at HW = 96, its K and
+// V rows at HW = 128, behind a barrier of their own.)
 template <int HW, int KW>
 struct DkvShape {
     static constexpr bool kVInLds = HW == 128 ? KW != 4 : HW == 96 && KW == 8, kKInLds = HW == 128 && KW == 8;
@@ -766,11 +767,11 @@ __device__ inline void attn_bwd_dkv_block(const CoreArgs& a, const int k0, const
         TileMover<Split<KW>::THREADS / 64, HW, Split<KW>::ROWS> mv, mk;
         mv.fetch(gV, (uint32_t)a.ldq, k0, S - 1, hd, tid);
         if constexpr (kKInLds) mk.fetch(gK, (uint32_t)a.ldq, k0, S - 1, hd, tid);
-        mv.stash(sV, hd, tid); // KW = 1: read after the barriers of the first tile
-        if constexpr (kKInLds) {
-            mk.stash(sK, hd, tid);
-            __syncthreads();
-        }
+        mv.stash(sV, hd, tid);
+        if constexpr (kKInLds) mk.stash(sK, hd, tid);
+        // Every wave reads rows that all of them have put away.  KW = 1: after the barriers of the first tile; KW > 1 has none in
+        // its loop.
+        if constexpr (KW > 1) __syncthreads();
     } else {
         load_row_operand<HW>(gV, a.ldq, kc, hd, lhi, vf);
     }

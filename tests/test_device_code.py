@@ -5,7 +5,10 @@ for them.  Two hazards apply: a scalar register that the vector unit wrote may b
 states later, M0 by a load to LDS one instruction after a scalar move.  Each such load from a scalar base must stand behind
     s_mov_b32 m0, ..
     s_mov_b64 <its scalar base>, ..
-and the move's source may come from wherever it likes (the scalar unit waits for the vector unit by itself)."""
+and the move's source may come from wherever it likes (the scalar unit waits for the vector unit by itself).
+
+The attention core's matrix instructions that read LDS rows which the whole workgroup has put there stand behind a barrier on every
+path from the kernel's entry."""
 import os
 import re
 import subprocess
@@ -34,17 +37,70 @@ def unsafe_loads(lines):
     return n, bad
 
 
-def test_written_out_loads_meet_their_hazards(tmp_path):
+def gfx950_code(folder):
+    """the disassembly of each of the library's device objects, as lines"""
     if not os.path.exists(OBJDUMP):
         pytest.skip("no llvm-objdump")
     lib = build.LIB if os.path.exists(build.LIB) else build.build_library()
-    local = tmp_path / "lib.so"
+    local = folder / "lib.so"
     os.symlink(lib, local)
-    subprocess.run([OBJDUMP, "--offloading", str(local)], cwd=tmp_path, check=True, stdout=subprocess.DEVNULL)
+    subprocess.run([OBJDUMP, "--offloading", str(local)], cwd=folder, check=True, stdout=subprocess.DEVNULL)
+    for obj in sorted(folder.glob("lib.so.*gfx950")):
+        yield subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", str(obj)], check=True, capture_output=True, text=True).stdout.splitlines()
+
+
+def test_written_out_loads_meet_their_hazards(tmp_path):
     total, bad = 0, []
-    for obj in sorted(tmp_path.glob("lib.so.*gfx950")):
-        text = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", str(obj)], check=True, capture_output=True, text=True).stdout
-        n, b = unsafe_loads([line.split("//")[0].strip() for line in text.splitlines()])
+    for lines in gfx950_code(tmp_path):
+        n, b = unsafe_loads([line.split("//")[0].strip() for line in lines])
         total, bad = total + n, bad + b
     assert total > 0
     assert not bad, "\n\n".join("\n".join(b) for b in bad[:3]) + f"\n{len(bad)} of {total} loads"
+
+
+def kernels(lines):
+    """{symbol: [(offset, instruction, offset of the branch target or None)]}"""
+    out, code, base = {}, None, 0
+    for line in lines:
+        m = re.match(r"([0-9a-f]+) <(.*)>:", line)
+        if m:
+            base, code = int(m[1], 16), out.setdefault(m[2], [])
+        elif code is not None and "//" in line:
+            ins, note = line.split("//", 1)
+            target = re.search(r"\+0x([0-9a-f]+)>\s*$", note)
+            code.append((int(note.split(":")[0], 16) - base, ins.strip(), int(target[1], 16) if target else None))
+    return out
+
+
+def mfmas_before_a_barrier(code):
+    """matrix instructions that some path from the entry reaches without a barrier"""
+    at = {offset: i for i, (offset, _, _) in enumerate(code)}
+    seen, todo, n = set(), [0], 0
+    while todo:
+        i = todo.pop()
+        while i is not None and i not in seen:
+            seen.add(i)
+            _, ins, target = code[i]
+            assert not ins.startswith(("s_setpc", "s_swappc")), "the paths cannot be followed"
+            if ins.startswith(("s_barrier", "s_endpgm")):
+                break
+            n += ins.startswith("v_mfma")
+            if ins.startswith("s_cbranch"):
+                todo.append(at[target])
+            i = at[target] if ins.startswith("s_branch") else i + 1
+    return n
+
+
+def test_rows_that_a_workgroup_shares_are_read_behind_a_barrier(tmp_path):
+    counts = {}
+    for lines in gfx950_code(tmp_path):
+        for symbol, code in kernels(lines).items():
+            k = re.search(r"(attn_(?:fwd|bwd|bwd_dq|bwd_dkv)_kernel)ILi(\d+)ELi(\d)EE", symbol)
+            if k:
+                counts[k[1], int(k[2]), int(k[3])] = mfmas_before_a_barrier(code)
+    # one wave along the walked axis: the workgroup's tiles; eight: dK/dV's rows of V (heads above 64), of K (above 96)
+    shared = {(name, hw, 1): 0 for name in ("attn_fwd_kernel", "attn_bwd_dq_kernel", "attn_bwd_dkv_kernel") for hw in (64, 96, 128)}
+    shared |= {("attn_bwd_dkv_kernel", hw, 8): 0 for hw in (96, 128)}
+    # dK/dV and dQ in one launch: dQ's waves have tiles of their own, and no more than these come without a barrier
+    shared |= {("attn_bwd_kernel", hw, 8): counts["attn_bwd_dq_kernel", hw, 8] for hw in (96, 128)}
+    assert {k: counts[k] for k in shared} == shared
