@@ -25,6 +25,7 @@
 // are, for this lane, the depth indices {16 s + 4 (L / 32) + r} and {16 s + 8 + 4 (L / 32) + r}, and the other
 // operand is read from LDS in that same order with two transposing reads (ds_read_tr16_b64), which turn a
 // row-major [depth][column] tile into the per-lane layout of an A operand.
+#include "sdp_attn_rule.h"
 #include "sdp_attn_rows.h"
 #include "sdp_transpose.h"
 
@@ -926,7 +927,6 @@ void attn_bwd_dkv_kernel(CoreArgs a, int nblocks, int nbh, SideJobs side) {
 // of 128 49.9 / 40.9, 1 x 512, 4 67 / 55.8, 1 x 1500, 4 105 / 92.6, 1 x 1024, 8 (256 blocks, KW = 8) 106.8 / 101.9, 1 x 155, 13 of 96
 // 77.5 / 68.1, 2 x 200, 8 of 128 69.4 / 62; but 2 x 256, 16 (256, KW = 4) 114.3 / 115.7, 1 x 1100, 8 of 96 (280) 103.8 / 110.6, 2 x 1024,
 // 12 of 128 (768) 244 / 270: the re-read of O and the longer tail of a launch of several rounds cost more than the gap there.
-constexpr bool merged(int hw, int kw) { return kw > 1; }
 template <int HW, int KW>
 __global__ __launch_bounds__(Split<KW>::THREADS) __attribute__((amdgpu_waves_per_eu(waves_dkv(HW, KW), waves_dkv(HW, KW))))
 void attn_bwd_kernel(CoreArgs a, int nblocks, int nbh, SideJobs side) {
@@ -942,19 +942,6 @@ void attn_bwd_kernel(CoreArgs a, int nblocks, int nbh, SideJobs side) {
     else attn_bwd_dq_block<HW, KW, false>(a, blk * Split<KW>::ROWS, head, b, lds);
 }
 
-// KW = 4 up to this many workgroups of the KW = 1 form, i.e. while those leave CUs idle: its shorter chains then weigh
-// more than the re-reads.  Block forward + backward in us, KW = 1 / KW = 4: heads of 64, 96 workgroups (1 x 1024 tokens,
-// 12 heads) 158 / 124, 192 (2 x 1024) 168 / 149, 384 (4 x 1024) 184 / 187; heads of 128, 64 workgroups (1 x 1024, 8 heads)
-// 238 / 165, 128 (2 x 1024) 249 / 203, 256 (4 x 1024) 267 / 281; heads of 96, 192 workgroups 208 / 195.
-constexpr int split_below(int hw) { return hw <= HD ? 256 : 192; }
-// KW = 8 (heads wider than 64): a chain half as long again, two waves on a SIMD where KW = 4 with a workgroup per CU has one, for
-// partial results of eight waves to add.  What it shortens grows with S, what it adds with the workgroups: taken from 512 tokens
-// on while four times the workgroups are no more than the tokens.  KW = 4 / KW = 8 at one sequence of 512, 1024, 1500, 2048 tokens
-// and 4, 4, 4, 8 heads: of 128 77 / 75, 103 / 95, 132 / 117, 250 / 232 us; of 96 72 / 70, 94 / 87, 119 / 105, 203 / 193; beyond that
-// line, 2 x 512 tokens, 8 heads: of 128 97 / 98, of 96 86 / 90; 4 x 256, 16 heads 148 / 150, 126 / 130.  Heads of 64 do not gain
-// (1 x 512, 8 heads 61 / 62; 1 x 2048 109 / 124): their tiles are half as long.
-inline bool split_in_eight(int hw, int64_t S, int64_t nbh) { return hw > HD && S >= 512 && (S + 31) / 32 * nbh * 4 <= S; }
-
 enum CoreKernel { CORE_FWD, CORE_DQ, CORE_DKV, CORE_BWD };
 template <int HW, int KW>
 int launch_core(CoreKernel which, const CoreArgs& a, int nbh, const SideJobs& side, hipStream_t s) {
@@ -964,7 +951,7 @@ int launch_core(CoreKernel which, const CoreArgs& a, int nbh, const SideJobs& si
         const int per = side_tiles(lds / HALVES) * HALVES;
         return workgroup_grid((int64_t)nblocks * nbh * kernels + (side.end[kMaxTransposeJobs - 1] + per - 1) / per);
     };
-    if constexpr (merged(HW, KW)) {
+    if constexpr (KW > 1) {
         constexpr int LDS = dq_lds<HW, KW>() > DkvShape<HW, KW>::LDS ? dq_lds<HW, KW>() : DkvShape<HW, KW>::LDS;
         if (which == CORE_BWD) {
             attn_bwd_kernel<HW, KW><<<grid(LDS, 2), Split<KW>::THREADS, 0, s>>>(a, nblocks, nbh, side);
@@ -977,20 +964,14 @@ int launch_core(CoreKernel which, const CoreArgs& a, int nbh, const SideJobs& si
     else attn_bwd_dkv_kernel<HW, KW><<<grid(DkvShape<HW, KW>::LDS), Split<KW>::THREADS, 0, s>>>(a, nblocks, nbh, side);
     return launch_status();
 }
-int64_t whole_walks(int64_t S, int64_t nbh) { return (S + Split<1>::ROWS - 1) / Split<1>::ROWS * nbh; } // workgroups of a launch with KW = 1
-// see attn_bwd_kernel
-bool merged_backward(const CoreArgs& a, int64_t nbh) {
-    if (whole_walks(a.S, nbh) > split_below(a.hd)) return false; // the walked axis is not split
-    return a.hd <= HD || ((int64_t)a.S + 31) / 32 * nbh <= (split_in_eight(a.hd, a.S, nbh) ? 256 : 224);
-}
 template <int HW>
 int launch_core(CoreKernel which, const CoreArgs& a, int64_t nbh, const SideJobs& side, hipStream_t s) {
-    const int64_t wide = whole_walks(a.S, nbh);
-    if (wide > INT32_MAX / 2) return SDP_ERR_UNSUPPORTED;
+    if (core_blocks_128(a.S, nbh) > INT32_MAX / 2) return SDP_ERR_UNSUPPORTED;
+    const int kw = core_waves(a.hd, a.S, nbh);
     if constexpr (HW > HD) {
-        if (split_in_eight(HW, a.S, nbh)) return launch_core<HW, 8>(which, a, (int)nbh, side, s);
+        if (kw == 8) return launch_core<HW, 8>(which, a, (int)nbh, side, s);
     }
-    return wide <= split_below(HW) ? launch_core<HW, 4>(which, a, (int)nbh, side, s) : launch_core<HW, 1>(which, a, (int)nbh, side, s);
+    return kw == 4 ? launch_core<HW, 4>(which, a, (int)nbh, side, s) : launch_core<HW, 1>(which, a, (int)nbh, side, s);
 }
 // the core kernel and, in its launch, n transposes
 int launch_core(CoreKernel which, const CoreArgs& a, int64_t nbh, const TransposeJob* jobs, int n, const char* name, hipStream_t s) {
@@ -1406,7 +1387,7 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
                                            {dY, w.dYt, d, ldt, nullptr, T, d}};
         const TransposeJob beside_dkv{w.dQKV, w.dQKVt, 3 * E, ldt, nullptr, T, E}; // dQ
         const int skip = stored ? 1 : 0; // dX needs no copy of Wqkv
-        const bool one = merged_backward(a, (int64_t)hr * Bt) && (direct || !want_dw);
+        const bool one = core_merged_backward(a.hd, a.S, (int64_t)hr * Bt) && (direct || !want_dw);
         rc = launch_core(one ? CORE_BWD : CORE_DQ, a, (int64_t)hr * Bt, beside_dq + skip, (want_dw && !direct ? 4 : 1) - skip,
                          one ? "attn_core_bwd" : "attn_core_bwd_dq", s);
         // reads the delta written by the dQ kernel

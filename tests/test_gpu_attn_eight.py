@@ -1,5 +1,5 @@
-"""GPU: bf16 heads wider than 64 where eight waves share a block's walk (from 512 tokens on, four times the blocks of 32 rows at
-most the tokens), at the edges of that rule, of its 32-row tiles and of the widths.  Tolerances and their reasons: test_gpu_attn.py."""
+"""GPU: bf16 heads wider than 64 where eight waves share a block's walk (from 512 tokens on, up to 8 pairs of sequence and head; the
+rule itself: test_attn_rule.py), at the edges of its 32-row tiles and of the widths.  Tolerances and their reasons: test_gpu_attn.py."""
 import pytest
 
 import test_gpu_attn as t
@@ -10,8 +10,9 @@ sdp = t.sdp  # the fixture
 
 CASES = [AttnWorkload(f"eight{hd}_S{S}_{Bt}x{ph}", Bt, S, 72, H, hd, ph, 2, 61) for hd, Bt, S, H, ph in
          ((72, 1, 512, 3, 2), (96, 2, 545, 3, 2), (104, 1, 575, 3, 2), (128, 1, 513, 3, 2), (120, 1, 800, 2, 1),
-          (80, 1, 512, 9, 8),    # 128 blocks on 512 tokens: the last that qualifies (forward masking)
+          (80, 1, 512, 9, 8),    # the most pairs that qualify (forward masking)
           (80, 1, 512, 10, 9),   # one head more
+          (88, 2, 515, 5, 4), (128, 1, 515, 9, 8),  # as many pairs, tokens that are no multiple of 32
           (128, 1, 511, 3, 2))]  # one token short
 
 
