@@ -11,6 +11,7 @@
 // that row's fp32 parameters and moments, which are read and written once; rows nobody covers are
 // left untouched.  A third form (sdp_coverage_grad_sqnorm) stores nothing and returns the squared norm of
 // the average, which global gradient clipping needs before that fused update.
+#include "sdp_avg_group.h"
 #include "sdp_internal.h"
 
 #include <cmath>
@@ -89,6 +90,7 @@ __device__ inline void adamw_one(const AdamArgs& a, float gs, float g, float& th
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef u32x4 __attribute__((aligned(2))) u32x4_any; // at the address of any parameter
 
 __device__ inline void add_bf16x8(const u32x4 w, float (&acc)[8]) {
     // a bf16 is the high half of an fp32: even elements sit in the low 16 bits of each word
@@ -281,9 +283,13 @@ __device__ inline double average_one(const GradPtrs& g, const uint8_t* __restric
 // parameters idle there.  8 workers, bf16, two thirds of the rows each, before / now: 60000 x 64 52.4 / 12.5 us (1.1 / 4.5 TB/s),
 // 100000 x 264 101 / 69, 100000 x 520 194 / 129, 100000 x 1288 347 / 314; with norm and update 100000 x 264 291 / 234, 100000 x 1288
 // 1147 / 1081.
-// STRADDLE: the same for rows that are no multiple of 8 (from 8 on): a group may hold the end of one row and the start of the next, and
-// takes each worker's parameters of those of the two that it trains.  One thread per parameter / this: 60000 x 1501 1086 / 218 us
-// (1.2 / 6.0 TB/s), 30000 x 257 75 / 25, with norm and update 2503 / 782 and 168 / 81.
+// STRADDLE: the same for rows that are no multiple of 8 (from 8 on): a group may hold the end of one row and the start of the next.  A
+// worker that trains both is asked for the group's 8 parameters; one that trains a single row for 8 of that row, which are then moved to
+// their places (group_shift, group_align), as rows a worker does not train are never read.  One thread per parameter / this, bf16, 8
+// workers: 60000 x 1501 1100 / 216 us (1.2 / 6.1 TB/s), 30000 x 257 105 / 24, 1000000 x 9 138 / 38, with norm and update 2531 / 771, 233 / 88
+// and 288 / 116; fp32 30000 x 257 109 / 40 and 235 / 108.  (Reading the whole group in every case: 1000000 x 9 33.5, 109, others up to 6 %
+// less.)  fp32 moves without asking whether it must: with a branch around it the compiler keeps a second copy of the batch's
+// registers (174 instead of 124, two waves a SIMD instead of four, 67 us instead of 40 at 30000 x 257).
 template <int BF16, int OPT, int STRADDLE>
 __global__ __launch_bounds__(256) void avg_groups_kernel(GradPtrs g, const uint8_t* __restrict__ mask, int K, int64_t R,
                                                          int D, double inv_d, float* __restrict__ out,
@@ -337,20 +343,18 @@ __global__ __launch_bounds__(256) void avg_groups_kernel(GradPtrs g, const uint8
                 mk1[i] = STRADDLE ? (int)mask[(int64_t)k * R + (two ? r + 1 : R - 1)] : 0;
             }
             bool covered[kBatch], covered1[kBatch];
-            u32x4 lo[kBatch];
-            f32x4 hi[kBatch];
+            // straddling, trained on one side: 8 parameters of that row, at the address of any of them
+            typedef std::conditional_t<STRADDLE, u32x4_any, u32x4> Piece;
+            auto shift = [&](int i) { return STRADDLE && two ? sdp::group_shift(split, covered[i], covered1[i]) : 0; };
+            u32x4 lo[kBatch], hi[kBatch];
 #pragma unroll
             for (int i = 0; i < kBatch; ++i) {
                 covered[i] = k0 + i < K && live && mk[i] != 0;
                 covered1[i] = STRADDLE && k0 + i < K && two && mk1[i] != 0;
                 if (covered[i] || covered1[i]) {
-                    if (BF16) {
-                        lo[i] = __builtin_nontemporal_load((const u32x4*)((const uint16_t*)g.p[k0 + i] + off));
-                    } else {
-                        const u32x4* src = (const u32x4*)((const float*)g.p[k0 + i] + off);
-                        lo[i] = __builtin_nontemporal_load(src);
-                        hi[i] = __builtin_nontemporal_load((const f32x4*)(src + 1));
-                    }
+                    const Piece* src = (const Piece*)((const char*)g.p[k0 + i] + (off + shift(i)) * (BF16 ? 2 : 4));
+                    lo[i] = __builtin_nontemporal_load(src);
+                    if (!BF16) hi[i] = __builtin_nontemporal_load(src + 1);
                 }
             }
 #pragma unroll
@@ -358,26 +362,16 @@ __global__ __launch_bounds__(256) void avg_groups_kernel(GradPtrs g, const uint8
                 if (!covered[i] && !covered1[i]) continue;
                 c += covered[i];
                 c1 += covered1[i];
-                if (STRADDLE) {
-                    // a row nobody of this worker trains is read where the group straddles two, and not used
-                    float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-                    if (BF16) {
-                        add_bf16x8(lo[i], x);
-                    } else {
-#pragma unroll
-                        for (int q = 0; q < 4; ++q) x[q] = __uint_as_float(lo[i][q]), x[4 + q] = hi[i][q];
-                    }
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) acc[q] += (q < split ? covered[i] : covered1[i]) ? x[q] : 0.f;
-                } else if (BF16) {
-                    add_bf16x8(lo[i], acc);
+                float x[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+                if (BF16) {
+                    add_bf16x8(lo[i], x);
                 } else {
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        acc[q] += __uint_as_float(lo[i][q]);
-                        acc[4 + q] += hi[i][q];
-                    }
+                    for (int q = 0; q < 4; ++q) x[q] = __uint_as_float(lo[i][q]), x[4 + q] = __uint_as_float(hi[i][q]);
                 }
+                if (STRADDLE && (!BF16 || shift(i) != 0)) sdp::group_align(x, shift(i));
+#pragma unroll
+                for (int q = 0; q < 8; ++q) acc[q] += x[q];
             }
         }
         // coverage of parameter i's row
