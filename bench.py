@@ -263,6 +263,11 @@ def bench_grad_avg_1b(sdp, torch, steps):
     return res
 
 
+def attention_core_ms(kern):
+    """(forward, backward) of the attention core from the per-kernel times: the backward is one launch or two"""
+    return kern["attn_core_fwd"], sum(ms for name, ms in kern.items() if name.startswith("attn_core_bwd"))
+
+
 def bench_attention(sdp, torch, steps, w=None):
     """One worker's head-masked attention block (forward + backward) at the 500M-like width: not part of `value`."""
     import workloads
@@ -302,14 +307,15 @@ def bench_attention(sdp, torch, steps, w=None):
     kern = {name: tot / calls for name, (calls, tot) in prof.items() if name.startswith("attn_")}
     core_fwd = 2 * w.Bt * w.ph * w.S * w.S * w.hd
     core_bwd = 5 * w.Bt * w.ph * w.S * w.S * w.hd
-    core_ms = kern["attn_core_fwd"] + kern["attn_core_bwd_dq"] + kern["attn_core_bwd_dkv"]
+    core_fwd_ms, core_bwd_ms = attention_core_ms(kern)
+    core_ms = core_fwd_ms + core_bwd_ms
     return {
         "workload": w.name, "sequences": w.Bt, "seq_len": w.S, "d_model": w.d, "heads": w.H, "head_dim": w.hd,
         "held_heads": w.ph, "workers_simulated": w.K, "active_flop_per_worker": w.active_flop_per_worker,
         "ms_per_worker": ms / w.K, "value": w.active_flop_per_worker * w.K / (ms * 1e-3) / 1e12, "unit": "TFLOP/s",
         "kernels_avg_ms": kern,
-        "core": {"forward_tflops": core_fwd / (kern["attn_core_fwd"] * 1e-3) / 1e12,
-                 "backward_tflops": core_bwd / ((core_ms - kern["attn_core_fwd"]) * 1e-3) / 1e12,
+        "core": {"forward_tflops": core_fwd / (core_fwd_ms * 1e-3) / 1e12,
+                 "backward_tflops": core_bwd / (core_bwd_ms * 1e-3) / 1e12,
                  "roofline": {"bound": "mfma", "achieved": (core_fwd + core_bwd) / (core_ms * 1e-3) / 1e12,
                               "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                               "frac": (core_fwd + core_bwd) / (core_ms * 1e-3) / 1e12 / PEAK_BF16_TFLOPS, "traffic": None},
