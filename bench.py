@@ -86,13 +86,22 @@ def flops_per_launch(name, w):
         "mlp_dact": 2 * w.T * w.d * n,
         "mlp_dx": 4 * w.T * w.d * n,
         "mlp_dw": 6 * w.T * w.d * w.p,  # one batched launch for dW1, dW3, dW2T
-        "mlp_dx_dw": 4 * w.T * w.d * n + 6 * w.T * w.d * w.p,  # fp32: dX and the weight gradients as one launch
+        "mlp_dx_dw": 4 * w.T * w.d * n + 6 * w.T * w.d * w.p,  # dX and the weight gradients as one launch: fp32, and small bf16 launches
     }.get(name)
 
 
 # bf16: transposes that a launch carries as extra workgroups when its last round leaves CUs idle; otherwise they are a
-# launch of their own, under this name.  A carrying kernel's time and rate include them.
+# launch of their own, under this name.  A carrying kernel's time and rate include them.  Launches of 64 x 64 tiles read the weights as
+# they are stored: no transposes then.
 CARRIED = {"mlp_gate_up": "mlp_wt_fwd", "mlp_dact": "mlp_tr_bwd (in this launch, or in that of mlp_dw)"}
+
+
+def carries(name, tiles):
+    """What the bf16 launch `name` carries, given the kernels that were launched and their tiles ({kernel: "BMxBN" or None}): nothing
+    where its transposes were a launch of their own, or where the contraction that would read them may take the weights as they are stored."""
+    note = CARRIED.get(name)
+    reader = {"mlp_gate_up": "mlp_down", "mlp_dact": "mlp_dx"}.get(name)
+    return note if note and note.split()[0] not in tiles and reader in tiles and tiles[reader] != "64x64" else None
 
 
 def _omp_threads(n=None):
@@ -543,6 +552,7 @@ def bench_mlp(sdp, torch, w, a, steps, warmup):
     # cost about a tenth of the step, so the timed region below only brackets that one kernel.
     def per_kernel(prof, nsteps, step_ms):
         out = {}
+        tiles = {name: (sdp.profile_launch_shape(name) or {}).get("tile") for name in prof}
         for name, (calls, ms) in prof.items():
             f = flops_per_launch(name, w)
             avg_ms = ms / calls
@@ -550,8 +560,8 @@ def bench_mlp(sdp, torch, w, a, steps, warmup):
             if f:
                 out[name]["tflops"] = f / (avg_ms * 1e-3) / 1e12
                 out[name]["launch"] = sdp.profile_launch_shape(name)
-            if w.dtype == "bf16" and name in CARRIED and CARRIED[name].split()[0] not in prof:
-                out[name]["carries"] = CARRIED[name]
+            if w.dtype == "bf16" and carries(name, tiles):
+                out[name]["carries"] = carries(name, tiles)
         return out
 
     kernels, dominant = {}, None

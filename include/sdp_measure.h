@@ -32,6 +32,7 @@ int sdp_profile_read(int cap, const char** names, int64_t* calls, double* ms);
  * while timing was on: what a recorded counter figure for that kernel has to be matched against.
  *   tile_m, tile_n: outputs per workgroup;  group_m: tile-rows walked together;  stacked: 1 if the problems of a
  *   batched launch that share an operand were walked as one matrix.  All host out.
+ * dX beside the weight gradients in one launch ("mlp_dx_dw", "attn_dx_dw"): each of the two under its own name ("mlp_dx", "mlp_dw").
  * INVALID_ARG when a pointer is null or no such launch has been seen. */
 int sdp_profile_launch_shape(const char* name, int* tile_m, int* tile_n, int* group_m, int* stacked);
 

@@ -26,18 +26,22 @@ sys.path.insert(0, ROOT)
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "hbm_traffic_recorded.json")
 COPY_NAME = "__amd_rocclr_copyBuffer"
 
-# call-site name of each contraction <-> the <epilogue, op> template arguments of its kernel symbol
+# call-site name of each contraction <-> the <epilogue, op> template arguments of its kernel symbol (dX beside the weight gradients in
+# one launch: sdp_gemm_pair_kernel<BX, BW, epilogue of dX, ..>)
 SITE_OF = {(2, 0): "mlp_gate_up", (0, 1): "mlp_down", (3, 2): "mlp_dact", (1, 3): "mlp_dx", (0, 4): "mlp_dw",
            (0, 6): "mlp_dw"}  # op 6: the weight-gradient launch with the tiles of its last round cut in depth
 
 
 def kernel_site(kernel_name):
-    """'mlp_dw' etc. for an sdp_gemm_kernel<BM, BN, WM, WN, EPI, OP> symbol, 'coverage_grad_avg' for the storing
-    average, the calibration copy's own name, else None."""
+    """'mlp_dw' etc. for an sdp_gemm_kernel<BM, BN, WM, WN, EPI, OP, ..> symbol, 'mlp_dx_dw' for an sdp_gemm_pair_kernel with dX of the
+    MLP, 'coverage_grad_avg' for the storing average, the calibration copy's own name, else None."""
     if COPY_NAME in kernel_name:
         return COPY_NAME
-    if "avg_rows_kernel<1, 0>" in kernel_name or "avg_rows_kernel<true, 0>" in kernel_name:
+    if "avg_rows_kernel<1, 0>" in kernel_name or "avg_rows_kernel<true, 0>" in kernel_name or "avg_groups_kernel<1, 0, " in kernel_name:
         return "coverage_grad_avg"
+    if "sdp_gemm_pair_kernel<" in kernel_name:
+        args = kernel_name.split("sdp_gemm_pair_kernel<", 1)[1].split(">", 1)[0].split(",")
+        return "mlp_dx_dw" if args[2].strip() == "1" else None
     if "tail_reduce_kernel" in kernel_name:
         return "mlp_dw_reduce"
     if "sdp_gemm_kernel<" in kernel_name:
@@ -158,7 +162,7 @@ def run(what, workload_name, zeros):
             Y, G, U = sdp.masked_mlp_fwd(w.mode, X, *Wd, idx[0])
             sdp.masked_mlp_bwd(w.mode, X, dY, *Wd, idx[0], G, U)
         torch.cuda.synchronize()
-        for site in set(SITE_OF.values()):
+        for site in set(SITE_OF.values()):  # the two of a paired launch under their own names
             shapes["launch"][site] = sdp.profile_launch_shape(site)
         sdp.profile_enable(False)
         print(f"{name}: one worker fwd+bwd x{reps}", flush=True)
