@@ -18,20 +18,21 @@ import pytest
 from paper_2507_09029_amd import build
 
 OBJDUMP = os.path.join(os.environ.get("ROCM_PATH", "/opt/rocm"), "llvm", "bin", "llvm-objdump")
-KERNEL = re.compile(r"[0-9a-f]+ <.*sdp_gemm_kernelI(?:Li\d+E){6}Li(\d)EEE.*>:")  # the last argument: which operands are depth-major
+# the last argument: which operands are depth-major; two contractions in one launch always have some
+KERNEL = re.compile(r"[0-9a-f]+ <.*sdp_gemm_(?:kernelI(?:Li\d+E){6}Li(\d)E|(pair)_kernelI(?:Li\d+E){5})EE.*>:")
 LOAD = re.compile(r"global_load_lds_dwordx4 v\d+, (s\[\d+:\d+\])")
 
 
 def unsafe_loads(lines):
-    """(scalar-base loads to LDS in the kernels that write them out, those that are not preceded by the two moves)"""
-    n, bad, written_out = 0, [], False
+    """({in a pair's kernel: scalar-base loads to LDS where they are written out}, those that are not preceded by the two moves)"""
+    n, bad, written_out, pair = {False: 0, True: 0}, [], False, False
     for i, line in enumerate(lines):
         if line.endswith(">:"):
             k = KERNEL.match(line)
-            written_out = bool(k) and k[1] != "0"
+            written_out, pair = bool(k) and k[1] != "0", bool(k) and bool(k[2])
         m = LOAD.match(line)
         if m and written_out:
-            n += 1
+            n[pair] += 1
             if not lines[i - 1].startswith(f"s_mov_b64 {m[1]}, ") or not lines[i - 2].startswith("s_mov_b32 m0, "):
                 bad.append(lines[max(0, i - 6): i + 1])
     return n, bad
@@ -50,12 +51,12 @@ def gfx950_code(folder):
 
 
 def test_written_out_loads_meet_their_hazards(tmp_path):
-    total, bad = 0, []
+    single, pairs, bad = 0, 0, []
     for lines in gfx950_code(tmp_path):
         n, b = unsafe_loads([line.split("//")[0].strip() for line in lines])
-        total, bad = total + n, bad + b
-    assert total > 0
-    assert not bad, "\n\n".join("\n".join(b) for b in bad[:3]) + f"\n{len(bad)} of {total} loads"
+        single, pairs, bad = single + n[False], pairs + n[True], bad + b
+    assert single > 0 and pairs > 0
+    assert not bad, "\n\n".join("\n".join(b) for b in bad[:3]) + f"\n{len(bad)} of {single + pairs} loads"
 
 
 def kernels(lines):
