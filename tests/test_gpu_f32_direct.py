@@ -2,6 +2,7 @@
 16-byte loads and with single floats (extents that are no multiples of 4, gathered columns): partial tiles, one to several depth
 steps, launches of dX and the weight gradients together and apart.  1e-5 against the fp64 oracle."""
 import pytest
+import torch
 
 import test_gpu_mlp as mlp
 from workloads import MlpWorkload
@@ -24,3 +25,22 @@ CASES = [MlpWorkload(f"{T}x{d}x{F}p{p}_{mode}", "f32", T, d, F, p, 2, mode, 81) 
 @pytest.mark.parametrize("w", CASES, ids=[w.name for w in CASES])
 def test_f32_direct_load_tiles(sdp, orc, w):
     mlp.run_case(sdp, orc, w, [1], dw_layout="scatter" if w.p % 2 else "compact")
+
+
+# lists that LDS does not take, on outputs for which the register-staged tiles of 64 and 128 are chosen (256 and 1024 tiles of 64),
+# with 16-byte loads and with single floats.  Reference: plain PyTorch in fp64; 4100 products summed in fp32 stay below 1e-5 normwise.
+@pytest.mark.parametrize("T,d,F,p", [(1024, 1024, 4200, 4100), (1023, 1021, 4201, 4097), (2048, 2048, 4200, 4100), (2047, 2045, 4201, 4097)])
+def test_f32_long_lists_on_large_tiles(sdp, T, d, F, p):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(82)
+    rnd = lambda *s, std=1.0: torch.randn(s, generator=g, device="cuda") * std
+    X, dY, W = rnd(T, d), rnd(T, d), [rnd(F, d, std=0.02) for _ in range(3)]
+    idx = sdp.make_masks(2, F, p, 5, True)[1][0].contiguous()
+    Y, G, U = sdp.masked_mlp_fwd("fm", X, *W, idx)
+    dX = sdp.masked_mlp_bwd("fm", X, dY, *W, idx, G, U)[0]
+    W1, W3, W2T = (t[idx.long()].double() for t in W)
+    G64, U64 = X.double() @ W1.t(), X.double() @ W3.t()
+    s = torch.sigmoid(G64)
+    dA = dY.double() @ W2T.t()
+    for got, want in ((Y, (G64 * s * U64) @ W2T), (dX, (dA * U64 * (s + G64 * s * (1 - s))) @ W1 + (dA * G64 * s) @ W3)):
+        assert float((got.double() - want).norm() / want.norm()) <= 1e-5
