@@ -921,7 +921,7 @@ void attn_bwd_dkv_kernel(CoreArgs a, int nblocks, int nbh, SideJobs side) {
 // dK, dV and dQ as one launch, where the walked axis is split: either alone leaves CUs idle, and what a launch costs between two
 // kernels is a sixteenth of such a call.  dK/dV then takes delta from dO and O itself.  Forward and backward of an attention, two
 // launches / one, heads up to 64: 2 x 256 tokens, 6 heads of 64 47 / 42.7 us, 1 x 64, 4 of 50 44 / 39, 4 x 100, 12 of 50 50.5 / 46,
-// 1 x 1024, 12 of 64 80.5 / 75.7, 2 x 1024, 12 122 / 119, 1 x 2048, 14 166 / 167.
+// 1 x 1024, 12 of 64 80.5 / 75.7, 2 x 1024, 12 122 / 119 (core_merged_backward has the lines).
 // Wider heads run one workgroup a CU, so that a block of keys and one of queries, longest first, take turns in the order of the
 // workgroups; up to as many blocks of 32 rows as the first half of them fills the CUs (KW = 8 256, KW = 4 224): 1 x 64 tokens, 4 heads
 // of 128 49.9 / 40.9, 1 x 512, 4 67 / 55.8, 1 x 1500, 4 105 / 92.6, 1 x 1024, 8 (256 blocks, KW = 8) 106.8 / 101.9, 1 x 155, 13 of 96

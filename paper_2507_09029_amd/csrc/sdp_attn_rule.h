@@ -35,11 +35,20 @@ constexpr int core_waves(int hd, int64_t S, int64_t pairs) {
     return core_in_eight(hd, S, pairs) ? 8 : core_blocks_128(S, pairs) <= core_split_below(hd) ? 4 : 1;
 }
 
-// dQ, dK and dV in one launch: where the walked axis is split; wider heads up to as many blocks of 32 rows as the first half of them
-// fills the CUs (measured at attn_bwd_kernel)
+// dQ, dK and dV in one launch, where the walked axis is split: saves the gap between two launches and fills the CUs that one of them
+// leaves idle, for reading O's rows again (attn_bwd_kernel).  Heads up to 64: up to 384 blocks of 32 rows, and beyond while blocks x tokens,
+// which the re-reads grow with, stay within 2^20.  Attention forward and backward, two launches / one, us: 1024 tokens, 8 heads (256
+// blocks) 59.7 / 55.9; 1024, 24 (768) 89.1 / 85.2; 2 x 1024, 14 (896) 103.0 / 101.9; 2048, 4 (256) 81.5 / 75.8; 2048, 8 (512) 89.7 / 88.1;
+// 4096, 3 (384) 115.4 / 106.9; 8192, 1 (256) 173.9 / 161.5; no difference beyond what runs differ: 2 x 1024, 16 (1024) 107.9 / 108.5, 4096, 4
+// (512) 121.2 / 119.0 and 117.9 / 122.0, 8192, 2 (512) 185.0 / 184.3; but 2048, 14 (896) 125.4 / 127.9, 3000, 7 (658) 116.1 / 121.7,
+// 4096, 5 (640) 133.8 / 143.1, 6000, 5 (940) 214.8 / 231.5, 8192, 4 (1024) 278.8 / 293.0.
+// Wider heads, one workgroup a CU: up to as many blocks as the first half of them fills the CUs.  Of 128: 1024, 8 (256, KW = 8) 91.7 /
+// 86.0; 4096, 2 (256) 171.0 / 159.7; but 3000, 3 (282) 149.5 / 152.2; 512, 14 (224, KW = 4) 84.4 / 82.3, but 512, 20 (320) 100.5 / 104.3.
 constexpr bool core_merged_backward(int hd, int64_t S, int64_t pairs) {
     const int kw = core_waves(hd, S, pairs);
-    return kw > 1 && (hd <= 64 || core_blocks_32(S, pairs) <= (kw == 8 ? 256 : 224));
+    const int64_t blocks = core_blocks_32(S, pairs);
+    if (kw == 1) return false;
+    return hd <= 64 ? blocks <= 384 || blocks * S <= (1 << 20) : blocks <= (kw == 8 ? 256 : 224);
 }
 
 } // namespace sdp

@@ -43,5 +43,11 @@ def test_one_backward_launch_only_where_the_walk_is_split(rule):
         for S in (1, 31, 32, 33, 128, 200, 511, 512, 1024, 1025, 1056, 2048, 5376, 8192, 65536):
             for n in (1, 2, 7, 8, 9, 28, 56, 57, 192, 193, 224, 225, 256, 257):
                 assert not rule.merged(hd, S, n) or rule.waves(hd, S, n) > 1, (hd, S, n)
-    assert [rule.merged(hd, S, n) for hd, S, n in ((128, 1024, 8), (128, 1025, 8), (128, 224, 32), (128, 224, 33), (64, 2048, 16), (64, 2048, 17), (128, 32, 193))] \
+    assert [rule.merged(hd, S, n) for hd, S, n in ((128, 1024, 8), (128, 1025, 8), (128, 224, 32), (128, 224, 33), (64, 32, 256), (64, 32, 257), (128, 32, 193))] \
         == [1, 0, 1, 0, 1, 0, 0]
+
+
+def test_one_backward_launch_of_narrow_heads_while_its_reads_are_few(rule):
+    # up to 384 blocks of 32 rows; beyond, blocks x tokens up to 2^20
+    assert [rule.merged(64, S, n) for S, n in ((2048, 8), (12288, 1), (4096, 3), (1024, 24), (1024, 32), (511, 64))] == [1, 1, 1, 1, 1, 1]
+    assert [rule.merged(64, S, n) for S, n in ((2048, 9), (2112, 8), (3000, 7), (4096, 4), (6000, 5), (8192, 4), (12320, 1))] == [0, 0, 0, 0, 0, 0, 0]

@@ -12,6 +12,7 @@ sdp = t.sdp  # the fixture
 CASES = [(AttnWorkload(f"merged_{dt}_{hd}_S{S}_{Bt}x{H}", Bt, S, 72, H, hd, H, 2, 91, dt), one) for dt, hd, Bt, S, H, one in
          (("bf16", 64, 1, 1, 2, 1), ("bf16", 50, 3, 31, 2, 1), ("bf16", 64, 2, 33, 3, 1), ("bf16", 32, 1, 129, 2, 1), ("bf16", 64, 1, 300, 2, 1),
           ("bf16", 64, 8, 130, 16, 1), ("bf16", 50, 8, 130, 17, 0),
+          ("bf16", 64, 4, 1040, 7, 1), ("bf16", 64, 1, 2112, 8, 0),  # four waves on a block, in two launches
           # wider heads: four waves on a block, then eight
           ("bf16", 72, 1, 1, 2, 1), ("bf16", 96, 2, 33, 3, 1), ("bf16", 104, 1, 300, 2, 1), ("bf16", 128, 4, 200, 8, 1), ("bf16", 80, 4, 200, 9, 0),
           ("bf16", 88, 1, 545, 2, 1), ("bf16", 120, 1, 1024, 8, 1), ("bf16", 80, 1, 1056, 8, 0),
