@@ -353,16 +353,27 @@ int sdp::mlp_bwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
     const bool apart = !overlap({{dX, tok_b}, {dW1, out_b}, {dW3, out_b}, {dW2T, out_b}}, {{W1, w_b}, {W3, w_b}});
     // and in the launch of the weight gradients, where dX does not take the place of what those read
     const bool pair = fused && apart && !overlap({{dX, tok_b}}, {{X, tok_b}, {dY, tok_b}}) && gemm_pairs(as_stored, dw);
-    const bool stored = pair || (apart && gemm_reads_as_stored(as_stored));
     // otherwise the operand copies that dX and the plain weight gradients read, made beside dact, which needs none of them, or beside the
     // weight gradients where dact's tiles leave no CU idle
     const TransposeJob tj[4] = {{W1, W1c, d, ldn, gather, n, d},
                                 {W3, W3c, d, ldn, gather, n, d},
                                 {X, XT, d, ldt, nullptr, T, d},
                                 {dY, dYT, d, ldt, nullptr, T, d}};
+    const bool beside_dw = fused && !overlap({{dW1, dw_b}, {dW3, dw_b}, {dW2T, dw_b}}, {{W1, w_b}, {W3, w_b}});
+    auto carried = [&] {
+        GemmDesc a = da, b = dw;
+        a.side = b.side = tj, a.nside = want_dw && !fused ? 4 : 2, b.nside = 2;
+        return gemm_carries(a) || (beside_dw && gemm_carries(b));
+    };
+    // In a launch of its own dX reads the weights as stored where their copies would need a launch, and with few tokens, whose launches
+    // the copies lengthen: they move 8 n d bytes beside 2 T n d flops.  Backward passes, copies / as stored, us, forward masking: own
+    // launch T = 1024, d = 1600, n = 2048 81.0 / 76.7, T = 256, d = 2048, n = 4096 76.5 / 67.9 (74 shapes 12 % less, none 1 % more); carried
+    // T = 512, d = 1600, n = 1024 34.6 / 33.0, T = 128, d = 2048, n = 1024 31.7 / 29.7; but T = 1024, d = 1024, n = 4096 79.8 / 82.7,
+    // T = 2048, d = 768, n = 2048 72.0 / 74.6, T = 2048, d = 1024, n = 2048 80.8 / 84.6.
+    const bool stored = pair || (apart && gemm_reads_as_stored(as_stored) && (T <= 512 || !carried()));
     const int first = stored ? 2 : 0;
     da.side = tj + first, da.nside = (want_dw && !fused ? 4 : 2) - first, da.side_name = "mlp_tr_bwd";
-    if (fused && !stored && !overlap({{dW1, dw_b}, {dW3, dw_b}, {dW2T, dw_b}}, {{W1, (size_t)F * d * e}, {W3, (size_t)F * d * e}})) {
+    if (beside_dw && !stored) {
         dw.side = tj, dw.nside = 2, dw.side_name = "mlp_tr_bwd";
         if (gemm_carries(da) || !gemm_carries(dw)) dw.nside = 0; else da.nside = 0;
     }

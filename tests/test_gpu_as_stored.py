@@ -84,11 +84,14 @@ def _copied(ws, base, copy):
 
 
 # 20 and 21 depth steps with rows that are no whole lines (down in a launch of its own; dX's two operands count twice), the longest
-# list and one chunk more; rows of whole lines and no list at any depth
-@pytest.mark.parametrize("mode,d,n,down,dx,pair", [("fm", 72, 1280, 1, 1, 1), ("fm", 72, 1288, 0, 0, 0), ("fm", 72, 1000, 1, 1, 1),
-                                                   ("fm", 64, 8192, 1, 1, 0), ("fm", 64, 8200, 0, 0, 0), ("bm", 64, 8200, 1, None, None)])
-def test_mlp_limits_of_weights_as_stored(sdp, mode, d, n, down, dx, pair):
-    T, F = 64, n + 16 if mode == "fm" else n
+# list and one chunk more; rows of whole lines and no list at any depth; copies that another launch carries, with few tokens and with
+# many, and copies that would need a launch
+@pytest.mark.parametrize("mode,T,d,n,down,dx,pair", [
+    ("fm", 64, 72, 1280, 1, 1, 1), ("fm", 64, 72, 1288, 0, 0, 0), ("fm", 64, 72, 1000, 1, 1, 1), ("fm", 64, 64, 8192, 1, 1, 0),
+    ("fm", 64, 64, 8200, 0, 0, 0), ("bm", 64, 64, 8200, 1, None, None), ("fm", 512, 1600, 1024, 1, 1, 0), ("fm", 1024, 768, 2048, 1, 0, 0),
+    ("fm", 1024, 1024, 2048, 1, 0, 0), ("fm", 1024, 1600, 2048, 1, 1, 0)])
+def test_mlp_limits_of_weights_as_stored(sdp, mode, T, d, n, down, dx, pair):
+    F = n + 16 if mode == "fm" else n
     X, dY, W = _inputs(T, d, F, 11)
     idx = sdp.make_masks(2, F, n if mode == "fm" else (F + 15) // 16 * 8, 5, True)[1][0].contiguous()
     ws = _workspace(sdp.masked_mlp_fwd_workspace_bytes(mode, X.dtype, T, d, F, len(idx)))
