@@ -983,6 +983,14 @@ int launch_core(CoreKernel which, const CoreArgs& a, int64_t nbh, const Transpos
     return launch_core<128>(which, a, nbh, side, s);
 }
 
+// bf16, out and dX in launches of their own: whether they read the weights as stored (E: the columns of the heads that run).  The core's
+// launch carries the transposes of small weights for nothing, and a contraction on copies is up to 1 us shorter; large ones lengthen it.
+// Copies / as stored, us, forward pass: 512 tokens, d = 1024, 16 heads of 64 26.6 / 25.3, 64, d = 1536, 24 of 64 24.8 / 23.0; but 2048, d = 256,
+// 2 of 64 24.6 / 25.5, 1024, d = 512, 2 of 128 26.0 / 27.2.  Backward: 256, d = 2048, 16 of 128 71.5 / 62.3, 64, d = 1536, 24 of 64 46.2 / 42.6; but
+// 512, d = 1200, 12 of 50 43.1 / 46.0, 2048, d = 512, 8 of 64 64.5 / 65.5.  From 2^20 elements of WoT on 99 passes take 2 % less as stored, five
+// of them 2 to 4 % more; below 194 take 0.2 % more.
+bool worth_as_stored(int64_t E, int64_t d) { return E * d >= (int64_t)1 << 20; }
+
 // rows of [Wq; Wk; Wv] ([3 H hd][d]) and of WoT ([H hd][d]) that belong to the held heads
 __global__ void head_rows_kernel(const int32_t* __restrict__ head_idx, int ph, int H, int hd, int32_t* __restrict__ rows_qkv,
                                  int32_t* __restrict__ rows_o) {
@@ -1228,7 +1236,7 @@ int sdp::attn_fwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     GemmDesc as_stored = op;
     as_stored.B = padded ? w.WoP : WoT, as_stored.ldb = ldp, as_stored.b_km = 1;
     as_stored.b_gather = rows_o, as_stored.b_rows = rows_o ? (int64_t)H * hd : E, as_stored.heads = heads;
-    const bool stored = dtype == SDP_BF16 && gemm_reads_as_stored(as_stored) &&
+    const bool stored = dtype == SDP_BF16 && worth_as_stored(E, d) && gemm_reads_as_stored(as_stored) &&
                         (padded || !overlap({{Y, (size_t)T * d * 2}, {O_save, (size_t)T * E * 2}, {LSE_save, (size_t)Bt * ph * S * 4}},
                                             {{WoT, (size_t)H * hd * d * 2}}));
 
@@ -1370,7 +1378,7 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
     // and in the launch of the weight gradients, where dX does not take the place of what those read
     const bool pair = direct && apart && gemm_pairs(as_stored, wg) &&
                       !overlap({{dX, (size_t)T * d * 2}}, {{X, (size_t)T * d * 2}, {dY, (size_t)T * d * 2}, {O_save, (size_t)T * E * 2}});
-    const bool stored = pair || (apart && gemm_reads_as_stored(as_stored));
+    const bool stored = pair || (apart && worth_as_stored(E, d) && gemm_reads_as_stored(as_stored));
     if (mfma_core(dtype)) {
         CoreArgs a{};
         a.qkv = (const uint16_t*)QKV_save, a.ldq = 3 * E;

@@ -367,9 +367,9 @@ int sdp::mlp_bwd_impl(int mode, int dtype, int T, int d, int F, int p, const voi
     };
     // In a launch of its own dX reads the weights as stored where their copies would need a launch, and with few tokens, whose launches
     // the copies lengthen: they move 8 n d bytes beside 2 T n d flops.  Backward passes, copies / as stored, us, forward masking: own
-    // launch T = 1024, d = 1600, n = 2048 81.0 / 76.7, T = 256, d = 2048, n = 4096 76.5 / 67.9 (74 shapes 12 % less, none 1 % more); carried
-    // T = 512, d = 1600, n = 1024 34.6 / 33.0, T = 128, d = 2048, n = 1024 31.7 / 29.7; but T = 1024, d = 1024, n = 4096 79.8 / 82.7,
-    // T = 2048, d = 768, n = 2048 72.0 / 74.6, T = 2048, d = 1024, n = 2048 80.8 / 84.6.
+    // launch T = 1024, d = 1600, n = 2048 79.0 / 73.8, T = 256, d = 2048, n = 4096 75.4 / 66.5 (74 shapes 12 % less, none 1 % more); carried
+    // T = 512, d = 1600, n = 1024 34.1 / 32.4, T = 128, d = 2048, n = 1024 32.3 / 29.1; but T = 1024, d = 1024, n = 4096 71.6 / 74.7,
+    // T = 2048, d = 768, n = 2048 67.8 / 69.2, T = 2048, d = 1024, n = 4096 130.0 / 135.3.
     const bool stored = pair || (apart && gemm_reads_as_stored(as_stored) && (T <= 512 || !carried()));
     const int first = stored ? 2 : 0;
     da.side = tj + first, da.nside = (want_dw && !fused ? 4 : 2) - first, da.side_name = "mlp_tr_bwd";

@@ -112,9 +112,11 @@ def test_mlp_limits_of_weights_as_stored(sdp, mode, T, d, n, down, dx, pair):
         assert torch.equal(a, b)
 
 
-@pytest.mark.parametrize("ph,out,dx,pair", [(20, 1, 0, 0), (21, 0, 0, 0), (6, 1, 1, 1), (7, 1, 0, 1), (13, 1, 0, 1), (14, 1, 0, 0)])
-def test_attention_limits_of_weights_as_stored(sdp, ph, out, dx, pair):
-    Bt, S, d, hd = 2, 32, 72, 64
+# the same for the attention's out and dX; weights of less than 2^20 elements a matrix: copies, which the core's launch carries
+@pytest.mark.parametrize("d,ph,out,dx,pair", [(840, 20, 1, 0, 0), (840, 21, 0, 0, 0), (2736, 6, 1, 1, 0), (2736, 7, 1, 0, 0), (72, 13, 0, 0, 1),
+                                              (72, 14, 0, 0, 0), (1024, 16, 1, 1, 1), (1024, 15, 0, 0, 1)])
+def test_attention_limits_of_weights_as_stored(sdp, d, ph, out, dx, pair):
+    Bt, S, hd = 2, 32, 64
     T, E = Bt * S, ph * hd
     X, dY, Wqkv, WoT, heads, _ = _attention(sdp, "fm", Bt, S, d, ph + 1, hd, ph, 4)
     a = ("fm", Bt, S, hd)
