@@ -9,10 +9,10 @@
 // What bounds it: the matrix cores give 157 TFLOP/s (a plain fp32 FMA half of that), i.e. 32 cycles per 16x16x4 tile, so
 // operand traffic is cheap here (a wave reads 4 KB of LDS per 512 matrix cycles) and the shapes that use fp32 are small:
 // latency, launches and idle CUs decide.  Hence three loops:
-//   64 x 64 and 128 x 128 outputs a workgroup, pipelined (gemm_f32_pipe_kernel): where these fill the CUs;
+//   64 x 64 outputs a workgroup, pipelined (gemm_f32_pipe_kernel): where these fill the CUs;
 //   16 x 16 and 32 x 32 outputs a workgroup, whose four waves split the depth (gemm_f32_wave_kernel): launches of few tiles;
-//   32 x 32 with the depth split inside each step of 64 (gemm_f32_kernel, also 64 and 128 wide for lists beyond kListMax): between
-//   the two.
+//   32 x 32 with the depth split inside each step of 64 (gemm_f32_kernel): between the two; and 64 and 128 wide, the largest launches
+//   and those that read a list beyond kListMax.
 // The first two fill LDS by direct loads, 16 bytes a lane or, where extents or strides are no multiples of 4 or columns are
 // gathered, 4; the third moves global -> registers -> LDS, the next three steps in registers, one barrier per step.
 //
@@ -623,8 +623,8 @@ int launch_wave(Dev g, const char* name, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Pipelined tile: 64 x 64 (or 128 x 128) outputs, four waves of 32 x 32 (64 x 64), depth steps of 32 in three LDS stages that
-// direct loads fill.  A step is two 16-deep halves; while a wave's MFMAs of one half run, its fragments of the next are read, and
+// Pipelined tile: 64 x 64 outputs (of both right operands: 64 x 32 each), four waves of 32 x 32, depth steps of 32 in three LDS stages
+// that direct loads fill.  A step is two 16-deep halves; while a wave's MFMAs of one half run, its fragments of the next are read, and
 // one barrier a step, between the halves, hands over the stages:
 //   first half of step k : MFMAs on (k, 0); reads of (k, 1)
 //   wait for the own loads of step k + 1 and the own reads of step k; barrier: step k + 1 has landed, step k is read
@@ -644,7 +644,7 @@ struct PipeOperand {
     static constexpr int F = R / 32;                              // fragments of a wave
     static constexpr int LPR = (DM ? R / 4 : 8) * (V ? 1 : 4), RPS = 64 / LPR; // lanes per LDS row, LDS rows per load
     static_assert(64 % LPR == 0, "whole rows a load");
-    static constexpr int swap(int k) { return DM && F == 2 ? 8 * (k >> 2 & 1) : 0; } // depth-major: chunk c sits at c ^ swap
+    static constexpr int swap(int k) { return DM ? 8 * (k >> 2 & 1) : 0; } // depth-major: chunk c sits at c ^ swap
     static constexpr int NP = DM ? (swap(4) && !V ? 2 : 1) : PER;
     int64_t off[NP]; // elements from the base: this lane's places at depth 0 (depth-major: its first column, of even and odd loads)
     int k[PER];      // and their depth within a step
@@ -657,7 +657,7 @@ struct PipeOperand {
             const int q = RPS * (4 * i + wave) + lane / LPR; // LDS row
             if constexpr (DM) {
                 // bit 2 of q: the same for all loads (V: 4 rows a load and wave), or that of i (one row)
-                static_assert(F != 2 || (V ? RPS == 4 : RPS == 1), "which loads share a swap");
+                static_assert(V ? RPS == 4 : RPS == 1, "which loads share a swap");
                 k[i] = q;
                 if (i < NP) {
                     int c = row0 + (V ? 4 * (pos ^ swap(q)) : pos ^ (4 * swap(q)));
@@ -693,16 +693,11 @@ struct PipeOperand {
         if constexpr (DM) {
             const int kk = 16 * h + 4 * lg + r;
             const unsigned char* p = stage + kk * R * 4;
-            if constexpr (F == 2) {
-                typedef float f32x2 __attribute__((ext_vector_type(2)));
-                const int col = part0 + 2 * l16; // floats; the swap is of 32 floats, the same for all steps of a lane group
-                const f32x2 v = *(const f32x2*)(p + (col ^ (32 * (lg & 1))) * 4);
-                fr[0][r] = v[0], fr[1][r] = v[1];
-            } else {
-                const f32x4 v = *(const f32x4*)(p + (part0 + 4 * l16) * 4);
-#pragma unroll
-                for (int f = 0; f < 4; ++f) fr[f][r] = v[f];
-            }
+            static_assert(F == 2, "64 rows");
+            typedef float f32x2 __attribute__((ext_vector_type(2)));
+            const int col = part0 + 2 * l16; // floats; the swap is of 32 floats, the same for all steps of a lane group
+            const f32x2 v = *(const f32x2*)(p + (col ^ (32 * (lg & 1))) * 4);
+            fr[0][r] = v[0], fr[1][r] = v[1];
         } else {
             const int row = part0 + 16 * r + l16;
             fr[r] = *(const f32x4*)(stage + row * 128 + (((4 * h + lg) ^ ((row >> 1) & 7)) * 16));
@@ -834,8 +829,7 @@ __device__ inline void pipe_body(const Dev& g, int block, unsigned char* smem) {
 #pragma unroll
             for (int c = 0; c < NB; ++c) {
                 if constexpr (!BDM) v[c] = acc[c][i][q];
-                else if constexpr (FN == 2) v[c] = f32x4{acc[c][i][0][2 * q], acc[c][i][1][2 * q], acc[c][i][0][2 * q + 1], acc[c][i][1][2 * q + 1]};
-                else v[c] = f32x4{acc[c][i][0][q], acc[c][i][1][q], acc[c][i][2][q], acc[c][i][3][q]};
+                else v[c] = f32x4{acc[c][i][0][2 * q], acc[c][i][1][2 * q], acc[c][i][0][2 * q + 1], acc[c][i][1][2 * q + 1]};
             }
             emit<EPI>(g, gC, m, n0 + pn + (BDM ? 4 * FN * lg + 4 * q : 16 * q + 4 * lg), v[0], v[NB - 1]);
         }
@@ -889,9 +883,12 @@ bool few_tiles(const Dev& g) {
 // Tile of a launch: the fewest matrix cycles on the busiest CU (rounds of tiles over 256 CUs x tile area), each tile
 // weighted by what its loop loses to staging and barriers.  With fewer 64-wide tiles than CUs the 32-wide ones win on
 // both counts (T = 256, p = 512, d = 256: 128 tiles whose waves each run a quarter of the depth, against 32).
-// Event times, the register-staged tile / the pipelined one: gate_up at T = 1024, d = 256, p = 1500 27.7 / 23.0 us (32 against 64
-// wide), T = 1024, d = 512, F = 2048 under backward masking 85 / 51 (128 wide); weight gradients of the latter 128.5 / 64.3.  32 x 32, four waves
-// on a step / on a tile's depth: down 17.3 / 15.8, attn_dout 9.8 / 8.3 with 256 tiles, but 25.9 / 27.5 with 512 (T = 1000).
+// Register-staged or pipelined, event times in us: gate_up at T = 1024, d = 256, p = 1500 27.7 (32 wide) / 23.0 (64), T = 2048, d = 1024,
+// n = 512 49.0 / 46.8 (both 64), but T = 4096, d = 2048, n = 512 146.9 / 154.7, n = 2048 568 (128) / 596 (128); dact at T = 2048, d = 1024,
+// n = 1024 50.4 / 50.1, n = 4096 164 (128) / 194 (128); down at T = 4096, d = 2048, n = 1024 146.5 (128) / 179.0 (128), T = 4096, d = 768, n = 2048
+// 124.5 (64) / 137.3 (64); dX there 240 / 267; weight gradients at T = 1024, d = 2048, p = 4000 432 (128) / 498 (128), 453 / 456 (64).  The
+// pipelined 128-wide tile had one workgroup a CU for the other's two.  32 x 32, four waves on a step / on a tile's depth: down 17.3 / 15.8, attn_dout 9.8 / 8.3 with 256 tiles, but 25.9 /
+// 27.5 with 512 (T = 1000).
 // Extents that are no multiples of 4, whole steps before / now: T = 1023, d = 510, F = 2046, p = 1025 610 / 471 us, T = 255, d = 126,
 // p = 401 126 / 69, T = 101, d = 301, p = 901 201 / 110, backward masking T = 600, d = 66, p = 900 257 / 130.
 template <int EPI, bool ADM, bool BDM, bool VA, bool VB>
@@ -909,13 +906,18 @@ int choose(const Dev& g, const char* name, hipStream_t s) {
     };
     if (direct) {
         if (few_tiles(g)) return launch_wave<16, 2, EPI, ADM, BDM, VA, VB>(g, name, s);
-        const double c128 = cost(128, 128 / NB, 1.0), c64 = cost(64, 64 / NB, 1.1), c32 = cost(32, 32, 1.3);
-        if (c32 < c64 && c32 < c128) {
+        const double c64 = cost(64, 64 / NB, 1.1), c32 = cost(32, 32, 1.3);
+        // single floats: the tiles that direct loads fill, of 64 and 32
+        const double staged128 = VEC ? cost(128, 128, 1.0) : HUGE_VAL, staged64 = VEC && NB == 2 ? cost(64, 64, 1.1) : HUGE_VAL;
+        if (c32 < c64 && c32 < staged64 && c32 < staged128) {
             if (!VEC || (!ADM && NB == 1 && EPI != EPI_SWIGLU_BWD && tiles(32, 32) <= 256)) return launch_wave<32, 2, EPI, ADM, BDM, VA, VB>(g, name, s);
             return launch<Cfg<32, 32, 4>, EPI, ADM, BDM, true>(g, name, s);
         }
-        if (c64 < c128 || !VEC) return launch_pipe<64, 64 / NB, EPI, ADM, BDM, VA, VB>(g, name, s);
-        return launch_pipe<128, 128 / NB, EPI, ADM, BDM, true, true>(g, name, s);
+        if constexpr (VEC) {
+            if (staged128 <= c64 && staged128 <= staged64) return launch<Cfg<128, 128, 1>, EPI, ADM, BDM, true>(g, name, s);
+            if ((BDM && !ADM) || (staged64 <= c64 && tiles(64, 64) > 256)) return launch<Cfg<64, 64, 1>, EPI, ADM, BDM, true>(g, name, s);
+        }
+        return launch_pipe<64, 64 / NB, EPI, ADM, BDM, VA, VB>(g, name, s);
     }
     if constexpr (BDM) { // a list too long for LDS
         const double c128 = cost(128, 128, 1.0), c64 = cost(64, 64, 1.1), c32 = cost(32, 32, 1.3);

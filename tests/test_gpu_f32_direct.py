@@ -1,4 +1,4 @@
-"""GPU: the fp32 contraction's direct-load tiles, pipelined (64 and 128 wide) and shared out over a tile's waves (16 and 32), with
+"""GPU: the fp32 contraction's direct-load tiles, pipelined (64 wide) and shared out over a tile's waves (16 and 32), with
 16-byte loads and with single floats (extents that are no multiples of 4, gathered columns): partial tiles, one to several depth
 steps, launches of dX and the weight gradients together and apart.  1e-5 against the fp64 oracle."""
 import pytest
@@ -18,6 +18,8 @@ CASES = [MlpWorkload(f"{T}x{d}x{F}p{p}_{mode}", "f32", T, d, F, p, 2, mode, 81) 
     (1000, 32, 1032, 1004, "fm"), (1000, 36, 1030, 1001, "fm"), (1001, 100, 1031, 1002, "bm"), (2044, 36, 2040, 2036, "fm"),
     # dX alone (more than 256 tiles of 32) and down in 32-wide tiles; gathered columns with 16-byte loads on the other side
     (520, 516, 300, 200, "fm"), (521, 515, 300, 201, "bm"), (100, 64, 300, 151, "bm"),
+    # register-staged tiles with 16-byte loads: down in tiles of 64 and of 128, weight gradients of 128 in a launch of their own
+    (1000, 1000, 64, 36, "fm"), (2044, 2044, 64, 36, "fm"), (520, 516, 2044, 2036, "fm"),
     # a list of depth rows that LDS does not take
     (8, 16, 4200, 4100, "fm"), (8, 17, 4200, 4097, "fm"))]
 
