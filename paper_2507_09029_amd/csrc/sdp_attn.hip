@@ -554,8 +554,12 @@ template <int LDS, int THREADS>
 __device__ inline void carried(const SideJobs& side, int w, unsigned char* lds) {
     constexpr int HALVES = THREADS / 256, PER = side_tiles(LDS / HALVES), ALL = PER * HALVES;
     if (w >= (side.end[kMaxTransposeJobs - 1] + ALL - 1) / ALL) return;
-    const int half = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
-    side_transposes<PER, true>(side, w * HALVES + half, lds + half * PER * kTransposeLds, threadIdx.x & 255);
+    if constexpr (HALVES == 1) {
+        side_transposes<PER, true>(side, w, lds, threadIdx.x);
+    } else {
+        const int half = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8);
+        side_transposes<PER, true>(side, w * HALVES + half, lds + half * PER * kTransposeLds, threadIdx.x & 255);
+    }
 }
 
 // waves per SIMD the registers are allotted for.  KW = 1, heads of 64: 3 beat 2 (86 -> 77 us at 4 x 2048 tokens, 12 heads)
@@ -736,7 +740,8 @@ struct DkvShape {
 
 // OWN_DELTA: the queries' delta is computed from their dO and O rows as the tile is staged (every wave its own tile), in the place
 // of what the dQ kernel has left.  O's rows are fetched a tile ahead like the others; KW = 8 has no registers for them and
-// fetches them into those that staging has freed (wide heads).
+// fetches them into those that staging has freed (wide heads).  KW = 8 is at the limit of 256 registers: heads above 96 spill 13 of them
+// in dK/dV alone (56 bytes of scratch a lane), 15 in the one launch with dQ; heads of 65 to 96 one and 9.
 template <int HW, int KW, bool OWN_DELTA = false>
 __device__ inline void attn_bwd_dkv_block(const CoreArgs& a, const int k0, const int head, const int b, unsigned char* lds) {
     using Shape = DkvShape<HW, KW>;
@@ -901,7 +906,7 @@ __device__ inline void attn_bwd_dkv_block(const CoreArgs& a, const int k0, const
         each_row_again<HW, KW>(lds, again, wave, lane, [&](int r) {
             const AttnRows<uint16_t> ar{gQ, gK, gV, a.ldq, gO, a.ldo, S, hd, a.scale, a.scale2};
             uint16_t* row = out + (int64_t)(krow0 + r) * a.ldq;
-            attn_row_dkv(ar, krow0 + r, lane, a.lse + stat, OWN_DELTA ? nullptr : a.delta + stat, row + a.ph * hd, row + 2 * a.ph * hd, gX);
+            attn_row_dkv<OWN_DELTA>(ar, krow0 + r, lane, a.lse + stat, OWN_DELTA ? nullptr : a.delta + stat, row + a.ph * hd, row + 2 * a.ph * hd, gX);
         });
 }
 

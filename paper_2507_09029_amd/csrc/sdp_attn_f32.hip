@@ -433,7 +433,7 @@ __device__ inline void dkv_block(const Args& a, const Item it, float* sX) {
     for (int r = 0; r < 4; ++r) {
         const int ka = it.row0 + 4 * wave + r;
         float* o = a.dqkv + ((int64_t)it.b * a.S + ka) * a.ldq + it.head * hd;
-        if (again >> (16 * r) & 1) attn_row_dkv(ar, ka, lane, a.lse + st, OWN_DELTA ? nullptr : a.delta + st, o + a.n * hd, o + 2 * a.n * hd, X0);
+        if (again >> (16 * r) & 1) attn_row_dkv<OWN_DELTA>(ar, ka, lane, a.lse + st, OWN_DELTA ? nullptr : a.delta + st, o + a.n * hd, o + 2 * a.n * hd, X0);
     }
 }
 

@@ -97,9 +97,9 @@ __device__ __forceinline__ void attn_row_dq(const AttnRows<T>& a, int q, int lan
     row_store(out, acc, a.hd, lane);
 }
 
-// dV[k] = sum_{q >= k} P[q][k] dO[q], dK[k] = scale sum_{q >= k} dZ[q][k] Q[q]; lse, delta of the sequence's rows, or, without the
-// latter, O's rows (strides of dO) to compute it from
-template <typename T>
+// dV[k] = sum_{q >= k} P[q][k] dO[q], dK[k] = scale sum_{q >= k} dZ[q][k] Q[q]; lse of the sequence's rows; delta of
+// these or, OWN_DELTA, O's rows (strides of dO) to compute it from
+template <bool OWN_DELTA, typename T>
 __device__ __forceinline__ void attn_row_dkv(const AttnRows<T>& a, int k, int lane, const float* lse, const float* delta, T* dK, T* dV, const T* O) {
     const T *K = a.K + k * a.ldq, *V = a.V + k * a.ldq;
     float ak[2] = {0.f, 0.f}, av[2] = {0.f, 0.f};
@@ -108,7 +108,7 @@ __device__ __forceinline__ void attn_row_dkv(const AttnRows<T>& a, int k, int la
         float p = 0.f, dz = 0.f;
         if (q < a.S) {
             p = exp2f(row_dot(a.Q + q * a.ldq, K, a.hd) * a.scale2 - lse[q]);
-            dz = p * (row_dot(a.dO + q * a.ldo, V, a.hd) - (delta ? delta[q] : row_dot(a.dO + q * a.ldo, O + q * a.ldo, a.hd)));
+            dz = p * (row_dot(a.dO + q * a.ldo, V, a.hd) - (OWN_DELTA ? row_dot(a.dO + q * a.ldo, O + q * a.ldo, a.hd) : delta[q]));
         }
         row_accumulate(p, a.dO + q0 * a.ldo, a.ldo, n, a.hd, lane, av);
         row_accumulate(dz, a.Q + q0 * a.ldq, a.ldq, n, a.hd, lane, ak);

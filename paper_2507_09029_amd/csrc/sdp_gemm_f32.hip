@@ -887,8 +887,8 @@ bool few_tiles(const Dev& g) {
 // n = 512 49.0 / 46.8 (both 64), but T = 4096, d = 2048, n = 512 146.9 / 154.7, n = 2048 568 (128) / 596 (128); dact at T = 2048, d = 1024,
 // n = 1024 50.4 / 50.1, n = 4096 164 (128) / 194 (128); down at T = 4096, d = 2048, n = 1024 146.5 (128) / 179.0 (128), T = 4096, d = 768, n = 2048
 // 124.5 (64) / 137.3 (64); dX there 240 / 267; weight gradients at T = 1024, d = 2048, p = 4000 432 (128) / 498 (128), 453 / 456 (64).  The
-// pipelined 128-wide tile had one workgroup a CU for the other's two.  32 x 32, four waves on a step / on a tile's depth: down 17.3 / 15.8, attn_dout 9.8 / 8.3 with 256 tiles, but 25.9 /
-// 27.5 with 512 (T = 1000).
+// pipelined 128-wide tile had one workgroup a CU for the other's two.  32 x 32, four waves on a step / on a tile's depth: down 17.3 / 15.8,
+// attn_dout 9.8 / 8.3 with 256 tiles, but 25.9 / 27.5 with 512 (T = 1000).
 // Extents that are no multiples of 4, whole steps before / now: T = 1023, d = 510, F = 2046, p = 1025 610 / 471 us, T = 255, d = 126,
 // p = 401 126 / 69, T = 101, d = 301, p = 901 201 / 110, backward masking T = 600, d = 66, p = 900 257 / 130.
 template <int EPI, bool ADM, bool BDM, bool VA, bool VB>

@@ -105,3 +105,15 @@ def test_rows_that_a_workgroup_shares_are_read_behind_a_barrier(tmp_path):
     # dK/dV and dQ in one launch: dQ's waves have tiles of their own, and no more than these come without a barrier
     shared |= {("attn_bwd_kernel", hw, 8): counts["attn_bwd_dq_kernel", hw, 8] for hw in (96, 128)}
     assert {k: counts[k] for k in shared} == shared
+
+
+def test_attention_kernels_know_where_delta_comes_from(tmp_path):
+    """dK/dV takes delta from memory or from O's rows by its kind: a choice at run time between the two pointers, one of them null, costs
+    registers and shows as an access of no known address space"""
+    seen = 0
+    for lines in gfx950_code(tmp_path):
+        for symbol, code in kernels(lines).items():
+            if re.search(r"attn_(?:f32_)?(?:fwd|bwd|dq|dkv|bwd_dq|bwd_dkv)_kernelI", symbol):
+                seen += 1
+                assert not [ins for _, ins, _ in code if ins.startswith("flat_")], symbol
+    assert seen > 0
