@@ -177,10 +177,10 @@ __device__ inline f32x4 fragment(const float* lds, int row, int t, int g) {
     }
 }
 
-// epilogue of four consecutive columns n .. n + 3 of row m
-template <int EPI>
-__device__ inline void emit(const Dev& g, float* gC, int m, int n, f32x4 v, f32x4 v2) {
-    if (m >= g.M || n >= g.N) return;
+// epilogue of four consecutive columns n .. n + 3 of row m; FROM: those from `lo` on (vec_out: lo - n is a multiple of 4)
+template <int EPI, bool FROM = false>
+__device__ inline void emit(const Dev& g, float* gC, int m, int n, f32x4 v, f32x4 v2, int lo = 0) {
+    if (m >= g.M || n >= g.N || (FROM && n + 3 < lo)) return;
     const int cnt = g.N - n < 4 ? g.N - n : 4;
     auto put = [&](float* base, int64_t row, int64_t ld, f32x4 x) {
         float* p = base + row * ld + n;
@@ -188,7 +188,7 @@ __device__ inline void emit(const Dev& g, float* gC, int m, int n, f32x4 v, f32x
         else {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                if (e < cnt) p[e] = x[e];
+                if (e < cnt && (!FROM || n + e >= lo)) p[e] = x[e];
         }
     };
     auto get = [&](const float* base, int64_t ld) {
@@ -622,6 +622,8 @@ int launch_wave(Dev g, const char* name, hipStream_t s) {
     return launch_status();
 }
 
+#include "sdp_f32_split.h"
+
 // ---------------------------------------------------------------------------------------------------
 // Pipelined tile: 64 x 64 outputs (of both right operands: 64 x 32 each), four waves of 32 x 32, depth steps of 32 in three LDS stages
 // that direct loads fill.  A step is two 16-deep halves; while a wave's MFMAs of one half run, its fragments of the next are read, and
@@ -891,6 +893,19 @@ bool few_tiles(const Dev& g) {
 // attn_dout 9.8 / 8.3 with 256 tiles, but 25.9 / 27.5 with 512 (T = 1000).
 // Extents that are no multiples of 4, whole steps before / now: T = 1023, d = 510, F = 2046, p = 1025 610 / 471 us, T = 255, d = 126,
 // p = 401 126 / 69, T = 101, d = 301, p = 901 201 / 110, backward masking T = 600, d = 66, p = 900 257 / 130.
+// Whether a launch takes the tiles of sdp_f32_split.h, from its tiles of 64: those pay where their depth is long enough for what a step
+// saves and they fill the chip better than 32-wide ones.  Before / split, kernel times in us (tiles, depth): gate_up 23.4 / 20.9
+// (344, 512), 15.2 / 13.7 (224, 512), 16.0 / 15.0 (156, 299), 563 / 469 (4000, 2048), but 11.7 / 13.3 (130, 367), 15.2 / 16.8 (260, 236);
+// dact 19.9 / 17.4 (256, 512), 287 / 254 (2016, 2048), but 14.9 / 16.3 (176, 512); down 30.3 / 26.5 (136, 1376), 39.2 / 30.8 (256, 1376), but
+// 23.8 / 26.8 (128, 1376: two even rounds of 32 x 32); dX 57 / 48.5 (136, 2 x 1376), 631 / 515 (1024, 2 x 4000); weight gradients 43.0 /
+// 36.5 (384, 1024), 830 / 714 (6048, 2048).  Extents that are no multiples of 4, which the others load by single floats: down 43.3 /
+// 31.0, dX 81 / 57 (128, 1535), weight gradients 115 / 53 (576, 1023).
+template <bool ADM, bool BDM, bool VEC>
+bool split_pays(const Dev& g, int64_t tiles, int nb) {
+    if (g.K < 256 || (ADM && g.M < 64) || (BDM && g.N < 64) || tiles > 0x7FFFFF) return false;
+    return tiles >= 256 || (tiles >= 150 && nb == 2) || (tiles > 128 && g.K >= 1024) || (tiles >= 128 && !VEC);
+}
+
 template <int EPI, bool ADM, bool BDM, bool VA, bool VB>
 int choose(const Dev& g, const char* name, hipStream_t s) {
     constexpr bool VEC = VA && VB;
@@ -904,6 +919,18 @@ int choose(const Dev& g, const char* name, hipStream_t s) {
         if (t * 256 > UINT32_MAX) return HUGE_VAL; // threads of one launch
         return (double)((t + 255) / 256) * b * bn * weight;
     };
+    if (split_pays<ADM, BDM, VEC>(g, tiles(64, 64 / NB), NB)) {
+        auto go = [&](auto listed) { // listed columns of the left operand
+            constexpr bool AG = decltype(listed)::value;
+            // two teams, one workgroup a CU, while the tiles leave room for it
+            if (tiles(64, 64 / NB) <= 256) return launch_split<2, EPI, ADM, BDM, AG>(g, name, s);
+            return launch_split<1, EPI, ADM, BDM, AG>(g, name, s);
+        };
+        if constexpr (ADM) {
+            if (g.ag) return go(std::true_type{});
+        }
+        return go(std::false_type{});
+    }
     if (direct) {
         if (few_tiles(g)) return launch_wave<16, 2, EPI, ADM, BDM, VA, VB>(g, name, s);
         const double c64 = cost(64, 64 / NB, 1.1), c32 = cost(32, 32, 1.3);
@@ -963,17 +990,24 @@ int describe(const GemmDesc& d, Dev& g, bool* va_out, bool* vb_out) {
 }
 
 // dX (BX x BX tiles, four waves on each) and one or two launches' worth of weight gradients (BW = 32: four waves on a tile;
-// 64: pipelined).  VX: 16-byte loads for both operands of dX; WA, WB: for the weight gradients'.
+// 64: pipelined; kSplit: 64 wide, sdp_f32_split.h).  VX: 16-byte loads for both operands of dX; WA, WB: for the weight gradients'.
+constexpr int kSplit = -64;
 template <int BX, int EPIX, int BW, bool VX, bool WA, bool WB>
 struct GroupShape {
     typedef WaveShape<BX, 2, EPIX, false, true, VX, VX> X;
-    static constexpr int W = BW == 32 ? WaveShape<32, 2, EPI_STORE, true, true, WA, WB>::TILES : PipeShape<64, 64, EPI_STORE, true, true, WA, WB, false>::RING;
+    static constexpr int W = BW == 32       ? WaveShape<32, 2, EPI_STORE, true, true, WA, WB>::TILES
+                             : BW == kSplit ? SplitTile<1, EPI_STORE, true, true, false>::LDS
+                                            : PipeShape<64, 64, EPI_STORE, true, true, WA, WB, false>::RING;
     static constexpr int LDS = X::LDS > W ? X::LDS : W;
 };
 template <int BW, bool WA, bool WB>
 __device__ inline void group_gradients(const Dev& w, int b, unsigned char* lds) {
     if constexpr (BW == 32) wave_body<32, 2, EPI_STORE, true, true, WA, WB>(w, b, lds);
-    else pipe_body<64, 64, EPI_STORE, true, true, WA, WB, false>(w, b, lds);
+    else if constexpr (BW == kSplit && WA) SplitTile<1, EPI_STORE, true, true, false>::run(w, b, lds); // 16-byte loads: columns in order
+    else if constexpr (BW == kSplit) {
+        if (w.ag) SplitTile<1, EPI_STORE, true, true, true>::run(w, b, lds);
+        else SplitTile<1, EPI_STORE, true, true, false>::run(w, b, lds);
+    } else pipe_body<64, 64, EPI_STORE, true, true, WA, WB, false>(w, b, lds);
 }
 template <int BX, int EPIX, int BW, bool VX, bool WA, bool WB>
 __global__ __launch_bounds__(256) void gemm_f32_group_kernel(Dev x, Dev w0, Dev w1, int nx, int n0) {
@@ -1002,7 +1036,8 @@ int launch_group(const Group& a) {
         g.tiles_m = (g.M + b - 1) / b, g.tiles_n = (g.N + b - 1) / b;
         return count_tiles(g, b);
     };
-    const int64_t nx = tiles(x, BX), n0 = tiles(w0, BW), n1 = a.n > 2 ? tiles(w1, BW) : 0;
+    constexpr int BT = BW == kSplit ? 64 : BW;
+    const int64_t nx = tiles(x, BX), n0 = tiles(w0, BT), n1 = a.n > 2 ? tiles(w1, BT) : 0;
     if (nx + n0 + n1 > 0x7FFFFFFF) return SDP_ERR_SHAPE;
     auto kern = gemm_f32_group_kernel<BX, EPIX, BW, VX, WA, WB>;
     static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, Sh::LDS);
@@ -1017,10 +1052,17 @@ int launch_group(const Group& a, bool vx, bool wa, bool wb) {
     // by tiles of 64 and steps of 32: 768, 4 (T = 128, d = 512, p = 2000) 32.8 / 25.9 us, 360, 16 57.6 / 56.1, an attention's 256, 16
     // 32.6 / 28.7; but 231, 16 (T = 512, d = 448) 37.5 / 47.5, 288, 32 58.4 / 66.8, 96, 16 19.3 / 22.4.
     const int64_t t64 = count_tiles(a.w0, 64) + (a.n > 2 ? count_tiles(a.w1, 64) : 0);
-    const bool pipe = t64 >= 16 * (int64_t)((a.w0.K + 31) / 32);
-    if (vx && wa && wb) return pipe ? launch_group<BX, EPIX, 64, true, true, true>(a) : launch_group<BX, EPIX, 32, true, true, true>(a);
-    if (vx && wb) return pipe ? launch_group<BX, EPIX, 64, true, false, true>(a) : launch_group<BX, EPIX, 32, true, false, true>(a);
-    return pipe ? launch_group<BX, EPIX, 64, false, false, false>(a) : launch_group<BX, EPIX, 32, false, false, false>(a);
+    // Split products from a depth of 448 on: 64-wide before / split 56.0 / 49.4 (528, 512 deep), 39.2 / 35.7 (288, 434, single floats),
+    // 36.5 / 31.0 (225, 700), but 34.4 / 36.0 (384, 400), 15.6 / 17.5 (384, 128); 32-wide / split 42.5 / 38.4 (156, 586).
+    auto go = [&](auto bw) {
+        constexpr int BW = decltype(bw)::value;
+        if (vx && wa && wb) return launch_group<BX, EPIX, BW, true, true, true>(a);
+        if (vx && wb) return launch_group<BX, EPIX, BW, true, false, true>(a);
+        return launch_group<BX, EPIX, BW, false, false, false>(a);
+    };
+    if (t64 >= 150 && a.w0.K >= 448 && a.w0.M >= 64 && a.w0.N >= 64) return go(std::integral_constant<int, kSplit>{});
+    if (t64 >= 16 * (int64_t)((a.w0.K + 31) / 32)) return go(std::integral_constant<int, 64>{});
+    return go(std::integral_constant<int, 32>{});
 }
 
 } // namespace

@@ -1,0 +1,55 @@
+"""GPU: the fp32 contraction's tiles of split products (three bf16 terms an operand): one and two teams of waves, every operand
+layout, partial last steps and tiles, listed rows, depths and columns, dX and the weight gradients together and apart: 1e-5 against the
+fp64 oracle.  Operands that are not finite, or that no bf16 holds, give what fp32 products give."""
+import pytest
+import torch
+
+import test_gpu_mlp as mlp
+from workloads import MlpWorkload
+
+pytestmark = pytest.mark.gpu
+sdp = mlp.sdp  # the fixture
+
+CASES = [MlpWorkload(f"{T}x{d}x{F}p{p}_{mode}", "f32", T, d, F, p, 2, mode, 91) for T, d, F, p, mode in (
+    # gate_up in 160 tiles, depths of one element more and less than whole steps, and of whole steps (an even and an odd number)
+    (640, 257, 1000, 511, "fm"), (620, 287, 1000, 501, "fm"), (613, 288, 1000, 512, "fm"), (640, 320, 1000, 500, "bm"),
+    # dact in 256 tiles (two teams) and 289 (one)
+    (1024, 256, 1100, 1024, "fm"), (1030, 260, 1030, 1027, "fm"),
+    # down and dX of single floats in 128 tiles, lists of depths of 10 and 11 steps; of four floats in 136
+    (1023, 511, 600, 301, "fm"), (1000, 500, 352, 352, "fm"), (1021, 510, 607, 321, "bm"), (500, 1032, 1100, 1024, "fm"),
+    # weight gradients in a launch of their own: columns in order and listed, last tiles of 1 and 60 columns
+    (1000, 700, 1100, 700, "fm"), (519, 769, 900, 577, "bm"),
+    # and beside dX
+    (449, 300, 1400, 701, "fm"), (480, 300, 1400, 700, "bm"), (500, 321, 1400, 705, "bm"))]
+
+
+@pytest.mark.parametrize("w", CASES, ids=[w.name for w in CASES])
+def test_f32_split_tiles(sdp, orc, w):
+    mlp.run_case(sdp, orc, w, [1], dw_layout="scatter" if w.p % 2 else "compact")
+
+
+# Rows with one bad element: G and U are then infinite, not a number or, for the largest float, finite where fp32 products are; all
+# other rows are untouched.  Reference: plain PyTorch in fp64, whose products of these do not overflow, rounded to fp32; 257 to 512
+# products summed in fp32 stay below 1e-5 normwise.
+@pytest.mark.parametrize("T,d,F", [(640, 257, 520), (1024, 512, 1024)])
+@pytest.mark.parametrize("bad", [float("inf"), float("-inf"), float("nan"), 3.4028234e38, -3.4e38])
+def test_f32_split_operands_that_are_not_finite(sdp, T, d, F, bad):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(92)
+    rnd = lambda *s, std=1.0: torch.randn(s, generator=g, device="cuda") * std
+    X, W = rnd(T, d), [rnd(F, d, std=0.02) for _ in range(3)]
+    W[0][5, 3] = 0.0
+    X[70, 3] = X[T - 1, d - 1] = bad
+    idx = torch.arange(F, dtype=torch.int32, device="cuda")
+    Y, G, U = sdp.masked_mlp_fwd("fm", X, *W, idx)
+    for got, w in ((G, W[0]), (U, W[1])):
+        want = (X.double() @ w.double().t()).float()
+        for row in (70, T - 1):
+            assert torch.equal(got[row].isnan(), want[row].isnan())
+            keep = ~want[row].isnan()
+            inf = want[row].isinf() & keep
+            assert torch.equal(got[row][inf], want[row][inf])
+            assert torch.allclose(got[row][keep & ~inf], want[row][keep & ~inf], rtol=1e-5, atol=0)
+        rest = torch.ones(T, dtype=torch.bool, device="cuda")
+        rest[70] = rest[T - 1] = False
+        assert float((got[rest].double() - want[rest].double()).norm() / want[rest].double().norm()) <= 1e-5
