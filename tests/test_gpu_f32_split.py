@@ -28,6 +28,18 @@ def test_f32_split_tiles(sdp, orc, w):
     mlp.run_case(sdp, orc, w, [1], dw_layout="scatter" if w.p % 2 else "compact")
 
 
+# dX in 16-wide tiles beside weight gradients in 32-wide ones of one LDS stage (513 to 768 tiles in all): one to five steps a wave, four
+# floats and single ones
+ONE_STAGE = [MlpWorkload(f"one_stage_{T}x{d}x{F}p{p}_{mode}", "f32", T, d, F, p, 2, mode, 93) for T, d, F, p, mode in (
+    (256, 256, 600, 512, "fm"), (250, 251, 600, 511, "fm"), (33, 500, 700, 400, "fm"), (600, 100, 500, 500, "fm"), (200, 200, 640, 600, "bm"),
+    (40, 449, 700, 401, "bm"))]
+
+
+@pytest.mark.parametrize("w", ONE_STAGE, ids=[w.name for w in ONE_STAGE])
+def test_f32_gradients_in_one_stage(sdp, orc, w):
+    mlp.run_case(sdp, orc, w, [1], dw_layout="scatter" if w.p % 2 else "compact")
+
+
 # Rows with one bad element: G and U are then infinite, not a number or, for the largest float, finite where fp32 products are; all
 # other rows are untouched.  Reference: plain PyTorch in fp64, whose products of these do not overflow, rounded to fp32; 257 to 512
 # products summed in fp32 stay below 1e-5 normwise.
