@@ -51,17 +51,48 @@ int check_common(int mode, int dtype, int T, int d, int F, int p) {
     return SDP_OK;
 }
 
-// one thread per column n: lower bound of n in the ascending list
-__global__ __launch_bounds__(256) void column_ranks_kernel(const int32_t* __restrict__ cidx, int pc, int N,
-                                                           int32_t* __restrict__ crank) {
-    const int n = blockIdx.x * blockDim.x + threadIdx.x;
-    if (n >= N) return;
+// first position of the ascending list whose entry is not below n, by all 64 lanes: a step reads 64 entries at equal distances and
+// keeps the piece between two of them, so that a list of 4096 takes two dependent loads and the longest five
+__device__ int lower_bound_wave(const int32_t* __restrict__ cidx, int pc, int n) {
+    const int lane = threadIdx.x & 63;
     int lo = 0, hi = pc;
     while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (cidx[mid] < n) lo = mid + 1; else hi = mid;
+        const int step = (hi - lo + 63) >> 6, at = lo + lane * step;
+        const int below = __popcll(__ballot(at < hi && cidx[at < hi ? at : lo] < n));
+        const int end = below * (int64_t)step < hi - lo ? lo + below * step : hi;
+        if (below) lo += (below - 1) * step + 1;
+        hi = below ? end : lo;
     }
-    crank[n] = lo < pc && cidx[lo] == n ? lo : -1 - lo;
+    return lo;
+}
+
+// Latency bounds it: a search for each column is a chain of log2(pc) loads from the L2.  So a wave finds where the entries of its 256
+// columns begin and another where they end, and the columns search that piece, at most 256 entries of a list without repeats, in the LDS.
+// Backward passes with backward masking, every column searching the list / this, us: T = 1024, d = 512, F = 2048, p = 1280 35.7 / 35.0,
+// T = 512, d = 768, F = 2048, p = 1536 31.3 / 30.8, T = 136, d = 2048, F = 5504, p = 4128 85.0 / 84.1.
+__global__ __launch_bounds__(256) void column_ranks_kernel(const int32_t* __restrict__ cidx, int pc, int N,
+                                                           int32_t* __restrict__ crank) {
+    __shared__ int ends[2];
+    __shared__ int32_t piece[256];
+    const int tid = threadIdx.x, n0 = blockIdx.x * 256, n = n0 + tid;
+    if (tid < 128) {
+        const int r = lower_bound_wave(cidx, pc, tid < 64 ? n0 : n0 > N - 256 ? N : n0 + 256);
+        if ((tid & 63) == 0) ends[tid >> 6] = r;
+    }
+    __syncthreads();
+    const int begin = ends[0];
+    int lo = begin, hi = ends[1];
+    const bool staged = hi - lo <= 256;
+    if (staged && tid < hi - lo) piece[tid] = cidx[lo + tid];
+    __syncthreads();
+    if (n >= N) return;
+    const int stop = hi;
+    auto entry = [&](int i) { return staged ? piece[i - begin] : cidx[i]; };
+    while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (entry(mid) < n) lo = mid + 1; else hi = mid;
+    }
+    crank[n] = lo < stop && entry(lo) == n ? lo : -1 - lo;
 }
 
 int run(int dtype, const GemmDesc& g, hipStream_t s) {
