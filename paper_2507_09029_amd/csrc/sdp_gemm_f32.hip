@@ -8,13 +8,15 @@
 //
 // What bounds it: the matrix cores give 157 TFLOP/s (a plain fp32 FMA half of that), i.e. 32 cycles per 16x16x4 tile, so
 // operand traffic is cheap here (a wave reads 4 KB of LDS per 512 matrix cycles) and the shapes that use fp32 are small:
-// latency, launches and idle CUs decide.  Hence three loops:
+// latency, launches and idle CUs decide.  Hence four loops:
+//   64 x 64 outputs a workgroup whose operands are split into three bf16 terms (gemm_f32_split_kernel, sdp_f32_split.h): where depth and
+//   tiles are many (split_pays);
 //   64 x 64 outputs a workgroup, pipelined (gemm_f32_pipe_kernel): where these fill the CUs;
 //   16 x 16 and 32 x 32 outputs a workgroup, whose four waves split the depth (gemm_f32_wave_kernel): launches of few tiles;
-//   32 x 32 with the depth split inside each step of 64 (gemm_f32_kernel): between the two; and 64 and 128 wide, the largest launches
-//   and those that read a list beyond kListMax.
-// The first two fill LDS by direct loads, 16 bytes a lane or, where extents or strides are no multiples of 4 or columns are
-// gathered, 4; the third moves global -> registers -> LDS, the next three steps in registers, one barrier per step.
+//   32 x 32 with the depth split inside each step of 64 (gemm_f32_kernel): between these; and 64 and 128 wide, the largest launches
+//   and those that read a list beyond kListMax where the split does not pay.
+// The pipelined and the wave-split loops fill LDS by direct loads, 16 bytes a lane or, where extents or strides are no multiples of 4 or
+// columns are gathered, 4; the split and the last move global -> registers -> LDS.
 //
 // A depth slot is free to stand for any k as long as both operands agree: in a group of 16 depth steps, lane group
 // g = lane / 16 takes k = 4 g + j in the j-th of four MFMAs, so an operand stored by rows is one 16-byte LDS read per
@@ -22,7 +24,7 @@
 //
 // Measured: four workers' steps at T = 256, d = 256, F = 1024, p = 512 (twelve launches a worker with a plain FMA kernel
 // and transposed copies before, five with this loop): 2079 -> 165 us, and 139 with the 16 x 16 tiles and dX and the weight
-// gradients as one launch (four a worker; 101 us since the host calls are compiled); per launch 5 - 10 us, of which about 4 us
+// gradients as one launch (four a worker; 101 us since the host calls are compiled, 99 with gradients in one LDS stage and the index without a chain); per launch 5 - 10 us, of which about 4 us
 // is what an empty kernel takes.  (206 us while every step waited for the newest list entry, computed clamped 64-bit addresses per load
 // and branched around its loads, so that the loads in flight could not be counted.)
 #include "sdp_internal.h"
