@@ -1,22 +1,24 @@
 // Part of sdp_gemm_f32.hip: fp32 contraction tiles on the bf16 matrix instructions.
 //
-// x = h + m + l, each term the bf16 nearest to what the terms before it leave: 8 + 8 + 8 bits, exact from 2^-110 up.  a b is then the
-// sum of nine products, of which h h, h m, m h, m m, h l and l h are taken; the other three are below 2^-26 |a b|.  Six
-// v_mfma_f32_32x32x16_bf16 (192 cycles) replace eight v_mfma_f32_32x32x2_f32 (512).  The five small products have an accumulator of
-// their own, since a sum added to the large one is rounded at its size.  Error against 64 bits, normwise, one sum of N(0, 1)
-// products, fp32 instruction / one accumulator / two: 32 terms 9.9e-8 / 3.7e-8 / 3.7e-8, 512 4.4e-7 / 3.5e-7 / 1.3e-7, 4096 1.1e-6 /
-// 9.6e-7 / 3.7e-7; of terms in [1, 2], 512 3.4e-7 / 2.2e-7 / 1.1e-7.
-// Operands that are not finite, and those that round to infinity (above 3.39e38), leave no finite output: a tile with such
-// an output is computed again with the fp32 instruction.
+// x 2^24 = h + m + l, each term the bf16 nearest to what the terms before it leave: 8 + 8 + 8 bits.  The scale makes this exact for every
+// float below 2^103: the last bit of the smallest, 2^-149, becomes 2^-125, and no term is subnormal (without it operands below 2^-110
+// lost bits, and those below 2^-134 all).  a b is then the sum of nine products, of which h h, h m, m h, m m, h l and l h are taken; the
+// other three are below 2^-26 |a b|.  Six v_mfma_f32_32x32x16_bf16 (192 cycles) replace eight v_mfma_f32_32x32x2_f32 (512).  The five
+// small products have an accumulator of their own, since a sum added to the large one is rounded at its size.  Error against 64 bits,
+// normwise, one sum of N(0, 1) products, fp32 instruction / one accumulator / two: 32 terms 9.9e-8 / 3.7e-8 / 3.7e-8, 512 4.4e-7 /
+// 3.5e-7 / 1.3e-7, 4096 1.1e-6 / 9.6e-7 / 3.7e-7; of terms in [1, 2], 512 3.4e-7 / 2.2e-7 / 1.1e-7.
+// Operands that are not finite or of about 2^104 and more, and sums of 2^80 and more, leave no finite scaled output: a tile with such an
+// output is computed again with the fp32 instruction.
 //
 // What bounds it: LDS.  A step of 32 depths of a 64 x 64 tile writes 24 KB of terms (64 bytes a cycle) and reads 48 KB of fragments (128),
 // about 800 cycles, for 12 MFMAs of 32 cycles a SIMD; a step takes 0.46 - 0.52 us whether one, two or three workgroups share a CU.
-// The vector instructions, 98 a wave and step, run between the MFMAs: beside MFMAs a SIMD issues one every 4 cycles, and a 16x16x32
+// The vector instructions, 114 a wave and step, run between the MFMAs: beside MFMAs a SIMD issues one every 4 cycles, and a 16x16x32
 // MFMA keeps it from that for 8 of its 16 cycles, a 32x32x16 one for 10 of its 32 (hence 32 x 32 fragments); v_dot2_f32_bf16, which
 // would take a term's value off in one instruction instead of two, does not run beside an MFMA at all.  Tried: a third LDS stage,
 // so that the next step's fragments are read between the MFMAs, 5 % slower (two workgroups a CU); 128 x 64 tiles 7 % faster from 4000
 // tiles on and much slower below; terms split by each wave as it reads (tiles of 16 and 32), 10 % slower.
-// T = 2048, d = 2048, p = 4000, both passes of a worker: 2628 us with the fp32 instruction, 2203 so; T = 1023, d = 511, p = 1535 327 / 219.
+// Kernel times of both passes of a worker, fp32 instruction / split without the scale / so, us: T = 2048, d = 2048, p = 4000 2655 / 2150 / 2216;
+// T = 1024, d = 1024, p = 2048 405 / 320 / 329; T = 1023, d = 511, p = 1535 324 / 224 / 228.
 #pragma once
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -28,6 +30,7 @@ typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) s16x4* lds_s16x4_ptr;
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4))); // four floats at any float's address
 
+constexpr float kUp = 0x1p24f, kDown = 0x1p-48f; // an operand's scale, and what it takes a sum back
 struct Terms {
     u32x4 h, m, l; // 8 bf16 each
 };
@@ -38,7 +41,7 @@ __device__ inline void split_pair(const f32x4 (&x)[2], int i, Terms& t) {
         asm("" : "+v"(w)); // one value: the compiler would convert the lower half again where it is taken off
         return w;
     };
-    const float a = x[i >> 1][2 * (i & 1)], b = x[i >> 1][2 * (i & 1) + 1];
+    const float a = kUp * x[i >> 1][2 * (i & 1)], b = kUp * x[i >> 1][2 * (i & 1) + 1];
     const uint32_t h = pack(a, b);
     const float ra = a - __uint_as_float(h << 16), rb = b - __uint_as_float(h & 0xFFFF0000u);
     const uint32_t m = pack(ra, rb);
@@ -313,7 +316,7 @@ struct SplitTile {
             if (u + 1 < rounds) step(team + KG * (u + 1), stages + STAGE, stages, ra, std::true_type{});
         }
 
-        acc += low[0] + low[1];
+        acc = (acc + (low[0] + low[1])) * kDown;
         // element 4 q + r of acc: row l32 of A's fragment, row 8 q + 4 lhi + r of B's.  KG = 2: team 0 finishes q = 0 and 2, team 1
         // the others; each leaves the other's in LDS.
         auto part = [&](int q) { return f32x4{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]}; };
