@@ -1089,6 +1089,8 @@ int gemm_f32_group(const GemmDesc* d, int n, const char* name, hipStream_t s) {
         if (i == 0 ? d[i].a_km || d[i].nbatch > 0 || (d[i].epilogue != EPI_STORE && d[i].epilogue != EPI_DUAL_ACC)
                    : !d[i].a_km || d[i].epilogue != EPI_STORE)
             return SDP_ERR_UNSUPPORTED;
+        // one tile for both launches' worth of weight gradients, chosen from the first's extents
+        if (i == 2 && (d[1].M != d[2].M || d[1].N != d[2].N || d[1].K != d[2].K)) return SDP_ERR_UNSUPPORTED;
     }
     // Worth it while d[0] alone leaves room on the chip.  Launches of 512 x 512 outputs, depth 2 x 1376, beside three of
     // 1376 x 512, depth 512: step 114 -> 109 us; 1000 x 512, depth 2 x 1600 (512 tiles of 32 x 32, two on every CU): 209 ->

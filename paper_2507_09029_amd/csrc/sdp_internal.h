@@ -190,8 +190,8 @@ enum GemmOp { OP_GATE_UP = 0, OP_DOWN = 1, OP_DACT = 2, OP_DX = 3, OP_DW = 4, OP
 
 // fp32 contraction on the matrix cores, any shape.
 int gemm_f32(const GemmDesc& g, hipStream_t s);
-// A contraction d[0] with a row-major left operand (STORE or DUAL_ACC) and one or two with depth-major ones (STORE), all with
-// depth-major right operands, none of whose outputs shares memory with an operand, as one launch.  SDP_ERR_UNSUPPORTED: not
+// A contraction d[0] with a row-major left operand (STORE or DUAL_ACC) and one or two of equal extents with depth-major ones (STORE), all
+// with depth-major right operands, none of whose outputs shares memory with an operand, as one launch.  SDP_ERR_UNSUPPORTED: not
 // these; nothing was launched.
 int gemm_f32_group(const GemmDesc* d, int n, const char* name, hipStream_t s);
 // Plain LDS-tiled bf16 contraction, any shape: what the MFMA kernel's address ranges do not take.
