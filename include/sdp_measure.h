@@ -28,10 +28,12 @@ int sdp_profile_filter(const char* name);
 int sdp_profile_reset(void);
 int sdp_profile_read(int cap, const char** names, int64_t* calls, double* ms);
 
-/* Tile shape and workgroup -> tile order of the last MFMA contraction launched under `name` (e.g. "mlp_dw")
+/* Tile shape and workgroup -> tile order of the last contraction launched under `name` (e.g. "mlp_dw")
  * while timing was on: what a recorded counter figure for that kernel has to be matched against.
  *   tile_m, tile_n: outputs per workgroup;  group_m: tile-rows walked together;  stacked: 1 if the problems of a
  *   batched launch that share an operand were walked as one matrix.  All host out.
+ * fp32 contractions: group_m is 0 and stacked names the loop: 1 staged through registers, 2 depth shared out over a tile's waves, 3 the
+ *   same with one LDS stage, 4 pipelined, 5 split products, 6 split products by two teams of waves.
  * dX beside the weight gradients in one launch ("mlp_dx_dw", "attn_dx_dw"): each of the two under its own name ("mlp_dx", "mlp_dw").
  * INVALID_ARG when a pointer is null or no such launch has been seen. */
 int sdp_profile_launch_shape(const char* name, int* tile_m, int* tile_n, int* group_m, int* stacked);

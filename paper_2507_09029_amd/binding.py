@@ -569,13 +569,18 @@ def profile_read(cap=64):
     return {names[i].decode(): (int(calls[i]), float(ms[i])) for i in range(n)}
 
 
+F32_LOOPS = ("staged", "waves", "waves, one stage", "pipelined", "split", "split, two teams")
+
+
 def profile_launch_shape(name):
-    """-> {"tile": "BMxBN", "group_m": g, "stacked": bool} of the last MFMA contraction launched under `name` while
-    timing was on, or None if there was none."""
+    """-> {"tile": "BMxBN", "group_m": g, "stacked": bool} of the last bf16 MFMA contraction launched under `name` while
+    timing was on, {"tile": "BMxBN", "loop": one of F32_LOOPS} of an fp32 one, or None if there was none."""
     v = [ctypes.c_int(0) for _ in range(4)]
     st = lib().sdp_profile_launch_shape(name.encode(), *[ctypes.byref(x) for x in v])
     if st != 0:
         return None
+    if v[2].value == 0:
+        return {"tile": f"{v[0].value}x{v[1].value}", "loop": F32_LOOPS[v[3].value - 1]}
     return {"tile": f"{v[0].value}x{v[1].value}", "group_m": v[2].value, "stacked": bool(v[3].value)}
 
 

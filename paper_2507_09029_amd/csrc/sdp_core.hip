@@ -1,4 +1,5 @@
 // Status strings and per-kernel event timing of libsdp_hip.so.
+#include <array>
 #include <atomic>
 #include <map>
 #include <mutex>
@@ -22,6 +23,7 @@ std::vector<hipEvent_t> g_free;
 std::map<std::string, std::pair<int64_t, double>> g_totals; // name -> (calls, ms)
 std::vector<const char*> g_names;                            // insertion order, static strings
 std::string g_filter;                                        // empty = every kernel
+std::map<std::string, std::array<int, 4>> g_last_shape;      // last launch configuration by name, kept only while timing is on
 
 hipEvent_t take_event() {
     if (!g_free.empty()) {
@@ -94,6 +96,12 @@ void profile_end(hipStream_t s) {
     if (p.stop) (void)hipEventRecord(p.stop, s);
 }
 
+void profile_shape(const char* name, int tile_m, int tile_n, int group_m, int stacked) {
+    if (!name || !profiling_on()) return;
+    std::lock_guard<std::mutex> lk(g_mu);
+    g_last_shape[name] = {tile_m, tile_n, group_m, stacked};
+}
+
 } // namespace sdp
 
 extern "C" const char* sdp_status_string(int status) {
@@ -143,4 +151,13 @@ extern "C" int sdp_profile_read(int cap, const char** names, int64_t* calls, dou
         ++n;
     }
     return n;
+}
+
+extern "C" int sdp_profile_launch_shape(const char* name, int* tile_m, int* tile_n, int* group_m, int* stacked) {
+    if (!name || !tile_m || !tile_n || !group_m || !stacked) return SDP_ERR_INVALID_ARG;
+    std::lock_guard<std::mutex> lk(sdp::g_mu);
+    auto it = sdp::g_last_shape.find(name);
+    if (it == sdp::g_last_shape.end()) return SDP_ERR_INVALID_ARG;
+    *tile_m = it->second[0], *tile_n = it->second[1], *group_m = it->second[2], *stacked = it->second[3];
+    return SDP_OK;
 }

@@ -398,6 +398,7 @@ int launch_split(Dev g, const char* name, hipStream_t s) {
     constexpr int COLS = SplitTile<KG, EPI, ADM, BDM, AG>::COLS;
     g.tiles_m = (g.M + 63) / 64, g.tiles_n = (g.N + COLS - 1) / COLS;
     const int64_t blocks = (int64_t)g.tiles_m * g.tiles_n * (g.nbatch > 0 ? g.nbatch : 1); // below 2^23 (split_pays)
+    profile_shape(name, 64, COLS, 0, KG == 1 ? F32_SPLIT : F32_SPLIT_TEAMS);
     ProfileScope ps(name, s);
     gemm_f32_split_kernel<KG, EPI, ADM, BDM, AG><<<(unsigned)blocks, 256 * KG, 0, s>>>(g);
     return launch_status();

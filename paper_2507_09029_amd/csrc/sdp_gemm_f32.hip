@@ -620,6 +620,7 @@ int launch_wave(Dev g, const char* name, hipStream_t s) {
     auto kern = gemm_f32_wave_kernel<B, S, EPI, ADM, BDM, VA, VB>;
     static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
     if (attr != hipSuccess) return SDP_ERR_HIP;
+    profile_shape(name, B, B, 0, S == 1 ? F32_WAVES_ONE_STAGE : F32_WAVES);
     ProfileScope ps(name, s);
     kern<<<(unsigned)blocks, 256, lds, s>>>(g);
     return launch_status();
@@ -857,6 +858,7 @@ int launch_pipe(Dev g, const char* name, hipStream_t s) {
     auto kern = gemm_f32_pipe_kernel<BM, BN, EPI, ADM, BDM, VA, VB>;
     static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, Sh::LDS);
     if (attr != hipSuccess) return SDP_ERR_HIP;
+    profile_shape(name, BM, BN, 0, F32_PIPELINED);
     ProfileScope ps(name, s);
     kern<<<(unsigned)blocks, 256, lds, s>>>(g);
     return launch_status();
@@ -873,6 +875,7 @@ int launch(Dev g, const char* name, hipStream_t s) {
     auto kern = gemm_f32_kernel<C, EPI, ADM, BDM, VEC>;
     static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
     if (attr != hipSuccess) return SDP_ERR_HIP;
+    profile_shape(name, C::BM, C::BN, 0, F32_STAGED);
     ProfileScope ps(name, s);
     kern<<<(unsigned)blocks, 256, LDS, s>>>(g);
     return launch_status();
@@ -1029,7 +1032,7 @@ int64_t count_tiles(const Dev& g, int b) {
 struct Group {
     Dev x, w0, w1;
     int n; // launches' worth: 2 or 3
-    const char* name;
+    const char *name, *name_x, *name_w; // of the launch; what dX and the weight gradients would be called alone
     hipStream_t s;
 };
 template <int BX, int EPIX, int BW, bool VX, bool WA, bool WB>
@@ -1047,6 +1050,8 @@ int launch_group(const Group& a) {
     auto kern = gemm_f32_group_kernel<BX, EPIX, BW, VX, WA, WB>;
     static const hipError_t attr = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, Sh::LDS);
     if (attr != hipSuccess) return SDP_ERR_HIP;
+    profile_shape(a.name_x, BX, BX, 0, F32_WAVES);
+    profile_shape(a.name_w, BT, BT, 0, BW == kSplit ? F32_SPLIT : BW == kOneStage ? F32_WAVES_ONE_STAGE : BW == 32 ? F32_WAVES : F32_PIPELINED);
     ProfileScope ps(a.name, a.s);
     kern<<<(unsigned)(nx + n0 + n1), 256, lds, a.s>>>(x, w0, w1, (int)nx, (int)n0);
     return launch_status();
@@ -1097,7 +1102,7 @@ int gemm_f32_group(const GemmDesc* d, int n, const char* name, hipStream_t s) {
     // 215 us.
     const bool few = few_tiles(g[0]);
     if (!few && (int64_t)((d[0].M + 31) / 32) * ((d[0].N + 31) / 32) > 256) return SDP_ERR_UNSUPPORTED;
-    const Group a{g[0], g[1], g[2], n, name, s};
+    const Group a{g[0], g[1], g[2], n, name, d[0].name, d[1].name, s};
     const bool vx = va[0] && vb[0], wa = va[1] && va[2], wb = vb[1] && vb[2];
     if (d[0].epilogue == EPI_DUAL_ACC) return few ? launch_group<16, EPI_DUAL_ACC>(a, vx, wa, wb) : launch_group<32, EPI_DUAL_ACC>(a, vx, wa, wb);
     return few ? launch_group<16, EPI_STORE>(a, vx, wa, wb) : launch_group<32, EPI_STORE>(a, vx, wa, wb);

@@ -55,7 +55,6 @@
 #include <cstdlib>
 #include <map>
 #include <mutex>
-#include <string>
 #include <type_traits>
 #include <vector>
 
@@ -1266,10 +1265,6 @@ int choose_group_shared(int tiles_m, int tiles_n, int np0, int nbatch, int kspli
     return best;
 }
 
-// last launch configuration per call-site name, kept only while per-kernel timing is on (sdp_profile_launch_shape)
-std::mutex g_shape_mu;
-std::map<std::string, std::array<int, 4>> g_last_shape;
-
 // OP_DW_TAIL, second kernel: the depth ranges' fp32 tiles of every tile of the last round, added in range order,
 // rounded and stored (optional row scatter).  One thread per 8 columns of a tile row; the tile's place in its
 // problem comes from the same mapping as in the contraction kernel.
@@ -1394,10 +1389,7 @@ int describe(const GemmDesc& d, Dev& g) {
         }
     }
     if (tuning().group_m > 0) g.group_m = tuning().group_m;
-    if (profiling_on() && d.name) {
-        std::lock_guard<std::mutex> lk(g_shape_mu);
-        g_last_shape[d.name] = {BM, BN, g.group_m, g.np0 > 0 ? 1 : 0};
-    }
+    profile_shape(d.name, BM, BN, g.group_m, g.np0 > 0 ? 1 : 0);
     return SDP_OK;
 }
 
@@ -1865,12 +1857,3 @@ int gemm_mfma_bf16(const GemmDesc& d, hipStream_t s) {
 }
 
 } // namespace sdp
-
-extern "C" int sdp_profile_launch_shape(const char* name, int* tile_m, int* tile_n, int* group_m, int* stacked) {
-    if (!name || !tile_m || !tile_n || !group_m || !stacked) return SDP_ERR_INVALID_ARG;
-    std::lock_guard<std::mutex> lk(sdp::g_shape_mu);
-    auto it = sdp::g_last_shape.find(name);
-    if (it == sdp::g_last_shape.end()) return SDP_ERR_INVALID_ARG;
-    *tile_m = it->second[0], *tile_n = it->second[1], *group_m = it->second[2], *stacked = it->second[3];
-    return SDP_OK;
-}

@@ -17,6 +17,10 @@ void profile_begin(const char* name, hipStream_t s);
 // start / stop events for a launch that records them itself (hipExtLaunchKernel); false = not timed
 bool profile_launch_events(const char* name, hipEvent_t* start, hipEvent_t* stop);
 void profile_end(hipStream_t s);
+// what sdp_profile_launch_shape will say of the last launch under `name`, while timing is on
+void profile_shape(const char* name, int tile_m, int tile_n, int group_m, int stacked);
+// fp32 contractions: group_m = 0, stacked = the loop
+enum F32Loop { F32_STAGED = 1, F32_WAVES = 2, F32_WAVES_ONE_STAGE = 3, F32_PIPELINED = 4, F32_SPLIT = 5, F32_SPLIT_TEAMS = 6 };
 
 struct ProfileScope {
     hipStream_t s;

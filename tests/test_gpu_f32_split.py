@@ -71,22 +71,32 @@ def _normal(*shape, scale, gen):
     return torch.randn(shape, generator=gen, device="cuda") * scale
 
 
+def _launched(sdp, names, call, *args):
+    """what the call returns, and the loop that each of the named launches took"""
+    sdp.profile_filter(None)
+    sdp.profile_enable(True)
+    out = call(*args)
+    sdp.profile_enable(False)
+    return out, [sdp.profile_launch_shape(n)["loop"] for n in names]
+
+
 def _off(got, want):
     return float((got.double() - want).norm() / want.norm())
 
 
 # Products of operands at the ends of fp32's range, numbers below its normal ones among them, whose sums lie well inside it: G and U, and
-# what dact, dX and the weight gradients make of such dY, U and weights, all in launches that split (1088 tokens: 17 rows of tiles).
+# what dact, dX and the weight gradients make of such dY, U and weights, all in launches that split (_launched sees to it).
 # Reference: plain PyTorch in fp64.  A sum is off by its own rounding (below 1e-6 normwise at these depths) and dG, dU and act by a few of theirs.
 @pytest.mark.parametrize("x,w", [(-110, 100), (-114, 100), (-118, 100), (-122, 100), (-126, 110), (-130, 110), (-140, 110), (100, -122), (110, -130),
                                  (120, -140), (-55, -55), (60, 55), (100, 20)])
 def test_f32_split_operands_at_the_ends_of_the_range(sdp, x, w):
-    T, d, F = 1088, 512, 1024
+    T, d, F = 1024, 544, 1024
     g = torch.Generator(device="cuda")
     g.manual_seed(94)
     idx = torch.arange(F, dtype=torch.int32, device="cuda")
     X, W = _normal(T, d, scale=2.0**x, gen=g), [_normal(F, d, scale=2.0**w, gen=g) for _ in range(3)]
-    _, G, U = sdp.masked_mlp_fwd("fm", X, *W, idx)
+    (_, G, U), loops = _launched(sdp, ("mlp_gate_up", "mlp_down"), sdp.masked_mlp_fwd, "fm", X, *W, idx)
+    assert all("split" in k for k in loops), loops
     for got, m in ((G, W[0]), (U, W[1])):
         assert _off(got, X.double() @ m.double().t()) <= 1e-6, (x, w)
 
@@ -94,13 +104,14 @@ def test_f32_split_operands_at_the_ends_of_the_range(sdp, x, w):
 @pytest.mark.parametrize("dy,w2,u,w13", [(-122, 100, 0, 0), (-130, 120, 0, 0), (100, -122, 0, 0), (0, 0, -122, 100), (0, 100, -122, 0), (-122, 120, 0, 100),
                                          (-100, -10, 0, 110), (60, 40, 0, -122)])
 def test_f32_split_gradients_at_the_ends_of_the_range(sdp, dy, w2, u, w13):
-    T, d, F = 1088, 512, 1024
+    T, d, F = 1024, 544, 1024
     g = torch.Generator(device="cuda")
     g.manual_seed(95)
     idx = torch.arange(F, dtype=torch.int32, device="cuda")
     X, dY, G, U = (_normal(*s, scale=2.0**e, gen=g) for s, e in (((T, d), 0), ((T, d), dy), ((T, F), 0), ((T, F), u)))
     W = [_normal(F, d, scale=2.0**e, gen=g) for e in (w13, w13, w2)]
-    got = sdp.masked_mlp_bwd("fm", X, dY, *W, idx, G, U)
+    got, loops = _launched(sdp, ("mlp_dact", "mlp_dx", "mlp_dw"), sdp.masked_mlp_bwd, "fm", X, dY, *W, idx, G, U)
+    assert all("split" in k for k in loops), loops
     X, dY, G, U, W1, W3, W2 = (t.double() for t in (X, dY, G, U, *W))
     s = torch.sigmoid(G)
     dA = dY @ W2.t()
