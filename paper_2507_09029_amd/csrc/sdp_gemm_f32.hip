@@ -179,9 +179,22 @@ __device__ inline f32x4 fragment(const float* lds, int row, int t, int g) {
     }
 }
 
-// epilogue of four consecutive columns n .. n + 3 of row m; FROM: those from `lo` on (vec_out: lo - n is a multiple of 4)
+// columns n .. n + 3 of row m of a matrix of the outputs' extents, zeros outside
+__device__ inline f32x4 row_of_four(const Dev& g, const float* base, int64_t ld, int m, int n) {
+    f32x4 x = {0.f, 0.f, 0.f, 0.f};
+    if (m >= g.M || n >= g.N) return x;
+    const float* p = base + (int64_t)m * ld + n;
+    if (g.vec_out) return *(const f32x4*)p;
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (n + e < g.N) x[e] = p[e];
+    return x;
+}
+
+// epilogue of four consecutive columns n .. n + 3 of row m; FROM: those from `lo` on (vec_out: lo - n is a multiple of 4);
+// gu: G and U there, where they have been read already
 template <int EPI, bool FROM = false>
-__device__ inline void emit(const Dev& g, float* gC, int m, int n, f32x4 v, f32x4 v2, int lo = 0) {
+__device__ inline void emit(const Dev& g, float* gC, int m, int n, f32x4 v, f32x4 v2, int lo = 0, const f32x4* gu = nullptr) {
     if (m >= g.M || n >= g.N || (FROM && n + 3 < lo)) return;
     const int cnt = g.N - n < 4 ? g.N - n : 4;
     auto put = [&](float* base, int64_t row, int64_t ld, f32x4 x) {
@@ -193,15 +206,7 @@ __device__ inline void emit(const Dev& g, float* gC, int m, int n, f32x4 v, f32x
                 if (e < cnt && (!FROM || n + e >= lo)) p[e] = x[e];
         }
     };
-    auto get = [&](const float* base, int64_t ld) {
-        const float* p = base + (int64_t)m * ld + n;
-        if (g.vec_out) return *(const f32x4*)p;
-        f32x4 x = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-            if (e < cnt) x[e] = p[e];
-        return x;
-    };
+    auto get = [&](const float* base, int64_t ld) { return row_of_four(g, base, ld, m, n); };
     if (EPI == EPI_STORE || EPI == EPI_DUAL_ACC) {
         const int64_t row = g.cs ? g.cs[m] : m;
         if (row < 0) return; // dropped row
@@ -215,7 +220,7 @@ __device__ inline void emit(const Dev& g, float* gC, int m, int n, f32x4 v, f32x
         for (int e = 0; e < 4; ++e) act[e] = swiglu_fwd<true>(v[e], v2[e]);
         put(g.C3, m, g.ldc, act);
     } else {
-        const f32x4 gv = get(g.Gin, g.ldg), uv = get(g.Uin, g.ldg);
+        const f32x4 gv = gu ? gu[0] : get(g.Gin, g.ldg), uv = gu ? gu[1] : get(g.Uin, g.ldg);
         f32x4 dg, du, act;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
