@@ -893,6 +893,58 @@ bool few_tiles(const Dev& g) {
     return (int64_t)((g.M + 15) / 16) * ((g.N + 15) / 16) * (g.nbatch > 0 ? g.nbatch : 1) <= 512;
 }
 
+// Whether a launch takes the tiles of sdp_f32_split.h instead of the fp32 ones: what either would take, from its rounds of tiles over the
+// 256 CUs and its steps of 32 depths.  The figures are kernel times in us, with about 5 of event overhead, of 850 launches of MLP and
+// attention passes (T = 64 .. 2400, widths 160 .. 3000, every alignment, listed columns), fitted within 3 to 8 % (rms).
+// A round of split tiles takes what two and a half rounds of 32-wide ones do with 16-byte loads, so one loses to two of those and two
+// lose to four, but win against three and five: fp32 / split (rounds), down T = 416, d = 1176, p = 1824 30.1 / 35.7 (2 / 1), T = 512, d = 1100,
+// p = 1376 35.5 / 30.4 (3 / 1), T = 1518, d = 668, p = 1444 42.3 / 48.1 (4 / 2), T = 1300, d = 800, p = 816 39.5 / 31.1 (6 / 2).  Single floats cost the
+// fp32 loops a quarter to all of a step again and the split ones nothing: weight gradients of 699 x 623, 813 deep 100.7 / 48.1.  Rows that end off
+// a multiple of four floats cost the split epilogues more, since a lane has single columns of 32 rows; the activation gradient's
+// then takes 12 us a round: n = 1407, d = 576, T = 900 27.4 / 39.4, and with single-float loads T = 599, d = 367, n = 799 15.4 / 21.9.  Listed columns of
+// the left operand cost them a third of a step: T = 408, d = 676, p = 372 17.2 / 21.6, but T = 2160, d = 460, p = 948 138 / 111.
+struct LaunchKind {
+    int kind; // 0 gate_up, 1 activation gradient, 2 both operands by rows, 3 right one depth-major, 4 both depth-major
+    int load; // 16-byte loads: 0 of both operands, 1 of the right one, 2 of neither
+    bool rows, listed; // 16-byte stores; listed columns of a depth-major left operand
+};
+constexpr double kRound32[5][3] = {{1.3, 0, 3.5}, {1, 0, 1.8}, {.6, 0, 1.8}, {1.2, .3, 2.4}, {.5, .4, .1}};
+constexpr double kStep32[5][3] = {{.303, 0, .43}, {.161, 0, .232}, {.165, 0, .232}, {.188, .262, .39}, {.184, .265, .352}};
+constexpr double kStart64[5][3] = {{8, 0, 8}, {9.7, 0, 12}, {7.5, 0, 12}, {8, 9, 15}, {9, 9, 13}};
+constexpr double kStep64[5][3] = {{.61, 0, .745}, {.64, 0, .745}, {.63, 0, .745}, {.70, .80, 1.2}, {.60, .66, .72}};
+double fp32_us(const LaunchKind& k, int width, int64_t tiles32, int64_t tiles64, int64_t steps) {
+    if (width == 32) return 6.2 + (tiles32 + 255) / 256 * (kRound32[k.kind][k.load] + (kStep32[k.kind][k.load] + (k.listed ? .025 : 0)) * steps);
+    const double round = k.kind == 1 ? (k.rows ? .6 : 3) : k.kind == 0 && !k.rows ? 1.3 : 0;
+    return kStart64[k.kind][k.load] + (tiles64 + 255) / 256 * (round + kStep64[k.kind][k.load] * steps);
+}
+constexpr double kSplitRound[5][2] = {{1.3, 4}, {5.5, 12}, {.9, 3}, {1.3, 1.8}, {1, 2}}; // rows, not rows
+constexpr double kSplitStart[5] = {5.2, 2, 5, 5.3, 5.2}, kSplitStep[5] = {.446, .425, .452, .46, .474};
+constexpr double kTeamsStart[5] = {7.1, 5, 7.1, 7, 7.2}, kTeamsStep[5] = {.455, .455, .46, .495, .567}; // two teams: one round
+double split_us(const LaunchKind& k, int64_t tiles64, int64_t steps) {
+    const int64_t rounds = (tiles64 + 255) / 256;
+    if (k.listed) return rounds == 1 ? 10 + .827 * steps : k.rows ? 4.5 + rounds * (3 + .652 * steps) : rounds * (5.5 + .69 * steps);
+    const double round = kSplitRound[k.kind][k.rows ? 0 : 1];
+    return rounds == 1 ? kTeamsStart[k.kind] + round + kTeamsStep[k.kind] * steps : kSplitStart[k.kind] + rounds * (round + kSplitStep[k.kind] * steps);
+}
+
+// width: of the fp32 tiles that the launch would have
+template <int EPI, bool ADM, bool BDM, bool VA, bool VB>
+bool split_pays(const Dev& g, int width, int64_t tiles32, int64_t tiles64) {
+    constexpr bool VEC = VA && VB, two = EPI == EPI_SWIGLU_FWD;
+    const LaunchKind k{two ? 0 : EPI == EPI_SWIGLU_BWD ? 1 : ADM ? 4 : BDM ? 3 : 2, VEC ? 0 : VB ? 1 : 2, g.vec_out != 0, ADM && g.ag};
+    // what the tiles need: a whole step, 64 rows of a depth-major operand
+    if (g.K < 256 || (ADM && g.M < 64) || (BDM && g.N < 64) || tiles64 > 0x7FFFFF) return false;
+    if (two && tiles64 <= 256 && g.K < 320 && (VEC || !k.rows)) return false; // T = 528, d = 280, n = 536 11.9 / 12.6
+    // less than a round: where it was measured to pay
+    if (tiles64 < 256 && !(two && tiles64 >= 150) && !(tiles64 > 128 && g.K >= 1024) && !(tiles64 >= 128 && !VEC)) return false;
+    if (width == 16) return false; // the chip holds the launch at once
+    if (k.kind == 1 && VEC && !k.rows) return false; // 26 launches: 24 slower, by 5 to 44 %
+    if (k.listed && width == 64) return false;       // 48 launches: 0.93 to 1.27 of the fp32 tiles' time
+    if (width == 128) return true;
+    const int64_t steps = (int64_t)((g.K + 31) / 32) * (EPI == EPI_DUAL_ACC ? 2 : 1);
+    return split_us(k, tiles64, steps) < fp32_us(k, width, tiles32, tiles64, steps);
+}
+
 // Tile of a launch: the fewest matrix cycles on the busiest CU (rounds of tiles over 256 CUs x tile area), each tile
 // weighted by what its loop loses to staging and barriers.  With fewer 64-wide tiles than CUs the 32-wide ones win on
 // both counts (T = 256, p = 512, d = 256: 128 tiles whose waves each run a quarter of the depth, against 32).
@@ -904,19 +956,6 @@ bool few_tiles(const Dev& g) {
 // attn_dout 9.8 / 8.3 with 256 tiles, but 25.9 / 27.5 with 512 (T = 1000).
 // Extents that are no multiples of 4, whole steps before / now: T = 1023, d = 510, F = 2046, p = 1025 610 / 471 us, T = 255, d = 126,
 // p = 401 126 / 69, T = 101, d = 301, p = 901 201 / 110, backward masking T = 600, d = 66, p = 900 257 / 130.
-// Whether a launch takes the tiles of sdp_f32_split.h, from its tiles of 64: those pay where their depth is long enough for what a step
-// saves and they fill the chip better than 32-wide ones.  Before / split, kernel times in us (tiles, depth): gate_up 23.4 / 20.9
-// (344, 512), 15.2 / 13.7 (224, 512), 16.0 / 15.0 (156, 299), 563 / 469 (4000, 2048), but 11.7 / 13.3 (130, 367), 15.2 / 16.8 (260, 236);
-// dact 19.9 / 17.4 (256, 512), 287 / 254 (2016, 2048), but 14.9 / 16.3 (176, 512); down 30.3 / 26.5 (136, 1376), 39.2 / 30.8 (256, 1376), but
-// 23.8 / 26.8 (128, 1376: two even rounds of 32 x 32); dX 57 / 48.5 (136, 2 x 1376), 631 / 515 (1024, 2 x 4000); weight gradients 43.0 /
-// 36.5 (384, 1024), 830 / 714 (6048, 2048).  Extents that are no multiples of 4, which the others load by single floats: down 43.3 /
-// 31.0, dX 81 / 57 (128, 1535), weight gradients 115 / 53 (576, 1023).
-template <bool ADM, bool BDM, bool VEC>
-bool split_pays(const Dev& g, int64_t tiles, int nb) {
-    if (g.K < 256 || (ADM && g.M < 64) || (BDM && g.N < 64) || tiles > 0x7FFFFF) return false;
-    return tiles >= 256 || (tiles >= 150 && nb == 2) || (tiles > 128 && g.K >= 1024) || (tiles >= 128 && !VEC);
-}
-
 template <int EPI, bool ADM, bool BDM, bool VA, bool VB>
 int choose(const Dev& g, const char* name, hipStream_t s) {
     constexpr bool VEC = VA && VB;
@@ -930,7 +969,16 @@ int choose(const Dev& g, const char* name, hipStream_t s) {
         if (t * 256 > UINT32_MAX) return HUGE_VAL; // threads of one launch
         return (double)((t + 255) / 256) * b * bn * weight;
     };
-    if (split_pays<ADM, BDM, VEC>(g, tiles(64, 64 / NB), NB)) {
+    // the fp32 tile first: 16, 32, 64 or 128 wide
+    const double c128 = cost(128, 128, 1.0), c32 = cost(32, 32, 1.3);
+    // single floats: the tiles that direct loads fill, of 64 and 32
+    const double c64 = direct ? cost(64, 64 / NB, 1.1) : HUGE_VAL, staged128 = VEC || !direct ? c128 : HUGE_VAL;
+    const double staged64 = (VEC && NB == 2) || !direct ? cost(64, 64, 1.1) : HUGE_VAL;
+    int width = 64;
+    if (direct && few_tiles(g)) width = 16;
+    else if (c32 < c64 && c32 < staged64 && c32 < staged128) width = 32;
+    else if (staged128 <= c64 && staged128 <= staged64) width = 128;
+    if (split_pays<EPI, ADM, BDM, VA, VB>(g, width, tiles(32, 32), tiles(64, 64 / NB))) {
         auto go = [&](auto listed) { // listed columns of the left operand
             constexpr bool AG = decltype(listed)::value;
             // two teams, one workgroup a CU, while the tiles leave room for it
@@ -943,25 +991,21 @@ int choose(const Dev& g, const char* name, hipStream_t s) {
         return go(std::false_type{});
     }
     if (direct) {
-        if (few_tiles(g)) return launch_wave<16, 2, EPI, ADM, BDM, VA, VB>(g, name, s);
-        const double c64 = cost(64, 64 / NB, 1.1), c32 = cost(32, 32, 1.3);
-        // single floats: the tiles that direct loads fill, of 64 and 32
-        const double staged128 = VEC ? cost(128, 128, 1.0) : HUGE_VAL, staged64 = VEC && NB == 2 ? cost(64, 64, 1.1) : HUGE_VAL;
-        if (c32 < c64 && c32 < staged64 && c32 < staged128) {
+        if (width == 16) return launch_wave<16, 2, EPI, ADM, BDM, VA, VB>(g, name, s);
+        if (width == 32) {
             if (!VEC || (!ADM && NB == 1 && EPI != EPI_SWIGLU_BWD && tiles(32, 32) <= 256)) return launch_wave<32, 2, EPI, ADM, BDM, VA, VB>(g, name, s);
             return launch<Cfg<32, 32, 4>, EPI, ADM, BDM, true>(g, name, s);
         }
         if constexpr (VEC) {
-            if (staged128 <= c64 && staged128 <= staged64) return launch<Cfg<128, 128, 1>, EPI, ADM, BDM, true>(g, name, s);
+            if (width == 128) return launch<Cfg<128, 128, 1>, EPI, ADM, BDM, true>(g, name, s);
             if ((BDM && !ADM) || (staged64 <= c64 && tiles(64, 64) > 256)) return launch<Cfg<64, 64, 1>, EPI, ADM, BDM, true>(g, name, s);
         }
         return launch_pipe<64, 64 / NB, EPI, ADM, BDM, VA, VB>(g, name, s);
     }
     if constexpr (BDM) { // a list too long for LDS
-        const double c128 = cost(128, 128, 1.0), c64 = cost(64, 64, 1.1), c32 = cost(32, 32, 1.3);
-        if (c32 < c64 && c32 < c128) return launch<Cfg<32, 32, 4>, EPI, ADM, BDM, VEC>(g, name, s);
-        if (c64 < c128) return launch<Cfg<64, 64, 1>, EPI, ADM, BDM, VEC>(g, name, s);
-        return launch<Cfg<128, 128, 1>, EPI, ADM, BDM, VEC>(g, name, s);
+        if (width == 32) return launch<Cfg<32, 32, 4>, EPI, ADM, BDM, VEC>(g, name, s);
+        if (width == 64) return launch<Cfg<64, 64, 1>, EPI, ADM, BDM, VEC>(g, name, s);
+        return launch<Cfg<128, 128, 1>, EPI, ADM, BDM, VEC>(g, name, s); // beyond the split tiles' 2^23, which leave nothing else to it
     }
     return SDP_ERR_INVALID_ARG; // not reached
 }

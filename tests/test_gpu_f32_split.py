@@ -80,6 +80,38 @@ def _launched(sdp, names, call, *args):
     return out, [sdp.profile_launch_shape(n)["loop"] for n in names]
 
 
+def _loop(sdp, T, d, F, p, mode, launch):
+    X, dY, W = _inputs(T, d, F, 96)
+    idx = torch.arange(F - p, F, dtype=torch.int32, device="cuda")
+
+    def both():
+        _, G, U = sdp.masked_mlp_fwd(mode, X, *W, idx)
+        sdp.masked_mlp_bwd(mode, X, dY, *W, idx, G, U)
+
+    return _launched(sdp, [f"mlp_{launch}"], both)[1][0]
+
+
+def _inputs(T, d, F, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+    return _normal(T, d, scale=1.0, gen=g), _normal(T, d, scale=1.0, gen=g), [_normal(F, d, scale=0.02, gen=g) for _ in range(3)]
+
+
+# sizes at both sides of the lines between the loops
+@pytest.mark.parametrize("T,d,F,p,mode,launch,loop", [
+    # one round of split tiles against two and three rounds of 32-wide ones, two against four and six
+    (416, 1176, 1824, 1824, "fm", "down", "staged"), (512, 1100, 1376, 1376, "fm", "down", "split, two teams"), (1518, 668, 1444, 1444, "fm", "dx", "staged"),
+    (1300, 800, 816, 816, "fm", "dx", "split"), (2041, 516, 620, 620, "fm", "dw", "staged"),
+    # depth against 64-wide tiles; single floats in less than 150 tiles
+    (528, 280, 536, 536, "fm", "gate_up", "pipelined"), (1024, 496, 312, 312, "fm", "gate_up", "split, two teams"), (278, 367, 818, 818, "fm", "gate_up", "waves"),
+    # the activation gradient's rows: no multiples of four floats; single-float loads
+    (900, 576, 1407, 1407, "fm", "dact", "staged"), (599, 367, 799, 799, "fm", "dact", "waves"), (964, 807, 621, 621, "fm", "dact", "split, two teams"),
+    # listed columns of the gradients
+    (408, 676, 636, 372, "bm", "dw", "pipelined"), (2160, 460, 2244, 948, "bm", "dw", "split")])
+def test_f32_loop_by_size(sdp, T, d, F, p, mode, launch, loop):
+    assert _loop(sdp, T, d, F, p, mode, launch) == loop
+
+
 def _off(got, want):
     return float((got.double() - want).norm() / want.norm())
 
