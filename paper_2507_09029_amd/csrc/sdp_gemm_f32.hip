@@ -1111,20 +1111,27 @@ int launch_group(const Group& a, bool vx, bool wa, bool wb) {
     // by tiles of 64 and steps of 32: 768, 4 (T = 128, d = 512, p = 2000) 32.8 / 25.9 us, 360, 16 57.6 / 56.1, an attention's 256, 16
     // 32.6 / 28.7; but 231, 16 (T = 512, d = 448) 37.5 / 47.5, 288, 32 58.4 / 66.8, 96, 16 19.3 / 22.4.
     const int64_t t64 = count_tiles(a.w0, 64) + (a.n > 2 ? count_tiles(a.w1, 64) : 0);
-    // Split products from a depth of 448 on: 64-wide before / split 56.0 / 49.4 (528, 512 deep), 39.2 / 35.7 (288, 434, single floats),
-    // 36.5 / 31.0 (225, 700), but 34.4 / 36.0 (384, 400), 15.6 / 17.5 (384, 128); 32-wide / split 42.5 / 38.4 (156, 586).
+    const bool wide = t64 >= 16 * (int64_t)((a.w0.K + 31) / 32);
+    const int64_t all = count_tiles(a.x, BX) + count_tiles(a.w0, 32) + (a.n > 2 ? count_tiles(a.w1, 32) : 0); // of dX's and 32-wide ones
+    // Split products from 150 tiles and a depth of 448 on: 64-wide before / split 53.6 / 49.0 (528, 512 deep), 39.2 / 35.7 (288, 434, single
+    // floats), 67.0 / 58.7 (432, 835), but 34.4 / 36.0 (384, 400), 15.6 / 17.5 (384, 128); 32-wide / split 33.7 / 29.7 (216, 600), 33.1 / 28.8
+    // (195, 698), single floats 48.0 / 31.9 (210, 592).  Not where 32-wide tiles with 16-byte loads nearly fit the chip at once: 31.1 / 34.5
+    // (168, 948; 798 tiles in all), 34.1 / 37.2 (153, 1048; 660), but 43.2 / 39.2 (153, 1136; 828).  Not listed columns, whose loads cost the
+    // split tiles most, instead of 64-wide ones: T = 468, d = 220, p = 1536 35.6 / 43.9, T = 502, d = 235, p = 1441 51.4 / 57.8; with 32-wide ones
+    // T = 558, d = 388, p = 737 43.6 / 35.0.
+    const bool fits = vx && wa && wb && all <= 800;
+    const bool split = t64 >= 150 && a.w0.K >= 448 && a.w0.M >= 64 && a.w0.N >= 64 && !fits && !(a.w0.ag && wide);
     auto go = [&](auto bw) {
         constexpr int BW = decltype(bw)::value;
         if (vx && wa && wb) return launch_group<BX, EPIX, BW, true, true, true>(a);
         if (vx && wb) return launch_group<BX, EPIX, BW, true, false, true>(a);
         return launch_group<BX, EPIX, BW, false, false, false>(a);
     };
-    if (t64 >= 150 && a.w0.K >= 448 && a.w0.M >= 64 && a.w0.N >= 64) return go(std::integral_constant<int, kSplit>{});
-    if (t64 >= 16 * (int64_t)((a.w0.K + 31) / 32)) return go(std::integral_constant<int, 64>{});
+    if (split) return go(std::integral_constant<int, kSplit>{});
+    if (wide) return go(std::integral_constant<int, 64>{});
     // 32-wide ones with one LDS stage where the launch then fits the chip at once, three workgroups a CU instead of two: T = 256, d = 256,
     // p = 512 (640 tiles) 10.2 / 9.8 us, four workers' step 101.1 / 99.7.
     if constexpr (BX == 16) {
-        const int64_t all = count_tiles(a.x, 16) + count_tiles(a.w0, 32) + (a.n > 2 ? count_tiles(a.w1, 32) : 0);
         if (all > 512 && all <= 768) return go(std::integral_constant<int, kOneStage>{});
     }
     return go(std::integral_constant<int, 32>{});

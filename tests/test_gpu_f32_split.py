@@ -112,6 +112,13 @@ def test_f32_loop_by_size(sdp, T, d, F, p, mode, launch, loop):
     assert _loop(sdp, T, d, F, p, mode, launch) == loop
 
 
+# the gradients beside dX: tiles that fit the chip at once, listed columns
+@pytest.mark.parametrize("T,d,F,p,mode,loop", [(948, 200, 880, 880, "fm", "waves"), (1136, 168, 1064, 1064, "fm", "split"), (468, 220, 2152, 1536, "bm", "pipelined"),
+                                               (558, 388, 1144, 737, "bm", "split"), (502, 235, 2039, 1441, "bm", "pipelined")])
+def test_f32_loop_of_gradients_beside_dx(sdp, T, d, F, p, mode, loop):
+    assert _loop(sdp, T, d, F, p, mode, "dw") == loop
+
+
 def _off(got, want):
     return float((got.double() - want).norm() / want.norm())
 
