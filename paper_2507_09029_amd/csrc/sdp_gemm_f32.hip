@@ -1129,10 +1129,14 @@ int launch_group(const Group& a, bool vx, bool wa, bool wb) {
     };
     if (split) return go(std::integral_constant<int, kSplit>{});
     if (wide) return go(std::integral_constant<int, 64>{});
-    // 32-wide ones with one LDS stage where the launch then fits the chip at once, three workgroups a CU instead of two: T = 256, d = 256,
-    // p = 512 (640 tiles) 10.2 / 9.8 us, four workers' step 101.1 / 99.7.
+    // 32-wide ones with one LDS stage where the launch then fits the chip at once, three workgroups a CU instead of two, unless dX's depth is
+    // so long beside the gradients' that the launch ends with it, slowed down by a third workgroup.  42 shapes of 513 to 768 tiles, forward and
+    // backward masking, two stages / one: T = 256, d = 256, p = 512 10.2 / 9.8 us, T = 200, d = 452, p = 140 10.6 / 8.9 and 12.0 / 9.9, T = 592,
+    // d = 133, p = 705 31.5 / 26.8 and 33.9 / 26.3 (median 14 % less), but T = 424, d = 121, p = 849 24.5 / 25.2, T = 256, d = 153, p = 861 22.3 / 23.3 and
+    // 19.4 / 20.9.  Listed columns (backward masking) load longer: T = 288, d = 217, p = 677 22.1 / 21.9 and 21.6 / 19.8.
     if constexpr (BX == 16) {
-        if (all > 512 && all <= 768) return go(std::integral_constant<int, kOneStage>{});
+        const int64_t depth = (int64_t)a.x.K * (EPIX == EPI_DUAL_ACC ? 2 : 1);
+        if (all > 512 && all <= 768 && depth <= (a.w0.ag ? 6 : 4) * (int64_t)a.w0.K) return go(std::integral_constant<int, kOneStage>{});
     }
     return go(std::integral_constant<int, 32>{});
 }

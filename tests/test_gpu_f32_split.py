@@ -119,6 +119,13 @@ def test_f32_loop_of_gradients_beside_dx(sdp, T, d, F, p, mode, loop):
     assert _loop(sdp, T, d, F, p, mode, "dw") == loop
 
 
+# and one LDS stage or two, by dX's depth
+@pytest.mark.parametrize("T,d,F,p,mode,loop", [(256, 153, 861, 861, "fm", "waves"), (256, 153, 861, 861, "bm", "waves"), (424, 121, 849, 849, "fm", "waves"),
+                                               (288, 217, 677, 600, "bm", "waves, one stage"), (592, 133, 705, 705, "fm", "waves, one stage")])
+def test_f32_one_stage_or_two(sdp, T, d, F, p, mode, loop):
+    assert _loop(sdp, T, d, F, p, mode, "dw") == loop
+
+
 def _off(got, want):
     return float((got.double() - want).norm() / want.norm())
 
