@@ -1444,7 +1444,7 @@ int sdp::attn_bwd_impl(int mode, int dtype, int Bt, int S, int d, int H, int hd,
         dw.name = "attn_dw";
         dw.M = Eh, dw.N = d, dw.K = T;
         dw.lda = 3 * E, dw.a_km = 1;
-        if (!gathered && !all_heads) dw.a_gather = w.rows_o, dw.a_rows = E;
+        if (!gathered && !all_heads) dw.a_gather = w.rows_o, dw.a_rows = E, dw.a_gather_chunks = hd % 8 == 0;
         dw.ldb = d, dw.b_km = 1;
         dw.epilogue = EPI_STORE;
         dw.ldc = d;

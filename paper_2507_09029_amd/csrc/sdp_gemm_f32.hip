@@ -43,6 +43,7 @@ struct Dev {
     const float *A, *A2, *B, *B2;
     int64_t lda, ldb;
     const int32_t *ag, *bg, *cs;
+    int runs; // ag's entries come in runs of eight
     float *C, *C2, *C3;
     int64_t ldc;
     const float *Gin, *Uin;
@@ -939,7 +940,9 @@ bool split_pays(const Dev& g, int width, int64_t tiles32, int64_t tiles64) {
     if (tiles64 < 256 && !(two && tiles64 >= 150) && !(tiles64 > 128 && g.K >= 1024) && !(tiles64 >= 128 && !VEC)) return false;
     if (width == 16) return false; // the chip holds the launch at once
     if (k.kind == 1 && VEC && !k.rows) return false; // 26 launches: 24 slower, by 5 to 44 %
-    if (k.listed && width == 64) return false;       // 48 launches: 0.93 to 1.27 of the fp32 tiles' time
+    // 48 launches of listed columns 0.93 to 1.27 of the 64-wide tiles' time.  Runs of columns, heads, are what the fp32 loops read well:
+    // T = 1248, d = 704, 9 of 11 heads of 64 88.7 / 111.0, T = 688, d = 960, 9 of 12 of 80 88.7 / 102.1; heads of 50 90.4 / 81.4
+    if (k.listed && (width == 64 || g.runs)) return false;
     if (width == 128) return true;
     const int64_t steps = (int64_t)((g.K + 31) / 32) * (EPI == EPI_DUAL_ACC ? 2 : 1);
     return split_us(k, tiles64, steps) < fp32_us(k, width, tiles32, tiles64, steps);
@@ -1025,7 +1028,7 @@ int describe(const GemmDesc& d, Dev& g, bool* va_out, bool* vb_out) {
     g = Dev{};
     g.M = d.M, g.N = d.N, g.K = d.K;
     g.A = (const float*)d.A, g.A2 = (const float*)d.A2, g.B = (const float*)d.B, g.B2 = (const float*)d.B2;
-    g.lda = d.lda, g.ldb = d.ldb, g.ag = d.a_gather, g.bg = d.b_gather, g.cs = d.c_scatter;
+    g.lda = d.lda, g.ldb = d.ldb, g.ag = d.a_gather, g.bg = d.b_gather, g.cs = d.c_scatter, g.runs = d.a_gather_chunks;
     g.C = (float*)d.C, g.C2 = (float*)d.C2, g.C3 = (float*)d.C3, g.ldc = d.ldc;
     g.Gin = (const float*)d.Gin, g.Uin = (const float*)d.Uin, g.ldg = d.ldg;
     g.R = (const float*)d.R, g.ldr = d.ldr;
@@ -1118,9 +1121,12 @@ int launch_group(const Group& a, bool vx, bool wa, bool wb) {
     // (195, 698), single floats 48.0 / 31.9 (210, 592).  Not where 32-wide tiles with 16-byte loads nearly fit the chip at once: 31.1 / 34.5
     // (168, 948; 798 tiles in all), 34.1 / 37.2 (153, 1048; 660), but 43.2 / 39.2 (153, 1136; 828).  Not listed columns, whose loads cost the
     // split tiles most, instead of 64-wide ones: T = 468, d = 220, p = 1536 35.6 / 43.9, T = 502, d = 235, p = 1441 51.4 / 57.8; with 32-wide ones
-    // T = 558, d = 388, p = 737 43.6 / 35.0.
+    // T = 558, d = 388, p = 737 43.6 / 35.0.  Nor, with 16-byte loads of the rest, beside more than 400 16-wide tiles of dX (T = 504,
+    // d = 216, p = 776 24.7 / 32.0, T = 461, d = 232, p = 796 30.7 / 35.1; with 273, T = 609, d = 112, p = 2249, 46.2 / 36.7) and not heads (512
+    // tokens, 3 of 4 of 128 29.6 / 31.0).
     const bool fits = vx && wa && wb && all <= 800;
-    const bool split = t64 >= 150 && a.w0.K >= 448 && a.w0.M >= 64 && a.w0.N >= 64 && !fits && !(a.w0.ag && wide);
+    const bool listed = a.w0.ag && (wide || (vx && wb && (a.w0.runs || (BX == 16 && count_tiles(a.x, 16) > 400))));
+    const bool split = t64 >= 150 && a.w0.K >= 448 && a.w0.M >= 64 && a.w0.N >= 64 && !fits && !listed;
     auto go = [&](auto bw) {
         constexpr int BW = decltype(bw)::value;
         if (vx && wa && wb) return launch_group<BX, EPIX, BW, true, true, true>(a);
