@@ -395,7 +395,8 @@ struct SplitTile {
         if (ADM && m < m_lo) return;
 #pragma unroll
         for (int q = 0; q < (kTwoB ? 2 : 4); ++q)
-            if (mine(q)) emit<EPI, BDM>(g, gC, m, n0 + pn + 8 * q + 4 * lhi, part(q), part(kTwoB ? q + 2 : q), n_lo, EPI == EPI_SWIGLU_BWD ? gu[q] : nullptr);
+            if (mine(q))
+                emit<EPI, BDM>(g, gC, m, n0 + pn + 8 * q + 4 * lhi, part(q), part(kTwoB ? q + 2 : q), n_lo, EPI == EPI_SWIGLU_BWD ? gu[q] : nullptr);
     }
 };
 

@@ -9,8 +9,8 @@
 // What bounds it: the matrix cores give 157 TFLOP/s (a plain fp32 FMA half of that), i.e. 32 cycles per 16x16x4 tile, so
 // operand traffic is cheap here (a wave reads 4 KB of LDS per 512 matrix cycles) and the shapes that use fp32 are small:
 // latency, launches and idle CUs decide.  Hence four loops:
-//   64 x 64 outputs a workgroup whose operands are split into three bf16 terms (gemm_f32_split_kernel, sdp_f32_split.h): where depth and
-//   tiles are many (split_pays);
+//   64 x 64 outputs a workgroup whose operands are split into three bf16 terms (gemm_f32_split_kernel, sdp_f32_split.h): where it is the
+//   faster one (split_pays), which takes depth and tiles;
 //   64 x 64 outputs a workgroup, pipelined (gemm_f32_pipe_kernel): where these fill the CUs;
 //   16 x 16 and 32 x 32 outputs a workgroup, whose four waves split the depth (gemm_f32_wave_kernel): launches of few tiles;
 //   32 x 32 with the depth split inside each step of 64 (gemm_f32_kernel): between these; and 64 and 128 wide, the largest launches
@@ -24,9 +24,10 @@
 //
 // Measured: four workers' steps at T = 256, d = 256, F = 1024, p = 512 (twelve launches a worker with a plain FMA kernel
 // and transposed copies before, five with this loop): 2079 -> 165 us, and 139 with the 16 x 16 tiles and dX and the weight
-// gradients as one launch (four a worker; 101 us since the host calls are compiled, 99 with gradients in one LDS stage and the index without a chain); per launch 5 - 10 us, of which about 4 us
-// is what an empty kernel takes.  (206 us while every step waited for the newest list entry, computed clamped 64-bit addresses per load
-// and branched around its loads, so that the loads in flight could not be counted.)
+// gradients as one launch (four a worker; 101 us since the host calls are compiled, 99 with gradients in one LDS stage and the index
+// without a chain); per launch 5 - 10 us, of which about 4 us is what an empty kernel takes.
+// (206 us while every step waited for the newest list entry, computed clamped 64-bit addresses per load and branched around its
+// loads, so that the loads in flight could not be counted.)
 #include "sdp_internal.h"
 #include "sdp_swiglu.h"
 
@@ -898,12 +899,13 @@ bool few_tiles(const Dev& g) {
 // 256 CUs and its steps of 32 depths.  The figures are kernel times in us, with about 5 of event overhead, of 850 launches of MLP and
 // attention passes (T = 64 .. 2400, widths 160 .. 3000, every alignment, listed columns), fitted within 3 to 8 % (rms).
 // A round of split tiles takes what two and a half rounds of 32-wide ones do with 16-byte loads, so one loses to two of those and two
-// lose to four, but win against three and five: fp32 / split (rounds), down T = 416, d = 1176, p = 1824 30.1 / 35.7 (2 / 1), T = 512, d = 1100,
-// p = 1376 35.5 / 30.4 (3 / 1), T = 1518, d = 668, p = 1444 42.3 / 48.1 (4 / 2), T = 1300, d = 800, p = 816 39.5 / 31.1 (6 / 2).  Single floats cost the
-// fp32 loops a quarter to all of a step again and the split ones nothing: weight gradients of 699 x 623, 813 deep 100.7 / 48.1.  Rows that end off
-// a multiple of four floats cost the split epilogues more, since a lane has single columns of 32 rows; the activation gradient's
-// then takes 12 us a round: n = 1407, d = 576, T = 900 27.4 / 39.4, and with single-float loads T = 599, d = 367, n = 799 15.4 / 21.9.  Listed columns of
-// the left operand cost them a third of a step: T = 408, d = 676, p = 372 17.2 / 21.6, but T = 2160, d = 460, p = 948 138 / 111.
+// lose to four, but win against three and five: fp32 / split (rounds), down T = 416, d = 1176, p = 1824 30.1 / 35.7 (2 / 1), T = 512,
+// d = 1100, p = 1376 35.5 / 30.4 (3 / 1), T = 1518, d = 668, p = 1444 42.3 / 48.1 (4 / 2), T = 1300, d = 800, p = 816 39.5 / 31.1 (6 / 2).  Single
+// floats cost the fp32 loops a quarter to all of a step again and the split ones nothing: weight gradients of 699 x 623, 813 deep
+// 100.7 / 48.1.  Rows that end off a multiple of four floats cost the split epilogues more, since a lane has single columns of 32 rows; the
+// activation gradient's then takes 12 us a round: n = 1407, d = 576, T = 900 27.4 / 39.4, and with single-float loads T = 599, d = 367, n = 799
+// 15.4 / 21.9.  Listed columns of the left operand cost them a third of a step: T = 408, d = 676, p = 372 17.2 / 21.6, but T = 2160, d = 460,
+// p = 948 138 / 111.
 struct LaunchKind {
     int kind; // 0 gate_up, 1 activation gradient, 2 both operands by rows, 3 right one depth-major, 4 both depth-major
     int load; // 16-byte loads: 0 of both operands, 1 of the right one, 2 of neither
@@ -1138,8 +1140,8 @@ int launch_group(const Group& a, bool vx, bool wa, bool wb) {
     // 32-wide ones with one LDS stage where the launch then fits the chip at once, three workgroups a CU instead of two, unless dX's depth is
     // so long beside the gradients' that the launch ends with it, slowed down by a third workgroup.  42 shapes of 513 to 768 tiles, forward and
     // backward masking, two stages / one: T = 256, d = 256, p = 512 10.2 / 9.8 us, T = 200, d = 452, p = 140 10.6 / 8.9 and 12.0 / 9.9, T = 592,
-    // d = 133, p = 705 31.5 / 26.8 and 33.9 / 26.3 (median 14 % less), but T = 424, d = 121, p = 849 24.5 / 25.2, T = 256, d = 153, p = 861 22.3 / 23.3 and
-    // 19.4 / 20.9.  Listed columns (backward masking) load longer: T = 288, d = 217, p = 677 22.1 / 21.9 and 21.6 / 19.8.
+    // d = 133, p = 705 31.5 / 26.8 and 33.9 / 26.3 (median 14 % less), but T = 424, d = 121, p = 849 24.5 / 25.2, T = 256, d = 153, p = 861
+    // 22.3 / 23.3 and 19.4 / 20.9.  Listed columns (backward masking) load longer: T = 288, d = 217, p = 677 22.1 / 21.9 and 21.6 / 19.8.
     if constexpr (BX == 16) {
         const int64_t depth = (int64_t)a.x.K * (EPIX == EPI_DUAL_ACC ? 2 : 1);
         if (all > 512 && all <= 768 && depth <= (a.w0.ag ? 6 : 4) * (int64_t)a.w0.K) return go(std::integral_constant<int, kOneStage>{});

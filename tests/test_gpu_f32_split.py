@@ -1,6 +1,7 @@
 """GPU: the fp32 contraction's tiles of split products (three bf16 terms an operand): one and two teams of waves, every operand
 layout, partial last steps and tiles, listed rows, depths and columns, dX and the weight gradients together and apart: 1e-5 against the
-fp64 oracle; each test sees to it that these tiles ran.  Which sizes take them.  Operands that are not finite, or that no bf16 holds, give what fp32 products give."""
+fp64 oracle; each test sees to it that these tiles ran.  Which sizes take them.  Operands that are not finite, or that no bf16 holds, give
+what fp32 products give."""
 import pytest
 import torch
 
