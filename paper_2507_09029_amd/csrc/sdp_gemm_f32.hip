@@ -940,7 +940,6 @@ bool split_pays(const Dev& g, int width, int64_t tiles32, int64_t tiles64) {
     if (two && tiles64 <= 256 && g.K < 320 && (VEC || !k.rows)) return false; // T = 528, d = 280, n = 536 11.9 / 12.6
     // less than a round: where it was measured to pay
     if (tiles64 < 256 && !(two && tiles64 >= 150) && !(tiles64 > 128 && g.K >= 1024) && !(tiles64 >= 128 && !VEC)) return false;
-    if (width == 16) return false; // the chip holds the launch at once
     if (k.kind == 1 && VEC && !k.rows) return false; // 26 launches: 24 slower, by 5 to 44 %
     // 48 launches of listed columns 0.93 to 1.27 of the 64-wide tiles' time.  Runs of columns, heads, are what the fp32 loops read well:
     // T = 1248, d = 704, 9 of 11 heads of 64 88.7 / 111.0, T = 688, d = 960, 9 of 12 of 80 88.7 / 102.1; heads of 50 90.4 / 81.4
@@ -974,14 +973,14 @@ int choose(const Dev& g, const char* name, hipStream_t s) {
         if (t * 256 > UINT32_MAX) return HUGE_VAL; // threads of one launch
         return (double)((t + 255) / 256) * b * bn * weight;
     };
-    // the fp32 tile first: 16, 32, 64 or 128 wide
+    if (direct && few_tiles(g)) return launch_wave<16, 2, EPI, ADM, BDM, VA, VB>(g, name, s); // never split
+    // the fp32 tile otherwise: 32, 64 or 128 wide
     const double c128 = cost(128, 128, 1.0), c32 = cost(32, 32, 1.3);
     // single floats: the tiles that direct loads fill, of 64 and 32
     const double c64 = direct ? cost(64, 64 / NB, 1.1) : HUGE_VAL, staged128 = VEC || !direct ? c128 : HUGE_VAL;
     const double staged64 = (VEC && NB == 2) || !direct ? cost(64, 64, 1.1) : HUGE_VAL;
     int width = 64;
-    if (direct && few_tiles(g)) width = 16;
-    else if (c32 < c64 && c32 < staged64 && c32 < staged128) width = 32;
+    if (c32 < c64 && c32 < staged64 && c32 < staged128) width = 32;
     else if (staged128 <= c64 && staged128 <= staged64) width = 128;
     if (split_pays<EPI, ADM, BDM, VA, VB>(g, width, tiles(32, 32), tiles(64, 64 / NB))) {
         auto go = [&](auto listed) { // listed columns of the left operand
@@ -996,7 +995,6 @@ int choose(const Dev& g, const char* name, hipStream_t s) {
         return go(std::false_type{});
     }
     if (direct) {
-        if (width == 16) return launch_wave<16, 2, EPI, ADM, BDM, VA, VB>(g, name, s);
         if (width == 32) {
             if (!VEC || (!ADM && NB == 1 && EPI != EPI_SWIGLU_BWD && tiles(32, 32) <= 256)) return launch_wave<32, 2, EPI, ADM, BDM, VA, VB>(g, name, s);
             return launch<Cfg<32, 32, 4>, EPI, ADM, BDM, true>(g, name, s);
